@@ -45,6 +45,12 @@ struct StepParams {
   int32_t pad;
 };
 
+// Element (row, k) of the activations of a product over many rows, which lie in MFMA fragment order
+// [row / 16][K / 32][64 lanes][8]; KS = K / 32.
+__device__ __forceinline__ size_t rows_frag_index(int row, int k, int KS) {
+  return (((size_t)(row >> 4) * KS + (k >> 5)) * 64 + (row & 15) + 16 * ((k & 31) >> 3)) * 8 + (k & 7);
+}
+
 template <typename T> struct Store;
 template <> struct Store<float> {
   static __device__ __forceinline__ float ld(const float* p) { return *p; }
@@ -71,6 +77,19 @@ template <> __device__ __forceinline__ void load8<bf16>(const bf16* p, float (&o
   const bf16x8 v = *reinterpret_cast<const bf16x8*>(p);
 #pragma unroll
   for (int e = 0; e < 8; ++e) o[e] = (float)v[e];
+}
+
+// Store 8 consecutive elements of T (aligned as for load8), rounded to T.
+template <typename T> __device__ __forceinline__ void store8(T* p, const float (&v)[8]);
+template <> __device__ __forceinline__ void store8<float>(float* p, const float (&v)[8]) {
+  *reinterpret_cast<float4*>(p) = make_float4(v[0], v[1], v[2], v[3]);
+  *reinterpret_cast<float4*>(p + 4) = make_float4(v[4], v[5], v[6], v[7]);
+}
+template <> __device__ __forceinline__ void store8<bf16>(bf16* p, const float (&v)[8]) {
+  bf16x8 o;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) o[e] = (bf16)v[e];
+  *reinterpret_cast<bf16x8*>(p) = o;
 }
 
 // ---------------------------------------------------------------------------

@@ -55,20 +55,23 @@ struct AttnArgs {
   const int* row_pos;       // [R]; self: causal limit of each row, < 0 = padding row
   int R, H, Hkv;
   int G, g_mul;             // query heads per kv head; 65536 / G + 1: x / G == (x * g_mul) >> 16 for x < 1024
-  int rows_per_wg;          // grid.y = ceil(R / rows_per_wg): rows are independent, no merge needed
+  int rows_per_wg;          // row groups = ceil(R / rows_per_wg): rows are independent, no merge needed
+  int groups;               // attn_mma_kernel: their number (grid.z = key ranges x row groups)
   // several sequences in one launch: grid.z = sequences, R rows each, one after the other
   // (sequence z: rows z * R ..); sequence z uses the page table at page_table + (seq0 + z) * pt_stride
   int seq0, pt_stride;
   // long contexts: the keys of a (sequence, kv head) are cut into nsplit ranges of split_keys keys
   // (a multiple of the key block) that different workgroups take (grid.y = row groups x nsplit);
   // each leaves its running maximum, denominator and unnormalised output in `partial`
-  // ([sequence][kv head][split][ATTN_MAX_RG][d_head + 2] floats) and attn_merge_kernel combines
+  // ([sequence][row group][kv head][split][ATTN_MAX_RG][d_head + 2] floats) and attn_merge_kernel combines
   // them.  nsplit is fixed per model (from max_len), so the split never depends on the other rows.
   int nsplit, split_keys;
   float* partial;
-  // attn_merge_kernel: when set, the merged output goes here in the batched GEMMs' fragment order
-  // ([H * d_head / 32][GEMM_WIDE_RT][64 lanes][8]: element (row, n) at k-step n / 32, slab row / 16,
-  // lane (row % 16) + 16 ((n % 32) / 8), element n % 8) instead of row-major into `out`
+  // when set, the output (attn_merge_kernel's with key ranges, else attn_mma_kernel's) goes here in
+  // fragment order instead of row-major into `out`: element (row, n) at fragment
+  // (n / 32) * frag_ks + (row / 16) * frag_slab, lane (row % 16) + 16 ((n % 32) / 8), element n % 8
+  // (batched GEMMs: [H * d_head / 32][GEMM_WIDE_RT][64][8]; products over many rows: [slab][H * d_head / 32][64][8])
+  int frag_ks, frag_slab;
   void* out_frag;
   int cross;                // 1: cross-attention over kv_len keys, no mask, no bias
   int kv_len;
@@ -89,6 +92,10 @@ struct AttnArgs {
   int pj_K, pj_npart, pj_q_off;
   float pj_eps;
 };
+
+__device__ __forceinline__ size_t attn_frag_index(const AttnArgs& a, int row, int n) {
+  return (((size_t)(n >> 5) * a.frag_ks + (size_t)(row >> 4) * a.frag_slab) * 64 + (row & 15) + 16 * ((n & 31) >> 3)) * 8 + (n & 7);
+}
 
 // THREADS (256, 512 or 1024) sets the key block: THREADS / LPK keys per pass, so a launch takes the
 // smallest workgroup whose block covers the contexts it expects; CROSS compiles the cross-attention
@@ -409,9 +416,9 @@ static __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_mma_kern
   const int j = lane & 15, kq = lane >> 4;
   const int hkv = blockIdx.x;
   const int seq = blockIdx.y;
-  // z: the key ranges of a launch that has them (it has one row group), else the row groups
-  const int split = (a.nsplit > 1) ? (int)blockIdx.z : 0;
-  const int rs = (a.nsplit > 1) ? 0 : (int)blockIdx.z * a.rows_per_wg;
+  // z: key ranges x row groups, the last rows (which see the most keys) first
+  const int split = (int)blockIdx.z / a.groups, grp = a.groups - 1 - (int)blockIdx.z % a.groups;
+  const int rs = grp * a.rows_per_wg;
   const int R = min(a.rows_per_wg, a.R - rs);
   const int r0 = seq * a.R + rs;
   const int G = a.G, RG = R * G;
@@ -531,7 +538,7 @@ static __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_mma_kern
     kv_len = wave_max(my_pos) + 1;
     pos_min = wave_min(lane < R ? my_pos : 0x7fffffff);
   }
-  float* pp = a.partial + ((((size_t)seq * a.Hkv + hkv) * a.nsplit + split) * ATTN_MAX_RG + (size_t)rs * G) * (DH + 2);
+  float* pp = a.partial + (((((size_t)seq * a.groups + grp) * a.Hkv + hkv) * a.nsplit + split) * ATTN_MAX_RG) * (DH + 2);
   if (a.nsplit > 1) {
     if (k_begin >= kv_len) {                        // nothing in this key range yet: an empty partial
       if (tid < RG) { pp[(size_t)tid * (DH + 2) + DH] = -INFINITY; pp[(size_t)tid * (DH + 2) + DH + 1] = 0.0f; }
@@ -791,7 +798,9 @@ static __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_mma_kern
       }
     }
     const int rr = (rg * a.g_mul) >> 16, gg = rg - rr * G;
-    og[(size_t)(r0 + rr) * a.H * DH + (size_t)(hkv * G + gg) * DH + d] = (bf16)((L > 0.0f) ? acc / L : 0.0f);
+    const bf16 res = (bf16)((L > 0.0f) ? acc / L : 0.0f);
+    if (a.out_frag != nullptr) static_cast<bf16*>(a.out_frag)[attn_frag_index(a, r0 + rr, (hkv * G + gg) * DH + d)] = res;
+    else og[(size_t)(r0 + rr) * a.H * DH + (size_t)(hkv * G + gg) * DH + d] = res;
   }
 }
 
@@ -802,7 +811,8 @@ template <typename T, int DH>
 static __global__ __launch_bounds__(DH) void attn_merge_kernel(const AttnArgs a) {
   const int hkv = blockIdx.x, G = a.H / a.Hkv, rg = blockIdx.y, d = threadIdx.x;
   const int r_base = (int)blockIdx.z * a.R;
-  const float* pp = a.partial + ((((size_t)blockIdx.z * a.Hkv + hkv) * a.nsplit) * ATTN_MAX_RG + rg) * (DH + 2);
+  const int grp = rg / (a.rows_per_wg * G), rgl = rg - grp * a.rows_per_wg * G;
+  const float* pp = a.partial + (((((size_t)blockIdx.z * a.groups + grp) * a.Hkv + hkv) * a.nsplit) * ATTN_MAX_RG + rgl) * (DH + 2);
   const size_t stride = (size_t)ATTN_MAX_RG * (DH + 2);
   float m = -INFINITY;
   for (int sp = 0; sp < a.nsplit; ++sp) m = fmaxf(m, pp[sp * stride + DH]);
@@ -819,8 +829,7 @@ static __global__ __launch_bounds__(DH) void attn_merge_kernel(const AttnArgs a)
   const int r = rg / G, h = hkv * G + rg % G;
   const float res = (L > 0.0f) ? o / L : 0.0f;
   if (a.out_frag != nullptr) {
-    const int row = r_base + r, n = h * DH + d;
-    Store<T>::st(static_cast<T*>(a.out_frag) + ((((size_t)(n >> 5) * GEMM_WIDE_RT + (row >> 4)) * 64 + (row & 15) + 16 * ((n & 31) >> 3)) * 8 + (n & 7)), res);
+    Store<T>::st(static_cast<T*>(a.out_frag) + attn_frag_index(a, r_base + r, h * DH + d), res);
   } else {
     Store<T>::st(static_cast<T*>(a.out) + (size_t)(r_base + r) * a.H * DH + h * DH + d, res);
   }

@@ -26,6 +26,7 @@ enum {
 // of sequence states.  row_seq[r] (when given) receives the row's sequence, logit_row[r] the
 // row of the logits buffer its LM-head output belongs in (< 0: not needed):
 // p rows [seq][gamma+1], q rows [seq][gamma], one row per sequence for plain decoding.
+// xg_frag: xg in the fragment order of the products over many rows instead of row-major.
 template <typename T>
 static __global__ __launch_bounds__(256) void embed_kernel(
     int mode, int step, const SeqState* __restrict__ st, const int* __restrict__ prompt, int start,
@@ -33,7 +34,7 @@ static __global__ __launch_bounds__(256) void embed_kernel(
     float* __restrict__ x, int* __restrict__ row_pos, const T* __restrict__ gain_next,
     T* __restrict__ xg, float* __restrict__ ss,
     int rps, int seq0, int gamma, int* __restrict__ row_seq, int* __restrict__ logit_row,
-    int ss_stride) {
+    int ss_stride, int xg_frag) {
   __shared__ float red[16];
   const int j = (int)blockIdx.x % rps, sl = (int)blockIdx.x / rps, seq = seq0 + sl;
   const int r = blockIdx.x, slab = r / MAX_ROWS, r16 = r % MAX_ROWS;     // row, its slab, row within the slab
@@ -71,14 +72,17 @@ static __global__ __launch_bounds__(256) void embed_kernel(
     for (int u = 0; u < 4; ++u) {
       const int g = g0 + u * blockDim.x;
       if (g < ngroups) {
+        float xv[8], xgv[8];
 #pragma unroll
         for (int k = 0; k < 8; ++k) {
           float val = v[u][k];
           if (p) val += w[u][k];
-          x[(size_t)r * d + g * 8 + k] = val;
-          if (xg) Store<T>::st(xg + (size_t)r * d + g * 8 + k, val * gn[u][k]);
+          xv[k] = val;
+          if (xg) xgv[k] = val * gn[u][k];
           q += val * val;
         }
+        store8<float>(x + (size_t)r * d + g * 8, xv);
+        if (xg) store8<T>(xg + (xg_frag ? rows_frag_index(r, g * 8, d >> 5) : (size_t)r * d + g * 8), xgv);
       }
     }
   }

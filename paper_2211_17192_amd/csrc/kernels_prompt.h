@@ -1,0 +1,492 @@
+// Products over many rows: the prompt of a new sequence and the encoder's positions.
+// With a few dozen rows or fewer the weights' way out of memory bounds a product (kernels_gemm.h);
+// with hundreds of rows the matrix cores do, and a pass over 16 rows at a time reads the weights
+// rows / 16 times.  Here one launch takes all rows of a pass.
+//
+// Both operands are in MFMA fragment order: the weights as they were re-tiled at load,
+// Wt[N/16][K/32][64 lanes][8], and the activations alike, Xf[rows/16][K/32][64 lanes][8], which the
+// producing kernels write directly (rows_frag_index).  Every fragment is one contiguous KB: 16-byte
+// loads, no swizzle, no LDS bank conflicts.
+#pragma once
+#include "kernels_gemm.h"
+
+namespace sd {
+
+// Row-major bf16 rows [rows][K] -> fragment order; rows beyond the last repeat it (their results are
+// never stored).  grid * 256 threads >= slabs * K/32 * 64.
+static __global__ __launch_bounds__(256) void rows_to_slabs_kernel(const bf16* __restrict__ X, bf16* __restrict__ Xf, int rows, int K) {
+  const int KS = K >> 5, slabs = (rows + 15) >> 4;
+  const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
+  if (idx >= (size_t)slabs * KS * 64) return;
+  const int lane = (int)(idx & 63);
+  const size_t f = idx >> 6;
+  const int slab = (int)(f / KS), ks = (int)(f % KS);
+  const int row = min(slab * 16 + (lane & 15), rows - 1);
+  *reinterpret_cast<bf16x8*>(Xf + idx * 8) = *reinterpret_cast<const bf16x8*>(X + (size_t)row * K + ks * 32 + (lane >> 4) * 8);
+}
+
+// 1 / rms of every row from the partial sums of squares ss [slab][n_part][16], added in gemm_kernel's
+// order.  grid = slabs.
+static __global__ __launch_bounds__(256) void rows_rs_kernel(const float* __restrict__ ss, int n_part, int ss_stride, int K, float eps,
+                                                             float* __restrict__ rs) {
+  const int row = threadIdx.x >> 4, f = threadIdx.x & 15;
+  const float* s = ss + (size_t)blockIdx.x * ss_stride;
+  float q = 0.0f;
+#pragma unroll 16
+  for (int p = f; p < n_part; p += 16) q += s[p * 16 + row];
+  q = lane_combine<1>(q, OpSumF()); q = lane_combine<2>(q, OpSumF());
+  q = lane_combine<4>(q, OpSumF()); q = lane_combine<8>(q, OpSumF());
+  if (f == 0) rs[blockIdx.x * 16 + row] = 1.0f / sqrtf(q / (float)K + eps);
+}
+
+// LayerNorm of fp32 rows into fragment order: gemm_kernel's statistics (the K-slices of its S
+// wavefronts, added in wavefront order) and its normalisation, once per row instead of in every
+// workgroup of the product.  grid = slabs, 64 S threads, S = the wavefronts of gemm_kernel.
+static __global__ __launch_bounds__(512) void rows_layernorm_kernel(const float* __restrict__ X, const bf16* __restrict__ gain,
+                                                                    const bf16* __restrict__ beta, bf16* __restrict__ Xf, int rows, int K,
+                                                                    int ksteps_per_wave, float eps) {
+  __shared__ float stat[2][8 * 16];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, S = blockDim.x >> 6;
+  const int j = lane & 15, kq = lane >> 4, KS = K >> 5;
+  const int ks0 = min(KS, wave * ksteps_per_wave), ks1 = min(KS, ks0 + ksteps_per_wave);
+  const float* x = X + (size_t)min((int)blockIdx.x * 16 + j, rows - 1) * K + kq * 8;
+  bf16x8* out = reinterpret_cast<bf16x8*>(Xf) + (size_t)blockIdx.x * KS * 64 + lane;
+  // up to HELD k-steps a wavefront (K 1024 with four of them, 2048 with eight) stay in registers over all
+  // three passes: one trip to memory instead of three
+  constexpr int HELD = 8;
+  auto slice_sums = [&](auto&& add) {
+    float s = add();
+    s = lane_combine<16>(s, OpSumF()); return lane_combine<32>(s, OpSumF());
+  };
+  auto total = [&](float s, int which) {
+    if (kq == 0) stat[which][wave * 16 + j] = s;
+    __syncthreads();
+    float t = 0.0f;
+    for (int w = 0; w < S; ++w) t += stat[which][w * 16 + j];
+    return t;
+  };
+  auto normalise = [&](const float (&xv)[8], int ks, float mu, float rstd) {
+    float v[8], g[8], b[8];
+    load8<bf16>(gain + ks * 32 + kq * 8, g);
+    load8<bf16>(beta + ks * 32 + kq * 8, b);
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = ln_apply(xv[e], mu, rstd, g[e], b[e]);
+    out[ks * 64] = Mma<bf16>::from_floats(v);
+  };
+  if (ksteps_per_wave <= HELD) {
+    float xv[HELD][8];
+#pragma unroll
+    for (int u = 0; u < HELD; ++u) load8<float>(x + min(ks0 + u, KS - 1) * 32, xv[u]);
+    const float mu = total(slice_sums([&] {
+      float s = 0.0f;
+#pragma unroll
+      for (int u = 0; u < HELD; ++u)
+        if (ks0 + u < ks1) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) s += xv[u][e];
+        }
+      return s;
+    }), 0) / (float)K;
+    const float var = total(slice_sums([&] {
+      float s = 0.0f;
+#pragma unroll
+      for (int u = 0; u < HELD; ++u)
+        if (ks0 + u < ks1) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) s = add_square(s, xv[u][e] - mu);
+        }
+      return s;
+    }), 1) / (float)K;
+    const float rstd = 1.0f / sqrtf(var + eps);
+#pragma unroll
+    for (int u = 0; u < HELD; ++u)
+      if (ks0 + u < ks1) normalise(xv[u], ks0 + u, mu, rstd);
+    return;
+  }
+  const float mu = total(slice_sums([&] {
+    float s = 0.0f;
+#pragma unroll 4
+    for (int ks = ks0; ks < ks1; ++ks) {
+      float v[8]; load8<float>(x + ks * 32, v);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) s += v[e];
+    }
+    return s;
+  }), 0) / (float)K;
+  const float var = total(slice_sums([&] {
+    float s = 0.0f;
+#pragma unroll 4
+    for (int ks = ks0; ks < ks1; ++ks) {
+      float v[8]; load8<float>(x + ks * 32, v);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) s = add_square(s, v[e] - mu);
+    }
+    return s;
+  }), 1) / (float)K;
+  const float rstd = 1.0f / sqrtf(var + eps);
+#pragma unroll 4
+  for (int ks = ks0; ks < ks1; ++ks) {
+    float v[8]; load8<float>(x + ks * 32, v);
+    normalise(v, ks, mu, rstd);
+  }
+}
+
+struct RowsGemmArgs {
+  const bf16* W;          // tiled weights; batch z starts z * w_stride elements further
+  const bf16* W2;         // EPI_GATED: the "up" weights
+  const bf16* X;          // fragment order
+  const bf16* zeros;      // 1 KB of zeros
+  const float* rs;        // 1 / rms of every row, or nullptr (no norm, or LayerNorm applied by the producer)
+  const bf16* bias;       // [N] or nullptr
+  int rows, K, N, kpw, nchunk;   // kpw, nchunk: gemm_kernel's k-steps per wavefront and wavefronts
+  int mtiles, ntiles_wg;  // workgroup tiles in either direction
+  // EPI_STORE: a batch of products over the same rows, two to a layer: product z takes the weights at
+  // W + (z / 2) w_layer + (z % 2) w_which and the output at out + (z / 2) out_layer + (z % 2) out_which
+  int batch;
+  size_t w_layer, w_which, out_layer, out_which;
+  bf16* out;              // EPI_ACT, EPI_GATED: fragment order [rows][N]; EPI_STORE: row-major [rows][N] or
+                          // head-major [N / d_head][rows][d_head] (hm != 0)
+  int hm, d_head, act;
+  // EPI_RESID: x += y; xg = x * gain_next in fragment order and the partial sums of x^2 (both optional)
+  float* x;
+  bf16* xg;
+  const bf16* gain_next;
+  float* ss;
+  int ss_stride;
+  // EPI_QKV
+  bf16* q;
+  int nq, nkv;
+  bf16* kv_pool;
+  const int* page_table;
+  const int* row_pos;
+  int page_size, n_kv_heads;
+  const float* rope;
+};
+
+// What a lane needs of row `row` (slab, j = row % 16) before it writes its features.
+template <int EPI>
+struct RowsEpilogue {
+  int slab, row, j, kq;
+  bool ok;
+  float r1;
+  int pos;
+  size_t kvbase;
+  __device__ __forceinline__ void row_inputs(const RowsGemmArgs& a, int slab_, int lane) {
+    slab = slab_; j = lane & 15; kq = lane >> 4; row = slab * 16 + j;
+    ok = row < a.rows;
+    const int rowc = min(row, a.rows - 1);
+    r1 = (a.rs != nullptr) ? a.rs[rowc] : 1.0f;
+    pos = 0; kvbase = 0;
+    if (EPI == EPI_QKV) {
+      pos = max(a.row_pos[rowc], 0);
+      const int page = a.page_table[pos / a.page_size], slot = pos % a.page_size;
+      kvbase = (size_t)page * 2 * a.n_kv_heads * a.page_size * a.d_head + (size_t)slot * a.d_head;
+    }
+  }
+  // The finished sums of one 16-feature tile (EPI_GATED: of its gate and up streams): this lane's are the
+  // features 16 tile + 4 kq + 0..3.  gemm_kernel's arithmetic.
+  __device__ __forceinline__ void tile_out(const RowsGemmArgs& a, int tile, int bz, const f32x4& s0, const f32x4& s1) const {
+    typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+    const int n0 = tile * 16 + kq * 4;
+    float y[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      y[r] = (a.rs != nullptr) ? s0[r] * r1 : s0[r];
+      y[r] += (a.bias != nullptr) ? (float)a.bias[n0 + r] : 0.0f;
+    }
+    if (EPI == EPI_RESID) {
+      float xn[4] = {0.f, 0.f, 0.f, 0.f};
+      if (ok) {
+        float4* xp = reinterpret_cast<float4*>(a.x + (size_t)row * a.N + n0);
+        const float4 o = *xp;
+        xn[0] = o.x + y[0]; xn[1] = o.y + y[1]; xn[2] = o.z + y[2]; xn[3] = o.w + y[3];
+        *xp = make_float4(xn[0], xn[1], xn[2], xn[3]);
+      }
+      if (a.xg != nullptr) {
+        bf16x4 g;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) g[r] = (bf16)(xn[r] * (float)a.gain_next[n0 + r]);
+        *reinterpret_cast<bf16x4*>(a.xg + rows_frag_index(row, n0, a.N >> 5)) = g;
+      }
+      if (a.ss != nullptr) {
+        // the order of gemm_kernel's 16-lane sum as its first lane sees it: quads 0 + 3, quads 1 + 2
+        float q = (square(xn[0]) + square(xn[1])) + (square(xn[2]) + square(xn[3]));
+        q += __shfl_xor(q, 48, 64);
+        q += __shfl_xor(q, 16, 64);
+        if (kq == 0) a.ss[(size_t)slab * a.ss_stride + tile * 16 + j] = q;
+      }
+    } else if (EPI == EPI_QKV) {
+      const bool is_q = n0 < a.nq, is_k = !is_q && n0 < a.nq + a.nkv;          // uniform over the tile
+      const int nn = is_q ? n0 : (is_k ? n0 - a.nq : n0 - a.nq - a.nkv);
+      const int head = nn / a.d_head, d = nn % a.d_head;
+      bf16x4 o;
+      if (a.rope != nullptr && (is_q || is_k)) {
+        const float4 cs = *reinterpret_cast<const float4*>(a.rope + ((size_t)pos * (a.d_head >> 1) + (d >> 1)) * 2);
+        o[0] = (bf16)rope_rotate(y[0], y[1], cs.x, cs.y, false); o[1] = (bf16)rope_rotate(y[1], y[0], cs.x, cs.y, true);
+        o[2] = (bf16)rope_rotate(y[2], y[3], cs.z, cs.w, false); o[3] = (bf16)rope_rotate(y[3], y[2], cs.z, cs.w, true);
+      } else {
+#pragma unroll
+        for (int r = 0; r < 4; ++r) o[r] = (bf16)y[r];
+      }
+      if (ok) {
+        if (is_q) *reinterpret_cast<bf16x4*>(a.q + (size_t)row * a.nq + n0) = o;
+        else *reinterpret_cast<bf16x4*>(a.kv_pool + kvbase + ((size_t)(is_k ? 0 : 1) * a.n_kv_heads + head) * a.page_size * a.d_head + d) = o;
+      }
+    } else {
+      bf16x4 o;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        float v = y[r];
+        if (EPI == EPI_ACT) v = gelu_tanh(v);
+        if (EPI == EPI_GATED) v = ((a.act == ACT_GELU) ? gelu_tanh(v) : silu(v)) * (s1[r] * r1);
+        o[r] = (bf16)v;
+      }
+      if (EPI == EPI_STORE) {
+        bf16* out = a.out + (size_t)(bz >> 1) * a.out_layer + (size_t)(bz & 1) * a.out_which;
+        if (ok) {
+          if (a.hm) *reinterpret_cast<bf16x4*>(out + ((size_t)(n0 / a.d_head) * a.rows + row) * a.d_head + n0 % a.d_head) = o;
+          else *reinterpret_cast<bf16x4*>(out + (size_t)row * a.N + n0) = o;
+        }
+      } else {
+        *reinterpret_cast<bf16x4*>(a.out + rows_frag_index(row, n0, a.N >> 5)) = o;   // rows past the last: in the padded slab
+      }
+    }
+  }
+};
+
+// Workgroups are dealt to the eight XCDs in turn: each XCD gets a contiguous run of tiles with the row
+// tiles fastest, so its L2 holds few weight tiles at a time and each is read from memory once.
+__device__ __forceinline__ void rows_tile_of_block(const RowsGemmArgs& a, int& bm, int& bn, int& bz) {
+  const int total = (int)gridDim.x, b = blockIdx.x, xcd = b & 7, q = total >> 3, r = total & 7;
+  const int id = xcd * q + min(xcd, r) + (b >> 3), per = a.mtiles * a.ntiles_wg;
+  bz = id / per;
+  bm = (id - bz * per) % a.mtiles; bn = (id - bz * per) / a.mtiles;
+}
+
+// A workgroup of four wavefronts takes NT * 64 features x MT * 16 rows.  A wavefront owns NT weight
+// tiles: their fragments go from memory into its registers and nowhere else, while the MT slabs of
+// activations pass through LDS and serve all four wavefronts.
+// Sums are gemm_kernel's, bit for bit: the k-steps of a K-slice accumulate from zero, the slices are
+// added in order to a running total.  That doubles the accumulators, so NT * MT is 16 at two wavefronts
+// a SIMD (256 registers).  The matrix cores bound it, then what a stall costs: a weight register is
+// reloaded for the next pass of SUB k-steps right after its last multiply, the next pass's activations
+// are in flight (registers) while this pass is multiplied and reach the other LDS buffer at its end,
+// one barrier per pass, and the two workgroups of a CU fill each other's prologue, epilogue and waits.
+// Measured (TFLOP/s; a library product of these sizes reaches 1100 - 1200 on this chip): 2000 rows, K 4096,
+// N 4096 953, N 6144 965, gated 14336 913; K 14336, N 4096 1035.  One wavefront a SIMD with NT 4, MT 8
+// (half the LDS reads per MFMA): 821, 667, 725, 1000: nothing hides its stalls.
+template <int EPI, int NT, int MT>
+static __global__ __launch_bounds__(256, 2) void gemm_rows_kernel(const RowsGemmArgs a) {
+  constexpr int SUB = 4, NT_OUT = (EPI == EPI_GATED) ? NT / 2 : NT;
+  constexpr int NFRAG = SUB * MT * 64, XPT = NFRAG / 256;
+  __shared__ __align__(16) bf16x8 xs[2][NFRAG];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int KS = a.K >> 5, ntiles = a.N >> 4, slabs = (a.rows + 15) >> 4;
+  int bn, bm, bz;
+  rows_tile_of_block(a, bm, bn, bz);
+  const bf16* wbase[NT];
+  int tile0 = (bn * 4 + wave) * NT_OUT;              // first output tile of this wavefront
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    const int ot = (EPI == EPI_GATED) ? (t >> 1) : t;
+    const bf16* w = (EPI == EPI_GATED && (t & 1)) ? a.W2 : a.W + (EPI == EPI_STORE ? (size_t)(bz >> 1) * a.w_layer + (size_t)(bz & 1) * a.w_which : 0);
+    wbase[t] = w + (size_t)min(tile0 + ot, ntiles - 1) * KS * 512;
+  }
+
+  f32x4 acc[NT][MT], tot[NT][MT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int m = 0; m < MT; ++m) { acc[t][m] = f32x4{0.f, 0.f, 0.f, 0.f}; tot[t][m] = f32x4{0.f, 0.f, 0.f, 0.f}; }
+
+  bf16x8 wf[NT][SUB], xr[XPT];
+  static_assert(SUB == 4 && NFRAG == 256 * MT, "wavefront w stages k-step w of every slab");
+  const bf16x8* xsrc[XPT];                           // uniform: slab i of this workgroup
+#pragma unroll
+  for (int i = 0; i < XPT; ++i) xsrc[i] = reinterpret_cast<const bf16x8*>(a.X) + (size_t)min(bm * MT + i, slabs - 1) * KS * 64;
+  // k-steps past a slice's end are multiplied with zeros, as gemm_kernel does: they come from a KB of zeros
+  auto load_x = [&](int ksb, int len) {
+#pragma unroll
+    for (int i = 0; i < XPT; ++i) {
+      const bf16x8* src = (wave < len) ? xsrc[i] + (size_t)(ksb + wave) * 64 : reinterpret_cast<const bf16x8*>(a.zeros);
+      xr[i] = src[(unsigned)lane];
+    }
+  };
+  auto load_w = [&](int u, int ks) {
+    const size_t o = (size_t)min(ks, KS - 1) * 512;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) wf[t][u] = reinterpret_cast<const bf16x8*>(wbase[t] + o)[(unsigned)lane];
+  };
+  auto store_x = [&](int buf) {
+#pragma unroll
+    for (int i = 0; i < XPT; ++i) xs[buf][tid + 256 * i] = xr[i];
+  };
+  // the order of a pass, which the scheduler would otherwise rearrange so that every load sinks to its
+  // end, a few MFMAs ahead of its use: the next k-step's fragments between this one's MFMAs, a
+  // weight register's reload behind its last MFMA
+  auto order_pass = [&] {
+    __builtin_amdgcn_sched_group_barrier(0x100, MT, 0);            // the first k-step's fragments
+#pragma unroll
+    for (int u = 0; u < SUB; ++u) {
+#pragma unroll
+      for (int m = 0; m < MT; ++m) {
+        __builtin_amdgcn_sched_group_barrier(0x008, NT, 0);        // MFMAs of one slab
+        if (u + 1 < SUB) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        if (u == SUB - 1) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
+      }
+      __builtin_amdgcn_sched_group_barrier(0x020, NT, 0);
+    }
+    __builtin_amdgcn_sched_group_barrier(0x020, XPT, 0);
+  };
+
+  // passes of SUB k-steps, never across the end of a K-slice
+  int end = min(KS, a.kpw);                          // of the slice being multiplied
+  load_x(0, end);
+#pragma unroll
+  for (int u = 0; u < SUB; ++u) load_w(u, u);
+  store_x(0);
+  int ksb = 0, next = min(SUB, end);                 // this pass, the next one
+  int end_next = (next < end) ? end : min(KS, end + a.kpw);                  // of the slice `next` lies in
+  load_x(next, end_next - next);
+  __syncthreads();
+  int buf = 0;
+  const int nslices = (KS + a.kpw - 1) / a.kpw;
+#pragma unroll 1
+  for (int c = 0; c < nslices; ++c) {
+#pragma unroll 1
+    do {
+      const bf16x8* xb = &xs[buf][lane];
+      bf16x8 fb[2][MT];
+#pragma unroll
+      for (int m = 0; m < MT; ++m) fb[0][m] = xb[(m * SUB) * 64];
+#pragma unroll
+      for (int u = 0; u < SUB; ++u) {
+#pragma unroll
+        for (int m = 0; m < MT; ++m) {
+#pragma unroll
+          for (int t = 0; t < NT; ++t) acc[t][m] = Mma<bf16>::mma(wf[t][u], fb[u & 1][m], acc[t][m]);
+          if (u + 1 < SUB) fb[(u + 1) & 1][m] = xb[(m * SUB + u + 1) * 64];
+        }
+        load_w(u, next + u);
+      }
+      store_x(buf ^ 1);
+      ksb = next;
+      next = min(next + SUB, end_next);
+      end_next = (next < end_next) ? end_next : min(KS, end_next + a.kpw);
+      load_x(next, end_next - next);
+      order_pass();
+      __syncthreads();
+      buf ^= 1;
+    } while (ksb < end);
+    end = min(KS, end + a.kpw);
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int m = 0; m < MT; ++m) { tot[t][m] += acc[t][m]; acc[t][m] = f32x4{0.f, 0.f, 0.f, 0.f}; }
+  }
+  // slices beyond K are empty in gemm_kernel too: it adds their zeros
+  if (nslices < a.nchunk) {
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int m = 0; m < MT; ++m) tot[t][m] += f32x4{0.f, 0.f, 0.f, 0.f};
+  }
+
+#pragma unroll
+  for (int m = 0; m < MT; ++m) {
+    if (bm * MT + m >= slabs) break;                 // uniform
+    RowsEpilogue<EPI> e;
+    e.row_inputs(a, bm * MT + m, lane);
+#pragma unroll
+    for (int t = 0; t < NT_OUT; ++t)
+      if (tile0 + t < ntiles) {                      // uniform
+        if (EPI == EPI_GATED) e.tile_out(a, tile0 + t, bz, tot[(2 * t) % NT][m], tot[(2 * t + 1) % NT][m]);
+        else e.tile_out(a, tile0 + t, bz, tot[t % NT][m], tot[t % NT][m]);
+      }
+  }
+}
+
+// The same product where that shape would leave most of the chip idle or walk a long K with few
+// wavefronts: a workgroup is gemm_kernel's S wavefronts, each with its K-slice, over NT weight tiles x MT
+// slabs.  Nothing is shared inside the workgroup, so both operands go straight into registers, D
+// k-steps ahead, and there is no barrier before the slices are added through LDS, in order.  Launches of
+// this kind are bound by latency (a few microseconds in all), then by what a CU can pull from L2: NT + MT
+// KB for NT * MT MFMAs.
+// D: kpw is a multiple of it, or the k-steps past a slice's end are multiplied with zeros.
+// dynamic LDS: S * NT * MT KB.
+template <int EPI, int NT, int MT, int D>
+static __global__ __launch_bounds__(512) void gemm_slices_kernel(const RowsGemmArgs a) {
+  extern __shared__ float lds[];
+  f32x4* part = reinterpret_cast<f32x4*>(lds);       // [S][NT][MT][64 lanes]
+  constexpr int NT_OUT = (EPI == EPI_GATED) ? NT / 2 : NT;
+  const int lane = threadIdx.x & 63, S = blockDim.x >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int KS = a.K >> 5, ntiles = a.N >> 4, slabs = (a.rows + 15) >> 4;
+  int bm, bn, bz;
+  rows_tile_of_block(a, bm, bn, bz);
+  const int tile0 = bn * NT_OUT;
+  const int ks0 = min(KS, wave * a.kpw), ks1 = min(KS, ks0 + a.kpw), ks_last = max(ks1 - 1, 0);
+  const bf16x8 *wb[NT], *xb[MT], *zeros = reinterpret_cast<const bf16x8*>(a.zeros);
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    const bf16* w = (EPI == EPI_GATED && (t & 1)) ? a.W2 : a.W + (EPI == EPI_STORE ? (size_t)(bz >> 1) * a.w_layer + (size_t)(bz & 1) * a.w_which : 0);
+    wb[t] = reinterpret_cast<const bf16x8*>(w) + (size_t)min(tile0 + ((EPI == EPI_GATED) ? (t >> 1) : t), ntiles - 1) * KS * 64;
+  }
+#pragma unroll
+  for (int m = 0; m < MT; ++m) xb[m] = reinterpret_cast<const bf16x8*>(a.X) + (size_t)min(bm * MT + m, slabs - 1) * KS * 64;
+  bf16x8 wf[D][NT], xf[D][MT];
+  auto load = [&](int u, int ks) {
+    const size_t o = (size_t)min(ks, ks_last) * 64;
+#pragma unroll
+    for (int t = 0; t < NT; ++t) wf[u][t] = (wb[t] + o)[(unsigned)lane];
+#pragma unroll
+    for (int m = 0; m < MT; ++m) xf[u][m] = (ks < ks1 ? xb[m] + o : zeros)[(unsigned)lane];
+  };
+  f32x4 acc[NT][MT];
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int m = 0; m < MT; ++m) acc[t][m] = f32x4{0.f, 0.f, 0.f, 0.f};
+  auto multiply = [&](int u) {
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+      for (int t = 0; t < NT; ++t) acc[t][m] = Mma<bf16>::mma(wf[u][t], xf[u][m], acc[t][m]);
+  };
+#pragma unroll
+  for (int u = 0; u < D; ++u) load(u, ks0 + u);
+  const int blocks = (a.kpw + D - 1) / D;
+#pragma unroll 1
+  for (int b = 1; b < blocks; ++b) {
+#pragma unroll
+    for (int u = 0; u < D; ++u) {
+      multiply(u);
+      load(u, ks0 + b * D + u);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < D; ++u) multiply(u);
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int m = 0; m < MT; ++m) part[((wave * NT + t) * MT + m) * 64 + lane] = acc[t][m];
+  RowsEpilogue<EPI> e;                               // the first pair's row constants arrive while the wavefronts meet
+  e.row_inputs(a, min(bm * MT + wave % MT, slabs - 1), lane);
+  __syncthreads();
+  for (int i = wave; i < NT_OUT * MT; i += S) {      // (tile, slab) pairs, slab fastest
+    const int t = i / MT, m = i % MT;
+    if (bm * MT + m >= slabs || tile0 + t >= ntiles) continue;                 // uniform
+    if (i != wave) e.row_inputs(a, bm * MT + m, lane);
+    f32x4 s[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+    for (int st = 0; st < ((EPI == EPI_GATED) ? 2 : 1); ++st) {
+      const int tt = (EPI == EPI_GATED) ? 2 * t + st : t;
+      for (int w = 0; w < S; ++w) s[st] += part[((w * NT + tt) * MT + m) * 64 + lane];
+    }
+    e.tile_out(a, tile0 + t, bz, s[0], s[1]);
+  }
+}
+
+}  // namespace sd

@@ -19,6 +19,7 @@
 #include "kernels_attn.h"
 #include "kernels_gemm.h"
 #include "kernels_misc.h"
+#include "kernels_prompt.h"
 #include "kernels_sample.h"
 
 namespace {
@@ -28,6 +29,7 @@ using namespace sd;
 thread_local std::string g_load_error;
 static_assert(sd::ATTN_MAX_RG == SD_ATTN_MAX_ROWS_X_GROUP, "sd.h states the attention kernels' row limit");
 int g_num_cus = 256;                 // compute units of the device, read at load
+constexpr int MAX_CUS = 256;         // of any gfx950 device: sizes the workspace
 
 size_t align_up(size_t v, size_t a = 256) { return (v + a - 1) / a * a; }
 
@@ -62,7 +64,10 @@ struct Model {
   float* rope = nullptr;
   std::vector<LayerW> L;
   int batch = 1;               // sequences; each owns n_pages pages of every layer's pool
-  int rows_cap = MAX_ROWS;     // activation rows: one group of MAX_ROWS rows per sequence at most
+  int rows_cap = MAX_ROWS;     // activation rows: one group of MAX_ROWS rows per sequence at most, or rows_pass
+  int rows_pass = 0;           // prompt rows one pass over the model takes (forward_rows); 0: MAX_ROWS-row passes only
+  float* rows_rs = nullptr;    // 1 / rms of the rows of such a pass
+  bf16* zeros = nullptr;       // 1 KB of zeros
   int* page_table = nullptr;   // [batch][n_pages]
   bool pages_in_order = true;  // sequence b's table is b * n_pages + 0, 1, 2, ...; false (SD_FLAG_SCATTER_PAGES): back to front
   int *row_seq = nullptr, *logit_row = nullptr;   // [rows_cap], written by the embedding kernel
@@ -104,11 +109,18 @@ bool cfg_ok(const sd_model_cfg& c, std::string& why) {
   return true;
 }
 
+// Prompt rows a workgroup of the matrix-core attention takes: as many as its two 16-row tiles hold.
+int prompt_rows_per_wg(const sd_model_cfg& c) { return ATTN_MAX_RG / (c.n_heads / c.n_kv_heads); }
+
 // Lays a model out in the arena (or sizes it).
 void plan_model(Arena& A, Model& m, const sd_model_cfg& c, int page_size, int batch) {
   m.cfg = c;
   m.batch = batch;
-  m.rows_cap = MAX_ROWS * batch;
+  // bf16 models with the matrix-core attention take a prompt many rows at a time: a product over 2048
+  // rows keeps the whole chip in matrix instructions, more rows only cost memory
+  const bool many = c.dtype == SD_BF16 && (c.d_head == 64 || c.d_head == 128);
+  m.rows_pass = many ? std::min(2048, (c.max_len + MAX_ROWS - 1) / MAX_ROWS * MAX_ROWS) : 0;
+  m.rows_cap = std::max(MAX_ROWS * batch, m.rows_pass);
   m.esz = (c.dtype == SD_BF16) ? 2 : 4;
   const size_t e = m.esz, d = c.d_model, ff = c.d_ff, V = c.vocab;
   m.nq = c.n_heads * c.d_head;
@@ -152,8 +164,8 @@ void plan_model(Arena& A, Model& m, const sd_model_cfg& c, int page_size, int ba
   const size_t rows = (size_t)m.rows_cap;
   m.page_table = static_cast<int*>(A.take((size_t)batch * m.n_pages * sizeof(int)));
   m.x = static_cast<float*>(A.take(rows * d * sizeof(float)));
-  m.xg = A.take(rows * d * e);
-  m.ss = static_cast<float*>(A.take((size_t)batch * (d / 16) * 16 * sizeof(float)));   // [group][d/16][16]
+  m.xg = A.take(std::max(rows, (size_t)(many ? (c.enc_len + MAX_ROWS - 1) / MAX_ROWS * MAX_ROWS : 0)) * d * e);   // (also the encoder's rows, once)
+  m.ss = static_cast<float*>(A.take(rows / MAX_ROWS * (d / 16) * 16 * sizeof(float)));   // [group][d/16][16]
   m.qbuf = A.take(rows * m.nq * e);
   m.attn = A.take(rows * m.nq * e);
   m.ffn = A.take(rows * ff * e);
@@ -165,8 +177,15 @@ void plan_model(Arena& A, Model& m, const sd_model_cfg& c, int page_size, int ba
   m.attn_nsplit = (c.max_len > 1024) ? std::min(16, (c.max_len + m.attn_split_keys - 1) / m.attn_split_keys) : 1;
   if (m.attn_nsplit > 1) {
     m.attn_split_keys = ((c.max_len + m.attn_nsplit - 1) / m.attn_nsplit + 511) / 512 * 512;
-    m.attn_partial = static_cast<float*>(A.take((size_t)batch * c.n_kv_heads * m.attn_nsplit * ATTN_MAX_RG *
+    // (a prompt pass with few workgroups makes its row groups half as large)
+    const int per = prompt_rows_per_wg(c);
+    const size_t row_groups = std::max({(size_t)batch, (size_t)((m.rows_pass + per - 1) / per), (size_t)(2 * MAX_CUS / c.n_kv_heads + 2)});
+    m.attn_partial = static_cast<float*>(A.take(row_groups * c.n_kv_heads * m.attn_nsplit * ATTN_MAX_RG *
                                                 (c.d_head + 2) * sizeof(float)));
+  }
+  if (m.rows_pass > 0) {
+    m.rows_rs = static_cast<float*>(A.take((size_t)m.rows_pass * sizeof(float)));
+    m.zeros = static_cast<bf16*>(A.take(1024));
   }
   if (batch > 1) {
     m.xfrag = A.take((size_t)std::max({(size_t)d, (size_t)m.nq, ff}) * GEMM_WIDE_RT * 16 * e);
@@ -368,6 +387,14 @@ hipError_t allow_wide_lds() {
   return e;
 }
 
+// So does gemm_slices_kernel's with eight wavefronts and 4 x 4 tiles.
+template <int EPI>
+hipError_t allow_slices_lds() {
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_slices_kernel<EPI, 4, 4, 4>), hipFuncAttributeMaxDynamicSharedMemorySize, 8 * 16 * 1024);
+  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_slices_kernel<EPI, 4, 4, 3>), hipFuncAttributeMaxDynamicSharedMemorySize, 8 * 16 * 1024);
+  return e;
+}
+
 template <typename T>
 void launch_gemm_wide(hipStream_t s, int pro, int epi, const GemmArgs& a) {
 #define SD_CASE(P, E) if (pro == P && epi == E) return launch_gemm_wide_t<T, P, E>(s, a)
@@ -438,19 +465,25 @@ void launch_attn_mma(hipStream_t s, const AttnArgs& a, dim3 grid, int nw, size_t
 template <typename T>
 void launch_attn(hipStream_t s, const Model& m, AttnArgs a, int nseq) {
   const int G = a.H / a.Hkv, DH = m.cfg.d_head;
+  const bool prompt = a.R > MAX_ROWS;              // one sequence's prompt rows: groups of full row tiles
   a.G = G; a.g_mul = 65536 / G + 1;
   // few kv heads leave most CUs idle: split the (independent) rows over more workgroups
-  a.rows_per_wg = (nseq * a.Hkv * ((a.R + 1) / 2) <= g_num_cus) ? std::min(2, a.R) : a.R;
+  if (prompt) {
+    a.rows_per_wg = prompt_rows_per_wg(m.cfg);
+    if (a.Hkv * ((a.R + a.rows_per_wg - 1) / a.rows_per_wg) < g_num_cus) a.rows_per_wg /= 2;   // one row tile: more workgroups
+  }
+  else a.rows_per_wg = (nseq * a.Hkv * ((a.R + 1) / 2) <= g_num_cus) ? std::min(2, a.R) : a.R;
   if (a.cross || m.attn_nsplit <= 1) { a.nsplit = 1; a.split_keys = 0; a.partial = nullptr; }
   else { a.nsplit = m.attn_nsplit; a.split_keys = m.attn_split_keys; a.partial = m.attn_partial; }
-  if (a.nsplit > 1) a.rows_per_wg = a.R;          // the key ranges already spread the work
+  if (a.nsplit > 1 && !prompt) a.rows_per_wg = a.R;          // the key ranges already spread the work
+  a.groups = (a.R + a.rows_per_wg - 1) / a.rows_per_wg;
   // The workgroup is sized for the context: all of the encoder's keys in one block for cross-attention,
   // half of max_len for self-attention (a sequence that grows to max_len spends half its life below
   // that; longer contexts take more blocks).  Fixed per model, so every forward of a model, plain or
   // (gamma+1)-row, adds a row's keys in the same order.
   const int threads = a.cross ? attn_threads(DH, a.kv_len) : (a.nsplit > 1 ? 1024 : attn_threads(DH, (m.cfg.max_len + 1) / 2));
   const size_t lds = attn_lds_bytes(a.rows_per_wg * G, DH, threads);
-  const dim3 grid(a.Hkv, ((a.R + a.rows_per_wg - 1) / a.rows_per_wg) * a.nsplit, nseq);
+  const dim3 grid(a.Hkv, a.groups * a.nsplit, nseq);
   // bf16 with d_head 64 or 128: the matrix-core kernel (key ranges: four wavefronts per range, as
   // the ranges already spread the work)
   if (std::is_same<T, bf16>::value && (DH == 64 || DH == 128)) {
@@ -577,7 +610,7 @@ void forward(sd_ctx* c, Model& m, const Rows& rw, float* logits) {
                        rw.start, static_cast<const T*>(m.tok_emb), static_cast<const T*>(m.pos_emb), d, f.vocab, q.x,
                        q.row_pos, static_cast<const T*>(rms ? m.L[0].ln1g : nullptr),
                        reinterpret_cast<T*>(rms ? q.xg : nullptr), rms ? q.ss : nullptr,
-                       rw.rps, rw.seq0, rw.gamma, q.row_seq, q.logit_row, (d / 16) * 16);
+                       rw.rps, rw.seq0, rw.gamma, q.row_seq, q.logit_row, (d / 16) * 16, 0);
   }
   // One GEMM over every group: groups are 16-row slabs one after the other in all row-indexed
   // buffers, so up to GEMM_WIDE_RT of them go into one launch of the wide kernel (weights
@@ -672,7 +705,7 @@ void forward(sd_ctx* c, Model& m, const Rows& rw, float* logits) {
         }
         // long contexts end in the merge kernel, which can leave its output in fragment order for
         // the batched O projection (no re-tile)
-        if (!cross && m.attn_nsplit > 1 && n_groups > 1 && n_groups <= GEMM_WIDE_RT) { a.out_frag = m.xfrag2; produced_frag = true; }
+        if (!cross && m.attn_nsplit > 1 && n_groups > 1 && n_groups <= GEMM_WIDE_RT) { a.out_frag = m.xfrag2; a.frag_ks = GEMM_WIDE_RT; a.frag_slab = 1; produced_frag = true; }
         launch_attn<T>(s, m, a, rw.nseq);
       }
     };
@@ -725,6 +758,148 @@ void forward(sd_ctx* c, Model& m, const Rows& rw, float* logits) {
 void forward_any(sd_ctx* c, Model& m, const Rows& rw, float* logits) {
   if (m.cfg.dtype == SD_BF16) forward<bf16>(c, m, rw, logits);
   else forward<float>(c, m, rw, logits);
+}
+
+// ---- products over many rows (kernels_prompt.h) ----
+template <int EPI, int NT, int MT>
+int rows_grid(RowsGemmArgs& a, int waves_n) {        // workgroups of NT weight tiles (per wavefront, waves_n of them) x MT slabs
+  constexpr int OUT = (EPI == EPI_GATED) ? NT / 2 : NT;     // output tiles
+  a.ntiles_wg = (a.N / 16 + waves_n * OUT - 1) / (waves_n * OUT);
+  a.mtiles = ((a.rows + 15) / 16 + MT - 1) / MT;
+  return a.ntiles_wg * a.mtiles * a.batch;
+}
+template <int EPI, int MT>
+void launch_gemm_rows_t(hipStream_t s, RowsGemmArgs a) {
+  const int grid = rows_grid<EPI, 2, MT>(a, 4);
+  hipLaunchKernelGGL((gemm_rows_kernel<EPI, 2, MT>), dim3(grid), dim3(256), 0, s, a);
+}
+template <int EPI, int NT, int MT>
+bool launch_gemm_slices_t(hipStream_t s, RowsGemmArgs a, int most) {
+  const int grid = rows_grid<EPI, NT, MT>(a, 1);
+  if (grid > most) return false;
+  const size_t lds = (size_t)a.nchunk * NT * MT * 1024;
+  if (a.kpw % 4 != 0 && a.kpw % 3 == 0) hipLaunchKernelGGL((gemm_slices_kernel<EPI, NT, MT, 3>), dim3(grid), dim3(64 * a.nchunk), lds, s, a);
+  else hipLaunchKernelGGL((gemm_slices_kernel<EPI, NT, MT, 4>), dim3(grid), dim3(64 * a.nchunk), lds, s, a);
+  return true;
+}
+// Which shape: measured on 256 CUs, us.
+//   The large one (128 features x 128 rows a workgroup, two workgroups a CU) from 1.6 workgroups a CU on,
+//   or where all rows fit one workgroup and the weights bound it: 2000 rows, N 6144, K 4096 (768
+//   workgroups) 104 against 132 with half the rows; 2000 x 3072 x 1024 (384) 23.1 against 19.9;
+//   128 x gated 14336 x 4096 (224, one row tile) 53 against 63.
+//   The medium one (half the rows) while it has 0.7 workgroups a CU: 256 x 6144 x 4096 (192) 28.7, K-slices
+//   34; 256 x 4096 x 4096 (128) 27.8, K-slices 19.0.
+//   Below that K is split over the wavefronts of a workgroup, with the smallest tile whose workgroups
+//   fit the chip in one round: 64 x 4096 x 4096 11.7 with 256 workgroups, 15.3 with 128 and with 512.
+//   (Four-wavefront workgroups, which a CU holds several of, may be a few more: 512 x 768 x 768 4.2 with
+//   384, 4.5 with 192, 4.8 with 768.)
+template <int EPI>
+void launch_gemm_rows(hipStream_t s, const Model& m, RowsGemmArgs a) {
+  const int KS = a.K / 32, S = pick_waves(KS);       // gemm_kernel's split of K: same sums
+  a.kpw = (KS + S - 1) / S; a.nchunk = S; a.zeros = m.zeros;
+  if (a.batch < 1) a.batch = 1;
+  const int large = rows_grid<EPI, 2, 8>(a, 4), row_tiles = a.mtiles, medium = rows_grid<EPI, 2, 4>(a, 4);
+  if (5 * large >= 8 * g_num_cus || (row_tiles == 1 && 4 * large >= 3 * g_num_cus)) return launch_gemm_rows_t<EPI, 8>(s, a);
+  if (10 * medium >= 7 * g_num_cus) return launch_gemm_rows_t<EPI, 4>(s, a);
+  const int most = (S == 4) ? g_num_cus * 3 / 2 : g_num_cus;
+  constexpr int N1 = (EPI == EPI_GATED) ? 2 : 1;     // a gated product has two weight streams
+  if (launch_gemm_slices_t<EPI, N1, 1>(s, a, most)) return;
+  if (launch_gemm_slices_t<EPI, N1, 2>(s, a, most)) return;
+  if (N1 == 1 && launch_gemm_slices_t<EPI, 2, 2>(s, a, most)) return;
+  if (launch_gemm_slices_t<EPI, 2, 4>(s, a, most)) return;
+  launch_gemm_slices_t<EPI, 4, 4>(s, a, 1 << 30);
+}
+
+// A pass of `rows` prompt rows of sequence `seq` from position `start` (bf16 models with the matrix-core
+// attention): the keys and values of every layer go to the cache.  Every row's arithmetic is forward()'s.
+// The last layer ends at its cache append: nothing reads what would follow.
+void forward_rows(sd_ctx* c, Model& m, int seq, int start, int rows) {
+  hipStream_t s = c->stream;
+  const sd_model_cfg& f = m.cfg;
+  const int d = f.d_model, slabs = (rows + MAX_ROWS - 1) / MAX_ROWS, ss_stride = (d / 16) * 16;
+  const bool rms = (f.arch != SD_ARCH_GPT);
+  const int n_layers = (int)m.L.size();
+  bf16 *xg = static_cast<bf16*>(m.xg), *attn = static_cast<bf16*>(m.attn), *ffn = static_cast<bf16*>(m.ffn), *q = static_cast<bf16*>(m.qbuf);
+  auto cb = [](const void* p) { return static_cast<const bf16*>(p); };
+  hipLaunchKernelGGL((embed_kernel<bf16>), dim3(rows), dim3(256), 0, s, (int)ROWS_PREFILL, 0, c->d_state, m.prompt, start,
+                     cb(m.tok_emb), cb(m.pos_emb), d, f.vocab, m.x, m.row_pos, cb(rms ? m.L[0].ln1g : nullptr),
+                     rms ? xg : (bf16*)nullptr, rms ? m.ss : nullptr, rows, seq, 0, m.row_seq, m.logit_row, ss_stride, 1);
+  int n_part = 1;
+  // the input of a product behind a norm: 1 / rms of the rows, or the normalised rows
+  auto normed = [&](const void* g, const void* b) {
+    RowsGemmArgs a{};
+    a.rows = rows; a.K = d; a.X = xg;
+    if (rms) {
+      hipLaunchKernelGGL(rows_rs_kernel, dim3(slabs), dim3(256), 0, s, m.ss, n_part, ss_stride, d, f.norm_eps, m.rows_rs);
+      a.rs = m.rows_rs;
+    } else {
+      const int KS = d / 32, S = pick_waves(KS);
+      hipLaunchKernelGGL(rows_layernorm_kernel, dim3(slabs), dim3(64 * S), 0, s, m.x, cb(g), cb(b), xg, rows, d, (KS + S - 1) / S, f.norm_eps);
+    }
+    return a;
+  };
+  auto resid = [&](const void* W, const bf16* X, int K, const void* bias, const void* gain_next) {
+    RowsGemmArgs a{};
+    a.rows = rows; a.K = K; a.N = d; a.W = cb(W); a.X = X; a.bias = cb(bias); a.x = m.x;
+    if (rms) { a.xg = xg; a.gain_next = cb(gain_next); a.ss = m.ss; a.ss_stride = ss_stride; }
+    launch_gemm_rows<EPI_RESID>(s, m, a);
+    n_part = d / 16;
+  };
+  for (int li = 0; li < n_layers; ++li) {
+    const LayerW& l = m.L[li];
+    {
+      RowsGemmArgs a = normed(l.ln1g, l.ln1b);
+      a.W = cb(l.wqkv); a.bias = cb(l.bqkv); a.N = m.nq + 2 * m.nkv;
+      a.q = q; a.nq = m.nq; a.nkv = m.nkv; a.kv_pool = static_cast<bf16*>(l.kv); a.page_table = m.page_table + (size_t)seq * m.n_pages;
+      a.row_pos = m.row_pos; a.page_size = m.page_size; a.n_kv_heads = f.n_kv_heads; a.d_head = f.d_head; a.rope = m.rope;
+      launch_gemm_rows<EPI_QKV>(s, m, a);
+    }
+    if (li + 1 == n_layers) break;
+    auto attention = [&](bool cross) {
+      AttnArgs a{};
+      a.q = q; a.out = attn; a.kv_pool = l.kv; a.page_table = m.page_table; a.page_size = m.page_size; a.n_pages = m.n_pages;
+      a.row_pos = m.row_pos; a.R = rows; a.H = f.n_heads; a.Hkv = f.n_kv_heads;
+      a.scale = (f.arch == SD_ARCH_T5DEC) ? 1.0f : 1.0f / sqrtf((float)f.d_head);
+      a.bias_by_key = m.bias_by_key; a.bias_off = f.max_len - 1;
+      a.seq0 = seq; a.pt_stride = m.n_pages;
+      if (cross) { a.cross = 1; a.ck = l.cross_k; a.cv = l.cross_v; a.kv_len = f.enc_len; a.scale = 1.0f; a.bias_by_key = nullptr; }
+      a.out_frag = attn; a.frag_ks = 1; a.frag_slab = m.nq / 32;
+      launch_attn<bf16>(s, m, a, 1);
+    };
+    attention(false);
+    resid(l.wo, attn, m.nq, l.bo, (f.arch == SD_ARCH_T5DEC) ? l.lncg : l.ln2g);
+    if (f.arch == SD_ARCH_T5DEC) {
+      RowsGemmArgs a = normed(l.lncg, nullptr);
+      a.W = cb(l.cq); a.N = m.nq; a.out = q;
+      launch_gemm_rows<EPI_STORE>(s, m, a);
+      attention(true);
+      resid(l.co, attn, m.nq, nullptr, l.ln2g);
+    }
+    RowsGemmArgs a = normed(l.ln2g, l.ln2b);
+    a.W = cb(l.w1); a.N = f.d_ff; a.out = ffn;
+    if (!rms) { a.bias = cb(l.b1); launch_gemm_rows<EPI_ACT>(s, m, a); }
+    else {
+      a.W2 = cb(l.wu); a.act = (f.arch == SD_ARCH_T5DEC) ? ACT_GELU : ACT_SILU;
+      launch_gemm_rows<EPI_GATED>(s, m, a);
+    }
+    resid(l.w2, ffn, f.d_ff, l.b2, m.L[li + 1].ln1g);
+  }
+}
+
+// The cross-attention keys / values of every layer in one launch.
+void cross_kv_rows(sd_ctx* c, Model& m, const void* enc) {
+  const sd_model_cfg& f = m.cfg;
+  const int slabs = (f.enc_len + MAX_ROWS - 1) / MAX_ROWS, threads = slabs * (f.d_model / 32) * 64;
+  hipLaunchKernelGGL(rows_to_slabs_kernel, dim3((threads + 255) / 256), dim3(256), 0, c->stream, static_cast<const bf16*>(enc),
+                     static_cast<bf16*>(m.xg), f.enc_len, f.d_model);
+  const LayerW &l0 = m.L[0], &l1 = m.L[std::min<size_t>(1, m.L.size() - 1)];       // the layers lie at one distance
+  auto dist = [](const void* to, const void* from) { return (size_t)(static_cast<const bf16*>(to) - static_cast<const bf16*>(from)); };
+  RowsGemmArgs a{};
+  a.rows = f.enc_len; a.K = f.d_model; a.N = m.nq; a.X = static_cast<const bf16*>(m.xg); a.W = static_cast<const bf16*>(l0.ck);
+  a.out = static_cast<bf16*>(l0.cross_k); a.hm = 1; a.d_head = f.d_head; a.batch = 2 * (int)m.L.size();
+  a.w_layer = dist(l1.ck, l0.ck); a.w_which = dist(l0.cv, l0.ck);
+  a.out_layer = dist(l1.cross_k, l0.cross_k); a.out_which = dist(l0.cross_v, l0.cross_k);
+  launch_gemm_rows<EPI_STORE>(c->stream, m, a);
 }
 
 // Cross-attention keys / values of every layer from the encoder output.
@@ -1007,7 +1182,9 @@ extern "C" sd_status sd_load_models(sd_ctx** out, const sd_model_cfg* p_cfg, con
       g_num_cus = cus;
   }
   if (allow_big_lds<bf16>() != hipSuccess || allow_big_lds<float>() != hipSuccess ||
-      allow_wide_lds<bf16>() != hipSuccess || allow_wide_lds<float>() != hipSuccess)
+      allow_wide_lds<bf16>() != hipSuccess || allow_wide_lds<float>() != hipSuccess ||
+      allow_slices_lds<EPI_STORE>() != hipSuccess || allow_slices_lds<EPI_QKV>() != hipSuccess || allow_slices_lds<EPI_RESID>() != hipSuccess ||
+      allow_slices_lds<EPI_ACT>() != hipSuccess || allow_slices_lds<EPI_GATED>() != hipSuccess)
     return bail(SD_EHIP, "cannot raise the LDS limit");
   std::string err;
   c->p.pages_in_order = c->q.pages_in_order = (rt->flags & SD_FLAG_SCATTER_PAGES) == 0;
@@ -1017,6 +1194,8 @@ extern "C" sd_status sd_load_models(sd_ctx** out, const sd_model_cfg* p_cfg, con
   st = (q_cfg->dtype == SD_BF16) ? load_model<bf16>(c->stream, c->q, q_w, n_q, err)
                                  : load_model<float>(c->stream, c->q, q_w, n_q, err);
   if (st != SD_OK) return bail(st, "Mq: " + err);
+  for (const Model* m : {&c->p, &c->q})
+    if (m->zeros) hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(256), 0, c->stream, reinterpret_cast<unsigned int*>(m->zeros), 0u, (size_t)256);
   {
     const size_t n = B * SAMPLE_COUNTER_STRIDE;
     hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c->stream, c->d_counter, 0u, n);
@@ -1071,10 +1250,15 @@ extern "C" sd_status sd_prefill(sd_ctx* c, int32_t row, const int32_t* prompt, i
     HIP_TRY(c, hipMemcpyAsync(m.prompt, prompt, (size_t)n * sizeof(int), hipMemcpyHostToDevice, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     if (m.cfg.arch == SD_ARCH_T5DEC) {
-      if (m.cfg.dtype == SD_BF16) cross_kv<bf16>(c, m, encs[k]); else cross_kv<float>(c, m, encs[k]);
+      if (m.rows_pass > 0 && m.cfg.enc_len > MAX_ROWS) cross_kv_rows(c, m, encs[k]);
+      else if (m.cfg.dtype == SD_BF16) cross_kv<bf16>(c, m, encs[k]);
+      else cross_kv<float>(c, m, encs[k]);
     }
+    int s0 = 0;
+    for (; m.rows_pass > 0 && n - 1 - s0 > MAX_ROWS; s0 += std::min(m.rows_pass, n - 1 - s0))
+      forward_rows(c, m, row, s0, std::min(m.rows_pass, n - 1 - s0));
     const int step = prefill_rows(m.cfg);
-    for (int s0 = 0; s0 < n - 1; s0 += step)
+    for (; s0 < n - 1; s0 += step)
       forward_any(c, m, Rows{ROWS_PREFILL, 0, std::min(step, n - 1 - s0), s0, row, 1, 0}, nullptr);
   }
   SeqState st{};

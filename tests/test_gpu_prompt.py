@@ -1,0 +1,62 @@
+"""Prefill of many rows at once: a sequence that is prefilled whole must stand exactly where the same
+sequence stands after it was decoded token by token (other kernels, the same additions in the same
+order), so the next iteration's logits of both models are equal bit for bit."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import transformer as T
+from paper_2211_17192_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+# (arch, d_model, heads, kv heads, d_head, d_ff, layers, rows, enc_len): what each one reaches
+CASES = {
+    # fewer rows than two slabs, one K-step per wavefront: the smallest product over K-slices
+    "gpt-17": (T.GPT, 128, 2, 2, 64, 512, 3, 17, 0),
+    # odd row count, K of 23 k-steps (slices of 6, 6, 6, 5: three k-steps a block) and a 63-tile FFN
+    "gqa-121-odd-k": (T.GQA, 736, 12, 6, 64, 1008 * 2, 2, 121, 0),
+    # LayerNorm rows longer than what a wavefront holds in registers; K of eight slices
+    "gpt-200-wide": (T.GPT, 2304, 4, 4, 64, 2080, 2, 200, 0),
+    # position bias, cross-attention over a ragged number of encoder positions
+    "t5-75-enc-61": (T.T5DEC, 256, 4, 4, 64, 704, 3, 75, 61),
+    "t5-33-dh128": (T.T5DEC, 512, 4, 4, 128, 544, 2, 33, 17),
+    # enough rows for the 64-row and the 128-row workgroups, four query heads per KV head
+    "gqa-1050-medium-large": (T.GQA, 512, 16, 4, 64, 5120, 2, 1050, 0),
+    # a context beyond 1024 positions: key ranges times row groups; two passes of the pass limit
+    "gqa-2100-two-passes": (T.GQA, 256, 4, 2, 128, 512, 2, 2100, 0),
+}
+
+
+@pytest.mark.parametrize("scatter", [False, True])
+@pytest.mark.parametrize("name", list(CASES))
+def test_prefill_equals_token_by_token(name, scatter):
+    from paper_2211_17192_amd import binding
+    arch, d, heads, kv, dh, ff, layers, rows, enc = CASES[name]
+    if scatter and rows > 300:
+        pytest.skip("the page table's order is covered by the small cases")
+    gamma, vocab = 3, 512
+    kw = dict(n_kv_heads=kv) if arch == T.GQA else {}
+    cfg = synth.model_cfg(arch, layers, d, heads, ff, vocab, rows + 40, d_head=dh, enc_len=enc, dtype="bf16", logit_scale=4.0, **kw)
+    w = synth.random_weights(cfg, 5, "cuda", 0.04)
+    cfg_q, w_q = synth.truncated_noisy_copy(cfg, w, layers - 1, 9, 0.004)
+    enc_out = synth.counter_normal((enc, d), 3, 1.0, 0.0, "cuda").to(torch.bfloat16) if enc else None
+    flags = binding.SD_FLAG_GRAPH | (binding.SD_FLAG_SCATTER_PAGES if scatter else 0)
+    dec = binding.SpecDecoder(cfg, w, cfg_q, w_q, max_gamma=gamma, flags=flags)
+    tokens = [int(t) for t in synth.random_tokens(7, 9, vocab)]
+    u = synth.uniform_stream(11, (rows + 8) * (2 * gamma + 1)).reshape(-1, 2 * gamma + 1)
+    dec.prefill(tokens, enc_out, enc_out)            # 8 rows: the decoding kernels
+    it = 0
+    while len(tokens) < rows + 1:
+        tokens += dec.step(gamma, 1.0, u[it])[1]
+        it += 1
+    n1, t1 = dec.step(gamma, 1.0, u[it])
+    p1, q1 = dec.logits(0, gamma + 1), dec.logits(1, gamma)
+    dec.reset()
+    dec.prefill(tokens, enc_out, enc_out)            # len(tokens) - 1 >= rows rows at once
+    n2, t2 = dec.step(gamma, 1.0, u[it])
+    p2, q2 = dec.logits(0, gamma + 1), dec.logits(1, gamma)
+    dec.close()
+    assert np.isfinite(p1).all() and np.ptp(p1) > 1.0
+    assert np.array_equal(p1, p2) and np.array_equal(q1, q2)
+    assert (n1, t1) == (n2, t2)
