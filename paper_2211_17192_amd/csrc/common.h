@@ -195,28 +195,13 @@ __device__ __forceinline__ V block_reduce(V v, V* red, Op op, V identity) {
   if (lane == 0) red[wave] = v;
   __syncthreads();
   V r = identity;
-  for (int w = 0; w < nw; ++w) r = op(r, red[w]);
-  return r;
-}
-
-// Ticket: returns true in every thread of exactly one workgroup, the one that
-// arrives last among `expected`; that workgroup sees all global writes the
-// others made before their call.  It also re-arms the counter for the next use.
-__device__ __forceinline__ bool last_block_arrives(unsigned int* counter, unsigned int expected,
-                                                   int* lds_flag) {
-  // The barrier orders every thread's earlier global writes before thread 0's
-  // device-scope release; one wavefront pays for the cache write-back /
-  // invalidate instead of all of them.
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    const unsigned int t =
-        __hip_atomic_fetch_add(counter, 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-    const int last = (t == expected - 1u);
-    if (last) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    *lds_flag = last;
+  if (nw == 16) {                        // (the reads of a loop of unknown length would wait for one another)
+#pragma unroll
+    for (int w = 0; w < 16; ++w) r = op(r, red[w]);
+  } else {
+    for (int w = 0; w < nw; ++w) r = op(r, red[w]);
   }
-  __syncthreads();
-  return *lds_flag != 0;
+  return r;
 }
 
 }  // namespace sd

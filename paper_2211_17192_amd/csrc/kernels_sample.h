@@ -1,8 +1,7 @@
 // Sampling kernels: section 2.2 standardisation (temperature softmax / argmax),
 // inverse-CDF draws from caller-supplied uniforms, and the accept / resample
-// part of Algorithm 1 fused into one launch (row statistics in parallel, then
-// the last-finishing workgroup of a sequence takes the decisions, draws the
-// extra token and commits / rolls back the sequence state).
+// part of Algorithm 1 in two launches (row statistics spread over the chip, then
+// the decisions, the draw of the extra token and the commit / roll-back).
 //
 // Arithmetic of a standardised row z at temperature T > 0:
 //   m = max_k z_k,  e_k = exp((z_k - m) / T)  (fp32 hardware exp2 path),
@@ -19,8 +18,11 @@ namespace sd {
 constexpr int SAMPLE_THREADS = 1024;
 constexpr int SAMPLE_CHUNK = 256;           // vocabulary entries per scan chunk (64 lanes x 4)
 constexpr int SAMPLE_MAX_CHUNKS = 1024;     // vocab <= 262144
-constexpr int SAMPLE_COUNTER_STRIDE = 64;    // uint32 elements between the tickets of two sequences
 constexpr int SAMPLE_REG_F4 = 8;            // a row up to 32768 entries is held in registers
+constexpr int SAMPLE_MAX_GAMMA = 15;
+constexpr int SAMPLE_PARTS = 64;            // parts a logits row is cut into for its statistics, at most
+constexpr int SAMPLE_PART = 1024;           // entries a wavefront takes at a time
+constexpr int SAMPLE_CHUNKS_WG = 16;        // scan chunks of one workgroup: one per wavefront
 
 struct RowStat {
   float  m;      // max logit
@@ -29,6 +31,25 @@ struct RowStat {
   float  thr;    // entries with a logit below it are dropped (top-k / nucleus); -inf: none
   float  pad;
 };
+
+// The statistics of one part of a row.
+struct RowPart {
+  double S;      // sum of exp((z - m) / T) over its kept entries
+  float  m;      // its max logit
+  union { int arg; float thr; };   // argmax sampling: lowest index attaining m; filtered rows (one part): the threshold
+};
+
+// Working memory of one sequence's accept / resample call or draw.  The layout depends on nothing, so
+// calls of any size may follow each other on one allocation; the ticket is zero between calls.
+struct SampleScratch {
+  unsigned int ticket[64];
+  RowPart part[2 * SAMPLE_MAX_GAMMA + 1][SAMPLE_PARTS];
+  double beta[SAMPLE_MAX_GAMMA][SAMPLE_PARTS];
+  double tot[SAMPLE_MAX_CHUNKS];
+};
+
+constexpr int SAMPLE_BINS = 2048;           // 11 bits of the order-preserving key
+constexpr int SAMPLE_LIST = 2048;
 
 struct SampleSmem {
   float  redf[16];
@@ -41,6 +62,12 @@ struct SampleSmem {
   double before;         // scan: cumulative weight before that chunk
   double total;
   double ctot[SAMPLE_MAX_CHUNKS];
+  unsigned long long bins[SAMPLE_BINS];
+  unsigned long long wsum[16];
+  unsigned int sel;
+  unsigned long long above;
+  unsigned int list[SAMPLE_LIST];        // keys of the entries a filter still has to look at
+  int listed;
 };
 
 __device__ __forceinline__ float exp_scaled(float z, float m, float invT, float thr) {
@@ -54,6 +81,27 @@ __device__ __forceinline__ unsigned float_key(float z) {
 }
 __device__ __forceinline__ float key_float(unsigned k) {
   return __uint_as_float((k & 0x80000000u) ? (k & 0x7fffffffu) : ~k);
+}
+
+// Entries k .. k + 3 of a row of V entries that starts at any 4-byte boundary (-inf past its end).
+typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ float4 load4_row(const float* __restrict__ z, int k, int V) {
+  constexpr float NONE = -INFINITY;
+  if (V < 4) {                                       // uniform
+    return make_float4(k < V ? z[min(k, V - 1)] : NONE, k + 1 < V ? z[min(k + 1, V - 1)] : NONE, k + 2 < V ? z[min(k + 2, V - 1)] : NONE, NONE);
+  }
+  const f32x4_any t = *reinterpret_cast<const f32x4_any*>(z + min(k, V - 4));    // unconditional, within the row
+  const int over = k - (V - 4);                      // > 0: the group runs past the row's end
+  if ((V & 3) == 0) return over <= 0 ? make_float4(t[0], t[1], t[2], t[3]) : make_float4(NONE, NONE, NONE, NONE);
+  return make_float4(over <= 0 ? t[0] : over == 1 ? t[1] : over == 2 ? t[2] : over == 3 ? t[3] : NONE,
+                     over <= 0 ? t[1] : over == 1 ? t[2] : over == 2 ? t[3] : NONE,
+                     over <= 0 ? t[2] : over == 1 ? t[3] : NONE, over <= 0 ? t[3] : NONE);
+}
+
+// A sum of exponentials relative to m, brought to the maximum M >= m.  (Nothing above -inf: no weight;
+// m == M needs no factor, which keeps a row without any finite entry what it is, not a number.)
+__device__ __forceinline__ double rescaled_sum(double s, float m, float M, float invT) {
+  return (m == M) ? s : (m == -INFINITY) ? 0.0 : s * (double)__expf((m - M) * invT);
 }
 
 // A row of up to 32768 entries fits the registers of one 1024-thread workgroup:
@@ -73,12 +121,193 @@ __device__ __forceinline__ void load_row_regs(const float* __restrict__ z, int V
     v[it] = (i < n4) ? t : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
   }
 }
+// The search behind the filters: the largest key tau such that the entries with a key >= tau weigh at
+// least `target` together (weights are integers, so the sums do not depend on the order), 11, 11 and 10
+// bits at a time.  One step: a histogram of the entries that share the bits found so far, and the bin
+// in which the sum from the top reaches the target; `above` is the weight of what lies beyond the
+// bins.  each(f) calls f(key, weight) for this thread's entries, weight as a function.  False (in every
+// thread): all entries together weigh less.
+struct RadixSearch { unsigned tau; unsigned long long above; int step; };
+template <typename Each>
+__device__ __forceinline__ bool radix_step(RadixSearch& q, unsigned long long target, SampleSmem& sm, Each&& each) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int shift = (q.step == 0) ? 21 : (q.step == 1) ? 10 : 0, bits = (q.step < 2) ? 11 : 10;
+  __syncthreads();
+  sm.bins[tid] = 0ull; sm.bins[tid + SAMPLE_THREADS] = 0ull;
+  if (tid == 0) sm.sel = 0xffffffffu;
+  __syncthreads();
+  const unsigned mask = (1u << bits) - 1u, top = (q.step == 0) ? 0u : q.tau >> (shift + bits);
+  each([&](unsigned k, auto&& weight) {
+    if (q.step == 0 || (k >> (shift + bits)) == top) {
+      const unsigned long long w = weight();
+      if (w != 0ull) atomicAdd(&sm.bins[(k >> shift) & mask], w);
+    }
+  });
+  __syncthreads();
+  // sums from the top: thread tid owns two bins
+  const int hi = SAMPLE_BINS - 1 - 2 * tid, lo = hi - 1;
+  const unsigned long long bh = sm.bins[hi], bl = sm.bins[lo];
+  unsigned long long inc = bh + bl;
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1) {
+    const unsigned long long t = __shfl_up(inc, o, WAVE);
+    if (lane >= o) inc += t;
+  }
+  if (lane == 63) sm.wsum[wave] = inc;
+  __syncthreads();
+  unsigned long long before = q.above + inc - (bh + bl);
+  for (int w = 0; w < wave; ++w) before += sm.wsum[w];
+  if (before < target && before + bh + bl >= target) {              // exactly one thread, if any
+    const bool upper = before + bh >= target;
+    sm.sel = (unsigned)(upper ? hi : lo);
+    sm.above = upper ? before : before + bh;
+  }
+  __syncthreads();
+  if (sm.sel == 0xffffffffu) return false;
+  q.tau |= sm.sel << shift;
+  q.above = sm.above;
+  ++q.step;
+  return true;
+}
+// Puts the keys of this thread's entries that `want` into the list (order: whatever; the sums are
+// integers); the number of them, which may exceed the list's room.
+template <typename Want>
+__device__ __forceinline__ int list_entries(const float4 (&v)[SAMPLE_REG_F4], int nv4, SampleSmem& sm, Want&& want) {
+  const int tid = threadIdx.x;
+  __syncthreads();
+  if (tid == 0) sm.listed = 0;
+  __syncthreads();
+#pragma unroll
+  for (int it = 0; it < SAMPLE_REG_F4; ++it) {
+    const float z[4] = {v[it].x, v[it].y, v[it].z, v[it].w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const unsigned k = float_key(z[e]);
+      if (it * SAMPLE_THREADS + tid < nv4 && want(k)) {
+        const int i = atomicAdd(&sm.listed, 1);
+        if (i < SAMPLE_LIST) sm.list[i] = k;
+      }
+    }
+  }
+  __syncthreads();
+  return sm.listed;
+}
+// The rest of a search, by one wavefront over a list of keys in LDS: the key bits below `bits`, eight at a
+// time, without a barrier.  (A step of the whole workgroup costs 3 us: five barriers of sixteen
+// wavefronts.)  False: all listed entries together weigh less than the target.
+template <typename W>
+__device__ __forceinline__ bool list_search(RadixSearch& q, int bits, unsigned long long target, const unsigned* list, int n, SampleSmem& sm, W&& weight) {
+  const int lane = threadIdx.x & 63;
+  while (bits > 0) {
+    const int take = min(8, bits), shift = bits - take;
+    const unsigned mask = (1u << take) - 1u;
+    unsigned long long* bins = sm.bins;              // 256 of them: lane owns four
+#pragma unroll
+    for (int e = 0; e < 4; ++e) bins[lane * 4 + e] = 0ull;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    for (int i = lane; i < n; i += WAVE) {
+      const unsigned k = list[i];
+      if (bits == 32 || (k >> bits) == (q.tau >> bits)) {
+        const unsigned long long w = weight(k);
+        if (w != 0ull) atomicAdd(&bins[(k >> shift) & mask], w);
+      }
+    }
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    unsigned long long b[4];                         // from the top: bins 255 - 4 lane - e
+#pragma unroll
+    for (int e = 0; e < 4; ++e) b[e] = bins[255 - 4 * lane - e];
+    const unsigned long long own = b[0] + b[1] + b[2] + b[3];
+    unsigned long long inc = own;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const unsigned long long t = __shfl_up(inc, o, WAVE);
+      if (lane >= o) inc += t;
+    }
+    unsigned long long before = q.above + inc - own;
+    const bool here = before < target && before + own >= target;
+    const unsigned long long who = __ballot(here);
+    if (who == 0ull) return false;
+    int bin = 255 - 4 * lane;
+#pragma unroll
+    for (int e = 0; e < 3; ++e)
+      if (before + b[e] < target && bin == 255 - 4 * lane - e) { before += b[e]; --bin; }
+    const int src = __ffsll((long long)who) - 1;
+    q.tau |= (unsigned)__shfl(bin, src, WAVE) << shift;
+    q.above = __shfl(before, src, WAVE);
+    bits = shift;
+  }
+  return true;
+}
+// weight(key): an integer.  nv4: the row's float4 groups (the registers beyond hold padding).
+// Most rows are settled on a short list: a first bound (k_first > 0: the k_first-th largest of the threads'
+// own maxima, which the k_first-th largest entry cannot lie below; else the first 11 bits) leaves few
+// entries, and one wavefront finishes on those.  A row that overflows the list (ties) is
+// searched in the registers to the end.  `listed`: on entry, the list holds all entries that weigh
+// anything; on return, it holds every entry with a key >= tau.
+template <typename W>
+__device__ __forceinline__ unsigned filter_threshold(const float4 (&v)[SAMPLE_REG_F4], int nv4, unsigned long long target, int k_first,
+                                                     SampleSmem& sm, bool& listed, W&& weight) {
+  const int tid = threadIdx.x, wave = tid >> 6;
+  auto in_regs = [&](auto&& f) {
+#pragma unroll
+    for (int it = 0; it < SAMPLE_REG_F4; ++it) {
+      const float z[4] = {v[it].x, v[it].y, v[it].z, v[it].w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const unsigned k = float_key(z[e]);
+        f(k, [&] { return (it * SAMPLE_THREADS + tid < nv4) ? weight(k) : 0ull; });
+      }
+    }
+  };
+  RadixSearch q{0u, 0ull, 0};
+  bool ok = true;
+  int bits = 32;
+  const bool given = listed;
+  if (given) {
+  } else if (k_first > 0) {
+    unsigned best = 0u;
+#pragma unroll
+    for (int it = 0; it < SAMPLE_REG_F4; ++it)
+      best = max(best, max(max(float_key(v[it].x), float_key(v[it].y)), max(float_key(v[it].z), float_key(v[it].w))));
+    const int real = min(nv4, SAMPLE_THREADS);       // threads with entries
+    __syncthreads();
+    if (tid < real) sm.list[tid] = best;
+    __syncthreads();
+    if (wave == 0) {
+      RadixSearch p{0u, 0ull, 0};
+      const bool found = list_search(p, 32, (unsigned long long)k_first, sm.list, real, sm, [](unsigned) { return 1ull; });
+      if (tid == 0) sm.sel = found ? p.tau : 0u;     // (fewer threads with entries than k_first: no bound)
+    }
+    __syncthreads();
+    const unsigned bound = sm.sel;
+    listed = list_entries(v, nv4, sm, [&](unsigned k) { return k >= bound; }) <= SAMPLE_LIST;
+  } else {
+    ok = radix_step(q, target, sm, in_regs);
+    if (ok) listed = list_entries(v, nv4, sm, [&](unsigned k) { return (k >> 21) == (q.tau >> 21); }) <= SAMPLE_LIST;
+    bits = 21;
+  }
+  if (ok && listed) {
+    const int n = sm.listed;
+    if (wave == 0) {
+      const bool found = list_search(q, bits, target, sm.list, n, sm, weight);
+      if (tid == 0) sm.sel = found ? q.tau : 0u;
+    }
+    __syncthreads();
+    q.tau = sm.sel;
+  } else {
+    while (ok && q.step < 3) ok = radix_step(q, target, sm, in_regs);
+    if (!ok) q.tau = 0u;
+  }
+  if (k_first <= 0 && !given) listed = false;
+  __syncthreads();
+  return q.tau;
+}
+
 // top_k > 0 / 0 < top_p < 1 (section 2.2: top-k and nucleus sampling as an adjusted
-// distribution): the kept set is {z >= thr}.  Top-k: thr = k-th largest logit, found bit by
-// bit on the order-preserving integer key (32 counting passes over the registers).  Nucleus,
-// applied to what top-k left: thr = the largest value whose upper set still carries top_p of
-// the mass, found the same way with sums in place of counts.  Ties with the last kept entry
-// are kept.  Argmax sampling ignores both.
+// distribution): the kept set is {z >= thr}.  Top-k: thr = k-th largest logit.  Nucleus, applied to
+// what top-k left: thr = the largest value whose upper set still carries top_p of the mass (in units
+// of 2^-44 of the largest entry's).  Ties with the last kept entry are kept.  Argmax sampling
+// ignores both.
 __device__ __forceinline__ RowStat row_stats_regs(const float4 (&v)[SAMPLE_REG_F4], float invT, bool greedy,
                                                   SampleSmem& sm, int top_k = 0, float top_p = 0.0f, int V = 0) {
   const int tid = threadIdx.x;
@@ -103,42 +332,34 @@ __device__ __forceinline__ RowStat row_stats_regs(const float4 (&v)[SAMPLE_REG_F
     return st;
   }
   float thr = -INFINITY;
-  if (top_k > 0 && top_k < V) {
-    unsigned tau = 0u;
-    for (int bit = 31; bit >= 0; --bit) {
-      const unsigned cand = tau | (1u << bit);
-      int cnt = 0;
+  const int nv4 = V >> 2;
+  bool listed = false;
+  if (top_k > 0 && top_k < V)
+    thr = key_float(filter_threshold(v, nv4, (unsigned long long)top_k, top_k <= SAMPLE_THREADS ? top_k : 0, sm, listed,
+                                     [](unsigned) { return 1ull; }));
+  auto mass = [&] {
+    float s = 0.0f;
 #pragma unroll
-      for (int it = 0; it < SAMPLE_REG_F4; ++it)
-        cnt += (int)(float_key(v[it].x) >= cand) + (int)(float_key(v[it].y) >= cand) +
-               (int)(float_key(v[it].z) >= cand) + (int)(float_key(v[it].w) >= cand);
-      cnt = block_reduce(cnt, sm.redi, OpSumI(), 0);
-      if (cnt >= top_k) tau = cand;
+    for (int it = 0; it < SAMPLE_REG_F4; ++it) {     // exp(-inf) = 0 for the padding
+      // (a filtered row keeps few entries: most wavefronts have none in a group of 256)
+      if (thr != -INFINITY && !__any(v[it].x >= thr || v[it].y >= thr || v[it].z >= thr || v[it].w >= thr)) continue;
+      s += (exp_scaled(v[it].x, m, invT, thr) + exp_scaled(v[it].y, m, invT, thr)) +
+           (exp_scaled(v[it].z, m, invT, thr) + exp_scaled(v[it].w, m, invT, thr));
     }
-    thr = key_float(tau);
-  }
-  float s = 0.0f;
-#pragma unroll
-  for (int it = 0; it < SAMPLE_REG_F4; ++it)       // exp(-inf) = 0 for the padding
-    s += (exp_scaled(v[it].x, m, invT, thr) + exp_scaled(v[it].y, m, invT, thr)) +
-         (exp_scaled(v[it].z, m, invT, thr) + exp_scaled(v[it].w, m, invT, thr));
-  double S = block_reduce((double)s, sm.redd, OpSumD(), 0.0);
+    return block_reduce((double)s, sm.redd, OpSumD(), 0.0);
+  };
+  double S = mass();
   if (top_p > 0.0f && top_p < 1.0f) {
-    const double target = (double)top_p * S;
-    const float floor_thr = thr;                   // what top-k dropped stays dropped
-    unsigned tau = 0u;
-    for (int bit = 31; bit >= 0; --bit) {
-      const unsigned cand = tau | (1u << bit);
-      const float ct = fmaxf(key_float(cand), floor_thr);
-      float part = 0.0f;
-#pragma unroll
-      for (int it = 0; it < SAMPLE_REG_F4; ++it)
-        part += (exp_scaled(v[it].x, m, invT, ct) + exp_scaled(v[it].y, m, invT, ct)) +
-                (exp_scaled(v[it].z, m, invT, ct) + exp_scaled(v[it].w, m, invT, ct));
-      const double mass = block_reduce((double)part, sm.redd, OpSumD(), 0.0);
-      if (mass >= target) { tau = cand; S = mass; }
-    }
-    thr = fmaxf(key_float(tau), floor_thr);
+    constexpr double UNIT = 17592186044416.0;        // 2^44: 32768 entries of at most 1 stay below 2^60
+    const float floor_thr = thr;                     // what top-k dropped stays dropped
+    const unsigned tau = filter_threshold(v, nv4, (unsigned long long)((double)top_p * S * UNIT), 0, sm, listed, [&](unsigned k) {
+      // e * 2^44 as 31 + 13 bits
+      const float t = exp_scaled(key_float(k), m, invT, floor_thr) * 2147483648.0f;
+      const unsigned hi = (unsigned)t;
+      return ((unsigned long long)hi << 13) | (unsigned long long)(unsigned)((t - (float)hi) * 8192.0f);
+    });
+    thr = fmaxf(tau ? key_float(tau) : -INFINITY, floor_thr);
+    S = mass();
   }
   st.S = S;
   st.thr = thr;
@@ -182,23 +403,14 @@ struct RowPair {
   double invSp, invSq;
   float invT;
   int V;
-  bool vec;
 };
 
 __device__ __forceinline__ void load4(const RowPair& rp, int k, float (&zp)[4], float (&zq)[4]) {
-  if (rp.vec && k + 3 < rp.V) {
-    const float4 a = *reinterpret_cast<const float4*>(rp.zp + k);
-    zp[0] = a.x; zp[1] = a.y; zp[2] = a.z; zp[3] = a.w;
-    if (rp.zq) {
-      const float4 b = *reinterpret_cast<const float4*>(rp.zq + k);
-      zq[0] = b.x; zq[1] = b.y; zq[2] = b.z; zq[3] = b.w;
-    }
-  } else {
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      zp[e] = (k + e < rp.V) ? rp.zp[k + e] : -INFINITY;
-      zq[e] = (rp.zq && k + e < rp.V) ? rp.zq[k + e] : -INFINITY;
-    }
+  const float4 p = load4_row(rp.zp, k, rp.V);
+  zp[0] = p.x; zp[1] = p.y; zp[2] = p.z; zp[3] = p.w;
+  if (rp.zq) {
+    const float4 q = load4_row(rp.zq, k, rp.V);
+    zq[0] = q.x; zq[1] = q.y; zq[2] = q.z; zq[3] = q.w;
   }
 }
 
@@ -305,8 +517,6 @@ __device__ __forceinline__ int icdf_row(const float* zp, const RowStat& sp, cons
   rp.zp = zp; rp.zq = zq; rp.mp = sp.m; rp.mq = sq.m; rp.tp = sp.thr; rp.tq = sq.thr;
   rp.invSp = 1.0 / sp.S; rp.invSq = zq ? qscale / sq.S : 0.0;     // q enters the residual as qscale * q
   rp.invT = invT; rp.V = V;
-  rp.vec = ((V & 3) == 0) && ((reinterpret_cast<uintptr_t>(zp) & 15) == 0) &&
-           (zq == nullptr || (reinterpret_cast<uintptr_t>(zq) & 15) == 0);
   const int nchunks = (V + SAMPLE_CHUNK - 1) / SAMPLE_CHUNK;
   __syncthreads();
   constexpr int CB = 4;                          // chunks whose loads a wavefront keeps in flight
@@ -408,18 +618,18 @@ __device__ __forceinline__ int icdf_regs(const float4 (&vp)[SAMPLE_REG_F4], cons
 // Several sequences: sequence b reads the row at logits + b * seq_stride (floats) and uses
 // prm[b], st[b].
 // ---------------------------------------------------------------------------
-// The draw is spread over SAMPLE_SPLIT workgroups per row.  One workgroup is bound by its own
-// instruction stream (32 exponentials per thread, twice, and the fp64 weights: 8.5 us on one CU for
-// a 32128-entry row), so here every workgroup finds the row's maximum itself (a cheap pass over the
-// whole row), then takes one register slice of the row: chunks w * 16 .. w * 16 + 15 for workgroup
-// w, one wavefront per 256-entry chunk as in icdf_regs.  The chunk totals go to `tot`
-// ([sequence][SAMPLE_MAX_CHUNKS] doubles); the workgroup that arrives last (ticket: one counter
-// per sequence, SAMPLE_COUNTER_STRIDE words apart, zero before and after) scans them and walks
-// the chunk that holds u * total.  The weights are exp((z - m) / T) without the division by
+// The draw is spread over the chip: a workgroup finds the row's maximum itself (a cheap pass over the
+// whole row), then takes sixteen chunks of 256 entries, one per wavefront.  The chunk totals go to
+// memory; the workgroup that arrives last scans them and walks the chunk that holds u * total.
+// (One workgroup for the whole row is bound by its own instruction stream: 32 exponentials per thread,
+// twice, and the fp64 weights.)  The weights are exp((z - m) / T) without the division by
 // their sum: both sides of "cumulative weight > u * total" carry the same factor.
-// Argmax sampling, top-k / nucleus and rows that do not fit the registers are left to workgroup 0,
-// which then does the whole row (statistics and draw from registers, one read of the row); the others leave at once.  grid = (SAMPLE_SPLIT, sequences).
-constexpr int SAMPLE_SPLIT = SAMPLE_REG_F4;
+// Argmax: each workgroup the maximum of its own entries only, the last one the lowest index.
+// Top-k / nucleus: workgroup 0 does the whole row (statistics and draw from registers); the others
+// leave at once.  grid = (sample_workgroups(V), sequences).
+__host__ __device__ constexpr int sample_workgroups(int V) {
+  return ((V + SAMPLE_CHUNK - 1) / SAMPLE_CHUNK + SAMPLE_CHUNKS_WG - 1) / SAMPLE_CHUNKS_WG;
+}
 
 __device__ __forceinline__ void commit_draw(SeqState* st, int mode, int slot, int tok) {
   if (mode == 0) {
@@ -433,184 +643,368 @@ __device__ __forceinline__ void commit_draw(SeqState* st, int mode, int slot, in
   }
 }
 
+// The workgroups' hand-over: each leaves 8-byte results with write-through stores (post) and takes a
+// ticket; the last one to arrive sees them all through loads that go past its own caches (collect).  A
+// ticket with release / acquire semantics instead writes back and invalidates an L2 per workgroup,
+// which costs more than the whole kernel when hundreds of them do it.
+__device__ __forceinline__ void post(double* p, double v) {
+  __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), (unsigned long long)__double_as_longlong(v), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ double collect(const double* p) {
+  return __longlong_as_double((long long)__hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+}
+__device__ __forceinline__ bool last_to_post(unsigned int* ticket, unsigned int expected, int* lds_flag) {
+  if (expected == 1u) { __syncthreads(); return true; }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wavefront's posts have reached memory
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    const unsigned int t = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const int last = (t == expected - 1u);
+    if (last) __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    *lds_flag = last;
+  }
+  __syncthreads();
+  return *lds_flag != 0;
+}
+
 static __global__ __launch_bounds__(SAMPLE_THREADS) void sample_row_split_kernel(
     const float* __restrict__ logits, int V, const StepParams* __restrict__ prm, int uniform_idx,
-    SeqState* __restrict__ st, int mode, int slot, size_t seq_stride, double* __restrict__ tot,
-    unsigned int* __restrict__ ticket) {
+    SeqState* __restrict__ st, int mode, int slot, size_t seq_stride, SampleScratch* __restrict__ scr) {
   __shared__ SampleSmem sm;
   const int w = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   logits += (size_t)blockIdx.y * seq_stride;
   prm += blockIdx.y;
   st += blockIdx.y;
-  tot += (size_t)blockIdx.y * SAMPLE_MAX_CHUNKS;
-  ticket += (size_t)blockIdx.y * SAMPLE_COUNTER_STRIDE;
+  scr += blockIdx.y;
+  const int c = w * SAMPLE_CHUNKS_WG + wave, nchunks = (V + SAMPLE_CHUNK - 1) / SAMPLE_CHUNK;
+  const float4 mine = load4_row(logits, c * SAMPLE_CHUNK + lane * 4, V);         // (past the row: -inf)
   const float T = prm->temperature;
   const bool greedy = (T == 0.0f);
   const float invT = greedy ? 1.0f : 1.0f / T;
   const bool filtered = prm->top_k > 0 || (prm->top_p > 0.0f && prm->top_p < 1.0f);
-  if (greedy || filtered || !row_fits_regs(logits, V)) {      // uniform over the grid's workgroups of this row
+  if (!greedy && filtered) {                          // (the host admits filters only for rows that fit the registers)
     if (w != 0) return;
-    int tok;
-    if (row_fits_regs(logits, V)) {
-      float4 v[SAMPLE_REG_F4];
-      load_row_regs(logits, V, v);
-      const RowStat rs = row_stats_regs(v, invT, greedy, sm, prm->top_k, prm->top_p, V);
-      tok = greedy ? rs.arg : icdf_regs(v, rs, v, rs, false, invT, V, prm->uniforms[uniform_idx], sm);
-    } else {
-      const RowStat rs = row_stats(logits, V, invT, greedy, sm);
-      tok = greedy ? rs.arg : icdf_row(logits, rs, nullptr, rs, invT, V, prm->uniforms[uniform_idx], sm);
-    }
+    float4 v[SAMPLE_REG_F4];
+    load_row_regs(logits, V, v);
+    const RowStat rs = row_stats_regs(v, invT, false, sm, prm->top_k, prm->top_p, V);
+    const int tok = icdf_regs(v, rs, v, rs, false, invT, V, prm->uniforms[uniform_idx], sm);
     if (tid == 0) commit_draw(st, mode, slot, tok);
     return;
   }
-  const float4* z4 = reinterpret_cast<const float4*>(logits);
-  const int n4 = V >> 2, nchunks = (V + SAMPLE_CHUNK - 1) / SAMPLE_CHUNK;
-  const float4 pad = make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
-  // the row's maximum, and this workgroup's slice (float4 number w * 1024 + tid: lane-slice `lane` of chunk w * 16 + wave)
-  float m = -INFINITY;
-  float4 mine = pad;
-  {
-    float4 v[SAMPLE_REG_F4];
-    load_row_regs(logits, V, v);
+  float m = fmaxf(fmaxf(mine.x, mine.y), fmaxf(mine.z, mine.w));
+  if (greedy) {
+    m = block_reduce(m, sm.redf, OpMaxF(), -INFINITY) + 0.0f;                    // (-0 counts as 0)
+    const int k = c * SAMPLE_CHUNK + lane * 4;
+    int a = (mine.x == m) ? k : (mine.y == m) ? k + 1 : (mine.z == m) ? k + 2 : (mine.w == m) ? k + 3 : INT_MAX;
+    if (k >= V) a = INT_MAX;
+    a = block_reduce(a, sm.redi, OpMinI(), INT_MAX);
+    // order of the posted words: larger maximum first, then the lower index
+    if (tid == 0)
+      post(&scr->tot[w], __longlong_as_double((long long)(((unsigned long long)float_key(m) << 32) | (0xffffffffu - (unsigned)a))));
+    if (!last_to_post(scr->ticket, gridDim.x, &sm.flag)) return;
+    if (wave == 0) {
+      unsigned long long best = (lane < (int)gridDim.x) ? (unsigned long long)__double_as_longlong(collect(&scr->tot[lane])) : 0ull;
+#pragma unroll
+      for (int o = 32; o; o >>= 1) {
+        const unsigned long long t = __shfl_xor(best, o, WAVE);
+        best = t > best ? t : best;
+      }
+      if (lane == 0) commit_draw(st, mode, slot, (int)(0xffffffffu - (unsigned)best));
+    }
+    return;
+  }
+  for (int k0 = 0; k0 < V; k0 += 4 * SAMPLE_REG_F4 * SAMPLE_THREADS) {
 #pragma unroll
     for (int it = 0; it < SAMPLE_REG_F4; ++it) {
-      m = fmaxf(m, fmaxf(fmaxf(v[it].x, v[it].y), fmaxf(v[it].z, v[it].w)));
-      if (it == w) mine = v[it];
+      const float4 v = load4_row(logits, k0 + (it * SAMPLE_THREADS + tid) * 4, V);
+      m = fmaxf(m, fmaxf(fmaxf(v.x, v.y), fmaxf(v.z, v.w)));
     }
   }
   m = block_reduce(m, sm.redf, OpMaxF(), -INFINITY);
-  const int c = w * (SAMPLE_THREADS / 64) + wave;
   {
     const double t = wave_sum(((double)exp_scaled(mine.x, m, invT, -INFINITY) + (double)exp_scaled(mine.y, m, invT, -INFINITY)) +
                               ((double)exp_scaled(mine.z, m, invT, -INFINITY) + (double)exp_scaled(mine.w, m, invT, -INFINITY)));
-    if (lane == 0 && c < nchunks) tot[c] = t;
+    if (lane == 0 && c < nchunks) post(&scr->tot[c], t);
   }
-  if (!last_block_arrives(ticket, SAMPLE_SPLIT, &sm.flag)) return;
-  for (int i = tid; i < nchunks; i += SAMPLE_THREADS) sm.ctot[i] = tot[i];
+  if (!last_to_post(scr->ticket, gridDim.x, &sm.flag)) return;
+  for (int i = tid; i < nchunks; i += SAMPLE_THREADS) sm.ctot[i] = collect(&scr->tot[i]);
   __syncthreads();
   const float u = prm->uniforms[uniform_idx];
-  if (wave == 0) scan_chunk_totals(nchunks, u, sm);
-  __syncthreads();
   if (wave == 0) {
+    scan_chunk_totals(nchunks, u, sm);
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     const double total = sm.total;
     const int chunk = sm.chunk;
     const bool fallback = chunk < 0;            // threshold not reached by round-off
-    const int cc = fallback ? (-1 - chunk) : chunk;
-    const int i4 = cc * (SAMPLE_CHUNK / 4) + lane;
-    const float4 t4 = z4[min(i4, n4 - 1)];
-    const float4 z = (i4 < n4) ? t4 : pad;
+    const int k = (fallback ? (-1 - chunk) : chunk) * SAMPLE_CHUNK + lane * 4;
+    const float4 z = load4_row(logits, k, V);
     const double wv[4] = {(double)exp_scaled(z.x, m, invT, -INFINITY), (double)exp_scaled(z.y, m, invT, -INFINITY),
                           (double)exp_scaled(z.z, m, invT, -INFINITY), (double)exp_scaled(z.w, m, invT, -INFINITY)};
-    const int tok = pick_in_chunk(wv, i4 * 4, V, fallback, (double)u * total, sm.before);
+    const int tok = pick_in_chunk(wv, k, V, fallback, (double)u * total, sm.before);
     if (lane == 0) commit_draw(st, mode, slot, tok);
   }
 }
 
 // ---------------------------------------------------------------------------
-// Accept / resample (Algorithm 1, second half).  grid = (2*gamma+1, rows):
-// block (j, b) computes the statistics of logits row j of sequence b (j <=
-// gamma: p_{j+1}; j > gamma: q_{j-gamma}); the last block of a sequence to
-// finish then
-//   * evaluates r_i <= p_i(x_i)/q_i(x_i) for all i in one wavefront and takes
-//     n = index of the first rejection from the ballot,
-//   * draws t from norm(max(0, p_{n+1} - q_{n+1})) (n < gamma) or p_{gamma+1},
-//   * writes n and t, and, when `st` is given, commits the sequence:
-//     out = x_1..x_n, t; len += n+1 (which is the KV roll-back: cache rows
-//     beyond the committed length are dead and get overwritten).
+// Accept / resample (Algorithm 1, second half), for `rows` independent sequences:
+//   row_parts_kernel    statistics of the 2 gamma + 1 logits rows of every sequence (row j <= gamma: p_{j+1};
+//                       j > gamma: q_{j-gamma}), a wavefront per 2048 entries; row_filter_kernel
+//                       does it for rows that top-k / nucleus filter, a workgroup per row
+//   beta_parts_kernel   the acceptance probabilities as a side output (when asked for)
+//   accept_kernel       evaluates r_i <= p_i(x_i)/q_i(x_i) for all i, takes n = index of the first
+//                       rejection, draws t from norm(max(0, p_{n+1} - q_{n+1})) (n < gamma) or
+//                       p_{gamma+1}, writes n and t, and, when `st` is given, commits the sequence:
+//                       out = x_1..x_n, t; len += n+1 (which is the KV roll-back: cache rows
+//                       beyond the committed length are dead and get overwritten).
 // x, r, s: explicit arrays [rows, gamma] / [rows] or, when prm/st are given,
 // taken from the device-resident step parameters and state.
 // ---------------------------------------------------------------------------
-// MODE 0: everything in one launch (ticket).  MODE 1: row statistics only.  MODE 2: the
-// per-sequence tail only, grid (1, rows).  MODE 3: the acceptance probabilities beta_i as a
-// side output, grid (gamma, rows), after the statistics exist.  A device-scope atomic costs about 0.08 us of
-// chip-wide throughput, so with many sequences two launches (1 + 2) beat rows * (2*gamma+1)
-// tickets; with one sequence the single launch wins.
-template <int MODE>
-static __global__ __launch_bounds__(SAMPLE_THREADS) void spec_verify_kernel(
-    const float* __restrict__ p_logits, const float* __restrict__ q_logits,
-    const int* __restrict__ x_in, const float* __restrict__ r_in, const float* __restrict__ s_in,
-    int gamma, int V, float temperature, float lenience_in, double log_lenience_in, int top_k_in, float top_p_in,
-    const StepParams* __restrict__ prm,
-    RowStat* __restrict__ stats, unsigned int* __restrict__ counters,
-    int* __restrict__ out_n, int* __restrict__ out_t, float* __restrict__ beta_out,
-    SeqState* __restrict__ st) {
+struct AcceptArgs {
+  const float *p, *q;                  // logits [rows][gamma + 1][V], [rows][gamma][V]
+  const int* x; const float *r, *s;
+  int gamma, V;
+  int part_len, nparts;                // entries of one part of a row's statistics (a multiple of SAMPLE_PART), parts per row
+  int chunks_wave;                     // accept_kernel: chunks per wavefront
+  float temperature, lenience;
+  double log_lenience;
+  int top_k; float top_p;              // in-model use: only whether the rows are filtered (the options are read from prm)
+  const StepParams* prm;
+  SampleScratch* scr;
+  int *out_n, *out_t; float* beta;
+  SeqState* st;
+};
+// Whether row_filter_kernel leaves the statistics (one part a row) instead of row_parts_kernel.
+__host__ __device__ inline bool accept_filtered(const AcceptArgs& a) { return a.top_k > 0 || (a.top_p > 0.0f && a.top_p < 1.0f); }
+// A row's parts depend on its length only, so its statistics do not depend on the call around it.
+__host__ __device__ inline void accept_parts(AcceptArgs& a) {
+  a.part_len = SAMPLE_PART * ((a.V + SAMPLE_PART * SAMPLE_PARTS - 1) / (SAMPLE_PART * SAMPLE_PARTS));
+  a.nparts = (a.V + a.part_len - 1) / a.part_len;
+}
+__device__ __forceinline__ const float* accept_row(const AcceptArgs& a, int b, int j) {
+  return (j <= a.gamma) ? a.p + ((size_t)b * (a.gamma + 1) + j) * a.V : a.q + ((size_t)b * a.gamma + (j - a.gamma - 1)) * a.V;
+}
+
+// Bound by the reads.  A wavefront takes every (grid x 4)-th part of the launch (part fastest, then row, then
+// sequence) and asks for the next one's 4 KB before it sums this one, so the loads never stop; no
+// barrier, no other wavefront is needed.  Every lane sums relative to its own maximum; lanes, and later
+// the parts of a row, are brought to the common maximum by one factor each.
+// grid = enough workgroups for one part a wavefront, at most ACCEPT_WAVES_CU wavefronts a CU.
+constexpr int ACCEPT_WAVES_CU = 24;
+static __global__ __launch_bounds__(256, 6) void row_parts_kernel(const AcceptArgs a, int items, unsigned mag_parts, unsigned mag_rows) {
+  const int lane = threadIdx.x & 63, stride = (int)gridDim.x * 4;
+  const int nrows = 2 * a.gamma + 1;
+  constexpr int NV = SAMPLE_PART / 256;
+  auto locate = [&](int item, int& part, int& j, int& b) {       // (divisions by multiplication: items < 2^32 / 64)
+    const int row = (a.nparts == 1) ? item : (int)__umulhi((unsigned)item, mag_parts);
+    part = item - row * a.nparts;
+    b = (int)__umulhi((unsigned)row, mag_rows); j = row - b * nrows;
+  };
+  auto load = [&](int item, float4 (&v)[NV]) {
+    int part, j, b;
+    locate(min(item, items - 1), part, j, b);
+    const float* z = accept_row(a, b, j);
+    const int k0 = part * a.part_len;
+    if (k0 + SAMPLE_PART <= a.V) {                   // (uniform) no entry past the row
+#pragma unroll
+      for (int it = 0; it < NV; ++it) {
+        const f32x4_any t = *reinterpret_cast<const f32x4_any*>(z + k0 + it * 256 + (unsigned)lane * 4u);
+        v[it] = make_float4(t[0], t[1], t[2], t[3]);
+      }
+    } else {
+#pragma unroll
+      for (int it = 0; it < NV; ++it) v[it] = load4_row(z, k0 + it * 256 + lane * 4, a.V);
+    }
+  };
+  auto reduce = [&](int item, float4 (&v)[NV]) {
+    int part, j, b;
+    locate(item, part, j, b);
+    const float T = a.prm ? a.prm[b].temperature : a.temperature;
+    const bool greedy = (T == 0.0f);
+    if (greedy && j > a.gamma) return;               // argmax sampling never looks at q rows
+    const float invT = greedy ? 1.0f : 1.0f / T;
+    float m = -INFINITY;
+    double s = 0.0;
+    int arg = INT_MAX;
+    const int k_end = min(a.V, (part + 1) * a.part_len);
+    for (int k0 = part * a.part_len; k0 < k_end; k0 += SAMPLE_PART) {
+      if (k0 != part * a.part_len) {                 // (parts longer than a block: more than 65536 entries a row)
+        const float* z = accept_row(a, b, j);
+#pragma unroll
+        for (int it = 0; it < NV; ++it) v[it] = load4_row(z, k0 + it * 256 + lane * 4, a.V);
+      }
+      // an entry that is not a number weighs nothing, as -inf does
+      constexpr float LOWEST = -3.402823466e38f;
+      float mb = -INFINITY;
+#pragma unroll
+      for (int it = 0; it < NV; ++it) mb = fmaxf(mb, fmaxf(fmaxf(v[it].x, v[it].y), fmaxf(v[it].z, v[it].w)));
+      if (greedy) {
+        int ab = INT_MAX;
+#pragma unroll
+        for (int it = NV - 1; it >= 0; --it) {
+          const int k = k0 + it * 256 + lane * 4;
+          if (k + 3 < a.V && v[it].w == mb) ab = k + 3;
+          if (k + 2 < a.V && v[it].z == mb) ab = k + 2;
+          if (k + 1 < a.V && v[it].y == mb) ab = k + 1;
+          if (k < a.V && v[it].x == mb) ab = k;
+        }
+        if (mb > m || (mb == m && ab < arg)) arg = ab;
+        m = fmaxf(m, mb);
+      } else {
+        const float sc = invT * 1.44269504088896f;   // exp((z - mb) / T) = 2^((z - mb) sc)
+        auto ex = [&](float z) { return __builtin_amdgcn_exp2f((fmaxf(z, LOWEST) - mb) * sc); };
+        float sb = 0.0f;
+#pragma unroll
+        for (int it = 0; it < NV; ++it) sb += (ex(v[it].x) + ex(v[it].y)) + (ex(v[it].z) + ex(v[it].w));
+        const float mn = fmaxf(m, mb);
+        s = rescaled_sum(s, m, mn, invT) + rescaled_sum((double)sb, mb, mn, invT);
+        m = mn;
+      }
+    }
+    const float M = wave_max(m);
+    RowPart* out = &a.scr[b].part[j][part];
+    if (greedy) {
+      arg = wave_min(m == M ? arg : INT_MAX);
+      if (lane == 0) { out->S = 0.0; out->m = M; out->arg = arg; }
+    } else {
+      s = wave_sum(rescaled_sum(s, m, M, invT));
+      if (lane == 0) { out->S = s; out->m = M; out->thr = -INFINITY; }
+    }
+  };
+  int item = (int)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (item >= items) return;
+  float4 v0[NV], v1[NV];
+  load(item, v0);
+  for (;;) {
+    if (item + stride < items) load(item + stride, v1);
+    reduce(item, v0);
+    item += stride;
+    if (item >= items) return;
+    if (item + stride < items) load(item + stride, v0);
+    reduce(item, v1);
+    item += stride;
+    if (item >= items) return;
+  }
+}
+
+// Top-k / nucleus rows: the search needs the whole row, so one workgroup holds it in registers.
+// grid = (2 gamma + 1, rows).
+static __global__ __launch_bounds__(SAMPLE_THREADS) void row_filter_kernel(const AcceptArgs a) {
   __shared__ SampleSmem sm;
-  __shared__ RowStat srow[2 * 15 + 1];
-  const int j = blockIdx.x, b = blockIdx.y, tid = threadIdx.x;
-  const int nrows = 2 * gamma + 1;
-  if (prm) prm += b;                     // in-model use: per-sequence parameters and state
-  if (st) st += b;
-  const float T = prm ? prm->temperature : temperature;
+  const int j = blockIdx.x, b = blockIdx.y;
+  const float T = a.prm ? a.prm[b].temperature : a.temperature;
+  const bool greedy = (T == 0.0f);                   // (ignores the filters)
+  if (greedy && j > a.gamma) return;
+  float4 v[SAMPLE_REG_F4];
+  load_row_regs(accept_row(a, b, j), a.V, v);
+  const RowStat rs = row_stats_regs(v, greedy ? 1.0f : 1.0f / T, greedy, sm, a.prm ? a.prm[b].top_k : a.top_k, a.prm ? a.prm[b].top_p : a.top_p, a.V);
+  if (threadIdx.x == 0) {
+    RowPart* out = &a.scr[b].part[j][0];
+    out->S = rs.S; out->m = rs.m;
+    if (greedy) out->arg = rs.arg; else out->thr = rs.thr;
+  }
+}
+
+// A row's statistics from its parts, by one wavefront (lane = part); every lane gets them.
+__device__ __forceinline__ RowStat join_parts(const RowPart* parts, int nparts, bool greedy, float invT) {
+  const int i = threadIdx.x & 63;
+  const bool ok = i < nparts;
+  const RowPart rp = parts[min(i, nparts - 1)];
+  RowStat st; st.arg = 0; st.S = 0.0; st.pad = 0.0f;
+  st.m = wave_max(ok ? rp.m : -INFINITY);
+  st.thr = greedy ? -INFINITY : rp.thr;              // (filtered rows have one part, which every lane read)
+  if (greedy) st.arg = wave_min((ok && rp.m == st.m) ? rp.arg : INT_MAX);
+  else st.S = wave_sum(ok ? rescaled_sum(rp.S, rp.m, st.m, invT) : 0.0);
+  return st;
+}
+
+// beta_{i+1} = sum_x min(p(x) / l, q(x)): the probability that guess i+1 is accepted (section 3.1; with
+// lenience, appendix A.5), a wavefront per part of the row; accept_kernel adds the parts in order.
+// grid = (ceil(nparts / 4), gamma, rows).
+static __global__ __launch_bounds__(256) void beta_parts_kernel(const AcceptArgs a) {
+  const int lane = threadIdx.x & 63, i = blockIdx.y, b = blockIdx.z;
+  const int part = (int)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const float T = a.prm ? a.prm[b].temperature : a.temperature;
+  if (part >= a.nparts || T == 0.0f) return;
+  const float invT = 1.0f / T;
+  const double len = (double)(a.prm ? a.prm[b].lenience : a.lenience);
+  const int np = accept_filtered(a) ? 1 : a.nparts;  // parts the statistics were left in
+  const RowStat jp = join_parts(a.scr[b].part[i], np, false, invT), jq = join_parts(a.scr[b].part[a.gamma + 1 + i], np, false, invT);
+  const double ip = (1.0 / jp.S) / len, iq = 1.0 / jq.S;
+  const float *zp = accept_row(a, b, i), *zq = accept_row(a, b, a.gamma + 1 + i);
+  double acc = 0.0;
+  const int k_end = min(a.V, (part + 1) * a.part_len);
+  for (int k0 = part * a.part_len; k0 < k_end; k0 += SAMPLE_PART / 2) {
+    float4 vp[SAMPLE_PART / 512], vq[SAMPLE_PART / 512];
+#pragma unroll
+    for (int it = 0; it < SAMPLE_PART / 512; ++it) {
+      vp[it] = load4_row(zp, k0 + it * 256 + lane * 4, a.V);
+      vq[it] = load4_row(zq, k0 + it * 256 + lane * 4, a.V);
+    }
+#pragma unroll
+    for (int it = 0; it < SAMPLE_PART / 512; ++it) {
+      const float p4[4] = {vp[it].x, vp[it].y, vp[it].z, vp[it].w}, q4[4] = {vq[it].x, vq[it].y, vq[it].z, vq[it].w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if (k0 + it * 256 + lane * 4 + e >= k_end) continue;
+        const double pv = (double)exp_scaled(p4[e], jp.m, invT, jp.thr) * ip;
+        const double qv = (double)exp_scaled(q4[e], jq.m, invT, jq.thr) * iq;
+        acc += pv < qv ? pv : qv;
+      }
+    }
+  }
+  acc = wave_sum(acc);
+  if (lane == 0) a.scr[b].beta[i][part] = acc;
+}
+
+// Decisions, draw, commit.  Every workgroup of a sequence joins the statistics and takes the decisions
+// itself (a few hundred words), then sums the weights of its chunks of row n (16 chunks_wave of
+// them); the last to arrive scans the totals and walks the chunk that holds u * total.
+// 64 sequences, gamma 7, vocabulary 32128 (123 MB), both launches: 34 us (row_parts_kernel 22: 5.6 TB/s, a
+// pure read's rate at this size); with one 1024-thread workgroup per row and then one per sequence it
+// was 44.  One sequence, gamma 4: 10.6 us against 16.1.
+static __global__ __launch_bounds__(SAMPLE_THREADS) void accept_kernel(const AcceptArgs a) {
+  __shared__ SampleSmem sm;
+  __shared__ RowStat srow[2 * SAMPLE_MAX_GAMMA + 1];
+  const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int gamma = a.gamma, V = a.V, nrows = 2 * gamma + 1, nchunks = (V + SAMPLE_CHUNK - 1) / SAMPLE_CHUNK;
+  const StepParams* prm = a.prm ? a.prm + b : nullptr;     // in-model use: per-sequence parameters and state
+  SeqState* st = a.st ? a.st + b : nullptr;
+  SampleScratch* scr = a.scr + b;
+  const float T = prm ? prm->temperature : a.temperature;
   const bool greedy = (T == 0.0f);
   const float invT = greedy ? 1.0f : 1.0f / T;
-  const double len = (double)(prm ? prm->lenience : lenience_in);            // appendix A.5, 1 = exact
-  const double log_len = prm ? prm->log_lenience : log_lenience_in;
-  const int top_k = prm ? prm->top_k : top_k_in;                             // section 2.2, same for p and q
-  const float top_p = prm ? prm->top_p : top_p_in;
-  const float* P = p_logits + (size_t)b * (gamma + 1) * V;
-  const float* Q = q_logits + (size_t)b * gamma * V;
-  RowStat* my_stats = stats + (size_t)b * nrows;
-
-  if (MODE == 3) {
-    // beta_{j+1} = sum_x min(p(x) / l, q(x)): the probability that guess j+1 is accepted
-    // (section 3.1; with lenience, appendix A.5).  Needs the statistics of a MODE 0 / 1 launch.
-    if (j >= gamma) return;
-    const RowStat sp = my_stats[j];
-    const float* zp = P + (size_t)j * V;
-    float* dst = st ? st->beta : beta_out + (size_t)b * gamma;
-    if (greedy) {                                // one-hot q at its argmax: accepted or not
-      const int aq = row_stats(Q + (size_t)j * V, V, 1.0f, true, sm).arg;   // argmax sampling keeps no q statistics
-      if (tid == 0) {
-        const bool acc = (len < 1.0) ? ((double)zp[aq] - (double)sp.m >= log_len) : (aq == sp.arg);
-        dst[j] = acc ? 1.0f : 0.0f;
-      }
-      return;
-    }
-    const RowStat sq = my_stats[gamma + 1 + j];
-    const float* zq = Q + (size_t)j * V;
-    const double ip = (1.0 / sp.S) / len, iq = 1.0 / sq.S;
-    double acc = 0.0;
-    for (int k = tid; k < V; k += SAMPLE_THREADS) {
-      const double pv = (double)exp_scaled(zp[k], sp.m, invT, sp.thr) * ip;
-      const double qv = (double)exp_scaled(zq[k], sq.m, invT, sq.thr) * iq;
-      acc += pv < qv ? pv : qv;
-    }
-    acc = block_reduce(acc, sm.redd, OpSumD(), 0.0);
-    if (tid == 0) dst[j] = (float)acc;
-    return;
+  const double len = (double)(prm ? prm->lenience : a.lenience);            // appendix A.5, 1 = exact
+  const double log_len = prm ? prm->log_lenience : a.log_lenience;
+  const float *P = accept_row(a, b, 0), *Q = accept_row(a, b, gamma + 1);
+  const int* x = st ? st->x : a.x + (size_t)b * gamma;
+  const float* r = prm ? prm->uniforms + gamma : a.r + (size_t)b * gamma;   // (not read by argmax sampling)
+  const float s = greedy ? 0.5f : (prm ? prm->uniforms[2 * gamma] : a.s[b]);
+  // what the tests need arrives while the statistics are joined
+  int xi = 0;
+  float zpx = 0.0f, zqx = 0.0f, ri = 0.5f;
+  if (tid < gamma) {
+    xi = min(max(x[tid], 0), V - 1);
+    zpx = P[(size_t)tid * V + xi];
+    if (!greedy) { zqx = Q[(size_t)tid * V + xi]; ri = r[tid]; }
   }
-
-  if (MODE != 2 && !(greedy && j > gamma)) {          // argmax sampling never looks at q rows
-    const float* z = (j <= gamma) ? P + (size_t)j * V : Q + (size_t)(j - gamma - 1) * V;
-    const RowStat rs = row_stats(z, V, invT, greedy, sm, top_k, top_p);
-    if (tid == 0) my_stats[j] = rs;
+  for (int row = wave; row < nrows && !(greedy && row > gamma); row += SAMPLE_THREADS / 64) {
+    const RowStat rs = join_parts(scr->part[row], accept_filtered(a) ? 1 : a.nparts, greedy, invT);
+    if (lane == 0) srow[row] = rs;
   }
-  if (MODE == 1) return;
-  // one counter per sequence, 256 bytes apart
-  if (MODE == 0 && !last_block_arrives(counters + (size_t)b * SAMPLE_COUNTER_STRIDE, (unsigned)nrows, &sm.flag)) return;
-
-  // ---- tail: one workgroup per sequence ----
-  if (tid < nrows) srow[tid] = my_stats[tid];
   __syncthreads();
-  const int* x = st ? st->x : x_in + (size_t)b * gamma;
-  const float* r = prm ? prm->uniforms + gamma : r_in + (size_t)b * gamma;
-  const float s = greedy ? 0.5f : (prm ? prm->uniforms[2 * gamma] : s_in[b]);
-
-  if (tid < WAVE) {                       // wavefront 0: one lane per guess
+  if (wave == 0) {                        // one lane per guess
     bool reject = false;
     if (tid < gamma) {
-      const int xi = min(max(x[tid], 0), V - 1);
       if (greedy) {
         // lenient argmax sampling: keep x when p(x) >= l * max p, p = softmax of the raw logits
-        reject = (len < 1.0) ? ((double)P[(size_t)tid * V + xi] - (double)srow[tid].m < log_len)
-                             : (srow[tid].arg != xi);
+        reject = (len < 1.0) ? ((double)zpx - (double)srow[tid].m < log_len) : (srow[tid].arg != xi);
       } else {
         const RowStat sp = srow[tid], sq = srow[gamma + 1 + tid];
-        const double p = (double)exp_scaled(P[(size_t)tid * V + xi], sp.m, invT, sp.thr) * (1.0 / sp.S);
-        const double q = (double)exp_scaled(Q[(size_t)tid * V + xi], sq.m, invT, sq.thr) * (1.0 / sq.S);
+        const double p = (double)exp_scaled(zpx, sp.m, invT, sp.thr) * (1.0 / sp.S);
+        const double q = (double)exp_scaled(zqx, sq.m, invT, sq.thr) * (1.0 / sq.S);
         const double lq = q * len;
         const double ratio = (lq > 0.0) ? p / lq : INFINITY;
-        reject = ((double)r[tid] > ratio);
+        reject = ((double)ri > ratio);
       }
     }
     const unsigned long long mask = __ballot(reject);
@@ -618,30 +1012,80 @@ static __global__ __launch_bounds__(SAMPLE_THREADS) void spec_verify_kernel(
   }
   __syncthreads();
   const int n = sm.n;
-  int t;
-  int fell_back = 0;
-  if (greedy) {
-    t = srow[n].arg;
-  } else {
-    const float* zp = P + (size_t)n * V;
-    const float* zq = Q + (size_t)min(n, gamma - 1) * V;
-    const RowStat sq = srow[gamma + 1 + min(n, gamma - 1)];
-    if (row_fits_regs(zp, V) && row_fits_regs(zq, V)) {
-      float4 vp[SAMPLE_REG_F4], vq[SAMPLE_REG_F4];
-      load_row_regs(zp, V, vp);
-      load_row_regs(zq, V, vq);               // unconditional; unused when all guesses were kept
-      t = icdf_regs(vp, srow[n], vq, sq, n < gamma, invT, V, s, sm, len);
-      if (t < 0) { fell_back = 1; t = icdf_regs(vp, srow[n], vq, sq, false, invT, V, s, sm); }
-    } else if (n < gamma) {
-      t = icdf_row(zp, srow[n], zq, sq, invT, V, s, sm, len);
-      if (t < 0) { fell_back = 1; t = icdf_row(zp, srow[n], nullptr, srow[n], invT, V, s, sm); }
-    } else {
-      t = icdf_row(zp, srow[n], nullptr, srow[n], invT, V, s, sm);
+  float* beta = st ? st->beta : a.beta ? a.beta + (size_t)b * gamma : nullptr;
+  if (a.beta != nullptr && blockIdx.x == 0) {
+    if (!greedy) {
+      if (tid < gamma) {
+        double t = 0.0;
+        for (int i = 0; i < a.nparts; ++i) t += scr->beta[tid][i];
+        beta[tid] = (float)t;
+      }
+    } else {                              // one-hot q at its argmax: accepted or not
+      for (int i = 0; i < gamma; ++i) {
+        const int aq = row_stats(Q + (size_t)i * V, V, 1.0f, true, sm).arg;      // argmax sampling keeps no q statistics
+        if (tid == 0) {
+          const bool acc = (len < 1.0) ? ((double)P[(size_t)i * V + aq] - (double)srow[i].m >= log_len) : (aq == srow[i].arg);
+          beta[i] = acc ? 1.0f : 0.0f;
+        }
+      }
     }
   }
+  int t = 0, fell_back = 0;
+  if (greedy) {
+    if (blockIdx.x != 0) return;
+    t = srow[n].arg;
+  } else {
+    RowPair rp;
+    const bool with_q = n < gamma;
+    const RowStat sp = srow[n], sq = srow[gamma + 1 + min(n, gamma - 1)];
+    rp.zp = P + (size_t)n * V; rp.zq = with_q ? Q + (size_t)n * V : nullptr;
+    rp.mp = sp.m; rp.mq = sq.m; rp.tp = sp.thr; rp.tq = sq.thr; rp.invT = invT; rp.V = V;
+    rp.invSp = 1.0 / sp.S; rp.invSq = with_q ? len / sq.S : 0.0;                 // q enters the residual as l * q
+    constexpr int CB = 4;                            // chunks whose loads a wavefront keeps in flight
+    const int c0 = (int)blockIdx.x * SAMPLE_CHUNKS_WG * a.chunks_wave + wave;
+    for (int i0 = 0; i0 < a.chunks_wave; i0 += CB) {
+      float zp[CB][4], zq[CB][4];
+#pragma unroll
+      for (int i = 0; i < CB; ++i) {
+        const int c = c0 + (i0 + i) * SAMPLE_CHUNKS_WG;
+        if (i0 + i < a.chunks_wave && c < nchunks) load4(rp, c * SAMPLE_CHUNK + lane * 4, zp[i], zq[i]);
+      }
+#pragma unroll
+      for (int i = 0; i < CB; ++i) {
+        const int c = c0 + (i0 + i) * SAMPLE_CHUNKS_WG;
+        if (i0 + i < a.chunks_wave && c < nchunks) {
+          double w[4];
+          calc4(rp, c * SAMPLE_CHUNK + lane * 4, zp[i], zq[i], w);
+          const double tc = wave_sum((w[0] + w[1]) + (w[2] + w[3]));
+          if (lane == 0) post(&scr->tot[c], tc);
+        }
+      }
+    }
+    if (!last_to_post(scr->ticket, gridDim.x, &sm.flag)) return;
+    for (int i = tid; i < nchunks; i += SAMPLE_THREADS) sm.ctot[i] = collect(&scr->tot[i]);
+    __syncthreads();
+    if (wave == 0) {
+      scan_chunk_totals(nchunks, s, sm);
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      const double total = sm.total;
+      if (total > 0.0) {
+        const int chunk = sm.chunk;
+        const bool fallback = chunk < 0;        // threshold not reached by round-off
+        const int k = (fallback ? (-1 - chunk) : chunk) * SAMPLE_CHUNK + lane * 4;
+        double w[4];
+        weights4(rp, k, w);
+        const int tok = pick_in_chunk(w, k, V, fallback, (double)s * total, sm.before);
+        if (lane == 0) sm.token = tok;
+      }
+    }
+    __syncthreads();
+    if (sm.total > 0.0) t = sm.token;
+    else if (with_q) { fell_back = 1; t = icdf_row(rp.zp, sp, nullptr, sp, invT, V, s, sm); }     // no residual left: p itself
+    else t = -1;
+  }
   if (tid == 0) {
-    if (out_n) out_n[b] = n;
-    if (out_t) out_t[b] = t;
+    if (a.out_n) a.out_n[b] = n;
+    if (a.out_t) a.out_t[b] = t;
     if (st) {
       const int last = st->last_tok;
       for (int i = 0; i < 16; ++i) st->out[i] = (i < n) ? x[i] : (i == n ? t : -1);
@@ -652,6 +1096,29 @@ static __global__ __launch_bounds__(SAMPLE_THREADS) void spec_verify_kernel(
       st->fallbacks += fell_back;
     }
   }
+}
+
+static __global__ void clear_tickets_kernel(SampleScratch* scr, int rows) {
+  const int b = (int)(blockIdx.x * blockDim.x + threadIdx.x);
+  if (b < rows) scr[b].ticket[0] = 0u;
+}
+
+// The launches of one accept / resample call over `rows` sequences.
+inline void launch_accept(hipStream_t stream, AcceptArgs a, int rows, int cus) {
+  accept_parts(a);
+  const int nrows = 2 * a.gamma + 1;
+  if (accept_filtered(a)) {
+    hipLaunchKernelGGL(row_filter_kernel, dim3(nrows, rows), dim3(SAMPLE_THREADS), 0, stream, a);
+  } else {
+    const int items = rows * nrows * a.nparts;
+    hipLaunchKernelGGL(row_parts_kernel, dim3(min((items + 3) / 4, cus * ACCEPT_WAVES_CU / 4)), dim3(256), 0, stream, a, items,
+                       (unsigned)((0x100000000ull + a.nparts - 1) / a.nparts), (unsigned)((0x100000000ull + nrows - 1) / nrows));
+  }
+  if (a.beta != nullptr) hipLaunchKernelGGL(beta_parts_kernel, dim3((a.nparts + 3) / 4, a.gamma, rows), dim3(256), 0, stream, a);
+  // more workgroups than CUs only repeat the decisions more often
+  const int wgs = sample_workgroups(a.V);
+  a.chunks_wave = min(wgs, (rows * wgs + cus - 1) / cus);
+  hipLaunchKernelGGL(accept_kernel, dim3((wgs + a.chunks_wave - 1) / a.chunks_wave, rows), dim3(SAMPLE_THREADS), 0, stream, a);
 }
 
 }  // namespace sd

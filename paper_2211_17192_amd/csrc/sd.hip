@@ -207,10 +207,7 @@ struct sd_ctx {
   SeqState* d_state = nullptr;
   StepParams* d_params = nullptr;
   float *p_logits = nullptr, *q_logits = nullptr;
-  RowStat* d_stats = nullptr;
-  unsigned int* d_counter = nullptr;
-  double* d_draw_tot = nullptr;          // sample_row_split_kernel: chunk totals [batch][SAMPLE_MAX_CHUNKS]
-  unsigned int* d_draw_ticket = nullptr; // and its tickets, SAMPLE_COUNTER_STRIDE words per sequence
+  SampleScratch* d_scratch = nullptr;    // [batch]
   SeqState* h_state = nullptr;       // pinned
   StepParams* h_params = nullptr;    // pinned
   int batch = 1;
@@ -221,7 +218,9 @@ struct sd_ctx {
   bool all_ready() const { for (int r : ready) if (!r) return false; return true; }
   bool any_stale() const { for (int m : mq_stale) if (m) return true; return false; }
   int last_gamma = 0, last_kind = -1;   // for sd_debug_logits
-  hipGraphExec_t graphs[SD_MAX_GAMMA + 1] = {};
+  hipGraphExec_t graphs[2 * (SD_MAX_GAMMA + 1)] = {};    // iterations: gamma, and again with filtered rows
+  bool filtered() const { return sampling.top_k > 0 || (sampling.top_p > 0.0f && sampling.top_p < 1.0f); }
+  hipGraphExec_t* graph_of(int gamma) { return &graphs[gamma + (filtered() ? SD_MAX_GAMMA + 1 : 0)]; }
   hipGraphExec_t graph_baseline = nullptr;
   hipEvent_t ev[4] = {};
   std::vector<hipEvent_t> kev;       // 2 per Mp layer: around the gated FFN-in GEMM (SD_FLAG_PROFILE)
@@ -257,10 +256,7 @@ void plan_ctx(Arena& A, sd_ctx& c, const sd_model_cfg& pc, const sd_model_cfg& q
   c.d_params = static_cast<StepParams*>(A.take(B * sizeof(StepParams)));
   c.p_logits = static_cast<float*>(A.take(B * (rt.max_gamma + 1) * pc.vocab * sizeof(float)));   // [seq][gamma+1][V]
   c.q_logits = static_cast<float*>(A.take(B * rt.max_gamma * pc.vocab * sizeof(float)));         // [seq][gamma][V]
-  c.d_stats = static_cast<RowStat*>(A.take(B * (2 * SD_MAX_GAMMA + 1) * sizeof(RowStat)));
-  c.d_counter = static_cast<unsigned int*>(A.take(B * SAMPLE_COUNTER_STRIDE * sizeof(unsigned int)));
-  c.d_draw_tot = static_cast<double*>(A.take(B * SAMPLE_MAX_CHUNKS * sizeof(double)));
-  c.d_draw_ticket = static_cast<unsigned int*>(A.take(B * SAMPLE_COUNTER_STRIDE * sizeof(unsigned int)));
+  c.d_scratch = static_cast<SampleScratch*>(A.take(B * sizeof(SampleScratch)));
   c.hist_stride = pc.max_len;
   c.d_hist = static_cast<int*>(A.take(B * (size_t)pc.max_len * sizeof(int)));
 }
@@ -922,8 +918,8 @@ void cross_kv(sd_ctx* c, Model& m, const void* enc) {
 
 // One draw per sequence from the row at logits + b * seq_stride (mode 0: guess number `slot`; 1: commit).
 void launch_draw(sd_ctx* c, const float* logits, int uniform_idx, int mode, int slot, size_t seq_stride) {
-  hipLaunchKernelGGL(sample_row_split_kernel, dim3(SAMPLE_SPLIT, c->batch), dim3(SAMPLE_THREADS), 0, c->stream, logits,
-                     c->p.cfg.vocab, c->d_params, uniform_idx, c->d_state, mode, slot, seq_stride, c->d_draw_tot, c->d_draw_ticket);
+  hipLaunchKernelGGL(sample_row_split_kernel, dim3(sample_workgroups(c->p.cfg.vocab), c->batch), dim3(SAMPLE_THREADS), 0, c->stream,
+                     logits, c->p.cfg.vocab, c->d_params, uniform_idx, c->d_state, mode, slot, seq_stride, c->d_scratch);
 }
 
 // The launch sequence of one run of Algorithm 1 for every sequence (everything between the
@@ -950,19 +946,11 @@ void enqueue_step(sd_ctx* c, int gamma, bool profile) {
   forward_any(c, c->p, Rows{ROWS_VERIFY, 0, gamma + 1, 0, 0, B, gamma}, c->p_logits);
   c->time_ffn = false;
   if (profile) hipEventRecord(c->ev[2], s);
-#define SD_VERIFY(MODE, GRID)                                                                                        \
-  hipLaunchKernelGGL(spec_verify_kernel<MODE>, GRID, dim3(SAMPLE_THREADS), 0, s, c->p_logits, c->q_logits,             \
-                     (const int*)nullptr, (const float*)nullptr, (const float*)nullptr, gamma, V, 0.0f, 1.0f, 0.0, 0,  \
-                     0.0f, c->d_params, c->d_stats, c->d_counter, (int*)nullptr, (int*)nullptr, (float*)nullptr,       \
-                     c->d_state)
-  if (B * (2 * gamma + 1) <= 64) {              // few tickets: one launch
-    SD_VERIFY(0, dim3(2 * gamma + 1, B));
-  } else {                                       // many sequences: statistics, then one tail workgroup each
-    SD_VERIFY(1, dim3(2 * gamma + 1, B));
-    SD_VERIFY(2, dim3(1, B));
-  }
-  if (c->rt.flags & SD_FLAG_BETA) SD_VERIFY(3, dim3(gamma, B));   // side output: beta_i of every guess, into the states
-#undef SD_VERIFY
+  AcceptArgs a{};
+  a.p = c->p_logits; a.q = c->q_logits; a.gamma = gamma; a.V = V; a.prm = c->d_params; a.st = c->d_state; a.scr = c->d_scratch;
+  a.top_k = c->filtered() ? 1 : 0;
+  if (c->rt.flags & SD_FLAG_BETA) a.beta = c->d_state->beta;           // side output: beta_i of every guess, into the states
+  launch_accept(s, a, B, g_num_cus);
   if (c->copy_match > 0) hipLaunchKernelGGL(hist_append_kernel, dim3(B), dim3(32), 0, s, c->d_hist, c->hist_stride, c->d_state, 1);
   if (profile) hipEventRecord(c->ev[3], s);
 }
@@ -1196,11 +1184,7 @@ extern "C" sd_status sd_load_models(sd_ctx** out, const sd_model_cfg* p_cfg, con
   if (st != SD_OK) return bail(st, "Mq: " + err);
   for (const Model* m : {&c->p, &c->q})
     if (m->zeros) hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(256), 0, c->stream, reinterpret_cast<unsigned int*>(m->zeros), 0u, (size_t)256);
-  {
-    const size_t n = B * SAMPLE_COUNTER_STRIDE;
-    hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c->stream, c->d_counter, 0u, n);
-    hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, c->stream, c->d_draw_ticket, 0u, n);
-  }
+  hipLaunchKernelGGL(clear_tickets_kernel, dim3(1), dim3(SD_MAX_BATCH), 0, c->stream, c->d_scratch, (int)B);
   hipError_t e = hipStreamSynchronize(c->stream);
   if (e == hipSuccess) e = hipGetLastError();
   if (e != hipSuccess) return bail(SD_EHIP, std::string("load: ") + hipGetErrorString(e));
@@ -1313,15 +1297,16 @@ extern "C" sd_status sd_step(sd_ctx* c, const int32_t* prefix, int32_t prefix_le
   const bool profile = (c->rt.flags & SD_FLAG_PROFILE) != 0;
   const bool graph = (c->rt.flags & SD_FLAG_GRAPH) != 0 && !profile;
   if (graph) {
-    if (!c->graphs[gamma]) {
-      st = capture_graph(c, &c->graphs[gamma], [&] {
+    hipGraphExec_t* ge = c->graph_of(gamma);
+    if (!*ge) {
+      st = capture_graph(c, ge, [&] {
         hipMemcpyAsync(c->d_params, c->h_params, pbytes, hipMemcpyHostToDevice, c->stream);
         enqueue_step(c, gamma, false);
         hipMemcpyAsync(c->h_state, c->d_state, sbytes, hipMemcpyDeviceToHost, c->stream);
       });
       if (st != SD_OK) return st;
     }
-    HIP_TRY(c, hipGraphLaunch(c->graphs[gamma], c->stream));
+    HIP_TRY(c, hipGraphLaunch(*ge, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
   } else {
     HIP_TRY(c, hipMemcpyAsync(c->d_params, c->h_params, pbytes, hipMemcpyHostToDevice, c->stream));
@@ -1648,7 +1633,7 @@ extern "C" sd_status sd_time_stream_read(sd_ctx* c, int32_t which, int32_t reps,
   const char* hi = static_cast<const char*>(last.kv);
   if (hi <= lo) return fail(c, SD_EINVAL, "unexpected workspace layout");
   const size_t n_blocks = (size_t)(hi - lo) / 1024;
-  float* sink = reinterpret_cast<float*>(c->d_counter);      // never written: the kernel's condition cannot hold
+  float* sink = reinterpret_cast<float*>(c->d_scratch);      // never written: the kernel's condition cannot hold
   hipLaunchKernelGGL(stream_read_kernel, dim3(g_num_cus), dim3(512), 0, c->stream, reinterpret_cast<const f32x4*>(lo), n_blocks, sink);
   hipEventRecord(c->ev[0], c->stream);
   for (int i = 0; i < reps; ++i)

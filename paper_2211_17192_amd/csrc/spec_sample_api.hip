@@ -9,14 +9,9 @@
 #include "kernels_misc.h"
 #include "kernels_sample.h"
 
-namespace {
-size_t scratch_align(size_t v, size_t a) { return (v + a - 1) / a * a; }
-}
-
 extern "C" size_t sd_spec_sample_scratch_bytes(int32_t rows, int32_t gamma) {
   if (rows < 1 || gamma < 1 || gamma > SD_MAX_GAMMA) return 0;
-  return scratch_align((size_t)rows * sd::SAMPLE_COUNTER_STRIDE * sizeof(unsigned int), 256) +
-         (size_t)rows * (2 * gamma + 1) * sizeof(sd::RowStat);
+  return (size_t)rows * sizeof(sd::SampleScratch);
 }
 
 namespace {
@@ -43,25 +38,18 @@ sd_status check_sample_args(const float* p_logits, const float* q_logits, const 
   return SD_OK;
 }
 
-// The launches of one call; counters: one ticket per row, SAMPLE_COUNTER_STRIDE words apart, zero
-// before the call (the one-launch form leaves them zero again); stats: rows x (2 gamma + 1).
+static_assert(SD_MAX_GAMMA == sd::SAMPLE_MAX_GAMMA, "the sampling kernels' scratch holds SD_MAX_GAMMA guesses");
+
+// The launches of one call; scr: one block per row, its ticket zero before the call and after it.
 sd_status launch_spec_sample(const float* p_logits, const float* q_logits, const int32_t* x, const float* r,
                              const float* s, int32_t rows, int32_t gamma, int32_t vocab, float temperature,
                              const SampleOpts& o, int32_t* out_n, int32_t* out_t, float* beta,
-                             unsigned int* counters, sd::RowStat* stats, hipStream_t s_) {
-  const dim3 grid(2 * gamma + 1, rows), block(sd::SAMPLE_THREADS);
-#define SD_VERIFY(MODE, GRID)                                                                                   \
-  hipLaunchKernelGGL(sd::spec_verify_kernel<MODE>, GRID, block, 0, s_, p_logits, q_logits, x, r, s, gamma, vocab, \
-                     temperature, o.len, o.log_len, o.top_k, o.top_p, (const sd::StepParams*)nullptr, stats, counters, out_n, out_t,  \
-                     beta, (sd::SeqState*)nullptr)
-  if (rows * (2 * gamma + 1) <= 64) {           // few tickets: one launch
-    SD_VERIFY(0, grid);
-  } else {                                       // many sequences: statistics, then one tail workgroup each
-    SD_VERIFY(1, grid);
-    SD_VERIFY(2, dim3(1, rows));
-  }
-  if (beta) SD_VERIFY(3, dim3(gamma, rows));
-#undef SD_VERIFY
+                             sd::SampleScratch* scr, hipStream_t s_) {
+  sd::AcceptArgs a{};
+  a.p = p_logits; a.q = q_logits; a.x = x; a.r = r; a.s = s; a.gamma = gamma; a.V = vocab; a.temperature = temperature;
+  a.lenience = o.len; a.log_lenience = o.log_len; a.top_k = o.top_k; a.top_p = o.top_p;
+  a.scr = scr; a.out_n = out_n; a.out_t = out_t; a.beta = beta;
+  sd::launch_accept(s_, a, rows, 256);   // (every gfx950 device has 256 CUs)
   return hipGetLastError() == hipSuccess ? SD_OK : SD_EHIP;
 }
 }  // namespace
@@ -74,11 +62,8 @@ extern "C" sd_status sd_spec_sample_ex(const float* p_logits, const float* q_log
   SampleOpts o{};
   const sd_status st = check_sample_args(p_logits, q_logits, x, r, s, rows, gamma, vocab, temperature, opt, out_n, out_t, o);
   if (st != SD_OK) return st;
-  unsigned int* counters = static_cast<unsigned int*>(scratch);
-  sd::RowStat* stats = reinterpret_cast<sd::RowStat*>(
-      static_cast<char*>(scratch) + scratch_align((size_t)rows * sd::SAMPLE_COUNTER_STRIDE * sizeof(unsigned int), 256));
   return launch_spec_sample(p_logits, q_logits, x, r, s, rows, gamma, vocab, temperature, o, out_n, out_t, beta,
-                            counters, stats, static_cast<hipStream_t>(stream));
+                            static_cast<sd::SampleScratch*>(scratch), static_cast<hipStream_t>(stream));
 }
 
 extern "C" sd_status sd_spec_sample(const float* p_logits, const float* q_logits, const int32_t* x,
@@ -98,10 +83,8 @@ extern "C" sd_status sd_spec_sample(const float* p_logits, const float* q_logits
 // ---------------------------------------------------------------------------
 namespace {
 constexpr int STATIC_ROWS = SD_SPEC_SAMPLE_STATIC_MAX_ROWS;
-constexpr size_t STATIC_COUNTER_BYTES = (size_t)STATIC_ROWS * sd::SAMPLE_COUNTER_STRIDE * sizeof(unsigned int);
-constexpr size_t STATIC_STAT_BYTES = (size_t)STATIC_ROWS * (2 * SD_MAX_GAMMA + 1) * sizeof(sd::RowStat);
-static_assert(STATIC_COUNTER_BYTES % 256 == 0, "the statistics start 256-byte aligned");
-static __device__ __align__(256) unsigned char scratch[STATIC_COUNTER_BYTES + STATIC_STAT_BYTES];   // 250 KB
+static __device__ __align__(256) unsigned char scratch[STATIC_ROWS * sizeof(sd::SampleScratch)];   // 12 MB
+static_assert(sizeof(sd::SampleScratch) % 16 == 0, "the blocks keep their alignment");
 
 constexpr int STATIC_MAX_DEVICES = 64;
 void* g_scratch_ptr[STATIC_MAX_DEVICES] = {};    // device address of `scratch` on each device, once known
@@ -143,12 +126,9 @@ extern "C" sd_status sd_spec_sample_static(const float* p_logits, const float* q
     return SD_EHIP;
   }
   hipStream_t s_ = static_cast<hipStream_t>(stream);
-  unsigned int* counters = static_cast<unsigned int*>(ptr);
-  sd::RowStat* stats = reinterpret_cast<sd::RowStat*>(static_cast<char*>(ptr) + STATIC_COUNTER_BYTES);
-  // the tickets must start at zero whatever an earlier (possibly failed) call left: a fill kernel,
+  // the tickets must start at zero whatever an earlier (possibly failed) call left: a small kernel,
   // not a memset, so that the call can be recorded into a graph
-  const size_t words = (size_t)rows * sd::SAMPLE_COUNTER_STRIDE;
-  hipLaunchKernelGGL(sd::fill_u32_kernel, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, s_, counters, 0u, words);
-  return launch_spec_sample(p_logits, q_logits, x, r, s, rows, gamma, vocab, temperature, o, out_n, out_t, beta,
-                            counters, stats, s_);
+  sd::SampleScratch* scr = static_cast<sd::SampleScratch*>(ptr);
+  hipLaunchKernelGGL(sd::clear_tickets_kernel, dim3((unsigned)((rows + 63) / 64)), dim3(64), 0, s_, scr, rows);
+  return launch_spec_sample(p_logits, q_logits, x, r, s, rows, gamma, vocab, temperature, o, out_n, out_t, beta, scr, s_);
 }

@@ -1,0 +1,103 @@
+"""The accept / resample kernels where their partition changes: parts of a row's statistics, chunks and
+workgroups of the draw, lists and bins of the filters; against the oracle on the same inputs."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import sampling
+from paper_2211_17192_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def call(zp, zq, x, r, s, temperature, scratch=None, **kw):
+    from paper_2211_17192_amd import binding
+    beta = torch.full((zq.shape[0], zq.shape[1]), -1.0, device="cuda")
+    n, t = binding.spec_sample(*(torch.from_numpy(np.ascontiguousarray(v)).cuda() for v in (zp, zq, x, r, s)), temperature,
+                               scratch=scratch, beta=beta, **kw)
+    torch.cuda.synchronize()
+    return n.cpu().numpy(), t.cpu().numpy(), beta.cpu().numpy()
+
+
+def check(zp, zq, x, r, s, temperature, top_k=0, top_p=0.0, scratch=None):
+    """n and t exact, but for decisions and draws next to an edge; beta to fp32 rounding."""
+    rows, gamma, _ = zq.shape
+    n_g, t_g, beta_g = call(zp, zq, x, r, s, temperature, scratch, top_k=top_k, top_p=top_p)
+    tol = 0
+    for b in range(rows):
+        p = np.stack([sampling.standardise(z, temperature, top_k, top_p) for z in zp[b]])
+        q = np.stack([sampling.standardise(z, temperature, top_k, top_p) for z in zq[b]])
+        n_o, t_o, info = sampling.accept_and_resample(p, q, list(x[b]), r[b], s[b])
+        for i in range(gamma):
+            # fp32 exponentials: an error of a few ulp in every weight
+            assert abs(beta_g[b, i] - sampling.beta(p[i], q[i])) <= 2e-6
+        if (n_g[b], t_g[b]) == (n_o, t_o):
+            continue
+        tol += 1
+        if n_g[b] != n_o:
+            assert info["margins"][min(n_g[b], n_o)] < 1e-3
+        else:
+            w = p[n_o] if n_o == gamma else sampling.adjusted_distribution(p[n_o], q[n_o])
+            assert sampling.icdf_edge_distance(w, s[b], int(t_g[b])) < 1e-5
+    assert tol <= 1
+
+
+# below four entries, around a group of 4, a chunk (256), a part (1024), a workgroup of chunks (4096), the
+# register row (32768) and the vocabulary whose parts get longer (65536); beyond it, ragged
+@pytest.mark.parametrize("vocab", [3, 5, 255, 257, 1023, 1024, 1025, 4097, 8190, 32771, 65537, 140001])
+def test_vocabulary_edges(vocab):
+    rows, gamma = (3, 3) if vocab < 30000 else (2, 1)
+    zp, zq, x, r, s = synth.sampler_case(rows, gamma, vocab, 1.0, vocab)
+    check(zp, zq, x, r, s, 0.9)
+
+
+@pytest.mark.parametrize("rows", [1, 33, 300])
+def test_many_rows_and_one(rows):
+    """One part a wavefront, and wavefronts that take several; one chunk a wavefront, and more."""
+    zp, zq, x, r, s = synth.sampler_case(rows, 4, 5000, 1.0, rows)
+    check(zp, zq, x, r, s, 1.0)
+
+
+def test_masked_entries_and_infinite_gaps():
+    """Constrained decoding: most entries -inf, whole parts of a row without a finite entry."""
+    zp, zq, x, r, s = synth.sampler_case(6, 3, 9001, 1.0, 5)
+    zp[:, :, 50:8900] = -np.inf
+    zq[:, :, 50:8900] = -np.inf
+    x = (x % 50).astype(np.int32)
+    check(zp, zq, x, r, s, 1.0)
+
+
+@pytest.mark.parametrize("kind,vocab,top_k,top_p", [
+    ("ties", 8192, 5, 0.0),        # every entry ties with the k-th: more than the list holds, all are kept
+    ("levels", 8192, 700, 0.0),    # a few hundred distinct values
+    ("flat", 32768, 0, 0.7),       # all entries share their first bits: the search stays in the registers
+    ("normal", 32768, 0, 0.9), ("normal", 32764, 1024, 0.5), ("normal", 20000, 1025, 0.0), ("normal", 64, 60, 0.0),
+    ("masked", 4096, 40, 0.9),     # fewer finite entries than k
+])
+def test_filter_paths(kind, vocab, top_k, top_p):
+    zp, zq, _, r, s = synth.sampler_case(4, 3, vocab, 1.0, 17)
+    if kind == "ties":
+        zp, zq = np.full_like(zp, 1.5), np.full_like(zq, 1.5)
+    elif kind == "levels":
+        zp, zq = np.round(zp * 16) / 16, np.round(zq * 16) / 16
+    elif kind == "flat":
+        zp, zq = 40 + zp * np.float32(1e-3), 40 + zq * np.float32(1e-3)
+    elif kind == "masked":
+        zp[:, :, 25:], zq[:, :, 25:] = -np.inf, -np.inf
+    top_p = float(np.float32(top_p))
+    zp, zq = zp.astype(np.float32), zq.astype(np.float32)
+    if kind in ("flat", "normal") and 0.0 < top_p:
+        # a boundary this close to top_p may fall either way in fp32: such a row is replaced by one that is not
+        for z in [*zp.reshape(-1, vocab), *zq.reshape(-1, vocab)]:
+            while sampling.nucleus_margin(z, 1.0, top_k, top_p) < 2e-6:
+                z[0] += np.float32(0.01)
+    x = np.argmax(zq, -1).astype(np.int32)
+    check(zp, zq, x, r, s, 1.0, top_k, top_p)
+
+
+def test_calls_of_any_size_share_one_scratch():
+    from paper_2211_17192_amd import binding
+    scratch = binding.spec_sample_scratch(64, 7)
+    for rows, gamma in ((2, 7), (64, 1), (5, 3), (64, 7), (1, 1)):
+        zp, zq, x, r, s = synth.sampler_case(rows, gamma, 6000, 1.0, rows * 8 + gamma)
+        check(zp, zq, x, r, s, 1.0, scratch=scratch)
