@@ -389,7 +389,7 @@ sd_status sd_spec_sample(const float* p_logits, const float* q_logits, const int
  * sd_spec_sample_ex for callers that cannot allocate device memory or pass a
  * scratch buffer: code under HIP graph capture, tight serving loops, harnesses
  * that forbid hipMalloc.  Same arguments, same kernels and same results; the
- * scratch (tickets, row statistics and partial sums, 12 MB) is a fixed array in device
+ * scratch (tickets, row statistics and partial sums, 10 MB) is a fixed array in device
  * memory that the library holds on every GPU it runs on until the process ends.
  * The call allocates nothing (no hipMalloc / hipFree, no allocating library
  * routine) and clears the tickets it uses with a small fill kernel, so it may

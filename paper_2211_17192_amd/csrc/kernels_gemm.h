@@ -84,6 +84,9 @@ struct GemmArgs {
   // gemm_gated_wide_kernel: when set, the output goes here in fragment order
   // ([N/32][GEMM_WIDE_RT][64 lanes][8], what the FFN-out product reads) instead of row-major into `out`
   void* out_frag;
+  // gemm_split_kernel: where fragment (k-step, slab) of the activations lies, (ks * x_ks + slab * x_slab) KB;
+  // its finish kernel: xg_out in fragment order ([slab][N/32][64 lanes][8]) instead of row-major
+  int x_ks, x_slab, xg_frag;
 };
 
 template <typename T> struct Mma;
@@ -918,7 +921,7 @@ static __global__ __launch_bounds__(64 * NW) void gemm_split_kernel(const GemmAr
   const T* wbase[NS];
   wbase[0] = static_cast<const T*>(a.W) + ((size_t)tilec * KS) * 512 + lane * 8;
   if (NS == 2) wbase[NS - 1] = static_cast<const T*>(a.W2) + ((size_t)tilec * KS) * 512 + lane * 8;
-  const Frag* xf = reinterpret_cast<const Frag*>(a.X);            // [KS][RT][64 lanes]
+  const Frag* xf = reinterpret_cast<const Frag*>(a.X);
 
   f32x4 acc[NS][RT];
 #pragma unroll
@@ -940,7 +943,7 @@ static __global__ __launch_bounds__(64 * NW) void gemm_split_kernel(const GemmAr
     for (int m = 0; m < XPT; ++m) {
       const int i = min(tid + NT * m, nfrag - 1);
       const int u = i / (nrt * 64), rem = i - u * (nrt * 64);
-      xr[m] = xf[(size_t)min(ksb + u, ks_last) * (RT * 64) + rem];
+      xr[m] = xf[((size_t)min(ksb + u, ks_last) * a.x_ks + (size_t)(rem >> 6) * a.x_slab) * 64 + (rem & 63)];
     }
   };
   load_x(ks0);
@@ -1037,7 +1040,8 @@ static __global__ __launch_bounds__(256) void gemm_split_finish_kernel(const Gem
       xn = static_cast<const float*>(a.out)[(size_t)row * a.ldo + n] + y[0];
       static_cast<float*>(a.out)[(size_t)row * a.ldo + n] = xn;
       if (a.xg_out != nullptr)
-        Store<T>::st(static_cast<T*>(a.xg_out) + (size_t)row * a.ldo + n, xn * Store<T>::ld(static_cast<const T*>(a.gain_next) + n));
+        Store<T>::st(static_cast<T*>(a.xg_out) + (a.xg_frag ? rows_frag_index(row, n, a.N >> 5) : (size_t)row * a.ldo + n),
+                     xn * Store<T>::ld(static_cast<const T*>(a.gain_next) + n));
     }
     if (a.ss_out != nullptr) {
       float q = square(xn);

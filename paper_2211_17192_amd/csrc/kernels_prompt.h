@@ -1,7 +1,7 @@
-// Products over many rows: the prompt of a new sequence and the encoder's positions.
-// With a few dozen rows or fewer the weights' way out of memory bounds a product (kernels_gemm.h);
-// with hundreds of rows the matrix cores do, and a pass over 16 rows at a time reads the weights
-// rows / 16 times.  Here one launch takes all rows of a pass.
+// Products over more than one slab of 16 rows (bf16): the prompt of a new sequence, the encoder's
+// positions, several sequences decoded together.  Up to 16 rows the weights' way out of memory bounds a
+// product (kernels_gemm.h); with hundreds of rows the matrix cores do, and a pass over 16 rows at a time
+// reads the weights rows / 16 times.  Here one launch takes all rows of a pass.
 //
 // Both operands are in MFMA fragment order: the weights as they were re-tiled at load,
 // Wt[N/16][K/32][64 lanes][8], and the activations alike, Xf[rows/16][K/32][64 lanes][8], which the
@@ -23,20 +23,6 @@ static __global__ __launch_bounds__(256) void rows_to_slabs_kernel(const bf16* _
   const int slab = (int)(f / KS), ks = (int)(f % KS);
   const int row = min(slab * 16 + (lane & 15), rows - 1);
   *reinterpret_cast<bf16x8*>(Xf + idx * 8) = *reinterpret_cast<const bf16x8*>(X + (size_t)row * K + ks * 32 + (lane >> 4) * 8);
-}
-
-// 1 / rms of every row from the partial sums of squares ss [slab][n_part][16], added in gemm_kernel's
-// order.  grid = slabs.
-static __global__ __launch_bounds__(256) void rows_rs_kernel(const float* __restrict__ ss, int n_part, int ss_stride, int K, float eps,
-                                                             float* __restrict__ rs) {
-  const int row = threadIdx.x >> 4, f = threadIdx.x & 15;
-  const float* s = ss + (size_t)blockIdx.x * ss_stride;
-  float q = 0.0f;
-#pragma unroll 16
-  for (int p = f; p < n_part; p += 16) q += s[p * 16 + row];
-  q = lane_combine<1>(q, OpSumF()); q = lane_combine<2>(q, OpSumF());
-  q = lane_combine<4>(q, OpSumF()); q = lane_combine<8>(q, OpSumF());
-  if (f == 0) rs[blockIdx.x * 16 + row] = 1.0f / sqrtf(q / (float)K + eps);
 }
 
 // LayerNorm of fp32 rows into fragment order: gemm_kernel's statistics (the K-slices of its S
@@ -65,18 +51,22 @@ static __global__ __launch_bounds__(512) void rows_layernorm_kernel(const float*
     for (int w = 0; w < S; ++w) t += stat[which][w * 16 + j];
     return t;
   };
-  auto normalise = [&](const float (&xv)[8], int ks, float mu, float rstd) {
-    float v[8], g[8], b[8];
-    load8<bf16>(gain + ks * 32 + kq * 8, g);
-    load8<bf16>(beta + ks * 32 + kq * 8, b);
+  auto normalise = [&](const float (&xv)[8], int ks, float mu, float rstd, const bf16x8& g, const bf16x8& b) {
+    float v[8];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = ln_apply(xv[e], mu, rstd, g[e], b[e]);
+    for (int e = 0; e < 8; ++e) v[e] = ln_apply(xv[e], mu, rstd, (float)g[e], (float)b[e]);
     out[ks * 64] = Mma<bf16>::from_floats(v);
   };
   if (ksteps_per_wave <= HELD) {
     float xv[HELD][8];
+    bf16x8 g[HELD], b[HELD];
 #pragma unroll
-    for (int u = 0; u < HELD; ++u) load8<float>(x + min(ks0 + u, KS - 1) * 32, xv[u]);
+    for (int u = 0; u < HELD; ++u) {
+      const int k = min(ks0 + u, KS - 1) * 32;
+      load8<float>(x + k, xv[u]);
+      g[u] = Mma<bf16>::load(gain + k + kq * 8);
+      b[u] = Mma<bf16>::load(beta + k + kq * 8);
+    }
     const float mu = total(slice_sums([&] {
       float s = 0.0f;
 #pragma unroll
@@ -100,7 +90,7 @@ static __global__ __launch_bounds__(512) void rows_layernorm_kernel(const float*
     const float rstd = 1.0f / sqrtf(var + eps);
 #pragma unroll
     for (int u = 0; u < HELD; ++u)
-      if (ks0 + u < ks1) normalise(xv[u], ks0 + u, mu, rstd);
+      if (ks0 + u < ks1) normalise(xv[u], ks0 + u, mu, rstd, g[u], b[u]);
     return;
   }
   const float mu = total(slice_sums([&] {
@@ -127,7 +117,7 @@ static __global__ __launch_bounds__(512) void rows_layernorm_kernel(const float*
 #pragma unroll 4
   for (int ks = ks0; ks < ks1; ++ks) {
     float v[8]; load8<float>(x + ks * 32, v);
-    normalise(v, ks, mu, rstd);
+    normalise(v, ks, mu, rstd, Mma<bf16>::load(gain + ks * 32 + kq * 8), Mma<bf16>::load(beta + ks * 32 + kq * 8));
   }
 }
 
@@ -136,7 +126,11 @@ struct RowsGemmArgs {
   const bf16* W2;         // EPI_GATED: the "up" weights
   const bf16* X;          // fragment order
   const bf16* zeros;      // 1 KB of zeros
-  const float* rs;        // 1 / rms of every row, or nullptr (no norm, or LayerNorm applied by the producer)
+  // a product behind an RMSNorm: the partial sums of squares of its rows, [slab][n_part][16], slabs
+  // ss_stride floats apart (nullptr: no norm, or a LayerNorm that the producer applied)
+  const float* ss_in;
+  int n_part;
+  float eps;
   const bf16* bias;       // [N] or nullptr
   int rows, K, N, kpw, nchunk;   // kpw, nchunk: gemm_kernel's k-steps per wavefront and wavefronts
   int mtiles, ntiles_wg;  // workgroup tiles in either direction
@@ -158,9 +152,46 @@ struct RowsGemmArgs {
   int nq, nkv;
   bf16* kv_pool;
   const int* page_table;
-  const int* row_pos;
+  const int* row_pos;     // < 0: a padding row, nothing goes to the cache
+  const int* row_seq;     // several sequences: each row's; its page table starts at page_table + seq * pt_stride
+  int pt_stride;
   int page_size, n_kv_heads;
   const float* rope;
+  // EPI_LOGITS: row r goes to row out_row[r] of logits (< 0: dropped), times scale
+  float* logits;
+  const int* out_row;
+  float scale;
+};
+
+// 1 / rms of the 16 rows of a slab, by one wavefront, into out (LDS): the partial sums in gemm_kernel's
+// order.  load() asks for the first 256 of them (d_model <= 4096: all), finish() adds.
+struct SlabRms {
+  float4 v[16];
+  __device__ __forceinline__ void load(const RowsGemmArgs& a, int slab, int lane) {
+    const float* s = a.ss_in + (size_t)slab * a.ss_stride + (lane & 3) * 4;      // lane: partials f = lane / 4, f + 16, ..; four rows
+#pragma unroll
+    for (int u = 0; u < 16; ++u) v[u] = *reinterpret_cast<const float4*>(s + (size_t)min((lane >> 2) + 16 * u, a.n_part - 1) * 16);
+  }
+  __device__ __forceinline__ void finish(const RowsGemmArgs& a, int slab, int lane, float* out) const {
+    float q[4] = {0.f, 0.f, 0.f, 0.f};
+    const int f = lane >> 2;
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      const bool ok = f + 16 * u < a.n_part;
+      q[0] += ok ? v[u].x : 0.0f; q[1] += ok ? v[u].y : 0.0f; q[2] += ok ? v[u].z : 0.0f; q[3] += ok ? v[u].w : 0.0f;
+    }
+    const float* s = a.ss_in + (size_t)slab * a.ss_stride + (lane & 3) * 4;
+    for (int p = f + 256; p < a.n_part; p += 16) {
+      const float4 w = *reinterpret_cast<const float4*>(s + (size_t)p * 16);
+      q[0] += w.x; q[1] += w.y; q[2] += w.z; q[3] += w.w;
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      q[e] += __shfl_xor(q[e], 4, 64); q[e] += __shfl_xor(q[e], 8, 64);
+      q[e] += __shfl_xor(q[e], 48, 64); q[e] += __shfl_xor(q[e], 16, 64);      // quads 0 + 3, 1 + 2: as the first lane of gemm_kernel's sum
+      if (f == 0) out[(lane & 3) * 4 + e] = 1.0f / sqrtf(q[e] / (float)a.K + a.eps);
+    }
+  }
 };
 
 // What a lane needs of row `row` (slab, j = row % 16) before it writes its features.
@@ -171,17 +202,21 @@ struct RowsEpilogue {
   float r1;
   int pos;
   size_t kvbase;
-  __device__ __forceinline__ void row_inputs(const RowsGemmArgs& a, int slab_, int lane) {
+  int orow;
+  // rs: LDS, 1 / rms of the slab's 16 rows
+  __device__ __forceinline__ void row_inputs(const RowsGemmArgs& a, int slab_, int lane, const float* rs) {
     slab = slab_; j = lane & 15; kq = lane >> 4; row = slab * 16 + j;
     ok = row < a.rows;
     const int rowc = min(row, a.rows - 1);
-    r1 = (a.rs != nullptr) ? a.rs[rowc] : 1.0f;
-    pos = 0; kvbase = 0;
+    r1 = (a.ss_in != nullptr) ? rs[j] : 1.0f;
+    pos = 0; kvbase = 0; orow = row;
     if (EPI == EPI_QKV) {
-      pos = max(a.row_pos[rowc], 0);
-      const int page = a.page_table[pos / a.page_size], slot = pos % a.page_size;
+      pos = a.row_pos[rowc];
+      const int pc = max(pos, 0), pt0 = (a.row_seq != nullptr) ? a.row_seq[rowc] * a.pt_stride : 0;
+      const int page = a.page_table[pt0 + pc / a.page_size], slot = pc % a.page_size;
       kvbase = (size_t)page * 2 * a.n_kv_heads * a.page_size * a.d_head + (size_t)slot * a.d_head;
     }
+    if (EPI == EPI_LOGITS && a.out_row != nullptr) orow = a.out_row[rowc];
   }
   // The finished sums of one 16-feature tile (EPI_GATED: of its gate and up streams): this lane's are the
   // features 16 tile + 4 kq + 0..3.  gemm_kernel's arithmetic.
@@ -191,7 +226,7 @@ struct RowsEpilogue {
     float y[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      y[r] = (a.rs != nullptr) ? s0[r] * r1 : s0[r];
+      y[r] = (a.ss_in != nullptr) ? s0[r] * r1 : s0[r];
       y[r] += (a.bias != nullptr) ? (float)a.bias[n0 + r] : 0.0f;
     }
     if (EPI == EPI_RESID) {
@@ -220,7 +255,7 @@ struct RowsEpilogue {
       const int nn = is_q ? n0 : (is_k ? n0 - a.nq : n0 - a.nq - a.nkv);
       const int head = nn / a.d_head, d = nn % a.d_head;
       bf16x4 o;
-      if (a.rope != nullptr && (is_q || is_k)) {
+      if (a.rope != nullptr && (is_q || is_k) && pos >= 0) {
         const float4 cs = *reinterpret_cast<const float4*>(a.rope + ((size_t)pos * (a.d_head >> 1) + (d >> 1)) * 2);
         o[0] = (bf16)rope_rotate(y[0], y[1], cs.x, cs.y, false); o[1] = (bf16)rope_rotate(y[1], y[0], cs.x, cs.y, true);
         o[2] = (bf16)rope_rotate(y[2], y[3], cs.z, cs.w, false); o[3] = (bf16)rope_rotate(y[3], y[2], cs.z, cs.w, true);
@@ -230,8 +265,11 @@ struct RowsEpilogue {
       }
       if (ok) {
         if (is_q) *reinterpret_cast<bf16x4*>(a.q + (size_t)row * a.nq + n0) = o;
-        else *reinterpret_cast<bf16x4*>(a.kv_pool + kvbase + ((size_t)(is_k ? 0 : 1) * a.n_kv_heads + head) * a.page_size * a.d_head + d) = o;
+        else if (pos >= 0) *reinterpret_cast<bf16x4*>(a.kv_pool + kvbase + ((size_t)(is_k ? 0 : 1) * a.n_kv_heads + head) * a.page_size * a.d_head + d) = o;
       }
+    } else if (EPI == EPI_LOGITS) {
+      if (ok && orow >= 0)
+        *reinterpret_cast<float4*>(a.logits + (size_t)orow * a.N + n0) = make_float4(a.scale * y[0], a.scale * y[1], a.scale * y[2], a.scale * y[3]);
     } else {
       bf16x4 o;
 #pragma unroll
@@ -280,6 +318,7 @@ static __global__ __launch_bounds__(256, 2) void gemm_rows_kernel(const RowsGemm
   constexpr int SUB = 4, NT_OUT = (EPI == EPI_GATED) ? NT / 2 : NT;
   constexpr int NFRAG = SUB * MT * 64, XPT = NFRAG / 256;
   __shared__ __align__(16) bf16x8 xs[2][NFRAG];
+  __shared__ float rs_s[MT][16];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int KS = a.K >> 5, ntiles = a.N >> 4, slabs = (a.rows + 15) >> 4;
@@ -340,6 +379,11 @@ static __global__ __launch_bounds__(256, 2) void gemm_rows_kernel(const RowsGemm
     __builtin_amdgcn_sched_group_barrier(0x020, XPT, 0);
   };
 
+  // 1 / rms of the rows: slab w (and w + 4) by wavefront w, its loads ahead of the stream's
+  SlabRms rms;
+  const bool normed = a.ss_in != nullptr;            // (uniform)
+  if (normed && wave < MT) rms.load(a, min(bm * MT + wave, slabs - 1), lane);
+
   // passes of SUB k-steps, never across the end of a K-slice
   int end = min(KS, a.kpw);                          // of the slice being multiplied
   load_x(0, end);
@@ -349,6 +393,13 @@ static __global__ __launch_bounds__(256, 2) void gemm_rows_kernel(const RowsGemm
   int ksb = 0, next = min(SUB, end);                 // this pass, the next one
   int end_next = (next < end) ? end : min(KS, end + a.kpw);                  // of the slice `next` lies in
   load_x(next, end_next - next);
+  if (normed) {
+    if (wave < MT) rms.finish(a, min(bm * MT + wave, slabs - 1), lane, rs_s[wave]);
+    if (wave + 4 < MT) {
+      rms.load(a, min(bm * MT + wave + 4, slabs - 1), lane);
+      rms.finish(a, min(bm * MT + wave + 4, slabs - 1), lane, rs_s[(wave + 4) % MT]);
+    }
+  }
   __syncthreads();
   int buf = 0;
   const int nslices = (KS + a.kpw - 1) / a.kpw;
@@ -397,7 +448,7 @@ static __global__ __launch_bounds__(256, 2) void gemm_rows_kernel(const RowsGemm
   for (int m = 0; m < MT; ++m) {
     if (bm * MT + m >= slabs) break;                 // uniform
     RowsEpilogue<EPI> e;
-    e.row_inputs(a, bm * MT + m, lane);
+    e.row_inputs(a, bm * MT + m, lane, rs_s[m]);
 #pragma unroll
     for (int t = 0; t < NT_OUT; ++t)
       if (tile0 + t < ntiles) {                      // uniform
@@ -414,7 +465,7 @@ static __global__ __launch_bounds__(256, 2) void gemm_rows_kernel(const RowsGemm
 // this kind are bound by latency (a few microseconds in all), then by what a CU can pull from L2: NT + MT
 // KB for NT * MT MFMAs.
 // D: kpw is a multiple of it, or the k-steps past a slice's end are multiplied with zeros.
-// dynamic LDS: S * NT * MT KB.
+// dynamic LDS: S * NT * MT KB + MT * 64 bytes.
 template <int EPI, int NT, int MT, int D>
 static __global__ __launch_bounds__(512) void gemm_slices_kernel(const RowsGemmArgs a) {
   extern __shared__ float lds[];
@@ -454,8 +505,13 @@ static __global__ __launch_bounds__(512) void gemm_slices_kernel(const RowsGemmA
 #pragma unroll
       for (int t = 0; t < NT; ++t) acc[t][m] = Mma<bf16>::mma(wf[u][t], xf[u][m], acc[t][m]);
   };
+  float* rs_s = lds + (size_t)S * NT * MT * 256;     // [MT][16]
+  const bool normed = a.ss_in != nullptr;            // (uniform)
+  SlabRms rms;
+  if (normed && wave < MT) rms.load(a, min(bm * MT + wave, slabs - 1), lane);
 #pragma unroll
   for (int u = 0; u < D; ++u) load(u, ks0 + u);
+  if (normed && wave < MT) rms.finish(a, min(bm * MT + wave, slabs - 1), lane, rs_s + wave * 16);      // (S >= MT)
   const int blocks = (a.kpw + D - 1) / D;
 #pragma unroll 1
   for (int b = 1; b < blocks; ++b) {
@@ -472,13 +528,13 @@ static __global__ __launch_bounds__(512) void gemm_slices_kernel(const RowsGemmA
   for (int t = 0; t < NT; ++t)
 #pragma unroll
     for (int m = 0; m < MT; ++m) part[((wave * NT + t) * MT + m) * 64 + lane] = acc[t][m];
-  RowsEpilogue<EPI> e;                               // the first pair's row constants arrive while the wavefronts meet
-  e.row_inputs(a, min(bm * MT + wave % MT, slabs - 1), lane);
+  RowsEpilogue<EPI> e;
   __syncthreads();
+  e.row_inputs(a, min(bm * MT + wave % MT, slabs - 1), lane, rs_s + (wave % MT) * 16);
   for (int i = wave; i < NT_OUT * MT; i += S) {      // (tile, slab) pairs, slab fastest
     const int t = i / MT, m = i % MT;
     if (bm * MT + m >= slabs || tile0 + t >= ntiles) continue;                 // uniform
-    if (i != wave) e.row_inputs(a, bm * MT + m, lane);
+    if (i != wave) e.row_inputs(a, bm * MT + m, lane, rs_s + m * 16);
     f32x4 s[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
     for (int st = 0; st < ((EPI == EPI_GATED) ? 2 : 1); ++st) {

@@ -44,7 +44,6 @@ struct RowPart {
 struct SampleScratch {
   unsigned int ticket[64];
   RowPart part[2 * SAMPLE_MAX_GAMMA + 1][SAMPLE_PARTS];
-  double beta[SAMPLE_MAX_GAMMA][SAMPLE_PARTS];
   double tot[SAMPLE_MAX_CHUNKS];
 };
 
@@ -625,8 +624,8 @@ __device__ __forceinline__ int icdf_regs(const float4 (&vp)[SAMPLE_REG_F4], cons
 // twice, and the fp64 weights.)  The weights are exp((z - m) / T) without the division by
 // their sum: both sides of "cumulative weight > u * total" carry the same factor.
 // Argmax: each workgroup the maximum of its own entries only, the last one the lowest index.
-// Top-k / nucleus: workgroup 0 does the whole row (statistics and draw from registers); the others
-// leave at once.  grid = (sample_workgroups(V), sequences).
+// Rows that top-k / nucleus filter go to sample_row_filter_kernel: one workgroup, the row in registers.
+// grid = (sample_workgroups(V), sequences).
 __host__ __device__ constexpr int sample_workgroups(int V) {
   return ((V + SAMPLE_CHUNK - 1) / SAMPLE_CHUNK + SAMPLE_CHUNKS_WG - 1) / SAMPLE_CHUNKS_WG;
 }
@@ -681,16 +680,6 @@ static __global__ __launch_bounds__(SAMPLE_THREADS) void sample_row_split_kernel
   const float T = prm->temperature;
   const bool greedy = (T == 0.0f);
   const float invT = greedy ? 1.0f : 1.0f / T;
-  const bool filtered = prm->top_k > 0 || (prm->top_p > 0.0f && prm->top_p < 1.0f);
-  if (!greedy && filtered) {                          // (the host admits filters only for rows that fit the registers)
-    if (w != 0) return;
-    float4 v[SAMPLE_REG_F4];
-    load_row_regs(logits, V, v);
-    const RowStat rs = row_stats_regs(v, invT, false, sm, prm->top_k, prm->top_p, V);
-    const int tok = icdf_regs(v, rs, v, rs, false, invT, V, prm->uniforms[uniform_idx], sm);
-    if (tid == 0) commit_draw(st, mode, slot, tok);
-    return;
-  }
   float m = fmaxf(fmaxf(mine.x, mine.y), fmaxf(mine.z, mine.w));
   if (greedy) {
     m = block_reduce(m, sm.redf, OpMaxF(), -INFINITY) + 0.0f;                    // (-0 counts as 0)
@@ -745,17 +734,34 @@ static __global__ __launch_bounds__(SAMPLE_THREADS) void sample_row_split_kernel
   }
 }
 
+static __global__ __launch_bounds__(SAMPLE_THREADS) void sample_row_filter_kernel(
+    const float* __restrict__ logits, int V, const StepParams* __restrict__ prm, int uniform_idx,
+    SeqState* __restrict__ st, int mode, int slot, size_t seq_stride) {
+  __shared__ SampleSmem sm;
+  logits += (size_t)blockIdx.x * seq_stride;
+  prm += blockIdx.x;
+  st += blockIdx.x;
+  const float T = prm->temperature;
+  const bool greedy = (T == 0.0f);                   // (ignores the filters)
+  const float invT = greedy ? 1.0f : 1.0f / T;
+  float4 v[SAMPLE_REG_F4];
+  load_row_regs(logits, V, v);
+  const RowStat rs = row_stats_regs(v, invT, greedy, sm, prm->top_k, prm->top_p, V);
+  const int tok = greedy ? rs.arg : icdf_regs(v, rs, v, rs, false, invT, V, prm->uniforms[uniform_idx], sm);
+  if (threadIdx.x == 0) commit_draw(st, mode, slot, tok);
+}
+
 // ---------------------------------------------------------------------------
 // Accept / resample (Algorithm 1, second half), for `rows` independent sequences:
 //   row_parts_kernel    statistics of the 2 gamma + 1 logits rows of every sequence (row j <= gamma: p_{j+1};
 //                       j > gamma: q_{j-gamma}), a wavefront per 2048 entries; row_filter_kernel
 //                       does it for rows that top-k / nucleus filter, a workgroup per row
-//   beta_parts_kernel   the acceptance probabilities as a side output (when asked for)
 //   accept_kernel       evaluates r_i <= p_i(x_i)/q_i(x_i) for all i, takes n = index of the first
 //                       rejection, draws t from norm(max(0, p_{n+1} - q_{n+1})) (n < gamma) or
 //                       p_{gamma+1}, writes n and t, and, when `st` is given, commits the sequence:
 //                       out = x_1..x_n, t; len += n+1 (which is the KV roll-back: cache rows
-//                       beyond the committed length are dead and get overwritten).
+//                       beyond the committed length are dead and get overwritten); further
+//                       workgroups compute the acceptance probabilities beta when asked for.
 // x, r, s: explicit arrays [rows, gamma] / [rows] or, when prm/st are given,
 // taken from the device-resident step parameters and state.
 // ---------------------------------------------------------------------------
@@ -764,7 +770,8 @@ struct AcceptArgs {
   const int* x; const float *r, *s;
   int gamma, V;
   int part_len, nparts;                // entries of one part of a row's statistics (a multiple of SAMPLE_PART), parts per row
-  int chunks_wave;                     // accept_kernel: chunks per wavefront
+  int chunks_wave, draw_wgs;           // accept_kernel: chunks per wavefront; workgroups of a sequence's draw (beta's follow)
+  int self;                            // accept_kernel: the statistics are its own work
   float temperature, lenience;
   double log_lenience;
   int top_k; float top_p;              // in-model use: only whether the rows are filtered (the options are read from prm)
@@ -782,6 +789,76 @@ __host__ __device__ inline void accept_parts(AcceptArgs& a) {
 }
 __device__ __forceinline__ const float* accept_row(const AcceptArgs& a, int b, int j) {
   return (j <= a.gamma) ? a.p + ((size_t)b * (a.gamma + 1) + j) * a.V : a.q + ((size_t)b * a.gamma + (j - a.gamma - 1)) * a.V;
+}
+
+// A part's first block of entries, and its statistics.
+__device__ __forceinline__ void load_part(const AcceptArgs& a, int b, int j, int part, int lane, float4 (&v)[SAMPLE_PART / 256]) {
+  const float* z = accept_row(a, b, j);
+  const int k0 = part * a.part_len;
+  if (k0 + SAMPLE_PART <= a.V) {                     // (uniform) no entry past the row
+#pragma unroll
+    for (int it = 0; it < SAMPLE_PART / 256; ++it) {
+      const f32x4_any t = *reinterpret_cast<const f32x4_any*>(z + k0 + it * 256 + (unsigned)lane * 4u);
+      v[it] = make_float4(t[0], t[1], t[2], t[3]);
+    }
+  } else {
+#pragma unroll
+    for (int it = 0; it < SAMPLE_PART / 256; ++it) v[it] = load4_row(z, k0 + it * 256 + lane * 4, a.V);
+  }
+}
+__device__ __forceinline__ void reduce_part(const AcceptArgs& a, int b, int j, int part, int lane, float4 (&v)[SAMPLE_PART / 256]) {
+  constexpr int NV = SAMPLE_PART / 256;
+      const float T = a.prm ? a.prm[b].temperature : a.temperature;
+      const bool greedy = (T == 0.0f);
+      if (greedy && j > a.gamma && a.beta == nullptr) return;      // argmax sampling looks at q rows for beta only
+      const float invT = greedy ? 1.0f : 1.0f / T;
+      float m = -INFINITY;
+      double s = 0.0;
+      int arg = INT_MAX;
+      const int k_end = min(a.V, (part + 1) * a.part_len);
+      for (int k0 = part * a.part_len; k0 < k_end; k0 += SAMPLE_PART) {
+        if (k0 != part * a.part_len) {                 // (parts longer than a block: more than 65536 entries a row)
+          const float* z = accept_row(a, b, j);
+  #pragma unroll
+          for (int it = 0; it < NV; ++it) v[it] = load4_row(z, k0 + it * 256 + lane * 4, a.V);
+        }
+        // an entry that is not a number weighs nothing, as -inf does
+        constexpr float LOWEST = -3.402823466e38f;
+        float mb = -INFINITY;
+  #pragma unroll
+        for (int it = 0; it < NV; ++it) mb = fmaxf(mb, fmaxf(fmaxf(v[it].x, v[it].y), fmaxf(v[it].z, v[it].w)));
+        if (greedy) {
+          int ab = INT_MAX;
+  #pragma unroll
+          for (int it = NV - 1; it >= 0; --it) {
+            const int k = k0 + it * 256 + lane * 4;
+            if (k + 3 < a.V && v[it].w == mb) ab = k + 3;
+            if (k + 2 < a.V && v[it].z == mb) ab = k + 2;
+            if (k + 1 < a.V && v[it].y == mb) ab = k + 1;
+            if (k < a.V && v[it].x == mb) ab = k;
+          }
+          if (mb > m || (mb == m && ab < arg)) arg = ab;
+          m = fmaxf(m, mb);
+        } else {
+          const float sc = invT * 1.44269504088896f;   // exp((z - mb) / T) = 2^((z - mb) sc)
+          auto ex = [&](float z) { return __builtin_amdgcn_exp2f((fmaxf(z, LOWEST) - mb) * sc); };
+          float sb = 0.0f;
+  #pragma unroll
+          for (int it = 0; it < NV; ++it) sb += (ex(v[it].x) + ex(v[it].y)) + (ex(v[it].z) + ex(v[it].w));
+          const float mn = fmaxf(m, mb);
+          s = rescaled_sum(s, m, mn, invT) + rescaled_sum((double)sb, mb, mn, invT);
+          m = mn;
+        }
+      }
+      const float M = wave_max(m);
+      RowPart* out = &a.scr[b].part[j][part];
+      if (greedy) {
+        arg = wave_min(m == M ? arg : INT_MAX);
+        if (lane == 0) { out->S = 0.0; out->m = M; out->arg = arg; }
+      } else {
+        s = wave_sum(rescaled_sum(s, m, M, invT));
+        if (lane == 0) { out->S = s; out->m = M; out->thr = -INFINITY; }
+      }
 }
 
 // Bound by the reads.  A wavefront takes every (grid x 4)-th part of the launch (part fastest, then row, then
@@ -802,73 +879,12 @@ static __global__ __launch_bounds__(256, 6) void row_parts_kernel(const AcceptAr
   auto load = [&](int item, float4 (&v)[NV]) {
     int part, j, b;
     locate(min(item, items - 1), part, j, b);
-    const float* z = accept_row(a, b, j);
-    const int k0 = part * a.part_len;
-    if (k0 + SAMPLE_PART <= a.V) {                   // (uniform) no entry past the row
-#pragma unroll
-      for (int it = 0; it < NV; ++it) {
-        const f32x4_any t = *reinterpret_cast<const f32x4_any*>(z + k0 + it * 256 + (unsigned)lane * 4u);
-        v[it] = make_float4(t[0], t[1], t[2], t[3]);
-      }
-    } else {
-#pragma unroll
-      for (int it = 0; it < NV; ++it) v[it] = load4_row(z, k0 + it * 256 + lane * 4, a.V);
-    }
+    load_part(a, b, j, part, lane, v);
   };
   auto reduce = [&](int item, float4 (&v)[NV]) {
     int part, j, b;
     locate(item, part, j, b);
-    const float T = a.prm ? a.prm[b].temperature : a.temperature;
-    const bool greedy = (T == 0.0f);
-    if (greedy && j > a.gamma) return;               // argmax sampling never looks at q rows
-    const float invT = greedy ? 1.0f : 1.0f / T;
-    float m = -INFINITY;
-    double s = 0.0;
-    int arg = INT_MAX;
-    const int k_end = min(a.V, (part + 1) * a.part_len);
-    for (int k0 = part * a.part_len; k0 < k_end; k0 += SAMPLE_PART) {
-      if (k0 != part * a.part_len) {                 // (parts longer than a block: more than 65536 entries a row)
-        const float* z = accept_row(a, b, j);
-#pragma unroll
-        for (int it = 0; it < NV; ++it) v[it] = load4_row(z, k0 + it * 256 + lane * 4, a.V);
-      }
-      // an entry that is not a number weighs nothing, as -inf does
-      constexpr float LOWEST = -3.402823466e38f;
-      float mb = -INFINITY;
-#pragma unroll
-      for (int it = 0; it < NV; ++it) mb = fmaxf(mb, fmaxf(fmaxf(v[it].x, v[it].y), fmaxf(v[it].z, v[it].w)));
-      if (greedy) {
-        int ab = INT_MAX;
-#pragma unroll
-        for (int it = NV - 1; it >= 0; --it) {
-          const int k = k0 + it * 256 + lane * 4;
-          if (k + 3 < a.V && v[it].w == mb) ab = k + 3;
-          if (k + 2 < a.V && v[it].z == mb) ab = k + 2;
-          if (k + 1 < a.V && v[it].y == mb) ab = k + 1;
-          if (k < a.V && v[it].x == mb) ab = k;
-        }
-        if (mb > m || (mb == m && ab < arg)) arg = ab;
-        m = fmaxf(m, mb);
-      } else {
-        const float sc = invT * 1.44269504088896f;   // exp((z - mb) / T) = 2^((z - mb) sc)
-        auto ex = [&](float z) { return __builtin_amdgcn_exp2f((fmaxf(z, LOWEST) - mb) * sc); };
-        float sb = 0.0f;
-#pragma unroll
-        for (int it = 0; it < NV; ++it) sb += (ex(v[it].x) + ex(v[it].y)) + (ex(v[it].z) + ex(v[it].w));
-        const float mn = fmaxf(m, mb);
-        s = rescaled_sum(s, m, mn, invT) + rescaled_sum((double)sb, mb, mn, invT);
-        m = mn;
-      }
-    }
-    const float M = wave_max(m);
-    RowPart* out = &a.scr[b].part[j][part];
-    if (greedy) {
-      arg = wave_min(m == M ? arg : INT_MAX);
-      if (lane == 0) { out->S = 0.0; out->m = M; out->arg = arg; }
-    } else {
-      s = wave_sum(rescaled_sum(s, m, M, invT));
-      if (lane == 0) { out->S = s; out->m = M; out->thr = -INFINITY; }
-    }
+    reduce_part(a, b, j, part, lane, v);
   };
   int item = (int)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (item >= items) return;
@@ -893,7 +909,7 @@ static __global__ __launch_bounds__(SAMPLE_THREADS) void row_filter_kernel(const
   const int j = blockIdx.x, b = blockIdx.y;
   const float T = a.prm ? a.prm[b].temperature : a.temperature;
   const bool greedy = (T == 0.0f);                   // (ignores the filters)
-  if (greedy && j > a.gamma) return;
+  if (greedy && j > a.gamma && a.beta == nullptr) return;
   float4 v[SAMPLE_REG_F4];
   load_row_regs(accept_row(a, b, j), a.V, v);
   const RowStat rs = row_stats_regs(v, greedy ? 1.0f : 1.0f / T, greedy, sm, a.prm ? a.prm[b].top_k : a.top_k, a.prm ? a.prm[b].top_p : a.top_p, a.V);
@@ -918,30 +934,22 @@ __device__ __forceinline__ RowStat join_parts(const RowPart* parts, int nparts, 
 }
 
 // beta_{i+1} = sum_x min(p(x) / l, q(x)): the probability that guess i+1 is accepted (section 3.1; with
-// lenience, appendix A.5), a wavefront per part of the row; accept_kernel adds the parts in order.
-// grid = (ceil(nparts / 4), gamma, rows).
-static __global__ __launch_bounds__(256) void beta_parts_kernel(const AcceptArgs a) {
-  const int lane = threadIdx.x & 63, i = blockIdx.y, b = blockIdx.z;
-  const int part = (int)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const float T = a.prm ? a.prm[b].temperature : a.temperature;
-  if (part >= a.nparts || T == 0.0f) return;
-  const float invT = 1.0f / T;
-  const double len = (double)(a.prm ? a.prm[b].lenience : a.lenience);
-  const int np = accept_filtered(a) ? 1 : a.nparts;  // parts the statistics were left in
-  const RowStat jp = join_parts(a.scr[b].part[i], np, false, invT), jq = join_parts(a.scr[b].part[a.gamma + 1 + i], np, false, invT);
+// lenience, appendix A.5); one part of the row, by a wavefront.
+__device__ __forceinline__ double beta_part(const AcceptArgs& a, int b, int i, int part, int lane, const RowStat& jp, const RowStat& jq, float invT, double len) {
   const double ip = (1.0 / jp.S) / len, iq = 1.0 / jq.S;
   const float *zp = accept_row(a, b, i), *zq = accept_row(a, b, a.gamma + 1 + i);
   double acc = 0.0;
   const int k_end = min(a.V, (part + 1) * a.part_len);
-  for (int k0 = part * a.part_len; k0 < k_end; k0 += SAMPLE_PART / 2) {
-    float4 vp[SAMPLE_PART / 512], vq[SAMPLE_PART / 512];
+  constexpr int NV = SAMPLE_PART / 256;
+  for (int k0 = part * a.part_len; k0 < k_end; k0 += SAMPLE_PART) {
+    float4 vp[NV], vq[NV];
 #pragma unroll
-    for (int it = 0; it < SAMPLE_PART / 512; ++it) {
+    for (int it = 0; it < NV; ++it) {
       vp[it] = load4_row(zp, k0 + it * 256 + lane * 4, a.V);
       vq[it] = load4_row(zq, k0 + it * 256 + lane * 4, a.V);
     }
 #pragma unroll
-    for (int it = 0; it < SAMPLE_PART / 512; ++it) {
+    for (int it = 0; it < NV; ++it) {
       const float p4[4] = {vp[it].x, vp[it].y, vp[it].z, vp[it].w}, q4[4] = {vq[it].x, vq[it].y, vq[it].z, vq[it].w};
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -952,13 +960,15 @@ static __global__ __launch_bounds__(256) void beta_parts_kernel(const AcceptArgs
       }
     }
   }
-  acc = wave_sum(acc);
-  if (lane == 0) a.scr[b].beta[i][part] = acc;
+  return wave_sum(acc);
 }
 
 // Decisions, draw, commit.  Every workgroup of a sequence joins the statistics and takes the decisions
 // itself (a few hundred words), then sums the weights of its chunks of row n (16 chunks_wave of
 // them); the last to arrive scans the totals and walks the chunk that holds u * total.
+// A small call (`self`: up to 48 parts a sequence, three a wavefront) is this one launch, one
+// workgroup a sequence: a second launch would cost it more than its work (5 sequences, gamma 5, vocabulary
+// 1216, 22 parts: 9.6 us a call against 12.8; one, gamma 4, vocabulary 8192, 72 parts: 15.3 against 11.0).
 // 64 sequences, gamma 7, vocabulary 32128 (123 MB), both launches: 34 us (row_parts_kernel 22: 5.6 TB/s, a
 // pure read's rate at this size); with one 1024-thread workgroup per row and then one per sequence it
 // was 44.  One sequence, gamma 4: 10.6 us against 16.1.
@@ -979,6 +989,28 @@ static __global__ __launch_bounds__(SAMPLE_THREADS) void accept_kernel(const Acc
   const int* x = st ? st->x : a.x + (size_t)b * gamma;
   const float* r = prm ? prm->uniforms + gamma : a.r + (size_t)b * gamma;   // (not read by argmax sampling)
   const float s = greedy ? 0.5f : (prm ? prm->uniforms[2 * gamma] : a.s[b]);
+  if ((int)blockIdx.x >= a.draw_wgs) {               // beta of guess i (after a.self's statistics: none of those launches come here)
+    const int i = (int)blockIdx.x - a.draw_wgs;
+    if (wave < 2) {
+      const RowStat rs = join_parts(scr->part[wave ? gamma + 1 + i : i], accept_filtered(a) ? 1 : a.nparts, greedy, invT);
+      if (lane == 0) srow[wave] = rs;
+    }
+    __syncthreads();
+    double t = 0.0;
+    if (greedy) {                                    // one-hot q at its argmax: accepted or not
+      const int aq = srow[1].arg;
+      t = ((len < 1.0) ? ((double)P[(size_t)i * V + aq] - (double)srow[0].m >= log_len) : (aq == srow[0].arg)) ? 1.0 : 0.0;
+    } else {
+      for (int part = wave; part < a.nparts; part += SAMPLE_THREADS / 64) {
+        const double w = beta_part(a, b, i, part, lane, srow[0], srow[1], invT, len);
+        if (lane == 0) sm.ctot[part] = w;
+      }
+      __syncthreads();
+      for (int part = 0; part < a.nparts; ++part) t += sm.ctot[part];
+    }
+    if (tid == 0) (st ? st->beta : a.beta + (size_t)b * gamma)[i] = (float)t;
+    return;
+  }
   // what the tests need arrives while the statistics are joined
   int xi = 0;
   float zpx = 0.0f, zqx = 0.0f, ri = 0.5f;
@@ -987,7 +1019,15 @@ static __global__ __launch_bounds__(SAMPLE_THREADS) void accept_kernel(const Acc
     zpx = P[(size_t)tid * V + xi];
     if (!greedy) { zqx = Q[(size_t)tid * V + xi]; ri = r[tid]; }
   }
-  for (int row = wave; row < nrows && !(greedy && row > gamma); row += SAMPLE_THREADS / 64) {
+  if (a.self) {
+    for (int item = wave; item < nrows * a.nparts; item += SAMPLE_THREADS / 64) {
+      float4 v[SAMPLE_PART / 256];
+      load_part(a, b, item / a.nparts, item % a.nparts, lane, v);
+      reduce_part(a, b, item / a.nparts, item % a.nparts, lane, v);
+    }
+    __syncthreads();
+  }
+  for (int row = wave; row < nrows && !(greedy && row > gamma && a.beta == nullptr); row += SAMPLE_THREADS / 64) {
     const RowStat rs = join_parts(scr->part[row], accept_filtered(a) ? 1 : a.nparts, greedy, invT);
     if (lane == 0) srow[row] = rs;
   }
@@ -1012,24 +1052,6 @@ static __global__ __launch_bounds__(SAMPLE_THREADS) void accept_kernel(const Acc
   }
   __syncthreads();
   const int n = sm.n;
-  float* beta = st ? st->beta : a.beta ? a.beta + (size_t)b * gamma : nullptr;
-  if (a.beta != nullptr && blockIdx.x == 0) {
-    if (!greedy) {
-      if (tid < gamma) {
-        double t = 0.0;
-        for (int i = 0; i < a.nparts; ++i) t += scr->beta[tid][i];
-        beta[tid] = (float)t;
-      }
-    } else {                              // one-hot q at its argmax: accepted or not
-      for (int i = 0; i < gamma; ++i) {
-        const int aq = row_stats(Q + (size_t)i * V, V, 1.0f, true, sm).arg;      // argmax sampling keeps no q statistics
-        if (tid == 0) {
-          const bool acc = (len < 1.0) ? ((double)P[(size_t)i * V + aq] - (double)srow[i].m >= log_len) : (aq == srow[i].arg);
-          beta[i] = acc ? 1.0f : 0.0f;
-        }
-      }
-    }
-  }
   int t = 0, fell_back = 0;
   if (greedy) {
     if (blockIdx.x != 0) return;
@@ -1061,7 +1083,7 @@ static __global__ __launch_bounds__(SAMPLE_THREADS) void accept_kernel(const Acc
         }
       }
     }
-    if (!last_to_post(scr->ticket, gridDim.x, &sm.flag)) return;
+    if (!last_to_post(scr->ticket, (unsigned)a.draw_wgs, &sm.flag)) return;
     for (int i = tid; i < nchunks; i += SAMPLE_THREADS) sm.ctot[i] = collect(&scr->tot[i]);
     __syncthreads();
     if (wave == 0) {
@@ -1098,6 +1120,50 @@ static __global__ __launch_bounds__(SAMPLE_THREADS) void accept_kernel(const Acc
   }
 }
 
+// Argmax sampling on explicit logits, without beta: only the target's rows count and nothing is drawn, so
+// one launch does it, a workgroup per row; the last of a sequence to arrive decides.
+// grid = (gamma + 1, rows).
+static __global__ __launch_bounds__(SAMPLE_THREADS) void accept_argmax_kernel(const AcceptArgs a) {
+  __shared__ SampleSmem sm;
+  const int j = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, V = a.V, gamma = a.gamma;
+  const float* z = accept_row(a, b, j);
+  float m = -INFINITY;
+  int arg = INT_MAX;
+  for (int k0 = 0; k0 < V; k0 += 4 * SAMPLE_REG_F4 * SAMPLE_THREADS) {
+    float4 v[SAMPLE_REG_F4];
+#pragma unroll
+    for (int it = 0; it < SAMPLE_REG_F4; ++it) v[it] = load4_row(z, k0 + (it * SAMPLE_THREADS + tid) * 4, V);
+#pragma unroll
+    for (int it = 0; it < SAMPLE_REG_F4; ++it) {
+      const float w[4] = {v[it].x, v[it].y, v[it].z, v[it].w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {                  // (ascending: the first that attains it stays)
+        const int k = k0 + (it * SAMPLE_THREADS + tid) * 4 + e;
+        const bool better = k < V && (w[e] > m || (w[e] == m && arg == INT_MAX));
+        m = better ? w[e] : m; arg = better ? k : arg;
+      }
+    }
+  }
+  const float M = block_reduce(m, sm.redf, OpMaxF(), -INFINITY) + 0.0f;            // (-0 counts as 0)
+  arg = block_reduce(m == M ? arg : INT_MAX, sm.redi, OpMinI(), INT_MAX);
+  SampleScratch* scr = a.scr + b;
+  if (tid == 0) post(&scr->tot[j], __longlong_as_double((long long)(((unsigned long long)__float_as_uint(M) << 32) | (unsigned)arg)));
+  if (!last_to_post(scr->ticket, (unsigned)gamma + 1u, &sm.flag)) return;
+  if (tid >= WAVE) return;
+  const unsigned long long w = (unsigned long long)__double_as_longlong(collect(&scr->tot[min(tid, gamma)]));
+  bool reject = false;
+  if (tid < gamma) {
+    const int xi = min(max(a.x[(size_t)b * gamma + tid], 0), V - 1);
+    // lenient argmax sampling: keep x when p(x) >= l * max p, p = softmax of the raw logits
+    reject = ((double)a.lenience < 1.0) ? ((double)accept_row(a, b, tid)[xi] - (double)__uint_as_float((unsigned)(w >> 32)) < a.log_lenience)
+                                        : ((int)(unsigned)w != xi);
+  }
+  const unsigned long long mask = __ballot(reject);
+  const int n = mask ? (__ffsll((long long)mask) - 1) : gamma;
+  const int t = __shfl((int)(unsigned)w, n, WAVE);
+  if (tid == 0) { a.out_n[b] = n; a.out_t[b] = t; }
+}
+
 static __global__ void clear_tickets_kernel(SampleScratch* scr, int rows) {
   const int b = (int)(blockIdx.x * blockDim.x + threadIdx.x);
   if (b < rows) scr[b].ticket[0] = 0u;
@@ -1107,18 +1173,23 @@ static __global__ void clear_tickets_kernel(SampleScratch* scr, int rows) {
 inline void launch_accept(hipStream_t stream, AcceptArgs a, int rows, int cus) {
   accept_parts(a);
   const int nrows = 2 * a.gamma + 1;
+  const int wgs = sample_workgroups(a.V);
+  if (a.prm == nullptr && a.temperature == 0.0f && a.beta == nullptr) {
+    hipLaunchKernelGGL(accept_argmax_kernel, dim3(a.gamma + 1, rows), dim3(SAMPLE_THREADS), 0, stream, a);
+    return;
+  }
+  a.self = !accept_filtered(a) && a.beta == nullptr && nrows * a.nparts <= 48 && wgs <= 4;
   if (accept_filtered(a)) {
     hipLaunchKernelGGL(row_filter_kernel, dim3(nrows, rows), dim3(SAMPLE_THREADS), 0, stream, a);
-  } else {
+  } else if (!a.self) {
     const int items = rows * nrows * a.nparts;
     hipLaunchKernelGGL(row_parts_kernel, dim3(min((items + 3) / 4, cus * ACCEPT_WAVES_CU / 4)), dim3(256), 0, stream, a, items,
                        (unsigned)((0x100000000ull + a.nparts - 1) / a.nparts), (unsigned)((0x100000000ull + nrows - 1) / nrows));
   }
-  if (a.beta != nullptr) hipLaunchKernelGGL(beta_parts_kernel, dim3((a.nparts + 3) / 4, a.gamma, rows), dim3(256), 0, stream, a);
   // more workgroups than CUs only repeat the decisions more often
-  const int wgs = sample_workgroups(a.V);
-  a.chunks_wave = min(wgs, (rows * wgs + cus - 1) / cus);
-  hipLaunchKernelGGL(accept_kernel, dim3((wgs + a.chunks_wave - 1) / a.chunks_wave, rows), dim3(SAMPLE_THREADS), 0, stream, a);
+  a.chunks_wave = a.self ? wgs : min(wgs, (rows * wgs + cus - 1) / cus);
+  a.draw_wgs = (wgs + a.chunks_wave - 1) / a.chunks_wave;
+  hipLaunchKernelGGL(accept_kernel, dim3(a.draw_wgs + (a.beta != nullptr ? a.gamma : 0), rows), dim3(SAMPLE_THREADS), 0, stream, a);
 }
 
 }  // namespace sd

@@ -66,7 +66,6 @@ struct Model {
   int batch = 1;               // sequences; each owns n_pages pages of every layer's pool
   int rows_cap = MAX_ROWS;     // activation rows: one group of MAX_ROWS rows per sequence at most, or rows_pass
   int rows_pass = 0;           // prompt rows one pass over the model takes (forward_rows); 0: MAX_ROWS-row passes only
-  float* rows_rs = nullptr;    // 1 / rms of the rows of such a pass
   bf16* zeros = nullptr;       // 1 KB of zeros
   int* page_table = nullptr;   // [batch][n_pages]
   bool pages_in_order = true;  // sequence b's table is b * n_pages + 0, 1, 2, ...; false (SD_FLAG_SCATTER_PAGES): back to front
@@ -184,7 +183,6 @@ void plan_model(Arena& A, Model& m, const sd_model_cfg& c, int page_size, int ba
                                                 (c.d_head + 2) * sizeof(float)));
   }
   if (m.rows_pass > 0) {
-    m.rows_rs = static_cast<float*>(A.take((size_t)m.rows_pass * sizeof(float)));
     m.zeros = static_cast<bf16*>(A.take(1024));
   }
   if (batch > 1) {
@@ -221,7 +219,7 @@ struct sd_ctx {
   hipGraphExec_t graphs[2 * (SD_MAX_GAMMA + 1)] = {};    // iterations: gamma, and again with filtered rows
   bool filtered() const { return sampling.top_k > 0 || (sampling.top_p > 0.0f && sampling.top_p < 1.0f); }
   hipGraphExec_t* graph_of(int gamma) { return &graphs[gamma + (filtered() ? SD_MAX_GAMMA + 1 : 0)]; }
-  hipGraphExec_t graph_baseline = nullptr;
+  hipGraphExec_t graph_baseline[2] = {};                 // plain decoding steps, and with filtered rows
   hipEvent_t ev[4] = {};
   std::vector<hipEvent_t> kev;       // 2 per Mp layer: around the gated FFN-in GEMM (SD_FLAG_PROFILE)
   bool time_ffn = false;             // set while the verify forward of a profiled step is enqueued
@@ -326,6 +324,7 @@ void launch_gemm_split_t(hipStream_t s, GemmArgs a, float* partial) {
   a.ksteps_per_wave = (KS + S - 1) / S;
   a.nchunk = S;
   a.partial = partial;
+  if (a.x_ks == 0) { a.x_ks = GEMM_WIDE_RT; a.x_slab = 1; }       // rows_to_fragments_kernel's layout
   constexpr int NS = (EPI == EPI_GATED) ? 2 : 1;
   const size_t lds = (size_t)SplitShape<T>::SUB * a.nrt * 64 * 8 * sizeof(T);
   // 8 tiles per workgroup, 12 when 8 would need a second round of workgroups and 12 does not
@@ -386,8 +385,8 @@ hipError_t allow_wide_lds() {
 // So does gemm_slices_kernel's with eight wavefronts and 4 x 4 tiles.
 template <int EPI>
 hipError_t allow_slices_lds() {
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_slices_kernel<EPI, 4, 4, 4>), hipFuncAttributeMaxDynamicSharedMemorySize, 8 * 16 * 1024);
-  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_slices_kernel<EPI, 4, 4, 3>), hipFuncAttributeMaxDynamicSharedMemorySize, 8 * 16 * 1024);
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_slices_kernel<EPI, 4, 4, 4>), hipFuncAttributeMaxDynamicSharedMemorySize, 8 * 16 * 1024 + 4 * 64);
+  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_slices_kernel<EPI, 4, 4, 3>), hipFuncAttributeMaxDynamicSharedMemorySize, 8 * 16 * 1024 + 4 * 64);
   return e;
 }
 
@@ -751,11 +750,6 @@ void forward(sd_ctx* c, Model& m, const Rows& rw, float* logits) {
   }
 }
 
-void forward_any(sd_ctx* c, Model& m, const Rows& rw, float* logits) {
-  if (m.cfg.dtype == SD_BF16) forward<bf16>(c, m, rw, logits);
-  else forward<float>(c, m, rw, logits);
-}
-
 // ---- products over many rows (kernels_prompt.h) ----
 template <int EPI, int NT, int MT>
 int rows_grid(RowsGemmArgs& a, int waves_n) {        // workgroups of NT weight tiles (per wavefront, waves_n of them) x MT slabs
@@ -773,7 +767,7 @@ template <int EPI, int NT, int MT>
 bool launch_gemm_slices_t(hipStream_t s, RowsGemmArgs a, int most) {
   const int grid = rows_grid<EPI, NT, MT>(a, 1);
   if (grid > most) return false;
-  const size_t lds = (size_t)a.nchunk * NT * MT * 1024;
+  const size_t lds = (size_t)a.nchunk * NT * MT * 1024 + MT * 64;
   if (a.kpw % 4 != 0 && a.kpw % 3 == 0) hipLaunchKernelGGL((gemm_slices_kernel<EPI, NT, MT, 3>), dim3(grid), dim3(64 * a.nchunk), lds, s, a);
   else hipLaunchKernelGGL((gemm_slices_kernel<EPI, NT, MT, 4>), dim3(grid), dim3(64 * a.nchunk), lds, s, a);
   return true;
@@ -806,28 +800,38 @@ void launch_gemm_rows(hipStream_t s, const Model& m, RowsGemmArgs a) {
   launch_gemm_slices_t<EPI, 4, 4>(s, a, 1 << 30);
 }
 
-// A pass of `rows` prompt rows of sequence `seq` from position `start` (bf16 models with the matrix-core
-// attention): the keys and values of every layer go to the cache.  Every row's arithmetic is forward()'s.
-// The last layer ends at its cache append: nothing reads what would follow.
-void forward_rows(sd_ctx* c, Model& m, int seq, int start, int rows) {
+// A residual product over two to six slabs whose weights are many: the split design's K chunks over
+// workgroups read the activations least often, and what its finish kernel costs (5 us) is small beside the
+// weights' own time.  64 rows, N 4096: K 14336 (117 MB) 31 us against 35 with the K-slices of one
+// workgroup, K 4096 (34 MB) 15 against 11.7.
+bool rows_split_ok(int rows, int K, int N) {
+  return rows <= GEMM_WIDE_RT * MAX_ROWS && pick_waves(K / 32) == 8 && (size_t)K * N * 2 >= ((size_t)64 << 20);
+}
+
+// forward() over more than one slab of rows (bf16 models with the matrix-core attention): the rows of
+// several sequences, or a pass of prompt rows.  Every row's arithmetic is forward()'s.  Activations pass from
+// product to product in fragment order.
+// Without `logits` (a prompt) the last layer ends at its cache append: nothing reads what would follow.
+void forward_rows(sd_ctx* c, Model& m, const Rows& rw, float* logits) {
   hipStream_t s = c->stream;
   const sd_model_cfg& f = m.cfg;
+  const int rows = rw.nseq * rw.rps;
   const int d = f.d_model, slabs = (rows + MAX_ROWS - 1) / MAX_ROWS, ss_stride = (d / 16) * 16;
   const bool rms = (f.arch != SD_ARCH_GPT);
   const int n_layers = (int)m.L.size();
+  const int skip = c->skip_ops;                      // measurement only (sd_time_forward)
   bf16 *xg = static_cast<bf16*>(m.xg), *attn = static_cast<bf16*>(m.attn), *ffn = static_cast<bf16*>(m.ffn), *q = static_cast<bf16*>(m.qbuf);
   auto cb = [](const void* p) { return static_cast<const bf16*>(p); };
-  hipLaunchKernelGGL((embed_kernel<bf16>), dim3(rows), dim3(256), 0, s, (int)ROWS_PREFILL, 0, c->d_state, m.prompt, start,
+  hipLaunchKernelGGL((embed_kernel<bf16>), dim3(rows), dim3(256), 0, s, rw.mode, rw.step, c->d_state, m.prompt, rw.start,
                      cb(m.tok_emb), cb(m.pos_emb), d, f.vocab, m.x, m.row_pos, cb(rms ? m.L[0].ln1g : nullptr),
-                     rms ? xg : (bf16*)nullptr, rms ? m.ss : nullptr, rows, seq, 0, m.row_seq, m.logit_row, ss_stride, 1);
+                     rms ? xg : (bf16*)nullptr, rms ? m.ss : nullptr, rw.rps, rw.seq0, rw.gamma, m.row_seq, m.logit_row, ss_stride, 1);
   int n_part = 1;
-  // the input of a product behind a norm: 1 / rms of the rows, or the normalised rows
+  // the input of a product behind a norm: the rows' partial sums, or the normalised rows
   auto normed = [&](const void* g, const void* b) {
     RowsGemmArgs a{};
     a.rows = rows; a.K = d; a.X = xg;
     if (rms) {
-      hipLaunchKernelGGL(rows_rs_kernel, dim3(slabs), dim3(256), 0, s, m.ss, n_part, ss_stride, d, f.norm_eps, m.rows_rs);
-      a.rs = m.rows_rs;
+      a.ss_in = m.ss; a.n_part = n_part; a.ss_stride = ss_stride; a.eps = f.norm_eps;
     } else {
       const int KS = d / 32, S = pick_waves(KS);
       hipLaunchKernelGGL(rows_layernorm_kernel, dim3(slabs), dim3(64 * S), 0, s, m.x, cb(g), cb(b), xg, rows, d, (KS + S - 1) / S, f.norm_eps);
@@ -835,51 +839,80 @@ void forward_rows(sd_ctx* c, Model& m, int seq, int start, int rows) {
     return a;
   };
   auto resid = [&](const void* W, const bf16* X, int K, const void* bias, const void* gain_next) {
-    RowsGemmArgs a{};
-    a.rows = rows; a.K = K; a.N = d; a.W = cb(W); a.X = X; a.bias = cb(bias); a.x = m.x;
-    if (rms) { a.xg = xg; a.gain_next = cb(gain_next); a.ss = m.ss; a.ss_stride = ss_stride; }
-    launch_gemm_rows<EPI_RESID>(s, m, a);
+    if (m.wide_partial != nullptr && rows_split_ok(rows, K, d)) {
+      GemmArgs o{};
+      o.W = W; o.X = X; o.bias = bias; o.K = K; o.N = d; o.out = m.x; o.ldo = d; o.nrt = slabs; o.R = MAX_ROWS;
+      o.R_last = rows - (slabs - 1) * MAX_ROWS; o.ss_stride = ss_stride; o.x_ks = 1; o.x_slab = K / 32;
+      if (rms) { o.xg_out = xg; o.xg_frag = 1; o.gain_next = gain_next; o.ss_out = m.ss; }
+      launch_gemm_split<bf16>(s, PRO_NONE, EPI_RESID, o, m.wide_partial);
+    } else {
+      RowsGemmArgs a{};
+      a.rows = rows; a.K = K; a.N = d; a.W = cb(W); a.X = X; a.bias = cb(bias); a.x = m.x;
+      if (rms) { a.xg = xg; a.gain_next = cb(gain_next); a.ss = m.ss; a.ss_stride = ss_stride; }
+      launch_gemm_rows<EPI_RESID>(s, m, a);
+    }
     n_part = d / 16;
   };
   for (int li = 0; li < n_layers; ++li) {
     const LayerW& l = m.L[li];
-    {
+    if (!(skip & SD_OP_QKV)) {
       RowsGemmArgs a = normed(l.ln1g, l.ln1b);
       a.W = cb(l.wqkv); a.bias = cb(l.bqkv); a.N = m.nq + 2 * m.nkv;
-      a.q = q; a.nq = m.nq; a.nkv = m.nkv; a.kv_pool = static_cast<bf16*>(l.kv); a.page_table = m.page_table + (size_t)seq * m.n_pages;
+      a.q = q; a.nq = m.nq; a.nkv = m.nkv; a.kv_pool = static_cast<bf16*>(l.kv); a.page_table = m.page_table;
+      a.row_seq = m.row_seq; a.pt_stride = m.n_pages;
       a.row_pos = m.row_pos; a.page_size = m.page_size; a.n_kv_heads = f.n_kv_heads; a.d_head = f.d_head; a.rope = m.rope;
       launch_gemm_rows<EPI_QKV>(s, m, a);
     }
-    if (li + 1 == n_layers) break;
+    if (logits == nullptr && li + 1 == n_layers) break;
     auto attention = [&](bool cross) {
       AttnArgs a{};
       a.q = q; a.out = attn; a.kv_pool = l.kv; a.page_table = m.page_table; a.page_size = m.page_size; a.n_pages = m.n_pages;
-      a.row_pos = m.row_pos; a.R = rows; a.H = f.n_heads; a.Hkv = f.n_kv_heads;
+      a.row_pos = m.row_pos; a.R = rw.rps; a.H = f.n_heads; a.Hkv = f.n_kv_heads;
       a.scale = (f.arch == SD_ARCH_T5DEC) ? 1.0f : 1.0f / sqrtf((float)f.d_head);
       a.bias_by_key = m.bias_by_key; a.bias_off = f.max_len - 1;
-      a.seq0 = seq; a.pt_stride = m.n_pages;
+      a.seq0 = rw.seq0; a.pt_stride = m.n_pages;
       if (cross) { a.cross = 1; a.ck = l.cross_k; a.cv = l.cross_v; a.kv_len = f.enc_len; a.scale = 1.0f; a.bias_by_key = nullptr; }
       a.out_frag = attn; a.frag_ks = 1; a.frag_slab = m.nq / 32;
-      launch_attn<bf16>(s, m, a, 1);
+      launch_attn<bf16>(s, m, a, rw.nseq);
     };
-    attention(false);
-    resid(l.wo, attn, m.nq, l.bo, (f.arch == SD_ARCH_T5DEC) ? l.lncg : l.ln2g);
+    if (!(skip & SD_OP_ATTN)) attention(false);
+    if (!(skip & SD_OP_O)) resid(l.wo, attn, m.nq, l.bo, (f.arch == SD_ARCH_T5DEC) ? l.lncg : l.ln2g);
+    else n_part = d / 16;
     if (f.arch == SD_ARCH_T5DEC) {
-      RowsGemmArgs a = normed(l.lncg, nullptr);
-      a.W = cb(l.cq); a.N = m.nq; a.out = q;
-      launch_gemm_rows<EPI_STORE>(s, m, a);
-      attention(true);
-      resid(l.co, attn, m.nq, nullptr, l.ln2g);
+      if (!(skip & SD_OP_CROSS_Q)) {
+        RowsGemmArgs a = normed(l.lncg, nullptr);
+        a.W = cb(l.cq); a.N = m.nq; a.out = q;
+        launch_gemm_rows<EPI_STORE>(s, m, a);
+      }
+      if (!(skip & SD_OP_CROSS_ATTN)) attention(true);
+      if (!(skip & SD_OP_CROSS_O)) resid(l.co, attn, m.nq, nullptr, l.ln2g);
     }
-    RowsGemmArgs a = normed(l.ln2g, l.ln2b);
-    a.W = cb(l.w1); a.N = f.d_ff; a.out = ffn;
-    if (!rms) { a.bias = cb(l.b1); launch_gemm_rows<EPI_ACT>(s, m, a); }
-    else {
-      a.W2 = cb(l.wu); a.act = (f.arch == SD_ARCH_T5DEC) ? ACT_GELU : ACT_SILU;
-      launch_gemm_rows<EPI_GATED>(s, m, a);
+    const bool timed = rms && c->time_ffn && &m == &c->p && 2 * li + 1 < (int)c->kev.size();
+    if (timed) hipEventRecord(c->kev[2 * li], s);
+    if (!(skip & SD_OP_FFN_IN)) {
+      RowsGemmArgs a = normed(l.ln2g, l.ln2b);
+      a.W = cb(l.w1); a.N = f.d_ff; a.out = ffn;
+      if (!rms) { a.bias = cb(l.b1); launch_gemm_rows<EPI_ACT>(s, m, a); }
+      else {
+        a.W2 = cb(l.wu); a.act = (f.arch == SD_ARCH_T5DEC) ? ACT_GELU : ACT_SILU;
+        launch_gemm_rows<EPI_GATED>(s, m, a);
+      }
     }
-    resid(l.w2, ffn, f.d_ff, l.b2, m.L[li + 1].ln1g);
+    if (timed) hipEventRecord(c->kev[2 * li + 1], s);
+    if (!(skip & SD_OP_FFN_OUT)) resid(l.w2, ffn, f.d_ff, l.b2, (li + 1 < n_layers) ? m.L[li + 1].ln1g : m.lnfg);
+    else n_part = d / 16;
   }
+  if (logits != nullptr && !(skip & SD_OP_HEAD)) {
+    RowsGemmArgs a = normed(m.lnfg, m.lnfb);
+    a.W = cb(m.head); a.N = f.vocab; a.logits = logits; a.out_row = m.logit_row; a.scale = f.logit_scale;
+    launch_gemm_rows<EPI_LOGITS>(s, m, a);
+  }
+}
+
+void forward_any(sd_ctx* c, Model& m, const Rows& rw, float* logits) {
+  if (m.rows_pass > 0 && rw.nseq * rw.rps > MAX_ROWS) forward_rows(c, m, rw, logits);
+  else if (m.cfg.dtype == SD_BF16) forward<bf16>(c, m, rw, logits);
+  else forward<float>(c, m, rw, logits);
 }
 
 // The cross-attention keys / values of every layer in one launch.
@@ -918,6 +951,11 @@ void cross_kv(sd_ctx* c, Model& m, const void* enc) {
 
 // One draw per sequence from the row at logits + b * seq_stride (mode 0: guess number `slot`; 1: commit).
 void launch_draw(sd_ctx* c, const float* logits, int uniform_idx, int mode, int slot, size_t seq_stride) {
+  if (c->filtered()) {
+    hipLaunchKernelGGL(sample_row_filter_kernel, dim3(c->batch), dim3(SAMPLE_THREADS), 0, c->stream, logits, c->p.cfg.vocab, c->d_params,
+                       uniform_idx, c->d_state, mode, slot, seq_stride);
+    return;
+  }
   hipLaunchKernelGGL(sample_row_split_kernel, dim3(sample_workgroups(c->p.cfg.vocab), c->batch), dim3(SAMPLE_THREADS), 0, c->stream,
                      logits, c->p.cfg.vocab, c->d_params, uniform_idx, c->d_state, mode, slot, seq_stride, c->d_scratch);
 }
@@ -1172,7 +1210,7 @@ extern "C" sd_status sd_load_models(sd_ctx** out, const sd_model_cfg* p_cfg, con
   if (allow_big_lds<bf16>() != hipSuccess || allow_big_lds<float>() != hipSuccess ||
       allow_wide_lds<bf16>() != hipSuccess || allow_wide_lds<float>() != hipSuccess ||
       allow_slices_lds<EPI_STORE>() != hipSuccess || allow_slices_lds<EPI_QKV>() != hipSuccess || allow_slices_lds<EPI_RESID>() != hipSuccess ||
-      allow_slices_lds<EPI_ACT>() != hipSuccess || allow_slices_lds<EPI_GATED>() != hipSuccess)
+      allow_slices_lds<EPI_ACT>() != hipSuccess || allow_slices_lds<EPI_GATED>() != hipSuccess || allow_slices_lds<EPI_LOGITS>() != hipSuccess)
     return bail(SD_EHIP, "cannot raise the LDS limit");
   std::string err;
   c->p.pages_in_order = c->q.pages_in_order = (rt->flags & SD_FLAG_SCATTER_PAGES) == 0;
@@ -1196,7 +1234,7 @@ extern "C" void sd_free(sd_ctx* c) {
   if (!c) return;
   if (c->stream) hipStreamSynchronize(c->stream);
   for (auto& g : c->graphs) if (g) hipGraphExecDestroy(g);
-  if (c->graph_baseline) hipGraphExecDestroy(c->graph_baseline);
+  for (auto& g : c->graph_baseline) if (g) hipGraphExecDestroy(g);
   for (auto& e : c->ev) if (e) hipEventDestroy(e);
   for (auto& e : c->kev) if (e) hipEventDestroy(e);
   if (c->h_state) hipHostFree(c->h_state);
@@ -1240,7 +1278,7 @@ extern "C" sd_status sd_prefill(sd_ctx* c, int32_t row, const int32_t* prompt, i
     }
     int s0 = 0;
     for (; m.rows_pass > 0 && n - 1 - s0 > MAX_ROWS; s0 += std::min(m.rows_pass, n - 1 - s0))
-      forward_rows(c, m, row, s0, std::min(m.rows_pass, n - 1 - s0));
+      forward_any(c, m, Rows{ROWS_PREFILL, 0, std::min(m.rows_pass, n - 1 - s0), s0, row, 1, 0}, nullptr);
     const int step = prefill_rows(m.cfg);
     for (; s0 < n - 1; s0 += step)
       forward_any(c, m, Rows{ROWS_PREFILL, 0, std::min(step, n - 1 - s0), s0, row, 1, 0}, nullptr);
@@ -1372,15 +1410,16 @@ extern "C" sd_status sd_step_baseline(sd_ctx* c, float temperature, const float*
   }
   const size_t pbytes = (size_t)B * sizeof(StepParams), sbytes = (size_t)B * sizeof(SeqState);
   if ((c->rt.flags & SD_FLAG_GRAPH) != 0) {
-    if (!c->graph_baseline) {
-      st = capture_graph(c, &c->graph_baseline, [&] {
+    hipGraphExec_t* ge = &c->graph_baseline[c->filtered() ? 1 : 0];
+    if (!*ge) {
+      st = capture_graph(c, ge, [&] {
         hipMemcpyAsync(c->d_params, c->h_params, pbytes, hipMemcpyHostToDevice, c->stream);
         enqueue_baseline(c);
         hipMemcpyAsync(c->h_state, c->d_state, sbytes, hipMemcpyDeviceToHost, c->stream);
       });
       if (st != SD_OK) return st;
     }
-    HIP_TRY(c, hipGraphLaunch(c->graph_baseline, c->stream));
+    HIP_TRY(c, hipGraphLaunch(*ge, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
   } else {
     HIP_TRY(c, hipMemcpyAsync(c->d_params, c->h_params, pbytes, hipMemcpyHostToDevice, c->stream));
@@ -1422,7 +1461,7 @@ extern "C" sd_status sd_set_flags(sd_ctx* c, int32_t flags) {
   if ((flags ^ c->rt.flags) & (SD_FLAG_BETA | SD_FLAG_SEPARATE_CROSS_Q)) {            // the captured iteration changes
     HIP_TRY(c, hipStreamSynchronize(c->stream));
     for (auto& g : c->graphs) if (g) { hipGraphExecDestroy(g); g = nullptr; }
-    if (c->graph_baseline) { hipGraphExecDestroy(c->graph_baseline); c->graph_baseline = nullptr; }
+    for (auto& g : c->graph_baseline) if (g) { hipGraphExecDestroy(g); g = nullptr; }
   }
   c->rt.flags = flags;
   return SD_OK;
@@ -1444,7 +1483,7 @@ extern "C" sd_status sd_set_copy_draft(sd_ctx* c, int32_t match) {
   if (match < 0 || match > SD_MAX_COPY_MATCH) return fail(c, SD_EINVAL, "match must lie in [0, SD_MAX_COPY_MATCH]");
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   for (auto& g : c->graphs) if (g) { hipGraphExecDestroy(g); g = nullptr; }     // the captured launches change
-  if (c->graph_baseline) { hipGraphExecDestroy(c->graph_baseline); c->graph_baseline = nullptr; }
+  for (auto& g : c->graph_baseline) if (g) { hipGraphExecDestroy(g); g = nullptr; }
   c->copy_match = match;
   return SD_OK;
 }

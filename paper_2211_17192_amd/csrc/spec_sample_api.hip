@@ -47,7 +47,8 @@ sd_status launch_spec_sample(const float* p_logits, const float* q_logits, const
                              sd::SampleScratch* scr, hipStream_t s_) {
   sd::AcceptArgs a{};
   a.p = p_logits; a.q = q_logits; a.x = x; a.r = r; a.s = s; a.gamma = gamma; a.V = vocab; a.temperature = temperature;
-  a.lenience = o.len; a.log_lenience = o.log_len; a.top_k = o.top_k; a.top_p = o.top_p;
+  a.lenience = o.len; a.log_lenience = o.log_len; 
+  if (temperature > 0.0f) { a.top_k = o.top_k; a.top_p = o.top_p; }            // (argmax sampling ignores the filters)
   a.scr = scr; a.out_n = out_n; a.out_t = out_t; a.beta = beta;
   sd::launch_accept(s_, a, rows, 256);   // (every gfx950 device has 256 CUs)
   return hipGetLastError() == hipSuccess ? SD_OK : SD_EHIP;
@@ -83,7 +84,7 @@ extern "C" sd_status sd_spec_sample(const float* p_logits, const float* q_logits
 // ---------------------------------------------------------------------------
 namespace {
 constexpr int STATIC_ROWS = SD_SPEC_SAMPLE_STATIC_MAX_ROWS;
-static __device__ __align__(256) unsigned char scratch[STATIC_ROWS * sizeof(sd::SampleScratch)];   // 12 MB
+static __device__ __align__(256) unsigned char scratch[STATIC_ROWS * sizeof(sd::SampleScratch)];   // 10 MB
 static_assert(sizeof(sd::SampleScratch) % 16 == 0, "the blocks keep their alignment");
 
 constexpr int STATIC_MAX_DEVICES = 64;
