@@ -301,31 +301,36 @@ __device__ __forceinline__ void rows_tile_of_block(const RowsGemmArgs& a, int& b
   bm = (id - bz * per) % a.mtiles; bn = (id - bz * per) / a.mtiles;
 }
 
-// A workgroup of four wavefronts takes NT * 64 features x MT * 16 rows.  A wavefront owns NT weight
-// tiles: their fragments go from memory into its registers and nowhere else, while the MT slabs of
-// activations pass through LDS and serve all four wavefronts.
+// A workgroup of NWV (4 or 8) wavefronts takes NT * 16 * NWV features x MT * 16 rows.  A wavefront owns NT
+// weight tiles: their fragments go from memory into its registers and nowhere else, while the MT slabs of
+// activations pass through LDS and serve all wavefronts.
 // Sums are gemm_kernel's, bit for bit: the k-steps of a K-slice accumulate from zero, the slices are
 // added in order to a running total.  That doubles the accumulators, so NT * MT is 16 at two wavefronts
-// a SIMD (256 registers).  The matrix cores bound it, then what a stall costs: a weight register is
-// reloaded for the next pass of SUB k-steps right after its last multiply, the next pass's activations
-// are in flight (registers) while this pass is multiplied and reach the other LDS buffer at its end,
-// one barrier per pass, and the two workgroups of a CU fill each other's prologue, epilogue and waits.
-// Measured (TFLOP/s; a library product of these sizes reaches 1100 - 1200 on this chip): 2000 rows, K 4096,
-// N 4096 953, N 6144 965, gated 14336 913; K 14336, N 4096 1035.  One wavefront a SIMD with NT 4, MT 8
-// (half the LDS reads per MFMA): 821, 667, 725, 1000: nothing hides its stalls.
-template <int EPI, int NT, int MT>
-static __global__ __launch_bounds__(256, 2) void gemm_rows_kernel(const RowsGemmArgs a) {
+// a SIMD (256 registers).  Matrix cores, LDS reads (8 KB per wavefront and k-step for 16 MFMAs, as much as the
+// pipe delivers in their time) and the way from L2 (NT KB a wavefront and MT KB a workgroup) are all near their
+// limits; then counts what a stall costs: a weight register is reloaded for the next pass of SUB
+// k-steps right after its last multiply, the next pass's activations are in flight (registers) while
+// this pass is multiplied and reach the other LDS buffer at its end, one barrier per pass.
+// Measured with 2000 rows (TFLOP/s; a library product of these sizes reaches 1100 - 1200 on this chip):
+//                                     N 4096   N 4096, K 14336   gated 14336   N 6144   (else K 4096)
+//   NT 2, MT 8, eight wavefronts        1115        1253             1022        874
+//   NT 2, MT 8, four (two workgroups)    938        1066              811        921
+//   NT 4, MT 8, four (one a SIMD)        821        1000              725        667
+// Eight read the activations once per CU instead of twice, but their workgroups fill the chip in coarser
+// rounds (N 6144: 384 workgroups, one round and a half).
+template <int EPI, int NT, int MT, int NWV>
+static __global__ __launch_bounds__(64 * NWV, 2) void gemm_rows_kernel(const RowsGemmArgs a) {
   constexpr int SUB = 4, NT_OUT = (EPI == EPI_GATED) ? NT / 2 : NT;
-  constexpr int NFRAG = SUB * MT * 64, XPT = NFRAG / 256;
+  constexpr int NFRAG = SUB * MT * 64, XPT = NFRAG / (64 * NWV);
   __shared__ __align__(16) bf16x8 xs[2][NFRAG];
   __shared__ float rs_s[MT][16];
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int KS = a.K >> 5, ntiles = a.N >> 4, slabs = (a.rows + 15) >> 4;
   int bn, bm, bz;
   rows_tile_of_block(a, bm, bn, bz);
   const bf16* wbase[NT];
-  int tile0 = (bn * 4 + wave) * NT_OUT;              // first output tile of this wavefront
+  int tile0 = (bn * NWV + wave) * NT_OUT;              // first output tile of this wavefront
 #pragma unroll
   for (int t = 0; t < NT; ++t) {
     const int ot = (EPI == EPI_GATED) ? (t >> 1) : t;
@@ -340,15 +345,16 @@ static __global__ __launch_bounds__(256, 2) void gemm_rows_kernel(const RowsGemm
     for (int m = 0; m < MT; ++m) { acc[t][m] = f32x4{0.f, 0.f, 0.f, 0.f}; tot[t][m] = f32x4{0.f, 0.f, 0.f, 0.f}; }
 
   bf16x8 wf[NT][SUB], xr[XPT];
-  static_assert(SUB == 4 && NFRAG == 256 * MT, "wavefront w stages k-step w of every slab");
-  const bf16x8* xsrc[XPT];                           // uniform: slab i of this workgroup
+  static_assert(SUB == 4 && XPT * NWV == 4 * MT, "wavefront w stages k-step w % 4 of XPT slabs");
+  const int kst = wave & 3, slab0 = (wave >> 2) * XPT;
+  const bf16x8* xsrc[XPT];                           // uniform
 #pragma unroll
-  for (int i = 0; i < XPT; ++i) xsrc[i] = reinterpret_cast<const bf16x8*>(a.X) + (size_t)min(bm * MT + i, slabs - 1) * KS * 64;
+  for (int i = 0; i < XPT; ++i) xsrc[i] = reinterpret_cast<const bf16x8*>(a.X) + (size_t)min(bm * MT + slab0 + i, slabs - 1) * KS * 64;
   // k-steps past a slice's end are multiplied with zeros, as gemm_kernel does: they come from a KB of zeros
   auto load_x = [&](int ksb, int len) {
 #pragma unroll
     for (int i = 0; i < XPT; ++i) {
-      const bf16x8* src = (wave < len) ? xsrc[i] + (size_t)(ksb + wave) * 64 : reinterpret_cast<const bf16x8*>(a.zeros);
+      const bf16x8* src = (kst < len) ? xsrc[i] + (size_t)(ksb + kst) * 64 : reinterpret_cast<const bf16x8*>(a.zeros);
       xr[i] = src[(unsigned)lane];
     }
   };
@@ -359,7 +365,7 @@ static __global__ __launch_bounds__(256, 2) void gemm_rows_kernel(const RowsGemm
   };
   auto store_x = [&](int buf) {
 #pragma unroll
-    for (int i = 0; i < XPT; ++i) xs[buf][tid + 256 * i] = xr[i];
+    for (int i = 0; i < XPT; ++i) xs[buf][((slab0 + i) * SUB + kst) * 64 + lane] = xr[i];
   };
   // the order of a pass, which the scheduler would otherwise rearrange so that every load sinks to its
   // end, a few MFMAs ahead of its use: the next k-step's fragments between this one's MFMAs, a
@@ -372,14 +378,14 @@ static __global__ __launch_bounds__(256, 2) void gemm_rows_kernel(const RowsGemm
       for (int m = 0; m < MT; ++m) {
         __builtin_amdgcn_sched_group_barrier(0x008, NT, 0);        // MFMAs of one slab
         if (u + 1 < SUB) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-        if (u == SUB - 1) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
+        if (u == SUB - 1 && m < XPT) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);
       }
       __builtin_amdgcn_sched_group_barrier(0x020, NT, 0);
     }
     __builtin_amdgcn_sched_group_barrier(0x020, XPT, 0);
   };
 
-  // 1 / rms of the rows: slab w (and w + 4) by wavefront w, its loads ahead of the stream's
+  // 1 / rms of the rows: slab w (of four wavefronts: and w + 4) by wavefront w, its loads ahead of the stream's
   SlabRms rms;
   const bool normed = a.ss_in != nullptr;            // (uniform)
   if (normed && wave < MT) rms.load(a, min(bm * MT + wave, slabs - 1), lane);
@@ -395,7 +401,7 @@ static __global__ __launch_bounds__(256, 2) void gemm_rows_kernel(const RowsGemm
   load_x(next, end_next - next);
   if (normed) {
     if (wave < MT) rms.finish(a, min(bm * MT + wave, slabs - 1), lane, rs_s[wave]);
-    if (wave + 4 < MT) {
+    if (NWV == 4 && wave + 4 < MT) {
       rms.load(a, min(bm * MT + wave + 4, slabs - 1), lane);
       rms.finish(a, min(bm * MT + wave + 4, slabs - 1), lane, rs_s[(wave + 4) % MT]);
     }

@@ -82,21 +82,36 @@ __device__ __forceinline__ float key_float(unsigned k) {
   return __uint_as_float((k & 0x80000000u) ? (k & 0x7fffffffu) : ~k);
 }
 
-// Entries k .. k + 3 of a row of V entries that starts at any 4-byte boundary (-inf past its end).
+// Entries k .. k + 3 of a row of V entries that starts at any 4-byte boundary (-inf past its end), in two
+// steps, so that several loads can leave before any is looked at: a 16-byte load within the row, then
+// the entries moved to their places.  Rows of fewer than four entries are read entry by entry.
 typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
-__device__ __forceinline__ float4 load4_row(const float* __restrict__ z, int k, int V) {
-  constexpr float NONE = -INFINITY;
-  if (V < 4) {                                       // uniform
-    return make_float4(k < V ? z[min(k, V - 1)] : NONE, k + 1 < V ? z[min(k + 1, V - 1)] : NONE, k + 2 < V ? z[min(k + 2, V - 1)] : NONE, NONE);
-  }
-  const f32x4_any t = *reinterpret_cast<const f32x4_any*>(z + min(k, V - 4));    // unconditional, within the row
-  const int over = k - (V - 4);                      // > 0: the group runs past the row's end
-  if ((V & 3) == 0) return over <= 0 ? make_float4(t[0], t[1], t[2], t[3]) : make_float4(NONE, NONE, NONE, NONE);
-  return make_float4(over <= 0 ? t[0] : over == 1 ? t[1] : over == 2 ? t[2] : over == 3 ? t[3] : NONE,
-                     over <= 0 ? t[1] : over == 1 ? t[2] : over == 2 ? t[3] : NONE,
-                     over <= 0 ? t[2] : over == 1 ? t[3] : NONE, over <= 0 ? t[3] : NONE);
+__device__ __forceinline__ f32x4_any raw4_row(const float* __restrict__ z, int k, int V) {
+  if (__builtin_expect(V >= 4, 1)) return *reinterpret_cast<const f32x4_any*>(z + min(k, V - 4));
+  return f32x4_any{z[min(k, V - 1)], z[min(k + 1, V - 1)], z[min(k + 2, V - 1)], 0.0f};
 }
-
+__device__ __forceinline__ float4 placed4_row(const f32x4_any& t, int k, int V) {
+  constexpr float NONE = -INFINITY;
+  const int over = (V >= 4) ? k - (V - 4) : 0;       // > 0: the group runs past the row's end
+  const float x = over <= 0 ? t[0] : over == 1 ? t[1] : over == 2 ? t[2] : t[3];
+  const float y = over <= 0 ? t[1] : over == 1 ? t[2] : t[3];
+  const float z = over <= 0 ? t[2] : t[3];
+  return make_float4(k < V ? x : NONE, k + 1 < V ? y : NONE, k + 2 < V ? z : NONE, k + 3 < V ? t[3] : NONE);
+}
+__device__ __forceinline__ float4 load4_row(const float* __restrict__ z, int k, int V) { return placed4_row(raw4_row(z, k, V), k, V); }
+// N groups, the m-th at k + m * step: all loads first.
+template <int N> __device__ __forceinline__ void load4_rows(const float* __restrict__ z, int k, int step, int V, float4 (&v)[N]) {
+  f32x4_any t[N];
+  if (__builtin_expect(V >= 4, 1)) {
+#pragma unroll
+    for (int m = 0; m < N; ++m) t[m] = *reinterpret_cast<const f32x4_any*>(z + min(k + m * step, V - 4));
+  } else {
+#pragma unroll
+    for (int m = 0; m < N; ++m) t[m] = raw4_row(z, k + m * step, V);
+  }
+#pragma unroll
+  for (int m = 0; m < N; ++m) v[m] = placed4_row(t[m], k + m * step, V);
+}
 // A sum of exponentials relative to m, brought to the maximum M >= m.  (Nothing above -inf: no weight;
 // m == M needs no factor, which keeps a row without any finite entry what it is, not a number.)
 __device__ __forceinline__ double rescaled_sum(double s, float m, float M, float invT) {
@@ -404,17 +419,17 @@ struct RowPair {
   int V;
 };
 
-__device__ __forceinline__ void load4(const RowPair& rp, int k, float (&zp)[4], float (&zq)[4]) {
-  const float4 p = load4_row(rp.zp, k, rp.V);
-  zp[0] = p.x; zp[1] = p.y; zp[2] = p.z; zp[3] = p.w;
-  if (rp.zq) {
-    const float4 q = load4_row(rp.zq, k, rp.V);
-    zq[0] = q.x; zq[1] = q.y; zq[2] = q.z; zq[3] = q.w;
-  }
+struct RawPair { f32x4_any p, q; };
+__device__ __forceinline__ RawPair load4(const RowPair& rp, int k) {
+  RawPair t;
+  t.p = raw4_row(rp.zp, k, rp.V);
+  t.q = raw4_row(rp.zq ? rp.zq : rp.zp, k, rp.V);    // (a plain row: the same line again, unused)
+  return t;
 }
 
-__device__ __forceinline__ void calc4(const RowPair& rp, int k, const float (&zp)[4], const float (&zq)[4],
-                                      double (&w)[4]) {
+__device__ __forceinline__ void calc4(const RowPair& rp, int k, const RawPair& t, double (&w)[4]) {
+  const float4 p4 = placed4_row(t.p, k, rp.V), q4 = placed4_row(t.q, k, rp.V);
+  const float zp[4] = {p4.x, p4.y, p4.z, p4.w}, zq[4] = {q4.x, q4.y, q4.z, q4.w};
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
     double p = (k + e < rp.V) ? (double)exp_scaled(zp[e], rp.mp, rp.invT, rp.tp) * rp.invSp : 0.0;
@@ -428,9 +443,7 @@ __device__ __forceinline__ void calc4(const RowPair& rp, int k, const float (&zp
 }
 
 __device__ __forceinline__ void weights4(const RowPair& rp, int k, double (&w)[4]) {
-  float zp[4], zq[4];
-  load4(rp, k, zp, zq);
-  calc4(rp, k, zp, zq, w);
+  calc4(rp, k, load4(rp, k), w);
 }
 
 // Wavefront 0: scan the chunk totals (lane l owns chunks [l*cpl, (l+1)*cpl)), find the
@@ -520,18 +533,18 @@ __device__ __forceinline__ int icdf_row(const float* zp, const RowStat& sp, cons
   __syncthreads();
   constexpr int CB = 4;                          // chunks whose loads a wavefront keeps in flight
   for (int cb = wave; cb < nchunks; cb += nw * CB) {
-    float zpv[CB][4], zqv[CB][4];
+    RawPair raw[CB];
 #pragma unroll
     for (int u = 0; u < CB; ++u) {
       const int c = cb + u * nw;
-      if (c < nchunks) load4(rp, c * SAMPLE_CHUNK + lane * 4, zpv[u], zqv[u]);
+      raw[u] = load4(rp, min(c, nchunks - 1) * SAMPLE_CHUNK + lane * 4);
     }
 #pragma unroll
     for (int u = 0; u < CB; ++u) {
       const int c = cb + u * nw;
       if (c < nchunks) {
         double w[4];
-        calc4(rp, c * SAMPLE_CHUNK + lane * 4, zpv[u], zqv[u], w);
+        calc4(rp, c * SAMPLE_CHUNK + lane * 4, raw[u], w);
         const double t = wave_sum((w[0] + w[1]) + (w[2] + w[3]));
         if (lane == 0) sm.ctot[c] = t;
       }
@@ -680,8 +693,8 @@ static __global__ __launch_bounds__(SAMPLE_THREADS) void sample_row_split_kernel
   const float T = prm->temperature;
   const bool greedy = (T == 0.0f);
   const float invT = greedy ? 1.0f : 1.0f / T;
-  float m = fmaxf(fmaxf(mine.x, mine.y), fmaxf(mine.z, mine.w));
   if (greedy) {
+    float m = fmaxf(fmaxf(mine.x, mine.y), fmaxf(mine.z, mine.w));
     m = block_reduce(m, sm.redf, OpMaxF(), -INFINITY) + 0.0f;                    // (-0 counts as 0)
     const int k = c * SAMPLE_CHUNK + lane * 4;
     int a = (mine.x == m) ? k : (mine.y == m) ? k + 1 : (mine.z == m) ? k + 2 : (mine.w == m) ? k + 3 : INT_MAX;
@@ -702,12 +715,12 @@ static __global__ __launch_bounds__(SAMPLE_THREADS) void sample_row_split_kernel
     }
     return;
   }
+  float m = -INFINITY;
   for (int k0 = 0; k0 < V; k0 += 4 * SAMPLE_REG_F4 * SAMPLE_THREADS) {
+    float4 v[SAMPLE_REG_F4];
+    load4_rows(logits, k0 + tid * 4, 4 * SAMPLE_THREADS, V, v);
 #pragma unroll
-    for (int it = 0; it < SAMPLE_REG_F4; ++it) {
-      const float4 v = load4_row(logits, k0 + (it * SAMPLE_THREADS + tid) * 4, V);
-      m = fmaxf(m, fmaxf(fmaxf(v.x, v.y), fmaxf(v.z, v.w)));
-    }
+    for (int it = 0; it < SAMPLE_REG_F4; ++it) m = fmaxf(m, fmaxf(fmaxf(v[it].x, v[it].y), fmaxf(v[it].z, v[it].w)));
   }
   m = block_reduce(m, sm.redf, OpMaxF(), -INFINITY);
   {
@@ -802,8 +815,7 @@ __device__ __forceinline__ void load_part(const AcceptArgs& a, int b, int j, int
       v[it] = make_float4(t[0], t[1], t[2], t[3]);
     }
   } else {
-#pragma unroll
-    for (int it = 0; it < SAMPLE_PART / 256; ++it) v[it] = load4_row(z, k0 + it * 256 + lane * 4, a.V);
+    load4_rows(z, k0 + lane * 4, 256, a.V, v);
   }
 }
 __device__ __forceinline__ void reduce_part(const AcceptArgs& a, int b, int j, int part, int lane, float4 (&v)[SAMPLE_PART / 256]) {
@@ -943,10 +955,16 @@ __device__ __forceinline__ double beta_part(const AcceptArgs& a, int b, int i, i
   constexpr int NV = SAMPLE_PART / 256;
   for (int k0 = part * a.part_len; k0 < k_end; k0 += SAMPLE_PART) {
     float4 vp[NV], vq[NV];
+    f32x4_any tp[NV], tq[NV];
 #pragma unroll
     for (int it = 0; it < NV; ++it) {
-      vp[it] = load4_row(zp, k0 + it * 256 + lane * 4, a.V);
-      vq[it] = load4_row(zq, k0 + it * 256 + lane * 4, a.V);
+      tp[it] = raw4_row(zp, k0 + it * 256 + lane * 4, a.V);
+      tq[it] = raw4_row(zq, k0 + it * 256 + lane * 4, a.V);
+    }
+#pragma unroll
+    for (int it = 0; it < NV; ++it) {
+      vp[it] = placed4_row(tp[it], k0 + it * 256 + lane * 4, a.V);
+      vq[it] = placed4_row(tq[it], k0 + it * 256 + lane * 4, a.V);
     }
 #pragma unroll
     for (int it = 0; it < NV; ++it) {
@@ -1066,18 +1084,16 @@ static __global__ __launch_bounds__(SAMPLE_THREADS) void accept_kernel(const Acc
     constexpr int CB = 4;                            // chunks whose loads a wavefront keeps in flight
     const int c0 = (int)blockIdx.x * SAMPLE_CHUNKS_WG * a.chunks_wave + wave;
     for (int i0 = 0; i0 < a.chunks_wave; i0 += CB) {
-      float zp[CB][4], zq[CB][4];
+      RawPair raw[CB];
 #pragma unroll
-      for (int i = 0; i < CB; ++i) {
-        const int c = c0 + (i0 + i) * SAMPLE_CHUNKS_WG;
-        if (i0 + i < a.chunks_wave && c < nchunks) load4(rp, c * SAMPLE_CHUNK + lane * 4, zp[i], zq[i]);
-      }
+      for (int i = 0; i < CB; ++i)
+        if (i0 + i < a.chunks_wave) raw[i] = load4(rp, min(c0 + (i0 + i) * SAMPLE_CHUNKS_WG, nchunks - 1) * SAMPLE_CHUNK + lane * 4);
 #pragma unroll
       for (int i = 0; i < CB; ++i) {
         const int c = c0 + (i0 + i) * SAMPLE_CHUNKS_WG;
         if (i0 + i < a.chunks_wave && c < nchunks) {
           double w[4];
-          calc4(rp, c * SAMPLE_CHUNK + lane * 4, zp[i], zq[i], w);
+          calc4(rp, c * SAMPLE_CHUNK + lane * 4, raw[i], w);
           const double tc = wave_sum((w[0] + w[1]) + (w[2] + w[3]));
           if (lane == 0) post(&scr->tot[c], tc);
         }
@@ -1131,8 +1147,7 @@ static __global__ __launch_bounds__(SAMPLE_THREADS) void accept_argmax_kernel(co
   int arg = INT_MAX;
   for (int k0 = 0; k0 < V; k0 += 4 * SAMPLE_REG_F4 * SAMPLE_THREADS) {
     float4 v[SAMPLE_REG_F4];
-#pragma unroll
-    for (int it = 0; it < SAMPLE_REG_F4; ++it) v[it] = load4_row(z, k0 + (it * SAMPLE_THREADS + tid) * 4, V);
+    load4_rows(z, k0 + tid * 4, 4 * SAMPLE_THREADS, V, v);
 #pragma unroll
     for (int it = 0; it < SAMPLE_REG_F4; ++it) {
       const float w[4] = {v[it].x, v[it].y, v[it].z, v[it].w};

@@ -758,10 +758,10 @@ int rows_grid(RowsGemmArgs& a, int waves_n) {        // workgroups of NT weight 
   a.mtiles = ((a.rows + 15) / 16 + MT - 1) / MT;
   return a.ntiles_wg * a.mtiles * a.batch;
 }
-template <int EPI, int MT>
+template <int EPI, int MT, int NWV>
 void launch_gemm_rows_t(hipStream_t s, RowsGemmArgs a) {
-  const int grid = rows_grid<EPI, 2, MT>(a, 4);
-  hipLaunchKernelGGL((gemm_rows_kernel<EPI, 2, MT>), dim3(grid), dim3(256), 0, s, a);
+  const int grid = rows_grid<EPI, 2, MT>(a, NWV);
+  hipLaunchKernelGGL((gemm_rows_kernel<EPI, 2, MT, NWV>), dim3(grid), dim3(64 * NWV), 0, s, a);
 }
 template <int EPI, int NT, int MT>
 bool launch_gemm_slices_t(hipStream_t s, RowsGemmArgs a, int most) {
@@ -772,12 +772,15 @@ bool launch_gemm_slices_t(hipStream_t s, RowsGemmArgs a, int most) {
   else hipLaunchKernelGGL((gemm_slices_kernel<EPI, NT, MT, 4>), dim3(grid), dim3(64 * a.nchunk), lds, s, a);
   return true;
 }
-// Which shape: measured on 256 CUs, us.
-//   The large one (128 features x 128 rows a workgroup, two workgroups a CU) from 1.6 workgroups a CU on,
-//   or where all rows fit one workgroup and the weights bound it: 2000 rows, N 6144, K 4096 (768
-//   workgroups) 104 against 132 with half the rows; 2000 x 3072 x 1024 (384) 23.1 against 19.9;
-//   128 x gated 14336 x 4096 (224, one row tile) 53 against 63.
-//   The medium one (half the rows) while it has 0.7 workgroups a CU: 256 x 6144 x 4096 (192) 28.7, K-slices
+// Which shape: measured on 256 CUs, us (rows x N x K).
+//   Eight wavefronts, 256 features x 128 rows a workgroup, one workgroup a CU, where the rounds of
+//   workgroups are at least 85 % full: 2000 rows, gated 14336 x 4096 (1792 workgroups) 460 against 515 - 580
+//   with four wavefronts; 2000 x 6144 x 4096 (384, 75 % full) 115 against 104 - 109.
+//   Four wavefronts, 128 features x 128 rows, two workgroups a CU, from 1.6 workgroups a CU on, or where all rows
+//   fit one workgroup and the weights bound it: 2000 x 6144 x 4096 (768) 104 against 132 with half the
+//   rows; 2000 x 3072 x 1024 (384) 23.1 against 19.9; 128 x gated 14336 x 4096 (224, one row tile) 53
+//   against 63; but 64 rows of it 46.7 against 43.8.
+//   Half the rows while there are 0.7 workgroups a CU: 256 x 6144 x 4096 (192) 28.7, K-slices
 //   34; 256 x 4096 x 4096 (128) 27.8, K-slices 19.0.
 //   Below that K is split over the wavefronts of a workgroup, with the smallest tile whose workgroups
 //   fit the chip in one round: 64 x 4096 x 4096 11.7 with 256 workgroups, 15.3 with 128 and with 512.
@@ -788,9 +791,11 @@ void launch_gemm_rows(hipStream_t s, const Model& m, RowsGemmArgs a) {
   const int KS = a.K / 32, S = pick_waves(KS);       // gemm_kernel's split of K: same sums
   a.kpw = (KS + S - 1) / S; a.nchunk = S; a.zeros = m.zeros;
   if (a.batch < 1) a.batch = 1;
-  const int large = rows_grid<EPI, 2, 8>(a, 4), row_tiles = a.mtiles, medium = rows_grid<EPI, 2, 4>(a, 4);
-  if (5 * large >= 8 * g_num_cus || (row_tiles == 1 && 4 * large >= 3 * g_num_cus)) return launch_gemm_rows_t<EPI, 8>(s, a);
-  if (10 * medium >= 7 * g_num_cus) return launch_gemm_rows_t<EPI, 4>(s, a);
+  const int eight = rows_grid<EPI, 2, 8>(a, 8), large = rows_grid<EPI, 2, 8>(a, 4), medium = rows_grid<EPI, 2, 4>(a, 4);
+  const bool one_tile = a.rows > 64 && a.rows <= 128;
+  if (a.rows > 128 && 100 * eight >= 85 * g_num_cus * ((eight + g_num_cus - 1) / g_num_cus)) return launch_gemm_rows_t<EPI, 8, 8>(s, a);
+  if (5 * large >= 8 * g_num_cus || (one_tile && 4 * large >= 3 * g_num_cus)) return launch_gemm_rows_t<EPI, 8, 4>(s, a);
+  if (10 * medium >= 7 * g_num_cus) return launch_gemm_rows_t<EPI, 4, 4>(s, a);
   const int most = (S == 4) ? g_num_cus * 3 / 2 : g_num_cus;
   constexpr int N1 = (EPI == EPI_GATED) ? 2 : 1;     // a gated product has two weight streams
   if (launch_gemm_slices_t<EPI, N1, 1>(s, a, most)) return;
