@@ -88,7 +88,7 @@ __device__ __forceinline__ float key_float(unsigned k) {
 typedef float f32x4_any __attribute__((ext_vector_type(4), aligned(4)));
 __device__ __forceinline__ f32x4_any raw4_row(const float* __restrict__ z, int k, int V) {
   if (__builtin_expect(V >= 4, 1)) return *reinterpret_cast<const f32x4_any*>(z + min(k, V - 4));
-  return f32x4_any{z[min(k, V - 1)], z[min(k + 1, V - 1)], z[min(k + 2, V - 1)], 0.0f};
+  return f32x4_any{z[min(k, V - 1)], z[min(k + 1, V - 1)], z[min(k + 2, V - 1)], z[V - 1]};
 }
 __device__ __forceinline__ float4 placed4_row(const f32x4_any& t, int k, int V) {
   constexpr float NONE = -INFINITY;
@@ -100,8 +100,7 @@ __device__ __forceinline__ float4 placed4_row(const f32x4_any& t, int k, int V) 
 }
 __device__ __forceinline__ float4 load4_row(const float* __restrict__ z, int k, int V) { return placed4_row(raw4_row(z, k, V), k, V); }
 // N groups, the m-th at k + m * step: all loads first.
-template <int N> __device__ __forceinline__ void load4_rows(const float* __restrict__ z, int k, int step, int V, float4 (&v)[N]) {
-  f32x4_any t[N];
+template <int N> __device__ __forceinline__ void raw4_rows(const float* __restrict__ z, int k, int step, int V, f32x4_any (&t)[N]) {
   if (__builtin_expect(V >= 4, 1)) {
 #pragma unroll
     for (int m = 0; m < N; ++m) t[m] = *reinterpret_cast<const f32x4_any*>(z + min(k + m * step, V - 4));
@@ -109,6 +108,10 @@ template <int N> __device__ __forceinline__ void load4_rows(const float* __restr
 #pragma unroll
     for (int m = 0; m < N; ++m) t[m] = raw4_row(z, k + m * step, V);
   }
+}
+template <int N> __device__ __forceinline__ void load4_rows(const float* __restrict__ z, int k, int step, int V, float4 (&v)[N]) {
+  f32x4_any t[N];
+  raw4_rows(z, k, step, V, t);
 #pragma unroll
   for (int m = 0; m < N; ++m) v[m] = placed4_row(t[m], k + m * step, V);
 }
@@ -121,10 +124,6 @@ __device__ __forceinline__ double rescaled_sum(double s, float m, float M, float
 // A row of up to 32768 entries fits the registers of one 1024-thread workgroup:
 // thread tid holds float4 number it * 1024 + tid, it = 0..7.  In terms of the
 // 256-entry scan chunks, v[it] of wavefront w is lane-slice `lane` of chunk it * 16 + w.
-__device__ __forceinline__ bool row_fits_regs(const float* z, int V) {
-  return ((V & 3) == 0) && ((reinterpret_cast<uintptr_t>(z) & 15) == 0) &&
-         (V <= SAMPLE_REG_F4 * 4 * SAMPLE_THREADS) && (blockDim.x == SAMPLE_THREADS);
-}
 __device__ __forceinline__ void load_row_regs(const float* __restrict__ z, int V, float4 (&v)[SAMPLE_REG_F4]) {
   const float4* z4 = reinterpret_cast<const float4*>(z);
   const int n4 = V >> 2, tid = threadIdx.x;
@@ -380,34 +379,6 @@ __device__ __forceinline__ RowStat row_stats_regs(const float4 (&v)[SAMPLE_REG_F
   return st;
 }
 
-// max / argmax / sum-of-exponentials of one logits row; every thread gets it.
-// Rows of up to 32768 entries are read from memory exactly once.
-__device__ __forceinline__ RowStat row_stats(const float* __restrict__ z, int V, float invT,
-                                             bool greedy, SampleSmem& sm, int top_k = 0, float top_p = 0.0f) {
-  const int tid = threadIdx.x, nt = blockDim.x;
-  RowStat st; st.arg = 0; st.S = 0.0; st.thr = -INFINITY; st.pad = 0.0f;
-  if (row_fits_regs(z, V)) {
-    float4 v[SAMPLE_REG_F4];
-    load_row_regs(z, V, v);
-    return row_stats_regs(v, invT, greedy, sm, top_k, top_p, V);
-  }
-  // longer rows: no top-k / nucleus (the host side refuses the combination)
-  float m = -INFINITY;
-  for (int i = tid; i < V; i += nt) m = fmaxf(m, z[i]);
-  m = block_reduce(m, sm.redf, OpMaxF(), -INFINITY);
-  st.m = m;
-  if (greedy) {
-    int a = INT_MAX;
-    for (int i = tid; i < V; i += nt) if (z[i] == m) a = min(a, i);
-    st.arg = block_reduce(a, sm.redi, OpMinI(), INT_MAX);
-    return st;
-  }
-  double s = 0.0;
-  for (int i = tid; i < V; i += nt) s += (double)exp_scaled(z[i], m, invT, -INFINITY);
-  st.S = block_reduce(s, sm.redd, OpSumD(), 0.0);
-  return st;
-}
-
 // The four weights of entries k..k+3: prob_p, minus prob_q clipped at zero when
 // a draft row is given (the unnormalised adjusted distribution of section 2.3).
 struct RowPair {
@@ -569,7 +540,7 @@ __device__ __forceinline__ int icdf_row(const float* zp, const RowStat& sp, cons
   return sm.token;
 }
 
-// Inverse-CDF draw from rows held in registers (see row_fits_regs for the layout):
+// Inverse-CDF draw from rows held in registers (see load_row_regs for the layout):
 // same arithmetic and summation order as icdf_row, without touching memory.
 __device__ __forceinline__ void weights_of(const float4& zp, const float4& zq, bool with_q, float mp, float mq,
                                            float tp, float tq, double invSp, double invSq, float invT,
@@ -717,10 +688,12 @@ static __global__ __launch_bounds__(SAMPLE_THREADS) void sample_row_split_kernel
   }
   float m = -INFINITY;
   for (int k0 = 0; k0 < V; k0 += 4 * SAMPLE_REG_F4 * SAMPLE_THREADS) {
-    float4 v[SAMPLE_REG_F4];
-    load4_rows(logits, k0 + tid * 4, 4 * SAMPLE_THREADS, V, v);
+    // A group past the row's end reads the row's last entries a second time, which leaves the maximum
+    // what it is: no entry is moved or masked (that was 1.5 us of 8.4 at 32128 entries).
+    f32x4_any v[SAMPLE_REG_F4];
+    raw4_rows(logits, k0 + tid * 4, 4 * SAMPLE_THREADS, V, v);
 #pragma unroll
-    for (int it = 0; it < SAMPLE_REG_F4; ++it) m = fmaxf(m, fmaxf(fmaxf(v[it].x, v[it].y), fmaxf(v[it].z, v[it].w)));
+    for (int it = 0; it < SAMPLE_REG_F4; ++it) m = fmaxf(m, fmaxf(fmaxf(v[it][0], v[it][1]), fmaxf(v[it][2], v[it][3])));
   }
   m = block_reduce(m, sm.redf, OpMaxF(), -INFINITY);
   {
