@@ -404,7 +404,7 @@ def sampler_workload(args):
         "config": {"workload": "isolated fused speculative-sampling kernel (configs[2]): 64 rows, vocab 32128, gamma 7, "
                                "target logits N(0,9), draft = target + N(0, sigma^2), sigma 0.5 / 1 / 2, temperature 1"},
         "per_sigma": per_sigma,
-        "roofline": {"bound": "hbm", "kernel": "spec_verify_kernel<1> + <2> (statistics pass over 15 logits rows per sequence, then the tail)",
+        "roofline": {"bound": "hbm", "kernel": "row_parts_kernel + accept_kernel (statistics of 15 logits rows per sequence, then decisions, draw and commit)",
                      "achieved": mid["GBps"], "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": mid["frac_of_hbm_peak"],
                      "bytes_per_launch": nbytes, "us_per_launch": mid["us_per_call"], "traffic": None},
         "cpu_baseline": None}), flush=True)

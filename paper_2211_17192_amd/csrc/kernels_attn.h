@@ -417,7 +417,8 @@ static __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_mma_kern
   const int hkv = blockIdx.x;
   const int seq = blockIdx.y;
   // z: key ranges x row groups, the last rows (which see the most keys) first
-  const int split = (int)blockIdx.z / a.groups, grp = a.groups - 1 - (int)blockIdx.z % a.groups;
+  int split = (int)blockIdx.z, grp = 0;
+  if (a.groups > 1) { split = (int)blockIdx.z / a.groups; grp = a.groups - 1 - (int)blockIdx.z % a.groups; }
   const int rs = grp * a.rows_per_wg;
   const int R = min(a.rows_per_wg, a.R - rs);
   const int r0 = seq * a.R + rs;
