@@ -101,3 +101,34 @@ def test_calls_of_any_size_share_one_scratch():
     for rows, gamma in ((2, 7), (64, 1), (5, 3), (64, 7), (1, 1)):
         zp, zq, x, r, s = synth.sampler_case(rows, gamma, 6000, 1.0, rows * 8 + gamma)
         check(zp, zq, x, r, s, 1.0, scratch=scratch)
+
+
+@pytest.mark.parametrize("vocab", [3, 1000, 1216, 32128, 65540])
+@pytest.mark.parametrize("masked", [False, True])
+def test_rows_of_the_types_lowest_value(vocab, masked):
+    """A target row whose every entry is the mask value -FLT_MAX is uniform over them: what pads the last part
+    of a row, and entries at -inf, weigh nothing beside it."""
+    gamma = 2
+    zp = np.full((2, gamma + 1, vocab), np.finfo(np.float32).min, np.float32)
+    zq = np.zeros((2, gamma, vocab), np.float32)
+    if masked:
+        zp[:, :, 1::3], zq[:, :, 1::3] = -np.inf, -np.inf
+    x = np.zeros((2, gamma), np.int32)
+    r, s = np.array([[0.997, 0.2], [0.5, 0.97]], np.float32), np.array([0.31373, 0.90411], np.float32)
+    check(zp, zq, x, r, s, 0.9)
+
+
+def test_denominator_sums_in_64_bits():
+    """A vocabulary that is no multiple of 4: one entry in sixteen weighs 1, the others 1.4e-8, less than half a
+    unit in the last place of a 32-bit sum that holds a 1.  Together they are 2.1e-7 of the row."""
+    vocab = 50257
+    z = np.full(vocab, -18.1, np.float32)
+    k = np.arange(vocab)
+    z[(k % 1024 < 256) & (k % 4 == 0)] = 0.0
+    zq = np.full((1, 1, vocab), -60.0, np.float32)
+    zq[0, 0, 0] = 0.0                                 # the draft's mass on one of the heavy entries: beta = p(0) = 1 / S
+    _, _, beta = call(np.stack([z, z])[None], zq, np.zeros((1, 1), np.int32), np.full((1, 1), 0.5, np.float32),
+                      np.full(1, 0.5, np.float32), 1.0)
+    exact = 1.0 / np.exp(z.astype(np.float64)).sum()
+    # half a unit in the last place of the fp32 output (6e-8) and the exponentials' error on 2e-7 of the sum
+    assert abs(beta[0, 0] / exact - 1.0) <= 7e-8
