@@ -993,8 +993,8 @@ static __global__ __launch_bounds__(SAMPLE_THREADS) void accept_kernel(const Acc
     __syncthreads();
     double t = 0.0;
     if (greedy) {                                    // one-hot q at its argmax: accepted or not
-      const int aq = srow[1].arg;
-      t = ((len < 1.0) ? ((double)P[(size_t)i * V + aq] - (double)srow[0].m >= log_len) : (aq == srow[0].arg)) ? 1.0 : 0.0;
+      const int aq = srow[1].arg;                    // (INT_MAX: no entry of the draft's row is a number)
+      t = ((len < 1.0) ? (aq < V && (double)P[(size_t)i * V + min(aq, V - 1)] - (double)srow[0].m >= log_len) : (aq == srow[0].arg)) ? 1.0 : 0.0;
     } else {
       for (int part = wave; part < a.nparts; part += SAMPLE_THREADS / 64) {
         const double w = beta_part(a, b, i, part, lane, srow[0], srow[1], invT, len);

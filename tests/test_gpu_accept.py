@@ -132,3 +132,16 @@ def test_denominator_sums_in_64_bits():
     exact = 1.0 / np.exp(z.astype(np.float64)).sum()
     # half a unit in the last place of the fp32 output (6e-8) and the exponentials' error on 2e-7 of the sum
     assert abs(beta[0, 0] / exact - 1.0) <= 7e-8
+
+
+def test_lenient_argmax_beta_of_a_draft_row_without_a_number():
+    """No entry of such a row attains its maximum: the guess counts as refused, and no logit is looked up for it."""
+    vocab, gamma = 1000, 2
+    zp, zq, x, r, s = synth.sampler_case(2, gamma, vocab, 1.0, 3)
+    zq[1, 0] = np.nan
+    n, t, beta = call(zp, zq, x, r, s, 0.0, lenience=0.5)
+    for b in range(2):
+        assert (n[b], t[b]) == sampling.accept_and_resample_argmax_lenient(zp[b], x[b], 0.5)
+        for i in range(gamma):
+            keep = (b, i) != (1, 0) and zp[b, i, np.argmax(zq[b, i])] - zp[b, i].max() >= np.log(np.float64(np.float32(0.5)))
+            assert beta[b, i] == float(keep)
