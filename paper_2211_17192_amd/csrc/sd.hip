@@ -382,11 +382,33 @@ hipError_t allow_wide_lds() {
   return e;
 }
 
-// So does gemm_slices_kernel's with eight wavefronts and 4 x 4 tiles.
+// So does gemm_slices_kernel's in some of its shapes (NT, MT): every shape that launch_gemm_rows may take is
+// listed here, and each gets the most it asks for, at eight wavefronts.
+constexpr size_t slices_lds_bytes(int S, int NT, int MT) { return (size_t)S * NT * MT * 1024 + MT * 64; }
+#define SD_SLICES_SHAPES(X) X(1, 1) X(2, 1) X(1, 2) X(2, 2) X(2, 4) X(4, 4)
+constexpr bool slices_shape_listed(int nt, int mt) {
+#define SD_CASE(NT, MT) if (nt == NT && mt == MT) return true;
+  SD_SLICES_SHAPES(SD_CASE)
+#undef SD_CASE
+  return false;
+}
+template <int EPI, int NT, int MT>
+hipError_t allow_slices_lds_t() {
+  constexpr size_t bytes = slices_lds_bytes(8, NT, MT);
+  static_assert(bytes <= 160 * 1024, "gemm_slices_kernel: dynamic LDS");
+  if constexpr (bytes <= 64 * 1024) return hipSuccess;
+  else {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_slices_kernel<EPI, NT, MT, 4>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_slices_kernel<EPI, NT, MT, 3>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    return e;
+  }
+}
 template <int EPI>
 hipError_t allow_slices_lds() {
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_slices_kernel<EPI, 4, 4, 4>), hipFuncAttributeMaxDynamicSharedMemorySize, 8 * 16 * 1024 + 4 * 64);
-  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_slices_kernel<EPI, 4, 4, 3>), hipFuncAttributeMaxDynamicSharedMemorySize, 8 * 16 * 1024 + 4 * 64);
+  hipError_t e = hipSuccess;
+#define SD_CASE(NT, MT) if (e == hipSuccess) e = allow_slices_lds_t<EPI, NT, MT>();
+  SD_SLICES_SHAPES(SD_CASE)
+#undef SD_CASE
   return e;
 }
 
@@ -765,9 +787,10 @@ void launch_gemm_rows_t(hipStream_t s, RowsGemmArgs a) {
 }
 template <int EPI, int NT, int MT>
 bool launch_gemm_slices_t(hipStream_t s, RowsGemmArgs a, int most) {
+  static_assert(slices_shape_listed(NT, MT), "allow_slices_lds raises the LDS limit of the listed shapes only");
   const int grid = rows_grid<EPI, NT, MT>(a, 1);
   if (grid > most) return false;
-  const size_t lds = (size_t)a.nchunk * NT * MT * 1024 + MT * 64;
+  const size_t lds = slices_lds_bytes(a.nchunk, NT, MT);
   if (a.kpw % 4 != 0 && a.kpw % 3 == 0) hipLaunchKernelGGL((gemm_slices_kernel<EPI, NT, MT, 3>), dim3(grid), dim3(64 * a.nchunk), lds, s, a);
   else hipLaunchKernelGGL((gemm_slices_kernel<EPI, NT, MT, 4>), dim3(grid), dim3(64 * a.nchunk), lds, s, a);
   return true;
