@@ -145,3 +145,32 @@ def test_lenient_argmax_beta_of_a_draft_row_without_a_number():
         for i in range(gamma):
             keep = (b, i) != (1, 0) and zp[b, i, np.argmax(zq[b, i])] - zp[b, i].max() >= np.log(np.float64(np.float32(0.5)))
             assert beta[b, i] == float(keep)
+
+
+# a thread takes 1, 2, 4 or 8 groups of four entries of a row, and longer rows in several passes
+@pytest.mark.parametrize("temperature", [0.0, 0.9])
+@pytest.mark.parametrize("vocab", [3, 5, 255, 1026, 4096, 4097, 8193, 16390, 32768, 32771, 140001])
+def test_calls_without_beta(vocab, temperature):
+    """Without beta: argmax sampling is one launch, a small call of any temperature is one launch.  Logits on a
+    coarse grid, so that maxima tie across threads, parts and passes; masked entries; both zeros."""
+    from paper_2211_17192_amd import binding
+    rows, gamma = 3, 2
+    zp, zq, x, r, s = synth.sampler_case(rows, gamma, vocab, 1.0, vocab)
+    zp, zq = np.round(zp), np.round(zq)
+    zp[1, :, : vocab // 2] = -np.inf                                       # whole wavefronts without a finite entry
+    zp[2, 1] = np.where(np.arange(vocab) % 2 == 0, -0.0, 0.0)              # maximum: the first entry, a negative zero
+    zq[1:] = zp[1:, :gamma]                                                # (guesses that are kept)
+    if temperature == 0.0:
+        x = np.argmax(zq, -1).astype(np.int32)
+    else:
+        x[1] = np.maximum(x[1], vocab // 2)
+    n_g, t_g = (v.cpu().numpy() for v in binding.spec_sample(*(torch.from_numpy(np.ascontiguousarray(v)).cuda() for v in (zp, zq, x, r, s)), temperature))
+    for b in range(rows):
+        n, t, info = sampling.accept_and_resample_from_logits(zp[b], zq[b], x[b], r[b], s[b], temperature)
+        if temperature == 0.0 or (n_g[b], t_g[b]) == (n, t):
+            assert (n_g[b], t_g[b]) == (n, t)
+        elif n_g[b] != n:
+            assert info["margins"][min(n_g[b], n)] < 1e-3
+        else:
+            p, q = (np.stack([sampling.standardise(z, temperature) for z in v[b]]) for v in (zp, zq))
+            assert sampling.icdf_edge_distance(p[n] if n == gamma else sampling.adjusted_distribution(p[n], q[n]), s[b], int(t_g[b])) < 1e-5
