@@ -1002,12 +1002,11 @@ __device__ __forceinline__ double beta_part(const AcceptArgs& a, int b, int i, i
 // Decisions, draw, commit.  Every workgroup of a sequence joins the statistics and takes the decisions
 // itself (a few hundred words), then sums the weights of its chunks of row n (16 chunks_wave of
 // them); the last to arrive scans the totals and walks the chunk that holds u * total.
-// A small call (`self`: up to 48 parts a sequence, three a wavefront) is this one launch, one
-// workgroup a sequence: a second launch would cost it more than its work (5 sequences, gamma 5, vocabulary
-// 1216, 22 parts: 9.6 us a call against 12.8; one, gamma 4, vocabulary 8192, 72 parts: 15.3 against 11.0).
-// 64 sequences, gamma 7, vocabulary 32128 (123 MB), both launches: 34 us (row_parts_kernel 22: 5.6 TB/s, a
-// pure read's rate at this size); with one 1024-thread workgroup per row and then one per sequence it
-// was 44.  One sequence, gamma 4: 10.6 us against 16.1.
+// A small call (`self`, launch_accept) is this one launch, one workgroup a sequence: a second launch would
+// cost it more than its work.
+// 64 sequences, gamma 7, vocabulary 32128 (123 MB), both launches, calls back to back in a graph: 35.7 us
+// (row_parts_kernel 22: 5.6 TB/s, a pure read's rate at this size); with one 1024-thread workgroup per row and
+// then one per sequence it was 42.2.  One sequence, gamma 4: 11.1 us against 16.8.
 static __global__ __launch_bounds__(SAMPLE_THREADS) void accept_kernel(const AcceptArgs a) {
   __shared__ SampleSmem sm;
   __shared__ RowStat srow[2 * SAMPLE_MAX_GAMMA + 1];
@@ -1222,7 +1221,10 @@ inline void launch_accept(hipStream_t stream, AcceptArgs a, int rows, int cus) {
     launch_argmax(stream, a, rows);
     return;
   }
-  a.self = !accept_filtered(a) && a.beta == nullptr && nrows * a.nparts <= 48 && wgs <= 4;
+  // one launch: up to one part a wavefront, and up to three where the sequences themselves fill the chip
+  // (us, one launch against two: 12 parts, one sequence 8.0 / 8.7; 28 parts 10.0 / 9.2; 48 parts 16.3 / 10.3;
+  // 28 parts, 200 sequences 11.0 / 12.7; 48 parts 19.6 / 22.9)
+  a.self = !accept_filtered(a) && a.beta == nullptr && nrows * a.nparts <= (2 * rows > cus ? 48 : 16) && wgs <= 4;
   if (accept_filtered(a)) {
     hipLaunchKernelGGL(row_filter_kernel, dim3(nrows, rows), dim3(SAMPLE_THREADS), 0, stream, a);
   } else if (!a.self) {
@@ -1230,8 +1232,10 @@ inline void launch_accept(hipStream_t stream, AcceptArgs a, int rows, int cus) {
     hipLaunchKernelGGL(row_parts_kernel, dim3(min((items + 3) / 4, cus * ACCEPT_WAVES_CU / 4)), dim3(256), 0, stream, a, items,
                        (unsigned)((0x100000000ull + a.nparts - 1) / a.nparts), (unsigned)((0x100000000ull + nrows - 1) / nrows));
   }
-  // more workgroups than CUs only repeat the decisions more often
-  a.chunks_wave = a.self ? wgs : min(wgs, (rows * wgs + cus - 1) / cus);
+  // as many workgroups a sequence as fit the CUs in one round; more only repeat the decisions more often
+  // (200 sequences, gamma 1, vocabulary 32128: 35.3 us with one, 49.1 with a second that takes the last chunks)
+  const int most = a.self ? 1 : min(wgs, max(1, cus / rows));
+  a.chunks_wave = (wgs + most - 1) / most;
   a.draw_wgs = (wgs + a.chunks_wave - 1) / a.chunks_wave;
   hipLaunchKernelGGL(accept_kernel, dim3(a.draw_wgs + (a.beta != nullptr ? a.gamma : 0), rows), dim3(SAMPLE_THREADS), 0, stream, a);
 }
