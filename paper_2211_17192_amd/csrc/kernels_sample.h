@@ -964,39 +964,90 @@ __device__ __forceinline__ RowStat join_parts(const RowPart* parts, int nparts, 
 }
 
 // beta_{i+1} = sum_x min(p(x) / l, q(x)): the probability that guess i+1 is accepted (section 3.1; with
-// lenience, appendix A.5); one part of the row, by a wavefront.
-__device__ __forceinline__ double beta_part(const AcceptArgs& a, int b, int i, int part, int lane, const RowStat& jp, const RowStat& jq, float invT, double len) {
-  const double ip = (1.0 / jp.S) / len, iq = 1.0 / jq.S;
-  const float *zp = accept_row(a, b, i), *zq = accept_row(a, b, a.gamma + 1 + i);
+// lenience, appendix A.5).  A wavefront takes SAMPLE_PART entries of both rows at a time.
+struct BetaPart { f32x4_any p[SAMPLE_PART / 256], q[SAMPLE_PART / 256]; };
+__device__ __forceinline__ void beta_load(BetaPart& t, const float* zp, const float* zq, int k0, int V, int lane) {
+  if (k0 + SAMPLE_PART <= V) {                       // (uniform) no entry past the rows
+#pragma unroll
+    for (int it = 0; it < SAMPLE_PART / 256; ++it) {
+      t.p[it] = *reinterpret_cast<const f32x4_any*>(zp + k0 + it * 256 + (unsigned)lane * 4u);
+      t.q[it] = *reinterpret_cast<const f32x4_any*>(zq + k0 + it * 256 + (unsigned)lane * 4u);
+    }
+  } else {
+    raw4_rows(zp, k0 + lane * 4, 256, V, t.p);
+    raw4_rows(zq, k0 + lane * 4, 256, V, t.q);
+  }
+}
+__device__ __forceinline__ double beta_sum(const BetaPart& t, int k0, int V, int lane, const RowStat& jp, const RowStat& jq, double ip, double iq, float invT) {
   double acc = 0.0;
-  const int k_end = min(a.V, (part + 1) * a.part_len);
-  constexpr int NV = SAMPLE_PART / 256;
-  for (int k0 = part * a.part_len; k0 < k_end; k0 += SAMPLE_PART) {
-    float4 vp[NV], vq[NV];
-    f32x4_any tp[NV], tq[NV];
+  auto add = [&](float z, float w) {
+    const double pv = (double)exp_scaled(z, jp.m, invT, jp.thr) * ip;
+    const double qv = (double)exp_scaled(w, jq.m, invT, jq.thr) * iq;
+    acc += pv < qv ? pv : qv;
+  };
 #pragma unroll
-    for (int it = 0; it < NV; ++it) {
-      tp[it] = raw4_row(zp, k0 + it * 256 + lane * 4, a.V);
-      tq[it] = raw4_row(zq, k0 + it * 256 + lane * 4, a.V);
-    }
+  for (int it = 0; it < SAMPLE_PART / 256; ++it) {
+    const int k = k0 + it * 256 + lane * 4;
+    if (k0 + SAMPLE_PART <= V) {                     // (uniform) none to move or to leave out
 #pragma unroll
-    for (int it = 0; it < NV; ++it) {
-      vp[it] = placed4_row(tp[it], k0 + it * 256 + lane * 4, a.V);
-      vq[it] = placed4_row(tq[it], k0 + it * 256 + lane * 4, a.V);
-    }
+      for (int e = 0; e < 4; ++e) add(t.p[it][e], t.q[it][e]);
+    } else {
+      const float4 p = placed4_row(t.p[it], k, V), q = placed4_row(t.q[it], k, V);
+      const float p4[4] = {p.x, p.y, p.z, p.w}, q4[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
-    for (int it = 0; it < NV; ++it) {
-      const float p4[4] = {vp[it].x, vp[it].y, vp[it].z, vp[it].w}, q4[4] = {vq[it].x, vq[it].y, vq[it].z, vq[it].w};
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        if (k0 + it * 256 + lane * 4 + e >= k_end) continue;
-        const double pv = (double)exp_scaled(p4[e], jp.m, invT, jp.thr) * ip;
-        const double qv = (double)exp_scaled(q4[e], jq.m, invT, jq.thr) * iq;
-        acc += pv < qv ? pv : qv;
-      }
+      for (int e = 0; e < 4; ++e)
+        if (k + e < V) add(p4[e], q4[e]);
     }
   }
   return wave_sum(acc);
+}
+
+// One guess's, by a workgroup of NT threads; jr: two entries, ctot: one per SAMPLE_PART entries of the row.
+template <int NT>
+__device__ __forceinline__ void beta_guess(const AcceptArgs& a, int b, int i, RowStat* jr, double* ctot) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, V = a.V, gamma = a.gamma;
+  const StepParams* prm = a.prm ? a.prm + b : nullptr;
+  const float T = prm ? prm->temperature : a.temperature;
+  const bool greedy = (T == 0.0f);
+  const float invT = greedy ? 1.0f : 1.0f / T;
+  const double len = (double)(prm ? prm->lenience : a.lenience), log_len = prm ? prm->log_lenience : a.log_lenience;
+  const float *zp = accept_row(a, b, i), *zq = accept_row(a, b, gamma + 1 + i);
+  BetaPart bp;
+  if (!greedy && wave * SAMPLE_PART < V) beta_load(bp, zp, zq, wave * SAMPLE_PART, V, lane);       // arrives while the statistics are joined
+  if (wave < 2) {
+    const RowStat rs = join_parts(a.scr[b].part[wave ? gamma + 1 + i : i], accept_filtered(a) ? 1 : a.nparts, greedy, invT);
+    if (lane == 0) jr[wave] = rs;
+  }
+  __syncthreads();
+  const RowStat jp = jr[0], jq = jr[1];
+  double t = 0.0;
+  if (greedy) {                                      // one-hot q at its argmax: accepted or not
+    const int aq = jq.arg;                           // (INT_MAX: no entry of the draft's row is a number)
+    t = ((len < 1.0) ? (aq < V && (double)zp[min(aq, V - 1)] - (double)jp.m >= log_len) : (aq == jp.arg)) ? 1.0 : 0.0;
+  } else {
+    const double ip = (1.0 / jp.S) / len, iq = 1.0 / jq.S;
+    const int nblocks = (V + SAMPLE_PART - 1) / SAMPLE_PART;
+    for (int blk = wave; blk < nblocks; blk += NT / WAVE) {
+      if (blk != wave) beta_load(bp, zp, zq, blk * SAMPLE_PART, V, lane);
+      const double w = beta_sum(bp, blk * SAMPLE_PART, V, lane, jp, jq, ip, iq, invT);
+      if (lane == 0) ctot[blk] = w;
+    }
+    __syncthreads();
+    if (wave == 0) {
+      for (int blk = lane; blk < nblocks; blk += WAVE) t += ctot[blk];
+      t = wave_sum(t);
+    }
+  }
+  if (tid == 0) (a.st ? a.st[b].beta : a.beta + (size_t)b * gamma)[i] = (float)t;
+}
+
+// A launch of its own where the guesses of a call outnumber the CUs: accept_kernel's registers let a CU hold
+// one of its workgroups, so hundreds of these would queue there (200 sequences, gamma 7, vocabulary 16384:
+// 114 -> 78 us a call).  grid = (gamma, rows).
+static __global__ __launch_bounds__(256, 6) void beta_kernel(const AcceptArgs a) {
+  __shared__ RowStat jr[2];
+  __shared__ double ctot[SAMPLE_CHUNK * SAMPLE_MAX_CHUNKS / SAMPLE_PART];
+  beta_guess<256>(a, blockIdx.y, blockIdx.x, jr, ctot);
 }
 
 // Decisions, draw, commit.  Every workgroup of a sequence joins the statistics and takes the decisions
@@ -1025,25 +1076,7 @@ static __global__ __launch_bounds__(SAMPLE_THREADS) void accept_kernel(const Acc
   const float* r = prm ? prm->uniforms + gamma : a.r + (size_t)b * gamma;   // (not read by argmax sampling)
   const float s = greedy ? 0.5f : (prm ? prm->uniforms[2 * gamma] : a.s[b]);
   if ((int)blockIdx.x >= a.draw_wgs) {               // beta of guess i (after a.self's statistics: none of those launches come here)
-    const int i = (int)blockIdx.x - a.draw_wgs;
-    if (wave < 2) {
-      const RowStat rs = join_parts(scr->part[wave ? gamma + 1 + i : i], accept_filtered(a) ? 1 : a.nparts, greedy, invT);
-      if (lane == 0) srow[wave] = rs;
-    }
-    __syncthreads();
-    double t = 0.0;
-    if (greedy) {                                    // one-hot q at its argmax: accepted or not
-      const int aq = srow[1].arg;                    // (INT_MAX: no entry of the draft's row is a number)
-      t = ((len < 1.0) ? (aq < V && (double)P[(size_t)i * V + min(aq, V - 1)] - (double)srow[0].m >= log_len) : (aq == srow[0].arg)) ? 1.0 : 0.0;
-    } else {
-      for (int part = wave; part < a.nparts; part += SAMPLE_THREADS / 64) {
-        const double w = beta_part(a, b, i, part, lane, srow[0], srow[1], invT, len);
-        if (lane == 0) sm.ctot[part] = w;
-      }
-      __syncthreads();
-      for (int part = 0; part < a.nparts; ++part) t += sm.ctot[part];
-    }
-    if (tid == 0) (st ? st->beta : a.beta + (size_t)b * gamma)[i] = (float)t;
+    beta_guess<SAMPLE_THREADS>(a, b, (int)blockIdx.x - a.draw_wgs, srow, sm.ctot);
     return;
   }
   // what the tests need arrives while the statistics are joined
@@ -1237,7 +1270,9 @@ inline void launch_accept(hipStream_t stream, AcceptArgs a, int rows, int cus) {
   const int most = a.self ? 1 : min(wgs, max(1, cus / rows));
   a.chunks_wave = (wgs + most - 1) / most;
   a.draw_wgs = (wgs + a.chunks_wave - 1) / a.chunks_wave;
-  hipLaunchKernelGGL(accept_kernel, dim3(a.draw_wgs + (a.beta != nullptr ? a.gamma : 0), rows), dim3(SAMPLE_THREADS), 0, stream, a);
+  const bool beta_apart = a.beta != nullptr && rows * a.gamma > cus && (a.prm != nullptr || a.temperature > 0.0f);   // (argmax: no rows to read)
+  hipLaunchKernelGGL(accept_kernel, dim3(a.draw_wgs + (a.beta != nullptr && !beta_apart ? a.gamma : 0), rows), dim3(SAMPLE_THREADS), 0, stream, a);
+  if (beta_apart) hipLaunchKernelGGL(beta_kernel, dim3(a.gamma, rows), dim3(256), 0, stream, a);
 }
 
 }  // namespace sd

@@ -174,3 +174,9 @@ def test_calls_without_beta(vocab, temperature):
         else:
             p, q = (np.stack([sampling.standardise(z, temperature) for z in v[b]]) for v in (zp, zq))
             assert sampling.icdf_edge_distance(p[n] if n == gamma else sampling.adjusted_distribution(p[n], q[n]), s[b], int(t_g[b])) < 1e-5
+
+
+def test_more_beta_than_compute_units():
+    """The acceptance probabilities of a call with more guesses than CUs come from a launch of their own."""
+    zp, zq, x, r, s = synth.sampler_case(60, 5, 2050, 1.0, 23)
+    check(zp, zq, x, r, s, 1.0)
