@@ -984,8 +984,10 @@ void launch_draw(sd_ctx* c, const float* logits, int uniform_idx, int mode, int 
                        uniform_idx, c->d_state, mode, slot, seq_stride);
     return;
   }
-  hipLaunchKernelGGL(sample_row_split_kernel, dim3(sample_workgroups(c->p.cfg.vocab), c->batch), dim3(SAMPLE_THREADS), 0, c->stream,
-                     logits, c->p.cfg.vocab, c->d_params, uniform_idx, c->d_state, mode, slot, seq_stride, c->d_scratch);
+  with_sample_groups(c->p.cfg.vocab, [&](auto ng) {
+    hipLaunchKernelGGL((sample_row_split_kernel<decltype(ng)::value>), dim3(sample_workgroups(c->p.cfg.vocab), c->batch), dim3(SAMPLE_THREADS), 0,
+                       c->stream, logits, c->p.cfg.vocab, c->d_params, uniform_idx, c->d_state, mode, slot, seq_stride, c->d_scratch);
+  });
 }
 
 // The launch sequence of one run of Algorithm 1 for every sequence (everything between the
