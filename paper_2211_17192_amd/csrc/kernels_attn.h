@@ -402,7 +402,9 @@ constexpr size_t attn_mma_proj_lds_bytes(int rg, int nw) {
 }
 typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));   // four floats at any 4-byte boundary
 
-template <int DH, int NRT, int NW, int MODE>
+// MANY: a prompt's row groups, output in fragment order.  Apart from the decoding of up to 16 rows, which would pay
+// for the choice (T5-XXL shape, 6 rows: cross-attention 5.27 -> 5.10 us, self-attention 3.72 -> 3.61).
+template <int DH, int NRT, int NW, int MODE, bool MANY>
 // (four wavefronts: capped at 128 registers so that two workgroups share a CU, which the long
 // contexts' key ranges need: one workgroup per CU took two rounds there)
 static __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_mma_kernel(const AttnArgs a) {
@@ -416,9 +418,10 @@ static __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_mma_kern
   const int j = lane & 15, kq = lane >> 4;
   const int hkv = blockIdx.x;
   const int seq = blockIdx.y;
-  // z: key ranges x row groups, the last rows (which see the most keys) first
-  int split = (int)blockIdx.z, grp = 0;
-  if (a.groups > 1) { split = (int)blockIdx.z / a.groups; grp = a.groups - 1 - (int)blockIdx.z % a.groups; }
+  // z: the key ranges of a launch that has them, else the row groups; MANY: key ranges x row groups, the last rows
+  // (which see the most keys) first
+  int split = (a.nsplit > 1) ? (int)blockIdx.z : 0, grp = (a.nsplit > 1) ? 0 : (int)blockIdx.z;
+  if (MANY) { split = (int)blockIdx.z / a.groups; grp = a.groups - 1 - (int)blockIdx.z % a.groups; }
   const int rs = grp * a.rows_per_wg;
   const int R = min(a.rows_per_wg, a.R - rs);
   const int r0 = seq * a.R + rs;
@@ -539,7 +542,7 @@ static __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_mma_kern
     kv_len = wave_max(my_pos) + 1;
     pos_min = wave_min(lane < R ? my_pos : 0x7fffffff);
   }
-  float* pp = a.partial + (((((size_t)seq * a.groups + grp) * a.Hkv + hkv) * a.nsplit + split) * ATTN_MAX_RG) * (DH + 2);
+  float* pp = a.partial + (((((size_t)seq * (MANY ? a.groups : 1) + (MANY ? grp : 0)) * a.Hkv + hkv) * a.nsplit + split) * ATTN_MAX_RG) * (DH + 2);
   if (a.nsplit > 1) {
     if (k_begin >= kv_len) {                        // nothing in this key range yet: an empty partial
       if (tid < RG) { pp[(size_t)tid * (DH + 2) + DH] = -INFINITY; pp[(size_t)tid * (DH + 2) + DH + 1] = 0.0f; }
@@ -800,7 +803,7 @@ static __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_mma_kern
     }
     const int rr = (rg * a.g_mul) >> 16, gg = rg - rr * G;
     const bf16 res = (bf16)((L > 0.0f) ? acc / L : 0.0f);
-    if (a.out_frag != nullptr) static_cast<bf16*>(a.out_frag)[attn_frag_index(a, r0 + rr, (hkv * G + gg) * DH + d)] = res;
+    if (MANY && a.out_frag != nullptr) static_cast<bf16*>(a.out_frag)[attn_frag_index(a, r0 + rr, (hkv * G + gg) * DH + d)] = res;
     else og[(size_t)(r0 + rr) * a.H * DH + (size_t)(hkv * G + gg) * DH + d] = res;
   }
 }
@@ -812,7 +815,8 @@ template <typename T, int DH>
 static __global__ __launch_bounds__(DH) void attn_merge_kernel(const AttnArgs a) {
   const int hkv = blockIdx.x, G = a.H / a.Hkv, rg = blockIdx.y, d = threadIdx.x;
   const int r_base = (int)blockIdx.z * a.R;
-  const int grp = rg / (a.rows_per_wg * G), rgl = rg - grp * a.rows_per_wg * G;
+  int grp = 0, rgl = rg;
+  if (a.groups > 1) { grp = rg / (a.rows_per_wg * G); rgl = rg - grp * a.rows_per_wg * G; }
   const float* pp = a.partial + (((((size_t)blockIdx.z * a.groups + grp) * a.Hkv + hkv) * a.nsplit) * ATTN_MAX_RG + rgl) * (DH + 2);
   const size_t stride = (size_t)ATTN_MAX_RG * (DH + 2);
   float m = -INFINITY;

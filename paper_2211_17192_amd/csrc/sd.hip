@@ -464,15 +464,18 @@ void launch_attn_mma(hipStream_t s, const AttnArgs& a, dim3 grid, int nw, size_t
   const int mode = a.cross ? (a.pj_w != nullptr ? ATTN_CROSS_PROJ : ATTN_CROSS) : (a.bias_by_key != nullptr ? ATTN_SELF_BIAS : ATTN_SELF);
   if constexpr (DH == 64 && NRT == 1) {
     if (mode == ATTN_CROSS_PROJ) {
-      if (nw == 4) hipLaunchKernelGGL((attn_mma_kernel<64, 1, 4, ATTN_CROSS_PROJ>), grid, dim3(256), lds, s, a);
-      else hipLaunchKernelGGL((attn_mma_kernel<64, 1, 8, ATTN_CROSS_PROJ>), grid, dim3(512), lds, s, a);
+      if (nw == 4) hipLaunchKernelGGL((attn_mma_kernel<64, 1, 4, ATTN_CROSS_PROJ, false>), grid, dim3(256), lds, s, a);
+      else hipLaunchKernelGGL((attn_mma_kernel<64, 1, 8, ATTN_CROSS_PROJ, false>), grid, dim3(512), lds, s, a);
       return;
     }
   }
-#define SD_MMA(NW_, MODE_)                                                                                \
-  if (nw == NW_ && mode == MODE_) {                                                                       \
-    hipLaunchKernelGGL((attn_mma_kernel<DH, NRT, NW_, MODE_>), grid, dim3(64 * NW_), lds, s, a);          \
-    return;                                                                                               \
+  // more than one slab of rows: row groups x key ranges, or fragments written by the kernel itself
+  const bool many = a.R > MAX_ROWS || (a.out_frag != nullptr && a.nsplit <= 1);
+#define SD_MMA(NW_, MODE_)                                                                                              \
+  if (nw == NW_ && mode == MODE_) {                                                                                     \
+    if (many) hipLaunchKernelGGL((attn_mma_kernel<DH, NRT, NW_, MODE_, true>), grid, dim3(64 * NW_), lds, s, a);        \
+    else hipLaunchKernelGGL((attn_mma_kernel<DH, NRT, NW_, MODE_, false>), grid, dim3(64 * NW_), lds, s, a);            \
+    return;                                                                                                             \
   }
   SD_MMA(4, ATTN_SELF) SD_MMA(4, ATTN_SELF_BIAS) SD_MMA(4, ATTN_CROSS)
   SD_MMA(8, ATTN_SELF) SD_MMA(8, ATTN_SELF_BIAS) SD_MMA(8, ATTN_CROSS)
@@ -554,7 +557,9 @@ hipError_t allow_mma_lds() {
   const size_t bytes = attn_mma_lds_bytes(NRT == 1 ? 16 : ATTN_MAX_RG, DH, NW);
   static_assert(attn_mma_lds_bytes(ATTN_MAX_RG, 128, 8) <= LDS_PER_CU, "matrix-core attention: LDS budget");
   if (bytes <= 64 * 1024) return hipSuccess;
-  return hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_mma_kernel<DH, NRT, NW, MODE>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_mma_kernel<DH, NRT, NW, MODE, false>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_mma_kernel<DH, NRT, NW, MODE, true>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  return e;
 }
 template <int DH, int NRT, int NW>
 hipError_t allow_mma_lds_modes() {
