@@ -162,15 +162,21 @@ typedef struct {
   int64_t beta_count;                       /*   and their number; beta_sum / beta_count estimates alpha = E(beta) */
 } sd_stats;
 
-/* Device bytes sd_load_models needs for this pair (weights, KV caches,
- * activations, logits).  Returns 0 for an invalid configuration. */
+/* Device bytes of a workspace for this pair (weights, KV caches, activations,
+ * logits).  Returns 0 for an invalid configuration.
+ * bf16 models with heads of 64 or 128 take a prompt in passes of up to 2048 rows, whose
+ * activations and, for max_len > 1024, partial attention results are part of it: for
+ * an 8B-class target with a 2-layer draft (one sequence) 0.35 GB at max_len 2048, 0.52 at
+ * 4096, 0.86 at 8192.  sd_load_models takes less: it halves the rows of a pass until they fit,
+ * down to 16 at a time, which needs none of that.  Results are the same to the bit; prompts
+ * take longer, and without any such room so do batches of more than 16 rows. */
 size_t sd_workspace_bytes(const sd_model_cfg* p_cfg, const sd_model_cfg* q_cfg,
                           const sd_runtime_cfg* rt);
 
 /* Section 2.1: bind the target model Mp and the approximation model Mq.
  * out: host, receives the context.  p_w / q_w: host arrays of descriptors of
  * device tensors.  Fails with SD_EINVAL on a missing / unknown / misshapen
- * tensor, SD_ENOMEM if the workspace is too small. */
+ * tensor, SD_ENOMEM if the workspace is too small for prompt passes of 16 rows. */
 sd_status sd_load_models(sd_ctx** out,
                          const sd_model_cfg* p_cfg, const sd_tensor* p_w, int32_t n_p,
                          const sd_model_cfg* q_cfg, const sd_tensor* q_w, int32_t n_q,
@@ -364,8 +370,8 @@ sd_status sd_time_stream_read(sd_ctx* ctx, int32_t which, int32_t reps, double* 
  *   p_logits : dev, [rows, gamma+1, vocab] fp32      q_logits : dev, [rows, gamma, vocab] fp32
  *   x        : dev, [rows, gamma] int32 guesses      r : dev, [rows, gamma] fp32
  *   s        : dev, [rows] fp32                      out_n, out_t : dev, [rows] int32
- *   scratch  : dev, sd_spec_sample_scratch_bytes(rows, gamma) bytes, zeroed
- *              once by the caller before the first call.
+ *   scratch  : dev, sd_spec_sample_scratch_bytes(rows, gamma) bytes (40 KB a
+ *              row), zeroed once by the caller before the first call.
  * Asynchronous on `stream`; no host output.
  */
 size_t    sd_spec_sample_scratch_bytes(int32_t rows, int32_t gamma);

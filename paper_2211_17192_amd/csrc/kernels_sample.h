@@ -40,12 +40,16 @@ struct RowPart {
   union { int arg; float thr; };   // argmax sampling: lowest index attaining m; filtered rows (one part): the threshold
 };
 
-// Working memory of one sequence's accept / resample call or draw.  The layout depends on nothing, so
-// calls of any size may follow each other on one allocation; the ticket is zero between calls.
+// Working memory of one sequence's accept / resample call or draw; the ticket is zero between calls.
 struct SampleScratch {
   unsigned int ticket[64];
-  RowPart part[2 * SAMPLE_MAX_GAMMA + 1][SAMPLE_PARTS];
   double tot[SAMPLE_MAX_CHUNKS];
+};
+// The same with the statistics of the sequence's rows, for calls on explicit logits.  The layout depends on
+// nothing, so calls of any size may follow each other on one allocation.
+struct SampleBlock {
+  SampleScratch s;
+  RowPart part[2 * SAMPLE_MAX_GAMMA + 1][SAMPLE_PARTS];
 };
 
 constexpr int SAMPLE_BINS = 2048;           // 11 bits of the order-preserving key
@@ -831,17 +835,20 @@ struct AcceptArgs {
   double log_lenience;
   int top_k; float top_p;              // in-model use: only whether the rows are filtered (the options are read from prm)
   const StepParams* prm;
-  SampleScratch* scr;
+  void* scr; size_t scr_stride;        // sequence b's SampleScratch: scr_stride bytes further each
+  RowPart* part; size_t part_seq; int part_row;      // statistics of row j of sequence b: part + b * part_seq + j * part_row
   int *out_n, *out_t; float* beta;
   SeqState* st;
 };
 // Whether row_filter_kernel leaves the statistics (one part a row) instead of row_parts_kernel.
 __host__ __device__ inline bool accept_filtered(const AcceptArgs& a) { return a.top_k > 0 || (a.top_p > 0.0f && a.top_p < 1.0f); }
 // A row's parts depend on its length only, so its statistics do not depend on the call around it.
-__host__ __device__ inline void accept_parts(AcceptArgs& a) {
-  a.part_len = SAMPLE_PART * ((a.V + SAMPLE_PART * SAMPLE_PARTS - 1) / (SAMPLE_PART * SAMPLE_PARTS));
-  a.nparts = (a.V + a.part_len - 1) / a.part_len;
+__host__ __device__ constexpr int sample_part_len(int V) { return SAMPLE_PART * ((V + SAMPLE_PART * SAMPLE_PARTS - 1) / (SAMPLE_PART * SAMPLE_PARTS)); }
+__host__ __device__ constexpr int sample_parts(int V) { return (V + sample_part_len(V) - 1) / sample_part_len(V); }
+__device__ __forceinline__ SampleScratch* accept_scratch(const AcceptArgs& a, int b) {
+  return reinterpret_cast<SampleScratch*>(static_cast<char*>(a.scr) + (size_t)b * a.scr_stride);
 }
+__device__ __forceinline__ RowPart* accept_part(const AcceptArgs& a, int b, int j) { return a.part + (size_t)b * a.part_seq + (size_t)j * a.part_row; }
 __device__ __forceinline__ const float* accept_row(const AcceptArgs& a, int b, int j) {
   return (j <= a.gamma) ? a.p + ((size_t)b * (a.gamma + 1) + j) * a.V : a.q + ((size_t)b * a.gamma + (j - a.gamma - 1)) * a.V;
 }
@@ -904,7 +911,7 @@ __device__ __forceinline__ void reduce_part(const AcceptArgs& a, int b, int j, i
              ((double)exp_scaled(v[it].z, m, invT, -INFINITY) + (double)exp_scaled(v[it].w, m, invT, -INFINITY));
     }
   }
-  RowPart* out = &a.scr[b].part[j][part];
+  RowPart* out = accept_part(a, b, j) + part;
   if (greedy) {
     const float M = wave_max(m);
     arg = wave_min(m == M ? arg : INT_MAX);
@@ -968,7 +975,7 @@ static __global__ __launch_bounds__(SAMPLE_THREADS) void row_filter_kernel(const
   load_row_regs(accept_row(a, b, j), a.V, v);
   const RowStat rs = row_stats_regs(v, greedy ? 1.0f : 1.0f / T, greedy, sm, a.prm ? a.prm[b].top_k : a.top_k, a.prm ? a.prm[b].top_p : a.top_p, a.V);
   if (threadIdx.x == 0) {
-    RowPart* out = &a.scr[b].part[j][0];
+    RowPart* out = accept_part(a, b, j);
     out->S = rs.S; out->m = rs.m;
     if (greedy) out->arg = rs.arg; else out->thr = rs.thr;
   }
@@ -1039,7 +1046,7 @@ __device__ __forceinline__ void beta_guess(const AcceptArgs& a, int b, int i, Ro
   BetaPart bp;
   if (!greedy && wave * SAMPLE_PART < V) beta_load(bp, zp, zq, wave * SAMPLE_PART, V, lane);       // arrives while the statistics are joined
   if (wave < 2) {
-    const RowStat rs = join_parts(a.scr[b].part[wave ? gamma + 1 + i : i], accept_filtered(a) ? 1 : a.nparts, greedy, invT);
+    const RowStat rs = join_parts(accept_part(a, b, wave ? gamma + 1 + i : i), accept_filtered(a) ? 1 : a.nparts, greedy, invT);
     if (lane == 0) jr[wave] = rs;
   }
   __syncthreads();
@@ -1089,7 +1096,7 @@ static __global__ __launch_bounds__(SAMPLE_THREADS) void accept_kernel(const Acc
   const int gamma = a.gamma, V = a.V, nrows = 2 * gamma + 1, nchunks = (V + SAMPLE_CHUNK - 1) / SAMPLE_CHUNK;
   const StepParams* prm = a.prm ? a.prm + b : nullptr;     // in-model use: per-sequence parameters and state
   SeqState* st = a.st ? a.st + b : nullptr;
-  SampleScratch* scr = a.scr + b;
+  SampleScratch* scr = accept_scratch(a, b);
   const float T = prm ? prm->temperature : a.temperature;
   const bool greedy = (T == 0.0f);
   const float invT = greedy ? 1.0f : 1.0f / T;
@@ -1120,7 +1127,7 @@ static __global__ __launch_bounds__(SAMPLE_THREADS) void accept_kernel(const Acc
     __syncthreads();
   }
   for (int row = wave; row < nrows && !(greedy && row > gamma && a.beta == nullptr); row += SAMPLE_THREADS / 64) {
-    const RowStat rs = join_parts(scr->part[row], accept_filtered(a) ? 1 : a.nparts, greedy, invT);
+    const RowStat rs = join_parts(accept_part(a, b, row), accept_filtered(a) ? 1 : a.nparts, greedy, invT);
     if (lane == 0) srow[row] = rs;
   }
   __syncthreads();
@@ -1234,7 +1241,7 @@ static __global__ __launch_bounds__(SAMPLE_THREADS) void accept_argmax_kernel(co
   }
   argmax_workgroup(m, arg, V, wm, wa);
   if (wave != 0) return;
-  SampleScratch* scr = a.scr + b;
+  SampleScratch* scr = accept_scratch(a, b);
   int last = 0;
   if (lane == 0) {
     post(&scr->tot[j], __longlong_as_double((long long)(((unsigned long long)__float_as_uint(m + 0.0f) << 32) | (unsigned)arg)));     // (-0 counts as 0)
@@ -1264,14 +1271,14 @@ inline void launch_argmax(hipStream_t stream, const AcceptArgs& a, int rows) {
   });
 }
 
-static __global__ void clear_tickets_kernel(SampleScratch* scr, int rows) {
+static __global__ void clear_tickets_kernel(void* scr, size_t stride, int rows) {
   const int b = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-  if (b < rows) scr[b].ticket[0] = 0u;
+  if (b < rows) reinterpret_cast<SampleScratch*>(static_cast<char*>(scr) + (size_t)b * stride)->ticket[0] = 0u;
 }
 
 // The launches of one accept / resample call over `rows` sequences.
 inline void launch_accept(hipStream_t stream, AcceptArgs a, int rows, int cus) {
-  accept_parts(a);
+  a.part_len = sample_part_len(a.V); a.nparts = sample_parts(a.V);
   const int nrows = 2 * a.gamma + 1;
   const int wgs = sample_workgroups(a.V);
   if (a.prm == nullptr && a.temperature == 0.0f && a.beta == nullptr) {

@@ -67,6 +67,8 @@ struct Model {
   int rows_cap = MAX_ROWS;     // activation rows: one group of MAX_ROWS rows per sequence at most, or rows_pass
   int rows_pass = 0;           // prompt rows one pass over the model takes (forward_rows); 0: MAX_ROWS-row passes only
   bf16* zeros = nullptr;       // 1 KB of zeros
+  char* act = nullptr;         // the activations x .. ffn as one block of act_bytes
+  size_t act_bytes = 0;
   int* page_table = nullptr;   // [batch][n_pages]
   bool pages_in_order = true;  // sequence b's table is b * n_pages + 0, 1, 2, ...; false (SD_FLAG_SCATTER_PAGES): back to front
   int *row_seq = nullptr, *logit_row = nullptr;   // [rows_cap], written by the embedding kernel
@@ -111,14 +113,19 @@ bool cfg_ok(const sd_model_cfg& c, std::string& why) {
 // Prompt rows a workgroup of the matrix-core attention takes: as many as its two 16-row tiles hold.
 int prompt_rows_per_wg(const sd_model_cfg& c) { return ATTN_MAX_RG / (c.n_heads / c.n_kv_heads); }
 
-// Lays a model out in the arena (or sizes it).
-void plan_model(Arena& A, Model& m, const sd_model_cfg& c, int page_size, int batch) {
+// Prompt rows of one pass: a product over 2048 rows keeps the whole chip in matrix instructions, more rows only
+// cost memory.  The rows' activations and, for max_len > 1024, the partial results of their attention are the
+// part of a workspace that can shrink: a pass of fewer rows reads the weights more often and gives the same
+// results.  Below 32 rows there are no such passes (forward()'s kernels take 16 rows at a time).
+constexpr int ROWS_PASS_MAX = 2048, ROWS_PASS_MIN = 32;
+
+// Lays a model out in the arena (or sizes it); rows_limit: prompt rows of one pass at most, 0: no such passes.
+void plan_model(Arena& A, Model& m, const sd_model_cfg& c, int page_size, int batch, int rows_limit) {
   m.cfg = c;
   m.batch = batch;
-  // bf16 models with the matrix-core attention take a prompt many rows at a time: a product over 2048
-  // rows keeps the whole chip in matrix instructions, more rows only cost memory
-  const bool many = c.dtype == SD_BF16 && (c.d_head == 64 || c.d_head == 128);
-  m.rows_pass = many ? std::min(2048, (c.max_len + MAX_ROWS - 1) / MAX_ROWS * MAX_ROWS) : 0;
+  // bf16 models with the matrix-core attention take a prompt many rows at a time
+  const bool many = rows_limit > 0 && c.dtype == SD_BF16 && (c.d_head == 64 || c.d_head == 128);
+  m.rows_pass = many ? std::min(rows_limit, (c.max_len + MAX_ROWS - 1) / MAX_ROWS * MAX_ROWS) : 0;
   m.rows_cap = std::max(MAX_ROWS * batch, m.rows_pass);
   m.esz = (c.dtype == SD_BF16) ? 2 : 4;
   const size_t e = m.esz, d = c.d_model, ff = c.d_ff, V = c.vocab;
@@ -162,12 +169,15 @@ void plan_model(Arena& A, Model& m, const sd_model_cfg& c, int page_size, int ba
   }
   const size_t rows = (size_t)m.rows_cap;
   m.page_table = static_cast<int*>(A.take((size_t)batch * m.n_pages * sizeof(int)));
+  const size_t act0 = align_up(A.off);
+  m.act = A.base ? A.base + act0 : nullptr;
   m.x = static_cast<float*>(A.take(rows * d * sizeof(float)));
   m.xg = A.take(std::max(rows, (size_t)(many ? (c.enc_len + MAX_ROWS - 1) / MAX_ROWS * MAX_ROWS : 0)) * d * e);   // (also the encoder's rows, once)
   m.ss = static_cast<float*>(A.take(rows / MAX_ROWS * (d / 16) * 16 * sizeof(float)));   // [group][d/16][16]
   m.qbuf = A.take(rows * m.nq * e);
   m.attn = A.take(rows * m.nq * e);
   m.ffn = A.take(rows * ff * e);
+  m.act_bytes = A.off - act0;
   m.row_pos = static_cast<int*>(A.take(rows * sizeof(int)));
   m.row_seq = static_cast<int*>(A.take(rows * sizeof(int)));
   m.logit_row = static_cast<int*>(A.take(rows * sizeof(int)));
@@ -177,20 +187,22 @@ void plan_model(Arena& A, Model& m, const sd_model_cfg& c, int page_size, int ba
   if (m.attn_nsplit > 1) {
     m.attn_split_keys = ((c.max_len + m.attn_nsplit - 1) / m.attn_nsplit + 511) / 512 * 512;
     // (a prompt pass with few workgroups makes its row groups half as large)
-    const int per = prompt_rows_per_wg(c);
-    const size_t row_groups = std::max({(size_t)batch, (size_t)((m.rows_pass + per - 1) / per), (size_t)(2 * MAX_CUS / c.n_kv_heads + 2)});
-    m.attn_partial = static_cast<float*>(A.take(row_groups * c.n_kv_heads * m.attn_nsplit * ATTN_MAX_RG *
+    const int per = prompt_rows_per_wg(c), half = per / 2;
+    const int row_groups = std::max({batch, (m.rows_pass + per - 1) / per, std::min((m.rows_pass + half - 1) / half, 2 * MAX_CUS / c.n_kv_heads + 2)});
+    m.attn_partial = static_cast<float*>(A.take((size_t)row_groups * c.n_kv_heads * m.attn_nsplit * ATTN_MAX_RG *
                                                 (c.d_head + 2) * sizeof(float)));
   }
   if (m.rows_pass > 0) {
     m.zeros = static_cast<bf16*>(A.take(1024));
   }
   if (batch > 1) {
-    m.xfrag = A.take((size_t)std::max({(size_t)d, (size_t)m.nq, ff}) * GEMM_WIDE_RT * 16 * e);
+    if (m.rows_pass == 0) {                          // (forward_rows passes activations on in fragment order)
+      m.xfrag = A.take((size_t)std::max({(size_t)d, (size_t)m.nq, ff}) * GEMM_WIDE_RT * 16 * e);
+      m.wide_rs = static_cast<float*>(A.take((size_t)GEMM_WIDE_RT * 16 * sizeof(float)));
+      m.xfrag2 = A.take((size_t)std::max({(size_t)d, (size_t)m.nq, ff}) * GEMM_WIDE_RT * 16 * e);
+    }
     const size_t tiles = std::max((size_t)d, (size_t)(m.nq + 2 * m.nkv)) / 16;    // the products split_ok() lets through
     m.wide_partial = static_cast<float*>(A.take((size_t)8 * GEMM_WIDE_RT * tiles * 256 * sizeof(float)));
-    m.wide_rs = static_cast<float*>(A.take((size_t)GEMM_WIDE_RT * 16 * sizeof(float)));
-    m.xfrag2 = A.take((size_t)std::max({(size_t)d, (size_t)m.nq, ff}) * GEMM_WIDE_RT * 16 * e);
   }
   m.prompt = static_cast<int*>(A.take((size_t)c.max_len * sizeof(int)));
 }
@@ -206,6 +218,7 @@ struct sd_ctx {
   StepParams* d_params = nullptr;
   float *p_logits = nullptr, *q_logits = nullptr;
   SampleScratch* d_scratch = nullptr;    // [batch]
+  RowPart* d_parts = nullptr;            // statistics of the logits rows: [batch][2 max_gamma + 1][sample_parts(vocab)]
   SeqState* h_state = nullptr;       // pinned
   StepParams* h_params = nullptr;    // pinned
   int batch = 1;
@@ -245,18 +258,28 @@ struct sd_ctx {
 
 namespace {
 
-void plan_ctx(Arena& A, sd_ctx& c, const sd_model_cfg& pc, const sd_model_cfg& qc, const sd_runtime_cfg& rt) {
+void plan_ctx(Arena& A, sd_ctx& c, const sd_model_cfg& pc, const sd_model_cfg& qc, const sd_runtime_cfg& rt, int rows_limit) {
   const size_t B = (size_t)rt.batch;
   c.batch = rt.batch;
-  plan_model(A, c.p, pc, rt.page_size, rt.batch);
-  plan_model(A, c.q, qc, rt.page_size, rt.batch);
+  plan_model(A, c.p, pc, rt.page_size, rt.batch, rows_limit);
+  plan_model(A, c.q, qc, rt.page_size, rt.batch, rows_limit);
   c.d_state = static_cast<SeqState*>(A.take(B * sizeof(SeqState)));
   c.d_params = static_cast<StepParams*>(A.take(B * sizeof(StepParams)));
   c.p_logits = static_cast<float*>(A.take(B * (rt.max_gamma + 1) * pc.vocab * sizeof(float)));   // [seq][gamma+1][V]
   c.q_logits = static_cast<float*>(A.take(B * rt.max_gamma * pc.vocab * sizeof(float)));         // [seq][gamma][V]
   c.d_scratch = static_cast<SampleScratch*>(A.take(B * sizeof(SampleScratch)));
+  // the accept / resample launches follow the verify forward, whose activations nobody reads any more
+  const size_t parts = B * (2 * rt.max_gamma + 1) * sample_parts(pc.vocab) * sizeof(RowPart);
+  c.d_parts = reinterpret_cast<RowPart*>(parts <= c.p.act_bytes ? c.p.act : static_cast<char*>(A.take(parts)));
   c.hist_stride = pc.max_len;
   c.d_hist = static_cast<int*>(A.take(B * (size_t)pc.max_len * sizeof(int)));
+}
+
+size_t plan_bytes(const sd_model_cfg& pc, const sd_model_cfg& qc, const sd_runtime_cfg& rt, int rows_limit) {
+  sd_ctx tmp;
+  Arena A(nullptr);
+  plan_ctx(A, tmp, pc, qc, rt, rows_limit);
+  return align_up(A.off);
 }
 
 bool rt_ok(const sd_runtime_cfg& rt, std::string& why) {
@@ -1020,7 +1043,8 @@ void enqueue_step(sd_ctx* c, int gamma, bool profile) {
   c->time_ffn = false;
   if (profile) hipEventRecord(c->ev[2], s);
   AcceptArgs a{};
-  a.p = c->p_logits; a.q = c->q_logits; a.gamma = gamma; a.V = V; a.prm = c->d_params; a.st = c->d_state; a.scr = c->d_scratch;
+  a.p = c->p_logits; a.q = c->q_logits; a.gamma = gamma; a.V = V; a.prm = c->d_params; a.st = c->d_state;
+  a.scr = c->d_scratch; a.scr_stride = sizeof(SampleScratch); a.part = c->d_parts; a.part_row = sample_parts(V); a.part_seq = (size_t)(2 * gamma + 1) * a.part_row;
   a.top_k = c->filtered() ? 1 : 0;
   if (c->rt.flags & SD_FLAG_BETA) a.beta = c->d_state->beta;           // side output: beta_i of every guess, into the states
   launch_accept(s, a, B, g_num_cus);
@@ -1189,10 +1213,7 @@ extern "C" size_t sd_workspace_bytes(const sd_model_cfg* p_cfg, const sd_model_c
   std::string why;
   if (!p_cfg || !q_cfg || !rt || !cfg_ok(*p_cfg, why) || !cfg_ok(*q_cfg, why) || !rt_ok(*rt, why)) return 0;
   if (p_cfg->vocab != q_cfg->vocab) return 0;
-  sd_ctx tmp;
-  Arena A(nullptr);
-  plan_ctx(A, tmp, *p_cfg, *q_cfg, *rt);
-  return align_up(A.off);
+  return plan_bytes(*p_cfg, *q_cfg, *rt, ROWS_PASS_MAX);
 }
 
 extern "C" sd_status sd_load_models(sd_ctx** out, const sd_model_cfg* p_cfg, const sd_tensor* p_w, int32_t n_p,
@@ -1211,13 +1232,16 @@ extern "C" sd_status sd_load_models(sd_ctx** out, const sd_model_cfg* p_cfg, con
       2 * (q_cfg->n_heads / q_cfg->n_kv_heads) > ATTN_MAX_RG)
     return fail(nullptr, SD_EINVAL, "(max_gamma+1) x (query heads per kv head) exceeds the attention kernel's limit");
   if (!rt->workspace || (reinterpret_cast<uintptr_t>(rt->workspace) & 255)) return fail(nullptr, SD_EINVAL, "workspace must be 256-byte aligned");
-  const size_t need = sd_workspace_bytes(p_cfg, q_cfg, rt);
-  if (rt->workspace_bytes < need) return fail(nullptr, SD_ENOMEM, "workspace too small: need " + std::to_string(need));
+  int rows_limit = ROWS_PASS_MAX;                    // the longest prompt passes that the workspace has room for
+  while (plan_bytes(*p_cfg, *q_cfg, *rt, rows_limit) > rt->workspace_bytes) {
+    if (rows_limit == 0) return fail(nullptr, SD_ENOMEM, "workspace too small: need " + std::to_string(sd_workspace_bytes(p_cfg, q_cfg, rt)));
+    rows_limit = (rows_limit > ROWS_PASS_MIN) ? rows_limit / 2 : 0;
+  }
   sd_ctx* c = new (std::nothrow) sd_ctx();
   if (!c) return fail(nullptr, SD_ENOMEM, "host allocation failed");
   c->rt = *rt;
   Arena A(rt->workspace);
-  plan_ctx(A, *c, *p_cfg, *q_cfg, *rt);
+  plan_ctx(A, *c, *p_cfg, *q_cfg, *rt, rows_limit);
   auto bail = [&](sd_status s, const std::string& m) { sd_free(c); return fail(nullptr, s, m); };
   if (rt->stream) c->stream = static_cast<hipStream_t>(rt->stream);
   else {                       // a stream of the context's own (not the legacy default stream, which cannot be captured)
@@ -1257,7 +1281,7 @@ extern "C" sd_status sd_load_models(sd_ctx** out, const sd_model_cfg* p_cfg, con
   if (st != SD_OK) return bail(st, "Mq: " + err);
   for (const Model* m : {&c->p, &c->q})
     if (m->zeros) hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(256), 0, c->stream, reinterpret_cast<unsigned int*>(m->zeros), 0u, (size_t)256);
-  hipLaunchKernelGGL(clear_tickets_kernel, dim3(1), dim3(SD_MAX_BATCH), 0, c->stream, c->d_scratch, (int)B);
+  hipLaunchKernelGGL(clear_tickets_kernel, dim3(1), dim3(SD_MAX_BATCH), 0, c->stream, c->d_scratch, sizeof(SampleScratch), (int)B);
   hipError_t e = hipStreamSynchronize(c->stream);
   if (e == hipSuccess) e = hipGetLastError();
   if (e != hipSuccess) return bail(SD_EHIP, std::string("load: ") + hipGetErrorString(e));

@@ -11,7 +11,7 @@
 
 extern "C" size_t sd_spec_sample_scratch_bytes(int32_t rows, int32_t gamma) {
   if (rows < 1 || gamma < 1 || gamma > SD_MAX_GAMMA) return 0;
-  return (size_t)rows * sizeof(sd::SampleScratch);
+  return (size_t)rows * sizeof(sd::SampleBlock);
 }
 
 namespace {
@@ -44,12 +44,14 @@ static_assert(SD_MAX_GAMMA == sd::SAMPLE_MAX_GAMMA, "the sampling kernels' scrat
 sd_status launch_spec_sample(const float* p_logits, const float* q_logits, const int32_t* x, const float* r,
                              const float* s, int32_t rows, int32_t gamma, int32_t vocab, float temperature,
                              const SampleOpts& o, int32_t* out_n, int32_t* out_t, float* beta,
-                             sd::SampleScratch* scr, hipStream_t s_) {
+                             sd::SampleBlock* scr, hipStream_t s_) {
   sd::AcceptArgs a{};
   a.p = p_logits; a.q = q_logits; a.x = x; a.r = r; a.s = s; a.gamma = gamma; a.V = vocab; a.temperature = temperature;
-  a.lenience = o.len; a.log_lenience = o.log_len; 
+  a.lenience = o.len; a.log_lenience = o.log_len;
   if (temperature > 0.0f) { a.top_k = o.top_k; a.top_p = o.top_p; }            // (argmax sampling ignores the filters)
-  a.scr = scr; a.out_n = out_n; a.out_t = out_t; a.beta = beta;
+  a.scr = scr; a.scr_stride = sizeof(sd::SampleBlock);
+  a.part = &scr->part[0][0]; a.part_row = sd::SAMPLE_PARTS; a.part_seq = sizeof(sd::SampleBlock) / sizeof(sd::RowPart);
+  a.out_n = out_n; a.out_t = out_t; a.beta = beta;
   sd::launch_accept(s_, a, rows, 256);   // (every gfx950 device has 256 CUs)
   return hipGetLastError() == hipSuccess ? SD_OK : SD_EHIP;
 }
@@ -64,7 +66,7 @@ extern "C" sd_status sd_spec_sample_ex(const float* p_logits, const float* q_log
   const sd_status st = check_sample_args(p_logits, q_logits, x, r, s, rows, gamma, vocab, temperature, opt, out_n, out_t, o);
   if (st != SD_OK) return st;
   return launch_spec_sample(p_logits, q_logits, x, r, s, rows, gamma, vocab, temperature, o, out_n, out_t, beta,
-                            static_cast<sd::SampleScratch*>(scratch), static_cast<hipStream_t>(stream));
+                            static_cast<sd::SampleBlock*>(scratch), static_cast<hipStream_t>(stream));
 }
 
 extern "C" sd_status sd_spec_sample(const float* p_logits, const float* q_logits, const int32_t* x,
@@ -84,8 +86,8 @@ extern "C" sd_status sd_spec_sample(const float* p_logits, const float* q_logits
 // ---------------------------------------------------------------------------
 namespace {
 constexpr int STATIC_ROWS = SD_SPEC_SAMPLE_STATIC_MAX_ROWS;
-static __device__ __align__(256) unsigned char scratch[STATIC_ROWS * sizeof(sd::SampleScratch)];   // 10 MB
-static_assert(sizeof(sd::SampleScratch) % 16 == 0, "the blocks keep their alignment");
+static __device__ __align__(256) unsigned char scratch[STATIC_ROWS * sizeof(sd::SampleBlock)];   // 10 MB
+static_assert(sizeof(sd::SampleBlock) % sizeof(sd::RowPart) == 0, "the blocks keep their alignment, and a whole number of RowParts lies between two");
 
 constexpr int STATIC_MAX_DEVICES = 64;
 void* g_scratch_ptr[STATIC_MAX_DEVICES] = {};    // device address of `scratch` on each device, once known
@@ -129,7 +131,7 @@ extern "C" sd_status sd_spec_sample_static(const float* p_logits, const float* q
   hipStream_t s_ = static_cast<hipStream_t>(stream);
   // the tickets must start at zero whatever an earlier (possibly failed) call left: a small kernel,
   // not a memset, so that the call can be recorded into a graph
-  sd::SampleScratch* scr = static_cast<sd::SampleScratch*>(ptr);
-  hipLaunchKernelGGL(sd::clear_tickets_kernel, dim3((unsigned)((rows + 63) / 64)), dim3(64), 0, s_, scr, rows);
+  sd::SampleBlock* scr = static_cast<sd::SampleBlock*>(ptr);
+  hipLaunchKernelGGL(sd::clear_tickets_kernel, dim3((unsigned)((rows + 63) / 64)), dim3(64), 0, s_, scr, sizeof(sd::SampleBlock), rows);
   return launch_spec_sample(p_logits, q_logits, x, r, s, rows, gamma, vocab, temperature, o, out_n, out_t, beta, scr, s_);
 }

@@ -60,3 +60,51 @@ def test_prefill_equals_token_by_token(name, scatter):
     assert np.isfinite(p1).all() and np.ptp(p1) > 1.0
     assert np.array_equal(p1, p2) and np.array_equal(q1, q2)
     assert (n1, t1) == (n2, t2)
+
+
+# (arch, d_model, heads, kv heads, d_head, d_ff, vocab, max_len, enc_len, max_gamma, sequences), and the bytes of a
+# workspace without room for prompt passes of more than 16 rows (what the pair needs otherwise, with 31 KB of row
+# statistics a sequence beside the activations: sizes that loaded before those passes existed)
+WORKSPACES = {
+    "gqa-key-ranges": ((T.GQA, 256, 4, 2, 64, 512, 512, 1500, 0, 3, 1), 7933184),
+    "gqa-key-ranges-3": ((T.GQA, 256, 4, 2, 64, 512, 512, 1500, 0, 3, 3), 16591616),
+    "gpt-gamma-15": ((T.GPT, 128, 2, 2, 64, 256, 50256, 300, 0, 15, 1), 59184640),
+    "t5": ((T.T5DEC, 256, 4, 4, 64, 512, 512, 200, 100, 3, 1), 7660800),
+}
+
+
+@pytest.mark.parametrize("name", list(WORKSPACES))
+def test_smaller_workspaces_give_the_same_results(name, monkeypatch):
+    """Whatever room a workspace leaves for prompt passes, down to none."""
+    from paper_2211_17192_amd import binding
+    (arch, d, heads, kv, dh, ff, vocab, max_len, enc, gamma, B), least = WORKSPACES[name]
+    kw = dict(n_kv_heads=kv) if arch == T.GQA else {}
+    cfg = synth.model_cfg(arch, 2, d, heads, ff, vocab, max_len, d_head=dh, enc_len=enc, dtype="bf16", logit_scale=4.0, **kw)
+    w = synth.random_weights(cfg, 5, "cuda", 0.04)
+    cfg_q, w_q = synth.truncated_noisy_copy(cfg, w, 1, 9, 0.004)
+    enc_out = synth.counter_normal((enc, d), 3, 1.0, 0.0, "cuda").to(torch.bfloat16) if enc else None
+    prompt = [int(t) for t in synth.random_tokens(7, max_len - 3 * (gamma + 1), vocab)]
+    u = synth.uniform_stream(11, 2 * B * (2 * gamma + 1)).reshape(2, B, 2 * gamma + 1)
+
+    def decode(nbytes):
+        with monkeypatch.context() as mp:
+            if nbytes:
+                mp.setattr(binding.lib, "sd_workspace_bytes", lambda *a: nbytes)
+            dec = binding.SpecDecoder(cfg, w, cfg_q, w_q, max_gamma=gamma, flags=binding.SD_FLAG_GRAPH, batch=B)
+        for b in range(B):
+            dec.prefill(prompt[: len(prompt) - 5 * b], enc_out, enc_out, row=b)
+        out = []
+        for it in range(2):
+            out += [dec.step(gamma, 1.0, u[it] if B > 1 else u[it, 0]), dec.logits(0, B * (gamma + 1)), dec.logits(1, B * gamma)]
+        size = dec.workspace_bytes
+        dec.close()
+        return size, out
+
+    full, ref = decode(0)
+    assert least < full
+    for nbytes in (least, (least + full) // 2, full - 256):
+        _, got = decode(nbytes)
+        for a, b in zip(ref, got):
+            assert np.array_equal(a, b) if isinstance(a, np.ndarray) else a == b
+    with pytest.raises(binding.SdError, match="workspace too small"):
+        decode(least // 2)
