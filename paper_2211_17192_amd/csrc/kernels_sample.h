@@ -648,6 +648,17 @@ __device__ __forceinline__ void commit_draw(SeqState* st, int mode, int slot, in
   }
 }
 
+// One run of Algorithm 1: x_1 .. x_n, t.
+__device__ __forceinline__ void commit_run(SeqState* st, int n, int t, int fell_back) {
+  const int last = st->last_tok;
+  for (int i = 0; i < 16; ++i) st->out[i] = (i < n) ? st->x[i] : (i == n ? t : -1);
+  st->prev_tok = (n >= 1) ? st->x[n - 1] : last;
+  st->last_tok = t;
+  st->len += n + 1;
+  st->n = n;
+  st->fallbacks += fell_back;
+}
+
 // The workgroups' hand-over: each leaves 8-byte results with write-through stores (post) and takes a
 // ticket; the last one to arrive sees them all through loads that go past its own caches (collect).  A
 // ticket with release / acquire semantics instead writes back and invalidates an L2 per workgroup,
@@ -831,9 +842,10 @@ struct AcceptArgs {
   int part_len, nparts;                // entries of one part of a row's statistics (a multiple of SAMPLE_PART), parts per row
   int chunks_wave, draw_wgs;           // accept_kernel: chunks per wavefront; workgroups of a sequence's draw (beta's follow)
   int self;                            // accept_kernel: the statistics are its own work
+  // in-model use: only whether the temperature is 0 and whether the rows are filtered (the values are read from prm)
   float temperature, lenience;
   double log_lenience;
-  int top_k; float top_p;              // in-model use: only whether the rows are filtered (the options are read from prm)
+  int top_k; float top_p;
   const StepParams* prm;
   void* scr; size_t scr_stride;        // sequence b's SampleScratch: scr_stride bytes further each
   RowPart* part; size_t part_seq; int part_row;      // statistics of row j of sequence b: part + b * part_seq + j * part_row
@@ -1205,19 +1217,11 @@ static __global__ __launch_bounds__(SAMPLE_THREADS) void accept_kernel(const Acc
   if (tid == 0) {
     if (a.out_n) a.out_n[b] = n;
     if (a.out_t) a.out_t[b] = t;
-    if (st) {
-      const int last = st->last_tok;
-      for (int i = 0; i < 16; ++i) st->out[i] = (i < n) ? x[i] : (i == n ? t : -1);
-      st->prev_tok = (n >= 1) ? x[n - 1] : last;
-      st->last_tok = t;
-      st->len += n + 1;
-      st->n = n;
-      st->fallbacks += fell_back;
-    }
+    if (st) commit_run(st, n, t, fell_back);
   }
 }
 
-// Argmax sampling on explicit logits, without beta: only the target's rows count and nothing is drawn, so
+// Argmax sampling without beta: only the target's rows count and nothing is drawn, so
 // one launch does it, a workgroup per row; the last of a sequence to arrive decides.  Bound by its chain
 // (loads, one barrier, ticket), and with hundreds of sequences by its instructions: hence as many groups of
 // four entries a thread and as many threads as the row needs, and everything behind the barrier is one wavefront's.
@@ -1231,7 +1235,8 @@ static __global__ __launch_bounds__(SAMPLE_THREADS) void accept_argmax_kernel(co
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), nt = blockDim.x;
   const float* z = accept_row(a, b, j);
   int xi = 0;
-  if (tid < gamma) xi = min(max(a.x[(size_t)b * gamma + tid], 0), V - 1);
+  SeqState* st = a.st ? a.st + b : nullptr;
+  if (tid < gamma) xi = min(max(st ? st->x[tid] : a.x[(size_t)b * gamma + tid], 0), V - 1);
   float m = -INFINITY;
   int arg = INT_MAX;
   for (int k0 = 0; k0 < V; k0 += 4 * NG * nt) {
@@ -1255,13 +1260,19 @@ static __global__ __launch_bounds__(SAMPLE_THREADS) void accept_argmax_kernel(co
   bool reject = false;
   if (lane < gamma) {
     // lenient argmax sampling: keep x when p(x) >= l * max p, p = softmax of the raw logits
-    reject = ((double)a.lenience < 1.0) ? ((double)accept_row(a, b, lane)[xi] - (double)__uint_as_float((unsigned)(w >> 32)) < a.log_lenience)
-                                        : ((int)(unsigned)w != xi);
+    const float len = a.prm ? a.prm[b].lenience : a.lenience;
+    const double log_len = a.prm ? a.prm[b].log_lenience : a.log_lenience;
+    reject = ((double)len < 1.0) ? ((double)accept_row(a, b, lane)[xi] - (double)__uint_as_float((unsigned)(w >> 32)) < log_len)
+                                : ((int)(unsigned)w != xi);
   }
   const unsigned long long mask = __ballot(reject);
   const int n = mask ? (__ffsll((long long)mask) - 1) : gamma;
   const int t = __shfl((int)(unsigned)w, n, WAVE);
-  if (lane == 0) { a.out_n[b] = n; a.out_t[b] = t; }
+  if (lane == 0) {
+    if (a.out_n) a.out_n[b] = n;
+    if (a.out_t) a.out_t[b] = t;
+    if (st) commit_run(st, n, t, 0);
+  }
 }
 
 inline void launch_argmax(hipStream_t stream, const AcceptArgs& a, int rows) {
@@ -1281,7 +1292,7 @@ inline void launch_accept(hipStream_t stream, AcceptArgs a, int rows, int cus) {
   a.part_len = sample_part_len(a.V); a.nparts = sample_parts(a.V);
   const int nrows = 2 * a.gamma + 1;
   const int wgs = sample_workgroups(a.V);
-  if (a.prm == nullptr && a.temperature == 0.0f && a.beta == nullptr) {
+  if (a.temperature == 0.0f && a.beta == nullptr) {
     launch_argmax(stream, a, rows);
     return;
   }
@@ -1301,7 +1312,7 @@ inline void launch_accept(hipStream_t stream, AcceptArgs a, int rows, int cus) {
   const int most = a.self ? 1 : min(wgs, max(1, cus / rows));
   a.chunks_wave = (wgs + most - 1) / most;
   a.draw_wgs = (wgs + a.chunks_wave - 1) / a.chunks_wave;
-  const bool beta_apart = a.beta != nullptr && rows * a.gamma > cus && (a.prm != nullptr || a.temperature > 0.0f);   // (argmax: no rows to read)
+  const bool beta_apart = a.beta != nullptr && rows * a.gamma > cus && a.temperature > 0.0f;   // (argmax: no rows to read)
   hipLaunchKernelGGL(accept_kernel, dim3(a.draw_wgs + (a.beta != nullptr && !beta_apart ? a.gamma : 0), rows), dim3(SAMPLE_THREADS), 0, stream, a);
   if (beta_apart) hipLaunchKernelGGL(beta_kernel, dim3(a.gamma, rows), dim3(256), 0, stream, a);
 }

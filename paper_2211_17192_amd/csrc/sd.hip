@@ -229,9 +229,9 @@ struct sd_ctx {
   bool all_ready() const { for (int r : ready) if (!r) return false; return true; }
   bool any_stale() const { for (int m : mq_stale) if (m) return true; return false; }
   int last_gamma = 0, last_kind = -1;   // for sd_debug_logits
-  hipGraphExec_t graphs[2 * (SD_MAX_GAMMA + 1)] = {};    // iterations: gamma, and again with filtered rows
+  hipGraphExec_t graphs[3 * (SD_MAX_GAMMA + 1)] = {};    // iterations: gamma; again with filtered rows; again at temperature 0
   bool filtered() const { return sampling.top_k > 0 || (sampling.top_p > 0.0f && sampling.top_p < 1.0f); }
-  hipGraphExec_t* graph_of(int gamma) { return &graphs[gamma + (filtered() ? SD_MAX_GAMMA + 1 : 0)]; }
+  hipGraphExec_t* graph_of(int gamma, bool argmax) { return &graphs[gamma + (argmax ? 2 : filtered() ? 1 : 0) * (SD_MAX_GAMMA + 1)]; }
   hipGraphExec_t graph_baseline[2] = {};                 // plain decoding steps, and with filtered rows
   hipEvent_t ev[4] = {};
   std::vector<hipEvent_t> kev;       // 2 per Mp layer: around the gated FFN-in GEMM (SD_FLAG_PROFILE)
@@ -1006,8 +1006,8 @@ void cross_kv(sd_ctx* c, Model& m, const void* enc) {
 }
 
 // One draw per sequence from the row at logits + b * seq_stride (mode 0: guess number `slot`; 1: commit).
-void launch_draw(sd_ctx* c, const float* logits, int uniform_idx, int mode, int slot, size_t seq_stride) {
-  if (c->filtered()) {
+void launch_draw(sd_ctx* c, const float* logits, int uniform_idx, int mode, int slot, size_t seq_stride, bool argmax = false) {
+  if (c->filtered() && !argmax) {                    // (argmax sampling ignores the filters)
     hipLaunchKernelGGL(sample_row_filter_kernel, dim3(c->batch), dim3(SAMPLE_THREADS), 0, c->stream, logits, c->p.cfg.vocab, c->d_params,
                        uniform_idx, c->d_state, mode, slot, seq_stride);
     return;
@@ -1020,7 +1020,7 @@ void launch_draw(sd_ctx* c, const float* logits, int uniform_idx, int mode, int 
 
 // The launch sequence of one run of Algorithm 1 for every sequence (everything between the
 // upload of the step parameters and the download of the states).
-void enqueue_step(sd_ctx* c, int gamma, bool profile) {
+void enqueue_step(sd_ctx* c, int gamma, bool argmax, bool profile) {
   hipStream_t s = c->stream;
   const int V = c->p.cfg.vocab, B = c->batch;
   if (profile) hipEventRecord(c->ev[0], s);
@@ -1034,7 +1034,7 @@ void enqueue_step(sd_ctx* c, int gamma, bool profile) {
                          c->draft_row_of, c->draft_rows, V, c->d_state, i, c->q_logits + (size_t)i * V, (size_t)gamma * V);
     else if (i == 0) forward_any(c, c->q, Rows{ROWS_DRAFT_FIRST, 0, 2, 0, 0, B, gamma}, c->q_logits);
     else forward_any(c, c->q, Rows{ROWS_DRAFT_NEXT, i, 1, 0, 0, B, gamma}, c->q_logits);
-    launch_draw(c, c->q_logits + (size_t)i * V, i, 0, i, (size_t)gamma * V);
+    launch_draw(c, c->q_logits + (size_t)i * V, i, 0, i, (size_t)gamma * V, argmax);
   }
   if (profile) hipEventRecord(c->ev[1], s);
   // p_1..p_{gamma+1} in one forward
@@ -1045,7 +1045,8 @@ void enqueue_step(sd_ctx* c, int gamma, bool profile) {
   AcceptArgs a{};
   a.p = c->p_logits; a.q = c->q_logits; a.gamma = gamma; a.V = V; a.prm = c->d_params; a.st = c->d_state;
   a.scr = c->d_scratch; a.scr_stride = sizeof(SampleScratch); a.part = c->d_parts; a.part_row = sample_parts(V); a.part_seq = (size_t)(2 * gamma + 1) * a.part_row;
-  a.top_k = c->filtered() ? 1 : 0;
+  a.temperature = argmax ? 0.0f : 1.0f;
+  a.top_k = (!argmax && c->filtered()) ? 1 : 0;
   if (c->rt.flags & SD_FLAG_BETA) a.beta = c->d_state->beta;           // side output: beta_i of every guess, into the states
   launch_accept(s, a, B, g_num_cus);
   if (c->copy_match > 0) hipLaunchKernelGGL(hist_append_kernel, dim3(B), dim3(32), 0, s, c->d_hist, c->hist_stride, c->d_state, 1);
@@ -1394,11 +1395,11 @@ extern "C" sd_status sd_step(sd_ctx* c, const int32_t* prefix, int32_t prefix_le
   const bool profile = (c->rt.flags & SD_FLAG_PROFILE) != 0;
   const bool graph = (c->rt.flags & SD_FLAG_GRAPH) != 0 && !profile;
   if (graph) {
-    hipGraphExec_t* ge = c->graph_of(gamma);
+    hipGraphExec_t* ge = c->graph_of(gamma, temperature == 0.0f);
     if (!*ge) {
       st = capture_graph(c, ge, [&] {
         hipMemcpyAsync(c->d_params, c->h_params, pbytes, hipMemcpyHostToDevice, c->stream);
-        enqueue_step(c, gamma, false);
+        enqueue_step(c, gamma, temperature == 0.0f, false);
         hipMemcpyAsync(c->h_state, c->d_state, sbytes, hipMemcpyDeviceToHost, c->stream);
       });
       if (st != SD_OK) return st;
@@ -1407,7 +1408,7 @@ extern "C" sd_status sd_step(sd_ctx* c, const int32_t* prefix, int32_t prefix_le
     HIP_TRY(c, hipStreamSynchronize(c->stream));
   } else {
     HIP_TRY(c, hipMemcpyAsync(c->d_params, c->h_params, pbytes, hipMemcpyHostToDevice, c->stream));
-    enqueue_step(c, gamma, profile);
+    enqueue_step(c, gamma, temperature == 0.0f, profile);
     if ((st = sync_state_to_host(c)) != SD_OK) return st;
   }
   HIP_TRY(c, hipGetLastError());
