@@ -1,6 +1,7 @@
-"""Prefill of many rows at once: a sequence that is prefilled whole must stand exactly where the same
+"""Products over many rows.  Prefill: a sequence that is prefilled whole must stand exactly where the same
 sequence stands after it was decoded token by token (other kernels, the same additions in the same
-order), so the next iteration's logits of both models are equal bit for bit."""
+order), so the next iteration's logits of both models are equal bit for bit.  Several sequences: each must
+get the logits and tokens that it gets alone."""
 import numpy as np
 import pytest
 import torch
@@ -28,13 +29,39 @@ CASES = {
 }
 
 
+# Products whose tiles fill the rounds of 256 workgroups of eight wavefronts (256 features x 128 rows; a gated
+# product's half as many features), rows no multiple of 128: QKV, gated, O / FFN-out; and with LayerNorm and biases
+EIGHT = {
+    "gqa-1999-eight": (T.GQA, 4096, 32, 16, 64, 2048, 2, 1999, 0),
+    "gpt-2017-eight": (T.GPT, 4096, 32, 32, 64, 4096, 2, 2017, 0),
+}
+
+
+def takes_eight_wavefronts(rows, n, gated=False):
+    """The rule of the launcher on a device of 256 CUs."""
+    wgs = -(-(n // 16) // (8 if gated else 16)) * -(-(-(-rows // 16)) // 8)
+    return rows > 128 and 100 * wgs >= 85 * 256 * -(-wgs // 256)
+
+
+@pytest.mark.parametrize("name", list(EIGHT))
+def test_prefill_with_eight_wavefront_products_equals_token_by_token(name):
+    arch, d, heads, kv, dh, ff, layers, rows, enc = EIGHT[name]
+    assert takes_eight_wavefronts(rows, d) and takes_eight_wavefronts(rows, ff, arch == T.GQA)
+    assert arch != T.GQA or takes_eight_wavefronts(rows, (heads + 2 * kv) * dh)
+    prefill_equals_token_by_token(EIGHT[name], False)
+
+
 @pytest.mark.parametrize("scatter", [False, True])
 @pytest.mark.parametrize("name", list(CASES))
 def test_prefill_equals_token_by_token(name, scatter):
-    from paper_2211_17192_amd import binding
-    arch, d, heads, kv, dh, ff, layers, rows, enc = CASES[name]
-    if scatter and rows > 300:
+    if scatter and CASES[name][7] > 300:
         pytest.skip("the page table's order is covered by the small cases")
+    prefill_equals_token_by_token(CASES[name], scatter)
+
+
+def prefill_equals_token_by_token(case, scatter):
+    from paper_2211_17192_amd import binding
+    arch, d, heads, kv, dh, ff, layers, rows, enc = case
     gamma, vocab = 3, 512
     kw = dict(n_kv_heads=kv) if arch == T.GQA else {}
     cfg = synth.model_cfg(arch, layers, d, heads, ff, vocab, rows + 40, d_head=dh, enc_len=enc, dtype="bf16", logit_scale=4.0, **kw)
@@ -62,12 +89,60 @@ def test_prefill_equals_token_by_token(name, scatter):
     assert (n1, t1) == (n2, t2)
 
 
+# (arch, d_model, heads, kv heads, d_head, d_ff, vocab, sequences, gamma, temperature): rows = sequences x (gamma + 1)
+BATCHES = {
+    # LayerNorm rows: two slabs and a ragged one, the smallest products
+    "gpt-3x6": (T.GPT, 128, 2, 2, 64, 512, 512, 3, 5, 1.0),
+    # five slabs, argmax; key ranges are tested by the 8B-class shapes
+    "gpt-20x4-argmax": (T.GPT, 768, 12, 12, 64, 3072, 512, 20, 3, 0.0),
+    # the most rows of a draft and of a verify forward, d_head 128
+    "gpt-64x3": (T.GPT, 256, 2, 2, 128, 1024, 512, 64, 2, 1.0),
+    "gqa-48x4": (T.GQA, 512, 8, 4, 64, 1408, 512, 48, 3, 1.0),
+    # residual products of 64 MB over five slabs: K chunks over workgroups
+    "gqa-16x5-split": (T.GQA, 2048, 8, 2, 128, 16384, 512, 16, 4, 1.0),
+    # LM head over 144 rows: workgroups of eight wavefronts
+    "gqa-16x9-head": (T.GQA, 256, 4, 4, 64, 512, 32000, 16, 8, 1.0),
+}
+
+
+@pytest.mark.parametrize("name", list(BATCHES))
+def test_sequences_together_equal_each_alone(name):
+    from paper_2211_17192_amd import binding
+    arch, d, heads, kv, dh, ff, vocab, B, gamma, temperature = BATCHES[name]
+    assert "head" not in name or takes_eight_wavefronts(B * (gamma + 1), vocab)
+    kw = dict(n_kv_heads=kv) if arch == T.GQA else {}
+    cfg = synth.model_cfg(arch, 2, d, heads, ff, vocab, 160, d_head=dh, dtype="bf16", logit_scale=4.0, **kw)
+    w = synth.random_weights(cfg, 5, "cuda", 0.04)
+    cfg_q, w_q = synth.truncated_noisy_copy(cfg, w, 1, 9, 0.004)
+    together = binding.SpecDecoder(cfg, w, cfg_q, w_q, max_gamma=gamma, flags=binding.SD_FLAG_GRAPH, batch=B)
+    alone = binding.SpecDecoder(cfg, w, cfg_q, w_q, max_gamma=gamma, flags=binding.SD_FLAG_GRAPH)
+    prompts = [[int(t) for t in synth.random_tokens(40 + b, 4 + 37 * b % 50, vocab)] for b in range(B)]
+    iterations = 3
+    u = synth.uniform_stream(13, iterations * B * (2 * gamma + 1)).reshape(iterations, B, 2 * gamma + 1)
+    for b, p in enumerate(prompts):
+        together.prefill(p, row=b)
+    got = []
+    for it in range(iterations):
+        res = together.step(gamma, temperature, u[it])
+        got.append((res, together.logits(0, B * (gamma + 1)).reshape(B, gamma + 1, vocab), together.logits(1, B * gamma).reshape(B, gamma, vocab)))
+    assert np.isfinite(got[0][1]).all() and np.ptp(got[0][1]) > 1.0
+    for b, p in enumerate(prompts):
+        alone.reset()
+        alone.prefill(p)
+        for it in range(iterations):
+            assert alone.step(gamma, temperature, u[it, b]) == got[it][0][b], (it, b)
+            assert np.array_equal(alone.logits(0, gamma + 1), got[it][1][b]), (it, b)
+            assert np.array_equal(alone.logits(1, gamma), got[it][2][b]), (it, b)
+    together.close()
+    alone.close()
+
+
 # (arch, d_model, heads, kv heads, d_head, d_ff, vocab, max_len, enc_len, max_gamma, sequences), and the bytes of a
 # workspace without room for prompt passes of more than 16 rows (what the pair needs otherwise, with 31 KB of row
 # statistics a sequence beside the activations: sizes that loaded before those passes existed)
 WORKSPACES = {
     "gqa-key-ranges": ((T.GQA, 256, 4, 2, 64, 512, 512, 1500, 0, 3, 1), 7933184),
-    "gqa-key-ranges-3": ((T.GQA, 256, 4, 2, 64, 512, 512, 1500, 0, 3, 3), 16591616),
+    "gqa-key-ranges-6": ((T.GQA, 256, 4, 2, 64, 512, 512, 1500, 0, 3, 6), 24270592),          # 24 rows in two slabs
     "gpt-gamma-15": ((T.GPT, 128, 2, 2, 64, 256, 50256, 300, 0, 15, 1), 59184640),
     "t5": ((T.T5DEC, 256, 4, 4, 64, 512, 512, 200, 100, 3, 1), 7660800),
 }
