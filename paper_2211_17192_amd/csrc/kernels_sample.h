@@ -669,6 +669,19 @@ __device__ __forceinline__ void post(double* p, double v) {
 __device__ __forceinline__ double collect(const double* p) {
   return __longlong_as_double((long long)__hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
 }
+__device__ __forceinline__ void post_part(RowPart* p, const RowPart& r) {
+  static_assert(sizeof(RowPart) == 16, "two words");
+  double w[2];
+  __builtin_memcpy(w, &r, 16);
+  post(reinterpret_cast<double*>(p), w[0]);
+  post(reinterpret_cast<double*>(p) + 1, w[1]);
+}
+__device__ __forceinline__ RowPart collect_part(const RowPart* p) {
+  const double w[2] = {collect(reinterpret_cast<const double*>(p)), collect(reinterpret_cast<const double*>(p) + 1)};
+  RowPart r;
+  __builtin_memcpy(&r, w, 16);
+  return r;
+}
 __device__ __forceinline__ bool last_to_post(unsigned int* ticket, unsigned int expected, int* lds_flag) {
   if (expected == 1u) { __syncthreads(); return true; }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wavefront's posts have reached memory
@@ -841,7 +854,6 @@ struct AcceptArgs {
   int gamma, V;
   int part_len, nparts;                // entries of one part of a row's statistics (a multiple of SAMPLE_PART), parts per row
   int chunks_wave, draw_wgs;           // accept_kernel: chunks per wavefront; workgroups of a sequence's draw (beta's follow)
-  int self;                            // accept_kernel: the statistics are its own work
   // in-model use: only whether the temperature is 0 and whether the rows are filtered (the values are read from prm)
   float temperature, lenience;
   double log_lenience;
@@ -881,6 +893,8 @@ __device__ __forceinline__ void load_part(const AcceptArgs& a, int b, int j, int
 }
 // Every exponential is taken relative to the block's maximum over the whole wavefront (never to a lane's
 // own: a lane may hold nothing but padding) and goes into the sum as a double.
+// POSTED: another workgroup reads them in the same launch.
+template <bool POSTED>
 __device__ __forceinline__ void reduce_part(const AcceptArgs& a, int b, int j, int part, int lane, float4 (&v)[SAMPLE_PART / 256]) {
   constexpr int NV = SAMPLE_PART / 256;
   const float T = a.prm ? a.prm[b].temperature : a.temperature;
@@ -930,7 +944,12 @@ __device__ __forceinline__ void reduce_part(const AcceptArgs& a, int b, int j, i
     if (lane == 0) { out->S = 0.0; out->m = M; out->arg = arg; }
   } else {
     s = wave_sum(s);
-    if (lane == 0) { out->S = s; out->m = m; out->thr = -INFINITY; }
+    if (lane == 0) {
+      RowPart r;
+      r.S = s; r.m = m; r.thr = -INFINITY;
+      if (POSTED) post_part(out, r);
+      else *out = r;
+    }
   }
 }
 
@@ -957,7 +976,7 @@ static __global__ __launch_bounds__(256, 6) void row_parts_kernel(const AcceptAr
   auto reduce = [&](int item, float4 (&v)[NV]) {
     int part, j, b;
     locate(item, part, j, b);
-    reduce_part(a, b, j, part, lane, v);
+    reduce_part<false>(a, b, j, part, lane, v);
   };
   int item = (int)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (item >= items) return;
@@ -994,10 +1013,11 @@ static __global__ __launch_bounds__(SAMPLE_THREADS) void row_filter_kernel(const
 }
 
 // A row's statistics from its parts, by one wavefront (lane = part); every lane gets them.
+template <bool POSTED = false>
 __device__ __forceinline__ RowStat join_parts(const RowPart* parts, int nparts, bool greedy, float invT) {
   const int i = threadIdx.x & 63;
   const bool ok = i < nparts;
-  const RowPart rp = parts[min(i, nparts - 1)];
+  const RowPart rp = POSTED ? collect_part(parts + min(i, nparts - 1)) : parts[min(i, nparts - 1)];
   RowStat st; st.arg = 0; st.S = 0.0; st.pad = 0.0f;
   st.m = wave_max(ok ? rp.m : -INFINITY);
   st.thr = greedy ? -INFINITY : rp.thr;              // (filtered rows have one part, which every lane read)
@@ -1084,9 +1104,9 @@ __device__ __forceinline__ void beta_guess(const AcceptArgs& a, int b, int i, Ro
   if (tid == 0) (a.st ? a.st[b].beta : a.beta + (size_t)b * gamma)[i] = (float)t;
 }
 
-// A launch of its own where the guesses of a call outnumber the CUs: accept_kernel's registers let a CU hold
+// A launch of its own where there are three guesses to two CUs or more: accept_kernel's registers let a CU hold
 // one of its workgroups, so hundreds of these would queue there (200 sequences, gamma 7, vocabulary 16384:
-// 114 -> 78 us a call).  grid = (gamma, rows).
+// 114 -> 78 us a call; 38 of vocabulary 10454, 266 guesses: 23.2 there, 24.6 apart).  grid = (gamma, rows).
 static __global__ __launch_bounds__(256, 6) void beta_kernel(const AcceptArgs a) {
   __shared__ RowStat jr[2];
   __shared__ double ctot[SAMPLE_CHUNK * SAMPLE_MAX_CHUNKS / SAMPLE_PART];
@@ -1096,11 +1116,12 @@ static __global__ __launch_bounds__(256, 6) void beta_kernel(const AcceptArgs a)
 // Decisions, draw, commit.  Every workgroup of a sequence joins the statistics and takes the decisions
 // itself (a few hundred words), then sums the weights of its chunks of row n (16 chunks_wave of
 // them); the last to arrive scans the totals and walks the chunk that holds u * total.
-// A small call (`self`, launch_accept) is this one launch, one workgroup a sequence: a second launch would
-// cost it more than its work.
+// A small call is this one launch (OWN, launch_accept): a second one would cost it more than its work.
 // 64 sequences, gamma 7, vocabulary 32128 (123 MB), both launches, calls back to back in a graph: 35.7 us
 // (row_parts_kernel 22: 5.6 TB/s, a pure read's rate at this size); with one 1024-thread workgroup per row and
 // then one per sequence it was 42.2.  One sequence, gamma 4: 11.1 us against 16.8.
+enum { OWN_NONE, OWN_SEQUENCE, OWN_ROWS };           // whose the statistics are: row_parts_kernel's; this kernel's, a workgroup per sequence / per logits row
+template <int OWN>
 static __global__ __launch_bounds__(SAMPLE_THREADS) void accept_kernel(const AcceptArgs a) {
   __shared__ SampleSmem sm;
   __shared__ RowStat srow[2 * SAMPLE_MAX_GAMMA + 1];
@@ -1118,7 +1139,7 @@ static __global__ __launch_bounds__(SAMPLE_THREADS) void accept_kernel(const Acc
   const int* x = st ? st->x : a.x + (size_t)b * gamma;
   const float* r = prm ? prm->uniforms + gamma : a.r + (size_t)b * gamma;   // (not read by argmax sampling)
   const float s = greedy ? 0.5f : (prm ? prm->uniforms[2 * gamma] : a.s[b]);
-  if ((int)blockIdx.x >= a.draw_wgs) {               // beta of guess i (after a.self's statistics: none of those launches come here)
+  if (OWN == OWN_NONE && (int)blockIdx.x >= a.draw_wgs) {          // beta of guess i
     beta_guess<SAMPLE_THREADS>(a, b, (int)blockIdx.x - a.draw_wgs, srow, sm.ctot);
     return;
   }
@@ -1130,16 +1151,23 @@ static __global__ __launch_bounds__(SAMPLE_THREADS) void accept_kernel(const Acc
     zpx = P[(size_t)tid * V + xi];
     if (!greedy) { zqx = Q[(size_t)tid * V + xi]; ri = r[tid]; }
   }
-  if (a.self) {
+  if (OWN == OWN_SEQUENCE) {
     for (int item = wave; item < nrows * a.nparts; item += SAMPLE_THREADS / 64) {
       float4 v[SAMPLE_PART / 256];
       load_part(a, b, item / a.nparts, item % a.nparts, lane, v);
-      reduce_part(a, b, item / a.nparts, item % a.nparts, lane, v);
+      reduce_part<false>(a, b, item / a.nparts, item % a.nparts, lane, v);
     }
     __syncthreads();
+  } else if (OWN == OWN_ROWS) {
+    for (int part = wave; part < a.nparts; part += SAMPLE_THREADS / 64) {
+      float4 v[SAMPLE_PART / 256];
+      load_part(a, b, blockIdx.x, part, lane, v);
+      reduce_part<true>(a, b, blockIdx.x, part, lane, v);
+    }
+    if (!last_to_post(scr->ticket, (unsigned)nrows, &sm.flag)) return;
   }
   for (int row = wave; row < nrows && !(greedy && row > gamma && a.beta == nullptr); row += SAMPLE_THREADS / 64) {
-    const RowStat rs = join_parts(accept_part(a, b, row), accept_filtered(a) ? 1 : a.nparts, greedy, invT);
+    const RowStat rs = join_parts<OWN == OWN_ROWS>(accept_part(a, b, row), accept_filtered(a) ? 1 : a.nparts, greedy, invT);
     if (lane == 0) srow[row] = rs;
   }
   __syncthreads();
@@ -1165,7 +1193,7 @@ static __global__ __launch_bounds__(SAMPLE_THREADS) void accept_kernel(const Acc
   const int n = sm.n;
   int t = 0, fell_back = 0;
   if (greedy) {
-    if (blockIdx.x != 0) return;
+    if (OWN == OWN_NONE && blockIdx.x != 0) return;
     t = srow[n].arg;
   } else {
     RowPair rp;
@@ -1175,7 +1203,7 @@ static __global__ __launch_bounds__(SAMPLE_THREADS) void accept_kernel(const Acc
     rp.mp = sp.m; rp.mq = sq.m; rp.tp = sp.thr; rp.tq = sq.thr; rp.invT = invT; rp.V = V;
     rp.invSp = 1.0 / sp.S; rp.invSq = with_q ? len / sq.S : 0.0;                 // q enters the residual as l * q
     constexpr int CB = 4;                            // chunks whose loads a wavefront keeps in flight
-    const int c0 = (int)blockIdx.x * SAMPLE_CHUNKS_WG * a.chunks_wave + wave;
+    const int c0 = (OWN ? 0 : (int)blockIdx.x) * SAMPLE_CHUNKS_WG * a.chunks_wave + wave;
     for (int i0 = 0; i0 < a.chunks_wave; i0 += CB) {
       RawPair raw[CB];
 #pragma unroll
@@ -1296,24 +1324,37 @@ inline void launch_accept(hipStream_t stream, AcceptArgs a, int rows, int cus) {
     launch_argmax(stream, a, rows);
     return;
   }
-  // one launch: up to one part a wavefront, and up to three where the sequences themselves fill the chip
-  // (us, one launch against two: 12 parts, one sequence 8.0 / 8.7; 28 parts 10.0 / 9.2; 48 parts 16.3 / 10.3;
-  // 28 parts, 200 sequences 11.0 / 12.7; 48 parts 19.6 / 22.9)
-  a.self = !accept_filtered(a) && a.beta == nullptr && nrows * a.nparts <= (2 * rows > cus ? 48 : 16) && wgs <= 4;
+  // One launch or two: a second one costs the host 2.6 us, a loop of such calls its time.  Us a call, from a host loop /
+  // captured, one sequence of gamma 7 unless said:
+  //   vocabulary 1000 (15 parts)         OWN_SEQUENCE 9.6 / 9.0
+  //   2000 (30)                          OWN_SEQUENCE 12.1 / 11.9   OWN_ROWS 9.8 / 8.6     two 12.5 / 9.4
+  //   8000 (120)                                                    OWN_ROWS 11.4 / 11.1   two 12.5 / 11.2
+  //   16000, gamma 1 (48)                OWN_SEQUENCE 16.1 / 16.1   OWN_ROWS - / 12.9      two 12.4 / 10.3
+  //   50 sequences, gamma 4, 2919 (27)   OWN_SEQUENCE 10.9 / 10.7                          two 12.3 / 10.5
+  //   200 sequences, gamma 1, 16384 (48) OWN_SEQUENCE - / 19.6                             two - / 22.9
+  const int parts = nrows * a.nparts;
+  int own = OWN_NONE;
+  if (!accept_filtered(a) && a.beta == nullptr) {
+    if (parts <= 16 || (rows * nrows > cus && parts <= 28) || (2 * rows > cus && parts <= 48 && wgs <= 4)) own = OWN_SEQUENCE;
+    else if (rows * nrows <= cus && wgs <= 2) own = OWN_ROWS;
+  }
   if (accept_filtered(a)) {
     hipLaunchKernelGGL(row_filter_kernel, dim3(nrows, rows), dim3(SAMPLE_THREADS), 0, stream, a);
-  } else if (!a.self) {
+  } else if (own == OWN_NONE) {
     const int items = rows * nrows * a.nparts;
     hipLaunchKernelGGL(row_parts_kernel, dim3(min((items + 3) / 4, cus * ACCEPT_WAVES_CU / 4)), dim3(256), 0, stream, a, items,
                        (unsigned)((0x100000000ull + a.nparts - 1) / a.nparts), (unsigned)((0x100000000ull + nrows - 1) / nrows));
   }
   // as many workgroups a sequence as fit the CUs in one round; more only repeat the decisions more often
   // (200 sequences, gamma 1, vocabulary 32128: 35.3 us with one, 49.1 with a second that takes the last chunks)
-  const int most = a.self ? 1 : min(wgs, max(1, cus / rows));
+  const int most = own ? 1 : min(wgs, max(1, cus / rows));
   a.chunks_wave = (wgs + most - 1) / most;
-  a.draw_wgs = (wgs + a.chunks_wave - 1) / a.chunks_wave;
-  const bool beta_apart = a.beta != nullptr && rows * a.gamma > cus && a.temperature > 0.0f;   // (argmax: no rows to read)
-  hipLaunchKernelGGL(accept_kernel, dim3(a.draw_wgs + (a.beta != nullptr && !beta_apart ? a.gamma : 0), rows), dim3(SAMPLE_THREADS), 0, stream, a);
+  a.draw_wgs = (wgs + a.chunks_wave - 1) / a.chunks_wave;         // (1 where the statistics are its own work)
+  const bool beta_apart = a.beta != nullptr && 2 * rows * a.gamma > 3 * cus && a.temperature > 0.0f;   // (argmax: no rows to read)
+  const dim3 grid(own == OWN_ROWS ? nrows : a.draw_wgs + (a.beta != nullptr && !beta_apart ? a.gamma : 0), rows), block(SAMPLE_THREADS);
+  if (own == OWN_SEQUENCE) hipLaunchKernelGGL(accept_kernel<OWN_SEQUENCE>, grid, block, 0, stream, a);
+  else if (own == OWN_ROWS) hipLaunchKernelGGL(accept_kernel<OWN_ROWS>, grid, block, 0, stream, a);
+  else hipLaunchKernelGGL(accept_kernel<OWN_NONE>, grid, block, 0, stream, a);
   if (beta_apart) hipLaunchKernelGGL(beta_kernel, dim3(a.gamma, rows), dim3(256), 0, stream, a);
 }
 

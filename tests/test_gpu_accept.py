@@ -147,13 +147,28 @@ def test_lenient_argmax_beta_of_a_draft_row_without_a_number():
             assert beta[b, i] == float(keep)
 
 
+def check_without_beta(zp, zq, x, r, s, temperature, scratch=None):
+    from paper_2211_17192_amd import binding
+    n_g, t_g = (v.cpu().numpy() for v in binding.spec_sample(*(torch.from_numpy(np.ascontiguousarray(v)).cuda() for v in (zp, zq, x, r, s)),
+                                                             temperature, scratch=scratch))
+    for b in range(len(zp)):
+        n, t, info = sampling.accept_and_resample_from_logits(zp[b], zq[b], x[b], r[b], s[b], temperature)
+        if temperature == 0.0 or (n_g[b], t_g[b]) == (n, t):
+            assert (n_g[b], t_g[b]) == (n, t)
+        elif n_g[b] != n:
+            assert info["margins"][min(n_g[b], n)] < 1e-3
+        else:
+            p, q = (np.stack([sampling.standardise(z, temperature) for z in v[b]]) for v in (zp, zq))
+            w = p[n] if n == zq.shape[1] else sampling.adjusted_distribution(p[n], q[n])
+            assert sampling.icdf_edge_distance(w, s[b], int(t_g[b])) < 1e-5
+
+
 # a thread takes 1, 2, 4 or 8 groups of four entries of a row, and longer rows in several passes
 @pytest.mark.parametrize("temperature", [0.0, 0.9])
 @pytest.mark.parametrize("vocab", [3, 5, 255, 1026, 4096, 4097, 8193, 16390, 32768, 32771, 140001])
 def test_calls_without_beta(vocab, temperature):
     """Without beta: argmax sampling is one launch, a small call of any temperature is one launch.  Logits on a
     coarse grid, so that maxima tie across threads, parts and passes; masked entries; both zeros."""
-    from paper_2211_17192_amd import binding
     rows, gamma = 3, 2
     zp, zq, x, r, s = synth.sampler_case(rows, gamma, vocab, 1.0, vocab)
     zp, zq = np.round(zp), np.round(zq)
@@ -164,19 +179,22 @@ def test_calls_without_beta(vocab, temperature):
         x = np.argmax(zq, -1).astype(np.int32)
     else:
         x[1] = np.maximum(x[1], vocab // 2)
-    n_g, t_g = (v.cpu().numpy() for v in binding.spec_sample(*(torch.from_numpy(np.ascontiguousarray(v)).cuda() for v in (zp, zq, x, r, s)), temperature))
-    for b in range(rows):
-        n, t, info = sampling.accept_and_resample_from_logits(zp[b], zq[b], x[b], r[b], s[b], temperature)
-        if temperature == 0.0 or (n_g[b], t_g[b]) == (n, t):
-            assert (n_g[b], t_g[b]) == (n, t)
-        elif n_g[b] != n:
-            assert info["margins"][min(n_g[b], n)] < 1e-3
-        else:
-            p, q = (np.stack([sampling.standardise(z, temperature) for z in v[b]]) for v in (zp, zq))
-            assert sampling.icdf_edge_distance(p[n] if n == gamma else sampling.adjusted_distribution(p[n], q[n]), s[b], int(t_g[b])) < 1e-5
+    check_without_beta(zp, zq, x, r, s, temperature)
 
 
 def test_more_beta_than_compute_units():
-    """The acceptance probabilities of a call with more guesses than CUs come from a launch of their own."""
-    zp, zq, x, r, s = synth.sampler_case(60, 5, 2050, 1.0, 23)
+    """The acceptance probabilities of a call with 3/2 guesses a CU and more come from a launch of their own."""
+    zp, zq, x, r, s = synth.sampler_case(80, 5, 2050, 1.0, 23)
     check(zp, zq, x, r, s, 1.0)
+
+
+def test_one_launch_and_two_launch_calls_share_one_scratch():
+    """A workgroup per sequence, per logits row, statistics in a launch of their own, argmax: in turn."""
+    from paper_2211_17192_amd import binding
+    scratch = binding.spec_sample_scratch(60, 7)
+    for rows, gamma, vocab, temperature in ((1, 7, 2000, 0.9), (1, 4, 20000, 0.9), (60, 4, 3000, 0.9), (2, 3, 5000, 0.0), (8, 7, 8000, 0.9),
+                                            (3, 1, 1000, 0.9), (2, 7, 8192, 0.9), (1, 7, 2000, 0.9)):
+        zp, zq, x, r, s = synth.sampler_case(rows, gamma, vocab, 1.0, rows * 100 + gamma)
+        if temperature == 0.0:
+            x = np.argmax(zq, -1).astype(np.int32)
+        check_without_beta(zp, zq, x, r, s, temperature, scratch)
