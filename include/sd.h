@@ -54,7 +54,7 @@ enum {
   SD_FLAG_GRAPH   = 1,  /* replay each iteration as one hipGraph (draft loop, verify, accept) */
   SD_FLAG_PROFILE = 2,  /* record HIP events around the draft / verify / accept phases */
   SD_FLAG_BETA    = 4,  /* also compute beta_i = sum_x min(p_i(x), q_i(x)) of every guess (section 3.1)
-                           in each sd_step: one more small launch; feeds sd_stats.beta_sum */
+                           in each sd_step, beside the decisions; feeds sd_stats.beta_sum */
   SD_FLAG_SCATTER_PAGES = 8, /* at load only: every sequence's page table lists its KV-cache pages back to
                            front instead of in order.  Results are identical; it exists to show that
                            every kernel finds its pages through the table.  sd_set_flags leaves it as

@@ -1,13 +1,15 @@
 // Sampling kernels: section 2.2 standardisation (temperature softmax / argmax),
 // inverse-CDF draws from caller-supplied uniforms, and the accept / resample
-// part of Algorithm 1 in two launches (row statistics spread over the chip, then
-// the decisions, the draw of the extra token and the commit / roll-back).
+// part of Algorithm 1: row statistics spread over the chip, then the decisions, the
+// draw of the extra token and the commit / roll-back; two launches, small calls and
+// argmax sampling one.
 //
 // Arithmetic of a standardised row z at temperature T > 0:
 //   m = max_k z_k,  e_k = exp((z_k - m) / T)  (fp32 hardware exp2 path),
 //   S = sum_k e_k (fp64),  prob_k = e_k * (1/S) (fp64).
 // Sums and cumulative sums are carried in fp64, so the blocked summation order
-// differs from a sequential one only far below the resolution of the uniforms.
+// differs from a sequential one only far below the resolution of the uniforms.  (S of a row
+// that top-k / nucleus filter: a thread's up to 32 entries in fp32 first.)
 // T == 0 uses integer argmax compares (ties to the lowest index).
 #pragma once
 #include <limits.h>
