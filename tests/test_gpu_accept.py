@@ -198,3 +198,17 @@ def test_one_launch_and_two_launch_calls_share_one_scratch():
         if temperature == 0.0:
             x = np.argmax(zq, -1).astype(np.int32)
         check_without_beta(zp, zq, x, r, s, temperature, scratch)
+
+
+@pytest.mark.parametrize("vocab", [5, 1026, 32771, 65540, 140001])
+def test_argmax_with_beta(vocab):
+    """Temperature 0 with the acceptance probabilities: statistics of every row, parts of several blocks in the
+    longest; beta is 1 where both argmaxes agree."""
+    zp, zq, _, r, s = synth.sampler_case(2, 2, vocab, 1.0, vocab)
+    zp, zq = np.round(zp), np.round(zq)
+    zq[1] = zp[1, :2]
+    x = np.argmax(zq, -1).astype(np.int32)
+    n, t, beta = call(zp, zq, x, r, s, 0.0)
+    for b in range(2):
+        assert (n[b], t[b]) == sampling.accept_and_resample_from_logits(zp[b], zq[b], x[b], r[b], s[b], 0.0)[:2]
+        assert np.array_equal(beta[b], (np.argmax(zp[b, :2], -1) == x[b]).astype(np.float32))
