@@ -10,23 +10,24 @@
 //  * The weights sit on the MFMA "A" side (16 output features), the R
 //    activation rows on the 16-wide "B" side; fp32 accumulation.
 //  * A workgroup works through 16-feature tiles (tile = block, block + grid,
-//    ...) with a two-stage software pipeline: the loads of the next chunk, or of
-//    the next tile's first chunk, are in flight while the current one is
-//    multiplied, reduced and written out.  Its S wavefronts split K and the
-//    partial tiles are added through LDS in wave order 0..S-1.  S depends on
-//    (N, K) only, never on R, so a row's result is bit-identical whether it is
-//    computed alone or among gamma+1 rows.
+//    ...): the loads of the next chunk of K, or of the next tile's first chunk, are
+//    in flight while the current one is multiplied, reduced and written out.
+//    Its S wavefronts split K and the partial tiles are added through LDS in
+//    wave order 0..S-1.  S depends on K only, never on R, so a row's result is
+//    bit-identical whether it is computed alone or among gamma+1 rows.
 //  * Vector-memory loads complete in issue order as far as the wait counter can
 //    tell, so the kernel keeps them branch-free and issues whatever the epilogue
-//    reads (residual, bias, gain, rotary table) BEFORE the prefetch of the next
-//    chunk; otherwise every epilogue would drain the prefetch.
+//    reads (residual, bias, gain, rotary table) ahead of the next chunk's
+//    loads; otherwise every epilogue would drain those.
 //  * RMSNorm is folded around the GEMM: the producer of the residual stream
 //    (embedding or a residual-add epilogue) also writes xg = x * gain of the
 //    next norm in the storage type and, per 16-feature tile, the partial sums
 //    of x^2; the consumer multiplies plain xg rows and scales its output rows
 //    by 1/rms, which it gets by adding the partials in tile order.  No pass
 //    over x, no barrier before the weight stream starts.
-//  * LayerNorm (mean subtraction) is applied as a prologue on the fp32 rows.
+//  * LayerNorm (mean subtraction) is applied as a prologue on the fp32 rows; the row's
+//    mean and variance come from per-tile statistics that the producer of the
+//    residual stream left (LnTile).
 //  * Epilogues: bias, tanh-GELU, gated GELU / SwiGLU (two weight streams, one
 //    activation stream), residual add, rotary + scatter of q / k / v (k and v
 //    go straight into the paged KV cache), logit scaling.
@@ -36,7 +37,9 @@
 namespace sd {
 
 enum { PRO_NONE = 0, PRO_POST = 1, PRO_LN = 2 };
-enum { EPI_STORE = 0, EPI_QKV = 1, EPI_RESID = 2, EPI_ACT = 3, EPI_GATED = 4, EPI_LOGITS = 5 };
+// EPI_RESID_LN (gemm_kernel): the residual add of a LayerNorm model (bias, LnTile statistics) apart from an RMSNorm
+// model's (scaled rows, partial sums of squares); the other kernels tell them by their arguments.
+enum { EPI_STORE = 0, EPI_QKV = 1, EPI_RESID = 2, EPI_ACT = 3, EPI_GATED = 4, EPI_LOGITS = 5, EPI_RESID_LN = 6 };
 enum { ACT_GELU = 0, ACT_SILU = 1 };
 
 struct GemmArgs {
@@ -46,10 +49,11 @@ struct GemmArgs {
   const void* gain;       // T [K]   (PRO_LN)
   const void* beta;       // T [K]   (PRO_LN)
   const void* bias;       // T [N] or nullptr
-  const float* ss_in;     // PRO_POST: [n_part][16] partial sums of x^2 of the input rows
+  const float* ss_in;     // PRO_POST: [n_part][16] partial sums of x^2 of the input rows; PRO_LN: LnTile statistics of the rows
   int n_part;
   int R, K, N;
   int ksteps_per_wave;    // ceil((K/32) / waves)
+  int tiles_per_wg;       // gemm_kernel: most tiles a workgroup takes
   float eps;
   void* out;              // STORE/ACT/GATED: T [R][ldo]; RESID, LOGITS: float [R][ldo]
   int ldo;
@@ -60,12 +64,13 @@ struct GemmArgs {
   void* xg_out;           // T [R][ldo]: (x + y) * gain_next
   const void* gain_next;  // T [N]
   float* ss_out;          // [N/16][16] partial sums of (x + y)^2 per tile and row
+  float* ln_out;          // for a following LayerNorm instead: LnTile statistics of x + y (optional)
   // EPI_QKV
   void* q_out;            // T [R][nq]
   int nq, nkv;            // features [0,nq) q, [nq,nq+nkv) k, [nq+nkv,nq+2nkv) v
   void* kv_pool;          // this layer's pages: [page][2][n_kv_heads][page_size][d_head]
   const int* page_table;
-  int page_size, n_kv_heads, d_head;
+  int page_size, n_kv_heads, d_head;   // page_size and d_head: powers of two
   const int* row_pos;     // [R] position of each row; < 0: row is padding
   // several sequences in one launch (all optional)
   const int* row_seq;     // EPI_QKV: [R] sequence of each row; its page table starts at page_table + seq * pt_stride
@@ -173,11 +178,79 @@ __device__ __forceinline__ float square(float x) {
   const float q = x * x;
   return q;
 }
-// variance accumulation of the LayerNorm prologue
-__device__ __forceinline__ float add_square(float acc, float x) {
+// Statistics behind a LayerNorm: whoever writes the rows of the residual stream leaves, per row and
+// 16-feature tile, the tile's mean and its sum of squared distances from that mean; the tiles' means and
+// sums then give the row's mean and variance exactly as two passes over the row would (parallel-variance
+// identity, tiles of equal size).  They lie as [k-step][16 rows][tile of the k-step: mean, sum][..], 16 bytes per
+// (k-step, row): the two tiles of a 32-wide k-step.  All four functions below are shared by every kernel that
+// writes or reads them, contraction off, so that a row's statistics do not depend on the kernel.
+struct LnTile { float mean, m2; };
+// sum over the 16 lanes of a row, the same bits in every lane: ((q0 + q1) + (q2 + q3)), q = (f0 + f1) + (f2 + f3) of a quad
+__device__ __forceinline__ float row16_sum(float v) {
+  auto mirror = [](float x, auto ctrl) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), decltype(ctrl)::value, 0xf, 0xf, true));
+  };
+  v += mirror(v, std::integral_constant<int, 0xB1>());        // quad_perm 1 0 3 2
+  v += mirror(v, std::integral_constant<int, 0x4E>());        // quad_perm 2 3 0 1
+  v += mirror(v, std::integral_constant<int, 0x141>());       // row_half_mirror
+  v += mirror(v, std::integral_constant<int, 0x140>());       // row_mirror
+  return v;
+}
+// one feature a lane, 16 lanes a tile
+__device__ __forceinline__ LnTile ln_tile(float x) {
 #pragma clang fp contract(off)
-  const float q = x * x;
-  return acc + q;
+  LnTile t;
+  t.mean = row16_sum(x) * 0.0625f;
+  const float d = x - t.mean;
+  t.m2 = row16_sum(d * d);
+  return t;
+}
+// eight consecutive features a lane: tile = this lane and its partner; `with_partner(v)` adds the partner's value
+template <typename Add> __device__ __forceinline__ LnTile ln_tile8(const float (&x)[8], Add&& with_partner) {
+#pragma clang fp contract(off)
+  LnTile t;
+  t.mean = with_partner(((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]))) * 0.0625f;
+  float q[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) { const float d = x[e] - t.mean; q[e] = d * d; }
+  t.m2 = with_partner(((q[0] + q[1]) + (q[2] + q[3])) + ((q[4] + q[5]) + (q[6] + q[7])));
+  return t;
+}
+__device__ __forceinline__ void ln_put(float* stats, int tile, int row16, const LnTile& t) {
+  *reinterpret_cast<float2*>(stats + ((size_t)(tile >> 1) * 16 + row16) * 4 + (tile & 1) * 2) = make_float2(t.mean, t.m2);
+}
+// Mean and 1 / sqrt(variance + eps) of row j, by the four lanes (j, kq) of a wavefront: lane kq adds the k-steps kq, kq + 4, ..
+// The first LN_HELD of them come in registers (`held`, asked for early), the others through more(k-step).
+constexpr int LN_HELD = 8;
+__device__ __forceinline__ void ln_load(float4 (&held)[LN_HELD], const float* stats, int j, int kq, int KS) {
+#pragma unroll
+  for (int i = 0; i < LN_HELD; ++i) held[i] = *reinterpret_cast<const float4*>(stats + (unsigned)((min(kq + 4 * i, KS - 1) * 16 + j) * 4));
+}
+template <typename More>
+__device__ __forceinline__ void ln_row(const float4 (&held)[LN_HELD], More&& more, int kq, int KS, int K, float eps, float& mu, float& rstd) {
+#pragma clang fp contract(off)
+  auto total = [&](auto&& of) {                      // two sums a lane: shorter ones, closer to the exact sum
+    float s[2] = {0.0f, 0.0f};
+#pragma unroll
+    for (int i = 0; i < LN_HELD; ++i) {
+      const float t = s[i & 1] + of(held[i]);
+      s[i & 1] = (kq + 4 * i < KS) ? t : s[i & 1];
+    }
+    for (int ks = kq + 4 * LN_HELD; ks < KS; ks += 8) {
+      s[0] += of(more(ks));
+      const float t = s[1] + of(more(min(ks + 4, KS - 1)));
+      s[1] = (ks + 4 < KS) ? t : s[1];
+    }
+    float r = s[0] + s[1];
+    r = lane_combine<16>(r, OpSumF());
+    return lane_combine<32>(r, OpSumF());
+  };
+  mu = total([](const float4& v) { return v.x + v.z; }) / (float)(K >> 4);
+  const float q = total([&](const float4& v) {
+    const float d0 = v.x - mu, d1 = v.z - mu;
+    return (v.y + 16.0f * (d0 * d0)) + (v.w + 16.0f * (d1 * d1));
+  });
+  rstd = 1.0f / sqrtf(q / (float)K + eps);
 }
 // LayerNorm of one element
 __device__ __forceinline__ float ln_apply(float v, float mu, float rstd, float g, float b) {
@@ -188,356 +261,319 @@ __device__ __forceinline__ float ln_apply(float v, float mu, float rstd, float g
 }
 
 // k-steps per chunk of the software pipeline (a chunk's loads go out together, unconditionally:
-// k-steps beyond a wavefront's slice re-read its last one).  8 for long K-slices; a wavefront
-// whose whole slice is 4 k-steps or fewer (d_model 512 over 4 wavefronts) takes chunks of 4, so
-// that half of its loads are not duplicates: 7 % off the small draft model's forward.
-constexpr int GEMM_UNROLL = 8;
-constexpr int GEMM_UNROLL_SHORT = 4;
-constexpr int GEMM_PART_REGS = 16;          // partial sums of x^2 an epilogue thread adds from LDS: 16 x 16 tiles
-constexpr int GEMM_PART_STAGE = 16 * GEMM_PART_REGS;   // tiles whose partial sums are staged in LDS (d_model <= 4096)
+// k-steps beyond a wavefront's slice re-read its last one, so the launcher takes the chunk that wastes fewest).
+constexpr int GEMM_PART_STAGE = 256;        // tiles whose partial sums of x^2 are staged in LDS (d_model <= 4096)
 
-// Launched with 4 or 8 wavefronts; threads 0..255 (t = row * 16 + feature) run the epilogue.
-// U: k-steps per chunk (GEMM_UNROLL or GEMM_UNROLL_SHORT; it changes what is in flight, never the
-// order of a row's additions).
-template <typename T, int PRO, int EPI, int U = GEMM_UNROLL>
-static __global__ __launch_bounds__(512) void gemm_kernel(const GemmArgs a) {
-  extern __shared__ float lds[];
-  constexpr int ND = (EPI == EPI_GATED) ? 2 : 1;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, S = blockDim.x >> 6;
-  const int j = lane & 15, kq = lane >> 4;           // B side: row j, k-quarter kq
-  const int KS = a.K >> 5;
-  const int ks0 = min(KS, wave * a.ksteps_per_wave), ks1 = min(KS, ks0 + a.ksteps_per_wave);
-  const int nchunks = (a.ksteps_per_wave + U - 1) / U;          // same for every wave
-  const int ntiles = a.N >> 4;
-  const int my_tiles = (ntiles - (int)blockIdx.x + (int)gridDim.x - 1) / (int)gridDim.x;
-  float* part = lds;                                 // [2][S][ND][256], double-buffered per tile
-  float* stat = lds + 2 * S * ND * 256;              // [S][16]
-  float* ybuf = stat + S * 16;                       // [256]
-  const bool row_ok = (j < a.R);
-  const bool epi_thread = tid < 256;
-  const int e_row = (tid >> 4) & 15, e_f = tid & 15;  // epilogue role of this thread
-  const int e_rowc = min(e_row, a.R - 1);             // clamped: loads stay in bounds
+template <int EPI, int S> constexpr size_t gemm_lds_bytes(int pro) {
+  return (size_t)(2 * S * (EPI == EPI_GATED ? 2 : 1) * 256 + (pro == PRO_POST ? GEMM_PART_STAGE * 16 : 0)) * sizeof(float);
+}
 
-  float mu = 0.0f, rstd = 1.0f;
-
+// S wavefronts (4 or 8) split K; threads 0..255 (t = row * 16 + feature) run the epilogue.  U: k-steps per chunk (it
+// changes what is in flight, never the order of a row's additions).  ONE: a wavefront's K-slice is one chunk, so its
+// activations are the same for every tile: fetched (and normalised) once, only weights are loaded per tile.
+//
+// Large launches are bound by the weights' way out of memory, small ones by their chain of dependent steps, a few
+// hundred nanoseconds each.  So everything known at the start is asked for at the start, and no load waits for
+// another's value but the cache page (for a position) and the rotary table; loads are branch-free: a branch, a
+// conversion of a loaded value where it was loaded or a load into a register that some path has not yet
+// waited for makes the compiler wait for everything in flight (two chunks in flight behind such a branch were in
+// truth none); inputs that are absent are read from the weights and dropped; there are no divisions; the partial
+// tiles are read back with all reads in flight; the norms' statistics are taken while the weights arrive.
+// us a launch inside its forward, before -> after:
+//   GPT-like 97M shape, 8 rows: LayerNorm + QKV 7.2 -> 5.5, + FFN-in 7.0 -> 4.7, O 4.8 -> 3.3; FFN-out 6.5 -> 6.5 (48 tiles:
+//   what 48 CUs can pull); its draft (256 wide), 1 row: 5.5 -> 3.7, 4.6 -> 3.5, O 4.8 -> 2.5, FFN-out 4.4 -> 2.9
+//   T5-XXL shape, 6 rows: QKV 19.2 -> 18.1, O 8.3 -> 7.5, gated FFN-in 28.6 -> 26.9, FFN-out 15.5 -> 14.9; its draft
+//   (512 wide), 1 row: QKV 4.5 -> 3.2, gated FFN-in 4.5 -> 3.5, LM head 10.2 -> 7.6
+template <typename T, int PRO, int EPI, int U, int S, bool ONE>
+static __global__ __launch_bounds__(64 * S, 2) void gemm_kernel(const GemmArgs a) {
+  extern __shared__ __align__(16) float lds[];
   typedef typename Mma<T>::Frag Frag;
-  struct Buf { Frag fa[ND][U]; Frag fb[U]; };
-
-  // All loads are unconditional: a branch around a load makes the compiler wait
-  // for every outstanding load before the next multiply, which would undo the
-  // pipelining.  Out-of-range rows / k-steps re-read a valid address and are
-  // replaced by zeros with a select when they are used.
+  constexpr int ND = (EPI == EPI_GATED) ? 2 : 1;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int j = lane & 15, kq = lane >> 4;           // B side: row j, k-quarter kq
+  const int KS = a.K >> 5, kpw = a.ksteps_per_wave;
+  const int ks0 = min(KS, wave * kpw), ks1 = min(KS, ks0 + kpw), ks_last = max(ks1 - 1, 0);
+  const int nchunks = ONE ? 1 : (kpw + U - 1) / U;   // same for every wave
+  const int ntiles = a.N >> 4, grid = (int)gridDim.x, tile_first = (int)blockIdx.x;
+  int my_tiles = a.tiles_per_wg;
+  while (tile_first + (my_tiles - 1) * grid >= ntiles) --my_tiles;             // (uniform; the grid is no larger than the tiles)
+  float* ssb = lds + 2 * S * ND * 256;               // PRO_POST: GEMM_PART_STAGE * 16 floats
   const int jr = min(j, a.R - 1);
-  auto make_b = [&](int ks, bool valid) -> Frag {
-    const int k = ks * 32 + kq * 8;
-    if (PRO != PRO_LN) {
-      return Mma<T>::load(static_cast<const T*>(a.X) + (size_t)jr * a.K + k);
+  const int e_row = (tid >> 4) & 15, e_f = tid & 15;  // epilogue role of this thread (threads 256.. load alike, and drop it)
+  const int e_rowc = min(e_row, a.R - 1);             // clamped: loads stay in bounds
+  const bool epi_wave = S == 4 || wave < 4;
+
+  // ---- the rows' positions, and what the norm needs: the oldest loads ----
+  int e_pos = -1, e_seq = 0, e_orow = 0;
+  if (EPI == EPI_QKV) {
+    e_pos = a.row_pos[e_rowc];
+    e_seq = (a.row_seq != nullptr ? a.row_seq : a.row_pos)[e_rowc];           // (several sequences)
+  }
+  if (EPI == EPI_LOGITS) e_orow = (a.out_row != nullptr ? a.out_row : static_cast<const int*>(a.W))[e_rowc];
+  // PRO_POST: 1 / rms of every row.  The producer left one partial sum of x^2 per 16-feature tile and row
+  // ([n_part][16] floats, written by n_part different workgroups).  Lane l of epilogue wavefront w
+  // fetches the partials l, l + 64, .. of the rows 4 w .. 4 w + 3, 16 bytes each, and lays them out in LDS, where only
+  // that wavefront reads them (no barrier): thread (row, f) then adds the partials f, f + 16, ...
+  // in ascending order and the 16 lanes of the row: the order the batched kernels use too.  (Letting
+  // every epilogue thread load its 16 partials itself, 64 bytes apart, made 256 workgroups send a
+  // thousand requests each to the same 256 cache lines: 1.3 us per launch.)  The loads go out ahead
+  // of the weights, so that the in-order return of loads does not hold the weight stream back.
+  // LDS: partial p of row r sits at ((((r / 4) * 4 + p / 64) * 64) + p % 64) * 4 + r % 4.
+  f32x4 ss_held[4];
+  if (PRO == PRO_POST) {
+    auto fetch = [&](int i) { ss_held[i] = *reinterpret_cast<const f32x4*>(a.ss_in + (unsigned)(min(lane + 64 * i, a.n_part - 1) * 16 + 4 * (wave & 3))); };
+    fetch(0);
+    if (a.n_part > 64) { fetch(1); fetch(2); fetch(3); }
+    else { ss_held[1] = ss_held[2] = ss_held[3] = f32x4{0.f, 0.f, 0.f, 0.f}; }
+  }
+  float4 ln_held[LN_HELD];
+  if (PRO == PRO_LN) ln_load(ln_held, a.ss_in, j, kq, KS);
+
+  // ---- loads of k-step ks0 + c U + u: a tile's weights, the activations ----
+  // (k-steps past the slice re-read its last one and are not multiplied)
+  auto load_w = [&](Frag (&w)[ND][U], int tile, int c, int u) {
+    const size_t o = ((size_t)tile * KS + min(ks0 + c * U + u, ks_last)) * 64;
+    w[0][u] = Mma<T>::load_stream(reinterpret_cast<const T*>(reinterpret_cast<const Frag*>(a.W) + o + (unsigned)lane));
+    if (ND == 2) w[ND - 1][u] = Mma<T>::load_stream(reinterpret_cast<const T*>(reinterpret_cast<const Frag*>(a.W2) + o + (unsigned)lane));
+  };
+  struct LnIn { float x[8]; Frag g, b; };            // one k-step of a row that is still to be normalised
+  typedef typename std::conditional<PRO == PRO_LN, LnIn, Frag>::type In;
+  const unsigned xoff = (unsigned)(jr * a.K + kq * 8);
+  auto load_x = [&](In& x, int c, int u) {
+    unsigned row = xoff, k8 = (unsigned)(kq * 8);
+    asm volatile("" : "+v"(row), "+v"(k8));          // stay 32-bit offsets of a scalar base: no address registers to wait for
+    const int ks = min(ks0 + c * U + u, ks_last);
+    if constexpr (PRO == PRO_LN) {
+      load8<float>(static_cast<const float*>(a.X) + ks * 32 + row, x.x);
+      x.g = Mma<T>::load(static_cast<const T*>(a.gain) + ks * 32 + k8);
+      x.b = Mma<T>::load(static_cast<const T*>(a.beta) + ks * 32 + k8);
     } else {
-      float v[8], g[8], bb[8];
-      load8<float>(static_cast<const float*>(a.X) + (size_t)jr * a.K + k, v);
-      load8<T>(static_cast<const T*>(a.gain) + k, g);
-      load8<T>(static_cast<const T*>(a.beta) + k, bb);
+      x = Mma<T>::load(static_cast<const T*>(a.X) + ks * 32 + row);
+    }
+  };
+  float mu = 0.0f, rstd = 1.0f;
+  // one k-step as the product's operand (rows past the last one give results that nobody stores)
+  auto operand = [&](const In& x) -> Frag {
+    if constexpr (PRO == PRO_LN) {
+      float g[8], bb[8], v[8];
+      frag_to_floats<T>(x.g, g); frag_to_floats<T>(x.b, bb);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] = ln_apply(v[e], mu, rstd, g[e], bb[e]);
-      return Mma<T>::select(valid && row_ok, Mma<T>::from_floats(v));
+      for (int e = 0; e < 8; ++e) v[e] = ln_apply(x.x[e], mu, rstd, g[e], bb[e]);
+      return Mma<T>::from_floats(v);
+    } else {
+      return x;
     }
   };
 
-  // chunk g of this workgroup's work list: tile blockIdx.x + (g / nchunks) * gridDim.x,
-  // k-steps ks0 + (g % nchunks) * U ... of this wave's K-slice
-  const int ks_last = max(ks1 - 1, 0);
-  // (WHAT: 1 = the weights, 2 = the activations, 3 = both, interleaved per k-step)
-  auto load_chunk_part = [&](Buf& b, int g, auto what) {
-    constexpr int WHAT = decltype(what)::value;
-    const int ti = g / nchunks, c = g - ti * nchunks;
-    const size_t tile = (size_t)blockIdx.x + (size_t)ti * gridDim.x;
-    const T* w0 = static_cast<const T*>(a.W) + (tile * KS) * 512 + lane * 8;
-    const T* w1 = (ND == 2) ? static_cast<const T*>(a.W2) + (tile * KS) * 512 + lane * 8 : nullptr;
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int ks = ks0 + c * U + u;
-      const int ksc = min(ks, ks_last);
-      if (WHAT & 1) {
-        b.fa[0][u] = Mma<T>::load_stream(w0 + (size_t)ksc * 512);
-        if (ND == 2) b.fa[ND - 1][u] = Mma<T>::load_stream(w1 + (size_t)ksc * 512);
-      }
-      if (WHAT & 2) b.fb[u] = make_b(ksc, ks < ks1);
-    }
-  };
-  auto load_chunk = [&](Buf& b, int g) { load_chunk_part(b, g, std::integral_constant<int, 3>()); };
-
-  const int G = my_tiles * nchunks;
-  Buf b0, b1;
-  // ---- PRO_POST: 1 / rms of every row, once per workgroup.  The producer left one partial sum
-  // of x^2 per 16-feature tile and row ([n_part][16] floats, written by n_part different
-  // workgroups).  Thread t of the four epilogue wavefronts fetches block t with four 16-byte
-  // loads that go straight into LDS (no registers; the whole array crosses the memory system once
-  // per workgroup, 1 KB per wavefront and load); epilogue thread (row, f) then adds the partials
-  // f, f + 16, ... in ascending order and the 16 lanes of the row: the order the batched kernels
-  // use too.  (Letting every epilogue thread load its 16 partials itself, 64 bytes apart, made 256
-  // workgroups send a thousand requests each to the same 256 cache lines: 1.3 us per launch.)
-  // The loads go out ahead of the weights, so that the in-order return of loads does not hold the
-  // weight stream back, and are read under the barrier the first tile's end needs anyway.
-  // LDS layout: load i of wavefront w fills ssb[(4 i + w) * 256 ..] with one 16-byte piece per
-  // lane: partial (p, row) sits at (((row / 4) * 4 + p / 64) * 64 + p % 64) * 4 + row % 4.
-  float rs_row = 1.0f;
-  float* ssb = ybuf + 256;                       // GEMM_PART_STAGE * 16 floats
-  if (PRO == PRO_POST && epi_thread) {
-    const float* blk = a.ss_in + (size_t)min(tid, a.n_part - 1) * 16;
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(blk + 4 * i),
-                                       (__attribute__((address_space(3))) void*)(ssb + (4 * i + wave) * 256), 16, 0, 0);
-  }
-  // A LayerNorm model's rows cannot be normalised before their statistics are known, but the first
-  // chunk's weights depend on nothing: they are asked for first and arrive while the statistics
-  // (two passes over the rows, two barriers) are computed.
-  if (PRO == PRO_LN) {
-    if (G > 0) load_chunk_part(b0, 0, std::integral_constant<int, 1>());
-    // ---- statistics of the fp32 rows, reduced across the workgroup ----
-    if (sizeof(T) == 2 && nchunks == 1) {            // (fp32 fragments are twice the registers: general path)
-      // A wavefront's whole K-slice is one chunk (small d_model): the rows' elements, gains and
-      // offsets are fetched ONCE, with the weights, and both passes of the statistics and the
-      // normalised fragments come out of registers -- the same additions in the same order as
-      // the general path below, without its two further trips to memory.
-      const float* x = static_cast<const float*>(a.X) + (size_t)jr * a.K + kq * 8;
-      float xv[U][8];
-      typename Mma<T>::Frag gv[U], bv[U];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int k = min(ks0 + u, ks_last) * 32;
-        load8<float>(x + k, xv[u]);
-        gv[u] = Mma<T>::load(static_cast<const T*>(a.gain) + k + kq * 8);
-        bv[u] = Mma<T>::load(static_cast<const T*>(a.beta) + k + kq * 8);
-      }
-      float s = 0.0f;
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (ks0 + u < ks1) {
-#pragma unroll
-          for (int e = 0; e < 8; ++e) s += xv[u][e];
-        }
-      s = lane_combine<16>(s, OpSumF()); s = lane_combine<32>(s, OpSumF());
-      if (kq == 0) stat[wave * 16 + j] = s;
-      __syncthreads();
-      float t = 0.0f;
-      for (int w = 0; w < S; ++w) t += stat[w * 16 + j];
-      mu = t / (float)a.K;
-      __syncthreads();
-      float s2 = 0.0f;
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (ks0 + u < ks1) {
-#pragma unroll
-          for (int e = 0; e < 8; ++e) s2 = add_square(s2, xv[u][e] - mu);
-        }
-      s2 = lane_combine<16>(s2, OpSumF()); s2 = lane_combine<32>(s2, OpSumF());
-      if (kq == 0) stat[wave * 16 + j] = s2;
-      __syncthreads();
-      float t2 = 0.0f;
-      for (int w = 0; w < S; ++w) t2 += stat[w * 16 + j];
-      rstd = 1.0f / sqrtf(t2 / (float)a.K + a.eps);
-      if (G > 0) {
-#pragma unroll
-        for (int u = 0; u < U; ++u) {
-          float v[8], g[8], bb[8];
-          frag_to_floats<T>(gv[u], g); frag_to_floats<T>(bv[u], bb);
-#pragma unroll
-          for (int e = 0; e < 8; ++e) v[e] = ln_apply(xv[u][e], mu, rstd, g[e], bb[e]);
-          b0.fb[u] = Mma<T>::select((ks0 + u < ks1) && row_ok, Mma<T>::from_floats(v));
-        }
-      }
-    } else {
-      const float* x = static_cast<const float*>(a.X) + (size_t)min(j, a.R - 1) * a.K + kq * 8;
-      float s = 0.0f;
-#pragma unroll 4
-      for (int ks = ks0; ks < ks1; ++ks) {
-        float v[8]; load8<float>(x + ks * 32, v);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) s += v[e];
-      }
-      s = lane_combine<16>(s, OpSumF()); s = lane_combine<32>(s, OpSumF());
-      if (kq == 0) stat[wave * 16 + j] = s;
-      __syncthreads();
-      float t = 0.0f;
-      for (int w = 0; w < S; ++w) t += stat[w * 16 + j];
-      mu = t / (float)a.K;
-      __syncthreads();
-      float s2 = 0.0f;
-#pragma unroll 4
-      for (int ks = ks0; ks < ks1; ++ks) {
-        float v[8]; load8<float>(x + ks * 32, v);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) s2 = add_square(s2, v[e] - mu);
-      }
-      s2 = lane_combine<16>(s2, OpSumF()); s2 = lane_combine<32>(s2, OpSumF());
-      if (kq == 0) stat[wave * 16 + j] = s2;
-      __syncthreads();
-      float t2 = 0.0f;
-      for (int w = 0; w < S; ++w) t2 += stat[w * 16 + j];
-      rstd = 1.0f / sqrtf(t2 / (float)a.K + a.eps);
-      if (G > 0) load_chunk_part(b0, 0, std::integral_constant<int, 2>());
-    }
-  } else if (G > 0) {
-    load_chunk(b0, 0);
-  }
-  int e_pos = -1;
-  size_t e_kvbase = 0;                            // EPI_QKV: cache offset of this row's page / slot
-  if (EPI == EPI_QKV && epi_thread) {
-    e_pos = (e_row < a.R) ? a.row_pos[e_rowc] : -1;
-    const int pc = max(e_pos, 0);
-    const int pt0 = (a.row_seq != nullptr) ? a.row_seq[e_rowc] * a.pt_stride : 0;
-    const int page = a.page_table[pt0 + pc / a.page_size], slot = pc % a.page_size;
-    e_kvbase = (size_t)page * 2 * a.n_kv_heads * a.page_size * a.d_head + (size_t)slot * a.d_head;
-  }
-
-  // ---- per-tile epilogue inputs, issued before the prefetch of the next chunk ----
-  float pre_res = 0.0f, pre_bias = 0.0f, pre_gain = 0.0f, pre_cos = 1.0f, pre_sin = 0.0f;
-  auto prefetch_epilogue = [&](int ti) {
-    if (!epi_thread) return;
-    const int n = ((int)blockIdx.x + ti * (int)gridDim.x) * 16 + e_f;
-    if (a.bias != nullptr) pre_bias = Store<T>::ld(static_cast<const T*>(a.bias) + n);
-    if (EPI == EPI_RESID) {
-      pre_res = static_cast<const float*>(a.out)[(size_t)e_rowc * a.ldo + n];
-      if (a.xg_out != nullptr) pre_gain = Store<T>::ld(static_cast<const T*>(a.gain_next) + n);
-    }
-    if (EPI == EPI_QKV && a.rope != nullptr) {
-      const int nn = (n < a.nq) ? n : (n < a.nq + a.nkv ? n - a.nq : n - a.nq - a.nkv);
-      const float* cs = a.rope + ((size_t)max(e_pos, 0) * (a.d_head >> 1) + ((nn % a.d_head) >> 1)) * 2;
-      pre_cos = cs[0]; pre_sin = cs[1];
-    }
+  // ---- per-tile epilogue inputs, issued before the prefetch of the next chunk; raw, converted where they are used ----
+  // (only LayerNorm models have biases and, but for the LM head, all products have one; rotary: RMSNorm models)
+  constexpr bool RESID = EPI == EPI_RESID || EPI == EPI_RESID_LN, BIAS = PRO == PRO_LN || EPI == EPI_RESID_LN;
+  const bool has_bias = BIAS && a.bias != nullptr, has_rope = EPI == EPI_QKV && PRO == PRO_POST && a.rope != nullptr;
+  const T* bias_src = static_cast<const T*>(has_bias ? a.bias : a.W);
+  const float* rope_src = has_rope ? a.rope : static_cast<const float*>(a.W);       // (absent: any address that can be read)
+  const int rope_mul = has_rope ? a.d_head : 0;
+  T pre_bias{}, pre_gain{};
+  float pre_res = 0.0f;
+  float2 pre_rope = make_float2(1.0f, 0.0f);
+  const int dh_shift = (EPI == EPI_QKV || (EPI == EPI_STORE && a.hm_rows > 0)) ? __ffs(a.d_head) - 1 : 0, dh_mask = (1 << dh_shift) - 1;
+  // (q, k and v are whole heads: a feature's place within its head does not depend on which of them it is in)
+  auto prefetch_epilogue = [&](int tile) {
+    const int n = tile * 16 + e_f;
+    if (BIAS) pre_bias = bias_src[(unsigned)n];
+    if (RESID) pre_res = static_cast<const float*>(a.out)[(unsigned)(e_rowc * a.ldo + n)];
+    if (EPI == EPI_RESID) pre_gain = static_cast<const T*>(a.gain_next)[(unsigned)n];
+    if (EPI == EPI_QKV && PRO == PRO_POST)
+      pre_rope = *reinterpret_cast<const float2*>(rope_src + (size_t)max(e_pos, 0) * rope_mul + ((n & dh_mask) & ~1));
   };
 
   f32x4 acc[ND];
 #pragma unroll
   for (int d = 0; d < ND; ++d) acc[d] = f32x4{0.f, 0.f, 0.f, 0.f};
+  int e_page = 0;                                    // EPI_QKV: the page of this row's position
+  const int ps_shift = (EPI == EPI_QKV) ? __ffs(a.page_size) - 1 : 0;
+  auto find_page = [&] {
+    if (EPI != EPI_QKV) return;
+    asm volatile("" : "+v"(e_pos), "+v"(e_seq));     // (no earlier: what is computed of a loaded value waits for it)
+    e_page = a.page_table[((a.row_seq != nullptr) ? e_seq * a.pt_stride : 0) + (max(e_pos, 0) >> ps_shift)];
+  };
+  float rs_row = 1.0f;
+  auto row_scale = [&] {                             // PRO_POST, epilogue wavefronts
+    float q = 0.0f;
+    f32x4* put = reinterpret_cast<f32x4*>(ssb) + (wave * 4) * 64 + lane;
+    put[0] = ss_held[0];
+    if (a.n_part > 64) { put[64] = ss_held[1]; put[128] = ss_held[2]; put[192] = ss_held[3]; }
+    const float* mine = ssb + ((e_row >> 2) * 256 + e_f) * 4 + (e_row & 3);
+    auto add = [&](int u) { const float v = mine[(u >> 2) * 256 + (u & 3) * 64]; return (e_f + 16 * u < a.n_part) ? v : 0.0f; };
+    if (a.n_part > 64) {
+      float v[16];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) v[u] = add(u);
+#pragma unroll
+      for (int u = 0; u < 16; ++u) q += v[u];
+      for (int p = e_f + GEMM_PART_STAGE; p < a.n_part; p += 16) q += a.ss_in[p * 16 + e_rowc];
+    } else {
+      float v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = add(u);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) q += v[u];
+    }
+    q = lane_combine<1>(q, OpSumF()); q = lane_combine<2>(q, OpSumF());
+    q = lane_combine<4>(q, OpSumF()); q = lane_combine<8>(q, OpSumF());
+    q = row_first(q);                                // the total the batched kernels use: the first lane's
+    rs_row = 1.0f / sqrtf(q / (float)a.K + a.eps);
+  };
 
   // Adds the K-slices of a finished tile in wave order and applies the epilogue.
-  auto finish_tile = [&](int ti) {
-    const int tile = (int)blockIdx.x + ti * (int)gridDim.x;
-    float* pt = part + (ti & 1) * S * ND * 256;
+  auto finish_tile = [&](int tile, int which) {
     // accumulator layout: lane holds features (lane/16)*4 + r, r = 0..3, of row lane%16
+    float* pt = lds + which * (S * ND * 256);
 #pragma unroll
     for (int d = 0; d < ND; ++d) {
-#pragma unroll
-      for (int r = 0; r < 4; ++r) pt[(wave * ND + d) * 256 + j * 16 + kq * 4 + r] = acc[d][r];
+      *reinterpret_cast<f32x4*>(pt + (wave * ND + d) * 256 + j * 16 + kq * 4) = acc[d];
       acc[d] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
     __syncthreads();
-    if (epi_thread) {
-      const int t = tid, row = e_row, f = e_f, n = tile * 16 + f;
-      if (PRO == PRO_POST && ti == 0) {
-        float q = 0.0f;
+    if (!epi_wave) return;
+    const int row = e_row, f = e_f, n = tile * 16 + f;
+    float y[ND];
+    float pv[ND][S];
 #pragma unroll
-        for (int u = 0; u < GEMM_PART_REGS; ++u) {
-          const int p = e_f + 16 * u;
-          const int pc = min(p, a.n_part - 1);
-          const float v = ssb[((((e_row >> 2) << 2) + (pc >> 6)) * 64 + (pc & 63)) * 4 + (e_row & 3)];
-          q += (p < a.n_part) ? v : 0.0f;
+    for (int d = 0; d < ND; ++d)
+#pragma unroll
+      for (int w = 0; w < S; ++w) pv[d][w] = pt[(w * ND + d) * 256 + tid];
+#pragma unroll
+    for (int d = 0; d < ND; ++d) {
+      y[d] = 0.0f;
+#pragma unroll
+      for (int w = 0; w < S; ++w) y[d] += pv[d][w];
+      if (PRO == PRO_POST) y[d] *= rs_row;
+    }
+    y[0] += (BIAS && has_bias) ? Store<T>::ld(&pre_bias) : 0.0f;
+    if (EPI == EPI_QKV) {
+      float v = y[0];
+      const float other = __builtin_bit_cast(float, dpp_partner<1>(__builtin_bit_cast(unsigned, v)));       // feature f ^ 1 of the same row
+      const bool is_q = n < a.nq, is_k = !is_q && n < a.nq + a.nkv;           // (uniform: heads are whole tiles)
+      const int nn = is_q ? n : (is_k ? n - a.nq : n - a.nq - a.nkv);
+      if (has_rope && (is_q || is_k) && e_pos >= 0) v = rope_rotate(v, other, pre_rope.x, pre_rope.y, (f & 1) != 0);
+      if (row < a.R) {
+        if (is_q) {
+          Store<T>::st(static_cast<T*>(a.q_out) + (unsigned)(row * a.nq + n), v);
+        } else if (e_pos >= 0) {
+          int page = e_page;
+          asm volatile("" : "+v"(page));
+          const int head = nn >> dh_shift, d = nn & dh_mask, slot = e_pos & (a.page_size - 1);
+          const size_t row_of_pool = (((size_t)page * 2 + (is_k ? 0 : 1)) * a.n_kv_heads + head) << ps_shift;
+          Store<T>::st(static_cast<T*>(a.kv_pool) + ((row_of_pool + slot) << dh_shift) + d, v);
         }
-        for (int p = e_f + 16 * GEMM_PART_REGS; p < a.n_part; p += 16) q += a.ss_in[p * 16 + e_rowc];
+      }
+    } else if (RESID) {
+      float xn = 0.0f;
+      if (row < a.R) {
+        xn = pre_res + y[0];
+        static_cast<float*>(a.out)[(unsigned)(row * a.ldo + n)] = xn;
+        if (EPI == EPI_RESID) Store<T>::st(static_cast<T*>(a.xg_out) + (unsigned)(row * a.ldo + n), xn * Store<T>::ld(&pre_gain));
+      }
+      if (EPI == EPI_RESID) {
+        float q = square(xn);
         q = lane_combine<1>(q, OpSumF()); q = lane_combine<2>(q, OpSumF());
         q = lane_combine<4>(q, OpSumF()); q = lane_combine<8>(q, OpSumF());
-        q = row_first(q);                          // the total the batched kernels use: the first lane's
-        rs_row = 1.0f / sqrtf(q / (float)a.K + a.eps);
+        if (f == 0) a.ss_out[tile * 16 + row] = q;
+      } else {
+        const LnTile t = ln_tile(xn);
+        if (f == 0) ln_put(a.ln_out, tile, row, t);
       }
-      float y[ND];
-#pragma unroll
-      for (int d = 0; d < ND; ++d) {
-        float s = 0.0f;
-        for (int w = 0; w < S; ++w) s += pt[(w * ND + d) * 256 + t];
-        y[d] = s;
-      }
-      if (PRO == PRO_POST) {
-#pragma unroll
-        for (int d = 0; d < ND; ++d) y[d] *= rs_row;
-      }
-      y[0] += pre_bias;
-      if (EPI == EPI_QKV) {
-        ybuf[t] = y[0];
-      } else if (EPI == EPI_RESID) {
-        float xn = 0.0f;
-        if (row < a.R) {
-          xn = pre_res + y[0];
-          static_cast<float*>(a.out)[(size_t)row * a.ldo + n] = xn;
-          if (a.xg_out != nullptr) Store<T>::st(static_cast<T*>(a.xg_out) + (size_t)row * a.ldo + n, xn * pre_gain);
-        }
-        if (a.ss_out != nullptr) {
-          float q = square(xn);
-          q = lane_combine<1>(q, OpSumF()); q = lane_combine<2>(q, OpSumF());
-          q = lane_combine<4>(q, OpSumF()); q = lane_combine<8>(q, OpSumF());
-          if (f == 0) a.ss_out[tile * 16 + row] = q;
-        }
-      } else if (row < a.R) {
-        if (EPI == EPI_STORE) {
-          if (a.hm_rows > 0)       // head-major: [head][hm_rows][d_head], this launch's rows start at hm_row0
-            Store<T>::st(static_cast<T*>(a.out) +
-                             ((size_t)(n / a.d_head) * a.hm_rows + a.hm_row0 + row) * a.d_head + n % a.d_head, y[0]);
-          else
-            Store<T>::st(static_cast<T*>(a.out) + (size_t)row * a.ldo + n, y[0]);
-        } else if (EPI == EPI_ACT) {
-          Store<T>::st(static_cast<T*>(a.out) + (size_t)row * a.ldo + n, gelu_tanh(y[0]));
-        } else if (EPI == EPI_GATED) {
-          const float g = (a.act == ACT_GELU) ? gelu_tanh(y[0]) : silu(y[0]);
-          Store<T>::st(static_cast<T*>(a.out) + (size_t)row * a.ldo + n, g * y[ND - 1]);
-        } else if (EPI == EPI_LOGITS) {
-          const int orow = (a.out_row != nullptr) ? a.out_row[row] : row;
-          if (orow >= 0) static_cast<float*>(a.out)[(size_t)orow * a.ldo + n] = a.scale * y[0];
-        }
+    } else if (row < a.R) {
+      if (EPI == EPI_STORE) {
+        if (a.hm_rows > 0)       // head-major: [head][hm_rows][d_head], this launch's rows start at hm_row0
+          Store<T>::st(static_cast<T*>(a.out) + ((((size_t)(n >> dh_shift) * a.hm_rows + a.hm_row0 + row) << dh_shift) + (n & dh_mask)), y[0]);
+        else
+          Store<T>::st(static_cast<T*>(a.out) + (size_t)row * a.ldo + n, y[0]);
+      } else if (EPI == EPI_ACT) {
+        Store<T>::st(static_cast<T*>(a.out) + (unsigned)(row * a.ldo + n), gelu_tanh(y[0]));
+      } else if (EPI == EPI_GATED) {
+        const float g = (a.act == ACT_GELU) ? gelu_tanh(y[0]) : silu(y[0]);
+        Store<T>::st(static_cast<T*>(a.out) + (unsigned)(row * a.ldo + n), g * y[ND - 1]);
+      } else if (EPI == EPI_LOGITS) {
+        int orow = e_orow;
+        asm volatile("" : "+v"(orow));
+        if (a.out_row == nullptr) orow = row;
+        if (orow >= 0) static_cast<float*>(a.out)[(size_t)orow * a.ldo + n] = a.scale * y[0];
       }
     }
-    if (EPI == EPI_QKV) {
-      __syncthreads();
-      if (epi_thread && e_row < a.R) {
-        const int t = tid, n = tile * 16 + e_f;
-        float y = ybuf[t];
-        const bool is_q = n < a.nq, is_k = !is_q && n < a.nq + a.nkv;
-        const int nn = is_q ? n : (is_k ? n - a.nq : n - a.nq - a.nkv);
-        const int head = nn / a.d_head, d = nn % a.d_head;
-        if (a.rope != nullptr && (is_q || is_k) && e_pos >= 0) {
-          const float other = ybuf[t ^ 1];
-          y = rope_rotate(y, other, pre_cos, pre_sin, (d & 1) != 0);
-        }
-        if (is_q) {
-          Store<T>::st(static_cast<T*>(a.q_out) + (size_t)e_row * a.nq + n, y);
-        } else if (e_pos >= 0) {
-          const size_t idx = e_kvbase + ((size_t)(is_k ? 0 : 1) * a.n_kv_heads + head) * a.page_size * a.d_head + d;
-          Store<T>::st(static_cast<T*>(a.kv_pool) + idx, y);
-        }
-      }
-    }
+  };
+  auto statistics = [&] {
+    if (PRO == PRO_LN)
+      ln_row(ln_held, [&](int ks) { return *reinterpret_cast<const float4*>(a.ss_in + (unsigned)((ks * 16 + j) * 4)); }, kq, KS, a.K, a.eps, mu, rstd);
+    if (PRO == PRO_POST && epi_wave) row_scale();
   };
 
-  auto compute_chunk = [&](const Buf& b, int g) {
-    const int ti = g / nchunks, c = g - ti * nchunks;
+  // ---- a ring of U k-steps over the chunks of this workgroup's tiles: a k-step's registers take the same k-step of the
+  // next chunk (possibly of the next tile) right after its multiply, so U - 1 of them are in flight all
+  // the time, also while a finished tile is reduced and written out.  The last chunk is apart: loads behind a
+  // branch would all have to be waited for ----
+  Frag w[ND][U];
+  int c_tile = tile_first, c_c = 0, which = 0;       // the chunk being multiplied
+  auto mma_step = [&](const Frag& x, int u) {
+    if (ks0 + c_c * U + u >= ks1) return;            // (uniform)
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const bool valid = (ks0 + c * U + u < ks1) && row_ok;
-      const Frag fb = (PRO == PRO_LN) ? b.fb[u] : Mma<T>::select(valid, b.fb[u]);
-      acc[0] = Mma<T>::mma(b.fa[0][u], fb, acc[0]);
-      if (ND == 2) acc[ND - 1] = Mma<T>::mma(b.fa[ND - 1][u], fb, acc[ND - 1]);
-    }
-    if (c == nchunks - 1) finish_tile(ti);
+    for (int d = 0; d < ND; ++d) acc[d] = Mma<T>::mma(w[d][u], x, acc[d]);
   };
-  // chunk g closes its tile: fetch what that tile's epilogue reads, before the
-  // loads of chunk g + 1 go out
-  auto before_prefetch = [&](int g) {
-    const int ti = g / nchunks;
-    if (g - ti * nchunks == nchunks - 1) prefetch_epilogue(ti);
-  };
-
-  // ---- software pipeline over the work list: the loads of chunk g+1 (possibly
-  // the first chunk of the next tile) are in flight while chunk g is multiplied
-  // and while a finished tile is reduced and written out ----
-  for (int g = 0; g < G; g += 2) {
-    before_prefetch(g);
-    if (g + 1 < G) load_chunk(b1, g + 1);
-    compute_chunk(b0, g);
-    if (g + 1 < G) {
-      before_prefetch(g + 1);
-      if (g + 2 < G) load_chunk(b0, g + 2);
-      compute_chunk(b1, g + 1);
+  if constexpr (ONE && PRO == PRO_LN) {
+    Frag x[U];
+    constexpr int H = U > 8 ? U / 2 : U;             // (a LayerNorm's inputs are four times the registers)
+#pragma unroll
+    for (int u = 0; u < U; ++u) load_w(w, tile_first, 0, u);
+#pragma unroll
+    for (int h = 0; h < U; h += H) {
+      In xin[H];
+#pragma unroll
+      for (int u = 0; u < H; ++u) load_x(xin[u], 0, h + u);
+      __builtin_amdgcn_sched_barrier(0);             // (the scheduler would wait for a position before it asks for the weights)
+      if (h == 0) { find_page(); prefetch_epilogue(tile_first); statistics(); }
+#pragma unroll
+      for (int u = 0; u < H; ++u) x[h + u] = operand(xin[u]);
     }
+    for (int left = my_tiles - 1; left > 0; --left) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        mma_step(x[u], u);
+        load_w(w, c_tile + grid, 0, u);
+        __builtin_amdgcn_sched_barrier(0);           // (and hold the loads back to the end)
+      }
+      finish_tile(c_tile, which);
+      which ^= 1; c_tile += grid;
+      prefetch_epilogue(c_tile);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) mma_step(x[u], u);
+    finish_tile(c_tile, which);
+  } else {
+    In x[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) { load_w(w, tile_first, 0, u); load_x(x[u], 0, u); }
+    __builtin_amdgcn_sched_barrier(0);
+    find_page();
+    statistics();
+    for (int left = my_tiles * nchunks - 1; left > 0; --left) {
+      const bool closes = ONE || c_c == nchunks - 1;
+      const int l_c = closes ? 0 : c_c + 1, l_tile = closes ? c_tile + grid : c_tile;
+      prefetch_epilogue(c_tile);                     // (every time: cheaper than a branch around loads)
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        mma_step(operand(x[u]), u);
+        load_w(w, l_tile, l_c, u);
+        if (!ONE) load_x(x[u], l_c, u);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if (closes) { finish_tile(c_tile, which); which ^= 1; }
+      c_tile = l_tile; c_c = l_c;
+    }
+    prefetch_epilogue(c_tile);
+#pragma unroll
+    for (int u = 0; u < U; ++u) mma_step(operand(x[u]), u);
+    finish_tile(c_tile, which);
   }
 }
 
@@ -564,7 +600,7 @@ constexpr int GEMM_WIDE_U = 2;
 // LDS of the wide kernel: the partial tiles of every wavefront, stream and slab, the QKV
 // staging rows, and per-row constants.
 __host__ __device__ constexpr size_t gemm_wide_lds_bytes(int S) {
-  return (size_t)(S * 2 * GEMM_WIDE_RT * 256 + 2 * GEMM_WIDE_RT * 256 + S * 16 + GEMM_WIDE_RT * 16 * 4) * sizeof(float);
+  return (size_t)(S * 2 * GEMM_WIDE_RT * 256 + 2 * GEMM_WIDE_RT * 256 + GEMM_WIDE_RT * 16 * 4) * sizeof(float);
 }
 
 // Row-major activations [nrt * 16][K] -> fragment order [K/32][GEMM_WIDE_RT][64][8].
@@ -616,8 +652,7 @@ static __global__ __launch_bounds__(512) void gemm_wide_kernel(const GemmArgs a)
   auto stream_tile = [&](int pair, int st) { return (ND == 2) ? pair : 2 * pair + st; };
   float* part = lds;                                 // [S][2][RT][256]
   float* ybuf = part + S * 2 * RT * 256;             // [2][RT][256]
-  float* stat = ybuf + 2 * RT * 256;                 // [S][16]
-  float* rs_s = stat + S * 16;                       // [RT * 16] 1 / rms of every row (PRO_POST)
+  float* rs_s = ybuf + 2 * RT * 256;                 // [RT * 16] 1 / rms of every row (PRO_POST)
   int* pos_s = reinterpret_cast<int*>(rs_s + RT * 16);          // [RT * 16] position of every row (EPI_QKV)
   unsigned long long* kvb_s = reinterpret_cast<unsigned long long*>(pos_s + RT * 16);   // [RT * 16] cache offset
   const int nrt = a.nrt;
@@ -637,40 +672,16 @@ static __global__ __launch_bounds__(512) void gemm_wide_kernel(const GemmArgs a)
   const int e_row = (tid >> 4) & 15, e_f = tid & 15, e_idx = tid & 255;
   const int es_step = (int)blockDim.x >> 8, es0 = tid >> 8;          // 1 or 2; 0 or 1
 
-  // ---- PRO_LN: statistics of the fp32 rows, slab by slab ----
+  // ---- PRO_LN: statistics of the rows, slab by slab ----
   float mu[RT], rstd[RT];
 #pragma unroll
-  for (int rt = 0; rt < RT; ++rt) { mu[rt] = 0.0f; rstd[rt] = 1.0f; }
-  if (PRO == PRO_LN) {
-#pragma unroll
-    for (int rt = 0; rt < RT; ++rt) {
-      const float* x = static_cast<const float*>(a.X) + (size_t)jr[rt] * a.K + kq * 8;
-      float s1 = 0.0f;
-      for (int ks = ks0; ks < ks1; ++ks) {
-        float v[8]; load8<float>(x + ks * 32, v);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) s1 += v[e];
-      }
-      s1 = lane_combine<16>(s1, OpSumF()); s1 = lane_combine<32>(s1, OpSumF());
-      __syncthreads();
-      if (kq == 0) stat[wave * 16 + j] = s1;
-      __syncthreads();
-      float t = 0.0f;
-      for (int w = 0; w < S; ++w) t += stat[w * 16 + j];
-      mu[rt] = t / (float)a.K;
-      float s2 = 0.0f;
-      for (int ks = ks0; ks < ks1; ++ks) {
-        float v[8]; load8<float>(x + ks * 32, v);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) s2 = add_square(s2, v[e] - mu[rt]);
-      }
-      s2 = lane_combine<16>(s2, OpSumF()); s2 = lane_combine<32>(s2, OpSumF());
-      __syncthreads();
-      if (kq == 0) stat[wave * 16 + j] = s2;
-      __syncthreads();
-      float t2 = 0.0f;
-      for (int w = 0; w < S; ++w) t2 += stat[w * 16 + j];
-      rstd[rt] = 1.0f / sqrtf(t2 / (float)a.K + a.eps);
+  for (int rt = 0; rt < RT; ++rt) {
+    mu[rt] = 0.0f; rstd[rt] = 1.0f;
+    if (PRO == PRO_LN) {
+      const float* st = a.ss_in + (size_t)min(rt, nrt - 1) * a.ss_stride;
+      float4 held[LN_HELD];
+      ln_load(held, st, j, kq, KS);
+      ln_row(held, [&](int ks) { return *reinterpret_cast<const float4*>(st + (ks * 16 + j) * 4); }, kq, KS, a.K, a.eps, mu[rt], rstd[rt]);
     }
   }
 
@@ -800,6 +811,10 @@ static __global__ __launch_bounds__(512) void gemm_wide_kernel(const GemmArgs a)
               q = lane_combine<1>(q, OpSumF()); q = lane_combine<2>(q, OpSumF());
               q = lane_combine<4>(q, OpSumF()); q = lane_combine<8>(q, OpSumF());
               if (f == 0) a.ss_out[(size_t)rt * a.ss_stride + tile * 16 + e_row] = q;
+            }
+            if (a.ln_out != nullptr) {
+              const LnTile t = ln_tile(xn);
+              if (f == 0) ln_put(a.ln_out + (size_t)rt * a.ss_stride, tile, e_row, t);
             }
           } else if (ok) {
             if (EPI == EPI_STORE) {
@@ -1048,6 +1063,10 @@ static __global__ __launch_bounds__(256) void gemm_split_finish_kernel(const Gem
       q = lane_combine<1>(q, OpSumF()); q = lane_combine<2>(q, OpSumF());
       q = lane_combine<4>(q, OpSumF()); q = lane_combine<8>(q, OpSumF());
       if (f == 0) a.ss_out[(size_t)rt * a.ss_stride + tile * 16 + e_row] = q;
+    }
+    if (a.ln_out != nullptr) {
+      const LnTile t = ln_tile(xn);
+      if (f == 0) ln_put(a.ln_out + (size_t)rt * a.ss_stride, tile, e_row, t);
     }
   } else if (ok) {
     if (EPI == EPI_STORE) {

@@ -777,6 +777,23 @@ def test_fp32_long_context_with_the_most_rows_per_kv_head():
     dec.close()
 
 
+@pytest.mark.parametrize("arch", [T.GPT, T.GQA])
+def test_fp32_products_over_several_chunks_of_k(arch):
+    """fp32 models whose K-slices take several chunks of four k-steps: 5 (the last chunk of one), 8 and, with eight
+    wavefronts, 9 k-steps; one sequence and two in one slab, against the oracle."""
+    cfg = synth.model_cfg(arch, 2, 576, 16, 2080, 512, 64, d_head=64, dtype="f32", logit_scale=4.0, **(dict(n_kv_heads=8) if arch == T.GQA else {}))
+    w = synth.random_weights(cfg, 9, w_std=0.05)
+    cfg_q, w_q = synth.truncated_noisy_copy(cfg, w, 1, 59, 0.02)
+    sp, sq = oracle_models(cfg, w, cfg_q, w_q)
+    dec = make_decoder(cfg, w, cfg_q, w_q, max_gamma=3, flags=1)
+    prompt = synth.random_tokens(74, 11, cfg["vocab"])
+    dec.prefill(prompt)
+    _, tol, worst, _ = run_pair(dec, sp, sq, prompt, 8, 3, 1.0, 44, "f32", False)
+    print(f"fp32, several chunks: worst logit error {worst}, tolerated {tol}")
+    assert tol["accept"] + tol["draw"] <= 1
+    dec.close()
+
+
 def test_single_row_prefill_does_not_clear_the_other_rows_stale_draft_caches():
     """After a plain decoding step Mq's cache lags behind for every sequence; resetting and
     prefilling one of them must not make sd_step acceptable again: the others are still stale."""

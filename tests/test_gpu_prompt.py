@@ -89,6 +89,26 @@ def prefill_equals_token_by_token(case, scatter):
     assert (n1, t1) == (n2, t2)
 
 
+# Every chunk length and loop of the one-slab product (k-steps of 32 a wavefront; four wavefronts below K 2048, else
+# eight), with k-steps past a slice's end: K of d_model, of heads x 64 and of d_ff; several tiles a workgroup in the
+# LM head and, where d_ff is large, in FFN-in.
+SLICES = {
+    "gpt-2-3-5": (T.GPT, 160, 3, 3, 64, 544, 2, 18, 0),                      # a slice without k-steps; 3 and 5 of them
+    "gpt-9-8-12": (T.GPT, 1056, 16, 16, 64, 1536, 2, 18, 0),                 # LayerNorm rows in two halves
+    "gpt-15-9-17": (T.GPT, 1888, 33, 33, 64, 4128, 2, 18, 0),                # LayerNorm over chunks; eight wavefronts
+    "gpt-13-16-20": (T.GPT, 3104, 64, 64, 64, 5120, 2, 18, 0),
+    "gqa-16-11-24": (T.GQA, 1984, 22, 11, 64, 6112, 2, 18, 0),
+    "gqa-13-16-40": (T.GQA, 3104, 32, 8, 128, 10240, 2, 18, 0),
+    "gqa-18-24-8": (T.GQA, 4576, 48, 12, 128, 2016, 2, 18, 0),               # RMSNorm of more partial sums than are staged
+    "t5-6-7-14": (T.T5DEC, 736, 13, 13, 64, 1760, 2, 18, 20),
+}
+
+
+@pytest.mark.parametrize("name", list(SLICES))
+def test_k_slices_of_every_length_equal_the_products_over_many_rows(name):
+    prefill_equals_token_by_token(SLICES[name], False)
+
+
 # (arch, d_model, heads, kv heads, d_head, d_ff, vocab, sequences, gamma, temperature): rows = sequences x (gamma + 1)
 BATCHES = {
     # LayerNorm rows: two slabs and a ragged one, the smallest products
