@@ -45,6 +45,17 @@ struct StepParams {
   int32_t pad;
 };
 
+// Eight bytes that another workgroup of the same launch reads: written through to memory, read past the caches (their
+// order is made by a wait for the stores and a ticket).
+__device__ __forceinline__ void post8(float* p, float a, float b) {
+  const unsigned long long v = (unsigned long long)__float_as_uint(a) | ((unsigned long long)__float_as_uint(b) << 32);
+  __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ float2 collect8(const float* p) {
+  const unsigned long long v = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return make_float2(__uint_as_float((unsigned)v), __uint_as_float((unsigned)(v >> 32)));
+}
+
 // Element (row, k) of the activations of a product over many rows, which lie in MFMA fragment order
 // [row / 16][K / 32][64 lanes][8]; KS = K / 32.
 __device__ __forceinline__ size_t rows_frag_index(int row, int k, int KS) {

@@ -33,6 +33,7 @@ namespace sd {
 
 
 constexpr int ATTN_LDS_DIST = 4096;        // causal distances whose bias bucket is cached in LDS
+constexpr int ATTN_MAX_RANGES = 16;        // key ranges of a long context
 constexpr int ATTN_MAX_RG = 32;            // query rows x heads per kv head: two 16-row MFMA tiles; 150 KB of LDS in attn_kernel at d_head 64
 
 // LPK lanes per key and DP head-dim elements per lane in the score phase (a workgroup of THREADS
@@ -63,11 +64,15 @@ struct AttnArgs {
   // long contexts: the keys of a (sequence, kv head) are cut into nsplit ranges of split_keys keys
   // (a multiple of the key block) that different workgroups take (grid.y = row groups x nsplit);
   // each leaves its running maximum, denominator and unnormalised output in `partial`
-  // ([sequence][row group][kv head][split][ATTN_MAX_RG][d_head + 2] floats) and attn_merge_kernel combines
-  // them.  nsplit is fixed per model (from max_len), so the split never depends on the other rows.
+  // ([sequence][row group][kv head][split][ATTN_MAX_RG][d_head + 2] floats); attn_mma_kernel combines them itself,
+  // attn_merge_kernel does it for attn_kernel.  nsplit is fixed per model (from max_len), so the split never depends on the other rows.
   int nsplit, split_keys;
   float* partial;
-  // when set, the output (attn_merge_kernel's with key ranges, else attn_mma_kernel's) goes here in
+  // attn_mma_kernel: a ticket per (sequence, kv head), zero between launches, ticket_stride words from one sequence's
+  // to the next's (MANY: one workgroup takes the ranges in turn).  ml_off: where in dynamic LDS (in floats) the ranges' (m, l) go
+  unsigned* tickets;
+  int ticket_stride, ml_off;
+  // when set, the output goes here in
   // fragment order instead of row-major into `out`: element (row, n) at fragment
   // (n / 32) * frag_ks + (row / 16) * frag_slab, lane (row % 16) + 16 ((n % 32) / 8), element n % 8
   // (batched GEMMs: [H * d_head / 32][GEMM_WIDE_RT][64][8]; products over many rows: [slab][H * d_head / 32][64][8])
@@ -353,15 +358,20 @@ static __global__ __launch_bounds__(THREADS) void attn_kernel(const AttnArgs a) 
 //                 (ds_read_b64_tr_b16: two per 16-feature tile instead of eight 2-byte reads);
 //                 B = the probabilities the lane
 //                 already holds, each as the sum of two bf16 numbers (two MFMAs).
-// The wavefronts' results are merged through LDS, in wavefront order; a launch without key ranges
-// (nsplit == 1) normalises and writes the output rows, one with key ranges leaves (m, l, O) in
-// `partial` for attn_merge_kernel exactly as attn_kernel does.  Every row's arithmetic is
-// independent of the other rows.  MODE: causal self-attention over the paged cache, the same with
+// The wavefronts' results are merged through LDS, in wavefront order.  Long contexts are cut into key ranges
+// (nsplit > 1) whose results are merged in range order, always the same ranges, whoever computes them: in decoding a
+// workgroup each, the last of a (sequence, kv head) to arrive merging (`tickets`; a context within the first range is
+// written directly); for a prompt's row groups, which are many, one workgroup after the other.  A merge launch of its own
+// cost 4.3 - 6.4 us a layer, 58 for 2000 prompt rows.
+// Every row's arithmetic is independent of the other rows.  MODE: causal self-attention over the paged cache, the same with
 // the relative-position bias, or cross-attention (the fixed encoder keys, no mask, no bias).
 // The bias of (head, key - position) comes from a table the host lays out by distance
 // (bias_by_key: [head][max_len + 3], entry max_len - 1 - distance, zero-padded), so the four
 // consecutive keys a lane scores per 16-key tile are one 16-byte read, asked for with the step's
 // K and V rows: no tables in LDS, no barrier before the loop.
+// us per layer, before -> after merging in the launch, with no load behind a branch, and with three workgroups a CU:
+// 16 sequences of 2048 keys, 4 rows of 4 heads per KV head 43.9 -> 38.0, a draft's one row of one head 30.2 -> 26.9
+// (134 MB: 5 TB/s); one sequence of 500 keys, one row 10.9 -> 8.6; 2000 prompt rows, 32 heads 262 -> 157.
 // Memory latency: the rows' positions, the first step's page entries and the queries leave
 // together; the K and V rows follow as soon as the positions (hence the context length) are
 // known; page entries of later steps are asked for a step ahead.  No page table in LDS.
@@ -369,8 +379,9 @@ static __global__ __launch_bounds__(THREADS) void attn_kernel(const AttnArgs a) 
 // the first step's rows before the context length is known - clamped to the cache's extent, rows
 // past the context zeroed on their way through LDS - was tried: 0.3 us faster at 120 keys, 0.3 us
 // slower at 60, where two of four wavefronts then pull never-written rows from cold memory.)
-// grid = (kv heads, sequences, row groups or key ranges).
-// dynamic LDS: max(NW x 32 x (d_head + 8) bf16 staging, NW x RG x (d_head + 2) floats for the merge).
+// grid = (kv heads, sequences, row groups, or key ranges with tickets).
+// dynamic LDS: max(NW x 32 x (d_head + 8) bf16 staging, NW x RG x (d_head + 4) floats for the merge), then a pair of
+// floats per key range and row, and a flag.
 __device__ __forceinline__ bf16x8 ld_frag(const bf16* p) { return *reinterpret_cast<const bf16x8*>(p); }
 __device__ __forceinline__ bf16x8 zero_frag() {
   typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
@@ -383,9 +394,10 @@ __device__ __forceinline__ f32x4 mma_bf16(const bf16x8& a, const bf16x8& b, f32x
 }
 constexpr float ATTN_MMA_SLACK = 6.0f;       // how far scores may outgrow the softmax reference point before it moves
 constexpr size_t attn_mma_lds_bytes(int rg, int dh, int nw) {
-  const size_t stage = (size_t)nw * 32 * (dh + 8) * 2, merge = (size_t)nw * rg * (dh + 2) * 4;
+  const size_t stage = (size_t)nw * 32 * (dh + 8) * 2, merge = (size_t)nw * rg * (dh + 4) * 4;
   return stage > merge ? stage : merge;
 }
+constexpr size_t attn_mma_range_lds_bytes(int nsplit) { return nsplit > 1 ? (size_t)nsplit * ATTN_MAX_RG * 8 + 16 : 0; }
 
 constexpr int ATTN_SELF = 0, ATTN_SELF_BIAS = 1, ATTN_CROSS = 2, ATTN_CROSS_PROJ = 3;
 // ATTN_CROSS_PROJ (d_head 64, one row tile, one query head per kv head, K <= 512): cross-attention of a
@@ -402,14 +414,16 @@ constexpr size_t attn_mma_proj_lds_bytes(int rg, int nw) {
 }
 typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));   // four floats at any 4-byte boundary
 
-// MANY: a prompt's row groups, output in fragment order.  Apart from the decoding of up to 16 rows, which would pay
+// ROWS: the rows of a decoding forward (key ranges by workgroups of their own), or row groups of many rows, output in
+// fragment order, without key ranges / with key ranges one after the other.  Apart from the decoding of up to 16 rows, which would pay
 // for the choice (T5-XXL shape, 6 rows: cross-attention 5.27 -> 5.10 us, self-attention 3.72 -> 3.61).
-template <int DH, int NRT, int NW, int MODE, bool MANY>
-// (four wavefronts: capped at 128 registers so that two workgroups share a CU, which the long
-// contexts' key ranges need: one workgroup per CU took two rounds there)
-static __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_mma_kernel(const AttnArgs a) {
-  extern __shared__ float lds[];
-  constexpr bool PROJ = MODE == ATTN_CROSS_PROJ;
+enum { ATTN_FEW, ATTN_MANY, ATTN_MANY_RANGES };
+template <int DH, int NRT, int NW, int MODE, int ROWS>
+// (four wavefronts and one row tile: registers for three workgroups a CU, which the key ranges of a batch need: 512 full
+// ranges and the short last ones of 128 (sequence, kv head) pairs in one round)
+static __global__ __launch_bounds__(64 * NW, NW == 4 ? ((NRT == 1 && (DH == 64 || (MODE == ATTN_SELF && ROWS == ATTN_FEW))) ? 3 : 2) : 1) void attn_mma_kernel(const AttnArgs a) {
+  extern __shared__ __align__(16) float lds[];
+  constexpr bool PROJ = MODE == ATTN_CROSS_PROJ, MANY = ROWS != ATTN_FEW;
   constexpr bool CROSS = MODE == ATTN_CROSS || PROJ, BIAS = MODE == ATTN_SELF_BIAS, TABLE = !CROSS;   // TABLE: paged keys
   constexpr int KSQ = DH / 32;                     // k-steps of the score product
   constexpr int DT = DH / 16;                      // 16-feature tiles of the output
@@ -418,10 +432,11 @@ static __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_mma_kern
   const int j = lane & 15, kq = lane >> 4;
   const int hkv = blockIdx.x;
   const int seq = blockIdx.y;
-  // z: the key ranges of a launch that has them, else the row groups; MANY: key ranges x row groups, the last rows
-  // (which see the most keys) first
-  int split = (a.nsplit > 1) ? (int)blockIdx.z : 0, grp = (a.nsplit > 1) ? 0 : (int)blockIdx.z;
-  if (MANY) { split = (int)blockIdx.z / a.groups; grp = a.groups - 1 - (int)blockIdx.z % a.groups; }
+  constexpr bool in_turn = ROWS == ATTN_MANY_RANGES;          // one workgroup takes the key ranges
+  const bool ranges = TABLE && (in_turn || (!MANY && a.nsplit > 1));
+  // z: the key ranges of a launch that spreads them, else the row groups; MANY: the last rows (which see the most keys) first
+  const int split = (ranges && !in_turn) ? (int)blockIdx.z : 0;
+  const int grp = MANY ? a.groups - 1 - (int)blockIdx.z : (ranges ? 0 : (int)blockIdx.z);
   const int rs = grp * a.rows_per_wg;
   const int R = min(a.rows_per_wg, a.R - rs);
   const int r0 = seq * a.R + rs;
@@ -433,8 +448,9 @@ static __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_mma_kern
   const int kb0 = k_begin + wave * 32;
 
   // ---- positions, the first step's page entries, the queries: one round of loads ----
+  // (no load behind a branch: the compiler would wait for it there)
   int my_pos = -1;                                  // lane r: the causal limit of row r
-  if (!CROSS && lane < R) my_pos = a.row_pos[r0 + lane];
+  if (!CROSS) my_pos = a.row_pos[r0 + min(lane, R - 1)];
   int pg[2] = {0, 0};                               // TABLE: pages of keys kb .. kb + 15 and kb + 16 .. kb + 31 of the step to load
   auto ask_pages = [&](int kb, int (&out)[2]) {
     if (!TABLE) return;
@@ -473,17 +489,19 @@ static __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_mma_kern
   const float* brow[NRT];                           // BIAS: this lane's head in bias_by_key
 #pragma unroll
   for (int rt = 0; rt < NRT; ++rt) {
-    const int rg = rt * 16 + j;
-    const bool ok = rg < RG;
-    const int rgc = ok ? rg : 0;
+    const int rgc = (rt * 16 + j < RG) ? rt * 16 + j : 0;
     const int rr = (rgc * a.g_mul) >> 16;           // rgc / G
     gq[rt] = rgc - rr * G;
-    pos[rt] = ok ? (CROSS ? 0x7fffffff : a.row_pos[r0 + rr]) : -1;
+    pos[rt] = CROSS ? 0x7fffffff : a.row_pos[r0 + rr];
     brow[rt] = BIAS ? a.bias_by_key + (size_t)(hkv * G + gq[rt]) * (a.bias_off + 4) : nullptr;
     const bf16* qp = static_cast<const bf16*>(a.q) + (size_t)(r0 + rr) * a.H * DH + (size_t)(hkv * G + gq[rt]) * DH + kq * 8;
 #pragma unroll
-    for (int s = 0; s < KSQ; ++s) qf[rt][s] = (ok && !PROJ) ? ld_frag(qp + s * 32) : zero_frag();
+    for (int s = 0; s < KSQ; ++s) qf[rt][s] = PROJ ? zero_frag() : ld_frag(qp + s * 32);     // (columns past the last row repeat row 0; nobody reads them)
   }
+  __builtin_amdgcn_sched_barrier(0);                // (all of these leave before any is waited for)
+#pragma unroll
+  for (int rt = 0; rt < NRT; ++rt) pos[rt] = (rt * 16 + j < RG) ? pos[rt] : -1;
+  if (!CROSS) my_pos = (lane < R) ? my_pos : -1;
   auto row_ptr = [&](int key, int page, int which) -> const bf16* {   // which: 0 = K, 1 = V
     if (CROSS) return static_cast<const bf16*>(which ? a.cv : a.ck) + ((size_t)hkv * a.kv_len + key) * DH;
     return static_cast<const bf16*>(a.kv_pool) + ((((size_t)page * 2 + which) * a.Hkv + hkv) * a.page_size + (key & page_mask)) * DH;
@@ -495,18 +513,18 @@ static __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_mma_kern
   bf16x8 vr[DH / 16];
   constexpr int VKPL = 64 / (DH / 8);               // keys one V load of the wavefront covers
   const int vpiece = lane % (DH / 8), vkey = lane / (DH / 8);
-  int kv_len = a.kv_len;
-  int pg_last = 0;                                  // TABLE: page of the last key, what loads past the range re-read
+  int kv_len = a.kv_len;                            // the keys of this workgroup end here
+  int pg_cur = 0;                                   // TABLE: page of the first key of the step that was loaded last
   // TABLE: a step's 32 keys start at a multiple of 32 and pages hold a multiple of 16 keys, so keys
   // 0..15 of the step are consecutive slots of one page and keys 16..31 of one page: two page
-  // entries per step.  (Past the range kb is clamped and every lane re-reads the last key itself.)
+  // entries per step.  (Past the range every lane re-reads the first key of the wavefront's last step; a step
+  // of at most 16 keys does not look at its second half.)
   auto halves = [&](int kb, int which, const bf16* (&half)[2], int& nk) {
     const bool in = kb < kv_len;
-    const int kc = in ? kb : max(kv_len - 1, 0);
-    nk = max(min(32, kv_len - kc), 1);
-    const bool in1 = kb + 16 < kv_len;
-    half[0] = row_ptr(kc, in ? pg[0] : pg_last, which);
-    half[1] = row_ptr(in1 ? kb + 16 : max(kv_len - 1, 0), in1 ? pg[1] : pg_last, which);
+    const int kc = in ? kb : kb - NW * 32;
+    nk = in ? min(32, kv_len - kb) : 1;
+    half[0] = row_ptr(kc, in ? pg[0] : pg_cur, which);
+    half[1] = row_ptr(kc + 16, in ? pg[1] : pg_cur, which);
   };
   auto load_k = [&](int kb) {
     const bf16* half[2] = {nullptr, nullptr}; int nk = 0;
@@ -539,18 +557,19 @@ static __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_mma_kern
   };
   int pos_min = 0x7fffffff;                         // a step whose keys all lie at or below it needs no mask
   if (!CROSS) {
-    kv_len = wave_max(my_pos) + 1;
-    pos_min = wave_min(lane < R ? my_pos : 0x7fffffff);
+    kv_len = __builtin_amdgcn_readfirstlane(wave_max(my_pos)) + 1;
+    pos_min = __builtin_amdgcn_readfirstlane(wave_min(lane < R ? my_pos : 0x7fffffff));
   }
-  float* pp = a.partial + (((((size_t)seq * (MANY ? a.groups : 1) + (MANY ? grp : 0)) * a.Hkv + hkv) * a.nsplit + split) * ATTN_MAX_RG) * (DH + 2);
-  if (a.nsplit > 1) {
-    if (k_begin >= kv_len) {                        // nothing in this key range yet: an empty partial
-      if (tid < RG) { pp[(size_t)tid * (DH + 2) + DH] = -INFINITY; pp[(size_t)tid * (DH + 2) + DH + 1] = 0.0f; }
-      return;
-    }
-    kv_len = min(kv_len, k_begin + a.split_keys);
+  int n_act = 1;                                    // key ranges with keys
+  if (ranges) {
+    while (n_act < a.nsplit && n_act * a.split_keys < kv_len) ++n_act;
+    if (split >= n_act) return;
+    if (!in_turn) kv_len = min(kv_len, k_begin + a.split_keys);
   }
-  if (TABLE) pg_last = page_table[min(max(kv_len - 1, 0) >> page_shift, last_page)];
+  // results of key range s: O as [RG][DH], then (m, l) of every row
+  auto range_of = [&](int s) {
+    return a.partial + (((((size_t)seq * (MANY ? a.groups : 1) + (MANY ? grp : 0)) * a.Hkv + hkv) * a.nsplit + s) * ATTN_MAX_RG) * (DH + 2);
+  };
 
   float m_run[NRT], l_run[NRT];
   f32x4 o[DT][NRT];
@@ -579,6 +598,7 @@ static __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_mma_kern
   };
   if (kb0 < kv_len) { load_k(kb0); load_v(kb0); }   // a wavefront without keys loads nothing
   if (kb0 < kv_len) load_bias(kb0);
+  pg_cur = pg[0];
   ask_pages(kb0 + NW * 32, pg);
   if (PROJ) {
     // ---- the projection itself, while the first keys and values are on their way ----
@@ -630,7 +650,10 @@ static __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_mma_kern
     // everything the rest of the kernel writes)
   }
 
-  for (int kb = kb0; kb < kv_len; kb += NW * 32) {
+  int kb = kb0;
+  for (int s = split;; ++s) {                        // (key ranges: a multiple of NW x 32 keys each)
+  const int kr_end = in_turn ? min(kv_len, (s + 1) * a.split_keys) : kv_len;
+  for (; kb < kr_end; kb += NW * 32) {
     const int nkeys = min(32, kv_len - kb);
     const int kb_next = kb + NW * 32;
     int pgn[2] = {0, 0};
@@ -651,6 +674,7 @@ static __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_mma_kern
         for (int s = 0; s < KSQ; ++s) sc[kt][rt] = mma_bf16(kf[kt][s], qf[rt][s], sc[kt][rt]);
       }
     load_k(kb_next);
+    pg_cur = pg[0];
     pg[0] = pgn[0]; pg[1] = pgn[1];
     f32x4 bias[2][NRT];
 #pragma unroll
@@ -748,9 +772,9 @@ static __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_mma_kern
     }
   }
 
-  // ---- merge the wavefronts: each leaves (m, l, O) of its keys in LDS ----
+  // ---- merge the wavefronts: each leaves (m, l, O) of its keys in LDS, rows of DH + 4 ----
   __syncthreads();                                  // staging region no longer in use
-  float* mg = lds + (size_t)wave * RG * (DH + 2);
+  float* mg = lds + (size_t)wave * RG * (DH + 4);
 #pragma unroll
   for (int rt = 0; rt < NRT; ++rt) {
     float l = lane_combine<16>(l_run[rt], OpSumF());
@@ -758,57 +782,141 @@ static __global__ __launch_bounds__(64 * NW, NW == 4 ? 2 : 1) void attn_mma_kern
     const int rg = rt * 16 + j;
     if (rg < RG) {
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) mg[(size_t)rg * (DH + 2) + dt * 16 + kq * 4 + r] = o[dt][rt][r];
-      if (kq == 0) { mg[(size_t)rg * (DH + 2) + DH] = m_run[rt]; mg[(size_t)rg * (DH + 2) + DH + 1] = l; }
+      for (int dt = 0; dt < DT; ++dt) *reinterpret_cast<f32x4*>(mg + rg * (DH + 4) + dt * 16 + kq * 4) = o[dt][rt];
+      if (kq == 0) *reinterpret_cast<float2*>(mg + rg * (DH + 4) + DH) = make_float2(m_run[rt], l);
     }
   }
   __syncthreads();
-  if (a.nsplit > 1) {
-    for (int i = tid; i < RG * (DH + 2); i += 64 * NW) {
-      const int rg = i / (DH + 2), d = i % (DH + 2);
-      float m = -INFINITY;
+  constexpr int D4 = DH / 4;                        // a thread takes four features of a row at a time
+  float* ml = lds + a.ml_off;                       // [range][ATTN_MAX_RG][2]
+  int* last_wg = reinterpret_cast<int*>(ml + a.nsplit * ATTN_MAX_RG * 2);
+  auto write_row = [&](int rg, int d, const f32x4& acc, float L) {
+    typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+    const int rr = (rg * a.g_mul) >> 16, gg = rg - rr * G;
+    bf16x4 res;
 #pragma unroll
-      for (int w = 0; w < NW; ++w) m = fmaxf(m, lds[((size_t)w * RG + rg) * (DH + 2) + DH]);
-      float out = m;                                   // d == DH: the maximum itself
-      if (d != DH) {
-        out = 0.0f;
+    for (int e = 0; e < 4; ++e) res[e] = (bf16)((L > 0.0f) ? acc[e] / L : 0.0f);
+    bf16* to = ((MANY || ranges) && a.out_frag != nullptr) ? static_cast<bf16*>(a.out_frag) + attn_frag_index(a, r0 + rr, (hkv * G + gg) * DH + d)
+                                                           : static_cast<bf16*>(a.out) + (size_t)(r0 + rr) * a.H * DH + (size_t)(hkv * G + gg) * DH + d;
+    *reinterpret_cast<bf16x4*>(to) = res;
+  };
+  for (int i = tid; i < RG * D4; i += 64 * NW) {
+    const int rg = i / D4, d = (i % D4) * 4;
+    float mw[NW], lw[NW], m = -INFINITY, L = 0.0f;
+    f32x4 ow[NW], acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int w = 0; w < NW; ++w) {                 // wavefronts in order; d == DH + 1 sums the denominators
-          const float mw = lds[((size_t)w * RG + rg) * (DH + 2) + DH];
-          if (mw != -INFINITY) out += lds[((size_t)w * RG + rg) * (DH + 2) + d] * __expf(mw - m);
+    for (int w = 0; w < NW; ++w) {                   // (all reads in flight, none behind a branch)
+      const float* row = lds + (w * RG + rg) * (DH + 4);
+      const float2 x = *reinterpret_cast<const float2*>(row + DH);
+      mw[w] = x.x; lw[w] = x.y; ow[w] = *reinterpret_cast<const f32x4*>(row + d);
+    }
+#pragma unroll
+    for (int w = 0; w < NW; ++w) m = fmaxf(m, mw[w]);
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {                   // wavefronts in order; one without keys left zeros
+      const float e = (mw[w] != -INFINITY) ? __expf(mw[w] - m) : 0.0f;
+      L += lw[w] * e;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) acc[r] += ow[w][r] * e;
+    }
+    if (n_act == 1) write_row(rg, d, acc, L);
+    else if (in_turn) {
+      *reinterpret_cast<f32x4*>(range_of(s) + rg * DH + d) = acc;    // (read back by this thread)
+      if (d == 0) *reinterpret_cast<float2*>(ml + (s * ATTN_MAX_RG + rg) * 2) = make_float2(m, L);
+    } else if (!MANY) {
+      float* to = range_of(s) + rg * DH + d;
+      post8(to, acc[0], acc[1]); post8(to + 2, acc[2], acc[3]);
+      if (d == 0) post8(range_of(s) + ATTN_MAX_RG * DH + rg * 2, m, L);
+    }
+  }
+  if (n_act == 1) return;
+  if constexpr (in_turn) {
+    __syncthreads();                                // (the merge area is the next range's staging region)
+    if (s + 1 < n_act) {
+#pragma unroll
+      for (int rt = 0; rt < NRT; ++rt) {
+        m_run[rt] = -INFINITY; l_run[rt] = 0.0f;
+#pragma unroll
+        for (int dt = 0; dt < DT; ++dt) o[dt][rt] = f32x4{0.f, 0.f, 0.f, 0.f};
+      }
+      continue;
+    }
+  } else {
+    unsigned* ticket = a.tickets + (size_t)(a.seq0 + seq) * a.ticket_stride + hkv;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // this wavefront's posts have reached memory
+    __syncthreads();
+    if (tid == 0) {
+      const unsigned n = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const int last = n == (unsigned)n_act - 1u;
+      *last_wg = last;
+      if (last) __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    if (*last_wg == 0) return;
+  }
+  // ---- merge the key ranges, in order: with m = max m_s, sum_s O_s e^(m_s - m) / sum_s l_s e^(m_s - m) ----
+  // (a thread's features of all its rows and of NB ranges are asked for together, ahead of the ranges' (m, l))
+  constexpr int IT = (NRT * 16 * D4 + 64 * NW - 1) / (64 * NW), NB = IT <= 2 ? 8 : 4;
+  const int n_items = RG * D4;
+  f32x4 ov[NB][IT];
+  auto ask = [&](int x0) {
+#pragma unroll
+    for (int u = 0; u < NB; ++u)
+#pragma unroll
+      for (int k = 0; k < IT; ++k) {
+        const int i = min(tid + k * 64 * NW, n_items - 1);
+        const float* from = range_of(min(x0 + u, n_act - 1)) + i * 4;            // = (i / D4) * DH + (i % D4) * 4
+        if (MANY) ov[u][k] = *reinterpret_cast<const f32x4*>(from);
+        else {
+          const float2 lo = collect8(from), hi = collect8(from + 2);
+          ov[u][k] = f32x4{lo.x, lo.y, hi.x, hi.y};
         }
       }
-      pp[i] = out;
+  };
+  if (!MANY) {
+    for (int i = tid; i < n_act * RG; i += 64 * NW) {
+      const int x = i / RG, rg = i - x * RG;
+      *reinterpret_cast<float2*>(ml + (x * ATTN_MAX_RG + rg) * 2) = collect8(range_of(x) + ATTN_MAX_RG * DH + rg * 2);
     }
-    return;
+    ask(0);
+    __syncthreads();
+  } else {
+    ask(0);
   }
-  bf16* og = static_cast<bf16*>(a.out);
-  for (int i = tid; i < RG * DH; i += 64 * NW) {
-    const int rg = i / DH, d = i % DH;
-    float m = -INFINITY;
+  float m[IT], L[IT];
+  f32x4 acc[IT];
 #pragma unroll
-    for (int w = 0; w < NW; ++w) m = fmaxf(m, lds[((size_t)w * RG + rg) * (DH + 2) + DH]);
-    float L = 0.0f, acc = 0.0f;
+  for (int k = 0; k < IT; ++k) {
+    const int rg = min(tid + k * 64 * NW, n_items - 1) / D4;
+    m[k] = -INFINITY; L[k] = 0.0f; acc[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int x = 0; x < n_act; ++x) m[k] = fmaxf(m[k], ml[(x * ATTN_MAX_RG + rg) * 2]);
+  }
+  for (int x0 = 0; x0 < n_act; x0 += NB) {
+    if (x0 > 0) ask(x0);
 #pragma unroll
-    for (int w = 0; w < NW; ++w) {                     // wavefronts in order
-      const float* row = lds + ((size_t)w * RG + rg) * (DH + 2);
-      const float mw = row[DH];
-      if (mw != -INFINITY) {
-        const float e = __expf(mw - m);
-        L += row[DH + 1] * e;
-        acc += row[d] * e;
+    for (int u = 0; u < NB; ++u) {
+      if (x0 + u >= n_act) break;
+#pragma unroll
+      for (int k = 0; k < IT; ++k) {
+        const int rg = min(tid + k * 64 * NW, n_items - 1) / D4;
+        const float2 x = *reinterpret_cast<const float2*>(ml + ((x0 + u) * ATTN_MAX_RG + rg) * 2);
+        const float w = (x.x != -INFINITY) ? __expf(x.x - m[k]) : 0.0f;        // (a range whose keys this row does not see left zeros)
+        L[k] += x.y * w;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) acc[k][r] += ov[u][k][r] * w;
       }
     }
-    const int rr = (rg * a.g_mul) >> 16, gg = rg - rr * G;
-    const bf16 res = (bf16)((L > 0.0f) ? acc / L : 0.0f);
-    if (MANY && a.out_frag != nullptr) static_cast<bf16*>(a.out_frag)[attn_frag_index(a, r0 + rr, (hkv * G + gg) * DH + d)] = res;
-    else og[(size_t)(r0 + rr) * a.H * DH + (size_t)(hkv * G + gg) * DH + d] = res;
+  }
+#pragma unroll
+  for (int k = 0; k < IT; ++k) {
+    const int i = tid + k * 64 * NW;
+    if (i < n_items) write_row(i / D4, (i % D4) * 4, acc[k], L[k]);
+  }
+  return;
   }
 }
 
-// Combines the partial results of the key ranges of one (sequence, kv head): with
+// Combines the partial results of attn_kernel's key ranges of one (sequence, kv head): with
 // m = max m_s, the output is sum_s acc_s e^(m_s - m) / sum_s l_s e^(m_s - m), ranges taken in
 // order.  grid = (kv heads, rows x query heads of the kv head, sequences), one thread per feature.
 template <typename T, int DH>

@@ -43,8 +43,9 @@ struct RowPart {
 };
 
 // Working memory of one sequence's accept / resample call or draw; the ticket is zero between calls.
+constexpr int SAMPLE_TICKETS = 64;          // the first is the sampling kernels', the others the attention kernel's (one per kv head)
 struct SampleScratch {
-  unsigned int ticket[64];
+  unsigned int ticket[SAMPLE_TICKETS];
   double tot[SAMPLE_MAX_CHUNKS];
 };
 // The same with the statistics of the sequence's rows, for calls on explicit logits.  The layout depends on
@@ -1312,9 +1313,10 @@ inline void launch_argmax(hipStream_t stream, const AcceptArgs& a, int rows) {
   });
 }
 
-static __global__ void clear_tickets_kernel(void* scr, size_t stride, int rows) {
+static __global__ void clear_tickets_kernel(void* scr, size_t stride, int rows, int n) {
   const int b = (int)(blockIdx.x * blockDim.x + threadIdx.x);
-  if (b < rows) reinterpret_cast<SampleScratch*>(static_cast<char*>(scr) + (size_t)b * stride)->ticket[0] = 0u;
+  if (b < rows)
+    for (int i = 0; i < n; ++i) reinterpret_cast<SampleScratch*>(static_cast<char*>(scr) + (size_t)b * stride)->ticket[i] = 0u;
 }
 
 // The launches of one accept / resample call over `rows` sequences.

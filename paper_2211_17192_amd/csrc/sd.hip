@@ -186,7 +186,7 @@ void plan_model(Arena& A, Model& m, const sd_model_cfg& c, int page_size, int ba
   m.logit_row = static_cast<int*>(A.take(rows * sizeof(int)));
   // contexts beyond 1024 positions: key ranges of 512 keys taken by different workgroups
   m.attn_split_keys = 512;
-  m.attn_nsplit = (c.max_len > 1024) ? std::min(16, (c.max_len + m.attn_split_keys - 1) / m.attn_split_keys) : 1;
+  m.attn_nsplit = (c.max_len > 1024) ? std::min(ATTN_MAX_RANGES, (c.max_len + m.attn_split_keys - 1) / m.attn_split_keys) : 1;
   if (m.attn_nsplit > 1) {
     m.attn_split_keys = ((c.max_len + m.attn_nsplit - 1) / m.attn_nsplit + 511) / 512 * 512;
     // (a prompt pass with few workgroups makes its row groups half as large)
@@ -513,21 +513,26 @@ void launch_attn_kernel(hipStream_t s, const AttnArgs& a, dim3 grid, int threads
 // eight 32-key steps (measured at 512 encoder keys: 6.5 us against 6.8 with four and 7.7 with sixteen).
 int attn_mma_waves(int keys) { return (keys + 31) / 32 > 8 ? 8 : 4; }
 template <int DH, int NRT>
-void launch_attn_mma(hipStream_t s, const AttnArgs& a, dim3 grid, int nw, size_t lds) {
+void launch_attn_mma(hipStream_t s, const AttnArgs& a, dim3 grid, int nw, size_t lds, bool in_turn) {
   const int mode = a.cross ? (a.pj_w != nullptr ? ATTN_CROSS_PROJ : ATTN_CROSS) : (a.bias_by_key != nullptr ? ATTN_SELF_BIAS : ATTN_SELF);
   if constexpr (DH == 64 && NRT == 1) {
     if (mode == ATTN_CROSS_PROJ) {
-      if (nw == 4) hipLaunchKernelGGL((attn_mma_kernel<64, 1, 4, ATTN_CROSS_PROJ, false>), grid, dim3(256), lds, s, a);
-      else hipLaunchKernelGGL((attn_mma_kernel<64, 1, 8, ATTN_CROSS_PROJ, false>), grid, dim3(512), lds, s, a);
+      if (nw == 4) hipLaunchKernelGGL((attn_mma_kernel<64, 1, 4, ATTN_CROSS_PROJ, ATTN_FEW>), grid, dim3(256), lds, s, a);
+      else hipLaunchKernelGGL((attn_mma_kernel<64, 1, 8, ATTN_CROSS_PROJ, ATTN_FEW>), grid, dim3(512), lds, s, a);
       return;
     }
   }
-  // more than one slab of rows: row groups x key ranges, or fragments written by the kernel itself
-  const bool many = a.R > MAX_ROWS || (a.out_frag != nullptr && a.nsplit <= 1);
+  // more than one slab of rows: row groups, or fragments written without key ranges
+  const bool many = in_turn || a.R > MAX_ROWS || (a.out_frag != nullptr && a.nsplit <= 1);
 #define SD_MMA(NW_, MODE_)                                                                                              \
   if (nw == NW_ && mode == MODE_) {                                                                                     \
-    if (many) hipLaunchKernelGGL((attn_mma_kernel<DH, NRT, NW_, MODE_, true>), grid, dim3(64 * NW_), lds, s, a);        \
-    else hipLaunchKernelGGL((attn_mma_kernel<DH, NRT, NW_, MODE_, false>), grid, dim3(64 * NW_), lds, s, a);            \
+    if constexpr (NW_ == 4 && MODE_ != ATTN_CROSS)      /* (key ranges: four wavefronts) */                             \
+      if (many && a.nsplit > 1) {                                                                                       \
+        hipLaunchKernelGGL((attn_mma_kernel<DH, NRT, NW_, MODE_, ATTN_MANY_RANGES>), grid, dim3(64 * NW_), lds, s, a);  \
+        return;                                                                                                         \
+      }                                                                                                                 \
+    if (many) hipLaunchKernelGGL((attn_mma_kernel<DH, NRT, NW_, MODE_, ATTN_MANY>), grid, dim3(64 * NW_), lds, s, a);   \
+    else hipLaunchKernelGGL((attn_mma_kernel<DH, NRT, NW_, MODE_, ATTN_FEW>), grid, dim3(64 * NW_), lds, s, a);         \
     return;                                                                                                             \
   }
   SD_MMA(4, ATTN_SELF) SD_MMA(4, ATTN_SELF_BIAS) SD_MMA(4, ATTN_CROSS)
@@ -536,10 +541,11 @@ void launch_attn_mma(hipStream_t s, const AttnArgs& a, dim3 grid, int nw, size_t
 }
 
 template <typename T>
-void launch_attn(hipStream_t s, const Model& m, AttnArgs a, int nseq) {
+void launch_attn(hipStream_t s, const Model& m, AttnArgs a, int nseq, SampleScratch* tickets) {
   const int G = a.H / a.Hkv, DH = m.cfg.d_head;
   const bool prompt = a.R > MAX_ROWS;              // one sequence's prompt rows: groups of full row tiles
   a.G = G; a.g_mul = 65536 / G + 1;
+  a.tickets = tickets->ticket + 1; a.ticket_stride = (int)(sizeof(SampleScratch) / sizeof(unsigned));      // (the first is the draws')
   // few kv heads leave most CUs idle: split the (independent) rows over more workgroups
   if (prompt) {
     a.rows_per_wg = prompt_rows_per_wg(m.cfg);
@@ -563,17 +569,24 @@ void launch_attn(hipStream_t s, const Model& m, AttnArgs a, int nseq) {
     const int RG = a.rows_per_wg * G;
     const int nw = (a.nsplit > 1) ? 4 : attn_mma_waves(a.cross ? a.kv_len : (m.cfg.max_len + 1) / 2);
     if (a.pj_w != nullptr && !(a.cross && DH == 64 && RG <= 16 && G == 1)) a.pj_w = nullptr;   // (callers check; never project elsewhere)
+    // key ranges: a workgroup each, with a ticket per kv head, or one after the other (prompts; more heads than tickets)
+    const bool in_turn = a.nsplit > 1 && (prompt || a.Hkv >= SAMPLE_TICKETS);
     size_t ll = attn_mma_lds_bytes(RG, DH, nw);
+    a.ml_off = (int)(ll / 4);
+    ll += attn_mma_range_lds_bytes(a.nsplit);
     if (a.pj_w != nullptr) {
       ll = attn_mma_proj_lds_bytes(RG, nw);
       a.pj_q_off = (int)((ll - 16 * 64 * 2) / 4);
     }
-    const dim3 lg(grid.x, grid.z, grid.y);          // key ranges in z, the slowest index: the fullest ranges start first
-    if (DH == 64 && RG <= 16) launch_attn_mma<64, 1>(s, a, lg, nw, ll);
-    else if (DH == 64) launch_attn_mma<64, 2>(s, a, lg, nw, ll);
-    else if (RG <= 16) launch_attn_mma<128, 1>(s, a, lg, nw, ll);
-    else launch_attn_mma<128, 2>(s, a, lg, nw, ll);
-  } else if (DH == 32) launch_attn_kernel<T, 32>(s, a, grid, threads, lds);
+    // key ranges in z, the slowest index: the fullest ranges start first
+    const dim3 lg(a.Hkv, nseq, (a.nsplit > 1 && !in_turn) ? a.nsplit : a.groups);
+    if (DH == 64 && RG <= 16) launch_attn_mma<64, 1>(s, a, lg, nw, ll, in_turn);
+    else if (DH == 64) launch_attn_mma<64, 2>(s, a, lg, nw, ll, in_turn);
+    else if (RG <= 16) launch_attn_mma<128, 1>(s, a, lg, nw, ll, in_turn);
+    else launch_attn_mma<128, 2>(s, a, lg, nw, ll, in_turn);
+    return;
+  }
+  if (DH == 32) launch_attn_kernel<T, 32>(s, a, grid, threads, lds);
   else if (DH == 64) launch_attn_kernel<T, 64>(s, a, grid, threads, lds);
   else launch_attn_kernel<T, 128>(s, a, grid, threads, lds);
   if (a.nsplit > 1) {
@@ -607,11 +620,13 @@ hipError_t allow_attn_lds() {
 // The matrix-core kernel with eight wavefronts, 24 query rows and d_head 128 merges through 100 KB of LDS.
 template <int DH, int NRT, int NW, int MODE>
 hipError_t allow_mma_lds() {
-  const size_t bytes = attn_mma_lds_bytes(NRT == 1 ? 16 : ATTN_MAX_RG, DH, NW);
-  static_assert(attn_mma_lds_bytes(ATTN_MAX_RG, 128, 8) <= LDS_PER_CU, "matrix-core attention: LDS budget");
+  const size_t bytes = attn_mma_lds_bytes(NRT == 1 ? 16 : ATTN_MAX_RG, DH, NW) + attn_mma_range_lds_bytes(ATTN_MAX_RANGES);
+  static_assert(attn_mma_lds_bytes(ATTN_MAX_RG, 128, 8) + attn_mma_range_lds_bytes(ATTN_MAX_RANGES) + 16 <= LDS_PER_CU, "matrix-core attention: LDS budget");
   if (bytes <= 64 * 1024) return hipSuccess;
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_mma_kernel<DH, NRT, NW, MODE, false>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_mma_kernel<DH, NRT, NW, MODE, true>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_mma_kernel<DH, NRT, NW, MODE, ATTN_FEW>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_mma_kernel<DH, NRT, NW, MODE, ATTN_MANY>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  if constexpr (NW == 4 && MODE != ATTN_CROSS)
+    if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_mma_kernel<DH, NRT, NW, MODE, ATTN_MANY_RANGES>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
   return e;
 }
 template <int DH, int NRT, int NW>
@@ -785,7 +800,7 @@ void forward(sd_ctx* c, Model& m, const Rows& rw, float* logits) {
         // long contexts end in the merge kernel, which can leave its output in fragment order for
         // the batched O projection (no re-tile)
         if (!cross && m.attn_nsplit > 1 && n_groups > 1 && n_groups <= GEMM_WIDE_RT) { a.out_frag = m.xfrag2; a.frag_ks = GEMM_WIDE_RT; a.frag_slab = 1; produced_frag = true; }
-        launch_attn<T>(s, m, a, rw.nseq);
+        launch_attn<T>(s, m, a, rw.nseq, c->d_scratch);
       }
     };
     if (!(skip & SD_OP_ATTN)) attention(false);
@@ -962,7 +977,7 @@ void forward_rows(sd_ctx* c, Model& m, const Rows& rw, float* logits) {
       a.seq0 = rw.seq0; a.pt_stride = m.n_pages;
       if (cross) { a.cross = 1; a.ck = l.cross_k; a.cv = l.cross_v; a.kv_len = f.enc_len; a.scale = 1.0f; a.bias_by_key = nullptr; }
       a.out_frag = attn; a.frag_ks = 1; a.frag_slab = m.nq / 32;
-      launch_attn<bf16>(s, m, a, rw.nseq);
+      launch_attn<bf16>(s, m, a, rw.nseq, c->d_scratch);
     };
     if (!(skip & SD_OP_ATTN)) attention(false);
     if (!(skip & SD_OP_O)) resid(l.wo, attn, m.nq, l.bo, (f.arch == SD_ARCH_T5DEC) ? l.lncg : l.ln2g);
@@ -1316,7 +1331,7 @@ extern "C" sd_status sd_load_models(sd_ctx** out, const sd_model_cfg* p_cfg, con
   if (st != SD_OK) return bail(st, "Mq: " + err);
   for (const Model* m : {&c->p, &c->q})
     if (m->zeros) hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(256), 0, c->stream, reinterpret_cast<unsigned int*>(m->zeros), 0u, (size_t)256);
-  hipLaunchKernelGGL(clear_tickets_kernel, dim3(1), dim3(SD_MAX_BATCH), 0, c->stream, c->d_scratch, sizeof(SampleScratch), (int)B);
+  hipLaunchKernelGGL(clear_tickets_kernel, dim3(1), dim3(SD_MAX_BATCH), 0, c->stream, c->d_scratch, sizeof(SampleScratch), (int)B, SAMPLE_TICKETS);
   hipError_t e = hipStreamSynchronize(c->stream);
   if (e == hipSuccess) e = hipGetLastError();
   if (e != hipSuccess) return bail(SD_EHIP, std::string("load: ") + hipGetErrorString(e));

@@ -132,6 +132,6 @@ extern "C" sd_status sd_spec_sample_static(const float* p_logits, const float* q
   // the tickets must start at zero whatever an earlier (possibly failed) call left: a small kernel,
   // not a memset, so that the call can be recorded into a graph
   sd::SampleBlock* scr = static_cast<sd::SampleBlock*>(ptr);
-  hipLaunchKernelGGL(sd::clear_tickets_kernel, dim3((unsigned)((rows + 63) / 64)), dim3(64), 0, s_, scr, sizeof(sd::SampleBlock), rows);
+  hipLaunchKernelGGL(sd::clear_tickets_kernel, dim3((unsigned)((rows + 63) / 64)), dim3(64), 0, s_, scr, sizeof(sd::SampleBlock), rows, 1);
   return launch_spec_sample(p_logits, q_logits, x, r, s, rows, gamma, vocab, temperature, o, out_n, out_t, beta, scr, s_);
 }

@@ -109,6 +109,20 @@ def test_k_slices_of_every_length_equal_the_products_over_many_rows(name):
     prefill_equals_token_by_token(SLICES[name], False)
 
 
+# Contexts over several key ranges (512 keys): decoded tokens come from ranges merged by the last workgroup to arrive, or,
+# with more KV heads than there are tickets, taken in turn; a prompt's from ranges taken in turn.
+RANGES = {
+    "gqa-1100-two-row-tiles": (T.GQA, 256, 16, 4, 128, 512, 2, 1100, 0),
+    "gpt-1060-64-heads": (T.GPT, 128, 64, 64, 64, 256, 2, 1060, 0),
+    "t5-1040-bias": (T.T5DEC, 256, 4, 4, 64, 512, 2, 1040, 20),
+}
+
+
+@pytest.mark.parametrize("name", list(RANGES))
+def test_key_ranges_merged_by_ticket_equal_key_ranges_in_turn(name):
+    prefill_equals_token_by_token(RANGES[name], False)
+
+
 # (arch, d_model, heads, kv heads, d_head, d_ff, vocab, sequences, gamma, temperature): rows = sequences x (gamma + 1)
 BATCHES = {
     # LayerNorm rows: two slabs and a ragged one, the smallest products
