@@ -794,6 +794,26 @@ def test_fp32_products_over_several_chunks_of_k(arch):
     dec.close()
 
 
+def test_logits_are_arrays_of_their_own():
+    """Every call gives a new array, whether it lies in pinned memory or, beyond MAX_PINNED live ones, does not; a
+    view keeps its array's memory after the array's name is gone."""
+    cfg_p, w_p, cfg_q, w_q = synth.tiny_pair()
+    dec = make_decoder(cfg_p, w_p, cfg_q, w_q, max_gamma=4, flags=1)
+    dec.prefill(synth.random_tokens(7, 5, cfg_p["vocab"]))
+    U = synth.uniform_stream(5, 20 * 9).reshape(20, 9)
+    views, copies = [], []
+    for it in range(dec.MAX_PINNED + 4):
+        dec.step(4, 1.0, U[it])
+        a = dec.logits(0, 5)
+        assert a.flags.writeable and a.flags.c_contiguous and a.dtype == np.float32 and a.shape == (5, cfg_p["vocab"])
+        views.append(a[1:3]); copies.append(a[1:3].copy())
+        if it % 3 == 0:
+            views[it] = views[it].copy()               # its array may go, and its memory be handed out again
+    assert all(np.array_equal(v, c) for v, c in zip(views, copies))
+    dec.close()
+    assert all(np.array_equal(v, c) for v, c in zip(views, copies))
+
+
 def test_single_row_prefill_does_not_clear_the_other_rows_stale_draft_caches():
     """After a plain decoding step Mq's cache lags behind for every sequence; resetting and
     prefilling one of them must not make sd_step acceptable again: the others are still stale."""
