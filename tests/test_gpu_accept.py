@@ -95,6 +95,37 @@ def test_filter_paths(kind, vocab, top_k, top_p):
     check(zp, zq, x, r, s, 1.0, top_k, top_p)
 
 
+@pytest.mark.parametrize("kind,vocab,top_k,top_p", [
+    ("normal", 32768, 50, 0.0), ("normal", 32000, 50, 0.95), ("normal", 8192, 1, 0.5), ("normal", 4100, 64, 0.999),
+    ("normal", 32768, 110, 0.9),   # two keys a lane
+    ("normal", 32768, 128, 0.0),   # about as many as the list holds: some rows go on, some take the general search
+    ("normal", 512, 100, 0.9), ("normal", 512, 128, 0.3),                        # as many threads with entries as top_k, and fewer than a wavefront of lists
+    ("levels", 8192, 20, 0.8),     # ties with the last kept entry, in and out of the list's room
+    ("two", 16384, 30, 0.6),       # two values only: the bins' ends
+    ("lowest", 16384, 50, 0.9),    # most entries the type's lowest value
+    ("peak", 32768, 50, 0.9),      # one entry far above the others: all maxima but one in the last bin
+])
+def test_filter_on_a_short_list(kind, vocab, top_k, top_p):
+    zp, zq, _, r, s = synth.sampler_case(4, 3, vocab, 1.0, 23)
+    if kind == "levels":
+        zp, zq = np.round(zp * 8) / 8, np.round(zq * 8) / 8
+    elif kind == "two":
+        zp, zq = np.where(zp > 9.0, 4.0, 1.0), np.where(zq > 9.5, 4.0, 1.0)
+    elif kind == "lowest":
+        zp[:, :, 300:], zq[:, :, 300:] = np.finfo(np.float32).min, np.finfo(np.float32).min
+    elif kind == "peak":
+        zp[:, :, 77] += 60.0
+        zq[:, :, 77] += 30.0
+    top_p = float(np.float32(top_p))
+    zp, zq = zp.astype(np.float32), zq.astype(np.float32)
+    if kind == "normal" and 0.0 < top_p:
+        for z in [*zp.reshape(-1, vocab), *zq.reshape(-1, vocab)]:
+            while sampling.nucleus_margin(z, 1.0, top_k, top_p) < 2e-6:          # (see above)
+                z[0] += np.float32(0.01)
+    x = np.argmax(zq, -1).astype(np.int32)
+    check(zp, zq, x, r, s, 1.0, top_k, top_p)
+
+
 def test_calls_of_any_size_share_one_scratch():
     from paper_2211_17192_amd import binding
     scratch = binding.spec_sample_scratch(64, 7)
