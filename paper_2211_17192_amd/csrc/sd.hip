@@ -802,7 +802,7 @@ void forward(sd_ctx* c, Model& m, const Rows& rw, float* logits) {
         if (cross && fuse_cross_q && !(skip & SD_OP_CROSS_Q)) {
           a.pj_w = l.cq; a.pj_x = q.xg; a.pj_ss = q.ss; a.pj_K = d; a.pj_npart = n_part; a.pj_eps = f.norm_eps;
         }
-        // long contexts end in the merge kernel, which can leave its output in fragment order for
+        // long contexts end in a merge of their key ranges, which can leave its output in fragment order for
         // the batched O projection (no re-tile)
         if (!cross && m.attn_nsplit > 1 && n_groups > 1 && n_groups <= GEMM_WIDE_RT) { a.out_frag = m.xfrag2; a.frag_ks = GEMM_WIDE_RT; a.frag_slab = 1; produced_frag = true; }
         launch_attn<T>(s, m, a, rw.nseq, c->d_scratch);
