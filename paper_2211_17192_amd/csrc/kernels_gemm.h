@@ -25,9 +25,7 @@
 //    of x^2; the consumer multiplies plain xg rows and scales its output rows
 //    by 1/rms, which it gets by adding the partials in tile order.  No pass
 //    over x, no barrier before the weight stream starts.
-//  * LayerNorm (mean subtraction) is applied as a prologue on the fp32 rows; the row's
-//    mean and variance come from per-tile statistics that the producer of the
-//    residual stream left (LnTile).
+//  * LayerNorm (mean subtraction) is applied as a prologue on the fp32 rows.
 //  * Epilogues: bias, tanh-GELU, gated GELU / SwiGLU (two weight streams, one
 //    activation stream), residual add, rotary + scatter of q / k / v (k and v
 //    go straight into the paged KV cache), logit scaling.
@@ -37,7 +35,7 @@
 namespace sd {
 
 enum { PRO_NONE = 0, PRO_POST = 1, PRO_LN = 2 };
-// EPI_RESID_LN (gemm_kernel): the residual add of a LayerNorm model (bias, LnTile statistics) apart from an RMSNorm
+// EPI_RESID_LN (gemm_kernel): the residual add of a LayerNorm model (bias) apart from an RMSNorm
 // model's (scaled rows, partial sums of squares); the other kernels tell them by their arguments.
 enum { EPI_STORE = 0, EPI_QKV = 1, EPI_RESID = 2, EPI_ACT = 3, EPI_GATED = 4, EPI_LOGITS = 5, EPI_RESID_LN = 6 };
 enum { ACT_GELU = 0, ACT_SILU = 1 };
@@ -49,7 +47,7 @@ struct GemmArgs {
   const void* gain;       // T [K]   (PRO_LN)
   const void* beta;       // T [K]   (PRO_LN)
   const void* bias;       // T [N] or nullptr
-  const float* ss_in;     // PRO_POST: [n_part][16] partial sums of x^2 of the input rows; PRO_LN: LnTile statistics of the rows
+  const float* ss_in;     // PRO_POST: [n_part][16] partial sums of x^2 of the input rows
   int n_part;
   int R, K, N;
   int ksteps_per_wave;    // ceil((K/32) / waves)
@@ -64,7 +62,6 @@ struct GemmArgs {
   void* xg_out;           // T [R][ldo]: (x + y) * gain_next
   const void* gain_next;  // T [N]
   float* ss_out;          // [N/16][16] partial sums of (x + y)^2 per tile and row
-  float* ln_out;          // for a following LayerNorm instead: LnTile statistics of x + y (optional)
   // EPI_QKV
   void* q_out;            // T [R][nq]
   int nq, nkv;            // features [0,nq) q, [nq,nq+nkv) k, [nq+nkv,nq+2nkv) v
@@ -178,79 +175,11 @@ __device__ __forceinline__ float square(float x) {
   const float q = x * x;
   return q;
 }
-// Statistics behind a LayerNorm: whoever writes the rows of the residual stream leaves, per row and
-// 16-feature tile, the tile's mean and its sum of squared distances from that mean; the tiles' means and
-// sums then give the row's mean and variance exactly as two passes over the row would (parallel-variance
-// identity, tiles of equal size).  They lie as [k-step][16 rows][tile of the k-step: mean, sum][..], 16 bytes per
-// (k-step, row): the two tiles of a 32-wide k-step.  All four functions below are shared by every kernel that
-// writes or reads them, contraction off, so that a row's statistics do not depend on the kernel.
-struct LnTile { float mean, m2; };
-// sum over the 16 lanes of a row, the same bits in every lane: ((q0 + q1) + (q2 + q3)), q = (f0 + f1) + (f2 + f3) of a quad
-__device__ __forceinline__ float row16_sum(float v) {
-  auto mirror = [](float x, auto ctrl) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), decltype(ctrl)::value, 0xf, 0xf, true));
-  };
-  v += mirror(v, std::integral_constant<int, 0xB1>());        // quad_perm 1 0 3 2
-  v += mirror(v, std::integral_constant<int, 0x4E>());        // quad_perm 2 3 0 1
-  v += mirror(v, std::integral_constant<int, 0x141>());       // row_half_mirror
-  v += mirror(v, std::integral_constant<int, 0x140>());       // row_mirror
-  return v;
-}
-// one feature a lane, 16 lanes a tile
-__device__ __forceinline__ LnTile ln_tile(float x) {
+// the same in the sum behind a LayerNorm's variance
+__device__ __forceinline__ float add_square(float acc, float x) {
 #pragma clang fp contract(off)
-  LnTile t;
-  t.mean = row16_sum(x) * 0.0625f;
-  const float d = x - t.mean;
-  t.m2 = row16_sum(d * d);
-  return t;
-}
-// eight consecutive features a lane: tile = this lane and its partner; `with_partner(v)` adds the partner's value
-template <typename Add> __device__ __forceinline__ LnTile ln_tile8(const float (&x)[8], Add&& with_partner) {
-#pragma clang fp contract(off)
-  LnTile t;
-  t.mean = with_partner(((x[0] + x[1]) + (x[2] + x[3])) + ((x[4] + x[5]) + (x[6] + x[7]))) * 0.0625f;
-  float q[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) { const float d = x[e] - t.mean; q[e] = d * d; }
-  t.m2 = with_partner(((q[0] + q[1]) + (q[2] + q[3])) + ((q[4] + q[5]) + (q[6] + q[7])));
-  return t;
-}
-__device__ __forceinline__ void ln_put(float* stats, int tile, int row16, const LnTile& t) {
-  *reinterpret_cast<float2*>(stats + ((size_t)(tile >> 1) * 16 + row16) * 4 + (tile & 1) * 2) = make_float2(t.mean, t.m2);
-}
-// Mean and 1 / sqrt(variance + eps) of row j, by the four lanes (j, kq) of a wavefront: lane kq adds the k-steps kq, kq + 4, ..
-// The first LN_HELD of them come in registers (`held`, asked for early), the others through more(k-step).
-constexpr int LN_HELD = 8;
-__device__ __forceinline__ void ln_load(float4 (&held)[LN_HELD], const float* stats, int j, int kq, int KS) {
-#pragma unroll
-  for (int i = 0; i < LN_HELD; ++i) held[i] = *reinterpret_cast<const float4*>(stats + (unsigned)((min(kq + 4 * i, KS - 1) * 16 + j) * 4));
-}
-template <typename More>
-__device__ __forceinline__ void ln_row(const float4 (&held)[LN_HELD], More&& more, int kq, int KS, int K, float eps, float& mu, float& rstd) {
-#pragma clang fp contract(off)
-  auto total = [&](auto&& of) {                      // two sums a lane: shorter ones, closer to the exact sum
-    float s[2] = {0.0f, 0.0f};
-#pragma unroll
-    for (int i = 0; i < LN_HELD; ++i) {
-      const float t = s[i & 1] + of(held[i]);
-      s[i & 1] = (kq + 4 * i < KS) ? t : s[i & 1];
-    }
-    for (int ks = kq + 4 * LN_HELD; ks < KS; ks += 8) {
-      s[0] += of(more(ks));
-      const float t = s[1] + of(more(min(ks + 4, KS - 1)));
-      s[1] = (ks + 4 < KS) ? t : s[1];
-    }
-    float r = s[0] + s[1];
-    r = lane_combine<16>(r, OpSumF());
-    return lane_combine<32>(r, OpSumF());
-  };
-  mu = total([](const float4& v) { return v.x + v.z; }) / (float)(K >> 4);
-  const float q = total([&](const float4& v) {
-    const float d0 = v.x - mu, d1 = v.z - mu;
-    return (v.y + 16.0f * (d0 * d0)) + (v.w + 16.0f * (d1 * d1));
-  });
-  rstd = 1.0f / sqrtf(q / (float)K + eps);
+  const float q = x * x;
+  return acc + q;
 }
 // LayerNorm of one element
 __device__ __forceinline__ float ln_apply(float v, float mu, float rstd, float g, float b) {
@@ -265,7 +194,7 @@ __device__ __forceinline__ float ln_apply(float v, float mu, float rstd, float g
 constexpr int GEMM_PART_STAGE = 256;        // tiles whose partial sums of x^2 are staged in LDS (d_model <= 4096)
 
 template <int EPI, int S> constexpr size_t gemm_lds_bytes(int pro) {
-  return (size_t)(2 * S * (EPI == EPI_GATED ? 2 : 1) * 256 + (pro == PRO_POST ? GEMM_PART_STAGE * 16 : 0)) * sizeof(float);
+  return (size_t)(2 * S * (EPI == EPI_GATED ? 2 : 1) * 256 + (pro == PRO_POST ? GEMM_PART_STAGE * 16 : pro == PRO_LN ? 2 * S * 16 : 0)) * sizeof(float);
 }
 
 // S wavefronts (4 or 8) split K; threads 0..255 (t = row * 16 + feature) run the epilogue.  U: k-steps per chunk (it
@@ -298,7 +227,7 @@ static __global__ __launch_bounds__(64 * S, 2) void gemm_kernel(const GemmArgs a
   const int ntiles = a.N >> 4, grid = (int)gridDim.x, tile_first = (int)blockIdx.x;
   int my_tiles = a.tiles_per_wg;
   while (tile_first + (my_tiles - 1) * grid >= ntiles) --my_tiles;             // (uniform; the grid is no larger than the tiles)
-  float* ssb = lds + 2 * S * ND * 256;               // PRO_POST: GEMM_PART_STAGE * 16 floats
+  float* ssb = lds + 2 * S * ND * 256;               // PRO_POST: GEMM_PART_STAGE * 16 floats; PRO_LN: 2 * S * 16
   const int jr = min(j, a.R - 1);
   const int e_row = (tid >> 4) & 15, e_f = tid & 15;  // epilogue role of this thread (threads 256.. load alike, and drop it)
   const int e_rowc = min(e_row, a.R - 1);             // clamped: loads stay in bounds
@@ -327,8 +256,6 @@ static __global__ __launch_bounds__(64 * S, 2) void gemm_kernel(const GemmArgs a
     if (a.n_part > 64) { fetch(1); fetch(2); fetch(3); }
     else { ss_held[1] = ss_held[2] = ss_held[3] = f32x4{0.f, 0.f, 0.f, 0.f}; }
   }
-  float4 ln_held[LN_HELD];
-  if (PRO == PRO_LN) ln_load(ln_held, a.ss_in, j, kq, KS);
 
   // ---- loads of k-step ks0 + c U + u: a tile's weights, the activations ----
   // (k-steps past the slice re-read its last one and are not multiplied)
@@ -338,16 +265,21 @@ static __global__ __launch_bounds__(64 * S, 2) void gemm_kernel(const GemmArgs a
     if (ND == 2) w[ND - 1][u] = Mma<T>::load_stream(reinterpret_cast<const T*>(reinterpret_cast<const Frag*>(a.W2) + o + (unsigned)lane));
   };
   struct LnIn { float x[8]; Frag g, b; };            // one k-step of a row that is still to be normalised
+  auto load_gb = [&](Frag& g, Frag& b, int ks) {
+    unsigned k8 = (unsigned)(kq * 8);
+    asm volatile("" : "+v"(k8));
+    g = Mma<T>::load(static_cast<const T*>(a.gain) + ks * 32 + k8);
+    b = Mma<T>::load(static_cast<const T*>(a.beta) + ks * 32 + k8);
+  };
   typedef typename std::conditional<PRO == PRO_LN, LnIn, Frag>::type In;
   const unsigned xoff = (unsigned)(jr * a.K + kq * 8);
   auto load_x = [&](In& x, int c, int u) {
-    unsigned row = xoff, k8 = (unsigned)(kq * 8);
-    asm volatile("" : "+v"(row), "+v"(k8));          // stay 32-bit offsets of a scalar base: no address registers to wait for
+    unsigned row = xoff;
+    asm volatile("" : "+v"(row));                    // stays a 32-bit offset of a scalar base: no address registers to wait for
     const int ks = min(ks0 + c * U + u, ks_last);
     if constexpr (PRO == PRO_LN) {
       load8<float>(static_cast<const float*>(a.X) + ks * 32 + row, x.x);
-      x.g = Mma<T>::load(static_cast<const T*>(a.gain) + ks * 32 + k8);
-      x.b = Mma<T>::load(static_cast<const T*>(a.beta) + ks * 32 + k8);
+      load_gb(x.g, x.b, ks);
     } else {
       x = Mma<T>::load(static_cast<const T*>(a.X) + ks * 32 + row);
     }
@@ -480,9 +412,6 @@ static __global__ __launch_bounds__(64 * S, 2) void gemm_kernel(const GemmArgs a
         q = lane_combine<1>(q, OpSumF()); q = lane_combine<2>(q, OpSumF());
         q = lane_combine<4>(q, OpSumF()); q = lane_combine<8>(q, OpSumF());
         if (f == 0) a.ss_out[tile * 16 + row] = q;
-      } else {
-        const LnTile t = ln_tile(xn);
-        if (f == 0) ln_put(a.ln_out, tile, row, t);
       }
     } else if (row < a.R) {
       if (EPI == EPI_STORE) {
@@ -503,9 +432,22 @@ static __global__ __launch_bounds__(64 * S, 2) void gemm_kernel(const GemmArgs a
       }
     }
   };
-  auto statistics = [&] {
-    if (PRO == PRO_LN)
-      ln_row(ln_held, [&](int ks) { return *reinterpret_cast<const float4*>(a.ss_in + (unsigned)((ks * 16 + j) * 4)); }, kq, KS, a.K, a.eps, mu, rstd);
+  // LayerNorm: mean, then variance, of the fp32 rows: a lane adds its features of the wavefront's K-slice in order
+  // (`slice`), then come the four lanes of a row and the wavefronts, in order, through LDS (the barriers hold no load up)
+  auto statistics = [&](auto&& slice) {
+    if (PRO == PRO_LN) {
+      auto total = [&](float s, float* stat) {
+        s = lane_combine<16>(s, OpSumF()); s = lane_combine<32>(s, OpSumF());
+        if (kq == 0) stat[wave * 16 + j] = s;
+        __syncthreads();
+        float t = 0.0f;
+#pragma unroll
+        for (int w = 0; w < S; ++w) t += stat[w * 16 + j];
+        return t;
+      };
+      mu = total(slice([](float s, float v) { return s + v; }), ssb) / (float)a.K;
+      rstd = 1.0f / sqrtf(total(slice([&](float s, float v) { return add_square(s, v - mu); }), ssb + S * 16) / (float)a.K + a.eps);
+    }
     if (PRO == PRO_POST && epi_wave) row_scale();
   };
 
@@ -521,19 +463,52 @@ static __global__ __launch_bounds__(64 * S, 2) void gemm_kernel(const GemmArgs a
     for (int d = 0; d < ND; ++d) acc[d] = Mma<T>::mma(w[d][u], x, acc[d]);
   };
   if constexpr (ONE && PRO == PRO_LN) {
-    Frag x[U];
-    constexpr int H = U > 8 ? U / 2 : U;             // (a LayerNorm's inputs are four times the registers)
+    // the rows go out first: their statistics are taken while the weights arrive
+    Frag x[U], g[U], b[U];
+    float xv[U][8];
+    constexpr int H = U > 8 ? U / 2 : U;             // (all at once would be too many registers)
+    auto k_step = [&](int u) { return min(ks0 + u, ks_last); };
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      unsigned row = xoff;
+      asm volatile("" : "+v"(row));
+      load8<float>(static_cast<const float*>(a.X) + k_step(u) * 32 + row, xv[u]);
+    }
+    if (H == U) {
+#pragma unroll
+      for (int u = 0; u < U; ++u) load_gb(g[u], b[u], k_step(u));
+    }
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int u = 0; u < U; ++u) load_w(w, tile_first, 0, u);
+    __builtin_amdgcn_sched_barrier(0);               // (the scheduler would wait for a position before it asks for the weights)
+    find_page();
+    prefetch_epilogue(tile_first);
+    statistics([&](auto&& add) {
+      float s = 0.0f;
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        float t = s;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) t = add(t, xv[u][e]);
+        s = (ks0 + u < ks1) ? t : s;
+      }
+      return s;
+    });
 #pragma unroll
     for (int h = 0; h < U; h += H) {
-      In xin[H];
+      if (H != U) {
 #pragma unroll
-      for (int u = 0; u < H; ++u) load_x(xin[u], 0, h + u);
-      __builtin_amdgcn_sched_barrier(0);             // (the scheduler would wait for a position before it asks for the weights)
-      if (h == 0) { find_page(); prefetch_epilogue(tile_first); statistics(); }
+        for (int u = h; u < h + H; ++u) load_gb(g[u], b[u], k_step(u));
+      }
 #pragma unroll
-      for (int u = 0; u < H; ++u) x[h + u] = operand(xin[u]);
+      for (int u = h; u < h + H; ++u) {
+        LnIn in;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) in.x[e] = xv[u][e];
+        in.g = g[u]; in.b = b[u];
+        x[u] = operand(in);
+      }
     }
     for (int left = my_tiles - 1; left > 0; --left) {
 #pragma unroll
@@ -555,7 +530,18 @@ static __global__ __launch_bounds__(64 * S, 2) void gemm_kernel(const GemmArgs a
     for (int u = 0; u < U; ++u) { load_w(w, tile_first, 0, u); load_x(x[u], 0, u); }
     __builtin_amdgcn_sched_barrier(0);
     find_page();
-    statistics();
+    statistics([&](auto&& add) {                     // (the rows are in the caches)
+      const float* row = static_cast<const float*>(a.X) + xoff;
+      float s = 0.0f;
+#pragma unroll 4
+      for (int ks = ks0; ks < ks1; ++ks) {
+        float v[8];
+        load8<float>(row + ks * 32, v);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s = add(s, v[e]);
+      }
+      return s;
+    });
     for (int left = my_tiles * nchunks - 1; left > 0; --left) {
       const bool closes = ONE || c_c == nchunks - 1;
       const int l_c = closes ? 0 : c_c + 1, l_tile = closes ? c_tile + grid : c_tile;
@@ -600,7 +586,7 @@ constexpr int GEMM_WIDE_U = 2;
 // LDS of the wide kernel: the partial tiles of every wavefront, stream and slab, the QKV
 // staging rows, and per-row constants.
 __host__ __device__ constexpr size_t gemm_wide_lds_bytes(int S) {
-  return (size_t)(S * 2 * GEMM_WIDE_RT * 256 + 2 * GEMM_WIDE_RT * 256 + GEMM_WIDE_RT * 16 * 4) * sizeof(float);
+  return (size_t)(S * 2 * GEMM_WIDE_RT * 256 + 2 * GEMM_WIDE_RT * 256 + S * 16 + GEMM_WIDE_RT * 16 * 4) * sizeof(float);
 }
 
 // Row-major activations [nrt * 16][K] -> fragment order [K/32][GEMM_WIDE_RT][64][8].
@@ -652,7 +638,8 @@ static __global__ __launch_bounds__(512) void gemm_wide_kernel(const GemmArgs a)
   auto stream_tile = [&](int pair, int st) { return (ND == 2) ? pair : 2 * pair + st; };
   float* part = lds;                                 // [S][2][RT][256]
   float* ybuf = part + S * 2 * RT * 256;             // [2][RT][256]
-  float* rs_s = ybuf + 2 * RT * 256;                 // [RT * 16] 1 / rms of every row (PRO_POST)
+  float* stat = ybuf + 2 * RT * 256;                 // [S][16]
+  float* rs_s = stat + S * 16;                       // [RT * 16] 1 / rms of every row (PRO_POST)
   int* pos_s = reinterpret_cast<int*>(rs_s + RT * 16);          // [RT * 16] position of every row (EPI_QKV)
   unsigned long long* kvb_s = reinterpret_cast<unsigned long long*>(pos_s + RT * 16);   // [RT * 16] cache offset
   const int nrt = a.nrt;
@@ -672,16 +659,40 @@ static __global__ __launch_bounds__(512) void gemm_wide_kernel(const GemmArgs a)
   const int e_row = (tid >> 4) & 15, e_f = tid & 15, e_idx = tid & 255;
   const int es_step = (int)blockDim.x >> 8, es0 = tid >> 8;          // 1 or 2; 0 or 1
 
-  // ---- PRO_LN: statistics of the rows, slab by slab ----
+  // ---- PRO_LN: statistics of the fp32 rows, slab by slab ----
   float mu[RT], rstd[RT];
 #pragma unroll
-  for (int rt = 0; rt < RT; ++rt) {
-    mu[rt] = 0.0f; rstd[rt] = 1.0f;
-    if (PRO == PRO_LN) {
-      const float* st = a.ss_in + (size_t)min(rt, nrt - 1) * a.ss_stride;
-      float4 held[LN_HELD];
-      ln_load(held, st, j, kq, KS);
-      ln_row(held, [&](int ks) { return *reinterpret_cast<const float4*>(st + (ks * 16 + j) * 4); }, kq, KS, a.K, a.eps, mu[rt], rstd[rt]);
+  for (int rt = 0; rt < RT; ++rt) { mu[rt] = 0.0f; rstd[rt] = 1.0f; }
+  if (PRO == PRO_LN) {
+#pragma unroll
+    for (int rt = 0; rt < RT; ++rt) {
+      const float* x = static_cast<const float*>(a.X) + (size_t)jr[rt] * a.K + kq * 8;
+      float s1 = 0.0f;
+      for (int ks = ks0; ks < ks1; ++ks) {
+        float v[8]; load8<float>(x + ks * 32, v);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s1 += v[e];
+      }
+      s1 = lane_combine<16>(s1, OpSumF()); s1 = lane_combine<32>(s1, OpSumF());
+      __syncthreads();
+      if (kq == 0) stat[wave * 16 + j] = s1;
+      __syncthreads();
+      float t = 0.0f;
+      for (int w = 0; w < S; ++w) t += stat[w * 16 + j];
+      mu[rt] = t / (float)a.K;
+      float s2 = 0.0f;
+      for (int ks = ks0; ks < ks1; ++ks) {
+        float v[8]; load8<float>(x + ks * 32, v);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s2 = add_square(s2, v[e] - mu[rt]);
+      }
+      s2 = lane_combine<16>(s2, OpSumF()); s2 = lane_combine<32>(s2, OpSumF());
+      __syncthreads();
+      if (kq == 0) stat[wave * 16 + j] = s2;
+      __syncthreads();
+      float t2 = 0.0f;
+      for (int w = 0; w < S; ++w) t2 += stat[w * 16 + j];
+      rstd[rt] = 1.0f / sqrtf(t2 / (float)a.K + a.eps);
     }
   }
 
@@ -811,10 +822,6 @@ static __global__ __launch_bounds__(512) void gemm_wide_kernel(const GemmArgs a)
               q = lane_combine<1>(q, OpSumF()); q = lane_combine<2>(q, OpSumF());
               q = lane_combine<4>(q, OpSumF()); q = lane_combine<8>(q, OpSumF());
               if (f == 0) a.ss_out[(size_t)rt * a.ss_stride + tile * 16 + e_row] = q;
-            }
-            if (a.ln_out != nullptr) {
-              const LnTile t = ln_tile(xn);
-              if (f == 0) ln_put(a.ln_out + (size_t)rt * a.ss_stride, tile, e_row, t);
             }
           } else if (ok) {
             if (EPI == EPI_STORE) {
@@ -1063,10 +1070,6 @@ static __global__ __launch_bounds__(256) void gemm_split_finish_kernel(const Gem
       q = lane_combine<1>(q, OpSumF()); q = lane_combine<2>(q, OpSumF());
       q = lane_combine<4>(q, OpSumF()); q = lane_combine<8>(q, OpSumF());
       if (f == 0) a.ss_out[(size_t)rt * a.ss_stride + tile * 16 + e_row] = q;
-    }
-    if (a.ln_out != nullptr) {
-      const LnTile t = ln_tile(xn);
-      if (f == 0) ln_put(a.ln_out + (size_t)rt * a.ss_stride, tile, e_row, t);
     }
   } else if (ok) {
     if (EPI == EPI_STORE) {

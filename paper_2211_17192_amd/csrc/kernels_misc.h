@@ -4,7 +4,6 @@
 // every iteration.
 #pragma once
 #include "common.h"
-#include "kernels_gemm.h"
 
 namespace sd {
 
@@ -28,7 +27,6 @@ enum {
 // row of the logits buffer its LM-head output belongs in (< 0: not needed):
 // p rows [seq][gamma+1], q rows [seq][gamma], one row per sequence for plain decoding.
 // xg_frag: xg in the fragment order of the products over many rows instead of row-major.
-// LayerNorm models: `ln` (when given) receives the rows' LnTile statistics, blocks of ss_stride floats per slab.
 template <typename T>
 static __global__ __launch_bounds__(256) void embed_kernel(
     int mode, int step, const SeqState* __restrict__ st, const int* __restrict__ prompt, int start,
@@ -36,7 +34,7 @@ static __global__ __launch_bounds__(256) void embed_kernel(
     float* __restrict__ x, int* __restrict__ row_pos, const T* __restrict__ gain_next,
     T* __restrict__ xg, float* __restrict__ ss,
     int rps, int seq0, int gamma, int* __restrict__ row_seq, int* __restrict__ logit_row,
-    int ss_stride, int xg_frag, float* __restrict__ ln) {
+    int ss_stride, int xg_frag) {
   __shared__ float red[16];
   const int j = (int)blockIdx.x % rps, sl = (int)blockIdx.x / rps, seq = seq0 + sl;
   const int r = blockIdx.x, slab = r / MAX_ROWS, r16 = r % MAX_ROWS;     // row, its slab, row within the slab
@@ -84,10 +82,6 @@ static __global__ __launch_bounds__(256) void embed_kernel(
           q += val * val;
         }
         store8<float>(x + (size_t)r * d + g * 8, xv);
-        if (ln) {                                     // (uniform; both halves of a tile are here: d is a multiple of 32)
-          const LnTile t = ln_tile8(xv, [](float v) { return lane_combine<1>(v, OpSumF()); });
-          if ((g & 1) == 0) ln_put(ln + (size_t)slab * ss_stride, g >> 1, r16, t);
-        }
         if (xg) store8<T>(xg + (xg_frag ? rows_frag_index(r, g * 8, d >> 5) : (size_t)r * d + g * 8), xgv);
       }
     }

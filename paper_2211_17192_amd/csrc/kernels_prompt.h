@@ -25,57 +25,99 @@ static __global__ __launch_bounds__(256) void rows_to_slabs_kernel(const bf16* _
   *reinterpret_cast<bf16x8*>(Xf + idx * 8) = *reinterpret_cast<const bf16x8*>(X + (size_t)row * K + ks * 32 + (lane >> 4) * 8);
 }
 
-// LayerNorm of fp32 rows into fragment order: the statistics and the normalisation of gemm_kernel, once per row
-// instead of in every workgroup of the product.  The tiles' statistics (LnTile) are taken from the rows
-// themselves and meet in LDS; every wavefront then adds them up for itself, so there is one barrier, and up to HELD k-steps
-// a wavefront stay in registers: one trip to memory.  grid = slabs, 512 threads; dynamic LDS: K/32 * 256 bytes.
-constexpr size_t rows_layernorm_lds(int K) { return (size_t)(K >> 5) * 256; }
+// LayerNorm of fp32 rows into fragment order: gemm_kernel's statistics (the K-slices of its S
+// wavefronts, added in wavefront order) and its normalisation, once per row instead of in every
+// workgroup of the product.  grid = slabs, 64 S threads, S = the wavefronts of gemm_kernel.
 static __global__ __launch_bounds__(512) void rows_layernorm_kernel(const float* __restrict__ X, const bf16* __restrict__ gain,
-                                                                    const bf16* __restrict__ beta, bf16* __restrict__ Xf, int rows, int K, float eps) {
-  extern __shared__ __align__(16) float stats[];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+                                                                    const bf16* __restrict__ beta, bf16* __restrict__ Xf, int rows, int K,
+                                                                    int ksteps_per_wave, float eps) {
+  __shared__ float stat[2][8 * 16];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, S = blockDim.x >> 6;
   const int j = lane & 15, kq = lane >> 4, KS = K >> 5;
+  const int ks0 = min(KS, wave * ksteps_per_wave), ks1 = min(KS, ks0 + ksteps_per_wave);
   const float* x = X + (size_t)min((int)blockIdx.x * 16 + j, rows - 1) * K + kq * 8;
   bf16x8* out = reinterpret_cast<bf16x8*>(Xf) + (size_t)blockIdx.x * KS * 64 + lane;
-  constexpr int HELD = 4, S = 8;                     // k-steps wave, wave + S, ..
-  auto tile_stats = [&](const float (&xv)[8], int ks) {
-    const LnTile t = ln_tile8(xv, [](float v) { return lane_combine<16>(v, OpSumF()); });
-    if ((kq & 1) == 0) ln_put(stats, 2 * ks + (kq >> 1), j, t);
+  // up to HELD k-steps a wavefront (K 1024 with four of them, 2048 with eight) stay in registers over all
+  // three passes: one trip to memory instead of three
+  constexpr int HELD = 8;
+  auto slice_sums = [&](auto&& add) {
+    float s = add();
+    s = lane_combine<16>(s, OpSumF()); return lane_combine<32>(s, OpSumF());
   };
-  float xv[HELD][8];
-  bf16x8 g[HELD], b[HELD];
-#pragma unroll
-  for (int u = 0; u < HELD; ++u) {
-    const int k = min(wave + S * u, KS - 1) * 32;
-    load8<float>(x + k, xv[u]);
-    g[u] = Mma<bf16>::load(gain + k + kq * 8);
-    b[u] = Mma<bf16>::load(beta + k + kq * 8);
-  }
-#pragma unroll
-  for (int u = 0; u < HELD; ++u)
-    if (wave + S * u < KS) tile_stats(xv[u], wave + S * u);
-  for (int ks = wave + S * HELD; ks < KS; ks += S) {
-    float v[8]; load8<float>(x + ks * 32, v);
-    tile_stats(v, ks);
-  }
-  __syncthreads();
-  float4 held[LN_HELD];
-  float mu, rstd;
-  ln_load(held, stats, j, kq, KS);
-  ln_row(held, [&](int ks) { return *reinterpret_cast<const float4*>(stats + (ks * 16 + j) * 4); }, kq, KS, K, eps, mu, rstd);
-  auto normalise = [&](const float (&v)[8], int ks, const bf16x8& gg, const bf16x8& bb) {
-    float o[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) o[e] = ln_apply(v[e], mu, rstd, (float)gg[e], (float)bb[e]);
-    out[ks * 64] = Mma<bf16>::from_floats(o);
+  auto total = [&](float s, int which) {
+    if (kq == 0) stat[which][wave * 16 + j] = s;
+    __syncthreads();
+    float t = 0.0f;
+    for (int w = 0; w < S; ++w) t += stat[which][w * 16 + j];
+    return t;
   };
+  auto normalise = [&](const float (&xv)[8], int ks, float mu, float rstd, const bf16x8& g, const bf16x8& b) {
+    float v[8];
 #pragma unroll
-  for (int u = 0; u < HELD; ++u)
-    if (wave + S * u < KS) normalise(xv[u], wave + S * u, g[u], b[u]);
+    for (int e = 0; e < 8; ++e) v[e] = ln_apply(xv[e], mu, rstd, (float)g[e], (float)b[e]);
+    out[ks * 64] = Mma<bf16>::from_floats(v);
+  };
+  if (ksteps_per_wave <= HELD) {
+    float xv[HELD][8];
+    bf16x8 g[HELD], b[HELD];
+#pragma unroll
+    for (int u = 0; u < HELD; ++u) {
+      const int k = min(ks0 + u, KS - 1) * 32;
+      load8<float>(x + k, xv[u]);
+      g[u] = Mma<bf16>::load(gain + k + kq * 8);
+      b[u] = Mma<bf16>::load(beta + k + kq * 8);
+    }
+    const float mu = total(slice_sums([&] {
+      float s = 0.0f;
+#pragma unroll
+      for (int u = 0; u < HELD; ++u)
+        if (ks0 + u < ks1) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) s += xv[u][e];
+        }
+      return s;
+    }), 0) / (float)K;
+    const float var = total(slice_sums([&] {
+      float s = 0.0f;
+#pragma unroll
+      for (int u = 0; u < HELD; ++u)
+        if (ks0 + u < ks1) {
+#pragma unroll
+          for (int e = 0; e < 8; ++e) s = add_square(s, xv[u][e] - mu);
+        }
+      return s;
+    }), 1) / (float)K;
+    const float rstd = 1.0f / sqrtf(var + eps);
+#pragma unroll
+    for (int u = 0; u < HELD; ++u)
+      if (ks0 + u < ks1) normalise(xv[u], ks0 + u, mu, rstd, g[u], b[u]);
+    return;
+  }
+  const float mu = total(slice_sums([&] {
+    float s = 0.0f;
 #pragma unroll 4
-  for (int ks = wave + S * HELD; ks < KS; ks += S) {
+    for (int ks = ks0; ks < ks1; ++ks) {
+      float v[8]; load8<float>(x + ks * 32, v);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) s += v[e];
+    }
+    return s;
+  }), 0) / (float)K;
+  const float var = total(slice_sums([&] {
+    float s = 0.0f;
+#pragma unroll 4
+    for (int ks = ks0; ks < ks1; ++ks) {
+      float v[8]; load8<float>(x + ks * 32, v);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) s = add_square(s, v[e] - mu);
+    }
+    return s;
+  }), 1) / (float)K;
+  const float rstd = 1.0f / sqrtf(var + eps);
+#pragma unroll 4
+  for (int ks = ks0; ks < ks1; ++ks) {
     float v[8]; load8<float>(x + ks * 32, v);
-    normalise(v, ks, Mma<bf16>::load(gain + ks * 32 + kq * 8), Mma<bf16>::load(beta + ks * 32 + kq * 8));
+    normalise(v, ks, mu, rstd, Mma<bf16>::load(gain + ks * 32 + kq * 8), Mma<bf16>::load(beta + ks * 32 + kq * 8));
   }
 }
 

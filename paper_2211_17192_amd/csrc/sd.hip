@@ -118,16 +118,13 @@ int prompt_rows_per_wg(const sd_model_cfg& c) { return ATTN_MAX_RG / (c.n_heads 
 // part of a workspace that can shrink: a pass of fewer rows reads the weights more often and gives the same
 // results.  Below 32 rows there are no such passes (forward()'s kernels take 16 rows at a time).
 constexpr int ROWS_PASS_MAX = 2048, ROWS_PASS_MIN = 32;
-constexpr int ROWS_LAYERNORM_MAX = 16384;
 
 // Lays a model out in the arena (or sizes it); rows_limit: prompt rows of one pass at most, 0: no such passes.
 void plan_model(Arena& A, Model& m, const sd_model_cfg& c, int page_size, int batch, int rows_limit) {
   m.cfg = c;
   m.batch = batch;
   // bf16 models with the matrix-core attention take a prompt many rows at a time
-  // (a LayerNorm of that path keeps its slab's statistics in LDS: up to 16384 features)
-  const bool many = rows_limit > 0 && c.dtype == SD_BF16 && (c.d_head == 64 || c.d_head == 128) &&
-                    (c.arch != SD_ARCH_GPT || c.d_model <= ROWS_LAYERNORM_MAX);
+  const bool many = rows_limit > 0 && c.dtype == SD_BF16 && (c.d_head == 64 || c.d_head == 128);
   m.rows_pass = many ? std::min(rows_limit, (c.max_len + MAX_ROWS - 1) / MAX_ROWS * MAX_ROWS) : 0;
   m.rows_cap = std::max(MAX_ROWS * batch, m.rows_pass);
   m.esz = (c.dtype == SD_BF16) ? 2 : 4;
@@ -478,7 +475,7 @@ template <typename T>
 void launch_gemm(hipStream_t s, int pro, int epi, const GemmArgs& a) {
 #define SD_CASE(P, E) if (pro == P && epi == E) return launch_gemm_t<T, P, E>(s, a)
   SD_CASE(PRO_LN, EPI_QKV); SD_CASE(PRO_POST, EPI_QKV);
-  if (pro == PRO_NONE && epi == EPI_RESID && a.ln_out != nullptr) return launch_gemm_t<T, PRO_NONE, EPI_RESID_LN>(s, a);
+  if (pro == PRO_NONE && epi == EPI_RESID && a.xg_out == nullptr) return launch_gemm_t<T, PRO_NONE, EPI_RESID_LN>(s, a);
   SD_CASE(PRO_NONE, EPI_RESID); SD_CASE(PRO_NONE, EPI_STORE); SD_CASE(PRO_POST, EPI_STORE);
   SD_CASE(PRO_LN, EPI_ACT); SD_CASE(PRO_POST, EPI_GATED);
   SD_CASE(PRO_LN, EPI_LOGITS); SD_CASE(PRO_POST, EPI_LOGITS);
@@ -681,9 +678,8 @@ void forward(sd_ctx* c, Model& m, const Rows& rw, float* logits) {
   const int skip = c->skip_ops;                     // measurement only (sd_time_forward); 0 in every decoding call
   const int rows_total = rw.nseq * rw.rps;
   const int n_groups = (rows_total + MAX_ROWS - 1) / MAX_ROWS;
-  // LayerNorm models: the rows' statistics lie where an RMSNorm model's scaled rows do
-  const int stat_stride = rms ? d : 2 * d;          // floats from one slab's to the next's
-  struct Grp { int R; float* x; char* xg; float *ss, *ln; char *qbuf, *attn, *ffn; int *row_pos, *row_seq, *logit_row; };
+  const int ss_stride = (d / 16) * 16;              // floats from one slab's partial sums to the next's
+  struct Grp { int R; float* x; char* xg; float* ss; char *qbuf, *attn, *ffn; int *row_pos, *row_seq, *logit_row; };
   auto group = [&](int g) {
     Grp q;
     q.R = std::min(MAX_ROWS, rows_total - g * MAX_ROWS);
@@ -691,7 +687,6 @@ void forward(sd_ctx* c, Model& m, const Rows& rw, float* logits) {
     q.x = m.x + off * d;
     q.xg = static_cast<char*>(m.xg) + off * d * e;
     q.ss = m.ss + (size_t)g * d;
-    q.ln = static_cast<float*>(m.xg) + (size_t)g * 2 * d;
     q.qbuf = static_cast<char*>(m.qbuf) + off * m.nq * e;
     q.attn = static_cast<char*>(m.attn) + off * m.nq * e;
     q.ffn = static_cast<char*>(m.ffn) + off * f.d_ff * e;
@@ -704,7 +699,7 @@ void forward(sd_ctx* c, Model& m, const Rows& rw, float* logits) {
                        rw.start, static_cast<const T*>(m.tok_emb), static_cast<const T*>(m.pos_emb), d, f.vocab, q.x,
                        q.row_pos, static_cast<const T*>(rms ? m.L[0].ln1g : nullptr),
                        reinterpret_cast<T*>(rms ? q.xg : nullptr), rms ? q.ss : nullptr,
-                       rw.rps, rw.seq0, rw.gamma, q.row_seq, q.logit_row, stat_stride, 0, rms ? nullptr : q.ln);
+                       rw.rps, rw.seq0, rw.gamma, q.row_seq, q.logit_row, ss_stride, 0);
   }
   // One GEMM over every group: groups are 16-row slabs one after the other in all row-indexed
   // buffers, so up to GEMM_WIDE_RT of them go into one launch of the wide kernel (weights
@@ -726,7 +721,7 @@ void forward(sd_ctx* c, Model& m, const Rows& rw, float* logits) {
       a.nrt = std::min(GEMM_WIDE_RT, n_groups - g0);
       a.R = R_full;
       a.R_last = (g0 + a.nrt == n_groups) ? R_tail : R_full;
-      a.ss_stride = stat_stride;
+      a.ss_stride = ss_stride;
       if (frag_in != nullptr && pro_ == PRO_NONE && n_groups <= GEMM_WIDE_RT) {
         a.X = frag_in;
       } else if (pro_ != PRO_LN) {                // the wide kernel reads the activations in fragment order
@@ -755,14 +750,13 @@ void forward(sd_ctx* c, Model& m, const Rows& rw, float* logits) {
     a.R = q.R;
     a.eps = f.norm_eps;
     if (rms) { a.X = q.xg; a.ss_in = q.ss; a.n_part = n_part; }
-    else { a.X = q.x; a.gain = gain; a.beta = beta; a.ss_in = q.ln; }
+    else { a.X = q.x; a.gain = gain; a.beta = beta; }
   };
   // residual add that also prepares the input of the next norm
   auto resid = [&](const void* W, bool from_ffn, const void* bias, int K, const void* gain_next) {
     gemm_groups(PRO_NONE, EPI_RESID, [&](GemmArgs& o, const Grp& q) {
       o.R = q.R; o.W = W; o.X = from_ffn ? q.ffn : q.attn; o.bias = bias; o.K = K; o.N = d; o.out = q.x; o.ldo = d;
       if (rms) { o.xg_out = q.xg; o.gain_next = gain_next; o.ss_out = q.ss; }
-      else o.ln_out = q.ln;
     });
     n_part = d / 16;
   };
@@ -935,7 +929,7 @@ void forward_rows(sd_ctx* c, Model& m, const Rows& rw, float* logits) {
   auto cb = [](const void* p) { return static_cast<const bf16*>(p); };
   hipLaunchKernelGGL((embed_kernel<bf16>), dim3(rows), dim3(256), 0, s, rw.mode, rw.step, c->d_state, m.prompt, rw.start,
                      cb(m.tok_emb), cb(m.pos_emb), d, f.vocab, m.x, m.row_pos, cb(rms ? m.L[0].ln1g : nullptr),
-                     rms ? xg : (bf16*)nullptr, rms ? m.ss : nullptr, rw.rps, rw.seq0, rw.gamma, m.row_seq, m.logit_row, ss_stride, 1, nullptr);
+                     rms ? xg : (bf16*)nullptr, rms ? m.ss : nullptr, rw.rps, rw.seq0, rw.gamma, m.row_seq, m.logit_row, ss_stride, 1);
   int n_part = 1;
   // the input of a product behind a norm: the rows' partial sums, or the normalised rows
   auto normed = [&](const void* g, const void* b) {
@@ -944,7 +938,8 @@ void forward_rows(sd_ctx* c, Model& m, const Rows& rw, float* logits) {
     if (rms) {
       a.ss_in = m.ss; a.n_part = n_part; a.ss_stride = ss_stride; a.eps = f.norm_eps;
     } else {
-      hipLaunchKernelGGL(rows_layernorm_kernel, dim3(slabs), dim3(512), rows_layernorm_lds(d), s, m.x, cb(g), cb(b), xg, rows, d, f.norm_eps);
+      const int KS = d / 32, S = pick_waves(KS);
+      hipLaunchKernelGGL(rows_layernorm_kernel, dim3(slabs), dim3(64 * S), 0, s, m.x, cb(g), cb(b), xg, rows, d, (KS + S - 1) / S, f.norm_eps);
     }
     return a;
   };
@@ -1323,8 +1318,7 @@ extern "C" sd_status sd_load_models(sd_ctx** out, const sd_model_cfg* p_cfg, con
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0)
       g_num_cus = cus;
   }
-  if (hipFuncSetAttribute(reinterpret_cast<const void*>(&rows_layernorm_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)rows_layernorm_lds(ROWS_LAYERNORM_MAX)) != hipSuccess ||
-      allow_big_lds<bf16>() != hipSuccess || allow_big_lds<float>() != hipSuccess ||
+  if (allow_big_lds<bf16>() != hipSuccess || allow_big_lds<float>() != hipSuccess ||
       allow_wide_lds<bf16>() != hipSuccess || allow_wide_lds<float>() != hipSuccess ||
       allow_slices_lds<EPI_STORE>() != hipSuccess || allow_slices_lds<EPI_QKV>() != hipSuccess || allow_slices_lds<EPI_RESID>() != hipSuccess ||
       allow_slices_lds<EPI_ACT>() != hipSuccess || allow_slices_lds<EPI_GATED>() != hipSuccess || allow_slices_lds<EPI_LOGITS>() != hipSuccess)
@@ -1721,7 +1715,7 @@ extern "C" sd_status sd_time_ffn_in(sd_ctx* c, int32_t rows, int32_t reps, doubl
       if (f.dtype == SD_BF16) launch_gemm<bf16>(c->stream, PRO_POST, EPI_GATED, h);
       else launch_gemm<float>(c->stream, PRO_POST, EPI_GATED, h);
     } else {
-      h.X = m.x; h.gain = l.ln2g; h.beta = l.ln2b; h.bias = l.b1; h.ss_in = static_cast<const float*>(m.xg);
+      h.X = m.x; h.gain = l.ln2g; h.beta = l.ln2b; h.bias = l.b1;
       if (f.dtype == SD_BF16) launch_gemm<bf16>(c->stream, PRO_LN, EPI_ACT, h);
       else launch_gemm<float>(c->stream, PRO_LN, EPI_ACT, h);
     }
