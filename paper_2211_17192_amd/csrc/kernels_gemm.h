@@ -209,8 +209,9 @@ template <int EPI, int S> constexpr size_t gemm_lds_bytes(int pro) {
 // truth none); inputs that are absent are read from the weights and dropped; there are no divisions; the partial
 // tiles are read back with all reads in flight; the norms' statistics are taken while the weights arrive.
 // us a launch inside its forward, before -> after:
-//   GPT-like 97M shape, 8 rows: LayerNorm + QKV 7.2 -> 5.5, + FFN-in 7.0 -> 4.7, O 4.8 -> 3.3; FFN-out 6.5 -> 6.5 (48 tiles:
-//   what 48 CUs can pull); its draft (256 wide), 1 row: 5.5 -> 3.7, 4.6 -> 3.5, O 4.8 -> 2.5, FFN-out 4.4 -> 2.9
+//   GPT-like 97M shape, 8 rows: LayerNorm + QKV 7.2 -> 4.5, + FFN-in 7.0 -> 4.6, O 4.8 -> 3.2; FFN-out 6.5 -> 5.8 (48 tiles:
+//   what 48 CUs can pull); its draft (256 wide), 1 row: 5.5 -> 3.2, 4.6 -> 3.4, O 4.8 -> 2.4, FFN-out 4.4 -> 3.1
+//   (rows ahead of the weights; with statistics left by the rows' producer instead: QKV 5.5, FFN-in 4.7, draft 3.7, 3.5)
 //   T5-XXL shape, 6 rows: QKV 19.2 -> 18.1, O 8.3 -> 7.5, gated FFN-in 28.6 -> 26.9, FFN-out 15.5 -> 14.9; its draft
 //   (512 wide), 1 row: QKV 4.5 -> 3.2, gated FFN-in 4.5 -> 3.5, LM head 10.2 -> 7.6
 template <typename T, int PRO, int EPI, int U, int S, bool ONE>
