@@ -144,6 +144,12 @@ template <> struct Words<double> {
   }
 };
 
+template <> struct Words<unsigned long long> {
+  static constexpr int N = 2;
+  static __device__ __forceinline__ void split(unsigned long long v, unsigned (&w)[2]) { w[0] = (unsigned)v; w[1] = (unsigned)(v >> 32); }
+  static __device__ __forceinline__ unsigned long long join(const unsigned (&w)[2]) { return ((unsigned long long)w[1] << 32) | w[0]; }
+};
+
 template <int OFF, typename V, typename Op>
 __device__ __forceinline__ V lane_combine(V v, Op op) {
   unsigned w[2];
@@ -184,6 +190,7 @@ __device__ __forceinline__ V wave_allreduce(V v, Op op) {
 
 struct OpSumF { __device__ float operator()(float a, float b) const { return a + b; } };
 struct OpSumD { __device__ double operator()(double a, double b) const { return a + b; } };
+struct OpSumU { __device__ unsigned long long operator()(unsigned long long a, unsigned long long b) const { return a + b; } };
 struct OpMaxF { __device__ float operator()(float a, float b) const { return fmaxf(a, b); } };
 struct OpMinI { __device__ int operator()(int a, int b) const { return min(a, b); } };
 struct OpSumI { __device__ int operator()(int a, int b) const { return a + b; } };
@@ -191,6 +198,7 @@ struct OpMaxI { __device__ int operator()(int a, int b) const { return max(a, b)
 
 __device__ __forceinline__ float wave_sum(float v) { return wave_allreduce(v, OpSumF()); }
 __device__ __forceinline__ double wave_sum(double v) { return wave_allreduce(v, OpSumD()); }
+__device__ __forceinline__ unsigned long long wave_sum(unsigned long long v) { return wave_allreduce(v, OpSumU()); }
 __device__ __forceinline__ float wave_max(float v) { return wave_allreduce(v, OpMaxF()); }
 __device__ __forceinline__ int wave_min(int v) { return wave_allreduce(v, OpMinI()); }
 __device__ __forceinline__ int wave_max(int v) { return wave_allreduce(v, OpMaxI()); }

@@ -398,8 +398,17 @@ __device__ __forceinline__ bool filter_fast(const float4 (&v)[SAMPLE_REG_F4], in
     }
     float thr = key_float(tau);
     auto weight = [&](unsigned k, bool ok) { return ok ? exp_scaled(key_float(k), m, invT, thr) : 0.0f; };
+    // the sum, in whole numbers of 2^-56 (a weight is at most 1, the list holds 128): the list's order, which is how the
+    // wavefronts happened to arrive, does not show in it
+    auto whole = [](float e) {
+      const unsigned b = __float_as_uint(e);
+      const int up = (int)(b >> 23) - 94;            // 1.0: 33
+      const unsigned long long man = (b & 0x7fffffu) | 0x800000u;
+      return up >= 0 ? man << (up & 63) : up >= -25 ? (man + (1ull << (-up - 1))) >> -up : 0ull;
+    };
+    auto total = [&](float a, float b) { return (double)wave_sum(whole(a) + whole(b)) * 0x1p-56; };
     float e0 = weight(k0, ok0), e1 = weight(k1, ok1);
-    double S = wave_sum((double)e0 + (double)e1);
+    double S = total(e0, e1);
     if (top_p > 0.0f && top_p < 1.0f) {
       constexpr double UNIT = 17592186044416.0;      // weights in units of 2^-44 of the largest, as 31 + 13 bits
       auto units = [](float e) {
@@ -423,7 +432,7 @@ __device__ __forceinline__ bool filter_fast(const float4 (&v)[SAMPLE_REG_F4], in
       for (int o = 32; o; o >>= 1) best_key = max(best_key, (unsigned)__shfl_xor((int)best_key, o, WAVE));
       thr = fmaxf(best_key ? key_float(best_key) : -INFINITY, thr);
       e0 = weight(k0, ok0); e1 = weight(k1, ok1);
-      S = wave_sum((double)e0 + (double)e1);
+      S = total(e0, e1);
     }
     if (lane == 0) { sm.total = S; sm.sel = __float_as_uint(thr); }
   }

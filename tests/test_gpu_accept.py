@@ -126,6 +126,25 @@ def test_filter_on_a_short_list(kind, vocab, top_k, top_p):
     check(zp, zq, x, r, s, 1.0, top_k, top_p)
 
 
+def test_short_list_sums_do_not_depend_on_its_order():
+    """Six entries are kept: two weigh 1, four 0.45 * 2^-52.  Together 2 + 1.8 * 2^-52, as a 64-bit number 2 + 2^-51; added
+    one after the other in 64 bits they give that or 2, by where in the row they lie and which of them is listed
+    first.  The guess has p = 1 / S and q = 1, and r = 1/2 refuses it only if S > 2."""
+    rows, vocab, top_k = 128, 8192, 6               # (a thread holds entries 4 t .. 4 t + 3 and 4096 further on)
+    g = np.random.Generator(np.random.PCG64(3))
+    zp = (-60.0 - g.random((rows, 2, vocab))).astype(np.float32)
+    zq = (-200.0 - g.random((rows, 1, vocab))).astype(np.float32)
+    x = np.zeros((rows, 1), np.int32)
+    for b in range(rows):
+        at = g.choice(1024, top_k, replace=False) * 4 + g.integers(0, 4, top_k)      # (a thread each: else the list is too short for the row)
+        zp[b, :, at[:2]], zp[b, :, at[2:]] = 0.0, np.log(0.45) - 52 * np.log(2.0)
+        x[b], zq[b, 0, at[0]] = at[0], 0.0
+    r, s = np.full((rows, 1), 0.5, np.float32), np.full(rows, 0.25, np.float32)
+    for _ in range(5):
+        n, _, _ = call(zp, zq, x, r, s, 1.0, top_k=top_k)
+        assert not n.any(), n
+
+
 def test_calls_of_any_size_share_one_scratch():
     from paper_2211_17192_amd import binding
     scratch = binding.spec_sample_scratch(64, 7)
