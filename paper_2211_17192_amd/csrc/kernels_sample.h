@@ -348,10 +348,13 @@ __device__ __forceinline__ bool filter_fast(const float4 (&v)[SAMPLE_REG_F4], in
   unsigned* bins = reinterpret_cast<unsigned*>(sm.bins);
   if (tid < 256) bins[tid] = 0u;
   if (tid == 0) sm.listed = 0;
-  const float lo = -block_reduce(tid < real ? -best : -INFINITY, sm.redf, OpMaxF(), -INFINITY);       // the smallest maximum
-  const float span = m - lo, c = 255.0f / span;
-  if (!(lo > -INFINITY && span > 0.0f && span < INFINITY && c < INFINITY)) return false;             // (uniform)
-  if (tid < real) atomicAdd(&bins[min(255, (int)((m - best) * c))], 1u);
+  // the bins end at the smallest maximum, or where weights are zero anyway: entries that a mask moved down (to -inf, the type's
+  // lowest value, -1e9) would leave all others in one bin (and a row of one value has a span all the same)
+  const float reach = fmaxf(105.0f / invT, 1e-4f * fabsf(m));
+  const float lo = fmaxf(-block_reduce(tid < real ? -best : -INFINITY, sm.redf, OpMaxF(), -INFINITY), m - reach);
+  const float span = fmaxf(m - lo, 1e-6f * fabsf(m) + 1e-30f), c = 255.0f / span;
+  if (!(m - m == 0.0f && span < INFINITY)) return false;                         // (uniform)
+  if (tid < real) atomicAdd(&bins[(int)fminf((m - best) * c, 255.0f)], 1u);
   __syncthreads();
   if (wave == 0) {
     unsigned own[4], sum = 0u;
@@ -396,7 +399,7 @@ __device__ __forceinline__ bool filter_fast(const float4 (&v)[SAMPLE_REG_F4], in
       const unsigned t = tau | (1u << bit);
       if (__popcll(__ballot(ok0 && k0 >= t)) + __popcll(__ballot(ok1 && k1 >= t)) >= top_k) tau = t;
     }
-    float thr = key_float(tau);
+    float thr = tau ? key_float(tau) : -INFINITY;    // (fewer listed than top_k: the others weigh nothing)
     auto weight = [&](unsigned k, bool ok) { return ok ? exp_scaled(key_float(k), m, invT, thr) : 0.0f; };
     // the sum, in whole numbers of 2^-56 (a weight is at most 1, the list holds 128): the list's order, which is how the
     // wavefronts happened to arrive, does not show in it

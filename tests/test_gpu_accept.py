@@ -145,6 +145,66 @@ def test_short_list_sums_do_not_depend_on_its_order():
         assert not n.any(), n
 
 
+def call_us(zp, zq, x, r, s, temperature, calls=10, **kw):
+    """Microseconds of one of several calls in a replayed graph, the shortest of some replays."""
+    from paper_2211_17192_amd import binding
+    rows, gamma, _ = zq.shape
+    args = [torch.from_numpy(np.ascontiguousarray(v)).cuda() for v in (zp, zq, x, r, s)]
+    scratch = binding.spec_sample_scratch(rows, gamma)
+    n, t = (torch.empty(rows, dtype=torch.int32, device="cuda") for _ in range(2))
+    one = lambda: binding.spec_sample(*args, temperature, scratch=scratch, out_n=n, out_t=t, **kw)
+    one()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for _ in range(calls):
+            one()
+    times = []
+    for _ in range(12):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        graph.replay()
+        b.record()
+        b.synchronize()
+        times.append(a.elapsed_time(b) * 1000 / calls)
+    return min(times)
+
+
+MASKS = {"inf": -np.inf, "lowest": np.finfo(np.float32).min, "1e9": -1e9}
+
+
+@pytest.mark.parametrize("mask", list(MASKS))
+@pytest.mark.parametrize("vocab,keep,top_k,top_p", [
+    (4096, 3896, 50, 0.0),         # whole threads without an entry that is not masked
+    (8192, 200, 50, 0.9),          # as many threads with one as top_k
+    (8192, 100, 50, 0.9),          # fewer, but entries enough
+    (8192, 40, 50, 0.9),           # fewer entries
+    (512, 90, 100, 0.0), (256, 200, 80, 0.5), (4096, 1, 3, 0.5),
+])
+@pytest.mark.parametrize("temperature", [1.0, 0.05])
+def test_filters_of_masked_rows(mask, vocab, keep, top_k, top_p, temperature):
+    zp, zq, _, r, s = synth.sampler_case(3, 3, vocab, 1.0, keep)
+    zp[:, :, keep:], zq[:, :, keep:] = MASKS[mask], MASKS[mask]
+    top_p = float(np.float32(top_p))
+    for z in [*zp.reshape(-1, vocab), *zq.reshape(-1, vocab)]:
+        while 0.0 < top_p and sampling.nucleus_margin(z, temperature, top_k, top_p) < 2e-6:    # (see test_filter_paths)
+            z[0] += np.float32(0.01)
+    x = np.argmax(zq, -1).astype(np.int32)
+    check(zp, zq, x, r, s, temperature, top_k, top_p)
+
+
+@pytest.mark.parametrize("mask", list(MASKS))
+def test_masked_rows_take_the_short_list_too(mask):
+    """A padded vocabulary costs no more than a full one.  (50 largest of 4096: 25 us where rows with masked entries
+    take the general search, 13 without any.)"""
+    zp, zq, x, r, s = synth.sampler_case(16, 5, 4096, 1.0, 7)
+    full = call_us(zp, zq, x, r, s, 0.8, top_k=50)
+    zp[:, :, 3896:], zq[:, :, 3896:] = MASKS[mask], MASKS[mask]
+    masked = call_us(zp, zq, np.minimum(x, 3895), r, s, 0.8, top_k=50)
+    print(mask, full, masked)
+    assert masked <= 1.15 * full
+
+
 def test_calls_of_any_size_share_one_scratch():
     from paper_2211_17192_amd import binding
     scratch = binding.spec_sample_scratch(64, 7)
