@@ -268,14 +268,11 @@ __device__ __forceinline__ bool list_search(RadixSearch& q, int bits, unsigned l
   return true;
 }
 // weight(key): an integer.  nv4: the row's float4 groups (the registers beyond hold padding).
-// Most rows are settled on a short list: a first bound (k_first > 0: the k_first-th largest of the threads'
-// own maxima, which the k_first-th largest entry cannot lie below; else the first 11 bits) leaves few
-// entries, and one wavefront finishes on those.  A row that overflows the list (ties) is
-// searched in the registers to the end.  `listed`: on entry, the list holds all entries that weigh
-// anything; on return, it holds every entry with a key >= tau.
+// Most rows are settled on a short list, by one wavefront: filter_fast's (`listed`, on entry: the list holds every entry with a
+// key >= tau, whichever tau will be), else the entries that share the first 11 bits of tau.  A row that overflows
+// the list (ties) is searched in the registers to the end.
 template <typename W>
-__device__ __forceinline__ unsigned filter_threshold(const float4 (&v)[SAMPLE_REG_F4], int nv4, unsigned long long target, int k_first,
-                                                     SampleSmem& sm, bool& listed, W&& weight) {
+__device__ __forceinline__ unsigned filter_threshold(const float4 (&v)[SAMPLE_REG_F4], int nv4, unsigned long long target, SampleSmem& sm, bool listed, W&& weight) {
   const int tid = threadIdx.x, wave = tid >> 6;
   auto in_regs = [&](auto&& f) {
 #pragma unroll
@@ -291,26 +288,7 @@ __device__ __forceinline__ unsigned filter_threshold(const float4 (&v)[SAMPLE_RE
   RadixSearch q{0u, 0ull, 0};
   bool ok = true;
   int bits = 32;
-  const bool given = listed;
-  if (given) {
-  } else if (k_first > 0) {
-    unsigned best = 0u;
-#pragma unroll
-    for (int it = 0; it < SAMPLE_REG_F4; ++it)
-      best = max(best, max(max(float_key(v[it].x), float_key(v[it].y)), max(float_key(v[it].z), float_key(v[it].w))));
-    const int real = min(nv4, SAMPLE_THREADS);       // threads with entries
-    __syncthreads();
-    if (tid < real) sm.list[tid] = best;
-    __syncthreads();
-    if (wave == 0) {
-      RadixSearch p{0u, 0ull, 0};
-      const bool found = list_search(p, 32, (unsigned long long)k_first, sm.list, real, sm, [](unsigned) { return 1ull; });
-      if (tid == 0) sm.sel = found ? p.tau : 0u;     // (fewer threads with entries than k_first: no bound)
-    }
-    __syncthreads();
-    const unsigned bound = sm.sel;
-    listed = list_entries(v, nv4, sm, [&](unsigned k) { return k >= bound; }) <= SAMPLE_LIST;
-  } else {
+  if (!listed) {
     ok = radix_step(q, target, sm, in_regs);
     if (ok) listed = list_entries(v, nv4, sm, [&](unsigned k) { return (k >> 21) == (q.tau >> 21); }) <= SAMPLE_LIST;
     bits = 21;
@@ -327,55 +305,61 @@ __device__ __forceinline__ unsigned filter_threshold(const float4 (&v)[SAMPLE_RE
     while (ok && q.step < 3) ok = radix_step(q, target, sm, in_regs);
     if (!ok) q.tau = 0u;
   }
-  if (k_first <= 0 && !given) listed = false;
   __syncthreads();
   return q.tau;
 }
 
-// The filters of a row whose top-k is small beside its length (both filters, or top-k alone), in four barriers and
-// one wavefront's work: the threads' own maxima go into 256 linear bins between the largest and the smallest of
+// Top-k: the threads' own maxima go into 256 linear bins between the largest and the smallest of
 // them; the bin that holds the top_k-th bounds the top_k-th largest entry from below, so few entries are listed
-// (top_k to a dozen more); wavefront 0 keeps them in registers, two a lane, finds the top_k-th largest key bit by bit
-// with ballots, and for the nucleus gives every entry the weight of the entries that are not below it.
-// False (in every thread): the row does not suit (ties, infinities, too many listed); nothing is settled then.
-// (16 rows x 11, vocabulary 32000, top_k 50, top_p 0.95: the searches over bins of key bits took 22.6 us, eight
-// steps of one wavefront each with every key in one or two bins of the first; now 13.6.)
+// (top_k to a dozen more).  Where they are no more than two a lane, wavefront 0 settles both filters in its
+// registers: it finds the top_k-th largest key bit by bit with ballots, and for the nucleus gives every entry the weight of
+// the entries that are not below it.
+// False (in every thread): more are listed than that, and the list is where filter_threshold goes on (`listed`), or more than the
+// list has room for (ties), or the maximum is no finite number.
+// (16 rows x 11, vocabulary 32000, top_k 50, top_p 0.95: searches over bins of key bits took 22.6 us, eight
+// steps of one wavefront each with every key in one or two bins of the first; now 13.6.  A whole call of one sequence, gamma 4,
+// with top_k 128, some 140 listed: 27.8 us with those searches, 31.5 when a list too long for registers was thrown away, now 21.4.)
 constexpr int SAMPLE_FAST_LIST = 128;
 __device__ __forceinline__ bool filter_fast(const float4 (&v)[SAMPLE_REG_F4], int nv4, float best, float m, float invT, int top_k, float top_p,
-                                            SampleSmem& sm, RowStat& st) {
+                                            SampleSmem& sm, RowStat& st, bool& listed) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, real = min(nv4, SAMPLE_THREADS);
-  if (top_k > real || top_k > SAMPLE_FAST_LIST) return false;                    // (uniform)
-  unsigned* bins = reinterpret_cast<unsigned*>(sm.bins);
-  if (tid < 256) bins[tid] = 0u;
   if (tid == 0) sm.listed = 0;
-  // the bins end at the smallest maximum, or where weights are zero anyway: entries that a mask moved down (to -inf, the type's
-  // lowest value, -1e9) would leave all others in one bin (and a row of one value has a span all the same)
-  const float reach = fmaxf(105.0f / invT, 1e-4f * fabsf(m));
-  const float lo = fmaxf(-block_reduce(tid < real ? -best : -INFINITY, sm.redf, OpMaxF(), -INFINITY), m - reach);
-  const float span = fmaxf(m - lo, 1e-6f * fabsf(m) + 1e-30f), c = 255.0f / span;
-  if (!(m - m == 0.0f && span < INFINITY)) return false;                         // (uniform)
-  if (tid < real) atomicAdd(&bins[(int)fminf((m - best) * c, 255.0f)], 1u);
-  __syncthreads();
-  if (wave == 0) {
-    unsigned own[4], sum = 0u;
+  float bound = -INFINITY;
+  if (top_k <= real) {                               // (uniform; else fewer threads with entries: no bound, everything is listed)
+    unsigned* bins = reinterpret_cast<unsigned*>(sm.bins);
+    if (tid < 256) bins[tid] = 0u;
+    // the bins end at the smallest maximum, or where weights are zero anyway: entries that a mask moved down (to -inf, the
+    // type's lowest value, -1e9) would leave all others in one bin (and a row of one value has a span all the same)
+    const float reach = fmaxf(105.0f / invT, 1e-4f * fabsf(m));
+    const float lo = fmaxf(-block_reduce(tid < real ? -best : -INFINITY, sm.redf, OpMaxF(), -INFINITY), m - reach);
+    const float span = fmaxf(m - lo, 1e-6f * fabsf(m) + 1e-30f), c = 255.0f / span;
+    if (!(m - m == 0.0f && span < INFINITY)) return false;                       // (uniform)
+    if (tid < real) atomicAdd(&bins[(int)fminf((m - best) * c, 255.0f)], 1u);
+    __syncthreads();
+    if (wave == 0) {
+      unsigned own[4], sum = 0u;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) { own[e] = bins[lane * 4 + e]; sum += own[e]; }
-    unsigned inc = sum;
+      for (int e = 0; e < 4; ++e) { own[e] = bins[lane * 4 + e]; sum += own[e]; }
+      unsigned inc = sum;
 #pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const unsigned t = __shfl_up(inc, o, WAVE);
-      if (lane >= o) inc += t;
+      for (int o = 1; o < 64; o <<= 1) {
+        const unsigned t = __shfl_up(inc, o, WAVE);
+        if (lane >= o) inc += t;
+      }
+      unsigned before = inc - sum;
+      if (before < (unsigned)top_k && inc >= (unsigned)top_k) {                  // exactly one lane
+        int e = 0;
+        while (before + own[e] < (unsigned)top_k) before += own[e++];
+        sm.sel = (unsigned)(lane * 4 + e);
+      }
     }
-    unsigned before = inc - sum;
-    if (before < (unsigned)top_k && inc >= (unsigned)top_k) {                    // exactly one lane
-      int e = 0;
-      while (before + own[e] < (unsigned)top_k) before += own[e++];
-      sm.sel = (unsigned)(lane * 4 + e);
-    }
+    __syncthreads();
+    // every entry of a bin up to that one is at least this large (rounding of either side is far below the margins)
+    bound = m - (float)(sm.sel + 1u) / c * 1.00001f - 1e-6f * fabsf(m);
+  } else {
+    if (nv4 * 4 > SAMPLE_LIST) return false;         // (uniform)
+    __syncthreads();
   }
-  __syncthreads();
-  // every entry of a bin up to that one is at least this large (rounding of either side is far below the margins)
-  const float bound = m - (float)(sm.sel + 1u) / c * 1.00001f - 1e-6f * fabsf(m);
 #pragma unroll
   for (int it = 0; it < SAMPLE_REG_F4; ++it) {
     const bool hit = !(v[it].x < bound) || !(v[it].y < bound) || !(v[it].z < bound) || !(v[it].w < bound);
@@ -385,12 +369,12 @@ __device__ __forceinline__ bool filter_fast(const float4 (&v)[SAMPLE_REG_F4], in
     for (int e = 0; e < 4; ++e)
       if (!(z[e] < bound) && it * SAMPLE_THREADS + tid < nv4) {
         const int i = atomicAdd(&sm.listed, 1);
-        if (i < SAMPLE_FAST_LIST) sm.list[i] = float_key(z[e]);
+        if (i < SAMPLE_LIST) sm.list[i] = float_key(z[e]);
       }
   }
   __syncthreads();
   const int n = sm.listed;
-  if (n > SAMPLE_FAST_LIST) return false;             // (uniform)
+  if (n > SAMPLE_FAST_LIST) { listed = n <= SAMPLE_LIST; return false; }       // (uniform)
   if (wave == 0) {
     const bool ok0 = lane < n, ok1 = lane + 64 < n;
     const unsigned k0 = ok0 ? sm.list[lane] : 0u, k1 = ok1 ? sm.list[lane + 64] : 0u;
@@ -403,11 +387,10 @@ __device__ __forceinline__ bool filter_fast(const float4 (&v)[SAMPLE_REG_F4], in
     auto weight = [&](unsigned k, bool ok) { return ok ? exp_scaled(key_float(k), m, invT, thr) : 0.0f; };
     // the sum, in whole numbers of 2^-56 (a weight is at most 1, the list holds 128): the list's order, which is how the
     // wavefronts happened to arrive, does not show in it
-    auto whole = [](float e) {
-      const unsigned b = __float_as_uint(e);
-      const int up = (int)(b >> 23) - 94;            // 1.0: 33
-      const unsigned long long man = (b & 0x7fffffu) | 0x800000u;
-      return up >= 0 ? man << (up & 63) : up >= -25 ? (man + (1ull << (-up - 1))) >> -up : 0ull;
+    auto whole = [](float e) {                       // 31 + 25 bits, to nearest
+      const float t = e * 0x1p31f;
+      const unsigned hi = (unsigned)t;
+      return ((unsigned long long)hi << 25) + (unsigned)rintf((t - (float)hi) * 0x1p25f);
     };
     auto total = [&](float a, float b) { return (double)wave_sum(whole(a) + whole(b)) * 0x1p-56; };
     float e0 = weight(k0, ok0), e1 = weight(k1, ok1);
@@ -478,10 +461,11 @@ __device__ __forceinline__ RowStat row_stats_regs(const float4 (&v)[SAMPLE_REG_F
   float thr = -INFINITY;
   const int nv4 = V >> 2;
   bool listed = false;
-  if (top_k > 0 && top_k < V && filter_fast(v, nv4, best, m, invT, top_k, top_p, sm, st)) return st;
-  if (top_k > 0 && top_k < V)
-    thr = key_float(filter_threshold(v, nv4, (unsigned long long)top_k, top_k <= SAMPLE_THREADS ? top_k : 0, sm, listed,
-                                     [](unsigned) { return 1ull; }));
+  if (top_k > 0 && top_k < V) {
+    if (filter_fast(v, nv4, best, m, invT, top_k, top_p, sm, st, listed)) return st;
+    const unsigned tau = filter_threshold(v, nv4, (unsigned long long)top_k, sm, listed, [](unsigned) { return 1ull; });
+    thr = tau ? key_float(tau) : -INFINITY;          // (fewer listed than top_k: the others weigh nothing)
+  }
   auto mass = [&] {
     float s = 0.0f;
 #pragma unroll
@@ -497,7 +481,7 @@ __device__ __forceinline__ RowStat row_stats_regs(const float4 (&v)[SAMPLE_REG_F
   if (top_p > 0.0f && top_p < 1.0f) {
     constexpr double UNIT = 17592186044416.0;        // 2^44: 32768 entries of at most 1 stay below 2^60
     const float floor_thr = thr;                     // what top-k dropped stays dropped
-    const unsigned tau = filter_threshold(v, nv4, (unsigned long long)((double)top_p * S * UNIT), 0, sm, listed, [&](unsigned k) {
+    const unsigned tau = filter_threshold(v, nv4, (unsigned long long)((double)top_p * S * UNIT), sm, listed, [&](unsigned k) {
       // e * 2^44 as 31 + 13 bits
       const float t = exp_scaled(key_float(k), m, invT, floor_thr) * 2147483648.0f;
       const unsigned hi = (unsigned)t;
