@@ -45,6 +45,8 @@ struct StepParams {
   int32_t pad;
 };
 
+constexpr int SAMPLE_TICKETS = 64;          // words of a sequence's tickets: the first is the sampling kernels', the others the attention kernel's
+
 // Eight bytes that another workgroup of the same launch reads: written through to memory, read past the caches (their
 // order is made by a wait for the stores and a ticket).
 __device__ __forceinline__ void post8(float* p, float a, float b) {

@@ -34,6 +34,7 @@ namespace sd {
 
 constexpr int ATTN_LDS_DIST = 4096;        // causal distances whose bias bucket is cached in LDS
 constexpr int ATTN_MAX_RANGES = 16;        // key ranges of a long context
+constexpr int ATTN_TICKETS = SAMPLE_TICKETS - 1, ATTN_MAX_TICKETS = 4 * ATTN_TICKETS;     // words of a sequence's tickets, and the kv heads they serve
 constexpr int ATTN_MAX_RG = 32;            // query rows x heads per kv head: two 16-row MFMA tiles; 150 KB of LDS in attn_kernel at d_head 64
 
 // LPK lanes per key and DP head-dim elements per lane in the score phase (a workgroup of THREADS
@@ -69,7 +70,7 @@ struct AttnArgs {
   int nsplit, split_keys;
   float* partial;
   // attn_mma_kernel: a ticket per (sequence, kv head), zero between launches, ticket_stride words from one sequence's
-  // to the next's (MANY: one workgroup takes the ranges in turn).  ml_off: where in dynamic LDS (in floats) the ranges' (m, l) go
+  // to the next's: byte h / ATTN_TICKETS of word h % ATTN_TICKETS (MANY: one workgroup takes the ranges in turn).  ml_off: where in dynamic LDS (in floats) the ranges' (m, l) go
   unsigned* tickets;
   int ticket_stride, ml_off;
   // when set, the output goes here in
@@ -359,9 +360,9 @@ static __global__ __launch_bounds__(THREADS) void attn_kernel(const AttnArgs a) 
 //                 B = the probabilities the lane
 //                 already holds, each as the sum of two bf16 numbers (two MFMAs).
 // The wavefronts' results are merged through LDS, in wavefront order.  Long contexts are cut into key ranges
-// (nsplit > 1) whose results are merged in range order, always the same ranges, whoever computes them: in decoding a
+// (nsplit > 1) whose results are merged in range order, always the same ranges, whoever computes them: a
 // workgroup each, the last of a (sequence, kv head) to arrive merging (`tickets`; a context within the first range is
-// written directly); for a prompt's row groups, which are many, one workgroup after the other.  A merge launch of its own
+// written directly), or, for a prompt's row groups and for hundreds of (sequence, kv head) pairs, one workgroup for all.  A merge launch of its own
 // cost 4.3 - 6.4 us a layer, 58 for 2000 prompt rows.
 // Every row's arithmetic is independent of the other rows.  MODE: causal self-attention over the paged cache, the same with
 // the relative-position bias, or cross-attention (the fixed encoder keys, no mask, no bias).
@@ -842,14 +843,15 @@ static __global__ __launch_bounds__(64 * NW, NW == 4 ? ((NRT == 1 && (DH == 64 |
       continue;
     }
   } else {
-    unsigned* ticket = a.tickets + (size_t)(a.seq0 + seq) * a.ticket_stride + hkv;
+    unsigned* ticket = a.tickets + (size_t)(a.seq0 + seq) * a.ticket_stride + hkv % ATTN_TICKETS;
+    const int field = hkv / ATTN_TICKETS * 8;        // (a byte of it; at most 16 arrivals)
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");             // this wavefront's posts have reached memory
     __syncthreads();
     if (tid == 0) {
-      const unsigned n = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const unsigned n = __hip_atomic_fetch_add(ticket, 1u << field, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >> field & 0xffu;
       const int last = n == (unsigned)n_act - 1u;
       *last_wg = last;
-      if (last) __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (last) __hip_atomic_fetch_sub(ticket, (unsigned)n_act << field, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     __syncthreads();
     if (*last_wg == 0) return;

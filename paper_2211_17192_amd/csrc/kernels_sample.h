@@ -43,7 +43,6 @@ struct RowPart {
 };
 
 // Working memory of one sequence's accept / resample call or draw; the ticket is zero between calls.
-constexpr int SAMPLE_TICKETS = 64;          // the first is the sampling kernels', the others the attention kernel's (one per kv head)
 struct SampleScratch {
   unsigned int ticket[SAMPLE_TICKETS];
   double tot[SAMPLE_MAX_CHUNKS];

@@ -566,8 +566,11 @@ void launch_attn(hipStream_t s, const Model& m, AttnArgs a, int nseq, SampleScra
     const int RG = a.rows_per_wg * G;
     const int nw = (a.nsplit > 1) ? 4 : attn_mma_waves(a.cross ? a.kv_len : (m.cfg.max_len + 1) / 2);
     if (a.pj_w != nullptr && !(a.cross && DH == 64 && RG <= 16 && G == 1)) a.pj_w = nullptr;   // (callers check; never project elsewhere)
-    // key ranges: a workgroup each, with a ticket per kv head, or one after the other (prompts; more heads than tickets)
-    const bool in_turn = a.nsplit > 1 && (prompt || a.Hkv >= SAMPLE_TICKETS);
+    // key ranges: a workgroup each, with a ticket per kv head, or one after the other (a prompt's row groups; more heads than
+    // tickets; where sequences x kv heads are two workgroups a CU by themselves).  us a layer, in turn / spread, one row, heads
+    // of 64, max_len 8192: 64 heads, one sequence of 500, 2000, 8000 keys 6.7 / 6.3, 21.1 / 12.8, 71.7 / 28.7; four sequences
+    // 9.7 / 9.6, 27.1 / 26.4, 95.9 / 99.2; 32 heads, 16 sequences 14.1 / 16.4, 49.9 / 52.3, 183.7 / 184.8.
+    const bool in_turn = a.nsplit > 1 && (prompt || a.Hkv > ATTN_MAX_TICKETS || nseq * a.Hkv >= 2 * g_num_cus);
     size_t ll = attn_mma_lds_bytes(RG, DH, nw);
     a.ml_off = (int)(ll / 4);
     ll += attn_mma_range_lds_bytes(a.nsplit);

@@ -59,10 +59,10 @@ def test_prefill_equals_token_by_token(name, scatter):
     prefill_equals_token_by_token(CASES[name], scatter)
 
 
-def prefill_equals_token_by_token(case, scatter):
+def prefill_equals_token_by_token(case, scatter, gamma=3):
     from paper_2211_17192_amd import binding
     arch, d, heads, kv, dh, ff, layers, rows, enc = case
-    gamma, vocab = 3, 512
+    vocab = 512
     kw = dict(n_kv_heads=kv) if arch == T.GQA else {}
     cfg = synth.model_cfg(arch, layers, d, heads, ff, vocab, rows + 40, d_head=dh, enc_len=enc, dtype="bf16", logit_scale=4.0, **kw)
     w = synth.random_weights(cfg, 5, "cuda", 0.04)
@@ -110,17 +110,37 @@ def test_k_slices_of_every_length_equal_the_products_over_many_rows(name):
 
 
 # Contexts over several key ranges (512 keys): decoded tokens come from ranges merged by the last workgroup to arrive, or,
-# with more KV heads than there are tickets, taken in turn; a prompt's from ranges taken in turn.
-RANGES = {
-    "gqa-1100-two-row-tiles": (T.GQA, 256, 16, 4, 128, 512, 2, 1100, 0),
-    "gpt-1060-64-heads": (T.GPT, 128, 64, 64, 64, 256, 2, 1060, 0),
-    "t5-1040-bias": (T.T5DEC, 256, 4, 4, 64, 512, 2, 1040, 20),
+# with more KV heads than there are tickets (252), taken in turn; a prompt's from ranges taken in turn.
+RANGES = {                                           # case, gamma
+    "gqa-1100": ((T.GQA, 256, 16, 4, 128, 512, 2, 1100, 0), 3),
+    "gpt-1060-64-heads": ((T.GPT, 128, 64, 64, 64, 256, 2, 1060, 0), 3),                 # heads 63 and 0 share a ticket's word
+    "gpt-1060-253-heads": ((T.GPT, 128, 253, 253, 64, 256, 2, 1060, 0), 3),
+    "t5-1040-bias": ((T.T5DEC, 256, 4, 4, 64, 512, 2, 1040, 20), 3),
 }
 
 
 @pytest.mark.parametrize("name", list(RANGES))
 def test_key_ranges_merged_by_ticket_equal_key_ranges_in_turn(name):
-    prefill_equals_token_by_token(RANGES[name], False)
+    case, gamma = RANGES[name]
+    prefill_equals_token_by_token(case, False, gamma)
+
+
+def test_decoding_with_64_kv_heads_spreads_its_key_ranges():
+    """The attention of 64 KV heads over 8000 keys reads twice what 32 read.  (3.7 times their time when each of the 64 took
+    its 16 ranges in turn.)"""
+    from paper_2211_17192_amd import binding
+    us = {}
+    for heads in (32, 64):
+        cfg = synth.model_cfg(T.GPT, 2, 128, heads, 256, 512, 8192, d_head=64, dtype="bf16", logit_scale=4.0)
+        w = synth.random_weights(cfg, 5, "cuda", 0.04)
+        cfg_q, w_q = synth.truncated_noisy_copy(cfg, w, 1, 9, 0.004)
+        dec = binding.SpecDecoder(cfg, w, cfg_q, w_q, max_gamma=4, flags=binding.SD_FLAG_GRAPH)
+        dec.prefill(synth.random_tokens(7, 8000, 512))
+        whole, rest = (min(dec.time_forward(0, 1, skip, 20) for _ in range(5)) for skip in (0, binding.SD_OP["attn"]))
+        us[heads] = (whole - rest) / 2
+        dec.close()
+    print(us)
+    assert us[64] <= 2.6 * us[32]
 
 
 # (arch, d_model, heads, kv heads, d_head, d_ff, vocab, sequences, gamma, temperature): rows = sequences x (gamma + 1)
@@ -136,8 +156,9 @@ BATCHES = {
     "gqa-16x5-split": (T.GQA, 2048, 8, 2, 128, 16384, 512, 16, 4, 1.0),
     # LM head over 144 rows: workgroups of eight wavefronts
     "gqa-16x9-head": (T.GQA, 256, 4, 4, 64, 512, 32000, 16, 8, 1.0),
+    # contexts of one and of two key ranges, which 512 workgroups take in turn and 64, alone, do not
+    "gpt-8x3-ranges": (T.GPT, 128, 64, 64, 64, 256, 512, 8, 2, 1.0),
 }
-
 
 @pytest.mark.parametrize("name", list(BATCHES))
 def test_sequences_together_equal_each_alone(name):
@@ -145,12 +166,13 @@ def test_sequences_together_equal_each_alone(name):
     arch, d, heads, kv, dh, ff, vocab, B, gamma, temperature = BATCHES[name]
     assert "head" not in name or takes_eight_wavefronts(B * (gamma + 1), vocab)
     kw = dict(n_kv_heads=kv) if arch == T.GQA else {}
-    cfg = synth.model_cfg(arch, 2, d, heads, ff, vocab, 160, d_head=dh, dtype="bf16", logit_scale=4.0, **kw)
+    max_len, more = (1100, 540) if "ranges" in name else (160, 0)
+    cfg = synth.model_cfg(arch, 2, d, heads, ff, vocab, max_len, d_head=dh, dtype="bf16", logit_scale=4.0, **kw)
     w = synth.random_weights(cfg, 5, "cuda", 0.04)
     cfg_q, w_q = synth.truncated_noisy_copy(cfg, w, 1, 9, 0.004)
     together = binding.SpecDecoder(cfg, w, cfg_q, w_q, max_gamma=gamma, flags=binding.SD_FLAG_GRAPH, batch=B)
     alone = binding.SpecDecoder(cfg, w, cfg_q, w_q, max_gamma=gamma, flags=binding.SD_FLAG_GRAPH)
-    prompts = [[int(t) for t in synth.random_tokens(40 + b, 4 + 37 * b % 50, vocab)] for b in range(B)]
+    prompts = [[int(t) for t in synth.random_tokens(40 + b, 4 + 37 * b % 50 + more * (b % 2), vocab)] for b in range(B)]
     iterations = 3
     u = synth.uniform_stream(13, iterations * B * (2 * gamma + 1)).reshape(iterations, B, 2 * gamma + 1)
     for b, p in enumerate(prompts):
