@@ -677,12 +677,15 @@ static __global__ __launch_bounds__(64 * NW, NW == 4 ? ((NRT == 1 && (DH == 64 |
     load_k(kb_next);
     pg_cur = pg[0];
     pg[0] = pgn[0]; pg[1] = pgn[1];
+    // (the next step's bias: into its own registers while this step's is in use, or behind its last use, where two
+    // row tiles of 128 features leave no room for both: 9 and 47 registers spilled, none and 5 now)
+    constexpr bool LATE_BIAS = NRT == 2 && DH == 128;
     f32x4 bias[2][NRT];
 #pragma unroll
     for (int rt = 0; rt < NRT; ++rt)
 #pragma unroll
       for (int kt = 0; kt < 2; ++kt) bias[kt][rt] = BIAS ? bz[kt][rt] : f32x4{0.f, 0.f, 0.f, 0.f};
-    load_bias(kb_next);                              // (its index clamp keeps reads past the range in bounds)
+    if (!LATE_BIAS) load_bias(kb_next);              // (its index clamp keeps reads past the range in bounds)
     float p[2][NRT][4];
     float f[NRT];
     bool rescale = false;
@@ -731,6 +734,7 @@ static __global__ __launch_bounds__(64 * NW, NW == 4 ? ((NRT == 1 && (DH == 64 |
       l_run[rt] = l_run[rt] * f[rt] + sum;          // this lane's keys only; the quarters are added at the end
       m_run[rt] = m_new;
     }
+    if (LATE_BIAS) load_bias(kb_next);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");     // this step's V tile has landed in LDS
     // ---- O^T = f O^T + V^T P;  p as the sum of two bf16 numbers (16 mantissa bits): the
     //      matrix cores have time to spare ----
@@ -775,16 +779,21 @@ static __global__ __launch_bounds__(64 * NW, NW == 4 ? ((NRT == 1 && (DH == 64 |
 
   // ---- merge the wavefronts: each leaves (m, l, O) of its keys in LDS, rows of DH + 4 ----
   __syncthreads();                                  // staging region no longer in use
+  int tm = tid, jm = j, km = kq;
+  if (in_turn) {                                    // (or the merge's addresses would take registers in the key loop)
+    asm volatile("" : "+v"(tm));
+    jm = tm & 15; km = (tm & 63) >> 4;
+  }
   float* mg = lds + (size_t)wave * RG * (DH + 4);
 #pragma unroll
   for (int rt = 0; rt < NRT; ++rt) {
     float l = lane_combine<16>(l_run[rt], OpSumF());
     l = lane_combine<32>(l, OpSumF());
-    const int rg = rt * 16 + j;
+    const int rg = rt * 16 + jm;
     if (rg < RG) {
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt) *reinterpret_cast<f32x4*>(mg + rg * (DH + 4) + dt * 16 + kq * 4) = o[dt][rt];
-      if (kq == 0) *reinterpret_cast<float2*>(mg + rg * (DH + 4) + DH) = make_float2(m_run[rt], l);
+      for (int dt = 0; dt < DT; ++dt) *reinterpret_cast<f32x4*>(mg + rg * (DH + 4) + dt * 16 + km * 4) = o[dt][rt];
+      if (km == 0) *reinterpret_cast<float2*>(mg + rg * (DH + 4) + DH) = make_float2(m_run[rt], l);
     }
   }
   __syncthreads();
@@ -801,7 +810,7 @@ static __global__ __launch_bounds__(64 * NW, NW == 4 ? ((NRT == 1 && (DH == 64 |
                                                            : static_cast<bf16*>(a.out) + (size_t)(r0 + rr) * a.H * DH + (size_t)(hkv * G + gg) * DH + d;
     *reinterpret_cast<bf16x4*>(to) = res;
   };
-  for (int i = tid; i < RG * D4; i += 64 * NW) {
+  for (int i = tm; i < RG * D4; i += 64 * NW) {
     const int rg = i / D4, d = (i % D4) * 4;
     float mw[NW], lw[NW], m = -INFINITY, L = 0.0f;
     f32x4 ow[NW], acc = {0.f, 0.f, 0.f, 0.f};

@@ -3,6 +3,9 @@
 import ctypes
 import os
 import re
+import struct
+
+import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -19,6 +22,28 @@ def test_library_exports_every_declared_symbol():
     lib = ctypes.CDLL(lib_path)
     for n in sorted(names):
         assert hasattr(lib, n), n
+
+
+def kernels_of_the_library():
+    """name -> what the compiler notes of each kernel of the built library (its code object's metadata)."""
+    msgpack = pytest.importorskip("msgpack")
+    with open(os.path.join(ROOT, "paper_2211_17192_amd", "libsd.so"), "rb") as f:
+        data = f.read()
+    out, at = {}, data.find(b"AMDGPU\0\0")
+    while at >= 0:
+        namesz, descsz, kind = struct.unpack("<III", data[at - 12:at])
+        if (namesz, kind) == (7, 32):
+            out.update((k[".name"], k) for k in msgpack.unpackb(data[at + 8:at + 8 + descsz], strict_map_key=False)["amdhsa.kernels"])
+        at = data.find(b"AMDGPU\0\0", at + 8)
+    assert len(out) > 100
+    return out
+
+
+def test_attention_kernels_keep_their_registers():
+    """What the matrix-core attention kernels put into scratch lies outside their key loops: a handful of registers.  (47 with
+    position bias, heads of 128 and two row tiles, where two steps' biases were held at once.)"""
+    spilled = {n: k[".vgpr_spill_count"] for n, k in kernels_of_the_library().items() if "attn_mma_kernel" in n}
+    assert len(spilled) > 20 and max(spilled.values()) <= 8, {n: v for n, v in spilled.items() if v > 8}
 
 
 def test_workspace_sizing_needs_no_gpu():

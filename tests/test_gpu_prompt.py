@@ -116,6 +116,7 @@ RANGES = {                                           # case, gamma
     "gpt-1060-64-heads": ((T.GPT, 128, 64, 64, 64, 256, 2, 1060, 0), 3),                 # heads 63 and 0 share a ticket's word
     "gpt-1060-253-heads": ((T.GPT, 128, 253, 253, 64, 256, 2, 1060, 0), 3),
     "t5-1040-bias": ((T.T5DEC, 256, 4, 4, 64, 512, 2, 1040, 20), 3),
+    "t5-1100-bias-dh128": ((T.T5DEC, 256, 4, 4, 128, 512, 2, 1100, 20), 3),
 }
 
 
