@@ -238,12 +238,12 @@ def _tensor_array(w: dict, keep: list):
 class SpecDecoder:
     """One (Mp, Mq) pair bound with sd_load_models.  Weights are dicts name -> cuda tensor."""
 
-    MAX_PINNED = 8
+    MAX_PINNED, MAX_PINNED_BYTES = 8, 128 << 20      # logits() arrays alive in pinned memory, and what they take of it
 
     def __init__(self, cfg_p: dict, w_p: dict, cfg_q: dict, w_q: dict, max_gamma: int = 7,
                  page_size: int = 16, flags: int = 0, batch: int = 1):
         self._ctx = C.c_void_p()
-        self._pinned = []                             # the arrays logits() gave out in pinned memory, while they live
+        self._pinned = []                             # (array, bytes) that logits() gave out in pinned memory, while they live
         self.cfg_p, self.cfg_q = cfg_p, cfg_q
         self.batch = int(batch)
         cp, cq = _cfg_struct(cfg_p), _cfg_struct(cfg_q)
@@ -308,13 +308,15 @@ class SpecDecoder:
     def _host_array(self, n: int) -> np.ndarray:
         """A new float32 array for n values on their way from the GPU, in pinned memory: the copy goes there
         directly instead of through the runtime's staging buffers (2 MB: 47 us against 130, 0.5 MB: 19 against 30).
-        Torch's pinned allocator hands blocks of dead arrays out again.  A caller that holds on to more than
-        MAX_PINNED arrays gets ordinary memory for the others, so that what it collects is not all pinned."""
-        self._pinned = [r for r in self._pinned if r() is not None]
-        if len(self._pinned) >= self.MAX_PINNED:
+        Torch's pinned allocator takes blocks of a power of two and hands those of dead arrays out again, but does not give
+        them back.  A caller that holds on to more than MAX_PINNED arrays or MAX_PINNED_BYTES gets ordinary memory for the
+        others, so that what it collects is not all pinned."""
+        self._pinned = [(r, size) for r, size in self._pinned if r() is not None]
+        block = 1 << max(4 * n - 1, 0).bit_length()
+        if len(self._pinned) >= self.MAX_PINNED or block + sum(size for _, size in self._pinned) > self.MAX_PINNED_BYTES:
             return np.empty(n, dtype=np.float32)
         out = torch.empty(n, dtype=torch.float32, pin_memory=True).numpy()
-        self._pinned.append(weakref.ref(out))          # (views of it keep it alive)
+        self._pinned.append((weakref.ref(out), block))  # (views of it keep it alive)
         return out
 
     def logits(self, which: int, rows: int) -> np.ndarray:

@@ -98,3 +98,29 @@ def test_bench_refuses_more_than_one_gpu_and_unknown_workloads():
     assert r.returncode != 0 and "one GPU" in (r.stderr + r.stdout)
     r = subprocess.run([sys.executable, os.path.join(root, "bench.py"), "--workload", "nope"], capture_output=True, text=True, timeout=120)
     assert r.returncode != 0 and "invalid choice" in r.stderr
+
+
+def decoder_without_a_gpu(monkeypatch, pinned):
+    """A SpecDecoder that hands out host arrays; pinned(n) stands for the allocation of n values in pinned memory."""
+    from paper_2211_17192_amd import binding
+    empty = binding.torch.empty
+    monkeypatch.setattr(binding.torch, "empty", lambda n, pin_memory=False, **kw: pinned(n) if pin_memory else empty(n, **kw))
+    dec = object.__new__(binding.SpecDecoder)
+    dec._ctx, dec._pinned = ctypes.c_void_p(), []
+    return dec
+
+
+def test_pinned_host_arrays_are_bounded_in_bytes(monkeypatch):
+    import torch
+    taken, zeros = [], torch.zeros
+    dec = decoder_without_a_gpu(monkeypatch, lambda n: taken.append(n) or zeros(n))
+    n = 64 * 8 * 32000                                # 64 sequences' logits at gamma 7: 66 MB
+    held = [dec._host_array(n) for _ in range(8)]
+    assert all(x.shape == (n,) and x.dtype.name == "float32" for x in held)
+    assert taken and 4 * sum(taken) <= 128 << 20
+    before = len(taken)
+    held.clear()                                      # dead arrays no longer count
+    held.append(dec._host_array(n))
+    assert len(taken) == before + 1
+    assert dec._host_array(8 * n).shape == (8 * n,) and len(taken) == before + 1
+    assert dec._host_array(0).shape == (0,)
