@@ -310,12 +310,15 @@ class SpecDecoder:
         directly instead of through the runtime's staging buffers (2 MB: 47 us against 130, 0.5 MB: 19 against 30).
         Torch's pinned allocator takes blocks of a power of two and hands those of dead arrays out again, but does not give
         them back.  A caller that holds on to more than MAX_PINNED arrays or MAX_PINNED_BYTES gets ordinary memory for the
-        others, so that what it collects is not all pinned."""
+        others, so that what it collects is not all pinned; so does everyone where no pinned memory is to be had."""
         self._pinned = [(r, size) for r, size in self._pinned if r() is not None]
         block = 1 << max(4 * n - 1, 0).bit_length()
         if len(self._pinned) >= self.MAX_PINNED or block + sum(size for _, size in self._pinned) > self.MAX_PINNED_BYTES:
             return np.empty(n, dtype=np.float32)
-        out = torch.empty(n, dtype=torch.float32, pin_memory=True).numpy()
+        try:
+            out = torch.empty(n, dtype=torch.float32, pin_memory=True).numpy()
+        except RuntimeError:
+            return np.empty(n, dtype=np.float32)
         self._pinned.append((weakref.ref(out), block))  # (views of it keep it alive)
         return out
 

@@ -124,3 +124,12 @@ def test_pinned_host_arrays_are_bounded_in_bytes(monkeypatch):
     assert len(taken) == before + 1
     assert dec._host_array(8 * n).shape == (8 * n,) and len(taken) == before + 1
     assert dec._host_array(0).shape == (0,)
+
+
+def test_host_arrays_without_pinned_memory(monkeypatch):
+    def none_left(n):
+        raise RuntimeError("HIP error: out of memory")
+    dec = decoder_without_a_gpu(monkeypatch, none_left)
+    a = dec._host_array(1000)
+    a[:] = 1.0
+    assert a.shape == (1000,) and a.dtype.name == "float32" and not dec._pinned
