@@ -5,13 +5,12 @@
 // QKV projection just before) or to a fixed block of encoder keys
 // (cross-attention).
 //
+// bf16 with heads of 64 or 128: attn_mma_kernel, further down.  fp32, and heads of 32: attn_kernel.
 // One workgroup of 256, 512 or 1024 threads owns one kv head (and a few of the query rows:
 // rows are independent, so splitting them needs no merge) and walks its keys in blocks
 // (one key per 2 threads, per 4 for d_head 128) with an online softmax (running max m,
-// denominator l, unnormalised output O per row).  There is no split over
-// workgroups and therefore no cross-workgroup merge: device-scope atomics cost
-// about a quarter of a microsecond each on this chip when they queue on one
-// address, which is more than the whole kernel should take.  The kernel is
+// denominator l, unnormalised output O per row).  Only contexts of more than 1024 positions
+// are split over workgroups, with a launch that merges.  The kernel is
 // latency-bound, so every thread issues all its K and V loads of a key block
 // up front with 16-byte loads and no branches (they do not depend on the
 // scores), and the rest runs out of registers and LDS:
@@ -58,12 +57,12 @@ struct AttnArgs {
   int R, H, Hkv;
   int G, g_mul;             // query heads per kv head; 65536 / G + 1: x / G == (x * g_mul) >> 16 for x < 1024
   int rows_per_wg;          // row groups = ceil(R / rows_per_wg): rows are independent, no merge needed
-  int groups;               // attn_mma_kernel: their number (grid.z = key ranges x row groups)
-  // several sequences in one launch: grid.z = sequences, R rows each, one after the other
+  int groups;               // their number
+  // several sequences in one launch: R rows each, one after the other
   // (sequence z: rows z * R ..); sequence z uses the page table at page_table + (seq0 + z) * pt_stride
   int seq0, pt_stride;
   // long contexts: the keys of a (sequence, kv head) are cut into nsplit ranges of split_keys keys
-  // (a multiple of the key block) that different workgroups take (grid.y = row groups x nsplit);
+  // (a multiple of the key block) that different workgroups take, or (launch_attn's in_turn) one after the other;
   // each leaves its running maximum, denominator and unnormalised output in `partial`
   // ([sequence][row group][kv head][split][ATTN_MAX_RG][d_head + 2] floats); attn_mma_kernel combines them itself,
   // attn_merge_kernel does it for attn_kernel.  nsplit is fixed per model (from max_len), so the split never depends on the other rows.
@@ -127,9 +126,9 @@ static __global__ __launch_bounds__(THREADS) void attn_kernel(const AttnArgs a) 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int hkv = blockIdx.x;
-  // rows are independent: blockIdx.y takes rows [r0, r0 + R) of the launch
-  const int split = (a.nsplit > 1) ? (int)blockIdx.y % a.nsplit : 0;
-  const int rs = ((a.nsplit > 1) ? (int)blockIdx.y / a.nsplit : (int)blockIdx.y) * a.rows_per_wg;   // first row within the sequence
+  // blockIdx.y: a key range of all rows, or, as rows are independent, the rows [r0, r0 + R) of the launch
+  const int split = (a.nsplit > 1) ? (int)blockIdx.y : 0;
+  const int rs = (a.nsplit > 1) ? 0 : (int)blockIdx.y * a.rows_per_wg;            // first row within the sequence
   const int R = min(a.rows_per_wg, a.R - rs);
   const int r0 = (int)blockIdx.z * a.R + rs;      // first row within the launch
   const int* page_table = a.page_table + (size_t)(a.seq0 + blockIdx.z) * a.pt_stride;
@@ -934,9 +933,7 @@ template <typename T, int DH>
 static __global__ __launch_bounds__(DH) void attn_merge_kernel(const AttnArgs a) {
   const int hkv = blockIdx.x, G = a.H / a.Hkv, rg = blockIdx.y, d = threadIdx.x;
   const int r_base = (int)blockIdx.z * a.R;
-  int grp = 0, rgl = rg;
-  if (a.groups > 1) { grp = rg / (a.rows_per_wg * G); rgl = rg - grp * a.rows_per_wg * G; }
-  const float* pp = a.partial + (((((size_t)blockIdx.z * a.groups + grp) * a.Hkv + hkv) * a.nsplit) * ATTN_MAX_RG + rgl) * (DH + 2);
+  const float* pp = a.partial + ((((size_t)blockIdx.z * a.Hkv + hkv) * a.nsplit) * ATTN_MAX_RG + rg) * (DH + 2);
   const size_t stride = (size_t)ATTN_MAX_RG * (DH + 2);
   float m = -INFINITY;
   for (int sp = 0; sp < a.nsplit; ++sp) m = fmaxf(m, pp[sp * stride + DH]);

@@ -528,8 +528,12 @@ void launch_attn_mma(hipStream_t s, const AttnArgs& a, dim3 grid, int nw, size_t
         hipLaunchKernelGGL((attn_mma_kernel<DH, NRT, NW_, MODE_, ATTN_MANY_RANGES>), grid, dim3(64 * NW_), lds, s, a);  \
         return;                                                                                                         \
       }                                                                                                                 \
-    if (many) hipLaunchKernelGGL((attn_mma_kernel<DH, NRT, NW_, MODE_, ATTN_MANY>), grid, dim3(64 * NW_), lds, s, a);   \
-    else hipLaunchKernelGGL((attn_mma_kernel<DH, NRT, NW_, MODE_, ATTN_FEW>), grid, dim3(64 * NW_), lds, s, a);         \
+    if constexpr (NRT == 1 || MODE_ == ATTN_SELF)       /* (else a query head per KV head: 16 rows are one tile) */     \
+      if (!many) {                                                                                                      \
+        hipLaunchKernelGGL((attn_mma_kernel<DH, NRT, NW_, MODE_, ATTN_FEW>), grid, dim3(64 * NW_), lds, s, a);          \
+        return;                                                                                                         \
+      }                                                                                                                 \
+    hipLaunchKernelGGL((attn_mma_kernel<DH, NRT, NW_, MODE_, ATTN_MANY>), grid, dim3(64 * NW_), lds, s, a);             \
     return;                                                                                                             \
   }
   SD_MMA(4, ATTN_SELF) SD_MMA(4, ATTN_SELF_BIAS) SD_MMA(4, ATTN_CROSS)
@@ -553,16 +557,9 @@ void launch_attn(hipStream_t s, const Model& m, AttnArgs a, int nseq, SampleScra
   else { a.nsplit = m.attn_nsplit; a.split_keys = m.attn_split_keys; a.partial = m.attn_partial; }
   if (a.nsplit > 1 && !prompt) a.rows_per_wg = a.R;          // the key ranges already spread the work
   a.groups = (a.R + a.rows_per_wg - 1) / a.rows_per_wg;
-  // The workgroup is sized for the context: all of the encoder's keys in one block for cross-attention,
-  // half of max_len for self-attention (a sequence that grows to max_len spends half its life below
-  // that; longer contexts take more blocks).  Fixed per model, so every forward of a model, plain or
-  // (gamma+1)-row, adds a row's keys in the same order.
-  const int threads = a.cross ? attn_threads(DH, a.kv_len) : (a.nsplit > 1 ? 1024 : attn_threads(DH, (m.cfg.max_len + 1) / 2));
-  const size_t lds = attn_lds_bytes(a.rows_per_wg * G, DH, threads);
-  const dim3 grid(a.Hkv, a.groups * a.nsplit, nseq);
   // bf16 with d_head 64 or 128: the matrix-core kernel (key ranges: four wavefronts per range, as
   // the ranges already spread the work)
-  if (std::is_same<T, bf16>::value && (DH == 64 || DH == 128)) {
+  if (std::is_same<T, bf16>::value && DH != 32) {
     const int RG = a.rows_per_wg * G;
     const int nw = (a.nsplit > 1) ? 4 : attn_mma_waves(a.cross ? a.kv_len : (m.cfg.max_len + 1) / 2);
     if (a.pj_w != nullptr && !(a.cross && DH == 64 && RG <= 16 && G == 1)) a.pj_w = nullptr;   // (callers check; never project elsewhere)
@@ -586,14 +583,22 @@ void launch_attn(hipStream_t s, const Model& m, AttnArgs a, int nseq, SampleScra
     else launch_attn_mma<128, 2>(s, a, lg, nw, ll, in_turn);
     return;
   }
-  if (DH == 32) launch_attn_kernel<T, 32>(s, a, grid, threads, lds);
-  else if (DH == 64) launch_attn_kernel<T, 64>(s, a, grid, threads, lds);
-  else launch_attn_kernel<T, 128>(s, a, grid, threads, lds);
-  if (a.nsplit > 1) {
-    const dim3 mg(a.Hkv, a.R * G, nseq);
-    if (DH == 32) hipLaunchKernelGGL((attn_merge_kernel<T, 32>), mg, dim3(32), 0, s, a);
-    else if (DH == 64) hipLaunchKernelGGL((attn_merge_kernel<T, 64>), mg, dim3(64), 0, s, a);
-    else hipLaunchKernelGGL((attn_merge_kernel<T, 128>), mg, dim3(128), 0, s, a);
+  // The workgroup is sized for the context: all of the encoder's keys in one block for cross-attention,
+  // half of max_len for self-attention (a sequence that grows to max_len spends half its life below
+  // that; longer contexts take more blocks).  Fixed per model, so every forward of a model, plain or
+  // (gamma+1)-row, adds a row's keys in the same order.
+  const int threads = a.cross ? attn_threads(DH, a.kv_len) : (a.nsplit > 1 ? 1024 : attn_threads(DH, (m.cfg.max_len + 1) / 2));
+  const size_t lds = attn_lds_bytes(a.rows_per_wg * G, DH, threads);
+  const dim3 grid(a.Hkv, a.groups * a.nsplit, nseq);
+  auto launch = [&](auto dh) {
+    constexpr int D = decltype(dh)::value;
+    launch_attn_kernel<T, D>(s, a, grid, threads, lds);
+    if (a.nsplit > 1) hipLaunchKernelGGL((attn_merge_kernel<T, D>), dim3(a.Hkv, a.R * G, nseq), dim3(D), 0, s, a);
+  };
+  if (DH == 32) launch(std::integral_constant<int, 32>());
+  else if constexpr (std::is_same<T, float>::value) {
+    if (DH == 64) launch(std::integral_constant<int, 64>());
+    else launch(std::integral_constant<int, 128>());
   }
 }
 
@@ -623,8 +628,9 @@ hipError_t allow_mma_lds() {
   const size_t bytes = attn_mma_lds_bytes(NRT == 1 ? 16 : ATTN_MAX_RG, DH, NW) + attn_mma_range_lds_bytes(ATTN_MAX_RANGES);
   static_assert(attn_mma_lds_bytes(ATTN_MAX_RG, 128, 8) + attn_mma_range_lds_bytes(ATTN_MAX_RANGES) + 16 <= LDS_PER_CU, "matrix-core attention: LDS budget");
   if (bytes <= 64 * 1024) return hipSuccess;
-  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_mma_kernel<DH, NRT, NW, MODE, ATTN_FEW>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-  if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_mma_kernel<DH, NRT, NW, MODE, ATTN_MANY>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_mma_kernel<DH, NRT, NW, MODE, ATTN_MANY>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+  if constexpr (NRT == 1 || MODE == ATTN_SELF)
+    if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_mma_kernel<DH, NRT, NW, MODE, ATTN_FEW>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
   if constexpr (NW == 4 && MODE != ATTN_CROSS)
     if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&attn_mma_kernel<DH, NRT, NW, MODE, ATTN_MANY_RANGES>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
   return e;
@@ -647,10 +653,13 @@ hipError_t allow_mma_lds_dh() {
 template <typename T>
 hipError_t allow_big_lds() {
   hipError_t e = allow_attn_lds<T, 32>();
-  if (e == hipSuccess) e = allow_attn_lds<T, 64>();
-  if (e == hipSuccess) e = allow_attn_lds<T, 128>();
-  if (e == hipSuccess) e = allow_mma_lds_dh<64>();
-  if (e == hipSuccess) e = allow_mma_lds_dh<128>();
+  if constexpr (std::is_same<T, float>::value) {
+    if (e == hipSuccess) e = allow_attn_lds<T, 64>();
+    if (e == hipSuccess) e = allow_attn_lds<T, 128>();
+  } else {
+    if (e == hipSuccess) e = allow_mma_lds_dh<64>();
+    if (e == hipSuccess) e = allow_mma_lds_dh<128>();
+  }
   return e;
 }
 

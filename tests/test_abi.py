@@ -46,6 +46,15 @@ def test_attention_kernels_keep_their_registers():
     assert len(spilled) > 20 and max(spilled.values()) <= 8, {n: v for n, v in spilled.items() if v > 8}
 
 
+def test_no_attention_kernel_is_built_that_nothing_launches():
+    """bf16 heads of 64 and 128 have the matrix-core kernel, which merges its key ranges itself; two row tiles of a decoding
+    forward need several query heads per KV head, which models with position bias or cross-attention do not have."""
+    names = list(kernels_of_the_library())
+    assert any("attn_kernelIDF16bLi32E" in n for n in names) and any("attn_kernelIfLi128E" in n for n in names)
+    assert not [n for n in names if re.search(r"attn_(merge_)?kernelIDF16bLi(64|128)E", n)]
+    assert not [n for n in names if re.search(r"attn_mma_kernelILi\d+ELi2ELi\dELi[12]ELi0E", n)]
+
+
 def test_workspace_sizing_needs_no_gpu():
     from paper_2211_17192_amd import binding, synth
     cfg_p, _, cfg_q, _ = synth.tiny_pair()
