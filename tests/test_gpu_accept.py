@@ -95,19 +95,43 @@ def test_filter_paths(kind, vocab, top_k, top_p):
     check(zp, zq, x, r, s, 1.0, top_k, top_p)
 
 
-@pytest.mark.parametrize("kind,vocab,top_k,top_p", [
-    ("normal", 32768, 50, 0.0), ("normal", 32000, 50, 0.95), ("normal", 8192, 1, 0.5), ("normal", 4100, 64, 0.999),
-    ("normal", 32768, 110, 0.9),   # two keys a lane
-    ("normal", 32768, 128, 0.0),   # about as many as the list holds: some rows go on, some take the general search
-    ("normal", 512, 100, 0.9), ("normal", 512, 128, 0.3),                        # as many threads with entries as top_k, and fewer than a wavefront of lists
-    ("normal", 32768, 200, 0.95), ("normal", 16384, 1024, 0.9), ("normal", 8192, 1025, 0.0),       # more listed than that: up to as many as threads, beyond
-    ("normal", 2000, 600, 0.5), ("normal", 3000, 800, 0.9),                      # more than threads with entries: all listed, no room for all
-    ("levels", 8192, 20, 0.8),     # ties with the last kept entry, in and out of the list's room
-    ("two", 16384, 30, 0.6),       # two values only: the bins' ends
-    ("lowest", 16384, 50, 0.9),    # most entries the type's lowest value
-    ("peak", 32768, 50, 0.9),      # one entry far above the others: all maxima but one in the last bin
+def listed(z, top_k, temperature):
+    """How many entries of a row the top-k filter puts on its list: all that reach the bin of the top_k-th largest of the
+    threads' maxima (thread t holds the groups of four t, t + 1024, ..), 256 bins down to the smallest maximum or to
+    where weights are zero."""
+    one = np.float32
+    groups = z.reshape(-1, 4).max(-1)
+    best = np.full(1024 * 8, -np.inf, np.float32)
+    best[:len(groups)] = groups
+    best = best.reshape(8, 1024).max(0)[:min(len(groups), 1024)]
+    if top_k > len(best):
+        return len(z)
+    m = best.max()
+    lo = max(best.min(), m - max(one(105) * one(temperature), one(1e-4) * abs(m)))
+    c = one(255) / max(m - lo, one(1e-6) * abs(m) + one(1e-30))
+    with np.errstate(over="ignore"):
+        bins = np.minimum((m - best) * c, one(255)).astype(np.int64)
+    bound = m - one(np.sort(bins)[top_k - 1] + 1) / c * one(1.00001) - one(1e-6) * abs(m)
+    return int((z >= bound).sum())
+
+
+# the list is settled in a wavefront's registers (up to 128 entries), searched (up to 2048) or has no room for all
+SETTLED, SEARCHED, FULL = (1, 128), (129, 2048), (2049, 32768)
+
+
+@pytest.mark.parametrize("kind,vocab,top_k,top_p,where", [
+    ("normal", 32768, 50, 0.0, SETTLED), ("normal", 32000, 50, 0.95, SETTLED), ("normal", 8192, 1, 0.5, SETTLED), ("normal", 4100, 64, 0.999, SETTLED),
+    ("normal", 32768, 110, 0.9, SETTLED),            # two keys a lane
+    ("normal", 32768, 128, 0.0, SEARCHED), ("normal", 32768, 200, 0.95, SEARCHED),
+    ("normal", 512, 100, 0.9, SEARCHED), ("normal", 512, 128, 0.3, SEARCHED),    # up to as many of top_k as threads with entries
+    ("normal", 16384, 1024, 0.9, FULL),
+    ("normal", 2000, 600, 0.5, SEARCHED), ("normal", 3000, 800, 0.9, FULL), ("normal", 8192, 1025, 0.0, FULL),       # more: all entries are listed, no room for all
+    ("levels", 8192, 20, 0.8, SETTLED),              # ties with the last kept entry
+    ("two", 16384, 30, 0.6, None),                   # two values only, the upper one up to a few dozen times: the bins' ends
+    ("lowest", 16384, 50, 0.9, SETTLED),             # most entries the type's lowest value
+    ("peak", 32768, 50, 0.9, SETTLED),               # one entry far above the others
 ])
-def test_filter_on_a_short_list(kind, vocab, top_k, top_p):
+def test_filter_on_a_short_list(kind, vocab, top_k, top_p, where):
     zp, zq, _, r, s = synth.sampler_case(4, 3, vocab, 1.0, 23)
     if kind == "levels":
         zp, zq = np.round(zp * 8) / 8, np.round(zq * 8) / 8
@@ -125,6 +149,8 @@ def test_filter_on_a_short_list(kind, vocab, top_k, top_p):
             while sampling.nucleus_margin(z, 1.0, top_k, top_p) < 2e-6:          # (see above)
                 z[0] += np.float32(0.01)
     x = np.argmax(zq, -1).astype(np.int32)
+    n = [listed(z, top_k, 1.0) for z in [*zp.reshape(-1, vocab), *zq.reshape(-1, vocab)]]
+    assert where is None or (where[0] <= min(n) and max(n) <= where[1]), (min(n), max(n))
     check(zp, zq, x, r, s, 1.0, top_k, top_p)
 
 

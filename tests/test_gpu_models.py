@@ -780,7 +780,7 @@ def test_fp32_long_context_with_the_most_rows_per_kv_head():
 @pytest.mark.parametrize("arch", [T.GPT, T.GQA])
 def test_fp32_products_over_several_chunks_of_k(arch):
     """fp32 models whose K-slices take several chunks of four k-steps: 5 (the last chunk of one), 8 and, with eight
-    wavefronts, 9 k-steps; one sequence and two in one slab, against the oracle."""
+    wavefronts, 9 k-steps; one sequence against the oracle, two of different length in one slab against each alone."""
     cfg = synth.model_cfg(arch, 2, 576, 16, 2080, 512, 64, d_head=64, dtype="f32", logit_scale=4.0, **(dict(n_kv_heads=8) if arch == T.GQA else {}))
     w = synth.random_weights(cfg, 9, w_std=0.05)
     cfg_q, w_q = synth.truncated_noisy_copy(cfg, w, 1, 59, 0.02)
@@ -791,7 +791,20 @@ def test_fp32_products_over_several_chunks_of_k(arch):
     _, tol, worst, _ = run_pair(dec, sp, sq, prompt, 8, 3, 1.0, 44, "f32", False)
     print(f"fp32, several chunks: worst logit error {worst}, tolerated {tol}")
     assert tol["accept"] + tol["draw"] <= 1
+    two = make_decoder(cfg, w, cfg_q, w_q, max_gamma=3, flags=1, batch=2)
+    prompts = [prompt, synth.random_tokens(75, 30, cfg["vocab"])]
+    u = synth.uniform_stream(45, 3 * 2 * 7).reshape(3, 2, 7)
+    for b, p in enumerate(prompts):
+        two.prefill(p, row=b)
+    together = [(two.step(3, 1.0, u[it]), two.logits(0, 8).copy(), two.logits(1, 6).copy()) for it in range(3)]
+    for b, p in enumerate(prompts):
+        dec.reset()
+        dec.prefill(p)
+        for it, (res, zp, zq) in enumerate(together):
+            assert dec.step(3, 1.0, u[it, b]) == res[b], (it, b)
+            assert np.array_equal(dec.logits(0, 4), zp[4 * b:4 * b + 4]) and np.array_equal(dec.logits(1, 3), zq[3 * b:3 * b + 3]), (it, b)
     dec.close()
+    two.close()
 
 
 def test_logits_are_arrays_of_their_own():

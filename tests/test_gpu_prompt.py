@@ -112,7 +112,9 @@ def test_k_slices_of_every_length_equal_the_products_over_many_rows(name):
 # Contexts over several key ranges (512 keys): decoded tokens come from ranges merged by the last workgroup to arrive, or,
 # with more KV heads than there are tickets (252), taken in turn; a prompt's from ranges taken in turn.
 RANGES = {                                           # case, gamma
-    "gqa-1100": ((T.GQA, 256, 16, 4, 128, 512, 2, 1100, 0), 3),
+    "gqa-1100-two-row-tiles": ((T.GQA, 256, 16, 4, 128, 512, 2, 1100, 0), 7),            # (eight rows of four heads)
+    "gqa-2700-six-ranges": ((T.GQA, 256, 16, 4, 128, 512, 2, 2700, 0), 7),               # two row tiles of 128 features: four ranges are merged at a time,
+    "gqa-4700-ten-ranges": ((T.GQA, 128, 4, 2, 64, 256, 2, 4700, 0), 3),                 # else eight
     "gpt-1060-64-heads": ((T.GPT, 128, 64, 64, 64, 256, 2, 1060, 0), 3),                 # heads 63 and 0 share a ticket's word
     "gpt-1060-253-heads": ((T.GPT, 128, 253, 253, 64, 256, 2, 1060, 0), 3),
     "t5-1040-bias": ((T.T5DEC, 256, 4, 4, 64, 512, 2, 1040, 20), 3),
