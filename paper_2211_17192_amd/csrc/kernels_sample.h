@@ -9,7 +9,7 @@
 //   S = sum_k e_k (fp64),  prob_k = e_k * (1/S) (fp64).
 // Sums and cumulative sums are carried in fp64, so the blocked summation order
 // differs from a sequential one only far below the resolution of the uniforms.  (S of a row
-// that top-k / nucleus filter: a thread's up to 32 entries in fp32 first.)
+// that top-k / nucleus filter: whole numbers where its list is short, else a thread's up to 32 entries in fp32 first.)
 // T == 0 uses integer argmax compares (ties to the lowest index).
 #pragma once
 #include <limits.h>
@@ -1056,8 +1056,9 @@ __device__ __forceinline__ void reduce_part(const AcceptArgs& a, int b, int j, i
 }
 
 // Bound by the reads.  A wavefront takes every (grid x 4)-th part of the launch (part fastest, then row, then
-// sequence) and asks for the next one's 4 KB before it sums this one, so the loads never stop; no
-// barrier, no other wavefront is needed.  A part's sum is relative to the part's maximum; the parts of a
+// sequence) and asks for the next one's 4 KB before it sums this one; no
+// barrier, no other wavefront is needed.  (They do not stay in flight: that load, and the temperature's in
+// reduce_part, lie behind branches, where the compiler waits for everything outstanding.)  A part's sum is relative to the part's maximum; the parts of a
 // row are brought to the row's by one factor each.
 // grid = enough workgroups for one part a wavefront, at most ACCEPT_WAVES_CU wavefronts a CU.
 constexpr int ACCEPT_WAVES_CU = 24;
@@ -1220,7 +1221,7 @@ static __global__ __launch_bounds__(256, 6) void beta_kernel(const AcceptArgs a)
 // them); the last to arrive scans the totals and walks the chunk that holds u * total.
 // A small call is this one launch (OWN, launch_accept): a second one would cost it more than its work.
 // 64 sequences, gamma 7, vocabulary 32128 (123 MB), both launches, calls back to back in a graph: 35.7 us
-// (row_parts_kernel 22: 5.6 TB/s, a pure read's rate at this size); with one 1024-thread workgroup per row and
+// (row_parts_kernel 24.5 to 27: 4.6 to 5 TB/s, where a pure read reaches 7); with one 1024-thread workgroup per row and
 // then one per sequence it was 42.2.  One sequence, gamma 4: 11.1 us against 16.8.
 enum { OWN_NONE, OWN_SEQUENCE, OWN_ROWS };           // whose the statistics are: row_parts_kernel's; this kernel's, a workgroup per sequence / per logits row
 template <int OWN>
