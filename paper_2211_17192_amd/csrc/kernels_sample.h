@@ -1452,10 +1452,11 @@ inline void launch_accept(hipStream_t stream, AcceptArgs a, int rows, int cus) {
   // as many workgroups a sequence as fit the CUs in one round; more only repeat the decisions more often
   // (200 sequences, gamma 1, vocabulary 32128: 35.3 us with one, 49.1 with a second that takes the last chunks), beside
   // beta's (16 sequences, gamma 4, vocabulary 50257: 13 and 4 of them a sequence 17.7 us, 7 and 4 13.9), unless
-  // those alone are more than one round (48 sequences, gamma 7, 32128: 45.9 us a call with four, 55.6 with one)
+  // those leave less than two of a round (48 sequences, gamma 7, 32128: 45.9 us a call with four, 55.6 with one; 16, gamma
+  // 15, 50257: 45.2 with 13, 49.8 with the one that is left; gamma 14: 43.5 with 13, 41.8 with the two)
   const bool beta_apart = a.beta != nullptr && 2 * rows * a.gamma > 3 * cus && a.temperature > 0.0f;   // (argmax: no rows to read)
   const int beta_wgs = (a.beta != nullptr && !beta_apart) ? a.gamma : 0;
-  const int round = max(1, cus / rows), most = own ? 1 : min(wgs, round > beta_wgs ? round - beta_wgs : round);
+  const int round = max(1, cus / rows), left = round - beta_wgs, most = own ? 1 : min(wgs, left >= 2 ? left : round);
   a.chunks_wave = (wgs + most - 1) / most;
   a.draw_wgs = (wgs + a.chunks_wave - 1) / a.chunks_wave;         // (1 where the statistics are its own work)
   const dim3 grid(own == OWN_ROWS ? nrows : a.draw_wgs + beta_wgs, rows), block(SAMPLE_THREADS);

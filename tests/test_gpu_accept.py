@@ -361,3 +361,19 @@ def test_argmax_with_beta(vocab):
     for b in range(2):
         assert (n[b], t[b]) == sampling.accept_and_resample_from_logits(zp[b], zq[b], x[b], r[b], s[b], 0.0)[:2]
         assert np.array_equal(beta[b], (np.argmax(zp[b, :2], -1) == x[b]).astype(np.float32))
+
+
+def test_the_draw_keeps_its_workgroups_beside_much_beta():
+    """15 guesses' acceptance probabilities leave the draw of 16 sequences one workgroup each of a round of 256, 14 leave it
+    two.  (1.19 times the call of 14 where it made do with the one, 1.08 with as many as without beta; 1.07 times the rows.)"""
+    us = {}
+    for gamma in (14, 15):
+        case = synth.sampler_case(16, gamma, 50257, 1.0, 3)
+        us[gamma] = call_us(*case, 1.0, beta=torch.empty(16, gamma, device="cuda"))
+    print(us)
+    assert us[15] <= 1.13 * us[14]
+
+
+@pytest.mark.parametrize("gamma", [14, 15])
+def test_draw_beside_much_beta(gamma):
+    check(*synth.sampler_case(16, gamma, 9000, 1.0, 5), 1.0)
