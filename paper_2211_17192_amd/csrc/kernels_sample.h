@@ -329,10 +329,10 @@ __device__ __forceinline__ bool filter_fast(const float4 (&v)[SAMPLE_REG_F4], in
     if (tid < 256) bins[tid] = 0u;
     // the bins end at the smallest maximum, or where weights are zero anyway: entries that a mask moved down (to -inf, the
     // type's lowest value, -1e9) would leave all others in one bin (and a row of one value has a span all the same)
-    const float reach = fmaxf(105.0f / invT, 1e-4f * fabsf(m));
+    const float reach = fmaxf(105.0f * __builtin_amdgcn_rcpf(invT), 1e-4f * fabsf(m));
     const float lo = fmaxf(-block_reduce(tid < real ? -best : -INFINITY, sm.redf, OpMaxF(), -INFINITY), m - reach);
-    const float span = fmaxf(m - lo, 1e-6f * fabsf(m) + 1e-30f), c = 255.0f / span;
-    if (!(m - m == 0.0f && span < INFINITY)) return false;                       // (uniform)
+    const float span = fmaxf(m - lo, 1e-6f * fabsf(m) + 1e-30f), c = 255.0f * __builtin_amdgcn_rcpf(span);
+    if (!(m - m == 0.0f && span < 1e37f)) return false;                          // (uniform; 1 / span must be a number of its own)
     if (tid < real) atomicAdd(&bins[(int)fminf((m - best) * c, 255.0f)], 1u);
     __syncthreads();
     if (wave == 0) {
@@ -354,7 +354,7 @@ __device__ __forceinline__ bool filter_fast(const float4 (&v)[SAMPLE_REG_F4], in
     }
     __syncthreads();
     // every entry of a bin up to that one is at least this large (rounding of either side is far below the margins)
-    bound = m - (float)(sm.sel + 1u) / c * 1.00001f - 1e-6f * fabsf(m);
+    bound = m - (float)(sm.sel + 1u) * span * (1.00001f / 255.0f) - 1e-6f * fabsf(m);
   } else {
     if (nv4 * 4 > SAMPLE_LIST) return false;         // (uniform)
     __syncthreads();

@@ -223,6 +223,14 @@ def test_filters_of_masked_rows(mask, vocab, keep, top_k, top_p, temperature):
 
 
 @pytest.mark.parametrize("mask", list(MASKS))
+def test_top_k_of_masked_rows_at_a_boundless_temperature(mask):
+    """All kept entries weigh the same; the range of the bins is the lowest value's, whose reciprocal is no normal number."""
+    zp, zq, _, r, s = synth.sampler_case(3, 3, 8192, 1.0, 29)
+    zp[:, :, 200:], zq[:, :, 200:] = MASKS[mask], MASKS[mask]
+    check(zp, zq, np.argmax(zq, -1).astype(np.int32), r, s, 1e36, 50, 0.0)
+
+
+@pytest.mark.parametrize("mask", list(MASKS))
 def test_masked_rows_take_the_short_list_too(mask):
     """A padded vocabulary costs no more than a full one.  (50 largest of 4096: 25 us where rows with masked entries
     take the general search, 13 without any.)"""
