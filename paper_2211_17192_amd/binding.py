@@ -311,9 +311,14 @@ class SpecDecoder:
         Torch's pinned allocator takes blocks of a power of two and hands those of dead arrays out again, but does not give
         them back.  A caller that holds on to more than MAX_PINNED arrays or MAX_PINNED_BYTES gets ordinary memory for the
         others, so that what it collects is not all pinned; so does everyone where no pinned memory is to be had."""
-        self._pinned = [(r, size) for r, size in self._pinned if r() is not None]
-        block = 1 << max(4 * n - 1, 0).bit_length()
-        if len(self._pinned) >= self.MAX_PINNED or block + sum(size for _, size in self._pinned) > self.MAX_PINNED_BYTES:
+        block = taken = 1 << max(4 * n - 1, 0).bit_length()
+        live = []
+        for p in self._pinned:
+            if p[0]() is not None:
+                live.append(p)
+                taken += p[1]
+        self._pinned = live
+        if len(live) >= self.MAX_PINNED or taken > self.MAX_PINNED_BYTES:
             return np.empty(n, dtype=np.float32)
         try:
             out = torch.empty(n, dtype=torch.float32, pin_memory=True).numpy()
