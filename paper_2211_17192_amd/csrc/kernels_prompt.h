@@ -8,6 +8,7 @@
 // producing kernels write directly (rows_frag_index).  Every fragment is one contiguous KB: 16-byte
 // loads, no swizzle, no LDS bank conflicts.
 #pragma once
+#include <type_traits>
 #include "kernels_gemm.h"
 
 namespace sd {
@@ -164,83 +165,113 @@ struct RowsGemmArgs {
 };
 
 // 1 / rms of the 16 rows of a slab, by one wavefront, into out (LDS): the partial sums in gemm_kernel's
-// order.  load() asks for the first 256 of them (d_model <= 4096: all), finish() adds.
+// order.  load() asks for the first 256 of them (d_model <= 4096: all), sums() adds them as they arrive, finish() (lane
+// exchanges, division and root) is for behind the main loop, where no multiply waits for it.
 struct SlabRms {
   float4 v[16];
+  f32x4 q;                                           // rows 4 (lane % 4) .. + 3: the partials lane / 4, lane / 4 + 16, ..
   __device__ __forceinline__ void load(const RowsGemmArgs& a, int slab, int lane) {
-    const float* s = a.ss_in + (size_t)slab * a.ss_stride + (lane & 3) * 4;      // lane: partials f = lane / 4, f + 16, ..; four rows
+    const float* s = a.ss_in + (size_t)slab * a.ss_stride + (lane & 3) * 4;
 #pragma unroll
     for (int u = 0; u < 16; ++u) v[u] = *reinterpret_cast<const float4*>(s + (size_t)min((lane >> 2) + 16 * u, a.n_part - 1) * 16);
   }
-  __device__ __forceinline__ void finish(const RowsGemmArgs& a, int slab, int lane, float* out) const {
-    float q[4] = {0.f, 0.f, 0.f, 0.f};
+  __device__ __forceinline__ void sums(const RowsGemmArgs& a, int slab, int lane) {
     const int f = lane >> 2;
+    q = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int u = 0; u < 16; ++u) {
       const bool ok = f + 16 * u < a.n_part;
       q[0] += ok ? v[u].x : 0.0f; q[1] += ok ? v[u].y : 0.0f; q[2] += ok ? v[u].z : 0.0f; q[3] += ok ? v[u].w : 0.0f;
     }
-    const float* s = a.ss_in + (size_t)slab * a.ss_stride + (lane & 3) * 4;
-    for (int p = f + 256; p < a.n_part; p += 16) {
-      const float4 w = *reinterpret_cast<const float4*>(s + (size_t)p * 16);
-      q[0] += w.x; q[1] += w.y; q[2] += w.z; q[3] += w.w;
+    if (a.n_part > 256) {                            // (uniform)
+      const float* s = a.ss_in + (size_t)slab * a.ss_stride + (lane & 3) * 4;
+      for (int p = f + 256; p < a.n_part; p += 16) {
+        const float4 w = *reinterpret_cast<const float4*>(s + (size_t)p * 16);
+        q[0] += w.x; q[1] += w.y; q[2] += w.z; q[3] += w.w;
+      }
     }
+  }
+  static __device__ __forceinline__ void finish(const RowsGemmArgs& a, f32x4 q, int lane, float* out) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       q[e] += __shfl_xor(q[e], 4, 64); q[e] += __shfl_xor(q[e], 8, 64);
       q[e] += __shfl_xor(q[e], 48, 64); q[e] += __shfl_xor(q[e], 16, 64);      // quads 0 + 3, 1 + 2: as the first lane of gemm_kernel's sum
-      if (f == 0) out[(lane & 3) * 4 + e] = 1.0f / sqrtf(q[e] / (float)a.K + a.eps);
     }
+    const int f = lane >> 2;                         // (every lane holds the totals of its four rows: lanes f = 0 .. 3 take one each)
+    float t = q[0];
+    t = f == 1 ? q[1] : t; t = f == 2 ? q[2] : t; t = f == 3 ? q[3] : t;
+    const float r = 1.0f / sqrtf(t / (float)a.K + a.eps);
+    if (f < 4) out[(lane & 3) * 4 + f] = r;
   }
 };
 
-// What a lane needs of row `row` (slab, j = row % 16) before it writes its features.
+// What an epilogue needs of a row beside its sums, and of a tile: everything that can be asked for ahead of the main
+// loop is, raw, and what depends on a row's position behind the first loads of the stream.  (After the loop, as two or three
+// dependent trips to memory, with 1 / rms of the rows ahead of it: 768 features, 128 rows, K-slices, us a launch, LayerNorm
+// model: QKV 7.0 -> 6.3, FFN-in 7.3 -> 6.8, FFN-out 7.7 -> 7.4, O 4.9 -> 4.5; 256 features 4.5 -> 3.6; 64 rows of 4096, RMSNorm
+// model: QKV 18.7 -> 18.0; of 1024: QKV 6.6 -> 5.7, gated 7.1 -> 6.5; 2000 rows: QKV of 4096 140 -> 133, residual products
+// of 1024 27.4 -> 24.7.)
+struct RowIn {
+  float r1;              // 1 / rms
+  int pos;               // EPI_QKV
+  unsigned kvrow;        // EPI_QKV: the row of the cache (of d_head elements) that key head 0 goes to
+  int orow;              // EPI_LOGITS
+};
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+struct TileIn { bf16x4 bias, gain; };
+
 template <int EPI>
 struct RowsEpilogue {
-  int slab, row, j, kq;
-  bool ok;
-  float r1;
-  int pos;
-  size_t kvbase;
-  int orow;
-  // rs: LDS, 1 / rms of the slab's 16 rows
-  __device__ __forceinline__ void row_inputs(const RowsGemmArgs& a, int slab_, int lane, const float* rs) {
-    slab = slab_; j = lane & 15; kq = lane >> 4; row = slab * 16 + j;
-    ok = row < a.rows;
-    const int rowc = min(row, a.rows - 1);
-    r1 = (a.ss_in != nullptr) ? rs[j] : 1.0f;
-    pos = 0; kvbase = 0; orow = row;
+  // ---- loads: none behind a branch; what is absent is read from the weights and dropped ----
+  static __device__ __forceinline__ int ask_pos(const RowsGemmArgs& a, int rowc) { return EPI == EPI_QKV ? a.row_pos[rowc] : 0; }
+  static __device__ __forceinline__ int ask_seq(const RowsGemmArgs& a, int rowc) { return EPI == EPI_QKV ? (a.row_seq != nullptr ? a.row_seq : a.row_pos)[rowc] : 0; }
+  static __device__ __forceinline__ int ask_page(const RowsGemmArgs& a, int pos, int seq) {
+    return EPI == EPI_QKV ? a.page_table[(a.row_seq != nullptr ? seq * a.pt_stride : 0) + (max(pos, 0) >> (__ffs(a.page_size) - 1))] : 0;
+  }
+  static __device__ __forceinline__ unsigned cache_row(const RowsGemmArgs& a, int pos, int page) {
+    return (unsigned)page * 2u * (unsigned)a.n_kv_heads * (unsigned)a.page_size + (unsigned)(max(pos, 0) & (a.page_size - 1));
+  }
+  static __device__ __forceinline__ int ask_orow(const RowsGemmArgs& a, int rowc) {
+    return EPI == EPI_LOGITS ? (a.out_row != nullptr ? a.out_row : reinterpret_cast<const int*>(a.W))[rowc] : 0;
+  }
+  static __device__ __forceinline__ TileIn ask_tile(const RowsGemmArgs& a, int n0) {
+    TileIn t{};
+    if (EPI != EPI_GATED) t.bias = *reinterpret_cast<const bf16x4*>((a.bias != nullptr ? a.bias : a.W) + (unsigned)n0);
+    if (EPI == EPI_RESID) t.gain = *reinterpret_cast<const bf16x4*>((a.xg != nullptr ? a.gain_next : a.W) + (unsigned)n0);
+    return t;
+  }
+  // the residual (EPI_RESID), cos and sin of the position (EPI_QKV)
+  static __device__ __forceinline__ float4 ask_four(const RowsGemmArgs& a, int rowc, int n0, int pos) {
+    if (EPI == EPI_RESID) return *reinterpret_cast<const float4*>(a.x + (size_t)rowc * a.N + n0);
     if (EPI == EPI_QKV) {
-      pos = a.row_pos[rowc];
-      const int pc = max(pos, 0), pt0 = (a.row_seq != nullptr) ? a.row_seq[rowc] * a.pt_stride : 0;
-      const int page = a.page_table[pt0 + pc / a.page_size], slot = pc % a.page_size;
-      kvbase = (size_t)page * 2 * a.n_kv_heads * a.page_size * a.d_head + (size_t)slot * a.d_head;
+      const bool has = a.rope != nullptr;            // (a head's features are whole tiles, q, k and v whole heads: n0 % d_head is the place within the head)
+      return *reinterpret_cast<const float4*>((has ? a.rope : reinterpret_cast<const float*>(a.W)) + (has ? (size_t)max(pos, 0) * a.d_head + (n0 & (a.d_head - 1)) : (size_t)0));
     }
-    if (EPI == EPI_LOGITS && a.out_row != nullptr) orow = a.out_row[rowc];
+    return make_float4(0.f, 0.f, 0.f, 0.f);
   }
   // The finished sums of one 16-feature tile (EPI_GATED: of its gate and up streams): this lane's are the
-  // features 16 tile + 4 kq + 0..3.  gemm_kernel's arithmetic.
-  __device__ __forceinline__ void tile_out(const RowsGemmArgs& a, int tile, int bz, const f32x4& s0, const f32x4& s1) const {
-    typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+  // features 16 tile + 4 kq + 0..3 of row 16 slab + j.  gemm_kernel's arithmetic.
+  static __device__ __forceinline__ void tile_out(const RowsGemmArgs& a, int slab, int lane, int tile, int bz, const f32x4& s0, const f32x4& s1,
+                                                  const RowIn& in, const TileIn& ti, const float4& four) {
+    const int j = lane & 15, kq = lane >> 4, row = slab * 16 + j;
+    const bool ok = row < a.rows;
     const int n0 = tile * 16 + kq * 4;
     float y[4];
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      y[r] = (a.ss_in != nullptr) ? s0[r] * r1 : s0[r];
-      y[r] += (a.bias != nullptr) ? (float)a.bias[n0 + r] : 0.0f;
+      y[r] = (a.ss_in != nullptr) ? s0[r] * in.r1 : s0[r];
+      y[r] += (EPI != EPI_GATED && a.bias != nullptr) ? (float)ti.bias[r] : 0.0f;
     }
     if (EPI == EPI_RESID) {
       float xn[4] = {0.f, 0.f, 0.f, 0.f};
       if (ok) {
-        float4* xp = reinterpret_cast<float4*>(a.x + (size_t)row * a.N + n0);
-        const float4 o = *xp;
-        xn[0] = o.x + y[0]; xn[1] = o.y + y[1]; xn[2] = o.z + y[2]; xn[3] = o.w + y[3];
-        *xp = make_float4(xn[0], xn[1], xn[2], xn[3]);
+        xn[0] = four.x + y[0]; xn[1] = four.y + y[1]; xn[2] = four.z + y[2]; xn[3] = four.w + y[3];
+        *reinterpret_cast<float4*>(a.x + (size_t)row * a.N + n0) = make_float4(xn[0], xn[1], xn[2], xn[3]);
       }
       if (a.xg != nullptr) {
         bf16x4 g;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) g[r] = (bf16)(xn[r] * (float)a.gain_next[n0 + r]);
+        for (int r = 0; r < 4; ++r) g[r] = (bf16)(xn[r] * (float)ti.gain[r]);
         *reinterpret_cast<bf16x4*>(a.xg + rows_frag_index(row, n0, a.N >> 5)) = g;
       }
       if (a.ss != nullptr) {
@@ -253,30 +284,29 @@ struct RowsEpilogue {
     } else if (EPI == EPI_QKV) {
       const bool is_q = n0 < a.nq, is_k = !is_q && n0 < a.nq + a.nkv;          // uniform over the tile
       const int nn = is_q ? n0 : (is_k ? n0 - a.nq : n0 - a.nq - a.nkv);
-      const int head = nn / a.d_head, d = nn % a.d_head;
+      const int head = nn >> (__ffs(a.d_head) - 1), d = nn & (a.d_head - 1);
       bf16x4 o;
-      if (a.rope != nullptr && (is_q || is_k) && pos >= 0) {
-        const float4 cs = *reinterpret_cast<const float4*>(a.rope + ((size_t)pos * (a.d_head >> 1) + (d >> 1)) * 2);
-        o[0] = (bf16)rope_rotate(y[0], y[1], cs.x, cs.y, false); o[1] = (bf16)rope_rotate(y[1], y[0], cs.x, cs.y, true);
-        o[2] = (bf16)rope_rotate(y[2], y[3], cs.z, cs.w, false); o[3] = (bf16)rope_rotate(y[3], y[2], cs.z, cs.w, true);
+      if (a.rope != nullptr && (is_q || is_k) && in.pos >= 0) {
+        o[0] = (bf16)rope_rotate(y[0], y[1], four.x, four.y, false); o[1] = (bf16)rope_rotate(y[1], y[0], four.x, four.y, true);
+        o[2] = (bf16)rope_rotate(y[2], y[3], four.z, four.w, false); o[3] = (bf16)rope_rotate(y[3], y[2], four.z, four.w, true);
       } else {
 #pragma unroll
         for (int r = 0; r < 4; ++r) o[r] = (bf16)y[r];
       }
       if (ok) {
         if (is_q) *reinterpret_cast<bf16x4*>(a.q + (size_t)row * a.nq + n0) = o;
-        else if (pos >= 0) *reinterpret_cast<bf16x4*>(a.kv_pool + kvbase + ((size_t)(is_k ? 0 : 1) * a.n_kv_heads + head) * a.page_size * a.d_head + d) = o;
+        else if (in.pos >= 0) *reinterpret_cast<bf16x4*>(a.kv_pool + ((size_t)in.kvrow + (size_t)((is_k ? 0 : a.n_kv_heads) + head) * a.page_size) * a.d_head + d) = o;
       }
     } else if (EPI == EPI_LOGITS) {
-      if (ok && orow >= 0)
-        *reinterpret_cast<float4*>(a.logits + (size_t)orow * a.N + n0) = make_float4(a.scale * y[0], a.scale * y[1], a.scale * y[2], a.scale * y[3]);
+      if (ok && in.orow >= 0)
+        *reinterpret_cast<float4*>(a.logits + (size_t)in.orow * a.N + n0) = make_float4(a.scale * y[0], a.scale * y[1], a.scale * y[2], a.scale * y[3]);
     } else {
       bf16x4 o;
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
         float v = y[r];
         if (EPI == EPI_ACT) v = gelu_tanh(v);
-        if (EPI == EPI_GATED) v = ((a.act == ACT_GELU) ? gelu_tanh(v) : silu(v)) * (s1[r] * r1);
+        if (EPI == EPI_GATED) v = ((a.act == ACT_GELU) ? gelu_tanh(v) : silu(v)) * (s1[r] * in.r1);
         o[r] = (bf16)v;
       }
       if (EPI == EPI_STORE) {
@@ -323,7 +353,8 @@ static __global__ __launch_bounds__(64 * NWV, 2) void gemm_rows_kernel(const Row
   constexpr int SUB = 4, NT_OUT = (EPI == EPI_GATED) ? NT / 2 : NT;
   constexpr int NFRAG = SUB * MT * 64, XPT = NFRAG / (64 * NWV);
   __shared__ __align__(16) bf16x8 xs[2][NFRAG];
-  __shared__ float rs_s[MT][16];
+  __shared__ float rs_s[MT * 16];
+  __shared__ int pos_s[EPI == EPI_QKV ? MT * 16 : 1], row_s[EPI == EPI_QKV || EPI == EPI_LOGITS ? MT * 16 : 1];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int KS = a.K >> 5, ntiles = a.N >> 4, slabs = (a.rows + 15) >> 4;
@@ -385,8 +416,15 @@ static __global__ __launch_bounds__(64 * NWV, 2) void gemm_rows_kernel(const Row
     __builtin_amdgcn_sched_group_barrier(0x020, XPT, 0);
   };
 
-  // 1 / rms of the rows: slab w (of four wavefronts: and w + 4) by wavefront w, its loads ahead of the stream's
+  // what the epilogue needs of the rows, thread t of row t: asked for ahead of the stream, into LDS behind it
+  const int rowc = min(bm * MT * 16 + min((int)threadIdx.x, MT * 16 - 1), a.rows - 1);
+  int row_pos = RowsEpilogue<EPI>::ask_pos(a, rowc), row_seq = RowsEpilogue<EPI>::ask_seq(a, rowc);
+  const int row_out = RowsEpilogue<EPI>::ask_orow(a, rowc);
+  // 1 / rms of the rows: slab w (of four wavefronts: and w + 4) by wavefront w
   SlabRms rms;
+  constexpr bool TWO = NWV < MT;
+  static_assert(2 * NWV >= MT, "at most two slabs a wavefront");
+  f32x4 q2 = {0.f, 0.f, 0.f, 0.f};
   const bool normed = a.ss_in != nullptr;            // (uniform)
   if (normed && wave < MT) rms.load(a, min(bm * MT + wave, slabs - 1), lane);
 
@@ -400,11 +438,18 @@ static __global__ __launch_bounds__(64 * NWV, 2) void gemm_rows_kernel(const Row
   int end_next = (next < end) ? end : min(KS, end + a.kpw);                  // of the slice `next` lies in
   load_x(next, end_next - next);
   if (normed) {
-    if (wave < MT) rms.finish(a, min(bm * MT + wave, slabs - 1), lane, rs_s[wave]);
-    if (NWV == 4 && wave + 4 < MT) {
-      rms.load(a, min(bm * MT + wave + 4, slabs - 1), lane);
-      rms.finish(a, min(bm * MT + wave + 4, slabs - 1), lane, rs_s[(wave + 4) % MT]);
+    if (wave < MT) rms.sums(a, min(bm * MT + wave, slabs - 1), lane);
+    if (TWO && wave + NWV < MT) {
+      SlabRms second;
+      second.load(a, min(bm * MT + wave + NWV, slabs - 1), lane);
+      second.sums(a, min(bm * MT + wave + NWV, slabs - 1), lane);
+      q2 = second.q;
     }
+  }
+  int row_page = 0;
+  if (EPI == EPI_QKV) {
+    asm volatile("" : "+v"(row_pos), "+v"(row_seq)); // (no earlier: what is computed of a loaded value waits for it)
+    row_page = RowsEpilogue<EPI>::ask_page(a, row_pos, row_seq);
   }
   __syncthreads();
   int buf = 0;
@@ -450,16 +495,40 @@ static __global__ __launch_bounds__(64 * NWV, 2) void gemm_rows_kernel(const Row
       for (int m = 0; m < MT; ++m) tot[t][m] += f32x4{0.f, 0.f, 0.f, 0.f};
   }
 
+  // ---- epilogue: all its loads leave together ----
+  if (EPI == EPI_QKV && threadIdx.x < MT * 16) {
+    pos_s[threadIdx.x % (MT * 16)] = row_pos;
+    row_s[threadIdx.x % (MT * 16)] = (int)RowsEpilogue<EPI>::cache_row(a, row_pos, row_page);
+  }
+  if (EPI == EPI_LOGITS && threadIdx.x < MT * 16) row_s[threadIdx.x % (MT * 16)] = a.out_row != nullptr ? row_out : bm * MT * 16 + (int)threadIdx.x;
+  if (normed) {
+    if (wave < MT) SlabRms::finish(a, rms.q, lane, rs_s + wave * 16);
+    if (TWO && wave + NWV < MT) SlabRms::finish(a, q2, lane, rs_s + (wave + NWV) * 16);
+  }
+  if (normed || EPI == EPI_QKV || EPI == EPI_LOGITS) __syncthreads();
+  const int j = lane & 15, kq = lane >> 4;
+  TileIn ti[NT_OUT];
+  float4 four[NT_OUT][MT];
+#pragma unroll
+  for (int t = 0; t < NT_OUT; ++t) {
+    const int n0 = min(tile0 + t, ntiles - 1) * 16 + kq * 4;
+    ti[t] = RowsEpilogue<EPI>::ask_tile(a, n0);
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+      four[t][m] = RowsEpilogue<EPI>::ask_four(a, min((bm * MT + m) * 16 + j, a.rows - 1), n0, EPI == EPI_QKV ? pos_s[(m * 16 + j) % (EPI == EPI_QKV ? MT * 16 : 1)] : 0);
+  }
 #pragma unroll
   for (int m = 0; m < MT; ++m) {
     if (bm * MT + m >= slabs) break;                 // uniform
-    RowsEpilogue<EPI> e;
-    e.row_inputs(a, bm * MT + m, lane, rs_s[m]);
+    RowIn in{1.0f, 0, 0u, 0};
+    if (normed) in.r1 = rs_s[m * 16 + j];
+    if (EPI == EPI_QKV) { in.pos = pos_s[(m * 16 + j) % (EPI == EPI_QKV ? MT * 16 : 1)]; in.kvrow = (unsigned)row_s[(m * 16 + j) % (EPI == EPI_QKV ? MT * 16 : 1)]; }
+    if (EPI == EPI_LOGITS) in.orow = row_s[(m * 16 + j) % (EPI == EPI_LOGITS ? MT * 16 : 1)];
 #pragma unroll
     for (int t = 0; t < NT_OUT; ++t)
       if (tile0 + t < ntiles) {                      // uniform
-        if (EPI == EPI_GATED) e.tile_out(a, tile0 + t, bz, tot[(2 * t) % NT][m], tot[(2 * t + 1) % NT][m]);
-        else e.tile_out(a, tile0 + t, bz, tot[t % NT][m], tot[t % NT][m]);
+        if (EPI == EPI_GATED) RowsEpilogue<EPI>::tile_out(a, bm * MT + m, lane, tile0 + t, bz, tot[(2 * t) % NT][m], tot[(2 * t + 1) % NT][m], in, ti[t], four[t][m]);
+        else RowsEpilogue<EPI>::tile_out(a, bm * MT + m, lane, tile0 + t, bz, tot[t % NT][m], tot[t % NT][m], in, ti[t], four[t][m]);
       }
   }
 }
@@ -472,8 +541,9 @@ static __global__ __launch_bounds__(64 * NWV, 2) void gemm_rows_kernel(const Row
 // KB for NT * MT MFMAs.
 // D: kpw is a multiple of it, or the k-steps past a slice's end are multiplied with zeros.
 // dynamic LDS: S * NT * MT KB + MT * 64 bytes.
+// (the smaller shapes: 128 registers, two workgroups of eight wavefronts a CU)
 template <int EPI, int NT, int MT, int D>
-static __global__ __launch_bounds__(512) void gemm_slices_kernel(const RowsGemmArgs a) {
+static __global__ __launch_bounds__(512, (NT + MT <= 3 || (NT + MT == 4 && D == 3)) ? 4 : 2) void gemm_slices_kernel(const RowsGemmArgs a) {
   extern __shared__ float lds[];
   f32x4* part = reinterpret_cast<f32x4*>(lds);       // [S][NT][MT][64 lanes]
   constexpr int NT_OUT = (EPI == EPI_GATED) ? NT / 2 : NT;
@@ -512,12 +582,25 @@ static __global__ __launch_bounds__(512) void gemm_slices_kernel(const RowsGemmA
       for (int t = 0; t < NT; ++t) acc[t][m] = Mma<bf16>::mma(wf[u][t], xf[u][m], acc[t][m]);
   };
   float* rs_s = lds + (size_t)S * NT * MT * 256;     // [MT][16]
+  // what the epilogue reads leaves around the stream's first loads: first the row's position, behind them what depends on it.
+  // (tile, slab) pairs, slab fastest, pair i by wavefront i % S: the first of this wavefront's (the others ask for theirs later)
+  using Epi = RowsEpilogue<EPI>;
+  const int j = lane & 15, kq = lane >> 4;
+  const int m1 = wave % MT, t1 = wave / MT, n1 = min(tile0 + min(t1, NT_OUT - 1), ntiles - 1) * 16 + kq * 4;
+  const int row1 = (bm * MT + m1) * 16 + j, row1c = min(row1, a.rows - 1);
+  int pos1 = Epi::ask_pos(a, row1c), seq1 = Epi::ask_seq(a, row1c);
+  const int orow1 = Epi::ask_orow(a, row1c);
   const bool normed = a.ss_in != nullptr;            // (uniform)
   SlabRms rms;
   if (normed && wave < MT) rms.load(a, min(bm * MT + wave, slabs - 1), lane);
 #pragma unroll
   for (int u = 0; u < D; ++u) load(u, ks0 + u);
-  if (normed && wave < MT) rms.finish(a, min(bm * MT + wave, slabs - 1), lane, rs_s + wave * 16);      // (S >= MT)
+  __builtin_amdgcn_sched_barrier(0);
+  if (normed && wave < MT) rms.sums(a, min(bm * MT + wave, slabs - 1), lane);            // (S >= MT)
+  if (EPI == EPI_QKV) asm volatile("" : "+v"(pos1), "+v"(seq1));      // (no earlier: what is computed of a loaded value waits for it)
+  const int page1 = Epi::ask_page(a, pos1, seq1);
+  const TileIn ti1 = Epi::ask_tile(a, n1);
+  const float4 four1 = Epi::ask_four(a, row1c, n1, pos1);
   const int blocks = (a.kpw + D - 1) / D;
 #pragma unroll 1
   for (int b = 1; b < blocks; ++b) {
@@ -534,20 +617,42 @@ static __global__ __launch_bounds__(512) void gemm_slices_kernel(const RowsGemmA
   for (int t = 0; t < NT; ++t)
 #pragma unroll
     for (int m = 0; m < MT; ++m) part[((wave * NT + t) * MT + m) * 64 + lane] = acc[t][m];
-  RowsEpilogue<EPI> e;
+  if (normed && wave < MT) SlabRms::finish(a, rms.q, lane, rs_s + wave * 16);
   __syncthreads();
-  e.row_inputs(a, min(bm * MT + wave % MT, slabs - 1), lane, rs_s + (wave % MT) * 16);
-  for (int i = wave; i < NT_OUT * MT; i += S) {      // (tile, slab) pairs, slab fastest
+  for (int i = wave; i < NT_OUT * MT; i += S) {
     const int t = i / MT, m = i % MT;
     if (bm * MT + m >= slabs || tile0 + t >= ntiles) continue;                 // uniform
-    if (i != wave) e.row_inputs(a, bm * MT + m, lane, rs_s + m * 16);
-    f32x4 s[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
-#pragma unroll
-    for (int st = 0; st < ((EPI == EPI_GATED) ? 2 : 1); ++st) {
-      const int tt = (EPI == EPI_GATED) ? 2 * t + st : t;
-      for (int w = 0; w < S; ++w) s[st] += part[((w * NT + tt) * MT + m) * 64 + lane];
+    RowIn in{normed ? rs_s[m * 16 + j] : 1.0f, pos1, 0u, a.out_row != nullptr ? orow1 : row1};
+    TileIn ti = ti1;
+    float4 four = four1;
+    int page = page1;
+    if (i != wave) {                                 // (uniform)
+      const int row = (bm * MT + m) * 16 + j, rowc = min(row, a.rows - 1), n0 = (tile0 + t) * 16 + kq * 4;
+      if (m != m1) {
+        in.pos = Epi::ask_pos(a, rowc);
+        page = Epi::ask_page(a, in.pos, Epi::ask_seq(a, rowc));
+        in.orow = a.out_row != nullptr ? Epi::ask_orow(a, rowc) : row;
+      }
+      ti = Epi::ask_tile(a, n0);
+      four = Epi::ask_four(a, rowc, n0, in.pos);
     }
-    e.tile_out(a, tile0 + t, bz, s[0], s[1]);
+    if (EPI == EPI_QKV) in.kvrow = Epi::cache_row(a, in.pos, page);
+    f32x4 s[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+    auto add = [&](auto waves) {                     // (their number at compile time: all reads in flight)
+      constexpr int W = decltype(waves)::value;
+#pragma unroll
+      for (int st = 0; st < ((EPI == EPI_GATED) ? 2 : 1); ++st) {
+        const int tt = (EPI == EPI_GATED) ? 2 * t + st : t;
+        f32x4 v[W];
+#pragma unroll
+        for (int w = 0; w < W; ++w) v[w] = part[((w * NT + tt) * MT + m) * 64 + lane];
+#pragma unroll
+        for (int w = 0; w < W; ++w) s[st] += v[w];
+      }
+    };
+    if (S == 8) add(std::integral_constant<int, 8>());
+    else add(std::integral_constant<int, 4>());
+    Epi::tile_out(a, bm * MT + m, lane, tile0 + t, bz, s[0], s[1], in, ti, four);
   }
 }
 
