@@ -92,6 +92,22 @@ static __global__ __launch_bounds__(256) void embed_kernel(
   }
 }
 
+// A new sequence's tokens and state out of pinned host memory, to the models' prompts, the history and the state (each
+// optional), in one launch.  grid * 256 threads >= n.
+static __global__ __launch_bounds__(256) void start_sequence_kernel(const int* __restrict__ tokens, int n, int* __restrict__ prompt_p,
+                                                                    int* __restrict__ prompt_q, int* __restrict__ hist,
+                                                                    const SeqState* __restrict__ from, SeqState* __restrict__ to) {
+  const int i = (int)(blockIdx.x * 256 + threadIdx.x);
+  constexpr int WORDS = sizeof(SeqState) / 4;
+  static_assert(WORDS <= 256 && sizeof(SeqState) % 4 == 0, "one workgroup copies a state");
+  if (to != nullptr && i < WORDS) reinterpret_cast<int*>(to)[i] = reinterpret_cast<const int*>(from)[i];
+  if (i >= n) return;
+  const int t = tokens[i];
+  if (prompt_p != nullptr) prompt_p[i] = t;
+  if (prompt_q != nullptr) prompt_q[i] = t;
+  if (hist != nullptr) hist[i] = t;
+}
+
 // Negligible-cost approximation model (an n-gram table): the draft logits of guess `step`
 // of sequence b are the table row selected by the previous token (bigram; row_of == nullptr:
 // one row for every context, a unigram model).  grid = (slices, sequences); the row is

@@ -242,3 +242,47 @@ def test_smaller_workspaces_give_the_same_results(name, monkeypatch):
             assert np.array_equal(a, b) if isinstance(a, np.ndarray) else a == b
     with pytest.raises(binding.SdError, match="workspace too small"):
         decode(least // 2)
+
+
+def test_last_prompt_rows_of_both_models_beside_each_other():
+    """A pass of 2048 rows and one of 9, whose key ranges Mp merges by tickets while Mq, on its own stream, takes them in turn."""
+    prefill_equals_token_by_token((T.GQA, 256, 4, 2, 128, 512, 3, 2057, 0), False)
+
+
+@pytest.mark.parametrize("layers_q", [1, 3])        # Mq's launches behind Mp's, and ahead of them
+def test_prompt_waits_for_the_callers_stream(layers_q, monkeypatch):
+    """sd_prefill on a stream of the caller's that still computes the encoder outputs: both models' launches come behind it."""
+    import ctypes as C
+    from paper_2211_17192_amd import binding
+    cfg = synth.model_cfg(T.T5DEC, 2, 256, 4, 704, 512, 200, d_head=64, enc_len=61, dtype="bf16", logit_scale=4.0)
+    w = synth.random_weights(cfg, 5, "cuda", 0.04)
+    cfg_q = dict(cfg, n_layers=layers_q)
+    w_q = synth.random_weights(cfg_q, 6, "cuda", 0.04)
+    enc = synth.counter_normal((61, 256), 3, 1.0, 0.0, "cuda").to(torch.bfloat16)
+    tokens = np.asarray(synth.random_tokens(40, 9, 512), dtype=np.int32)
+    u = synth.uniform_stream(11, 7)
+
+    def logits(dec):
+        dec.step(3, 1.0, u)
+        return dec.logits(0, 4), dec.logits(1, 3)
+
+    dec = binding.SpecDecoder(cfg, w, cfg_q, w_q, max_gamma=3)
+    dec.prefill(tokens, enc, enc)
+    want = logits(dec)
+    stream = torch.cuda.Stream()
+    plain = binding._RuntimeCfg
+    monkeypatch.setattr(binding, "_RuntimeCfg", lambda **kw: plain(**{**kw, "stream": stream.cuda_stream}))
+    dec = binding.SpecDecoder(cfg, w, cfg_q, w_q, max_gamma=3)
+    big = torch.zeros(4096, 4096, device="cuda")
+    late = [torch.zeros_like(enc), torch.zeros_like(enc)]
+    torch.cuda.synchronize()
+    with torch.cuda.stream(stream):
+        for _ in range(20):
+            big = big @ big
+        for t in late:
+            t.copy_(enc)
+    ptr = lambda t: C.c_void_p(t.data_ptr())         # noqa: E731
+    st = binding.lib.sd_prefill(dec._ctx, 0, tokens.ctypes.data_as(C.POINTER(C.c_int32)), len(tokens), ptr(late[0]), ptr(late[1]))
+    assert st == 0
+    got = logits(dec)
+    assert np.array_equal(got[0], want[0]) and np.array_equal(got[1], want[1])
