@@ -105,7 +105,6 @@ __device__ __forceinline__ float4 placed4_row(const f32x4_any& t, int k, int V) 
   const float z = over <= 0 ? t[2] : t[3];
   return make_float4(k < V ? x : NONE, k + 1 < V ? y : NONE, k + 2 < V ? z : NONE, k + 3 < V ? t[3] : NONE);
 }
-__device__ __forceinline__ float4 load4_row(const float* __restrict__ z, int k, int V) { return placed4_row(raw4_row(z, k, V), k, V); }
 // The same where V >= 4 is known: no branch, whose two sides meeting would make the load be waited for at once.
 __device__ __forceinline__ f32x4_any raw4_long_row(const float* __restrict__ z, int k, int V) {
   return *reinterpret_cast<const f32x4_any*>(z + (unsigned)min(k, V - 4));
@@ -119,12 +118,6 @@ template <int N> __device__ __forceinline__ void raw4_rows(const float* __restri
 #pragma unroll
     for (int m = 0; m < N; ++m) t[m] = raw4_row(z, k + m * step, V);
   }
-}
-template <int N> __device__ __forceinline__ void load4_rows(const float* __restrict__ z, int k, int step, int V, float4 (&v)[N]) {
-  f32x4_any t[N];
-  raw4_rows(z, k, step, V, t);
-#pragma unroll
-  for (int m = 0; m < N; ++m) v[m] = placed4_row(t[m], k + m * step, V);
 }
 // A sum of exponentials relative to m, brought to the maximum M >= m.  The factor is the weight that every
 // other place gives an entry m (a 64-bit factor would not round as the weights do: probabilities would add up
@@ -979,27 +972,23 @@ __device__ __forceinline__ const float* accept_row(const AcceptArgs& a, int b, i
   return (j <= a.gamma) ? a.p + ((size_t)b * (a.gamma + 1) + j) * a.V : a.q + ((size_t)b * a.gamma + (j - a.gamma - 1)) * a.V;
 }
 
-// A part's first block of entries, and its statistics.
-__device__ __forceinline__ void load_part(const AcceptArgs& a, int b, int j, int part, int lane, float4 (&v)[SAMPLE_PART / 256]) {
-  const float* z = accept_row(a, b, j);
-  const int k0 = part * a.part_len;
-  if (k0 + SAMPLE_PART <= a.V) {                     // (uniform) no entry past the row
+// A part's first block of entries as it lies in memory, and its statistics.  ANY: rows of fewer than four entries among
+// them; else no branch is in the way of the loads, which the compiler would wait for behind it.
+typedef f32x4_any PartRaw[SAMPLE_PART / 256];
+template <bool ANY>
+__device__ __forceinline__ void load_part(const float* z, int k0, int lane, int V, PartRaw& t) {
+  if (ANY) raw4_rows(z, k0 + lane * 4, 256, V, t);
+  else {
 #pragma unroll
-    for (int it = 0; it < SAMPLE_PART / 256; ++it) {
-      const f32x4_any t = *reinterpret_cast<const f32x4_any*>(z + k0 + it * 256 + (unsigned)lane * 4u);
-      v[it] = make_float4(t[0], t[1], t[2], t[3]);
-    }
-  } else {
-    load4_rows(z, k0 + lane * 4, 256, a.V, v);
+    for (int it = 0; it < SAMPLE_PART / 256; ++it) t[it] = raw4_long_row(z, k0 + it * 256 + lane * 4, V);
   }
 }
 // Every exponential is taken relative to the block's maximum over the whole wavefront (never to a lane's
 // own: a lane may hold nothing but padding) and goes into the sum as a double.
 // POSTED: another workgroup reads them in the same launch.
 template <bool POSTED>
-__device__ __forceinline__ void reduce_part(const AcceptArgs& a, int b, int j, int part, int lane, float4 (&v)[SAMPLE_PART / 256]) {
+__device__ __forceinline__ void reduce_part(const AcceptArgs& a, int b, int j, int part, int lane, float T, const PartRaw& first) {
   constexpr int NV = SAMPLE_PART / 256;
-  const float T = a.prm ? a.prm[b].temperature : a.temperature;
   const bool greedy = (T == 0.0f);
   if (greedy && j > a.gamma && a.beta == nullptr) return;          // argmax sampling looks at q rows for beta only
   const float invT = greedy ? 1.0f : 1.0f / T;
@@ -1007,11 +996,22 @@ __device__ __forceinline__ void reduce_part(const AcceptArgs& a, int b, int j, i
   double s = 0.0;
   int arg = INT_MAX;
   const int k_end = min(a.V, (part + 1) * a.part_len);
+  float4 v[NV];
+  auto place = [&](const PartRaw& t, int k0) {
+    if (k0 + SAMPLE_PART <= a.V) {                   // (uniform) none to move or to leave out
+#pragma unroll
+      for (int it = 0; it < NV; ++it) v[it] = make_float4(t[it][0], t[it][1], t[it][2], t[it][3]);
+    } else {
+#pragma unroll
+      for (int it = 0; it < NV; ++it) v[it] = placed4_row(t[it], k0 + it * 256 + lane * 4, a.V);
+    }
+  };
+  place(first, part * a.part_len);
   for (int k0 = part * a.part_len; k0 < k_end; k0 += SAMPLE_PART) {
     if (k0 != part * a.part_len) {                   // (parts longer than a block: more than 65536 entries a row)
-      const float* z = accept_row(a, b, j);
-#pragma unroll
-      for (int it = 0; it < NV; ++it) v[it] = load4_row(z, k0 + it * 256 + lane * 4, a.V);
+      PartRaw t;
+      load_part<false>(accept_row(a, b, j), k0, lane, a.V, t);
+      place(t, k0);
     }
     float mb = -INFINITY;
 #pragma unroll
@@ -1057,41 +1057,46 @@ __device__ __forceinline__ void reduce_part(const AcceptArgs& a, int b, int j, i
 
 // Bound by the reads.  A wavefront takes every (grid x 4)-th part of the launch (part fastest, then row, then
 // sequence) and asks for the next one's 4 KB before it sums this one; no
-// barrier, no other wavefront is needed.  (They do not stay in flight: that load, and the temperature's in
-// reduce_part, lie behind branches, where the compiler waits for everything outstanding.)  A part's sum is relative to the part's maximum; the parts of a
-// row are brought to the row's by one factor each.
+// barrier, no other wavefront is needed.  No load lies behind a branch and the temperature comes by a scalar load, so the next
+// part's stays in flight: 123 MB (64 sequences, gamma 7, vocabulary 32128) 25.2 -> 22.8 us, 5.4 TB/s; 29 MB of unaligned rows
+// (16, gamma 4, 50257) 8.2 -> 7.8.  12, 16, 20 and 28 wavefronts a CU: 0.7, 1.0, 0.8 and 0.2 us slower than 24.
+// A part's sum is relative to the part's maximum; the parts of a row are brought to the row's by one factor each.
 // grid = enough workgroups for one part a wavefront, at most ACCEPT_WAVES_CU wavefronts a CU.
 constexpr int ACCEPT_WAVES_CU = 24;
+template <bool ANY>
 static __global__ __launch_bounds__(256, 6) void row_parts_kernel(const AcceptArgs a, int items, unsigned mag_parts, unsigned mag_rows) {
   const int lane = threadIdx.x & 63, stride = (int)gridDim.x * 4;
   const int nrows = 2 * a.gamma + 1;
-  constexpr int NV = SAMPLE_PART / 256;
   auto locate = [&](int item, int& part, int& j, int& b) {       // (divisions by multiplication: items < 2^32 / 64)
     const int row = (a.nparts == 1) ? item : (int)__umulhi((unsigned)item, mag_parts);
     part = item - row * a.nparts;
     b = (int)__umulhi((unsigned)row, mag_rows); j = row - b * nrows;
   };
-  auto load = [&](int item, float4 (&v)[NV]) {
-    int part, j, b;
-    locate(min(item, items - 1), part, j, b);
-    load_part(a, b, j, part, lane, v);
-  };
-  auto reduce = [&](int item, float4 (&v)[NV]) {
+  auto load = [&](int item, PartRaw& t) {
     int part, j, b;
     locate(item, part, j, b);
-    reduce_part<false>(a, b, j, part, lane, v);
+    load_part<ANY>(accept_row(a, b, j), part * a.part_len, lane, a.V, t);
+  };
+  auto reduce = [&](int item, const PartRaw& t) {
+    int part, j, b;
+    locate(item, part, j, b);
+    const StepParams* prm = a.prm + b;
+    const float T = a.prm ? *(const __attribute__((address_space(4))) float*)&prm->temperature : a.temperature;
+    reduce_part<false>(a, b, j, part, lane, T, t);
   };
   int item = (int)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (item >= items) return;
-  float4 v0[NV], v1[NV];
-  load(item, v0);
-  for (;;) {
-    if (item + stride < items) load(item + stride, v1);
-    reduce(item, v0);
+  PartRaw t0, t1;
+  load(item, t0);
+  for (;;) {                                         // (behind the last one: this one's again, from the caches)
+    load(item + stride < items ? item + stride : item, t1);
+    __builtin_amdgcn_sched_barrier(0);
+    reduce(item, t0);
     item += stride;
     if (item >= items) return;
-    if (item + stride < items) load(item + stride, v0);
-    reduce(item, v1);
+    load(item + stride < items ? item + stride : item, t0);
+    __builtin_amdgcn_sched_barrier(0);
+    reduce(item, t1);
     item += stride;
     if (item >= items) return;
   }
@@ -1220,8 +1225,8 @@ static __global__ __launch_bounds__(256, 6) void beta_kernel(const AcceptArgs a)
 // itself (a few hundred words), then sums the weights of its chunks of row n (16 chunks_wave of
 // them); the last to arrive scans the totals and walks the chunk that holds u * total.
 // A small call is this one launch (OWN, launch_accept): a second one would cost it more than its work.
-// 64 sequences, gamma 7, vocabulary 32128 (123 MB), both launches, calls back to back in a graph: 35.7 us
-// (row_parts_kernel 24.5 to 27: 4.6 to 5 TB/s, where a pure read reaches 7); with one 1024-thread workgroup per row and
+// 64 sequences, gamma 7, vocabulary 32128 (123 MB), both launches, calls back to back: 33.0 us
+// (row_parts_kernel 22.8: 5.4 TB/s, where a pure read reaches 7); with one 1024-thread workgroup per row and
 // then one per sequence it was 42.2.  One sequence, gamma 4: 11.1 us against 16.8.
 enum { OWN_NONE, OWN_SEQUENCE, OWN_ROWS };           // whose the statistics are: row_parts_kernel's; this kernel's, a workgroup per sequence / per logits row
 template <int OWN>
@@ -1256,16 +1261,16 @@ static __global__ __launch_bounds__(SAMPLE_THREADS) void accept_kernel(const Acc
   }
   if (OWN == OWN_SEQUENCE) {
     for (int item = wave; item < nrows * a.nparts; item += SAMPLE_THREADS / 64) {
-      float4 v[SAMPLE_PART / 256];
-      load_part(a, b, item / a.nparts, item % a.nparts, lane, v);
-      reduce_part<false>(a, b, item / a.nparts, item % a.nparts, lane, v);
+      PartRaw t;
+      load_part<true>(accept_row(a, b, item / a.nparts), item % a.nparts * a.part_len, lane, V, t);
+      reduce_part<false>(a, b, item / a.nparts, item % a.nparts, lane, T, t);
     }
     __syncthreads();
   } else if (OWN == OWN_ROWS) {
     for (int part = wave; part < a.nparts; part += SAMPLE_THREADS / 64) {
-      float4 v[SAMPLE_PART / 256];
-      load_part(a, b, blockIdx.x, part, lane, v);
-      reduce_part<true>(a, b, blockIdx.x, part, lane, v);
+      PartRaw t;
+      load_part<true>(accept_row(a, b, blockIdx.x), part * a.part_len, lane, V, t);
+      reduce_part<true>(a, b, blockIdx.x, part, lane, T, t);
     }
     if (!last_to_post(scr->ticket, (unsigned)nrows, &sm.flag)) return;
   }
@@ -1446,8 +1451,10 @@ inline void launch_accept(hipStream_t stream, AcceptArgs a, int rows, int cus) {
     hipLaunchKernelGGL(row_filter_kernel, dim3(nrows, rows), dim3(SAMPLE_THREADS), 0, stream, a);
   } else if (own == OWN_NONE) {
     const int items = rows * nrows * a.nparts;
-    hipLaunchKernelGGL(row_parts_kernel, dim3(min((items + 3) / 4, cus * ACCEPT_WAVES_CU / 4)), dim3(256), 0, stream, a, items,
-                       (unsigned)((0x100000000ull + a.nparts - 1) / a.nparts), (unsigned)((0x100000000ull + nrows - 1) / nrows));
+    const dim3 parts_grid(min((items + 3) / 4, cus * ACCEPT_WAVES_CU / 4));
+    const unsigned mag_parts = (unsigned)((0x100000000ull + a.nparts - 1) / a.nparts), mag_rows = (unsigned)((0x100000000ull + nrows - 1) / nrows);
+    if (a.V < 4) hipLaunchKernelGGL((row_parts_kernel<true>), parts_grid, dim3(256), 0, stream, a, items, mag_parts, mag_rows);
+    else hipLaunchKernelGGL((row_parts_kernel<false>), parts_grid, dim3(256), 0, stream, a, items, mag_parts, mag_rows);
   }
   // as many workgroups a sequence as fit the CUs in one round; more only repeat the decisions more often
   // (200 sequences, gamma 1, vocabulary 32128: 35.3 us with one, 49.1 with a second that takes the last chunks), beside
