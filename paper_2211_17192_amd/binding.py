@@ -34,13 +34,18 @@ class SdError(RuntimeError):
 
 
 def _ptr(t):
-    if t is None:
-        return None
-    return C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()       # (every parameter that takes one is declared c_void_p)
+
+
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """The current stream of the current device as an address.  (torch.cuda.current_stream() makes a Stream object first:
+    3.3 us of a sample call's 9 to 12 on the host, against 0.3.)"""
+    if _raw_stream is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(torch.cuda.current_device())
 
 
 lib.sd_spec_sample_scratch_bytes.restype = C.c_size_t
