@@ -130,13 +130,14 @@ __device__ __forceinline__ double rescaled_sum(double s, float m, float M, float
 }
 
 // A row of up to 32768 entries fits the registers of one 1024-thread workgroup:
-// thread tid holds float4 number it * 1024 + tid, it = 0..7.  In terms of the
+// thread tid holds float4 number it * 1024 + tid, it = 0 .. NG - 1 (with_sample_groups: as many as the row needs).  In terms of the
 // 256-entry scan chunks, v[it] of wavefront w is lane-slice `lane` of chunk it * 16 + w.
-__device__ __forceinline__ void load_row_regs(const float* __restrict__ z, int V, float4 (&v)[SAMPLE_REG_F4]) {
+template <int NG>
+__device__ __forceinline__ void load_row_regs(const float* __restrict__ z, int V, float4 (&v)[NG]) {
   const float4* z4 = reinterpret_cast<const float4*>(z);
   const int n4 = V >> 2, tid = threadIdx.x;
 #pragma unroll
-  for (int it = 0; it < SAMPLE_REG_F4; ++it) {
+  for (int it = 0; it < NG; ++it) {
     const int i = it * SAMPLE_THREADS + tid;
     const float4 t = z4[min(i, n4 - 1)];           // unconditional load, padding by select
     v[it] = (i < n4) ? t : make_float4(-INFINITY, -INFINITY, -INFINITY, -INFINITY);
@@ -149,34 +150,24 @@ __device__ __forceinline__ void load_row_regs(const float* __restrict__ z, int V
 // bins.  each(f) calls f(key, weight) for this thread's entries, weight as a function.  False (in every
 // thread): all entries together weigh less.
 struct RadixSearch { unsigned tau; unsigned long long above; int step; };
-template <typename Each>
-__device__ __forceinline__ bool radix_step(RadixSearch& q, unsigned long long target, SampleSmem& sm, Each&& each) {
+// fill() adds weights to sm.bins and returns the target; then the bin in which the sum from the top, `above` at its beginning,
+// reaches it is left in sm.sel and what lies beyond it in sm.above.  False (in every thread): no bin does.
+template <typename Fill>
+__device__ __forceinline__ bool find_bin(unsigned long long above, SampleSmem& sm, Fill&& fill) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int shift = (q.step == 0) ? 21 : (q.step == 1) ? 10 : 0, bits = (q.step < 2) ? 11 : 10;
   __syncthreads();
   sm.bins[tid] = 0ull; sm.bins[tid + SAMPLE_THREADS] = 0ull;
   if (tid == 0) sm.sel = 0xffffffffu;
   __syncthreads();
-  const unsigned mask = (1u << bits) - 1u, top = (q.step == 0) ? 0u : q.tau >> (shift + bits);
-  each([&](unsigned k, auto&& weight) {
-    if (q.step == 0 || (k >> (shift + bits)) == top) {
-      const unsigned long long w = weight();
-      if (w != 0ull) atomicAdd(&sm.bins[(k >> shift) & mask], w);
-    }
-  });
+  const unsigned long long target = fill();
   __syncthreads();
   // sums from the top: thread tid owns two bins
   const int hi = SAMPLE_BINS - 1 - 2 * tid, lo = hi - 1;
   const unsigned long long bh = sm.bins[hi], bl = sm.bins[lo];
-  unsigned long long inc = bh + bl;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const unsigned long long t = __shfl_up(inc, o, WAVE);
-    if (lane >= o) inc += t;
-  }
+  const unsigned long long inc = wave_scan(bh + bl);
   if (lane == 63) sm.wsum[wave] = inc;
   __syncthreads();
-  unsigned long long before = q.above + inc - (bh + bl);
+  unsigned long long before = above + inc - (bh + bl);
   for (int w = 0; w < wave; ++w) before += sm.wsum[w];
   if (before < target && before + bh + bl >= target) {              // exactly one thread, if any
     const bool upper = before + bh >= target;
@@ -184,7 +175,21 @@ __device__ __forceinline__ bool radix_step(RadixSearch& q, unsigned long long ta
     sm.above = upper ? before : before + bh;
   }
   __syncthreads();
-  if (sm.sel == 0xffffffffu) return false;
+  return sm.sel != 0xffffffffu;
+}
+template <typename Each>
+__device__ __forceinline__ bool radix_step(RadixSearch& q, unsigned long long target, SampleSmem& sm, Each&& each) {
+  const int shift = (q.step == 0) ? 21 : (q.step == 1) ? 10 : 0, bits = (q.step < 2) ? 11 : 10;
+  const unsigned mask = (1u << bits) - 1u, top = (q.step == 0) ? 0u : q.tau >> (shift + bits);
+  if (!find_bin(q.above, sm, [&] {
+        each([&](unsigned k, auto&& weight) {
+          if (q.step == 0 || (k >> (shift + bits)) == top) {
+            const unsigned long long w = weight();
+            if (w != 0ull) atomicAdd(&sm.bins[(k >> shift) & mask], w);
+          }
+        });
+        return target;
+      })) return false;
   q.tau |= sm.sel << shift;
   q.above = sm.above;
   ++q.step;
@@ -192,14 +197,14 @@ __device__ __forceinline__ bool radix_step(RadixSearch& q, unsigned long long ta
 }
 // Puts the keys of this thread's entries that `want` into the list (order: whatever; the sums are
 // integers); the number of them, which may exceed the list's room.
-template <typename Want>
-__device__ __forceinline__ int list_entries(const float4 (&v)[SAMPLE_REG_F4], int nv4, SampleSmem& sm, Want&& want) {
+template <int NG, typename Want>
+__device__ __forceinline__ int list_entries(const float4 (&v)[NG], int nv4, SampleSmem& sm, Want&& want) {
   const int tid = threadIdx.x;
   __syncthreads();
   if (tid == 0) sm.listed = 0;
   __syncthreads();
 #pragma unroll
-  for (int it = 0; it < SAMPLE_REG_F4; ++it) {
+  for (int it = 0; it < NG; ++it) {
     const float z[4] = {v[it].x, v[it].y, v[it].z, v[it].w};
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
@@ -238,12 +243,7 @@ __device__ __forceinline__ bool list_search(RadixSearch& q, int bits, unsigned l
 #pragma unroll
     for (int e = 0; e < 4; ++e) b[e] = bins[255 - 4 * lane - e];
     const unsigned long long own = b[0] + b[1] + b[2] + b[3];
-    unsigned long long inc = own;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-      const unsigned long long t = __shfl_up(inc, o, WAVE);
-      if (lane >= o) inc += t;
-    }
+    const unsigned long long inc = wave_scan(own);
     unsigned long long before = q.above + inc - own;
     const bool here = before < target && before + own >= target;
     const unsigned long long who = __ballot(here);
@@ -263,12 +263,12 @@ __device__ __forceinline__ bool list_search(RadixSearch& q, int bits, unsigned l
 // Most rows are settled on a short list, by one wavefront: filter_fast's (`listed`, on entry: the list holds every entry with a
 // key >= tau, whichever tau will be), else the entries that share the first 11 bits of tau.  A row that overflows
 // the list (ties) is searched in the registers to the end.
-template <typename W>
-__device__ __forceinline__ unsigned filter_threshold(const float4 (&v)[SAMPLE_REG_F4], int nv4, unsigned long long target, SampleSmem& sm, bool listed, W&& weight) {
+template <int NG, typename W>
+__device__ __forceinline__ unsigned filter_threshold(const float4 (&v)[NG], int nv4, unsigned long long target, SampleSmem& sm, bool listed, W&& weight) {
   const int tid = threadIdx.x, wave = tid >> 6;
   auto in_regs = [&](auto&& f) {
 #pragma unroll
-    for (int it = 0; it < SAMPLE_REG_F4; ++it) {
+    for (int it = 0; it < NG; ++it) {
       const float z[4] = {v[it].x, v[it].y, v[it].z, v[it].w};
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
@@ -301,18 +301,54 @@ __device__ __forceinline__ unsigned filter_threshold(const float4 (&v)[SAMPLE_RE
   return q.tau;
 }
 
+// The wavefront's keys (N = 1 or 2 a lane, key i in lane i % 64) in descending order: a bitonic network whose exchanges stay in
+// the vector ALU.
+template <int OFF> __device__ __forceinline__ unsigned xor_partner(unsigned v, int lane) {
+  if (OFF == 4) return (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)__builtin_amdgcn_mov_dpp((int)v, 0x141, 0xf, 0xf, true), 0x1b, 0xf, 0xf, true);     // lane ^ 7, ^ 3
+  if (OFF < 16) return dpp_partner<OFF == 4 ? 1 : OFF>(v);
+  const u32x2 r = half_swap<OFF < 16 ? 16 : OFF>(v); // {own, partner} in an order that depends on the lane
+  return (lane & OFF) ? r.x : r.y;
+}
+template <int N>
+__device__ __forceinline__ void sort_keys(unsigned (&k)[N]) {
+  const int lane = threadIdx.x & 63;
+  auto exchange = [&](auto off, auto run) {          // runs of `run` keys: the even ones descending, the odd ones ascending
+    constexpr int OFF = decltype(off)::value, RUN = decltype(run)::value;
+#pragma unroll
+    for (int r = 0; r < N; ++r) {
+      const unsigned o = xor_partner<OFF>(k[r], lane);
+      const bool down = ((lane + 64 * r) & RUN) == 0, low = (lane & OFF) == 0;
+      k[r] = (down == low) ? max(k[r], o) : min(k[r], o);
+    }
+  };
+  auto merge = [&](auto run) {
+    constexpr int RUN = decltype(run)::value;
+    if constexpr (RUN == 128) { const unsigned a = max(k[0], k[N - 1]), b = min(k[0], k[N - 1]); k[0] = a; k[N - 1] = b; }
+    if constexpr (RUN >= 64) exchange(std::integral_constant<int, 32>(), run);
+    if constexpr (RUN >= 32) exchange(std::integral_constant<int, 16>(), run);
+    if constexpr (RUN >= 16) exchange(std::integral_constant<int, 8>(), run);
+    if constexpr (RUN >= 8) exchange(std::integral_constant<int, 4>(), run);
+    if constexpr (RUN >= 4) exchange(std::integral_constant<int, 2>(), run);
+    exchange(std::integral_constant<int, 1>(), run);
+  };
+  merge(std::integral_constant<int, 2>()); merge(std::integral_constant<int, 4>()); merge(std::integral_constant<int, 8>());
+  merge(std::integral_constant<int, 16>()); merge(std::integral_constant<int, 32>()); merge(std::integral_constant<int, 64>());
+  if constexpr (N == 2) merge(std::integral_constant<int, 128>());
+}
+
 // Top-k: the threads' own maxima go into 256 linear bins between the largest and the smallest of
 // them; the bin that holds the top_k-th bounds the top_k-th largest entry from below, so few entries are listed
 // (top_k to a dozen more).  Where they are no more than two a lane, wavefront 0 settles both filters in its
-// registers: it finds the top_k-th largest key bit by bit with ballots, and for the nucleus gives every entry the weight of
-// the entries that are not below it.
+// registers: it sorts the keys, so that the top_k-th is one lane's and the nucleus one sum in lane order.
 // False (in every thread): more are listed than that, and the list is where filter_threshold goes on (`listed`), or more than the
 // list has room for (ties), or the maximum is no finite number.
 // (16 rows x 11, vocabulary 32000, top_k 50, top_p 0.95: searches over bins of key bits took 22.6 us, eight
-// steps of one wavefront each with every key in one or two bins of the first; now 13.6.  A whole call of one sequence, gamma 4,
-// with top_k 128, some 140 listed: 27.8 us with those searches, 31.5 when a list too long for registers was thrown away, now 21.4.)
+// steps of one wavefront each with every key in one or two bins of the first; 13.8 where the top_k-th key was found bit by bit with
+// ballots and every lane added up, entry by entry, what is not below its own; now 8.3.  Whole calls: 60 sequences, gamma 7, vocabulary
+// 3000, top_k 50 32.6 -> 16.4; one, gamma 4, 32128, top_k 128, some 140 listed: 31.5 when a list too long for registers was thrown away, then 21.4.)
 constexpr int SAMPLE_FAST_LIST = 128;
-__device__ __forceinline__ bool filter_fast(const float4 (&v)[SAMPLE_REG_F4], int nv4, float best, float m, float invT, int top_k, float top_p,
+template <int NG>
+__device__ __forceinline__ bool filter_fast(const float4 (&v)[NG], int nv4, float best, float m, float invT, int top_k, float top_p,
                                             SampleSmem& sm, RowStat& st, bool& listed) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, real = min(nv4, SAMPLE_THREADS);
   if (tid == 0) sm.listed = 0;
@@ -332,12 +368,7 @@ __device__ __forceinline__ bool filter_fast(const float4 (&v)[SAMPLE_REG_F4], in
       unsigned own[4], sum = 0u;
 #pragma unroll
       for (int e = 0; e < 4; ++e) { own[e] = bins[lane * 4 + e]; sum += own[e]; }
-      unsigned inc = sum;
-#pragma unroll
-      for (int o = 1; o < 64; o <<= 1) {
-        const unsigned t = __shfl_up(inc, o, WAVE);
-        if (lane >= o) inc += t;
-      }
+      const unsigned inc = wave_scan(sum);
       unsigned before = inc - sum;
       if (before < (unsigned)top_k && inc >= (unsigned)top_k) {                  // exactly one lane
         int e = 0;
@@ -353,7 +384,7 @@ __device__ __forceinline__ bool filter_fast(const float4 (&v)[SAMPLE_REG_F4], in
     __syncthreads();
   }
 #pragma unroll
-  for (int it = 0; it < SAMPLE_REG_F4; ++it) {
+  for (int it = 0; it < NG; ++it) {
     const bool hit = !(v[it].x < bound) || !(v[it].y < bound) || !(v[it].z < bound) || !(v[it].w < bound);
     if (!__any(hit)) continue;
     const float z[4] = {v[it].x, v[it].y, v[it].z, v[it].w};
@@ -368,51 +399,57 @@ __device__ __forceinline__ bool filter_fast(const float4 (&v)[SAMPLE_REG_F4], in
   const int n = sm.listed;
   if (n > SAMPLE_FAST_LIST) { listed = n <= SAMPLE_LIST; return false; }       // (uniform)
   if (wave == 0) {
-    const bool ok0 = lane < n, ok1 = lane + 64 < n;
-    const unsigned k0 = ok0 ? sm.list[lane] : 0u, k1 = ok1 ? sm.list[lane + 64] : 0u;
-    unsigned tau = 0u;                                // the largest key that top_k listed ones reach
-    for (int bit = 31; bit >= 0; --bit) {
-      const unsigned t = tau | (1u << bit);
-      if (__popcll(__ballot(ok0 && k0 >= t)) + __popcll(__ballot(ok1 && k1 >= t)) >= top_k) tau = t;
-    }
-    float thr = tau ? key_float(tau) : -INFINITY;    // (fewer listed than top_k: the others weigh nothing)
-    auto weight = [&](unsigned k, bool ok) { return ok ? exp_scaled(key_float(k), m, invT, thr) : 0.0f; };
-    // the sum, in whole numbers of 2^-56 (a weight is at most 1, the list holds 128): the list's order, which is how the
-    // wavefronts happened to arrive, does not show in it
-    auto whole = [](float e) {                       // 31 + 25 bits, to nearest
-      const float t = e * 0x1p31f;
-      const unsigned hi = (unsigned)t;
-      return ((unsigned long long)hi << 25) + (unsigned)rintf((t - (float)hi) * 0x1p25f);
-    };
-    auto total = [&](float a, float b) { return (double)wave_sum(whole(a) + whole(b)) * 0x1p-56; };
-    float e0 = weight(k0, ok0), e1 = weight(k1, ok1);
-    double S = total(e0, e1);
-    if (top_p > 0.0f && top_p < 1.0f) {
-      constexpr double UNIT = 17592186044416.0;      // weights in units of 2^-44 of the largest, as 31 + 13 bits
-      auto units = [](float e) {
-        const float t = e * 2147483648.0f;
-        const unsigned hi = (unsigned)t;
-        return ((unsigned long long)hi << 13) | (unsigned long long)(unsigned)((t - (float)hi) * 8192.0f);
-      };
-      const unsigned long long target = (unsigned long long)((double)top_p * S * UNIT), u0 = units(e0), u1 = units(e1);
-      unsigned long long w0 = 0ull, w1 = 0ull;        // what the entries not below this lane's weigh
-      for (int i = 0; i < n; ++i) {
-        const unsigned k = __builtin_amdgcn_readlane(i < 64 ? k0 : k1, i & 63);
-        const unsigned long long u = i < 64 ? u0 : u1;
-        const unsigned long long ui = (unsigned long long)(unsigned)__builtin_amdgcn_readlane((unsigned)u, i & 63) |
-                                      ((unsigned long long)(unsigned)__builtin_amdgcn_readlane((unsigned)(u >> 32), i & 63) << 32);
-        w0 += (k >= k0) ? ui : 0ull;
-        if (n > 64) w1 += (k >= k1) ? ui : 0ull;
-      }
-      // the largest key whose upper set reaches the target (entries that top-k dropped weigh nothing and lie below)
-      unsigned best_key = max((ok0 && w0 >= target) ? k0 : 0u, (ok1 && w1 >= target) ? k1 : 0u);
+    auto settle = [&](auto words) {                  // one key a lane, or two
+      constexpr int N = decltype(words)::value;
+      unsigned k[N];
 #pragma unroll
-      for (int o = 32; o; o >>= 1) best_key = max(best_key, (unsigned)__shfl_xor((int)best_key, o, WAVE));
-      thr = fmaxf(best_key ? key_float(best_key) : -INFINITY, thr);
-      e0 = weight(k0, ok0); e1 = weight(k1, ok1);
-      S = total(e0, e1);
-    }
-    if (lane == 0) { sm.total = S; sm.sel = __float_as_uint(thr); }
+      for (int r = 0; r < N; ++r) k[r] = (lane + 64 * r < n) ? sm.list[lane + 64 * r] : 0u;      // (0: no float's key but a NaN's; sorts behind all)
+      sort_keys(k);
+      // the top_k-th key; fewer listed than top_k: the others weigh nothing
+      const unsigned tau = top_k <= n ? (top_k <= 64 ? __builtin_amdgcn_readlane(k[0], (top_k - 1) & 63) : __builtin_amdgcn_readlane(k[N - 1], (top_k - 1) & 63)) : 0u;
+      float thr = tau ? key_float(tau) : -INFINITY;
+      float e[N];
+      // the sum, in whole numbers of 2^-56 (a weight is at most 1, the list holds 128), as the nucleus's are: exact whatever the order
+      auto whole = [](float x) {                     // 31 + 25 bits, to nearest
+        const float t = x * 0x1p31f;
+        const unsigned hi = (unsigned)t;
+        return ((unsigned long long)hi << 25) + (unsigned)rintf((t - (float)hi) * 0x1p25f);
+      };
+      auto total = [&] {
+        unsigned long long t = 0ull;
+#pragma unroll
+        for (int r = 0; r < N; ++r) {
+          e[r] = (lane + 64 * r < n) ? exp_scaled(key_float(k[r]), m, invT, thr) : 0.0f;
+          t += whole(e[r]);
+        }
+        return (double)wave_sum(t) * 0x1p-56;
+      };
+      double S = total();
+      if (top_p > 0.0f && top_p < 1.0f) {
+        constexpr double UNIT = 17592186044416.0;    // weights in units of 2^-44 of the largest, as 31 + 13 bits
+        auto units = [](float x) {
+          const float t = x * 2147483648.0f;
+          const unsigned hi = (unsigned)t;
+          return ((unsigned long long)hi << 13) | (unsigned long long)(unsigned)((t - (float)hi) * 8192.0f);
+        };
+        const unsigned long long target = (unsigned long long)((double)top_p * S * UNIT);
+        // the first key at which the sum from the top reaches the target (equal keys share the threshold, wherever the sum
+        // reaches it among them); entries that top-k dropped weigh nothing
+        unsigned long long before = 0ull;
+        unsigned best_key = 0u;
+#pragma unroll
+        for (int r = 0; r < N; ++r) {
+          const unsigned long long upto = before + wave_scan(units(e[r])), who = __ballot(lane + 64 * r < n && upto >= target);
+          if (who != 0ull && best_key == 0u) best_key = __builtin_amdgcn_readlane(k[r], __ffsll((long long)who) - 1);
+          before = lane_value(upto, 63);
+        }
+        thr = fmaxf(best_key ? key_float(best_key) : -INFINITY, thr);
+        S = total();
+      }
+      if (lane == 0) { sm.total = S; sm.sel = __float_as_uint(thr); }
+    };
+    if (n <= 64) settle(std::integral_constant<int, 1>());
+    else settle(std::integral_constant<int, 2>());
   }
   __syncthreads();
   st.S = sm.total;
@@ -421,18 +458,102 @@ __device__ __forceinline__ bool filter_fast(const float4 (&v)[SAMPLE_REG_F4], in
   return true;
 }
 
+// The nucleus of a row that top-k leaves whole: as filter_threshold, but the first bins are linear in the logit, from the maximum to
+// where weights are zero (or to the smallest entry, zmin).  Bins of key bits hold a row's bulk in a few dozen of 2048, and
+// hundreds of LDS additions to one address wait for one another; in linear bins they spread, and the bin that decides holds a
+// few dozen entries, which one wavefront sorts.  The row's sum, which the target hangs on, is taken in the same pass.  units(e): the
+// weight as an integer.  The thresholds are the same (exact sums, and the bin of an entry never decreases as the logit falls).
+// False (in every thread): left to filter_threshold.
+// Whole calls, top_p 0.9: one sequence, gamma 4, vocabulary 32128 36.1 -> 23.4 us; 16, gamma 2, 19424 26.8 -> 21.2; 15, gamma 7,
+// 4720 23.9 -> 16.1 (with as many groups a thread as the row needs; eight 19.3); 64, gamma 7, 32128 93.8 -> 75.9.
+template <int NG, typename U>
+__device__ __forceinline__ bool nucleus_bins(const float4 (&v)[NG], int nv4, float m, float zmin, float invT, double top_p_units,
+                                             SampleSmem& sm, unsigned& tau, U&& units) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  // (exp(-31) is below half a unit of 2^-44)
+  const float span = fmaxf(fminf(31.0f * __builtin_amdgcn_rcpf(invT), m - zmin), 1e-6f * fabsf(m) + 1e-30f);
+  const float c = (float)(SAMPLE_BINS - 1) * __builtin_amdgcn_rcpf(span);
+  if (!(m - m == 0.0f && span < 1e34f)) return false;                            // (uniform; 1 / span must be a number of its own)
+  auto bin = [&](float z) { return (unsigned)(SAMPLE_BINS - 1 - (int)fminf((m - z) * c, (float)(SAMPLE_BINS - 1))); };
+  auto each = [&](auto&& f) {
+#pragma unroll
+    for (int it = 0; it < NG; ++it) {
+      const float z[4] = {v[it].x, v[it].y, v[it].z, v[it].w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) f(z[e], it * SAMPLE_THREADS + tid < nv4);
+    }
+  };
+  auto weight = [&](float z) { return exp_scaled(z, m, invT, -INFINITY); };
+  unsigned long long target = 0ull;
+  if (!find_bin(0ull, sm, [&] {
+        float s = 0.0f;                              // (as row_stats_regs adds)
+#pragma unroll
+        for (int it = 0; it < NG; ++it) {
+          const float z[4] = {v[it].x, v[it].y, v[it].z, v[it].w}, e[4] = {weight(z[0]), weight(z[1]), weight(z[2]), weight(z[3])};
+          s += (e[0] + e[1]) + (e[2] + e[3]);
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const unsigned long long w = (it * SAMPLE_THREADS + tid < nv4) ? units(e[i]) : 0ull;
+            if (w != 0ull) atomicAdd(&sm.bins[bin(z[i])], w);
+          }
+        }
+        target = (unsigned long long)(top_p_units * block_reduce((double)s, sm.redd, OpSumD(), 0.0));
+        return target;
+      })) return false;
+  const unsigned sel = sm.sel;
+  const unsigned long long above = sm.above;
+  __syncthreads();
+  if (tid == 0) sm.listed = 0;
+  __syncthreads();
+  each([&](float z, bool ok) {
+    if (ok && bin(z) == sel && units(weight(z)) != 0ull) {
+      const int i = atomicAdd(&sm.listed, 1);
+      if (i < SAMPLE_LIST) sm.list[i] = float_key(z);
+    }
+  });
+  __syncthreads();
+  const int n = sm.listed;
+  if (n > SAMPLE_LIST) return false;                 // (uniform)
+  if (wave == 0) {
+    unsigned found = 0u;
+    if (n <= SAMPLE_FAST_LIST) {
+      unsigned k[2];
+#pragma unroll
+      for (int r = 0; r < 2; ++r) k[r] = (lane + 64 * r < n) ? sm.list[lane + 64 * r] : 0u;
+      sort_keys(k);
+      unsigned long long before = above;
+#pragma unroll
+      for (int r = 0; r < 2; ++r) {
+        const bool ok = lane + 64 * r < n;
+        const unsigned long long upto = before + wave_scan(ok ? units(weight(key_float(k[r]))) : 0ull), who = __ballot(ok && upto >= target);
+        if (who != 0ull && found == 0u) found = __builtin_amdgcn_readlane(k[r], __ffsll((long long)who) - 1);
+        before = lane_value(upto, 63);
+      }
+    } else {
+      RadixSearch q{0u, above, 0};
+      if (list_search(q, 32, target, sm.list, n, sm, [&](unsigned k) { return units(weight(key_float(k))); })) found = q.tau;
+    }
+    if (lane == 0) sm.sel = found;
+  }
+  __syncthreads();
+  tau = sm.sel;
+  __syncthreads();
+  return true;
+}
+
 // top_k > 0 / 0 < top_p < 1 (section 2.2: top-k and nucleus sampling as an adjusted
 // distribution): the kept set is {z >= thr}.  Top-k: thr = k-th largest logit.  Nucleus, applied to
 // what top-k left: thr = the largest value whose upper set still carries top_p of the mass (in units
 // of 2^-44 of the largest entry's).  Ties with the last kept entry are kept.  Argmax sampling
 // ignores both.
-__device__ __forceinline__ RowStat row_stats_regs(const float4 (&v)[SAMPLE_REG_F4], float invT, bool greedy,
+template <int NG>
+__device__ __forceinline__ RowStat row_stats_regs(const float4 (&v)[NG], float invT, bool greedy,
                                                   SampleSmem& sm, int top_k = 0, float top_p = 0.0f, int V = 0) {
   const int tid = threadIdx.x;
   RowStat st; st.arg = 0; st.S = 0.0; st.thr = -INFINITY; st.pad = 0.0f;
   float m = -INFINITY;
 #pragma unroll
-  for (int it = 0; it < SAMPLE_REG_F4; ++it)
+  for (int it = 0; it < NG; ++it)
     m = fmaxf(m, fmaxf(fmaxf(v[it].x, v[it].y), fmaxf(v[it].z, v[it].w)));
   const float best = m;
   m = block_reduce(m, sm.redf, OpMaxF(), -INFINITY);
@@ -440,7 +561,7 @@ __device__ __forceinline__ RowStat row_stats_regs(const float4 (&v)[SAMPLE_REG_F
   if (greedy) {
     int a = INT_MAX;
 #pragma unroll
-    for (int it = SAMPLE_REG_F4 - 1; it >= 0; --it) {
+    for (int it = NG - 1; it >= 0; --it) {
       const int k = (it * SAMPLE_THREADS + tid) * 4;
       if (v[it].w == m) a = k + 3;
       if (v[it].z == m) a = k + 2;
@@ -461,7 +582,7 @@ __device__ __forceinline__ RowStat row_stats_regs(const float4 (&v)[SAMPLE_REG_F
   auto mass = [&] {
     float s = 0.0f;
 #pragma unroll
-    for (int it = 0; it < SAMPLE_REG_F4; ++it) {     // exp(-inf) = 0 for the padding
+    for (int it = 0; it < NG; ++it) {     // exp(-inf) = 0 for the padding
       // (a filtered row keeps few entries: most wavefronts have none in a group of 256)
       if (thr != -INFINITY && !__any(v[it].x >= thr || v[it].y >= thr || v[it].z >= thr || v[it].w >= thr)) continue;
       s += (exp_scaled(v[it].x, m, invT, thr) + exp_scaled(v[it].y, m, invT, thr)) +
@@ -469,15 +590,29 @@ __device__ __forceinline__ RowStat row_stats_regs(const float4 (&v)[SAMPLE_REG_F
     }
     return block_reduce((double)s, sm.redd, OpSumD(), 0.0);
   };
+  const bool nucleus = top_p > 0.0f && top_p < 1.0f;
+  unsigned tau = 0u;
+  bool settled = false;
+  constexpr double UNIT = 17592186044416.0;          // 2^44: 32768 entries of at most 1 stay below 2^60
+  auto units = [](float e) {                         // e * 2^44 as 31 + 13 bits
+    const float t = e * 2147483648.0f;
+    const unsigned hi = (unsigned)t;
+    return ((unsigned long long)hi << 13) | (unsigned long long)(unsigned)((t - (float)hi) * 8192.0f);
+  };
+  if (nucleus && thr == -INFINITY) {                 // (uniform)
+    float zmin = m;
+#pragma unroll
+    for (int it = 0; it < NG; ++it)
+      if (it * SAMPLE_THREADS + tid < nv4) zmin = fminf(zmin, fminf(fminf(v[it].x, v[it].y), fminf(v[it].z, v[it].w)));
+    zmin = -block_reduce(-zmin, sm.redf, OpMaxF(), -INFINITY);
+    settled = nucleus_bins(v, nv4, m, zmin, invT, (double)top_p * UNIT, sm, tau, units);
+    if (settled) thr = tau ? key_float(tau) : -INFINITY;
+  }
   double S = mass();
-  if (top_p > 0.0f && top_p < 1.0f) {
-    constexpr double UNIT = 17592186044416.0;        // 2^44: 32768 entries of at most 1 stay below 2^60
+  if (nucleus && !settled) {
     const float floor_thr = thr;                     // what top-k dropped stays dropped
-    const unsigned tau = filter_threshold(v, nv4, (unsigned long long)((double)top_p * S * UNIT), sm, listed, [&](unsigned k) {
-      // e * 2^44 as 31 + 13 bits
-      const float t = exp_scaled(key_float(k), m, invT, floor_thr) * 2147483648.0f;
-      const unsigned hi = (unsigned)t;
-      return ((unsigned long long)hi << 13) | (unsigned long long)(unsigned)((t - (float)hi) * 8192.0f);
+    tau = filter_threshold(v, nv4, (unsigned long long)((double)top_p * S * UNIT), sm, listed, [&](unsigned k) {
+      return units(exp_scaled(key_float(k), m, invT, floor_thr));
     });
     thr = fmaxf(tau ? key_float(tau) : -INFINITY, floor_thr);
     S = mass();
@@ -506,23 +641,35 @@ __device__ __forceinline__ RawPair load4(const RowPair& rp, int k) {
   return t;
 }
 
-__device__ __forceinline__ void calc4(const RowPair& rp, int k, const RawPair& t, double (&w)[4]) {
-  const float4 p4 = placed4_row(t.p, k, rp.V), q4 = placed4_row(t.q, k, rp.V);
-  const float zp[4] = {p4.x, p4.y, p4.z, p4.w}, zq[4] = {q4.x, q4.y, q4.z, q4.w};
-#pragma unroll
-  for (int e = 0; e < 4; ++e) {
-    double p = (k + e < rp.V) ? (double)exp_scaled(zp[e], rp.mp, rp.invT, rp.tp) * rp.invSp : 0.0;
-    if (rp.zq) {
-      const double q = (k + e < rp.V) ? (double)exp_scaled(zq[e], rp.mq, rp.invT, rp.tq) * rp.invSq : 0.0;
-      p -= q;
-      p = p > 0.0 ? p : 0.0;
+// c: the chunk (uniform) that the wavefront's four entries a lane are of; only the row's last one has entries to move or to leave
+// out.  No branch but the uniform ones: a weight behind one each was half of the kernel's instructions.
+__device__ __forceinline__ void calc4(const RowPair& rp, int c, const RawPair& t, double (&w)[4]) {
+  const int k = c * SAMPLE_CHUNK + (int)(threadIdx.x & 63) * 4;
+  const bool whole = (c + 1) * SAMPLE_CHUNK <= rp.V;
+  auto weights = [&](const f32x4_any& raw, float m, float thr, double inv, double (&o)[4]) {
+    float z[4] = {raw[0], raw[1], raw[2], raw[3]};
+    if (!whole) {
+      const float4 p = placed4_row(raw, k, rp.V);
+      z[0] = p.x; z[1] = p.y; z[2] = p.z; z[3] = p.w;
     }
-    w[e] = p;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) o[e] = (double)exp_scaled(z[e], m, rp.invT, thr) * inv;
+  };
+  weights(t.p, rp.mp, rp.tp, rp.invSp, w);
+  if (rp.zq) {
+    double q[4];
+    weights(t.q, rp.mq, rp.tq, rp.invSq, q);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { w[e] -= q[e]; w[e] = w[e] > 0.0 ? w[e] : 0.0; }
+  }
+  if (!whole) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) w[e] = (k + e < rp.V) ? w[e] : 0.0;
   }
 }
 
-__device__ __forceinline__ void weights4(const RowPair& rp, int k, double (&w)[4]) {
-  calc4(rp, k, load4(rp, k), w);
+__device__ __forceinline__ void weights4(const RowPair& rp, int c, double (&w)[4]) {
+  calc4(rp, c, load4(rp, c * SAMPLE_CHUNK + (int)(threadIdx.x & 63) * 4), w);
 }
 
 // Wavefront 0: scan the chunk totals (lane l owns chunks [l*cpl, (l+1)*cpl)), find the
@@ -535,13 +682,7 @@ __device__ __forceinline__ void scan_chunk_totals(int nchunks, float u, SampleSm
   const int c0 = min(nchunks, lane * cpl), c1 = min(nchunks, c0 + cpl);
   double local = 0.0;
   for (int c = c0; c < c1; ++c) local += sm.ctot[c];
-  double inc = local;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const double t = __shfl_up(inc, o, WAVE);
-    if (lane >= o) inc += t;
-  }
-  const double total = __shfl(inc, 63, WAVE);
+  const double inc = wave_scan(local), total = lane_value(inc, 63);
   const double theta = (double)u * total;
   double cum = inc - local;
   int found = INT_MAX;
@@ -569,12 +710,7 @@ __device__ __forceinline__ int pick_in_chunk(const double (&w)[4], int k, int V,
                                              double before) {
   const int lane = threadIdx.x & 63;
   const double local = (w[0] + w[1]) + (w[2] + w[3]);
-  double inc = local;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const double t = __shfl_up(inc, o, WAVE);
-    if (lane >= o) inc += t;
-  }
+  const double inc = wave_scan(local);
   int cand = INT_MAX;
   if (!fallback) {
     double cum = before + (inc - local);
@@ -603,14 +739,14 @@ __device__ __forceinline__ int pick_in_chunk(const double (&w)[4], int k, int V,
 __device__ __forceinline__ int icdf_row(const float* zp, const RowStat& sp, const float* zq,
                                         const RowStat& sq, float invT, int V, float u,
                                         SampleSmem& sm, double qscale = 1.0) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nw = blockDim.x >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nw = blockDim.x >> 6;
   RowPair rp;
   rp.zp = zp; rp.zq = zq; rp.mp = sp.m; rp.mq = sq.m; rp.tp = sp.thr; rp.tq = sq.thr;
   rp.invSp = 1.0 / sp.S; rp.invSq = zq ? qscale / sq.S : 0.0;     // q enters the residual as qscale * q
   rp.invT = invT; rp.V = V;
   const int nchunks = (V + SAMPLE_CHUNK - 1) / SAMPLE_CHUNK;
   __syncthreads();
-  constexpr int CB = 4;                          // chunks whose loads a wavefront keeps in flight
+  constexpr int CB = 2;                          // chunks whose loads a wavefront keeps in flight
   for (int cb = wave; cb < nchunks; cb += nw * CB) {
     RawPair raw[CB];
 #pragma unroll
@@ -623,7 +759,7 @@ __device__ __forceinline__ int icdf_row(const float* zp, const RowStat& sp, cons
       const int c = cb + u * nw;
       if (c < nchunks) {
         double w[4];
-        calc4(rp, c * SAMPLE_CHUNK + lane * 4, raw[u], w);
+        calc4(rp, c, raw[u], w);
         const double t = wave_sum((w[0] + w[1]) + (w[2] + w[3]));
         if (lane == 0) sm.ctot[c] = t;
       }
@@ -637,10 +773,10 @@ __device__ __forceinline__ int icdf_row(const float* zp, const RowStat& sp, cons
   const int chunk = sm.chunk;
   if (wave == 0) {
     const bool fallback = chunk < 0;          // threshold not reached by round-off
-    const int c = fallback ? (-1 - chunk) : chunk;
+    const int c = __builtin_amdgcn_readfirstlane(fallback ? (-1 - chunk) : chunk);
     const int k = c * SAMPLE_CHUNK + lane * 4;
     double w[4];
-    weights4(rp, k, w);
+    weights4(rp, c, w);
     const int tok = pick_in_chunk(w, k, V, fallback, (double)u * total, sm.before);
     if (lane == 0) sm.token = tok;
   }
@@ -665,8 +801,9 @@ __device__ __forceinline__ void weights_of(const float4& zp, const float4& zq, b
   }
 }
 
-__device__ __forceinline__ int icdf_regs(const float4 (&vp)[SAMPLE_REG_F4], const RowStat& sp,
-                                         const float4 (&vq)[SAMPLE_REG_F4], const RowStat& sq, bool with_q,
+template <int NG>
+__device__ __forceinline__ int icdf_regs(const float4 (&vp)[NG], const RowStat& sp,
+                                         const float4 (&vq)[NG], const RowStat& sq, bool with_q,
                                          float invT, int V, float u, SampleSmem& sm, double qscale = 1.0) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   constexpr int NW = SAMPLE_THREADS / 64;
@@ -674,7 +811,7 @@ __device__ __forceinline__ int icdf_regs(const float4 (&vp)[SAMPLE_REG_F4], cons
   const int nchunks = (V + SAMPLE_CHUNK - 1) / SAMPLE_CHUNK;
   __syncthreads();
 #pragma unroll
-  for (int it = 0; it < SAMPLE_REG_F4; ++it) {
+  for (int it = 0; it < NG; ++it) {
     const int c = it * NW + wave;
     double w[4];
     weights_of(vp[it], vq[it], with_q, sp.m, sq.m, sp.thr, sq.thr, invSp, invSq, invT, w);
@@ -692,7 +829,7 @@ __device__ __forceinline__ int icdf_regs(const float4 (&vp)[SAMPLE_REG_F4], cons
   if (wave == c % NW) {
     double w[4] = {0.0, 0.0, 0.0, 0.0};
 #pragma unroll
-    for (int it = 0; it < SAMPLE_REG_F4; ++it)
+    for (int it = 0; it < NG; ++it)
       if (it == c / NW) weights_of(vp[it], vq[it], with_q, sp.m, sq.m, sp.thr, sq.thr, invSp, invSq, invT, w);
     const int tok = pick_in_chunk(w, c * SAMPLE_CHUNK + lane * 4, V, fallback, (double)u * total, sm.before);
     if (lane == 0) sm.token = tok;
@@ -912,6 +1049,7 @@ static __global__ __launch_bounds__(SAMPLE_THREADS) void sample_row_split_kernel
   }
 }
 
+template <int NG>
 static __global__ __launch_bounds__(SAMPLE_THREADS) void sample_row_filter_kernel(
     const float* __restrict__ logits, int V, const StepParams* __restrict__ prm, int uniform_idx,
     SeqState* __restrict__ st, int mode, int slot, size_t seq_stride) {
@@ -922,7 +1060,7 @@ static __global__ __launch_bounds__(SAMPLE_THREADS) void sample_row_filter_kerne
   const float T = prm->temperature;
   const bool greedy = (T == 0.0f);                   // (ignores the filters)
   const float invT = greedy ? 1.0f : 1.0f / T;
-  float4 v[SAMPLE_REG_F4];
+  float4 v[NG];
   load_row_regs(logits, V, v);
   const RowStat rs = row_stats_regs(v, invT, greedy, sm, prm->top_k, prm->top_p, V);
   const int tok = greedy ? rs.arg : icdf_regs(v, rs, v, rs, false, invT, V, prm->uniforms[uniform_idx], sm);
@@ -1104,13 +1242,14 @@ static __global__ __launch_bounds__(256, 6) void row_parts_kernel(const AcceptAr
 
 // Top-k / nucleus rows: the search needs the whole row, so one workgroup holds it in registers.
 // grid = (2 gamma + 1, rows).
+template <int NG>
 static __global__ __launch_bounds__(SAMPLE_THREADS) void row_filter_kernel(const AcceptArgs a) {
   __shared__ SampleSmem sm;
   const int j = blockIdx.x, b = blockIdx.y;
   const float T = a.prm ? a.prm[b].temperature : a.temperature;
   const bool greedy = (T == 0.0f);                   // (ignores the filters)
   if (greedy && j > a.gamma && a.beta == nullptr) return;
-  float4 v[SAMPLE_REG_F4];
+  float4 v[NG];
   load_row_regs(accept_row(a, b, j), a.V, v);
   const RowStat rs = row_stats_regs(v, greedy ? 1.0f : 1.0f / T, greedy, sm, a.prm ? a.prm[b].top_k : a.top_k, a.prm ? a.prm[b].top_p : a.top_p, a.V);
   if (threadIdx.x == 0) {
@@ -1176,7 +1315,7 @@ __device__ __forceinline__ double beta_sum(const BetaPart& t, int k0, int V, int
 // One guess's, by a workgroup of NT threads; jr: two entries, ctot: one per SAMPLE_PART entries of the row.
 template <int NT>
 __device__ __forceinline__ void beta_guess(const AcceptArgs& a, int b, int i, RowStat* jr, double* ctot) {
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, V = a.V, gamma = a.gamma;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), V = a.V, gamma = a.gamma;
   const StepParams* prm = a.prm ? a.prm + b : nullptr;
   const float T = prm ? prm->temperature : a.temperature;
   const bool greedy = (T == 0.0f);
@@ -1225,15 +1364,16 @@ static __global__ __launch_bounds__(256, 6) void beta_kernel(const AcceptArgs a)
 // itself (a few hundred words), then sums the weights of its chunks of row n (16 chunks_wave of
 // them); the last to arrive scans the totals and walks the chunk that holds u * total.
 // A small call is this one launch (OWN, launch_accept): a second one would cost it more than its work.
-// 64 sequences, gamma 7, vocabulary 32128 (123 MB), both launches, calls back to back: 33.0 us
-// (row_parts_kernel 22.8: 5.4 TB/s, where a pure read reaches 7); with one 1024-thread workgroup per row and
-// then one per sequence it was 42.2.  One sequence, gamma 4: 11.1 us against 16.8.
+// 64 sequences, gamma 7, vocabulary 32128 (123 MB), both launches, calls back to back: 31.2 us
+// (row_parts_kernel 21 - 23: 5.4 TB/s, where a pure read reaches 7); with one 1024-thread workgroup per row and
+// then one per sequence it was 42.2.  One sequence, gamma 4: 10.9 us against 16.8.
+// OWN_NONE: 64 registers, two workgroups a CU.
 enum { OWN_NONE, OWN_SEQUENCE, OWN_ROWS };           // whose the statistics are: row_parts_kernel's; this kernel's, a workgroup per sequence / per logits row
 template <int OWN>
-static __global__ __launch_bounds__(SAMPLE_THREADS) void accept_kernel(const AcceptArgs a) {
+static __global__ __launch_bounds__(SAMPLE_THREADS, OWN == OWN_NONE ? 8 : 4) void accept_kernel(const AcceptArgs a) {
   __shared__ SampleSmem sm;
   __shared__ RowStat srow[2 * SAMPLE_MAX_GAMMA + 1];
-  const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int gamma = a.gamma, V = a.V, nrows = 2 * gamma + 1, nchunks = (V + SAMPLE_CHUNK - 1) / SAMPLE_CHUNK;
   const StepParams* prm = a.prm ? a.prm + b : nullptr;     // in-model use: per-sequence parameters and state
   SeqState* st = a.st ? a.st + b : nullptr;
@@ -1310,7 +1450,7 @@ static __global__ __launch_bounds__(SAMPLE_THREADS) void accept_kernel(const Acc
     rp.zp = P + (size_t)n * V; rp.zq = with_q ? Q + (size_t)n * V : nullptr;
     rp.mp = sp.m; rp.mq = sq.m; rp.tp = sp.thr; rp.tq = sq.thr; rp.invT = invT; rp.V = V;
     rp.invSp = 1.0 / sp.S; rp.invSq = with_q ? len / sq.S : 0.0;                 // q enters the residual as l * q
-    constexpr int CB = 4;                            // chunks whose loads a wavefront keeps in flight
+    constexpr int CB = OWN == OWN_NONE ? 2 : 4;      // chunks whose loads a wavefront keeps in flight
     const int c0 = (OWN ? 0 : (int)blockIdx.x) * SAMPLE_CHUNKS_WG * a.chunks_wave + wave;
     for (int i0 = 0; i0 < a.chunks_wave; i0 += CB) {
       RawPair raw[CB];
@@ -1322,7 +1462,7 @@ static __global__ __launch_bounds__(SAMPLE_THREADS) void accept_kernel(const Acc
         const int c = c0 + (i0 + i) * SAMPLE_CHUNKS_WG;
         if (i0 + i < a.chunks_wave && c < nchunks) {
           double w[4];
-          calc4(rp, c * SAMPLE_CHUNK + lane * 4, raw[i], w);
+          calc4(rp, c, raw[i], w);
           const double tc = wave_sum((w[0] + w[1]) + (w[2] + w[3]));
           if (lane == 0) post(&scr->tot[c], tc);
         }
@@ -1338,9 +1478,9 @@ static __global__ __launch_bounds__(SAMPLE_THREADS) void accept_kernel(const Acc
       if (total > 0.0) {
         const int chunk = sm.chunk;
         const bool fallback = chunk < 0;        // threshold not reached by round-off
-        const int k = (fallback ? (-1 - chunk) : chunk) * SAMPLE_CHUNK + lane * 4;
+        const int c = __builtin_amdgcn_readfirstlane(fallback ? (-1 - chunk) : chunk), k = c * SAMPLE_CHUNK + lane * 4;
         double w[4];
-        weights4(rp, k, w);
+        weights4(rp, c, w);
         const int tok = pick_in_chunk(w, k, V, fallback, (double)s * total, sm.before);
         if (lane == 0) sm.token = tok;
       }
@@ -1448,7 +1588,9 @@ inline void launch_accept(hipStream_t stream, AcceptArgs a, int rows, int cus) {
     else if (rows * nrows <= cus && wgs <= 2) own = OWN_ROWS;
   }
   if (accept_filtered(a)) {
-    hipLaunchKernelGGL(row_filter_kernel, dim3(nrows, rows), dim3(SAMPLE_THREADS), 0, stream, a);
+    with_sample_groups(a.V, [&](auto ng) {
+      hipLaunchKernelGGL((row_filter_kernel<decltype(ng)::value>), dim3(nrows, rows), dim3(SAMPLE_THREADS), 0, stream, a);
+    });
   } else if (own == OWN_NONE) {
     const int items = rows * nrows * a.nparts;
     const dim3 parts_grid(min((items + 3) / 4, cus * ACCEPT_WAVES_CU / 4));
@@ -1456,14 +1598,16 @@ inline void launch_accept(hipStream_t stream, AcceptArgs a, int rows, int cus) {
     if (a.V < 4) hipLaunchKernelGGL((row_parts_kernel<true>), parts_grid, dim3(256), 0, stream, a, items, mag_parts, mag_rows);
     else hipLaunchKernelGGL((row_parts_kernel<false>), parts_grid, dim3(256), 0, stream, a, items, mag_parts, mag_rows);
   }
-  // as many workgroups a sequence as fit the CUs in one round; more only repeat the decisions more often
+  // as many workgroups a sequence as fit the CUs in one round, two on each (64 registers; with one on each, 64 sequences of gamma 7
+  // 31.9 us a call instead of 31.2, 40 of gamma 3 17.5 instead of 16.2; 128 of gamma 3 33.1 instead of 33.5), but beta's, which are
+  // bound by their arithmetic, take one each (16 of gamma 4, vocabulary 50257: 19.5, two on each 26.6); more only repeat the decisions more often
   // (200 sequences, gamma 1, vocabulary 32128: 35.3 us with one, 49.1 with a second that takes the last chunks), beside
   // beta's (16 sequences, gamma 4, vocabulary 50257: 13 and 4 of them a sequence 17.7 us, 7 and 4 13.9), unless
   // those leave less than two of a round (48 sequences, gamma 7, 32128: 45.9 us a call with four, 55.6 with one; 16, gamma
   // 15, 50257: 45.2 with 13, 49.8 with the one that is left; gamma 14: 43.5 with 13, 41.8 with the two)
   const bool beta_apart = a.beta != nullptr && 2 * rows * a.gamma > 3 * cus && a.temperature > 0.0f;   // (argmax: no rows to read)
   const int beta_wgs = (a.beta != nullptr && !beta_apart) ? a.gamma : 0;
-  const int round = max(1, cus / rows), left = round - beta_wgs, most = own ? 1 : min(wgs, left >= 2 ? left : round);
+  const int round = max(1, (beta_wgs ? 1 : 2) * cus / rows), left = round - beta_wgs, most = own ? 1 : min(wgs, left >= 2 ? left : round);
   a.chunks_wave = (wgs + most - 1) / most;
   a.draw_wgs = (wgs + a.chunks_wave - 1) / a.chunks_wave;         // (1 where the statistics are its own work)
   const dim3 grid(own == OWN_ROWS ? nrows : a.draw_wgs + beta_wgs, rows), block(SAMPLE_THREADS);

@@ -1076,8 +1076,10 @@ void cross_kv(Model& m, const void* enc) {
 // One draw per sequence from the row at logits + b * seq_stride (mode 0: guess number `slot`; 1: commit).
 void launch_draw(sd_ctx* c, const float* logits, int uniform_idx, int mode, int slot, size_t seq_stride, bool argmax = false) {
   if (c->filtered() && !argmax) {                    // (argmax sampling ignores the filters)
-    hipLaunchKernelGGL(sample_row_filter_kernel, dim3(c->batch), dim3(SAMPLE_THREADS), 0, c->stream, logits, c->p.cfg.vocab, c->d_params,
-                       uniform_idx, c->d_state, mode, slot, seq_stride);
+    with_sample_groups(c->p.cfg.vocab, [&](auto ng) {
+      hipLaunchKernelGGL((sample_row_filter_kernel<decltype(ng)::value>), dim3(c->batch), dim3(SAMPLE_THREADS), 0, c->stream, logits, c->p.cfg.vocab,
+                         c->d_params, uniform_idx, c->d_state, mode, slot, seq_stride);
+    });
     return;
   }
   with_sample_groups(c->p.cfg.vocab, [&](auto ng) {

@@ -385,3 +385,47 @@ def test_the_draw_keeps_its_workgroups_beside_much_beta():
 @pytest.mark.parametrize("gamma", [14, 15])
 def test_draw_beside_much_beta(gamma):
     check(*synth.sampler_case(16, gamma, 9000, 1.0, 5), 1.0)
+
+
+@pytest.mark.parametrize("m", [1, 2, 33, 63, 64, 65, 100, 127, 128])
+@pytest.mark.parametrize("part", [1.0, 0.5])
+def test_short_lists_of_every_length_with_ties(m, part):
+    """m entries on a grid of few values, far above the others and in as many threads: the list that one wavefront sorts, one key a
+    lane or two, cut by top-k at its end or in its middle (among equal keys) and again by the nucleus."""
+    vocab, gamma = 8192, 3
+    g = np.random.default_rng(1000 * m + int(10 * part))
+    zp, zq, _, r, s = synth.sampler_case(2, gamma, vocab, 1.0, m)
+    top_k, top_p = max(1, int(part * m)), float(np.float32(0.8))
+    for z in [*zp.reshape(-1, vocab), *zq.reshape(-1, vocab)]:
+        z[:] = -60.0
+        at = 4 * g.permutation(vocab // 4)[:m]
+        z[at] = np.round(8 * g.standard_normal(m)).astype(np.float32) / 4
+        while sampling.nucleus_margin(z, 1.0, top_k, top_p) < 2e-6:    # (see test_filter_paths)
+            z[at[0]] += np.float32(0.01)
+    x = np.argmax(zq, -1).astype(np.int32)
+    check(zp, zq, x, r, s, 1.0, top_k, top_p)
+
+
+# the groups a thread holds change behind 4096, 8192 and 16384 entries; few entries, and a bin whose entries are more than one
+# wavefront sorts (a grid of values), or more than the list holds (one value); temperatures at which all weights lie in the
+# first bin, and few are not zero
+@pytest.mark.parametrize("vocab", [4, 8, 4092, 4096, 4100, 8192, 8196, 16384, 16388, 32768])
+@pytest.mark.parametrize("kind,temperature", [("normal", 1.0), ("grid", 1.0), ("one", 1.0), ("normal", 1000.0), ("normal", 0.02), ("masked", 0.7)])
+def test_nucleus_alone(vocab, kind, temperature):
+    zp, zq, _, r, s = synth.sampler_case(2, 2, vocab, 1.0, vocab + int(temperature))
+    if kind == "grid":
+        zp, zq = np.round(zp), np.round(zq)
+    elif kind == "one":
+        zp, zq = np.zeros_like(zp), np.zeros_like(zq)
+    elif kind == "masked":
+        zp[:, :, 1::2], zq[:, :, 1::2] = -np.inf, np.finfo(np.float32).min
+    top_p = float(np.float32(0.9))
+    for z in [*zp.reshape(-1, vocab), *zq.reshape(-1, vocab)]:
+        for _ in range(50):
+            if sampling.nucleus_margin(z, temperature, 0, top_p) >= 2e-6:          # (see test_filter_paths)
+                break
+            z[0] += np.float32(0.01 * max(1.0, temperature))
+        else:
+            pytest.skip("no row of these values is clear of its threshold")
+    x = np.argmax(zq, -1).astype(np.int32)
+    check(zp, zq, x, r, s, temperature, 0, top_p)
