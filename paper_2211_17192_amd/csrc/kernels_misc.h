@@ -15,62 +15,51 @@ enum {
   ROWS_PREFILL = 4       // prompt[start .. start+R) at start ..
 };
 
-// grid = R workgroups.  row_pos[r] < 0 marks a padding row (first draft step of
-// a one-token sequence): it is embedded as token 0 at position 0 and ignored.
-// For RMSNorm models the kernel also writes xg = x * gain of the first norm in
-// the storage type and the row's sum of squares (one partial: ss[0][r]).
-// Several sequences: the launch covers sequences seq0, seq0+1, ... with rps rows
-// each, one after the other: workgroup b (sequence seq0 + b / rps) writes row b of
-// x / xg / row_pos / ..., and the sum of squares of its row into the block of ss that
-// belongs to the row's slab of MAX_ROWS rows (ss_stride floats per slab); `st` is the array
-// of sequence states.  row_seq[r] (when given) receives the row's sequence, logit_row[r] the
+// Where a model's embedded rows go.  For RMSNorm models also xg = x * gain of the first norm in
+// the storage type and the row's sum of squares (one partial, in the block of ss that belongs to the row's slab of
+// MAX_ROWS rows, ss_stride floats per slab).  row_seq[r] receives the row's sequence, logit_row[r] the
 // row of the logits buffer its LM-head output belongs in (< 0: not needed):
 // p rows [seq][gamma+1], q rows [seq][gamma], one row per sequence for plain decoding.
 // xg_frag: xg in the fragment order of the products over many rows instead of row-major.
-template <typename T>
-static __global__ __launch_bounds__(256) void embed_kernel(
-    int mode, int step, const SeqState* __restrict__ st, const int* __restrict__ prompt, int start,
-    const T* __restrict__ tok_emb, const T* __restrict__ pos_emb, int d, int vocab,
-    float* __restrict__ x, int* __restrict__ row_pos, const T* __restrict__ gain_next,
-    T* __restrict__ xg, float* __restrict__ ss,
-    int rps, int seq0, int gamma, int* __restrict__ row_seq, int* __restrict__ logit_row,
-    int ss_stride, int xg_frag) {
-  __shared__ float red[16];
-  const int j = (int)blockIdx.x % rps, sl = (int)blockIdx.x / rps, seq = seq0 + sl;
-  const int r = blockIdx.x, slab = r / MAX_ROWS, r16 = r % MAX_ROWS;     // row, its slab, row within the slab
-  st += seq;
-  int tok, pos, lrow = -1;
-  switch (mode) {
-    case ROWS_VERIFY:      tok = (j == 0) ? st->last_tok : st->x[j - 1]; pos = st->len - 1 + j; lrow = seq * (gamma + 1) + j; break;
-    case ROWS_DRAFT_FIRST: tok = (j == 0) ? st->prev_tok : st->last_tok; pos = st->len - 2 + j; lrow = (j == 1) ? seq * gamma : -1; break;
-    case ROWS_DRAFT_NEXT:  tok = st->x[step - 1]; pos = st->len - 1 + step; lrow = seq * gamma + step; break;
-    case ROWS_BASELINE:    tok = st->last_tok; pos = st->len - 1; lrow = seq; break;
-    default:               tok = prompt[start + r]; pos = start + r; break;
-  }
-  if (threadIdx.x == 0 && row_seq) { row_seq[r] = seq; logit_row[r] = lrow; }
-  if (threadIdx.x == 0) row_pos[r] = pos;
+struct EmbedArgs {
+  const void *tok_emb, *pos_emb, *gain;   // storage type; pos_emb and gain optional
+  float* x;                               // (nullptr: no embedding asked for)
+  void* xg;
+  float* ss;
+  int *row_pos, *row_seq, *logit_row;
+  int d, vocab, ss_stride, xg_frag, is_bf16;
+};
+
+// Row r: token tok at position pos (< 0: a padding row, the first draft step of a one-token sequence: embedded as
+// token 0 at position 0 and ignored).  Threads 0..255 of the workgroup work, all of them call; red: 16 floats of LDS.
+// 8 consecutive elements per thread and step, STEPS of them in flight: the row comes from cold memory and the loop would
+// otherwise pay its latency per step.
+template <typename T, int STEPS>
+__device__ __forceinline__ void embed_row(const EmbedArgs& a, int r, int tok, int pos, int seq, int lrow, float* red) {
+  const int tid = threadIdx.x, d = a.d;
+  if (tid == 0) { a.row_seq[r] = seq; a.logit_row[r] = lrow; a.row_pos[r] = pos; }
   if (pos < 0) { tok = 0; pos = 0; }
-  tok = min(max(tok, 0), vocab - 1);
-  const T* e = tok_emb + (size_t)tok * d;
-  const T* p = pos_emb ? pos_emb + (size_t)pos * d : nullptr;
+  tok = min(max(tok, 0), a.vocab - 1);
+  const T* e = static_cast<const T*>(a.tok_emb) + (size_t)tok * d;
+  const T* p = a.pos_emb ? static_cast<const T*>(a.pos_emb) + (size_t)pos * d : nullptr;
+  const T* gain = static_cast<const T*>(a.gain);
+  T* xg = static_cast<T*>(a.xg);
   float q = 0.0f;
-  // 8 consecutive elements per thread and step, four steps in flight: the row
-  // comes from cold memory and the loop would otherwise pay its latency per step
   const int ngroups = d >> 3;                       // d is a multiple of 32
-  for (int g0 = threadIdx.x; g0 < ngroups; g0 += blockDim.x * 4) {
-    float v[4][8], w[4][8], gn[4][8];
+  for (int g0 = (tid < 256) ? tid : ngroups; g0 < ngroups; g0 += 256 * STEPS) {
+    float v[STEPS][8], w[STEPS][8], gn[STEPS][8];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int g = g0 + u * blockDim.x;
+    for (int u = 0; u < STEPS; ++u) {
+      const int g = g0 + u * 256;
       if (g < ngroups) {
         load8<T>(e + g * 8, v[u]);
         if (p) load8<T>(p + g * 8, w[u]);
-        if (xg) load8<T>(gain_next + g * 8, gn[u]);
+        if (xg) load8<T>(gain + g * 8, gn[u]);
       }
     }
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int g = g0 + u * blockDim.x;
+    for (int u = 0; u < STEPS; ++u) {
+      const int g = g0 + u * 256;
       if (g < ngroups) {
         float xv[8], xgv[8];
 #pragma unroll
@@ -81,15 +70,49 @@ static __global__ __launch_bounds__(256) void embed_kernel(
           if (xg) xgv[k] = val * gn[u][k];
           q += val * val;
         }
-        store8<float>(x + (size_t)r * d + g * 8, xv);
-        if (xg) store8<T>(xg + (xg_frag ? rows_frag_index(r, g * 8, d >> 5) : (size_t)r * d + g * 8), xgv);
+        store8<float>(a.x + (size_t)r * d + g * 8, xv);
+        if (xg) store8<T>(xg + (a.xg_frag ? rows_frag_index(r, g * 8, d >> 5) : (size_t)r * d + g * 8), xgv);
       }
     }
   }
-  if (ss) {
+  if (a.ss) {                                       // (wavefronts without a share add zeros)
     q = block_reduce(q, red, OpSumF(), 0.0f);
-    if (threadIdx.x == 0) ss[(size_t)slab * ss_stride + r16] = q;
+    if (tid == 0) a.ss[(size_t)(r / MAX_ROWS) * a.ss_stride + r % MAX_ROWS] = q;
   }
+}
+// The row of Mq's next step, by the workgroup that drew its token (16 wavefronts): a launch less a guess.  (One step in flight holds
+// the row of a model up to 2048 wide; the drawing kernels have no registers for more.)
+__device__ __forceinline__ void embed_drawn(const EmbedArgs& a, int seq, int tok, int pos, int lrow, float* red) {
+  if (a.is_bf16) embed_row<bf16, 1>(a, seq, tok, pos, seq, lrow, red);
+  else embed_row<float, 1>(a, seq, tok, pos, seq, lrow, red);
+}
+
+// grid = R workgroups: the launch covers sequences seq0, seq0+1, ... with rps rows
+// each, one after the other: workgroup b (sequence seq0 + b / rps) writes row b; `st` is the array of sequence states.
+// params_from (optional): the step's parameters in pinned host memory, which the first launch of an iteration takes to params_to.
+template <typename T>
+static __global__ __launch_bounds__(256) void embed_kernel(
+    int mode, int step, const SeqState* __restrict__ st, const int* __restrict__ prompt, int start, const EmbedArgs a,
+    int rps, int seq0, int gamma, const StepParams* __restrict__ params_from, StepParams* __restrict__ params_to) {
+  __shared__ float red[16];
+  const int j = (int)blockIdx.x % rps, sl = (int)blockIdx.x / rps, seq = seq0 + sl;
+  const int r = blockIdx.x;
+  constexpr int WORDS = sizeof(StepParams) / 4;
+  static_assert(WORDS <= 192 && sizeof(StepParams) % 4 == 0, "a workgroup's last threads copy a sequence's parameters");
+  int word = 0;
+  const bool copies = params_from != nullptr && j == 0 && threadIdx.x >= 64 && threadIdx.x < 64 + WORDS;
+  if (copies) word = reinterpret_cast<const int*>(params_from + seq)[threadIdx.x - 64];
+  st += seq;
+  int tok, pos, lrow = -1;
+  switch (mode) {
+    case ROWS_VERIFY:      tok = (j == 0) ? st->last_tok : st->x[j - 1]; pos = st->len - 1 + j; lrow = seq * (gamma + 1) + j; break;
+    case ROWS_DRAFT_FIRST: tok = (j == 0) ? st->prev_tok : st->last_tok; pos = st->len - 2 + j; lrow = (j == 1) ? seq * gamma : -1; break;
+    case ROWS_DRAFT_NEXT:  tok = st->x[step - 1]; pos = st->len - 1 + step; lrow = seq * gamma + step; break;
+    case ROWS_BASELINE:    tok = st->last_tok; pos = st->len - 1; lrow = seq; break;
+    default:               tok = prompt[start + r]; pos = start + r; break;
+  }
+  embed_row<T, 4>(a, r, tok, pos, seq, lrow, red);
+  if (copies) reinterpret_cast<int*>(params_to + seq)[threadIdx.x - 64] = word;
 }
 
 // A new sequence's tokens and state out of pinned host memory, to the models' prompts, the history and the state (each

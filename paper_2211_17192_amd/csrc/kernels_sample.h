@@ -15,6 +15,7 @@
 #include <limits.h>
 #include <type_traits>
 #include "common.h"
+#include "kernels_misc.h"
 
 namespace sd {
 
@@ -868,27 +869,44 @@ template <typename F> void with_sample_groups(int V, F&& f) {
   else f(std::integral_constant<int, SAMPLE_REG_F4>());
 }
 
-__device__ __forceinline__ void commit_draw(SeqState* st, int mode, int slot, int tok) {
+// A finished draw or run of Algorithm 1 into the device's state and, where `host` is given, what the host reads of it into
+// pinned host memory, 16 bytes at a time: a copy less behind the launch.
+__device__ __forceinline__ void put4(int32_t* p, int a, int b, int c, int d) {
+  typedef int i32x4 __attribute__((ext_vector_type(4)));
+  *reinterpret_cast<i32x4*>(p) = i32x4{a, b, c, d};
+}
+__device__ __forceinline__ void commit_draw(SeqState* st, int mode, int slot, int tok, SeqState* host = nullptr) {
   if (mode == 0) {
     st->x[slot] = tok;
   } else {
-    st->prev_tok = st->last_tok;
-    st->last_tok = tok;
-    st->len += 1;
-    st->n = 0;
+    const int len = st->len + 1, last = st->last_tok;
+    put4(&st->len, len, tok, last, 0);
     st->out[0] = tok;
+    if (host) { put4(&host->len, len, tok, last, 0); host->out[0] = tok; }
   }
 }
 
 // One run of Algorithm 1: x_1 .. x_n, t.
-__device__ __forceinline__ void commit_run(SeqState* st, int n, int t, int fell_back) {
-  const int last = st->last_tok;
-  for (int i = 0; i < 16; ++i) st->out[i] = (i < n) ? st->x[i] : (i == n ? t : -1);
-  st->prev_tok = (n >= 1) ? st->x[n - 1] : last;
-  st->last_tok = t;
-  st->len += n + 1;
-  st->n = n;
-  st->fallbacks += fell_back;
+__device__ __forceinline__ void commit_run(SeqState* st, int n, int t, int fell_back, SeqState* host) {
+  static_assert(offsetof(SeqState, len) == 0 && offsetof(SeqState, last_tok) == 4 && offsetof(SeqState, prev_tok) == 8 &&
+                offsetof(SeqState, n) == 12 && offsetof(SeqState, out) % 16 == 0 && sizeof(SeqState) % 16 == 0, "put4");
+  int o[16];
+  for (int i = 0; i < 16; ++i) o[i] = st->x[i];
+  const int len = st->len + n + 1, last = st->last_tok, fallbacks = st->fallbacks + fell_back;
+  int prev = last;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    prev = (i == n - 1) ? o[i] : prev;
+    o[i] = (i < n) ? o[i] : (i == n ? t : -1);
+  }
+  auto put = [&](SeqState* s) {
+    put4(&s->len, len, t, prev, n);
+#pragma unroll
+    for (int i = 0; i < 16; i += 4) put4(s->out + i, o[i], o[i + 1], o[i + 2], o[i + 3]);
+    s->fallbacks = fallbacks;
+  };
+  put(st);
+  if (host) put(host);
 }
 
 // The workgroups' hand-over: each leaves 8-byte results with write-through stores (post) and takes a
@@ -960,13 +978,29 @@ __device__ __forceinline__ void argmax_workgroup(float& m, int& arg, int V, floa
   arg = wave_min(lane < nw && t == m ? wa[lane & 15] : INT_MAX);
 }
 
+// What follows a draw: the embedding of Mq's next step (e.x given), at position len - 1 + step, its logits for row seq * gamma + step;
+// or the committed state's copy for the host.
+struct DrawNext {
+  EmbedArgs e;
+  int step, gamma;
+  SeqState* host;        // pinned host memory, [sequences]
+};
+// Every thread of the workgroup that drew calls; tok: wavefront 0's.
+__device__ __forceinline__ void finish_draw(const DrawNext& next, SeqState* st, int mode, int slot, int tok, SampleSmem& sm, int seq) {
+  if (threadIdx.x == 0) commit_draw(st, mode, slot, tok, next.host ? next.host + seq : nullptr);
+  if (next.e.x == nullptr) return;                   // (uniform)
+  if (threadIdx.x == 0) sm.token = tok;
+  __syncthreads();
+  embed_drawn(next.e, seq, sm.token, st->len - 1 + next.step, seq * next.gamma + next.step, sm.redf);
+}
+
 // NG: groups of four entries that a thread takes of the row (with_sample_groups).  The row's first pass and
 // this workgroup's own entries are asked for before the step's parameters are waited for: 5.8 -> 5.0 us at
 // vocabulary 8192, 6.8 -> 6.6 at 32000; argmax 3.9 -> 2.3 and 4.2 -> 3.7.
 template <int NG>
 static __global__ __launch_bounds__(SAMPLE_THREADS) void sample_row_split_kernel(
     const float* __restrict__ logits, int V, const StepParams* __restrict__ prm, int uniform_idx,
-    SeqState* __restrict__ st, int mode, int slot, size_t seq_stride, SampleScratch* __restrict__ scr) {
+    SeqState* __restrict__ st, int mode, int slot, size_t seq_stride, SampleScratch* __restrict__ scr, const DrawNext next) {
   __shared__ SampleSmem sm;
   const int w = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   logits += (size_t)blockIdx.y * seq_stride;
@@ -981,78 +1015,77 @@ static __global__ __launch_bounds__(SAMPLE_THREADS) void sample_row_split_kernel
   const float T = prm->temperature, u = prm->uniforms[uniform_idx];
   const bool greedy = (T == 0.0f);
   const float invT = greedy ? 1.0f : 1.0f / T;
+  int tok = 0;                                       // (wavefront 0's)
   if (greedy) {
     float m = -INFINITY;
     int arg = INT_MAX;
-    // a row of one pass: one workgroup holds it whole, and needs no hand-over (0.7 us of 3.9 at 8192 entries)
     if (NG < SAMPLE_REG_F4 || V <= 4 * NG * SAMPLE_THREADS) {
+      // a row of one pass: one workgroup holds it whole, and needs no hand-over (0.7 us of 3.9 at 8192 entries)
       if (w != 0) return;
       argmax_groups(v, tid * 4, 4 * SAMPLE_THREADS, V, m, arg);
       argmax_workgroup(m, arg, V, sm.redf, sm.redi);
-      if (tid == 0) commit_draw(st, mode, slot, arg);
-      return;
-    }
-    // longer: each workgroup its own entries (V >= 4: no index to clamp)
-    const f32x4_any one[1] = {raw_mine};
-    argmax_groups(one, k_mine, 0, V, m, arg);
-    argmax_workgroup(m, arg, V, sm.redf, sm.redi);
-    // order of the posted words: larger maximum first (-0 counts as 0), then the lower index
-    if (tid == 0)
-      post(&scr->tot[w], __longlong_as_double((long long)(((unsigned long long)float_key(m + 0.0f) << 32) | (0xffffffffu - (unsigned)arg))));
-    if (!last_to_post(scr->ticket, gridDim.x, &sm.flag)) return;
-    if (wave == 0) {
-      unsigned long long best = (lane < (int)gridDim.x) ? (unsigned long long)__double_as_longlong(collect(&scr->tot[lane])) : 0ull;
+      tok = arg;
+    } else {
+      // longer: each workgroup its own entries (V >= 4: no index to clamp)
+      const f32x4_any one[1] = {raw_mine};
+      argmax_groups(one, k_mine, 0, V, m, arg);
+      argmax_workgroup(m, arg, V, sm.redf, sm.redi);
+      // order of the posted words: larger maximum first (-0 counts as 0), then the lower index
+      if (tid == 0)
+        post(&scr->tot[w], __longlong_as_double((long long)(((unsigned long long)float_key(m + 0.0f) << 32) | (0xffffffffu - (unsigned)arg))));
+      if (!last_to_post(scr->ticket, gridDim.x, &sm.flag)) return;
+      if (wave == 0) {
+        unsigned long long best = (lane < (int)gridDim.x) ? (unsigned long long)__double_as_longlong(collect(&scr->tot[lane])) : 0ull;
 #pragma unroll
-      for (int o = 32; o; o >>= 1) {
-        const unsigned long long t = __shfl_xor(best, o, WAVE);
-        best = t > best ? t : best;
+        for (int o = 32; o; o >>= 1) {
+          const unsigned long long t = __shfl_xor(best, o, WAVE);
+          best = t > best ? t : best;
+        }
+        tok = (int)(0xffffffffu - (unsigned)best);
       }
-      if (lane == 0) commit_draw(st, mode, slot, (int)(0xffffffffu - (unsigned)best));
     }
-    return;
-  }
-  // The row's maximum.  A group past the row's end reads the row's last entries a second time, which
-  // leaves it what it is: no entry is moved or masked (that was 1.0 us of 8.4 at 32128 entries).
-  float m = -INFINITY;
-  auto take = [&](const f32x4_any (&t)[NG]) {
+  } else {
+    // The row's maximum.  A group past the row's end reads the row's last entries a second time, which
+    // leaves it what it is: no entry is moved or masked (that was 1.0 us of 8.4 at 32128 entries).
+    float m = -INFINITY;
+    auto take = [&](const f32x4_any (&t)[NG]) {
 #pragma unroll
-    for (int it = 0; it < NG; ++it) m = fmaxf(m, fmaxf(fmaxf(t[it][0], t[it][1]), fmaxf(t[it][2], t[it][3])));
-  };
-  take(v);
-  for (int k0 = 4 * NG * SAMPLE_THREADS; k0 < V; k0 += 4 * NG * SAMPLE_THREADS) {
-#pragma unroll
-    for (int it = 0; it < NG; ++it) v[it] = raw4_long_row(logits, k0 + (it * SAMPLE_THREADS + tid) * 4, V);
+      for (int it = 0; it < NG; ++it) m = fmaxf(m, fmaxf(fmaxf(t[it][0], t[it][1]), fmaxf(t[it][2], t[it][3])));
+    };
     take(v);
-  }
-  m = block_reduce(m, sm.redf, OpMaxF(), -INFINITY);
-  const float4 mine = placed4_row(raw_mine, k_mine, V);                          // (past the row: -inf)
-  {
+    for (int k0 = 4 * NG * SAMPLE_THREADS; k0 < V; k0 += 4 * NG * SAMPLE_THREADS) {
+#pragma unroll
+      for (int it = 0; it < NG; ++it) v[it] = raw4_long_row(logits, k0 + (it * SAMPLE_THREADS + tid) * 4, V);
+      take(v);
+    }
+    m = block_reduce(m, sm.redf, OpMaxF(), -INFINITY);
+    const float4 mine = placed4_row(raw_mine, k_mine, V);                        // (past the row: -inf)
     const double t = wave_sum(((double)exp_scaled(mine.x, m, invT, -INFINITY) + (double)exp_scaled(mine.y, m, invT, -INFINITY)) +
                               ((double)exp_scaled(mine.z, m, invT, -INFINITY) + (double)exp_scaled(mine.w, m, invT, -INFINITY)));
     if (lane == 0 && c < nchunks) post(&scr->tot[c], t);
+    if (!last_to_post(scr->ticket, gridDim.x, &sm.flag)) return;
+    for (int i = tid; i < nchunks; i += SAMPLE_THREADS) sm.ctot[i] = collect(&scr->tot[i]);
+    __syncthreads();
+    if (wave == 0) {
+      scan_chunk_totals(nchunks, u, sm);
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      const double total = sm.total;
+      const int chunk = sm.chunk;
+      const bool fallback = chunk < 0;          // threshold not reached by round-off
+      const int k = (fallback ? (-1 - chunk) : chunk) * SAMPLE_CHUNK + lane * 4;
+      const float4 z = placed4_row(raw4_long_row(logits, k, V), k, V);
+      const double wv[4] = {(double)exp_scaled(z.x, m, invT, -INFINITY), (double)exp_scaled(z.y, m, invT, -INFINITY),
+                            (double)exp_scaled(z.z, m, invT, -INFINITY), (double)exp_scaled(z.w, m, invT, -INFINITY)};
+      tok = pick_in_chunk(wv, k, V, fallback, (double)u * total, sm.before);
+    }
   }
-  if (!last_to_post(scr->ticket, gridDim.x, &sm.flag)) return;
-  for (int i = tid; i < nchunks; i += SAMPLE_THREADS) sm.ctot[i] = collect(&scr->tot[i]);
-  __syncthreads();
-  if (wave == 0) {
-    scan_chunk_totals(nchunks, u, sm);
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    const double total = sm.total;
-    const int chunk = sm.chunk;
-    const bool fallback = chunk < 0;            // threshold not reached by round-off
-    const int k = (fallback ? (-1 - chunk) : chunk) * SAMPLE_CHUNK + lane * 4;
-    const float4 z = placed4_row(raw4_long_row(logits, k, V), k, V);
-    const double wv[4] = {(double)exp_scaled(z.x, m, invT, -INFINITY), (double)exp_scaled(z.y, m, invT, -INFINITY),
-                          (double)exp_scaled(z.z, m, invT, -INFINITY), (double)exp_scaled(z.w, m, invT, -INFINITY)};
-    const int tok = pick_in_chunk(wv, k, V, fallback, (double)u * total, sm.before);
-    if (lane == 0) commit_draw(st, mode, slot, tok);
-  }
+  finish_draw(next, st, mode, slot, tok, sm, (int)blockIdx.y);
 }
 
 template <int NG>
 static __global__ __launch_bounds__(SAMPLE_THREADS) void sample_row_filter_kernel(
     const float* __restrict__ logits, int V, const StepParams* __restrict__ prm, int uniform_idx,
-    SeqState* __restrict__ st, int mode, int slot, size_t seq_stride) {
+    SeqState* __restrict__ st, int mode, int slot, size_t seq_stride, const DrawNext next) {
   __shared__ SampleSmem sm;
   logits += (size_t)blockIdx.x * seq_stride;
   prm += blockIdx.x;
@@ -1064,7 +1097,7 @@ static __global__ __launch_bounds__(SAMPLE_THREADS) void sample_row_filter_kerne
   load_row_regs(logits, V, v);
   const RowStat rs = row_stats_regs(v, invT, greedy, sm, prm->top_k, prm->top_p, V);
   const int tok = greedy ? rs.arg : icdf_regs(v, rs, v, rs, false, invT, V, prm->uniforms[uniform_idx], sm);
-  if (threadIdx.x == 0) commit_draw(st, mode, slot, tok);
+  finish_draw(next, st, mode, slot, tok, sm, (int)blockIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -1096,6 +1129,7 @@ struct AcceptArgs {
   RowPart* part; size_t part_seq; int part_row;      // statistics of row j of sequence b: part + b * part_seq + j * part_row
   int *out_n, *out_t; float* beta;
   SeqState* st;
+  SeqState* host;                      // (with st, optional) pinned host memory for the committed states
 };
 // Whether row_filter_kernel leaves the statistics (one part a row) instead of row_parts_kernel.
 __host__ __device__ inline bool accept_filtered(const AcceptArgs& a) { return a.top_k > 0 || (a.top_p > 0.0f && a.top_p < 1.0f); }
@@ -1493,7 +1527,7 @@ static __global__ __launch_bounds__(SAMPLE_THREADS, OWN == OWN_NONE ? 8 : 4) voi
   if (tid == 0) {
     if (a.out_n) a.out_n[b] = n;
     if (a.out_t) a.out_t[b] = t;
-    if (st) commit_run(st, n, t, fell_back);
+    if (st) commit_run(st, n, t, fell_back, a.host ? a.host + b : nullptr);
   }
 }
 
@@ -1547,7 +1581,7 @@ static __global__ __launch_bounds__(SAMPLE_THREADS) void accept_argmax_kernel(co
   if (lane == 0) {
     if (a.out_n) a.out_n[b] = n;
     if (a.out_t) a.out_t[b] = t;
-    if (st) commit_run(st, n, t, 0);
+    if (st) commit_run(st, n, t, 0, a.host ? a.host + b : nullptr);
   }
 }
 

@@ -675,7 +675,28 @@ int prefill_rows(const sd_model_cfg& c) { return std::min(MAX_ROWS, ATTN_MAX_RG 
 // by (mode, step) from the device-resident sequence states (ROWS_PREFILL: rps prompt tokens
 // of sequence seq0 from position start).  gamma fixes where the LM-head rows land in the
 // logits buffers ([seq][gamma+1][V] for Mp, [seq][gamma][V] for Mq).
-struct Rows { int mode, step, rps, start, seq0, nseq, gamma; };
+// embedded: the draw before it left the rows' embeddings.
+struct Rows { int mode, step, rps, start, seq0, nseq, gamma; bool embedded = false; };
+
+// The rows of a forward of m, where forward() / forward_rows() read them.
+bool many_rows(const Model& m, int rows) { return m.rows_pass > 0 && rows > MAX_ROWS; }
+EmbedArgs embed_args(const Model& m, int rows) {
+  const bool rms = m.cfg.arch != SD_ARCH_GPT;
+  EmbedArgs e{};
+  e.tok_emb = m.tok_emb; e.pos_emb = m.pos_emb; e.x = m.x; e.d = m.cfg.d_model; e.vocab = m.cfg.vocab;
+  if (rms) { e.gain = m.L[0].ln1g; e.xg = m.xg; e.ss = m.ss; }
+  e.row_pos = m.row_pos; e.row_seq = m.row_seq; e.logit_row = m.logit_row;
+  e.ss_stride = (m.cfg.d_model / 16) * 16; e.xg_frag = many_rows(m, rows) ? 1 : 0; e.is_bf16 = m.cfg.dtype == SD_BF16 ? 1 : 0;
+  return e;
+}
+template <typename T>
+void launch_embed(sd_ctx* c, Model& m, const Rows& rw) {
+  if (rw.embedded) return;
+  // the first launch of an iteration brings the step's parameters
+  const bool first = rw.mode == ROWS_DRAFT_FIRST || rw.mode == ROWS_BASELINE;
+  hipLaunchKernelGGL((embed_kernel<T>), dim3(rw.nseq * rw.rps), dim3(256), 0, m.stream, rw.mode, rw.step, c->d_state, m.prompt, rw.start,
+                     embed_args(m, rw.nseq * rw.rps), rw.rps, rw.seq0, rw.gamma, first ? c->h_params : nullptr, c->d_params);
+}
 
 // One forward of model m; with `logits` the LM head runs on every row and each row's
 // output goes where the embedding kernel's row map says (or nowhere); without (a prompt) the last layer ends at
@@ -710,14 +731,7 @@ void forward(sd_ctx* c, Model& m, const Rows& rw, float* logits) {
     q.row_pos = m.row_pos + off; q.row_seq = m.row_seq + off; q.logit_row = m.logit_row + off;
     return q;
   };
-  {
-    const Grp q = group(0);                         // one launch: the kernel places each row in its slab
-    hipLaunchKernelGGL((embed_kernel<T>), dim3(rw.nseq * rw.rps), dim3(256), 0, s, rw.mode, rw.step, c->d_state, m.prompt,
-                       rw.start, static_cast<const T*>(m.tok_emb), static_cast<const T*>(m.pos_emb), d, f.vocab, q.x,
-                       q.row_pos, static_cast<const T*>(rms ? m.L[0].ln1g : nullptr),
-                       reinterpret_cast<T*>(rms ? q.xg : nullptr), rms ? q.ss : nullptr,
-                       rw.rps, rw.seq0, rw.gamma, q.row_seq, q.logit_row, ss_stride, 0);
-  }
+  launch_embed<T>(c, m, rw);
   // One GEMM over every group: groups are 16-row slabs one after the other in all row-indexed
   // buffers, so up to GEMM_WIDE_RT of them go into one launch of the wide kernel (weights
   // streamed once for all of them); a single group takes the one-slab kernel.
@@ -944,9 +958,7 @@ void forward_rows(sd_ctx* c, Model& m, const Rows& rw, float* logits) {
   const int skip = c->skip_ops;                      // measurement only (sd_time_forward)
   bf16 *xg = static_cast<bf16*>(m.xg), *attn = static_cast<bf16*>(m.attn), *ffn = static_cast<bf16*>(m.ffn), *q = static_cast<bf16*>(m.qbuf);
   auto cb = [](const void* p) { return static_cast<const bf16*>(p); };
-  hipLaunchKernelGGL((embed_kernel<bf16>), dim3(rows), dim3(256), 0, s, rw.mode, rw.step, c->d_state, m.prompt, rw.start,
-                     cb(m.tok_emb), cb(m.pos_emb), d, f.vocab, m.x, m.row_pos, cb(rms ? m.L[0].ln1g : nullptr),
-                     rms ? xg : (bf16*)nullptr, rms ? m.ss : nullptr, rw.rps, rw.seq0, rw.gamma, m.row_seq, m.logit_row, ss_stride, 1);
+  launch_embed<bf16>(c, m, rw);
   int n_part = 1;
   // the input of a product behind a norm: the rows' partial sums, or the normalised rows
   auto normed = [&](const void* g, const void* b) {
@@ -1034,7 +1046,7 @@ void forward_rows(sd_ctx* c, Model& m, const Rows& rw, float* logits) {
 }
 
 void forward_any(sd_ctx* c, Model& m, const Rows& rw, float* logits) {
-  if (m.rows_pass > 0 && rw.nseq * rw.rps > MAX_ROWS) forward_rows(c, m, rw, logits);
+  if (many_rows(m, rw.nseq * rw.rps)) forward_rows(c, m, rw, logits);
   else if (m.cfg.dtype == SD_BF16) forward<bf16>(c, m, rw, logits);
   else forward<float>(c, m, rw, logits);
 }
@@ -1074,25 +1086,31 @@ void cross_kv(Model& m, const void* enc) {
 }
 
 // One draw per sequence from the row at logits + b * seq_stride (mode 0: guess number `slot`; 1: commit).
-void launch_draw(sd_ctx* c, const float* logits, int uniform_idx, int mode, int slot, size_t seq_stride, bool argmax = false) {
+// next: what its last workgroup does behind it.
+void launch_draw(sd_ctx* c, const float* logits, int uniform_idx, int mode, int slot, size_t seq_stride, bool argmax = false, const DrawNext& next = DrawNext{}) {
   if (c->filtered() && !argmax) {                    // (argmax sampling ignores the filters)
     with_sample_groups(c->p.cfg.vocab, [&](auto ng) {
       hipLaunchKernelGGL((sample_row_filter_kernel<decltype(ng)::value>), dim3(c->batch), dim3(SAMPLE_THREADS), 0, c->stream, logits, c->p.cfg.vocab,
-                         c->d_params, uniform_idx, c->d_state, mode, slot, seq_stride);
+                         c->d_params, uniform_idx, c->d_state, mode, slot, seq_stride, next);
     });
     return;
   }
   with_sample_groups(c->p.cfg.vocab, [&](auto ng) {
     hipLaunchKernelGGL((sample_row_split_kernel<decltype(ng)::value>), dim3(sample_workgroups(c->p.cfg.vocab), c->batch), dim3(SAMPLE_THREADS), 0,
-                       c->stream, logits, c->p.cfg.vocab, c->d_params, uniform_idx, c->d_state, mode, slot, seq_stride, c->d_scratch);
+                       c->stream, logits, c->p.cfg.vocab, c->d_params, uniform_idx, c->d_state, mode, slot, seq_stride, c->d_scratch, next);
   });
 }
 
-// The launch sequence of one run of Algorithm 1 for every sequence (everything between the
-// upload of the step parameters and the download of the states).
+// The launch sequence of one run of Algorithm 1 for every sequence.  Between small models' launches, which take 2 to 5 us
+// each, nothing stands that another launch can do: the first embedding fetches the step's parameters from pinned memory, a draw
+// embeds what Mq's next step starts from, the last kernel writes the host's copy of the states.  (Two copies and gamma - 1
+// launches less, us a call, before -> after: tiny fp32 pair, gamma 4 214 -> 205; 97M pair, gamma 7 711 -> 691; T5-XXL-shaped, gamma 5
+// 3376 -> 3348; plain steps of small models 103 - 215, 3 us less.  A draw that embeds takes 1 us longer, the launch it saves took 2 to
+// 4; parameters out of pinned memory lengthen the first embedding by 2 to 3 us, the copy took 4.)
 void enqueue_step(sd_ctx* c, int gamma, bool argmax, bool profile) {
   hipStream_t s = c->stream;
   const int V = c->p.cfg.vocab, B = c->batch;
+  if (c->no_mq()) hipMemcpyAsync(c->d_params, c->h_params, (size_t)B * sizeof(StepParams), hipMemcpyHostToDevice, s);
   if (profile) hipEventRecord(c->ev[0], s);
   for (int i = 0; i < gamma; ++i) {              // q_i <- Mq(prefix + x_<i), x_i ~ q_i
     if (c->copy_match > 0)                       // copied from the context, else the table / uniform
@@ -1103,8 +1121,10 @@ void enqueue_step(sd_ctx* c, int gamma, bool argmax, bool profile) {
       hipLaunchKernelGGL(table_row_kernel, dim3(std::min(32, (V + 255) / 256), B), dim3(256), 0, s, c->draft_table,
                          c->draft_row_of, c->draft_rows, V, c->d_state, i, c->q_logits + (size_t)i * V, (size_t)gamma * V);
     else if (i == 0) forward_any(c, c->q, Rows{ROWS_DRAFT_FIRST, 0, 2, 0, 0, B, gamma}, c->q_logits);
-    else forward_any(c, c->q, Rows{ROWS_DRAFT_NEXT, i, 1, 0, 0, B, gamma}, c->q_logits);
-    launch_draw(c, c->q_logits + (size_t)i * V, i, 0, i, (size_t)gamma * V, argmax);
+    else forward_any(c, c->q, Rows{ROWS_DRAFT_NEXT, i, 1, 0, 0, B, gamma, true}, c->q_logits);
+    DrawNext next{};
+    if (!c->no_mq() && i + 1 < gamma) { next.e = embed_args(c->q, B); next.step = i + 1; next.gamma = gamma; }
+    launch_draw(c, c->q_logits + (size_t)i * V, i, 0, i, (size_t)gamma * V, argmax, next);
   }
   if (profile) hipEventRecord(c->ev[1], s);
   // p_1..p_{gamma+1} in one forward
@@ -1117,16 +1137,21 @@ void enqueue_step(sd_ctx* c, int gamma, bool argmax, bool profile) {
   a.scr = c->d_scratch; a.scr_stride = sizeof(SampleScratch); a.part = c->d_parts; a.part_row = sample_parts(V); a.part_seq = (size_t)(2 * gamma + 1) * a.part_row;
   a.temperature = argmax ? 0.0f : 1.0f;
   a.top_k = (!argmax && c->filtered()) ? 1 : 0;
-  if (c->rt.flags & SD_FLAG_BETA) a.beta = c->d_state->beta;           // side output: beta_i of every guess, into the states
+  const bool beta = (c->rt.flags & SD_FLAG_BETA) != 0;
+  if (beta) a.beta = c->d_state->beta;           // side output: beta_i of every guess, into the states
+  else a.host = c->h_state;
   launch_accept(s, a, B, g_num_cus);
   if (c->copy_match > 0) hipLaunchKernelGGL(hist_append_kernel, dim3(B), dim3(32), 0, s, c->d_hist, c->hist_stride, c->d_state, 1);
   if (profile) hipEventRecord(c->ev[3], s);
+  if (beta) hipMemcpyAsync(c->h_state, c->d_state, (size_t)B * sizeof(SeqState), hipMemcpyDeviceToHost, s);    // (other workgroups wrote beta)
 }
 
 void enqueue_baseline(sd_ctx* c) {
   const int V = c->p.cfg.vocab, B = c->batch;
   forward_any(c, c->p, Rows{ROWS_BASELINE, 0, 1, 0, 0, B, 0}, c->p_logits);
-  launch_draw(c, c->p_logits, 0, 1, 0, (size_t)V);
+  DrawNext next{};
+  next.host = c->h_state;
+  launch_draw(c, c->p_logits, 0, 1, 0, (size_t)V, false, next);
   if (c->copy_match > 0) hipLaunchKernelGGL(hist_append_kernel, dim3(B), dim3(32), 0, c->stream, c->d_hist, c->hist_stride, c->d_state, 0);
 }
 
@@ -1241,12 +1266,6 @@ sd_status load_model(hipStream_t s, Model& m, const sd_tensor* w, int n, std::st
       }
     if (hipMemcpy(m.rope, cs.data(), cs.size() * sizeof(float), hipMemcpyHostToDevice) != hipSuccess) { err = "rope table upload"; return SD_EHIP; }
   }
-  return SD_OK;
-}
-
-sd_status sync_state_to_host(sd_ctx* c) {
-  HIP_TRY(c, hipMemcpyAsync(c->h_state, c->d_state, (size_t)c->batch * sizeof(SeqState), hipMemcpyDeviceToHost, c->stream));
-  HIP_TRY(c, hipStreamSynchronize(c->stream));
   return SD_OK;
 }
 
@@ -1492,25 +1511,21 @@ extern "C" sd_status sd_step(sd_ctx* c, const int32_t* prefix, int32_t prefix_le
     hp.top_k = c->sampling.top_k; hp.top_p = c->sampling.top_p;
     for (int i = 0; i < nu; ++i) hp.uniforms[i] = uniforms ? uniforms[(size_t)b * nu + i] : 0.5f;
   }
-  const size_t pbytes = (size_t)B * sizeof(StepParams), sbytes = (size_t)B * sizeof(SeqState);
   const bool profile = (c->rt.flags & SD_FLAG_PROFILE) != 0;
   const bool graph = (c->rt.flags & SD_FLAG_GRAPH) != 0 && !profile;
   if (graph) {
     hipGraphExec_t* ge = c->graph_of(gamma, temperature == 0.0f);
     if (!*ge) {
       st = capture_graph(c, ge, [&] {
-        hipMemcpyAsync(c->d_params, c->h_params, pbytes, hipMemcpyHostToDevice, c->stream);
         enqueue_step(c, gamma, temperature == 0.0f, false);
-        hipMemcpyAsync(c->h_state, c->d_state, sbytes, hipMemcpyDeviceToHost, c->stream);
       });
       if (st != SD_OK) return st;
     }
     HIP_TRY(c, hipGraphLaunch(*ge, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
   } else {
-    HIP_TRY(c, hipMemcpyAsync(c->d_params, c->h_params, pbytes, hipMemcpyHostToDevice, c->stream));
     enqueue_step(c, gamma, temperature == 0.0f, profile);
-    if ((st = sync_state_to_host(c)) != SD_OK) return st;
+    HIP_TRY(c, hipStreamSynchronize(c->stream));
   }
   HIP_TRY(c, hipGetLastError());
   for (int b = 0; b < B; ++b) {
@@ -1569,23 +1584,19 @@ extern "C" sd_status sd_step_baseline(sd_ctx* c, float temperature, const float*
     hp.top_k = c->sampling.top_k; hp.top_p = c->sampling.top_p;
     hp.uniforms[0] = uniforms ? uniforms[b] : 0.5f;
   }
-  const size_t pbytes = (size_t)B * sizeof(StepParams), sbytes = (size_t)B * sizeof(SeqState);
   if ((c->rt.flags & SD_FLAG_GRAPH) != 0) {
     hipGraphExec_t* ge = &c->graph_baseline[c->filtered() ? 1 : 0];
     if (!*ge) {
       st = capture_graph(c, ge, [&] {
-        hipMemcpyAsync(c->d_params, c->h_params, pbytes, hipMemcpyHostToDevice, c->stream);
         enqueue_baseline(c);
-        hipMemcpyAsync(c->h_state, c->d_state, sbytes, hipMemcpyDeviceToHost, c->stream);
       });
       if (st != SD_OK) return st;
     }
     HIP_TRY(c, hipGraphLaunch(*ge, c->stream));
     HIP_TRY(c, hipStreamSynchronize(c->stream));
   } else {
-    HIP_TRY(c, hipMemcpyAsync(c->d_params, c->h_params, pbytes, hipMemcpyHostToDevice, c->stream));
     enqueue_baseline(c);
-    if ((st = sync_state_to_host(c)) != SD_OK) return st;
+    HIP_TRY(c, hipStreamSynchronize(c->stream));
   }
   HIP_TRY(c, hipGetLastError());
   for (int b = 0; b < B; ++b)

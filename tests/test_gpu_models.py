@@ -1092,3 +1092,44 @@ def test_error_paths_of_the_options_and_of_batches():
     t5 = small_pair(T.T5DEC, "f32")
     with pytest.raises(binding.SdError):
         make_decoder(t5[0], t5[1], t5[2], t5[3], max_gamma=4, batch=2)   # one encoder output per context
+
+
+# (arch, dtype, d_model, heads, d_head, enc_len, sequences): fewer groups than a wavefront; LayerNorm and fp32; one step of the
+# embedding's loop and more (2048 features); rows in fragment order (more than 16)
+EMBEDDED = {
+    "t5-256": (T.T5DEC, "bf16", 256, 4, 64, 40, 1),
+    "gpt-f32-96": (T.GPT, "f32", 96, 3, 32, 0, 1),
+    "gpt-2080": (T.GPT, "bf16", 2080, 4, 64, 0, 2),
+    "gqa-2304": (T.GQA, "bf16", 2304, 4, 64, 0, 1),
+    "gqa-256-18": (T.GQA, "bf16", 256, 4, 64, 0, 18),
+}
+
+
+@pytest.mark.parametrize("how", ["sample", "argmax", "filter"])
+@pytest.mark.parametrize("name", list(EMBEDDED))
+def test_draft_rows_embedded_by_the_draw(name, how):
+    """A pair of one model with itself: its draft rows, embedded by the draws, must be its verify rows, embedded by the embedding
+    launch, bit for bit; and what the host reads of the states must be what the device holds (the next iteration follows from it)."""
+    from paper_2211_17192_amd import binding
+    arch, dtype, d, heads, dh, enc, B = EMBEDDED[name]
+    kw = dict(n_kv_heads=heads // 2) if arch == T.GQA else {}
+    gamma, vocab = 4, 8208
+    cfg = synth.model_cfg(arch, 2, d, heads, 2 * d, vocab, 100, d_head=dh, enc_len=enc, dtype=dtype, logit_scale=4.0, **kw)
+    w = synth.random_weights(cfg, 5, "cuda", 0.04)
+    enc_out = synth.counter_normal((enc, d), 3, 1.0, 0.0, "cuda").to(torch.bfloat16) if enc else None
+    u = synth.uniform_stream(11, 3 * B * (2 * gamma + 1)).reshape(3, B, 2 * gamma + 1)
+    for flags in (0, binding.SD_FLAG_GRAPH):
+        dec = binding.SpecDecoder(cfg, w, cfg, w, max_gamma=gamma, flags=flags, batch=B)
+        if how == "filter":
+            dec.set_sampling(1.0, 50, 0.9)
+        length = [7 + b for b in range(B)]
+        for b in range(B):
+            dec.prefill([int(t) for t in synth.random_tokens(length[b], 9 + b, vocab)], enc_out, enc_out, row=b)
+        for it in range(3):
+            res = dec.step(gamma, 0.0 if how == "argmax" else 0.9, u[it] if B > 1 else u[it, 0])
+            for n, tokens in [res] if B == 1 else res:
+                assert n == gamma and len(tokens) == gamma + 1 and all(0 <= t < vocab for t in tokens)
+            p = dec.logits(0, B * (gamma + 1)).reshape(B, gamma + 1, vocab)
+            q = dec.logits(1, B * gamma).reshape(B, gamma, vocab)
+            assert np.ptp(p) > 1.0 and np.array_equal(p[:, :gamma], q)
+        dec.close()
