@@ -331,6 +331,16 @@ __device__ __forceinline__ void rows_tile_of_block(const RowsGemmArgs& a, int& b
   bm = (id - bz * per) % a.mtiles; bn = (id - bz * per) / a.mtiles;
 }
 
+// A weight fragment of the products below.  ONCE: all rows of the launch are one workgroup's, so each weight is read once and need not
+// stay in the L2s, where it would drive out the activations that every workgroup reads: non-temporal.  Where several row tiles
+// take the same weights they do stay.  64 rows, us a launch, plain / non-temporal: gated 14336 x 4096 49.0 / 42.0, QKV 6144 x 4096 18.4 / 17.7,
+// LM head 8192 x 4096 20.5 / 19.4 (a deeper stream without barriers, eight wavefronts with a K-slice each, was as slow as this one with plain
+// loads, 49.2); prompts of two row tiles and more (971 to 1314 rows, widths 2048 to 3424) 2 - 10 % slower a call with non-temporal loads.
+template <bool ONCE> __device__ __forceinline__ bf16x8 load_weight(const bf16x8* p) {
+  if (ONCE) return __builtin_nontemporal_load(p);
+  return *p;
+}
+
 // A workgroup of NWV (4 or 8) wavefronts takes NT * 16 * NWV features x MT * 16 rows.  A wavefront owns NT
 // weight tiles: their fragments go from memory into its registers and nowhere else, while the MT slabs of
 // activations pass through LDS and serve all wavefronts.
@@ -348,7 +358,7 @@ __device__ __forceinline__ void rows_tile_of_block(const RowsGemmArgs& a, int& b
 //   NT 4, MT 8, four (one a SIMD)        821        1000              725        667
 // Eight read the activations once per CU instead of twice, but their workgroups fill the chip in coarser
 // rounds (N 6144: 384 workgroups, one round and a half).
-template <int EPI, int NT, int MT, int NWV>
+template <int EPI, int NT, int MT, int NWV, bool ONCE>
 static __global__ __launch_bounds__(64 * NWV, 2) void gemm_rows_kernel(const RowsGemmArgs a) {
   constexpr int SUB = 4, NT_OUT = (EPI == EPI_GATED) ? NT / 2 : NT;
   constexpr int NFRAG = SUB * MT * 64, XPT = NFRAG / (64 * NWV);
@@ -392,7 +402,7 @@ static __global__ __launch_bounds__(64 * NWV, 2) void gemm_rows_kernel(const Row
   auto load_w = [&](int u, int ks) {
     const size_t o = (size_t)min(ks, KS - 1) * 512;
 #pragma unroll
-    for (int t = 0; t < NT; ++t) wf[t][u] = reinterpret_cast<const bf16x8*>(wbase[t] + o)[(unsigned)lane];
+    for (int t = 0; t < NT; ++t) wf[t][u] = load_weight<ONCE>(reinterpret_cast<const bf16x8*>(wbase[t] + o) + (unsigned)lane);
   };
   auto store_x = [&](int buf) {
 #pragma unroll
@@ -542,7 +552,7 @@ static __global__ __launch_bounds__(64 * NWV, 2) void gemm_rows_kernel(const Row
 // D: kpw is a multiple of it, or the k-steps past a slice's end are multiplied with zeros.
 // dynamic LDS: S * NT * MT KB + MT * 64 bytes.
 // (the smaller shapes: 128 registers, two workgroups of eight wavefronts a CU)
-template <int EPI, int NT, int MT, int D>
+template <int EPI, int NT, int MT, int D, bool ONCE>
 static __global__ __launch_bounds__(512, (NT + MT <= 3 || (NT + MT == 4 && D == 3)) ? 4 : 2) void gemm_slices_kernel(const RowsGemmArgs a) {
   extern __shared__ float lds[];
   f32x4* part = reinterpret_cast<f32x4*>(lds);       // [S][NT][MT][64 lanes]
@@ -566,7 +576,7 @@ static __global__ __launch_bounds__(512, (NT + MT <= 3 || (NT + MT == 4 && D == 
   auto load = [&](int u, int ks) {
     const size_t o = (size_t)min(ks, ks_last) * 64;
 #pragma unroll
-    for (int t = 0; t < NT; ++t) wf[u][t] = (wb[t] + o)[(unsigned)lane];
+    for (int t = 0; t < NT; ++t) wf[u][t] = load_weight<ONCE>(wb[t] + o + (unsigned)lane);
 #pragma unroll
     for (int m = 0; m < MT; ++m) xf[u][m] = (ks < ks1 ? xb[m] + o : zeros)[(unsigned)lane];
   };

@@ -452,8 +452,10 @@ hipError_t allow_slices_lds_t() {
   static_assert(bytes <= 160 * 1024, "gemm_slices_kernel: dynamic LDS");
   if constexpr (bytes <= 64 * 1024) return hipSuccess;
   else {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_slices_kernel<EPI, NT, MT, 4>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
-    if (e == hipSuccess) e = hipFuncSetAttribute(reinterpret_cast<const void*>(&gemm_slices_kernel<EPI, NT, MT, 3>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
+    hipError_t e = hipSuccess;
+    for (const void* f : {reinterpret_cast<const void*>(&gemm_slices_kernel<EPI, NT, MT, 4, false>), reinterpret_cast<const void*>(&gemm_slices_kernel<EPI, NT, MT, 3, false>),
+                          reinterpret_cast<const void*>(&gemm_slices_kernel<EPI, NT, MT, 4, true>), reinterpret_cast<const void*>(&gemm_slices_kernel<EPI, NT, MT, 3, true>)})
+      if (e == hipSuccess) e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes);
     return e;
   }
 }
@@ -890,7 +892,12 @@ int rows_grid(RowsGemmArgs& a, int waves_n) {        // workgroups of NT weight 
 template <int EPI, int MT, int NWV>
 void launch_gemm_rows_t(hipStream_t s, RowsGemmArgs a) {
   const int grid = rows_grid<EPI, 2, MT>(a, NWV);
-  hipLaunchKernelGGL((gemm_rows_kernel<EPI, 2, MT, NWV>), dim3(grid), dim3(64 * NWV), 0, s, a);
+  if constexpr (NWV == 4)                            // (eight wavefronts: more than one row tile)
+    if (a.mtiles == 1) {
+      hipLaunchKernelGGL((gemm_rows_kernel<EPI, 2, MT, NWV, true>), dim3(grid), dim3(64 * NWV), 0, s, a);
+      return;
+    }
+  hipLaunchKernelGGL((gemm_rows_kernel<EPI, 2, MT, NWV, false>), dim3(grid), dim3(64 * NWV), 0, s, a);
 }
 template <int EPI, int NT, int MT>
 bool launch_gemm_slices_t(hipStream_t s, RowsGemmArgs a, int most) {
@@ -898,8 +905,13 @@ bool launch_gemm_slices_t(hipStream_t s, RowsGemmArgs a, int most) {
   const int grid = rows_grid<EPI, NT, MT>(a, 1);
   if (grid > most) return false;
   const size_t lds = slices_lds_bytes(a.nchunk, NT, MT);
-  if (a.kpw % 4 != 0 && a.kpw % 3 == 0) hipLaunchKernelGGL((gemm_slices_kernel<EPI, NT, MT, 3>), dim3(grid), dim3(64 * a.nchunk), lds, s, a);
-  else hipLaunchKernelGGL((gemm_slices_kernel<EPI, NT, MT, 4>), dim3(grid), dim3(64 * a.nchunk), lds, s, a);
+  auto launch = [&](auto once) {
+    constexpr bool ONCE = decltype(once)::value;
+    if (a.kpw % 4 != 0 && a.kpw % 3 == 0) hipLaunchKernelGGL((gemm_slices_kernel<EPI, NT, MT, 3, ONCE>), dim3(grid), dim3(64 * a.nchunk), lds, s, a);
+    else hipLaunchKernelGGL((gemm_slices_kernel<EPI, NT, MT, 4, ONCE>), dim3(grid), dim3(64 * a.nchunk), lds, s, a);
+  };
+  if (a.mtiles == 1) launch(std::true_type());
+  else launch(std::false_type());
   return true;
 }
 // Which shape: measured on 256 CUs, us (rows x N x K).
