@@ -1401,10 +1401,12 @@ static __global__ __launch_bounds__(256, 6) void beta_kernel(const AcceptArgs a)
 // 64 sequences, gamma 7, vocabulary 32128 (123 MB), both launches, calls back to back: 31.2 us
 // (row_parts_kernel 21 - 23: 5.4 TB/s, where a pure read reaches 7); with one 1024-thread workgroup per row and
 // then one per sequence it was 42.2.  One sequence, gamma 4: 10.9 us against 16.8.
-// OWN_NONE: 64 registers, two workgroups a CU.
+// OWN_NONE, not ALONE: 64 registers, two workgroups a CU.  ALONE: twice the registers, where every workgroup has a CU of its own
+// (loads that 64 hold back leave at once: one sequence, gamma 4, 32128 11.2 us -> 10.9; two, gamma 5, 128000 13.6 -> 13.3; with beta,
+// two, gamma 6, 40397 13.5 -> 13.1; 16, gamma 5, top-k 50, 32000 15.6 -> 15.4).
 enum { OWN_NONE, OWN_SEQUENCE, OWN_ROWS };           // whose the statistics are: row_parts_kernel's; this kernel's, a workgroup per sequence / per logits row
-template <int OWN>
-static __global__ __launch_bounds__(SAMPLE_THREADS, OWN == OWN_NONE ? 8 : 4) void accept_kernel(const AcceptArgs a) {
+template <int OWN, bool ALONE = OWN != OWN_NONE>
+static __global__ __launch_bounds__(SAMPLE_THREADS, ALONE ? 4 : 8) void accept_kernel(const AcceptArgs a) {
   __shared__ SampleSmem sm;
   __shared__ RowStat srow[2 * SAMPLE_MAX_GAMMA + 1];
   const int b = blockIdx.y, tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -1484,7 +1486,7 @@ static __global__ __launch_bounds__(SAMPLE_THREADS, OWN == OWN_NONE ? 8 : 4) voi
     rp.zp = P + (size_t)n * V; rp.zq = with_q ? Q + (size_t)n * V : nullptr;
     rp.mp = sp.m; rp.mq = sq.m; rp.tp = sp.thr; rp.tq = sq.thr; rp.invT = invT; rp.V = V;
     rp.invSp = 1.0 / sp.S; rp.invSq = with_q ? len / sq.S : 0.0;                 // q enters the residual as l * q
-    constexpr int CB = OWN == OWN_NONE ? 2 : 4;      // chunks whose loads a wavefront keeps in flight
+    constexpr int CB = ALONE ? 4 : 2;      // chunks whose loads a wavefront keeps in flight
     const int c0 = (OWN ? 0 : (int)blockIdx.x) * SAMPLE_CHUNKS_WG * a.chunks_wave + wave;
     for (int i0 = 0; i0 < a.chunks_wave; i0 += CB) {
       RawPair raw[CB];
@@ -1647,7 +1649,8 @@ inline void launch_accept(hipStream_t stream, AcceptArgs a, int rows, int cus) {
   const dim3 grid(own == OWN_ROWS ? nrows : a.draw_wgs + beta_wgs, rows), block(SAMPLE_THREADS);
   if (own == OWN_SEQUENCE) hipLaunchKernelGGL(accept_kernel<OWN_SEQUENCE>, grid, block, 0, stream, a);
   else if (own == OWN_ROWS) hipLaunchKernelGGL(accept_kernel<OWN_ROWS>, grid, block, 0, stream, a);
-  else hipLaunchKernelGGL(accept_kernel<OWN_NONE>, grid, block, 0, stream, a);
+  else if ((a.draw_wgs + beta_wgs) * rows <= cus) hipLaunchKernelGGL((accept_kernel<OWN_NONE, true>), grid, block, 0, stream, a);
+  else hipLaunchKernelGGL((accept_kernel<OWN_NONE, false>), grid, block, 0, stream, a);
   if (beta_apart) hipLaunchKernelGGL(beta_kernel, dim3(a.gamma, rows), dim3(256), 0, stream, a);
 }
 

@@ -387,6 +387,12 @@ def test_draw_beside_much_beta(gamma):
     check(*synth.sampler_case(16, gamma, 9000, 1.0, 5), 1.0)
 
 
+@pytest.mark.parametrize("rows", [85, 86])
+def test_a_cu_of_its_own_and_two_on_each(rows):
+    """Three workgroups a sequence: 255 of them, and 258, which share the CUs two by two."""
+    check(*synth.sampler_case(rows, 3, 9000, 1.0, rows), 1.0)
+
+
 @pytest.mark.parametrize("m", [1, 2, 33, 63, 64, 65, 100, 127, 128])
 @pytest.mark.parametrize("part", [1.0, 0.5])
 def test_short_lists_of_every_length_with_ties(m, part):
