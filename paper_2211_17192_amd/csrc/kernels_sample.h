@@ -1385,9 +1385,8 @@ __device__ __forceinline__ void beta_guess(const AcceptArgs& a, int b, int i, Ro
   if (tid == 0) (a.st ? a.st[b].beta : a.beta + (size_t)b * gamma)[i] = (float)t;
 }
 
-// A launch of its own where there are three guesses to two CUs or more: accept_kernel's registers let a CU hold
-// one of its workgroups, so hundreds of these would queue there (200 sequences, gamma 7, vocabulary 16384:
-// 114 -> 78 us a call; 38 of vocabulary 10454, 266 guesses: 23.2 there, 24.6 apart).  grid = (gamma, rows).
+// A launch of its own where there are more than two guesses a CU, four in long rows: beyond that the workgroups of
+// accept_kernel, two on a CU, would queue (launch_accept, where both sides of the line are measured).  grid = (gamma, rows).
 static __global__ __launch_bounds__(256, 6) void beta_kernel(const AcceptArgs a) {
   __shared__ RowStat jr[2];
   __shared__ double ctot[SAMPLE_CHUNK * SAMPLE_MAX_CHUNKS / SAMPLE_PART];
@@ -1641,7 +1640,10 @@ inline void launch_accept(hipStream_t stream, AcceptArgs a, int rows, int cus) {
   // beta's (16 sequences, gamma 4, vocabulary 50257: 13 and 4 of them a sequence 17.7 us, 7 and 4 13.9), unless
   // those leave less than two of a round (48 sequences, gamma 7, 32128: 45.9 us a call with four, 55.6 with one; 16, gamma
   // 15, 50257: 45.2 with 13, 49.8 with the one that is left; gamma 14: 43.5 with 13, 41.8 with the two)
-  const bool beta_apart = a.beta != nullptr && 2 * rows * a.gamma > 3 * cus && a.temperature > 0.0f;   // (argmax: no rows to read)
+  // (beta in the launch / apart: 64, gamma 7, 32128 48.0 us / 52.2; 200, gamma 5, 12000 46.9 / 48.6; 40, gamma 10, 4096 12.9 / 16.3;
+  //  100, gamma 5, 4096 15.9 / 16.3; but 200, gamma 7, 16384 78.0 / 74.0; 200, gamma 5, 2048 19.7 / 16.5; 200, gamma 3, 1500 17.5 / 15.3;
+  //  1000, gamma 1, 8192 52.2 / 50.1)
+  const bool beta_apart = a.beta != nullptr && rows * a.gamma > (a.V > 8192 ? 4 : 2) * cus && a.temperature > 0.0f;   // (argmax: no rows to read)
   const int beta_wgs = (a.beta != nullptr && !beta_apart) ? a.gamma : 0;
   const int round = max(1, (beta_wgs ? 1 : 2) * cus / rows), left = round - beta_wgs, most = own ? 1 : min(wgs, left >= 2 ? left : round);
   a.chunks_wave = (wgs + most - 1) / most;

@@ -340,7 +340,7 @@ def test_calls_without_beta(vocab, temperature):
 
 
 def test_more_beta_than_compute_units():
-    """The acceptance probabilities of a call with 3/2 guesses a CU and more come from a launch of their own."""
+    """The acceptance probabilities of more guesses than there are CUs."""
     zp, zq, x, r, s = synth.sampler_case(80, 5, 2050, 1.0, 23)
     check(zp, zq, x, r, s, 1.0)
 
@@ -385,6 +385,12 @@ def test_the_draw_keeps_its_workgroups_beside_much_beta():
 @pytest.mark.parametrize("gamma", [14, 15])
 def test_draw_beside_much_beta(gamma):
     check(*synth.sampler_case(16, gamma, 9000, 1.0, 5), 1.0)
+
+
+@pytest.mark.parametrize("rows,gamma,vocab", [(128, 4, 1030), (171, 3, 1030), (204, 5, 8196), (205, 5, 8196)])
+def test_beta_in_the_launch_and_apart(rows, gamma, vocab):
+    """Two guesses a CU and one more in short rows, four and some more in long ones."""
+    check(*synth.sampler_case(rows, gamma, vocab, 1.0, rows), 1.0)
 
 
 @pytest.mark.parametrize("rows", [85, 86])
