@@ -11,7 +11,8 @@
  * Conventions
  *  - "host" / "dev" in a comment says where a pointer must live.
  *  - All calls are synchronous with respect to their host outputs: they
- *    enqueue on the context's stream and wait for it before returning.
+ *    enqueue on the context's stream (sd_runtime_cfg.stream) and wait for it
+ *    before returning.
  *  - A context is not thread-safe.  Calls on one context must not overlap.
  *  - Errors are return codes only; a failed call leaves the decoding state
  *    unchanged.  sd_last_error() gives a human-readable reason.
@@ -144,8 +145,10 @@ typedef struct {
   void*   workspace;        /* dev, 256-byte aligned, caller-owned, outlives the context */
   size_t  workspace_bytes;
   void*   stream;           /* hipStream_t every call enqueues on (default priority, capturable: not the
-                               legacy default stream), or NULL: the context creates a non-blocking stream
-                               of its own and destroys it in sd_free */
+                               legacy default stream), or NULL: the context creates non-blocking streams
+                               of its own, on the second of which Mq's prompt runs beside Mp's, and
+                               destroys them in sd_free; what a call reads on the device must then be
+                               finished before the call */
   int32_t flags;
 } sd_runtime_cfg;
 
@@ -186,7 +189,8 @@ sd_status sd_load_models(sd_ctx** out,
  * fills both KV caches for prompt[0 .. prompt_len-2] and records the last
  * token.  prompt: host, prompt_len >= 1 ids.  enc_out_p / enc_out_q: dev,
  * [enc_len, d_model] of the respective model in its dtype (T5DEC), else NULL;
- * their cross-attention keys / values are computed here, once.
+ * their cross-attention keys / values are computed here, once (read on the
+ * caller's stream, behind what it holds; without one they must be finished).
  * row: the sequence, 0..batch-1; sd_step needs every sequence prefilled.
  * Requires prompt_len + max_gamma + 1 <= max_len of both models. */
 sd_status sd_prefill(sd_ctx* ctx, int32_t row, const int32_t* prompt, int32_t prompt_len,

@@ -216,8 +216,7 @@ struct sd_ctx {
   sd_runtime_cfg rt{};
   hipStream_t stream = nullptr;
   bool own_stream = false;
-  hipStream_t side = nullptr;        // sd_prefill: Mq's launches
-  hipEvent_t fork = nullptr;
+  hipStream_t side = nullptr;        // sd_prefill: Mq's launches, where the stream is the context's own
   int* h_prompt = nullptr;           // pinned [max_len]: a prompt on its way to the device
   SeqState* d_state = nullptr;
   StepParams* d_params = nullptr;
@@ -1349,6 +1348,7 @@ extern "C" sd_status sd_load_models(sd_ctx** out, const sd_model_cfg* p_cfg, con
   else {                       // a stream of the context's own (not the legacy default stream, which cannot be captured)
     if (hipStreamCreateWithFlags(&c->stream, hipStreamNonBlocking) != hipSuccess) return bail(SD_EHIP, "stream creation failed");
     c->own_stream = true;
+    if (hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking) != hipSuccess) return bail(SD_EHIP, "stream creation failed");
   }
   const size_t B = (size_t)rt->batch;
   c->len.assign(B, 0); c->last_tok.assign(B, -1); c->ready.assign(B, 0); c->hist_len.assign(B, 0); c->mq_stale.assign(B, 0);
@@ -1356,9 +1356,6 @@ extern "C" sd_status sd_load_models(sd_ctx** out, const sd_model_cfg* p_cfg, con
       hipHostMalloc(reinterpret_cast<void**>(&c->h_params), B * sizeof(StepParams), hipHostMallocDefault) != hipSuccess ||
       hipHostMalloc(reinterpret_cast<void**>(&c->h_prompt), (size_t)p_cfg->max_len * sizeof(int), hipHostMallocDefault) != hipSuccess)
     return bail(SD_EHIP, "pinned allocation failed");
-  if (hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking) != hipSuccess ||
-      hipEventCreateWithFlags(&c->fork, hipEventDisableTiming) != hipSuccess)
-    return bail(SD_EHIP, "stream creation failed");
   c->p.stream = c->q.stream = c->stream;
   std::memset(c->h_state, 0, B * sizeof(SeqState));
   std::memset(c->h_params, 0, B * sizeof(StepParams));
@@ -1400,7 +1397,6 @@ extern "C" void sd_free(sd_ctx* c) {
   if (!c) return;
   if (c->stream) hipStreamSynchronize(c->stream);
   if (c->side) { hipStreamSynchronize(c->side); hipStreamDestroy(c->side); }
-  if (c->fork) hipEventDestroy(c->fork);
   for (auto& g : c->graphs) if (g) hipGraphExecDestroy(g);
   for (auto& g : c->graph_baseline) if (g) hipGraphExecDestroy(g);
   for (auto& e : c->ev) if (e) hipEventDestroy(e);
@@ -1439,8 +1435,9 @@ extern "C" sd_status sd_prefill(sd_ctx* c, int32_t row, const int32_t* prompt, i
   for (int i = 0; i < 16; ++i) { st.x[i] = 0; st.out[i] = -1; }
   c->h_state[row] = st;
   std::memcpy(c->h_prompt, prompt, (size_t)n * sizeof(int));
-  // The two models' prompts share nothing, so Mq's launches go to a stream of their own: small models' prompts are
-  // chains of short launches, and large ones' leave CUs to each other at the ends of their products.  (Before, each
+  // The two models' prompts share nothing, so Mq's launches go to a second stream of the context's: small models' prompts are
+  // chains of short launches, and large ones' leave CUs to each other at the ends of their products.  On a caller's stream
+  // they follow Mp's: the caller may have masked its CUs or time what is on it.  (Before, each
   // model's prompt was copied from pageable memory and waited for, and the state and the history behind both: four
   // copies and three waits.  us, a new sequence's
   // prefill and first plain step: 2000 tokens, two 8B-class layers 1619 -> 1512; 128 tokens, 97M pair 896 -> 785; T5-XXL
@@ -1460,12 +1457,7 @@ extern "C" sd_status sd_prefill(sd_ctx* c, int32_t row, const int32_t* prompt, i
       forward_any(c, m, Rows{ROWS_PREFILL, 0, std::min(step, n - 1 - s0), s0, row, 1, 0}, nullptr);
   };
   hipError_t e = hipSuccess;
-  const bool both = work[0] && work[1];
-  if (both && !c->own_stream) {                      // the caller's stream: what it holds comes first (our own is empty between calls)
-    e = hipEventRecord(c->fork, c->stream);
-    if (e == hipSuccess) e = hipStreamWaitEvent(c->side, c->fork, 0);
-  }
-  const bool apart = both && e == hipSuccess;        // (else one after the other)
+  const bool apart = work[0] && work[1] && c->side != nullptr;         // (both streams are empty between calls: no fork)
   if (apart) { c->q.stream = c->side; c->q.beside = true; }
   hipLaunchKernelGGL(start_sequence_kernel, dim3((n + 255) / 256), dim3(256), 0, c->stream, c->h_prompt, n, c->p.prompt, apart ? nullptr : c->q.prompt,
                      c->d_hist + (size_t)row * c->hist_stride, c->h_state + row, c->d_state + row);

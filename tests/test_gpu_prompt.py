@@ -249,7 +249,7 @@ def test_last_prompt_rows_of_both_models_beside_each_other():
     prefill_equals_token_by_token((T.GQA, 256, 4, 2, 128, 512, 3, 2057, 0), False)
 
 
-@pytest.mark.parametrize("layers_q", [1, 3])        # Mq's launches behind Mp's, and ahead of them
+@pytest.mark.parametrize("layers_q", [1, 3])        # a draft of fewer layers than the target, and of more
 def test_prompt_waits_for_the_callers_stream(layers_q, monkeypatch):
     """sd_prefill on a stream of the caller's that still computes the encoder outputs: both models' launches come behind it."""
     import ctypes as C

@@ -1,0 +1,66 @@
+"""What the library puts on which stream, seen from the HIP calls it makes (launch_log.cpp stands in for the runtime; no GPU)."""
+import os
+import subprocess
+
+import pytest
+
+from oracle import transformer as T
+from paper_2211_17192_amd import binding, synth
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+
+@pytest.fixture(scope="module")
+def run(tmp_path_factory):
+    lib = os.path.join(ROOT, "paper_2211_17192_amd")
+    exe = str(tmp_path_factory.mktemp("launches") / "launch_log")
+    subprocess.run(["g++", "-std=c++17", "-O1", "-rdynamic", "-I", os.path.join(ROOT, "include"), os.path.join(ROOT, "tests", "launch_log.cpp"),
+                    os.path.join(lib, "libsd.so"), "-Wl,-rpath," + lib, "-Wl,--allow-shlib-undefined", "-o", exe], check=True)
+
+    def go(cfg_p, cfg_q, *calls):
+        """One list of lines per call."""
+        text = []
+        for cfg in (cfg_p, cfg_q):
+            keys = ("arch", "n_layers", "d_model", "n_heads", "n_kv_heads", "d_head", "d_ff", "vocab", "max_len", "enc_len")
+            text.append("model " + " ".join(str(int(cfg[k])) for k in keys) + (" 1" if cfg["dtype"] == "bf16" else " 0"))
+            for name, (shape, _) in synth.weight_shapes(cfg).items():
+                text.append(f"tensor {name} {shape[0]} {shape[1] if len(shape) > 1 else 0}")
+        res = subprocess.run([exe], input="\n".join(text + list(calls)) + "\n", text=True, capture_output=True, timeout=60)
+        assert res.returncode == 0, res.stderr
+        out, part = [], []
+        for line in res.stdout.splitlines():
+            if line.startswith("call "):
+                out.append(part)
+                part = []
+            elif line == "loaded":
+                part = []
+            else:
+                part.append(line)
+        return out
+    return go
+
+
+def launches(lines):
+    """(stream, kernel, grid, notes) of every launch."""
+    words = [l.split() for l in lines if l.startswith("launch ")]
+    return [(int(w[1]), w[2], tuple(int(v) for v in w[3:6]), tuple(w[6:])) for w in words]
+
+
+def pair(arch, max_len=200, layers=2, dtype="bf16", **kw):
+    cfg = synth.model_cfg(arch, layers, 256, 4, 512, 512, max_len, d_head=64, dtype=dtype, **kw)
+    return cfg, dict(cfg, n_layers=1)
+
+
+@pytest.mark.parametrize("arch,kw", [(T.GPT, {}), (T.T5DEC, dict(enc_len=61)), (T.GQA, dict(n_kv_heads=2))])
+def test_a_callers_stream_gets_every_launch(run, arch, kw):
+    """sd_runtime_cfg.stream: every call enqueues on it (a caller may have masked its CUs, or time what is on it)."""
+    calls = ["load 1 4 1 1 0", "prefill 0 100", "step 4 1.0", "prefill 0 9", "measure", "plain 1.0"]
+    for call, lines in zip(calls, run(*pair(arch, **kw), *calls)):
+        assert launches(lines) and {l.split()[1] for l in lines if l.split()[0] in ("launch", "copy", "graph", "sync", "record")} == {"0"}, call
+
+
+def test_the_contexts_own_streams_are_both_waited_for(run):
+    """Without a caller's stream Mq's prompt runs beside Mp's; the host waits for both and nothing is enqueued behind."""
+    _, lines = run(*pair(T.GQA), "load 1 4 0 0 0", "prefill 0 100")
+    assert {l[0] for l in launches(lines)} == {1, 2}
+    assert sorted(lines[-2:]) == ["sync 1", "sync 2"]
