@@ -116,14 +116,15 @@ static __global__ __launch_bounds__(256) void embed_kernel(
 }
 
 // A new sequence's tokens and state out of pinned host memory, to the models' prompts, the history and the state (each
-// optional), in one launch.  grid * 256 threads >= n.
+// optional), in one launch; clears SAMPLE_TICKETS words of tickets.  grid * 256 threads >= n.
 static __global__ __launch_bounds__(256) void start_sequence_kernel(const int* __restrict__ tokens, int n, int* __restrict__ prompt_p,
                                                                     int* __restrict__ prompt_q, int* __restrict__ hist,
-                                                                    const SeqState* __restrict__ from, SeqState* __restrict__ to) {
+                                                                    const SeqState* __restrict__ from, SeqState* __restrict__ to, unsigned* __restrict__ tickets) {
   const int i = (int)(blockIdx.x * 256 + threadIdx.x);
   constexpr int WORDS = sizeof(SeqState) / 4;
   static_assert(WORDS <= 256 && sizeof(SeqState) % 4 == 0, "one workgroup copies a state");
   if (to != nullptr && i < WORDS) reinterpret_cast<int*>(to)[i] = reinterpret_cast<const int*>(from)[i];
+  if (tickets != nullptr && i < SAMPLE_TICKETS) tickets[i] = 0u;
   if (i >= n) return;
   const int t = tokens[i];
   if (prompt_p != nullptr) prompt_p[i] = t;

@@ -85,7 +85,7 @@ struct Model {
   int* row_pos = nullptr;
   int* prompt = nullptr;
   hipStream_t stream = nullptr;    // where its launches go: the context's stream, or while the other model's run beside them
-  bool beside = false;             // (sd_prefill) the context's second one; the tickets, which both models use, are then left alone
+  bool beside = false;             // (sd_prefill) the context's second one, with attention tickets of their own
 };
 
 bool cfg_ok(const sd_model_cfg& c, std::string& why) {
@@ -552,7 +552,11 @@ void launch_attn(hipStream_t s, const Model& m, AttnArgs a, int nseq, SampleScra
   const int G = a.H / a.Hkv, DH = m.cfg.d_head;
   const bool prompt = a.R > MAX_ROWS;              // one sequence's prompt rows: groups of full row tiles
   a.G = G; a.g_mul = 65536 / G + 1;
-  a.tickets = tickets->ticket + 1; a.ticket_stride = (int)(sizeof(SampleScratch) / sizeof(unsigned));      // (the first is the draws')
+  static_assert(sizeof(SampleScratch::tot) >= ATTN_TICKETS * sizeof(unsigned), "tickets of a prompt beside another");
+  // (the first is the draws'; beside the other model's prompt, where nothing is drawn: in the place of a draw's totals, cleared by start_sequence_kernel.
+  // Ranges in turn there: 8100 tokens in passes of 16 rows, two layers of 32 heads of 64 each 59 ms instead of 46.7; Mq of four layers of 8 heads 97 instead of 66)
+  a.tickets = m.beside ? reinterpret_cast<unsigned*>(tickets->tot) : tickets->ticket + 1;
+  a.ticket_stride = (int)(sizeof(SampleScratch) / sizeof(unsigned));
   // few kv heads leave most CUs idle: split the (independent) rows over more workgroups
   if (prompt) {
     a.rows_per_wg = prompt_rows_per_wg(m.cfg);
@@ -569,11 +573,10 @@ void launch_attn(hipStream_t s, const Model& m, AttnArgs a, int nseq, SampleScra
     const int RG = a.rows_per_wg * G;
     const int nw = (a.nsplit > 1) ? 4 : attn_mma_waves(a.cross ? a.kv_len : (m.cfg.max_len + 1) / 2);
     if (a.pj_w != nullptr && !(a.cross && DH == 64 && RG <= 16 && G == 1)) a.pj_w = nullptr;   // (callers check; never project elsewhere)
-    // key ranges: a workgroup each, with a ticket per kv head, or one after the other (a prompt's row groups; its last rows
-    // where the other model's launches run beside these; more heads than tickets; where sequences x kv heads are two workgroups a CU by themselves).  us a layer, in turn / spread, one row, heads
+    // key ranges: a workgroup each, with a ticket per kv head, or one after the other (a prompt's row groups; more heads than tickets; where sequences x kv heads are two workgroups a CU by themselves).  us a layer, in turn / spread, one row, heads
     // of 64, max_len 8192: 64 heads, one sequence of 500, 2000, 8000 keys 6.7 / 6.3, 21.1 / 12.8, 71.7 / 28.7; four sequences
     // 9.7 / 9.6, 27.1 / 26.4, 95.9 / 99.2; 32 heads, 16 sequences 14.1 / 16.4, 49.9 / 52.3, 183.7 / 184.8.
-    const bool in_turn = a.nsplit > 1 && (prompt || m.beside || a.Hkv > ATTN_MAX_TICKETS || nseq * a.Hkv >= 2 * g_num_cus);
+    const bool in_turn = a.nsplit > 1 && (prompt || a.Hkv > ATTN_MAX_TICKETS || nseq * a.Hkv >= 2 * g_num_cus);
     size_t ll = attn_mma_lds_bytes(RG, DH, nw);
     a.ml_off = (int)(ll / 4);
     ll += attn_mma_range_lds_bytes(a.nsplit);
@@ -1460,9 +1463,10 @@ extern "C" sd_status sd_prefill(sd_ctx* c, int32_t row, const int32_t* prompt, i
   const bool apart = work[0] && work[1] && c->side != nullptr;         // (both streams are empty between calls: no fork)
   if (apart) { c->q.stream = c->side; c->q.beside = true; }
   hipLaunchKernelGGL(start_sequence_kernel, dim3((n + 255) / 256), dim3(256), 0, c->stream, c->h_prompt, n, c->p.prompt, apart ? nullptr : c->q.prompt,
-                     c->d_hist + (size_t)row * c->hist_stride, c->h_state + row, c->d_state + row);
+                     c->d_hist + (size_t)row * c->hist_stride, c->h_state + row, c->d_state + row, nullptr);
   if (apart)
-    hipLaunchKernelGGL(start_sequence_kernel, dim3((n + 255) / 256), dim3(256), 0, c->side, c->h_prompt, n, nullptr, c->q.prompt, nullptr, nullptr, nullptr);
+    hipLaunchKernelGGL(start_sequence_kernel, dim3((n + 255) / 256), dim3(256), 0, c->side, c->h_prompt, n, nullptr, c->q.prompt, nullptr, nullptr, nullptr,
+                       reinterpret_cast<unsigned*>(c->d_scratch[row].tot));
   // the longer chain of launches first: the host takes half as long for a launch as the GPU
   const bool q_first = apart && c->q.L.size() > c->p.L.size();
   if (q_first) fill(c->q, enc_q);

@@ -245,7 +245,7 @@ def test_smaller_workspaces_give_the_same_results(name, monkeypatch):
 
 
 def test_last_prompt_rows_of_both_models_beside_each_other():
-    """A pass of 2048 rows and one of 9, whose key ranges Mp merges by tickets while Mq, on its own stream, takes them in turn."""
+    """A pass of 2048 rows and one of 9, whose key ranges both models merge by tickets, on a stream and with tickets each."""
     prefill_equals_token_by_token((T.GQA, 256, 4, 2, 128, 512, 3, 2057, 0), False)
 
 

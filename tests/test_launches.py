@@ -64,3 +64,13 @@ def test_the_contexts_own_streams_are_both_waited_for(run):
     _, lines = run(*pair(T.GQA), "load 1 4 0 0 0", "prefill 0 100")
     assert {l[0] for l in launches(lines)} == {1, 2}
     assert sorted(lines[-2:]) == ["sync 1", "sync 2"]
+
+
+@pytest.mark.parametrize("least", [0, 1])           # passes of 2048 rows and a last one of 9; of 16 rows
+def test_key_ranges_of_both_prompts_are_spread(run, least):
+    """Each pass of up to 16 rows over a long context gives Mq's key ranges the workgroups that Mp's, of the same heads, get."""
+    cfg, _ = pair(T.GQA, max_len=3000)
+    _, lines = run(cfg, cfg, f"load 1 4 0 0 {least}", "prefill 0 2058")
+    attn = {s: [(k, g) for s2, k, g, _ in launches(lines) if s2 == s and "attn_mma_kernel" in k] for s in (1, 2)}
+    assert len(attn[1]) == (129 if least else 2) and attn[1][-1][1] == (4, 1, 6)           # (the last layer's is left out)
+    assert attn[2] == attn[1]
