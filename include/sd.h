@@ -303,8 +303,10 @@ sd_status sd_choose_gamma(double alpha, double c, int32_t gamma_max, int32_t* ga
 
 /*
  * Measure the two run times behind the cost coefficient c on a prefilled
- * sequence: one draft step of Mq (1-row forward + draw) and one standard
- * decoding step of Mp (1-row forward + draw), each replayed reps (1..1000)
+ * sequence: one draft step of Mq as an iteration repeats it (1-row forward on
+ * the row that the draw before it embedded, and the draw, which embeds the
+ * next) and one standard decoding step of Mp (1-row forward + draw, without the
+ * fetch of the step's parameters, which is an iteration's once), each replayed reps (1..1000)
  * times from a hipGraph between two HIP events.  mq_us, mp_us: host outputs,
  * microseconds per run.  The runs write only cache rows beyond the committed
  * sequence (or rewrite a committed row with the same values) and commit
@@ -341,7 +343,8 @@ sd_status sd_time_ffn_in(sd_ctx* ctx, int32_t rows, int32_t reps, double* us_per
  * run back to back, so the difference is that launch's duration in its real surroundings).
  *   which    : 0 = Mp over `rows` rows (1 = the standard decoding step of section 1, r > 1 = the
  *              scoring of r - 1 guesses, section 2.3), rows <= max_gamma + 1;
- *              1 = Mq, rows 1 (a draft step) or 2 (the first draft step of an iteration)
+ *              1 = Mq, rows 1 (a draft step; its row is embedded by the draw before it, outside of what
+ *              is timed) or 2 (the first draft step of an iteration).  Parameters are not fetched.
  *   skip_ops : SD_OP_* bits: the launches of these kinds are not recorded (their outputs keep
  *              whatever the last forward left, so the remaining launches do the same work).
  *              Where the cross-attention launch computes its own queries (small T5-type models,

@@ -679,8 +679,8 @@ int prefill_rows(const sd_model_cfg& c) { return std::min(MAX_ROWS, ATTN_MAX_RG 
 // by (mode, step) from the device-resident sequence states (ROWS_PREFILL: rps prompt tokens
 // of sequence seq0 from position start).  gamma fixes where the LM-head rows land in the
 // logits buffers ([seq][gamma+1][V] for Mp, [seq][gamma][V] for Mq).
-// embedded: the draw before it left the rows' embeddings.
-struct Rows { int mode, step, rps, start, seq0, nseq, gamma; bool embedded = false; };
+// embedded: the draw before it left the rows' embeddings; params: the embedding brings the step's parameters.
+struct Rows { int mode, step, rps, start, seq0, nseq, gamma; bool embedded = false, params = false; };
 
 // The rows of a forward of m, where forward() / forward_rows() read them.
 bool many_rows(const Model& m, int rows) { return m.rows_pass > 0 && rows > MAX_ROWS; }
@@ -696,10 +696,12 @@ EmbedArgs embed_args(const Model& m, int rows) {
 template <typename T>
 void launch_embed(sd_ctx* c, Model& m, const Rows& rw) {
   if (rw.embedded) return;
-  // the first launch of an iteration brings the step's parameters
-  const bool first = rw.mode == ROWS_DRAFT_FIRST || rw.mode == ROWS_BASELINE;
   hipLaunchKernelGGL((embed_kernel<T>), dim3(rw.nseq * rw.rps), dim3(256), 0, m.stream, rw.mode, rw.step, c->d_state, m.prompt, rw.start,
-                     embed_args(m, rw.nseq * rw.rps), rw.rps, rw.seq0, rw.gamma, first ? c->h_params : nullptr, c->d_params);
+                     embed_args(m, rw.nseq * rw.rps), rw.rps, rw.seq0, rw.gamma, rw.params ? c->h_params : nullptr, c->d_params);
+}
+void launch_embed_any(sd_ctx* c, Model& m, const Rows& rw) {
+  if (m.cfg.dtype == SD_BF16) launch_embed<bf16>(c, m, rw);
+  else launch_embed<float>(c, m, rw);
 }
 
 // One forward of model m; with `logits` the LM head runs on every row and each row's
@@ -1115,6 +1117,13 @@ void launch_draw(sd_ctx* c, const float* logits, int uniform_idx, int mode, int 
   });
 }
 
+// A draw that embeds the row of Mq's step `step`.
+DrawNext draw_next(sd_ctx* c, int step, int gamma) {
+  DrawNext next{};
+  next.e = embed_args(c->q, c->batch); next.step = step; next.gamma = gamma;
+  return next;
+}
+
 // The launch sequence of one run of Algorithm 1 for every sequence.  Between small models' launches, which take 2 to 5 us
 // each, nothing stands that another launch can do: the first embedding fetches the step's parameters from pinned memory, a draw
 // embeds what Mq's next step starts from, the last kernel writes the host's copy of the states.  (Two copies and gamma - 1
@@ -1134,11 +1143,9 @@ void enqueue_step(sd_ctx* c, int gamma, bool argmax, bool profile) {
     else if (c->draft_table)                     // table lookup instead of a forward
       hipLaunchKernelGGL(table_row_kernel, dim3(std::min(32, (V + 255) / 256), B), dim3(256), 0, s, c->draft_table,
                          c->draft_row_of, c->draft_rows, V, c->d_state, i, c->q_logits + (size_t)i * V, (size_t)gamma * V);
-    else if (i == 0) forward_any(c, c->q, Rows{ROWS_DRAFT_FIRST, 0, 2, 0, 0, B, gamma}, c->q_logits);
+    else if (i == 0) forward_any(c, c->q, Rows{ROWS_DRAFT_FIRST, 0, 2, 0, 0, B, gamma, false, true}, c->q_logits);
     else forward_any(c, c->q, Rows{ROWS_DRAFT_NEXT, i, 1, 0, 0, B, gamma, true}, c->q_logits);
-    DrawNext next{};
-    if (!c->no_mq() && i + 1 < gamma) { next.e = embed_args(c->q, B); next.step = i + 1; next.gamma = gamma; }
-    launch_draw(c, c->q_logits + (size_t)i * V, i, 0, i, (size_t)gamma * V, argmax, next);
+    launch_draw(c, c->q_logits + (size_t)i * V, i, 0, i, (size_t)gamma * V, argmax, (!c->no_mq() && i + 1 < gamma) ? draw_next(c, i + 1, gamma) : DrawNext{});
   }
   if (profile) hipEventRecord(c->ev[1], s);
   // p_1..p_{gamma+1} in one forward
@@ -1162,7 +1169,7 @@ void enqueue_step(sd_ctx* c, int gamma, bool argmax, bool profile) {
 
 void enqueue_baseline(sd_ctx* c) {
   const int V = c->p.cfg.vocab, B = c->batch;
-  forward_any(c, c->p, Rows{ROWS_BASELINE, 0, 1, 0, 0, B, 0}, c->p_logits);
+  forward_any(c, c->p, Rows{ROWS_BASELINE, 0, 1, 0, 0, B, 0, false, true}, c->p_logits);
   DrawNext next{};
   next.host = c->h_state;
   launch_draw(c, c->p_logits, 0, 1, 0, (size_t)V, false, next);
@@ -1720,12 +1727,16 @@ extern "C" sd_status sd_measure_cost(sd_ctx* c, int32_t reps, double* mq_us, dou
   HIP_TRY(c, hipMemcpyAsync(c->d_params, c->h_params, (size_t)B * sizeof(StepParams), hipMemcpyHostToDevice, c->stream));
   HIP_TRY(c, hipStreamSynchronize(c->stream));
   double us[2] = {0.0, 0.0};
+  const Rows again{ROWS_DRAFT_NEXT, 1, 1, 0, 0, B, 2};           // a draft step that is not the first: logits rows [seq][2][V], second of each
+  launch_embed_any(c, c->q, again);
   for (int which = 0; which < 2; ++which) {
     hipGraphExec_t ge = nullptr;
     const sd_status cs = capture_graph(c, &ge, [&] {
-      if (which == 0) {      // a draft step that is not the first of an iteration: guess x_1 in, q_2 and x_2 out
-        forward_any(c, c->q, Rows{ROWS_DRAFT_NEXT, 1, 1, 0, 0, B, 2}, c->q_logits);     // rows [seq][2][V], second of each
-        launch_draw(c, c->q_logits + (size_t)V, 1, 0, 1, (size_t)2 * V);
+      if (which == 0) {      // as an iteration repeats it: the row embedded by the draw before, q_2 and x_2 out, the next row (here: its own) embedded
+        Rows step = again;
+        step.embedded = true;
+        forward_any(c, c->q, step, c->q_logits);
+        launch_draw(c, c->q_logits + (size_t)V, 1, 0, 1, (size_t)2 * V, false, draw_next(c, 1, 2));
       } else {               // standard decoding's forward and draw; the draw lands in a guess slot, nothing is committed
         forward_any(c, c->p, Rows{ROWS_BASELINE, 0, 1, 0, 0, B, 0}, c->p_logits);
         launch_draw(c, c->p_logits, 0, 0, 1, (size_t)V);
@@ -1816,13 +1827,18 @@ extern "C" sd_status sd_time_forward(sd_ctx* c, int32_t which, int32_t rows, int
   for (int b = 0; b < B; ++b)
     if (c->len[b] + rows > std::min(c->p.cfg.max_len, c->q.cfg.max_len)) return fail(c, SD_ERANGE, "no room behind the committed sequence");
   hipGraphExec_t ge = nullptr;
+  Rows again{ROWS_DRAFT_NEXT, 1, 1, 0, 0, B, 2};
+  if (which == 1 && rows == 1) {                       // (an iteration's draws embed what these steps start from)
+    launch_embed_any(c, c->q, again);
+    again.embedded = true;
+  }
   c->skip_ops = skip_ops;
   const sd_status cs = capture_graph(c, &ge, [&] {
     if (which == 0) {
       if (rows == 1) forward_any(c, c->p, Rows{ROWS_BASELINE, 0, 1, 0, 0, B, 0}, c->p_logits);
       else forward_any(c, c->p, Rows{ROWS_VERIFY, 0, rows, 0, 0, B, rows - 1}, c->p_logits);
     } else {
-      if (rows == 1) forward_any(c, c->q, Rows{ROWS_DRAFT_NEXT, 1, 1, 0, 0, B, 2}, c->q_logits);
+      if (rows == 1) forward_any(c, c->q, again, c->q_logits);
       else forward_any(c, c->q, Rows{ROWS_DRAFT_FIRST, 0, 2, 0, 0, B, 2}, c->q_logits);
     }
   });

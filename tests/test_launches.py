@@ -74,3 +74,35 @@ def test_key_ranges_of_both_prompts_are_spread(run, least):
     attn = {s: [(k, g) for s2, k, g, _ in launches(lines) if s2 == s and "attn_mma_kernel" in k] for s in (1, 2)}
     assert len(attn[1]) == (129 if least else 2) and attn[1][-1][1] == (4, 1, 6)           # (the last layer's is left out)
     assert attn[2] == attn[1]
+
+
+@pytest.mark.parametrize("options", [[], ["filter"]])
+@pytest.mark.parametrize("arch,dtype,kw,batch", [(T.GPT, "f32", {}, 1), (T.GPT, "f32", {}, 18), (T.T5DEC, "bf16", dict(enc_len=61), 1),
+                                                 (T.GQA, "bf16", dict(n_kv_heads=2), 1), (T.GQA, "bf16", dict(n_kv_heads=2), 18)])
+def test_measurements_time_what_an_iteration_runs(run, arch, dtype, kw, batch, options):
+    """sd_measure_cost and sd_time_forward: the launches of a draft step that is neither the first nor the last of an iteration, of
+    its verify forward and of a plain step; only the fetch of the parameters, once an iteration, is nobody's."""
+    prefill = [f"prefill {b} 9" for b in range(batch)]
+    calls = [f"load {batch} 4 1 1 0", *options, *prefill, "measure", "time 1 1", "time 0 4", "time 0 1", "step 3 1.0", *prefill, "plain 1.0"]
+    out = dict(zip(calls, run(*pair(arch, dtype=dtype, **kw), *calls)))
+
+    def graphs(call):
+        got = []
+        for line in out[call]:
+            if line == "begin":
+                got.append([])
+            elif line == "end":
+                got.append(None)
+            elif got and got[-1] is not None:
+                got[-1].append(line)
+        return [[(k, g, n) for _, k, g, n in launches(part)] for part in got if part is not None]
+
+    (step,), (plain,) = graphs("step 3 1.0"), graphs("plain 1.0")
+    draws = [i for i, (k, _, _) in enumerate(step) if "sample_row" in k]
+    accept = next(i for i, (k, _, _) in enumerate(step) if "accept" in k or "row_parts" in k or "row_filter_kernelI" in k and i > draws[2])
+    assert len(draws) == 3 and [n for _, _, n in step].count(("fetches",)) == 1 and plain[0][2] == ("fetches",)
+    again, verify = step[draws[0] + 1: draws[1] + 1], step[draws[2] + 1: accept]
+    plain[0] = (*plain[0][:2], ())
+    assert again[-1][2] == ("embeds",)
+    assert graphs("measure") == [again, plain]
+    assert graphs("time 1 1") == [again[:-1]] and graphs("time 0 4") == [verify] and graphs("time 0 1") == [plain[:-1]]
