@@ -333,7 +333,7 @@ __device__ __forceinline__ void rows_tile_of_block(const RowsGemmArgs& a, int& b
 
 // A weight fragment of the products below.  ONCE: all rows of the launch are one workgroup's, so each weight is read once and need not
 // stay in the L2s, where it would drive out the activations that every workgroup reads: non-temporal.  Where several row tiles
-// take the same weights they do stay.  64 rows, us a launch, plain / non-temporal: gated 14336 x 4096 49.0 / 42.0, QKV 6144 x 4096 18.4 / 17.7,
+// take the same weights, and where they are few (weights_past_l2), they do stay.  64 rows, us a launch, plain / non-temporal: gated 14336 x 4096 49.0 / 42.0, QKV 6144 x 4096 18.4 / 17.7,
 // LM head 8192 x 4096 20.5 / 19.4 (a deeper stream without barriers, eight wavefronts with a K-slice each, was as slow as this one with plain
 // loads, 49.2); prompts of two row tiles and more (971 to 1314 rows, widths 2048 to 3424) 2 - 10 % slower a call with non-temporal loads.
 template <bool ONCE> __device__ __forceinline__ bf16x8 load_weight(const bf16x8* p) {

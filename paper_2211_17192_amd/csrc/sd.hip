@@ -893,11 +893,19 @@ int rows_grid(RowsGemmArgs& a, int waves_n) {        // workgroups of NT weight 
   a.mtiles = ((a.rows + 15) / 16 + MT - 1) / MT;
   return a.ntiles_wg * a.mtiles * a.batch;
 }
+// Whether the weights of a launch pass the L2s by (load_weight's ONCE, which says why): one workgroup reads each of them, and they would not stay for
+// the next forward anyway, being as many as the eight L2s of 4 MB hold.  Smaller ones of a draft are read again at its next step.  us a step, gamma 4,
+// plain loads everywhere / past the L2s wherever there is one row tile / by this rule: two layers of 1024 x 4096 (16 MB a launch at most) with themselves,
+// 17 and 64 sequences 361.7 / 370.8 / 361.7 and 533.5 / 538.0 / 533.6; as the draft of four layers of 2048, 64 sequences 857 / 866 / 856; of four
+// layers of 4096 x 14336, 17 sequences 869 / 851 / 845.
+template <int EPI> bool weights_past_l2(const RowsGemmArgs& a) {
+  return a.mtiles == 1 && (size_t)a.N * a.K * a.batch * (EPI == EPI_GATED ? 4 : 2) >= ((size_t)32 << 20);
+}
 template <int EPI, int MT, int NWV>
 void launch_gemm_rows_t(hipStream_t s, RowsGemmArgs a) {
   const int grid = rows_grid<EPI, 2, MT>(a, NWV);
   if constexpr (NWV == 4)                            // (eight wavefronts: more than one row tile)
-    if (a.mtiles == 1) {
+    if (weights_past_l2<EPI>(a)) {
       hipLaunchKernelGGL((gemm_rows_kernel<EPI, 2, MT, NWV, true>), dim3(grid), dim3(64 * NWV), 0, s, a);
       return;
     }
@@ -914,7 +922,7 @@ bool launch_gemm_slices_t(hipStream_t s, RowsGemmArgs a, int most) {
     if (a.kpw % 4 != 0 && a.kpw % 3 == 0) hipLaunchKernelGGL((gemm_slices_kernel<EPI, NT, MT, 3, ONCE>), dim3(grid), dim3(64 * a.nchunk), lds, s, a);
     else hipLaunchKernelGGL((gemm_slices_kernel<EPI, NT, MT, 4, ONCE>), dim3(grid), dim3(64 * a.nchunk), lds, s, a);
   };
-  if (a.mtiles == 1) launch(std::true_type());
+  if (weights_past_l2<EPI>(a)) launch(std::true_type());
   else launch(std::false_type());
   return true;
 }

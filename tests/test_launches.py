@@ -106,3 +106,15 @@ def test_measurements_time_what_an_iteration_runs(run, arch, dtype, kw, batch, o
     assert again[-1][2] == ("embeds",)
     assert graphs("measure") == [again, plain]
     assert graphs("time 1 1") == [again[:-1]] and graphs("time 0 4") == [verify] and graphs("time 0 1") == [plain[:-1]]
+
+
+def test_weights_pass_the_l2s_only_where_they_would_not_stay(run):
+    """32 sequences: each product of a small draft's step leaves its weights in the L2s for the next step; those of 32 MB and more that one row tile
+    of workgroups reads go past them."""
+    small = synth.model_cfg(T.GQA, 1, 1024, 8, 4096, 8192, 200, n_kv_heads=8, d_head=128, dtype="bf16")
+    large = synth.model_cfg(T.GQA, 1, 4096, 32, 14336, 8192, 200, n_kv_heads=8, d_head=128, dtype="bf16")
+    calls = ["load 32 3 1 1 0", *(f"prefill {b} 9" for b in range(32)), "time 1 1", "time 0 2"]
+    past = [["Lb1E" in k for _, k, _, _ in launches(lines) if "gemm_rows_kernel" in k or "gemm_slices_kernel" in k]
+            for lines in run(large, small, *calls)[-2:]]
+    assert past[0] == [False] * 5                              # QKV, O, FFN-in, FFN-out, LM head
+    assert past[1] == [True, False, True, True]                # (64 rows: O by two row tiles; FFN-out is gemm_split_kernel's)
