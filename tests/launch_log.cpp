@@ -4,6 +4,7 @@
 //   tensor <name> <rows> <columns or 0>                                                                   of the model above
 //   load <batch> <max_gamma> <flags> <caller's stream: 0 / 1> <workspace: 0 = all, 1 = the least that loads>
 //   prefill <row> <tokens> | step <gamma> <temperature> | plain <temperature> | measure | time <which> <rows> | filter
+//   sample <rows> <gamma> <vocab> <beta: 0 / 1>                                        (needs no pair)
 // Lines: "launch <stream> <kernel> <grid x> <y> <z> [notes]", "copy <stream>", "begin" .. "end" (a graph's launches), "graph <stream>",
 // "sync <stream>", "record <stream>", "call <line> -> <status>".  Streams: 0 the caller's, 1, 2, .. as they were created.
 // Kernels do not run: device memory is never touched, and sd_step finds its states unchanged (SD_EHIP behind its launches).
@@ -141,6 +142,12 @@ int main() {
     } else if (what == "filter") {
       sd_sampling opt = {1.0f, 50, 0.9f};
       status = sd_set_sampling(c, &opt);
+    } else if (what == "sample") {
+      int vocab = 0, beta = 0;
+      in >> a >> b >> vocab >> beta;
+      static float f;                                  // (addresses only)
+      static int32_t n;
+      status = sd_spec_sample_ex(&f, &f, &n, &f, &f, a, b, vocab, 1.0f, nullptr, &n, &n, beta ? &f : nullptr, &f, streams);
     }
     printf("call %s -> %d\n", line.c_str(), status);
     if (status != 0 && what != "step" && what != "plain") { fprintf(stderr, "%s: %s\n", line.c_str(), sd_last_error(c)); return 1; }

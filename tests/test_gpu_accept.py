@@ -396,6 +396,13 @@ def test_beta_in_the_launch_and_apart(rows, gamma, vocab):
 @pytest.mark.parametrize("rows", [85, 86])
 def test_a_cu_of_its_own_and_two_on_each(rows):
     """Three workgroups a sequence: 255 of them, and 258, which share the CUs two by two."""
+    check_without_beta(*synth.sampler_case(rows, 3, 9000, 1.0, rows), 1.0)
+
+
+@pytest.mark.parametrize("rows", [51, 52])
+def test_a_cu_of_its_own_and_two_on_each_beside_beta(rows):
+    """Beta's three and two for the draw: 255 workgroups; beta's three and, where a round has room for one more only, the draw's
+    three after all: 312."""
     check(*synth.sampler_case(rows, 3, 9000, 1.0, rows), 1.0)
 
 
@@ -433,11 +440,11 @@ def test_nucleus_alone(vocab, kind, temperature):
         zp[:, :, 1::2], zq[:, :, 1::2] = -np.inf, np.finfo(np.float32).min
     top_p = float(np.float32(0.9))
     for z in [*zp.reshape(-1, vocab), *zq.reshape(-1, vocab)]:
-        for _ in range(50):
+        for k in range(50):                          # (whole steps of the temperature keep a grid one, and move the sums by far more than the margin)
             if sampling.nucleus_margin(z, temperature, 0, top_p) >= 2e-6:          # (see test_filter_paths)
                 break
-            z[0] += np.float32(0.01 * max(1.0, temperature))
+            z[2 * k % vocab] += np.float32(max(1.0, temperature))
         else:
-            pytest.skip("no row of these values is clear of its threshold")
+            raise AssertionError("no row of these values is clear of its threshold")
     x = np.argmax(zq, -1).astype(np.int32)
     check(zp, zq, x, r, s, temperature, 0, top_p)

@@ -118,3 +118,13 @@ def test_weights_pass_the_l2s_only_where_they_would_not_stay(run):
             for lines in run(large, small, *calls)[-2:]]
     assert past[0] == [False] * 5                              # QKV, O, FFN-in, FFN-out, LM head
     assert past[1] == [True, False, True, True]                # (64 rows: O by two row tiles; FFN-out is gemm_split_kernel's)
+
+
+# (rows, gamma, vocabulary, beta): three workgroups a sequence; beta's three and two for the draw; beta's three and, where a round has
+# room for one more only, the draw's three after all
+@pytest.mark.parametrize("case,workgroups", [((85, 3, 9000, 0), 255), ((86, 3, 9000, 0), 258), ((51, 3, 9000, 1), 255), ((52, 3, 9000, 1), 312)])
+def test_a_cu_of_its_own_where_the_workgroups_are_no_more_than_the_cus(run, case, workgroups):
+    """Which of its two builds an accept call takes (on 256 CUs)."""
+    (lines,) = run(*pair(T.GPT), "sample " + " ".join(map(str, case)))
+    (_, kernel, grid, _), = [l for l in launches(lines) if "accept_kernel" in l[1]]
+    assert grid[0] * grid[1] == workgroups and ("accept_kernelILi0ELb1E" in kernel) == (workgroups <= 256)
