@@ -551,9 +551,17 @@ static __global__ __launch_bounds__(64 * NWV, 2) void gemm_rows_kernel(const Row
 // KB for NT * MT MFMAs.
 // D: kpw is a multiple of it, or the k-steps past a slice's end are multiplied with zeros.
 // dynamic LDS: S * NT * MT KB + MT * 64 bytes.
-// (the smaller shapes: 128 registers, two workgroups of eight wavefronts a CU)
+// The smaller shapes get 128 registers, two workgroups of eight wavefronts a CU, but for three that need 130 and 132 and would keep
+// one or two in scratch (us a draft step of 32 rows, 128 / what they need: four layers of 512, LM head of 4096 85.6 / 85.1; of 1024
+// 102.3 / 101.9; of 768, 8192 139.0 / 138.5; two layers of 1024, QKV of 2048 over 64 rows 66.8 / 66.0).
+template <int EPI, int NT, int MT, int D>
+constexpr bool slices_fit_128() {
+  if (NT == 1 && MT == 2 && D == 4) return EPI != EPI_QKV && EPI != EPI_LOGITS;
+  if (NT + MT == 4 && D == 3) return EPI != EPI_LOGITS;
+  return NT + MT <= 3;
+}
 template <int EPI, int NT, int MT, int D, bool ONCE>
-static __global__ __launch_bounds__(512, (NT + MT <= 3 || (NT + MT == 4 && D == 3)) ? 4 : 2) void gemm_slices_kernel(const RowsGemmArgs a) {
+static __global__ __launch_bounds__(512, (slices_fit_128<EPI, NT, MT, D>() ? 4 : 2)) void gemm_slices_kernel(const RowsGemmArgs a) {
   extern __shared__ float lds[];
   f32x4* part = reinterpret_cast<f32x4*>(lds);       // [S][NT][MT][64 lanes]
   constexpr int NT_OUT = (EPI == EPI_GATED) ? NT / 2 : NT;
