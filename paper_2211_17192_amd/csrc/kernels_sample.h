@@ -471,7 +471,7 @@ template <int NG, typename U>
 __device__ __forceinline__ bool nucleus_bins(const float4 (&v)[NG], int nv4, float m, float zmin, float invT, double top_p_units,
                                              SampleSmem& sm, unsigned& tau, U&& units) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  // (exp(-31) is below half a unit of 2^-44)
+  // (exp(-31) is below one unit of 2^-44, and units() truncates: what lies beyond weighs nothing)
   const float span = fmaxf(fminf(31.0f * __builtin_amdgcn_rcpf(invT), m - zmin), 1e-6f * fabsf(m) + 1e-30f);
   const float c = (float)(SAMPLE_BINS - 1) * __builtin_amdgcn_rcpf(span);
   if (!(m - m == 0.0f && span < 1e34f)) return false;                            // (uniform; 1 / span must be a number of its own)
@@ -1275,6 +1275,8 @@ static __global__ __launch_bounds__(256, 6) void row_parts_kernel(const AcceptAr
 }
 
 // Top-k / nucleus rows: the search needs the whole row, so one workgroup holds it in registers.
+// (Eight groups a thread, vocabularies beyond 16384: the row's 32 registers live through the rare paths too, and 46 registers go to
+// 188 bytes a lane of scratch; in sample_row_filter_kernel 48 to 260.  Up to four groups: none.)
 // grid = (2 gamma + 1, rows).
 template <int NG>
 static __global__ __launch_bounds__(SAMPLE_THREADS) void row_filter_kernel(const AcceptArgs a) {
@@ -1400,8 +1402,9 @@ static __global__ __launch_bounds__(256, 6) void beta_kernel(const AcceptArgs a)
 // 64 sequences, gamma 7, vocabulary 32128 (123 MB), both launches, calls back to back: 31.2 us
 // (row_parts_kernel 21 - 23: 5.4 TB/s, where a pure read reaches 7); with one 1024-thread workgroup per row and
 // then one per sequence it was 42.2.  One sequence, gamma 4: 10.9 us against 16.8.
-// OWN_NONE, not ALONE: 64 registers, two workgroups a CU.  ALONE: twice the registers, where every workgroup has a CU of its own
-// (loads that 64 hold back leave at once: one sequence, gamma 4, 32128 11.2 us -> 10.9; two, gamma 5, 128000 13.6 -> 13.3; with beta,
+// OWN_NONE, not ALONE: at most 64 registers, two workgroups a CU, two chunks of row n in flight (60 registers; 33 scalars lie in 36
+// bytes a lane of scratch).  ALONE, where every workgroup has a CU of its own: the cap lifted, four chunks in flight, no scratch (65 registers;
+// one sequence, gamma 4, 32128 11.2 us -> 10.9; two, gamma 5, 128000 13.6 -> 13.3; with beta,
 // two, gamma 6, 40397 13.5 -> 13.1; 16, gamma 5, top-k 50, 32000 15.6 -> 15.4).
 enum { OWN_NONE, OWN_SEQUENCE, OWN_ROWS };           // whose the statistics are: row_parts_kernel's; this kernel's, a workgroup per sequence / per logits row
 template <int OWN, bool ALONE = OWN != OWN_NONE>

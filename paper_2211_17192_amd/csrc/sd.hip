@@ -1136,7 +1136,7 @@ DrawNext draw_next(sd_ctx* c, int step, int gamma) {
 // each, nothing stands that another launch can do: the first embedding fetches the step's parameters from pinned memory, a draw
 // embeds what Mq's next step starts from, the last kernel writes the host's copy of the states.  (Two copies and gamma - 1
 // launches less, us a call, before -> after: tiny fp32 pair, gamma 4 214 -> 205; 97M pair, gamma 7 711 -> 691; T5-XXL-shaped, gamma 5
-// 3376 -> 3348; plain steps of small models 103 - 215, 3 us less.  A draw that embeds takes 1 us longer, the launch it saves took 2 to
+// 1 %, by which two runs differ too; plain steps of small models 103 - 215, 3 us less.  A draw that embeds takes 1 us longer, the launch it saves took 2 to
 // 4; parameters out of pinned memory lengthen the first embedding by 2 to 3 us, the copy took 4.)
 void enqueue_step(sd_ctx* c, int gamma, bool argmax, bool profile) {
   hipStream_t s = c->stream;
