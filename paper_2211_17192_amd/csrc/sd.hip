@@ -922,8 +922,9 @@ bool launch_gemm_slices_t(hipStream_t s, RowsGemmArgs a, int most) {
     if (a.kpw % 4 != 0 && a.kpw % 3 == 0) hipLaunchKernelGGL((gemm_slices_kernel<EPI, NT, MT, 3, ONCE>), dim3(grid), dim3(64 * a.nchunk), lds, s, a);
     else hipLaunchKernelGGL((gemm_slices_kernel<EPI, NT, MT, 4, ONCE>), dim3(grid), dim3(64 * a.nchunk), lds, s, a);
   };
-  if (weights_past_l2<EPI>(a)) launch(std::true_type());
-  else launch(std::false_type());
+  if constexpr (MT > 1)                              // (more than 16 rows: never one tile of one slab)
+    if (weights_past_l2<EPI>(a)) { launch(std::true_type()); return true; }
+  launch(std::false_type());
   return true;
 }
 // Which shape: measured on 256 CUs, us (rows x N x K).
